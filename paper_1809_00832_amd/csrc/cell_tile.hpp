@@ -217,6 +217,7 @@ __device__ inline void tile_epilogue(const TileSmem &sm, const Fwd &f, const Gem
             st_f<COH>(f.c + o, cc);
             st_f<COH>(f.h + o, hh);
             if (f.hb) st_h<COH>(f.hb + (size_t)node * f.hs + hu, bf16_bits(hh));
+            if (f.hx) split_store_one(f, node, hu, hh);
         } else if (EPI == EPI_LSTM_INNER) {
             const float cl = ld_f<COH>(f.c + (size_t)sm.src0[row] * H + hu);
             const float cr = ld_f<COH>(f.c + (size_t)sm.src1[row] * H + hu);

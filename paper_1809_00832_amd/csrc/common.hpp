@@ -104,6 +104,15 @@ struct Gemm {
     int n_chunks;       // padded K / KC
 };
 
+// The same weights for the cell that splits fp32 operands into two fp16 terms (cell_split.hpp).
+struct SplitGemm {
+    const void *wp;         // packed terms, see pack.hpp
+    const float *scale;     // [n_cg][NG][HU]: what a sum of scaled products is multiplied by
+    const float *w;         // the matrix as given (used where `special` says so)
+    const int *special;     // [n_cg][NG]: not 0 where a column holds an infinity and has no split
+};
+constexpr float SPLIT_H_SCALE = 16384.f;    // power of two by which h (|h| <= 1) is scaled before it is split
+
 // Everything a forward kernel needs, passed by value.
 struct Fwd {
     int n_trees, n_nodes, n_leaf, n_int;
@@ -119,6 +128,9 @@ struct Fwd {
     const unsigned short *embb; // bf16 copy, rows of es elements (zero padded), for the bf16 weight-stationary leaf kernel
     int es;
     Gemm leaf, inner;
+    SplitGemm xi;               // inner weights for the split cell
+    unsigned *hx;               // split copy of h that the split cell gathers from (cell_split.hpp), hx_steps lines of 128 bytes a row; else null
+    int hx_steps;
     // workspace
     int32_t *parent, *pending, *leaf_list, *root_ws;
     int32_t *height, *arrive, *level_cnt, *level_off, *level_fill, *level_nodes;
@@ -230,6 +242,34 @@ template <bool COH> __device__ inline void buf_st_f(__amdgpu_buffer_rsrc_t r, un
 template <bool COH> __device__ inline void buf_st_h(__amdgpu_buffer_rsrc_t r, unsigned off, unsigned short v)
 {
     __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, COH ? 16 : 0);
+}
+
+// ---- two fp16 terms of a value, and the split copy of h (cell_split.hpp) ------------------
+// hi | lo << 16 of a value that has been scaled already
+__device__ inline unsigned split_bits(float x)
+{
+    const _Float16 hi = (_Float16)x;
+    const _Float16 lo = (_Float16)(x - (float)hi);
+    return (unsigned)__builtin_bit_cast(unsigned short, hi) | (unsigned)__builtin_bit_cast(unsigned short, lo) << 16;
+}
+// Byte offset of the word that lane hu stores for the pair of units (hu & ~1, hu | 1): the even lane the two hi halves, the odd
+// lane the two lo halves.
+__device__ inline unsigned split_word_off(int hu) { return (unsigned)((hu >> 5) * 128 + (hu & 1) * 64 + ((hu & 31) >> 1) * 4); }
+// ... and that word, from this lane's value and its neighbour's (lanes 2i and 2i + 1 hold neighbouring units of one row)
+__device__ inline unsigned split_word(float scaled, int hu)
+{
+    const unsigned own = split_bits(scaled);
+    const unsigned other = (unsigned)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2]
+    return (hu & 1) ? (other >> 16 | (own & 0xFFFF0000u)) : ((own & 0xFFFFu) | other << 16);
+}
+// One unit by itself, for writers that do not hold neighbouring units in neighbouring lanes.  (A pad unit beside the last one
+// keeps its zero.)
+__device__ inline void split_store_one(const Fwd &f, int node, int hu, float h)
+{
+    const unsigned b = split_bits(h * SPLIT_H_SCALE);
+    unsigned short *row = reinterpret_cast<unsigned short *>(f.hx) + (size_t)node * f.hx_steps * 64 + (hu >> 5) * 64 + (hu & 31);
+    row[0] = (unsigned short)b;
+    row[32] = (unsigned short)(b >> 16);
 }
 
 __device__ inline unsigned long long pack2(unsigned lo32, unsigned hi32) { return (unsigned long long)hi32 << 32 | lo32; }

@@ -5,6 +5,7 @@
 
 #include "structure.hpp"
 #include "cell_ws.hpp"
+#include "cell_split.hpp"
 #include "cell_rntn.hpp"
 
 namespace tl {
@@ -529,12 +530,21 @@ __device__ inline void flow_append(int4 *list, int capacity, int *len, unsigned 
     }
 }
 
-template <int EPI, bool VEC4, int SPW, bool BF16 = false>
-__global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fwd f)
+// MODE: which cell evaluates the nodes.  FLOW_F32: fp32 matrix instructions (TreeRNN: its leaves are embedding rows of any
+// magnitude, which the split cell's fixed scale does not take); FLOW_BF16: bf16 operands; FLOW_SPLIT: fp32 operands as two
+// fp16 terms (TreeLSTM; SPW counts k-steps of 32 there, as with bf16).
+enum FlowMode { FLOW_F32 = 0, FLOW_BF16 = 1, FLOW_SPLIT = 2 };
+template <int NG, int SPW, int MODE>
+using FlowWeights = std::conditional_t<MODE == FLOW_SPLIT, SplitWeights<NG, SPW>, PersistentWeights<NG, SPW, MODE == FLOW_BF16>>;
+template <int SPW, int MODE>
+using FlowSmem = std::conditional_t<MODE == FLOW_SPLIT, SplitSmem, PersistentSmem<SPW, MODE == FLOW_BF16>>;
+
+template <int EPI, bool VEC4, int SPW, int MODE = FLOW_F32>
+__global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_persistent(Fwd f)
 {
     static_assert(SPW > 0, "the data-flow scheduler uses the weight-stationary cell");
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    using Smem = PersistentSmem<SPW, BF16>;
+    using Smem = FlowSmem<SPW, MODE>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     Ctl *ctl = f.ctl;
     if (batch_rejected(f) || internal_kernel_skipped(f)) return;
@@ -542,7 +552,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     const int n_slots = gridDim.x / f.n_cg;
     const int member = blockIdx.x % f.n_cg, slot = blockIdx.x / f.n_cg;
     const int my_cg = member;
-    PersistentWeights<EpiTraits<EPI>::NG, SPW, BF16> w;        // (loaded below, behind the first requests of the scan)
+    FlowWeights<EpiTraits<EPI>::NG, SPW, MODE> w;              // (loaded below, behind the first requests of the scan)
 
     // the slot's trees: [t_lo, t_hi), cut where the node count passes slot / n_slots of the batch.  Both cuts are
     // looked for at once, lanes 0-31 of every wave for this slot's and lanes 32-63 for the next one's, 32 candidates per
@@ -598,7 +608,8 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     // of up to 1 024 nodes then runs while the weights arrive, instead of behind them.
     scan_requests(nb);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (BF16) ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
+    if constexpr (MODE == FLOW_SPLIT) split_load(w, f.xi, f.inner, my_cg, tid >> 6, tid & 63);
+    else if constexpr (MODE == FLOW_BF16) ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
     else ws_load(w, f.inner, my_cg, tid >> 6, tid & 63);
     __builtin_amdgcn_sched_barrier(0);
     for (int n = nb + tid; n < ne; n += WG_THREADS) seen[n] = 0u;
@@ -701,7 +712,8 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
                 ticket.p = -1;
             }
         };
-        if constexpr (BF16) ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
+        if constexpr (MODE == FLOW_SPLIT) split_tile<SPW>(sm, f, count, my_cg, w, hook);
+        else if constexpr (MODE == FLOW_BF16) ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
         else ws_tile<EPI, true, SPW, !VEC4, true>(sm, f, f.inner, f.h, f.n_nodes, count, my_cg, w, hook);
         if (sm.cmd[7] != 0) return;                   // a wait was abandoned: everybody leaves
         pieces += 1;

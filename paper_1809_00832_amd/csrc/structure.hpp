@@ -52,7 +52,7 @@ template <typename T> __device__ inline int block_append(T *counter, bool pred, 
 constexpr int NODE_BLOCK = 1024;
 
 // Data-flow scheduler: the rows that internal nodes will produce - c, and the h row their parents gather (the bf16
-// copy when there is one) - show "not written" (all ones) in every element until they are.  One wave per row; called
+// or the split copy when there is one) - show "not written" (all ones) in every element until they are.  One wave per row; called
 // by all lanes of wave number `wave` of `n_waves`.
 __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
 {
@@ -62,7 +62,7 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
     const floatx4 ones4 = floatx4{ones, ones, ones, ones};
     for (size_t n = wave; n < (size_t)f.n_nodes; n += n_waves) {
         if (f.left[n] < 0) continue;
-        float *c = f.c ? f.c + n * H : nullptr, *h = f.hb ? nullptr : f.h + n * H;
+        float *c = f.c ? f.c + n * H : nullptr, *h = f.hb || f.hx ? nullptr : f.h + n * H;
         if (quad) {
             for (int e = lane * 4; e < H; e += 256) {
                 if (c) *reinterpret_cast<floatx4 *>(c + e) = ones4;
@@ -79,6 +79,14 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
             for (int e = lane * 8; e < H; e += 512) {
                 if (e + 8 <= H) *reinterpret_cast<floatx4 *>(hb + e) = ones4;
                 else for (int k = e; k < H; ++k) hb[k] = (unsigned short)0xFFFFu;
+            }
+        }
+        if (f.hx) {
+            unsigned *hx = f.hx + n * (size_t)(f.hx_steps * 32);        // rows of whole 128-byte lines; words of pad units stay zero
+            for (int q = lane; q < f.hx_steps * 8; q += 64) {
+                const int unit = (q >> 3) * 32 + (q & 3) * 8;           // first of the 8 units of these 16 bytes
+                if (unit + 8 <= H) *reinterpret_cast<floatx4 *>(hx + 4 * q) = ones4;
+                else for (int k = 0; k < 4; ++k) if (unit + 2 * k < H) hx[4 * q + k] = 0xFFFFFFFFu;
             }
         }
     }

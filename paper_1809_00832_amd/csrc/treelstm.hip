@@ -67,6 +67,13 @@ struct tl_ctx {
     unsigned short *embb = nullptr;
     int hs = 0;                       // row stride of the bf16 copy of h
     unsigned short *hb = nullptr;     // bf16 copy of h, cap_nodes rows (bf16 weight-stationary cell only)
+    int split = 0;                    // k-steps per wave of the split cell (data-flow scheduler, fp32 TreeLSTM), 0 = not used
+    int hx_steps = 0;                 // 128-byte lines per row of the split copy of h
+    int flow_grid = 0;                // workgroups of the data-flow kernel
+    unsigned *hx = nullptr;           // split copy of h, cap_nodes rows
+    _Float16 *xp_inner = nullptr;     // its packed weights, their scales and flags
+    float *xs_inner = nullptr;
+    int *xf_inner = nullptr;
     // backward pass (TreeLSTM, fp32): transposed weights packed like the forward ones, workspace
     void *wp_bwd_inner = nullptr, *wp_bwd_leaf = nullptr, *wp_bwd_inner1 = nullptr;
     float *bp_bwd_inner = nullptr, *bp_bwd_leaf = nullptr, *bp_bwd_inner1 = nullptr;
@@ -188,31 +195,49 @@ template <int EPI> fwd_kernel levels_kernel_epi(bool vec4, int spw, bool bf16)
     default: return vec4 ? k_levels_persistent<EPI, true, 0> : k_levels_persistent<EPI, false, 0>;
     }
 }
-template <int EPI> fwd_kernel flow_kernel_epi(bool vec4, int spw, bool bf16)
+fwd_kernel flow_kernel_bf16(int cell, int s)
 {
-    if (bf16) {
-        switch (spw) {
-        case 1: return k_flow_persistent<EPI, true, 1, true>;
-        case 2: return k_flow_persistent<EPI, true, 2, true>;
-        case 3: return k_flow_persistent<EPI, true, 3, true>;
-        case 4: return k_flow_persistent<EPI, true, 4, true>;
-        case 6: return k_flow_persistent<EPI, true, 6, true>;
-        default: return k_flow_persistent<EPI, true, 8, true>;
-        }
-    }
-    switch (spw) {
-    case 1: return vec4 ? k_flow_persistent<EPI, true, 1> : k_flow_persistent<EPI, false, 1>;
-    case 2: return vec4 ? k_flow_persistent<EPI, true, 2> : k_flow_persistent<EPI, false, 2>;
-    case 4: return vec4 ? k_flow_persistent<EPI, true, 4> : k_flow_persistent<EPI, false, 4>;
-    case 5: return vec4 ? k_flow_persistent<EPI, true, 5> : k_flow_persistent<EPI, false, 5>;
-    case 8: return vec4 ? k_flow_persistent<EPI, true, 8> : k_flow_persistent<EPI, false, 8>;
-    default: return vec4 ? k_flow_persistent<EPI, true, 16> : k_flow_persistent<EPI, false, 16>;
+    const bool lstm = cell == TL_TREELSTM;
+    switch (s) {
+    case 1: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 1, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 1, FLOW_BF16>;
+    case 2: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 2, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 2, FLOW_BF16>;
+    case 3: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 3, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 3, FLOW_BF16>;
+    case 4: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 4, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 4, FLOW_BF16>;
+    case 6: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 6, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 6, FLOW_BF16>;
+    default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 8, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 8, FLOW_BF16>;
     }
 }
-// spw > 0 and not the RNTN cell
-fwd_kernel flow_kernel(int cell, bool vec4, int spw, bool bf16)
+// fp32 TreeRNN
+fwd_kernel flow_kernel_rnn(bool vec4, int spw)
 {
-    return cell == TL_TREELSTM ? flow_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16) : flow_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
+    switch (spw) {
+    case 1: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 1> : k_flow_persistent<EPI_RNN_INNER, false, 1>;
+    case 2: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 2> : k_flow_persistent<EPI_RNN_INNER, false, 2>;
+    case 4: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 4> : k_flow_persistent<EPI_RNN_INNER, false, 4>;
+    case 5: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 5> : k_flow_persistent<EPI_RNN_INNER, false, 5>;
+    case 8: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 8> : k_flow_persistent<EPI_RNN_INNER, false, 8>;
+    default: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 16> : k_flow_persistent<EPI_RNN_INNER, false, 16>;
+    }
+}
+// fp32 TreeLSTM, s k-steps of 32 per wave (1 ... SPLIT_MAX_S)
+fwd_kernel flow_kernel_split(int s)
+{
+    switch (s) {
+    case 1: return k_flow_persistent<EPI_LSTM_INNER, true, 1, FLOW_SPLIT>;
+    case 2: return k_flow_persistent<EPI_LSTM_INNER, true, 2, FLOW_SPLIT>;
+    case 3: return k_flow_persistent<EPI_LSTM_INNER, true, 3, FLOW_SPLIT>;
+    case 4: return k_flow_persistent<EPI_LSTM_INNER, true, 4, FLOW_SPLIT>;
+    case 5: return k_flow_persistent<EPI_LSTM_INNER, true, 5, FLOW_SPLIT>;
+    case 6: return k_flow_persistent<EPI_LSTM_INNER, true, 6, FLOW_SPLIT>;
+    case 7: return k_flow_persistent<EPI_LSTM_INNER, true, 7, FLOW_SPLIT>;
+    default: return k_flow_persistent<EPI_LSTM_INNER, true, 8, FLOW_SPLIT>;
+    }
+}
+// The data-flow kernel: split > 0 the split cell with that many k-steps per wave, else spw > 0 and not the RNTN cell
+fwd_kernel flow_kernel(int cell, bool vec4, int spw, int split, bool bf16)
+{
+    if (split > 0) return flow_kernel_split(split);
+    return bf16 ? flow_kernel_bf16(cell, spw) : flow_kernel_rnn(vec4, spw);
 }
 fwd_kernel ready_kernel(int cell, bool vec4, int spw, bool bf16)
 {
@@ -376,6 +401,25 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
     return TL_OK;
 }
 
+// The split cell's weights (fp32 TreeLSTM contexts of the data-flow scheduler), from the parameters kept in the context.
+int pack_split(tl_ctx *ctx, hipStream_t st)
+{
+    if (ctx->split == 0) return TL_OK;
+    const int H = ctx->cfg.hidden, n_cg = ctx->n_cg, n_steps = 4 * ctx->split;
+    if (!ctx->xp_inner) TL_HIP(hipMalloc(&ctx->xp_inner, (size_t)n_cg * n_steps * 5 * 2 * 64 * 8 * sizeof(_Float16)));
+    if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)n_cg * 5 * HU * sizeof(float)));
+    if (!ctx->xf_inner) TL_HIP(hipMalloc(&ctx->xf_inner, (size_t)n_cg * 5 * sizeof(int)));
+    SplitPackList pl{};
+    SplitPackJob &j = pl.job[0];
+    j.w = ctx->m_u; j.wp = ctx->xp_inner; j.scale = ctx->xs_inner; j.special = ctx->xf_inner;
+    j.NG = 5; j.H = H; j.SEG = 2; j.L = H; j.steps = ctx->hx_steps; j.n_steps = n_steps; j.n_cg = n_cg;
+    j.operand_scale = SPLIT_H_SCALE;
+    pl.n = 1;
+    hipLaunchKernelGGL(k_pack_split, dim3(n_cg * 5), dim3(256), 0, st, pl);
+    TL_HIP(hipGetLastError());
+    return TL_OK;
+}
+
 // One job of k_pack_many for a matrix that pack_gemm has packed before (g says how): [SEG * L x NG * H], from w as it is
 // stored (row-major) or, transposed = true, from the stored [NG * H x SEG * L] matrix whose transpose it is.
 PackJob repack_job(const Gemm &g, const float *w, const float *b, float *bp, int NG, int H, int SEG, int n_cg, bool transposed)
@@ -411,7 +455,7 @@ int repack_f32(tl_ctx *ctx, hipStream_t st)
     pl.n = n;
     hipLaunchKernelGGL(k_pack_many, dim3(2048), dim3(256), 0, st, pl);
     TL_HIP(hipGetLastError());
-    return TL_OK;
+    return lstm ? pack_split(ctx, st) : TL_OK;
 }
 
 // The same for an fp32 TreeRNN context: forward weights and W^T of the backward pass.
@@ -528,6 +572,7 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     const int B = n_trees > ctx->cap_trees ? n_trees : ctx->cap_trees;
     if (ctx->ws) { TL_HIP(hipFree(ctx->ws)); ctx->ws = nullptr; }
     if (ctx->hb) { TL_HIP(hipFree(ctx->hb)); ctx->hb = nullptr; }
+    if (ctx->hx) { TL_HIP(hipFree(ctx->hx)); ctx->hx = nullptr; }
     if (ctx->flow_ws) { TL_HIP(hipFree(ctx->flow_ws)); ctx->flow_ws = nullptr; }
     if (ctx->host_levels) { TL_HIP(hipHostFree(ctx->host_levels)); ctx->host_levels = nullptr; }
     ctx->cap_nodes = ctx->cap_trees = 0;
@@ -539,7 +584,12 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
         TL_HIP(hipMalloc(&ctx->hb, hb_bytes));
         TL_HIP(hipMemset(ctx->hb, 0, hb_bytes));   // the padding at the end of each row stays zero for good
     }
-    if (ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
+    if (ctx->split > 0) {
+        const size_t hx_bytes = (size_t)N * ctx->hx_steps * 128;
+        TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
+        TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));   // the padding stays zero for good
+    }
+    if ((ctx->spw > 0 || ctx->split > 0) && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
         TL_HIP(hipMalloc(&ctx->flow_ws, flow_bytes(ctx->n_cg, (size_t)N)));
     TL_HIP(hipHostMalloc(&ctx->host_levels, (size_t)(N + 2) * 4, hipHostMallocDefault));
     ctx->ws_bytes = bytes;
@@ -581,6 +631,10 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->ws);
     (void)hipFree(ctx->hb);
     (void)hipFree(ctx->flow_ws);
+    (void)hipFree(ctx->hx);
+    (void)hipFree(ctx->xp_inner);
+    (void)hipFree(ctx->xs_inner);
+    (void)hipFree(ctx->xf_inner);
     (void)hipFree(ctx->embb);
     (void)hipFree(ctx->wp_bwd_inner);
     (void)hipFree(ctx->wp_bwd_inner1);
@@ -665,6 +719,10 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
                 if (sz >= needed) { ctx->spw = sz; break; }
         }
     }
+    // Split cell: any hidden size up to 512 (its rows come from a padded copy of h)
+    ctx->hx_steps = (H + 31) / 32;
+    if (cfg->cell == TL_TREELSTM && !bf16 && cfg->scheduler == TL_SCHED_DATAFLOW && (2 * ctx->hx_steps + 3) / 4 <= SPLIT_MAX_S)
+        ctx->split = (2 * ctx->hx_steps + 3) / 4;
     const int ws_steps16 = bf16 ? 8 * ctx->spw : 4 * ctx->spw;   // K axis of the weight-stationary cell in k-steps of 16
     ctx->spw_leaf = 0;
     ctx->es = round_up(E, 8);
@@ -708,6 +766,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             ctx->ng_bwd_leaf = E % 4 == 0 ? 4 : 1;
             ctx->ws_steps16 = ws_steps16;
             rc = pack_treelstm_f32(ctx, nullptr);
+            if (rc == TL_OK) rc = pack_split(ctx, nullptr);
             TL_HIP(hipDeviceSynchronize());
             if (rc != TL_OK) return rc;
         } else {
@@ -811,18 +870,24 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o2, reinterpret_cast<const void *>(levels_kernel(cfg->cell, true, ctx->spw, bf16)),
                                                             WG_THREADS, ctx->ws_lds));
         if (o2 < o1) o1 = o2;
-        for (int v = 0; v < 2; ++v) {
-            const fwd_kernel fk = flow_kernel(cfg->cell, v != 0, ctx->spw, bf16);
-            if ((rc = allow_lds(fk, ctx->ws_lds)) != TL_OK) return rc;
-            TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o2, reinterpret_cast<const void *>(fk), WG_THREADS, ctx->ws_lds));
-            if (o2 < o1) o1 = o2;
-        }
         const int want = bf16 ? 2 : 1;   // fp32: the register file of a CU holds one workgroup's weights; bf16: two
         if (o1 > want) o1 = want;
         ctx->ws_grid = o1 * ctx->n_cu;
         if (o1 < 1 || ctx->ws_grid < ctx->n_cg + 1) ctx->spw = 0;
     }
 
+    if (cfg->scheduler == TL_SCHED_DATAFLOW && (ctx->spw > 0 || ctx->split > 0)) {
+        const size_t lds = ctx->split > 0 ? sizeof(SplitSmem) : ctx->ws_lds;
+        int o = 0, o_min = bf16 ? 2 : 1;
+        for (int v = 0; v < 2; ++v) {
+            const fwd_kernel fk = flow_kernel(cfg->cell, v != 0, ctx->spw, ctx->split, bf16);
+            if ((rc = allow_lds(fk, lds)) != TL_OK) return rc;
+            TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(fk), WG_THREADS, lds));
+            if (o < o_min) o_min = o;
+        }
+        ctx->flow_grid = o_min * ctx->n_cu;
+        if (ctx->flow_grid < ctx->n_cg) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
+    }
     if (ctx->spw_leaf > 0) {
         const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16);
         const fwd_kernel lk = bf16 ? leaf_ws_bf_kernel(ctx->spw_leaf) : leaf_ws_kernel(ctx->spw_leaf);
@@ -976,18 +1041,26 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool persistent = cfg.scheduler != TL_SCHED_LEVEL_HOST;
     // the data-flow scheduler needs the weight-stationary cell and its private lists; without them (RNTN, sizes the
     // cell does not take, the fixed workspace) the level scheduler on the device stands in.
-    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && spw > 0 && !static_ws && ctx->flow_ws != nullptr;
+    const bool split_range = n_nodes < (1 << 24) && (unsigned long long)n_nodes * ctx->hx_steps * 128ull < (1ull << 32);
+    const int split = split_range ? ctx->split : 0;
+    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_ws != nullptr && ctx->flow_grid > 0 &&
+                      (cfg.cell == TL_TREELSTM && !bf16 ? split > 0 : spw > 0);
     // A batch of few large trees: the data-flow scheduler deals whole trees to its sets of workgroups, so with fewer
     // trees than sets the others stay idle: one bushy tree of 16 384 leaves takes 3.5 ms on one set against 0.34 ms
     // level by level on all of them, while a deep chain of 2 048 leaves takes 6.4 ms data-flow and 11.8 ms level by
     // level.  The host does not know the shapes, so both kernels are launched and the device picks
     // (internal_kernel_skipped: by the width of the first frontier).  Small trees - a sentence, say - are left with
     // the data-flow kernel alone: one set holds all that is ready of such a tree.
-    const int flow_sets = ctx->n_cg > 0 ? ctx->ws_grid / ctx->n_cg : 0;
+    const int flow_sets = ctx->n_cg > 0 ? ctx->flow_grid / ctx->n_cg : 0;
     const bool flow_or_levels = flow && n_trees < flow_sets && n_nodes / (n_trees > 0 ? n_trees : 1) >= FLOW_LARGE_TREE_NODES;
     if (persistent && spw > 0 && bf16) {
         f.hb = static_ws ? reinterpret_cast<unsigned short *>(ctx->scratch + NOALLOC_WS_BYTES) : ctx->hb;
         f.hs = ctx->hs;
+    }
+    if (flow && split > 0) {
+        f.hx = ctx->hx;
+        f.hx_steps = ctx->hx_steps;
+        f.xi.wp = ctx->xp_inner; f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u; f.xi.special = ctx->xf_inner;
     }
     // The persistent kernels' workgroups wait for each other, so all of them must be resident at once: the grid is
     // cut to what the device holds of the very kernel that is launched (the figure taken at tl_create is that of one
@@ -995,23 +1068,25 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool ready_sched = cfg.scheduler == TL_SCHED_READY || cfg.scheduler == TL_SCHED_READY_PRIORITY;
     const fwd_kernel kern = !persistent ? nullptr
                             : ready_sched ? ready_kernel(cfg.cell, vec4_inner, spw, bf16)
-                            : flow ? flow_kernel(cfg.cell, vec4_inner, spw, bf16) : levels_kernel(cfg.cell, vec4_inner, spw, bf16);
-    const size_t kern_lds = spw > 0 ? ctx->ws_lds : TILE_SMEM_BYTES;
-    int grid_p = (persistent && spw > 0) ? ctx->ws_grid : ctx->persistent_grid;
+                            : flow ? flow_kernel(cfg.cell, vec4_inner, spw, split, bf16) : levels_kernel(cfg.cell, vec4_inner, spw, bf16);
+    const size_t level_lds = spw > 0 ? ctx->ws_lds : TILE_SMEM_BYTES;
+    const size_t kern_lds = flow && split > 0 ? sizeof(SplitSmem) : level_lds;
+    const bool whole_sets = spw > 0 || flow;          // every workgroup of the kernel is tied to one column group
+    int grid_p = flow ? ctx->flow_grid : (persistent && spw > 0) ? ctx->ws_grid : ctx->persistent_grid;
     if (kern) {
         int per_cu = 0;
         if ((rc = resident_per_cu(ctx, kern, kern_lds, &per_cu)) != TL_OK) return rc;
         if (per_cu * ctx->n_cu < grid_p) grid_p = per_cu * ctx->n_cu;
-        if (grid_p < (spw > 0 ? ctx->n_cg : 1) + (ready_sched ? 1 : 0)) return TL_EHIP;
+        if (grid_p < (whole_sets ? ctx->n_cg : 1) + (ready_sched ? 1 : 0)) return TL_EHIP;
     }
     int grid_l2 = 0;                                  // grid of the level kernel where it is launched beside the data-flow kernel
     if (flow_or_levels) {
         int per_cu = 0;
-        if ((rc = resident_per_cu(ctx, levels_kernel(cfg.cell, vec4_inner, spw, bf16), kern_lds, &per_cu)) != TL_OK) return rc;
-        grid_l2 = ctx->ws_grid;
+        if ((rc = resident_per_cu(ctx, levels_kernel(cfg.cell, vec4_inner, spw, bf16), level_lds, &per_cu)) != TL_OK) return rc;
+        grid_l2 = spw > 0 ? ctx->ws_grid : ctx->persistent_grid;
         if (per_cu * ctx->n_cu < grid_l2) grid_l2 = per_cu * ctx->n_cu;
-        grid_l2 = grid_l2 / ctx->n_cg * ctx->n_cg;
-        if (grid_l2 < ctx->n_cg) return TL_EHIP;
+        if (spw > 0) grid_l2 = grid_l2 / ctx->n_cg * ctx->n_cg;
+        if (grid_l2 < (spw > 0 ? ctx->n_cg : 1)) return TL_EHIP;
     }
     f.cap_tiles = grid_p / ctx->n_cg > 0 ? grid_p / ctx->n_cg : 1;
     // RNTN: a frontier of at most rntn_units tiles is cut into RNTN_PARTS workgroups per tile and column group
@@ -1112,13 +1187,13 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
             ctx->last_grid = grid_r;
         } else if (cfg.scheduler == TL_SCHED_LEVEL_DEVICE || cfg.scheduler == TL_SCHED_DATAFLOW) {
             // weight-stationary cell: every workgroup is tied to one column group, so whole sets only
-            const int grid_l = spw > 0 ? grid_p / ctx->n_cg * ctx->n_cg : grid_p;
+            const int grid_l = whole_sets ? grid_p / ctx->n_cg * ctx->n_cg : grid_p;
             if (flow_or_levels) {                     // both kernels; every workgroup of the one that is not picked returns at once
                 Fwd g = f;
                 g.pick = 1;
                 hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, g);
                 g.pick = 2;
-                hipLaunchKernelGGL(levels_kernel(cfg.cell, vec4_inner, spw, bf16), dim3(grid_l2), dim3(WG_THREADS), kern_lds, st, g);
+                hipLaunchKernelGGL(levels_kernel(cfg.cell, vec4_inner, spw, bf16), dim3(grid_l2), dim3(WG_THREADS), level_lds, st, g);
             } else {
                 hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, f);
             }
