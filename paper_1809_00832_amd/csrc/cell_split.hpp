@@ -17,8 +17,8 @@
 // The two halves of a 32-bit word belong to two hidden units and are stored together, so a word that shows all ones has not
 // been written yet (see cell_ws.hpp, validity carried by the data).
 //
-// A column that holds an infinity has no such split; the pack kernel then raises `special`, and every gate is summed
-// in fp32 from the parameters as given (slow, and only there).
+// An infinite weight has no such split; the scale of a column that holds one is a NaN, and its sums are taken in fp32
+// from the parameters as given (slow, and only there).
 #pragma once
 
 #include "cell_ws.hpp"
@@ -32,19 +32,13 @@ constexpr int SPLIT_MAX_S = 8;
 
 struct SplitSmem {
     float red[2][4 * MAX_GATES * 64 * 4];   // K-split partial sums, alternating per block: [wave][gate][lane][v]
-    int node[WS_TABLE_ROWS];                // tables as in WsSmemT
-    int src0[WS_TABLE_ROWS];
-    int src1[WS_TABLE_ROWS];
-    int par[WS_TABLE_ROWS];
-    int nxt[4][FLOW_NXT_ROWS];
-    int roots[FLOW_ROOTS_KEPT];
-    int cmd[8];
+    int gave_up;
 };
 
 template <int NG, int S> struct SplitWeights {
     halfx8 hi[S][NG], lo[S][NG];
     float bias[NG], scale[NG];
-    int special;
+    bool plain;                                                 // some unit of the column group has a weight that is infinite
 };
 
 // k-steps [wave * S, (wave + 1) * S) of column group cg; the packed matrix has exactly 4 * S of them.
@@ -64,10 +58,10 @@ __device__ inline void split_load(SplitWeights<NG, S> &w, const SplitGemm &x, co
         w.bias[g] = gm.bp[(cg * NG + g) * HU + (lane & 15)];
         w.scale[g] = x.scale[(cg * NG + g) * HU + (lane & 15)];
     }
-    int special = 0;
+    float scales = 0.f;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) special |= x.special[cg * NG + g];
-    w.special = __builtin_amdgcn_readfirstlane(special);
+    for (int g = 0; g < NG; ++g) scales += w.scale[g];
+    w.plain = __ballot(__builtin_isnan(scales)) != 0ull;
     // With more weights than fit into the vector registers beside the rows in flight, say which of them live in the
     // accumulation registers (a matrix instruction reads either; see ws_load).
     if constexpr (S * NG * 8 > 128) {
@@ -89,8 +83,8 @@ __device__ inline void split_load(SplitWeights<NG, S> &w, const SplitGemm &x, co
     }
 }
 
-// Gates of one node and hidden unit summed in fp32 from the parameters as given (weights that hold infinities); the
-// children's h from their split copies, which all waves have seen complete.
+// Gates of one node and hidden unit summed in fp32 from the parameters as given; the children's h from their split copies,
+// which all waves have seen complete.
 template <int NG>
 __device__ inline void split_gates_plain(const Fwd &f, const SplitGemm &x, int s0, int s1, int hu, float (&gate)[NG])
 {
@@ -107,18 +101,32 @@ __device__ inline void split_gates_plain(const Fwd &f, const SplitGemm &x, int s
     }
 }
 
-// Evaluates the `count` <= WS_TABLE_ROWS internal nodes of the row tables for column group cg, 16 at a time, the rows of a
-// block requested while the block before is computed.  Called and synchronised like ws_tile (cell_ws.hpp), same hooks.
+// Slot and column group of a workgroup.  Workgroups are dealt to the L2 domains round-robin; where whole slots fit into the
+// domains, a slot is kept inside one, so that its rows cross the fabric once and its dependent rows not at all.
+__device__ inline void split_place(const Fwd &f, int *slot, int *member)
+{
+    const int i = blockIdx.x / N_XCD;
+    if (f.n_slots % N_XCD == 0) {
+        *member = i % f.n_cg;
+        *slot = (i / f.n_cg) * N_XCD + blockIdx.x % N_XCD;
+    } else {
+        *member = blockIdx.x % f.n_cg;
+        *slot = blockIdx.x / f.n_cg;
+    }
+}
+
+// Evaluates the blocks of one slot's schedule (structure.hpp, flow_schedule) for column group cg: 16 internal nodes a block,
+// every node's children in earlier blocks, the rows of a block requested while the block before is computed - or,
+// where a row of it comes out of that very block, once its results are stored.
 // K axis: hx_steps k-steps of 32 units of the left child, then as many of the right one; wave w walks quarter w of
 // 4 * S steps (those beyond the axis re-read the right child's last step against zero weights), each step's three
 // products in the order hi hi, hi lo, lo hi; the four quarter sums are added in wave order.  A node's result so depends neither
 // on its place in a block nor on the batch.
-template <int S, typename Hook>
-__device__ inline void split_tile(SplitSmem &sm, const Fwd &f, int count, int cg, const SplitWeights<5, S> &w, Hook hook)
+template <int S>
+__device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__restrict__ entries, int n_blocks, int cg, const SplitWeights<5, S> &w)
 {
     constexpr int NG = 5;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int nrb = (count + 15) >> 4;
     const int H = f.H, steps = f.hx_steps;
     const int hu = cg * HU + (lane & 15);
     const bool hu_ok = hu < H;
@@ -130,92 +138,65 @@ __device__ inline void split_tile(SplitSmem &sm, const Fwd &f, int count, int cg
     const unsigned lane_off = (unsigned)(lane >> 4) * 16u;
     unsigned base0 = 0, base1 = 0;                              // this lane's row in the left and the right child's segment
 
-    auto prepare = [&](int row0) {
-        const int row = (row0 + (lane & 15)) & (WS_TABLE_ROWS - 1);
-        base0 = __umul24((unsigned)sm.src0[row], hx_row_b) + lane_off;
-        base1 = __umul24((unsigned)sm.src1[row], hx_row_b) + lane_off;
+    auto prepare = [&](const int4 &q) {
+        base0 = __umul24((unsigned)q.y, hx_row_b) + lane_off;
+        base1 = __umul24((unsigned)q.z, hx_row_b) + lane_off;
     };
     uintx4_t rows[S][2];
-    auto request = [&](__amdgpu_buffer_rsrc_t rs, int s) {
+    // Rows are first asked for with ordinary loads: a line that this CU's or this L2's copy shows too early shows the pattern,
+    // and only the repeated requests go past the caches.
+    auto request = [&](__amdgpu_buffer_rsrc_t rs, int s, auto past_caches) {
+        constexpr int POLICY = decltype(past_caches)::value ? 16 : 0;
         const int k = wave * S + s;
         const bool right = k >= steps;
         const int kk = min(right ? k - steps : k, steps - 1);
         const unsigned b = right ? base1 : base0;
-        rows[s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)b, kk * 128, 16);
-        rows[s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)b + 64, kk * 128, 16);
+        rows[s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)b, kk * 128, POLICY);
+        rows[s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)b + 64, kk * 128, POLICY);
+    };
+    auto shows_pattern = [&]() {
+        unsigned m = 0u;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) m = max(max(m, max(rows[s][t].x, rows[s][t].y)), max(rows[s][t].z, rows[s][t].w));
+        return __ballot(m == FLOW_SENTINEL) != 0ull;
     };
     // The block's rows: requests repeated until no word shows the pattern.  Bounded by the spin budget and the abort flag.
-    auto wait_rows = [&]() {
+    auto repeat_rows = [&]() {
         int spins = 0;
         unsigned aborted = 0u;
-        for (;;) {
-            unsigned m = 0u;
-#pragma unroll
-            for (int s = 0; s < S; ++s)
-#pragma unroll
-                for (int t = 0; t < 2; ++t) m = max(max(m, max(rows[s][t].x, rows[s][t].y)), max(rows[s][t].z, rows[s][t].w));
-            if (__ballot(m == FLOW_SENTINEL) == 0ull) return;
+        do {
             if (++spins > f.spin_limit || aborted != 0u) {
                 flow_give_up(f);
-                sm.cmd[7] = 1;
+                sm.gave_up = 1;
                 return;
             }
-            backoff();
+            __builtin_amdgcn_s_sleep(1);
 #pragma unroll
-            for (int s = 0; s < S; ++s) request(rs_x, s);
+            for (int s = 0; s < S; ++s) request(rs_x, s, std::true_type{});
             aborted = ld_dev(&f.ctl->abort.v);                  // arrives with the rows
-        }
-    };
-    // Second half of a block: wave w finishes its rows 4 w .. 4 w + 3, lane l row 4 w + (l >> 4), hidden unit l & 15.
-    auto finish = [&](const float *red, int enode, float cl, float cr, int erow) {
-        float gate[NG];
-#pragma unroll
-        for (int g = 0; g < NG; ++g) {
-            float p[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) p[q] = red[((q * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
-            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], w.scale[g], w.bias[g]);
-        }
-        if (enode >= 0) {
-            const int s0 = sm.src0[erow & (WS_TABLE_ROWS - 1)], s1 = sm.src1[erow & (WS_TABLE_ROWS - 1)];
-            float cc = 0.f, hh = 0.f;
-            if (hu_ok) {
-                cl = flow_wait_c<true>(f, rs_c, (unsigned)s0 * row_b + hu_b, cl);     // a child's c element may arrive after its h row
-                cr = flow_wait_c<true>(f, rs_c, (unsigned)s1 * row_b + hu_b, cr);
-                if (w.special) {
-                    split_gates_plain<NG>(f, f.xi, s0, s1, hu, gate);
-#pragma unroll
-                    for (int g = 0; g < NG; ++g) gate[g] += w.bias[g];
-                }
-                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, enode, hu), H);
-            }
-            const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
-            const unsigned o = (unsigned)enode * row_b + hu_b;
-            if (hu_ok) {
-                buf_st_f<true>(rs_h, o, hh);
-                buf_st_f<true>(rs_c, o, cc);
-            }
-            if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)enode * hx_row_b + split_word_off(hu), __uint_as_float(word));
-        }
+        } while (shows_pattern());
     };
 
-    prepare(0);
+    const int my_row = lane & 15, fin_row = 4 * wave + (lane >> 4);
+    int4 q = entries[my_row], e = entries[fin_row];
+    int4 q_next = n_blocks > 1 ? entries[16 + my_row] : q;
+    prepare(q);
 #pragma unroll
-    for (int s = 0; s < S; ++s) request(rs_x, s);
-    hook(-1);
-    int p_enode = -1, p_erow = 0;
-    float p_cl = 0.f, p_cr = 0.f;
-    constexpr int FINISH_AFTER = S > 1 ? 1 : 0;                 // k-step after which the block before is finished
-    for (int rb = 0; rb < nrb; ++rb) {
-        wait_rows();
-        prepare((rb + 1) * 16);
-        // (behind the last block the requests go to a table of no bytes: they return at once and read nothing)
-        const __amdgpu_buffer_rsrc_t rs_next = buf_of(f.hx, rb + 1 < nrb ? hx_bytes : 0ull);
-        hook(rb);
-        const int erow = rb * 16 + 4 * wave + (lane >> 4);
-        const int enode = erow < count ? sm.node[erow] : -1;
-        const float cl = buf_ld_f<true>(rs_c, (unsigned)sm.src0[erow & (WS_TABLE_ROWS - 1)] * row_b + hu_b);
-        const float cr = buf_ld_f<true>(rs_c, (unsigned)sm.src1[erow & (WS_TABLE_ROWS - 1)] * row_b + hu_b);
+    for (int s = 0; s < S; ++s) request(rs_x, s, std::false_type{});
+    for (int b = 0; b < n_blocks; ++b) {
+        const bool last = b + 1 >= n_blocks;
+        const bool late = last || __builtin_amdgcn_readfirstlane(q_next.w) < 0;     // the next block waits for this one
+        const float cl0 = buf_ld_f<false>(rs_c, (unsigned)e.y * row_b + hu_b);
+        const float cr0 = buf_ld_f<false>(rs_c, (unsigned)e.z * row_b + hu_b);
+        const int4 *ahead = entries + (size_t)min(b + 2, n_blocks - 1) * 16;
+        const int4 q_ahead = ahead[my_row];
+        const int4 e_next = entries[(size_t)min(b + 1, n_blocks - 1) * 16 + fin_row];
+        if (shows_pattern()) repeat_rows();
+        prepare(q_next);
+        // (requests that are not to be made yet go to a table of no bytes: they return at once and read nothing)
+        const __amdgpu_buffer_rsrc_t rs_next = buf_of(f.hx, late ? 0ull : hx_bytes);
         __builtin_amdgcn_sched_barrier(0);
         floatx4 acc[NG];
 #pragma unroll
@@ -229,26 +210,56 @@ __device__ inline void split_tile(SplitSmem &sm, const Fwd &f, int count, int cg
             for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, w.lo[s][g], acc[g], 0, 0, 0);
 #pragma unroll
             for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, w.hi[s][g], acc[g], 0, 0, 0);
-            request(rs_next, s);
+            request(rs_next, s, std::false_type{});
             __builtin_amdgcn_sched_barrier(0);
-            if (s == FINISH_AFTER && rb > 0) {
-                __syncthreads();                                // every wave has written its partial sums of block rb - 1
-                finish(sm.red[(rb - 1) & 1], p_enode, p_cl, p_cr, p_erow);
-                __builtin_amdgcn_sched_barrier(0);
-            }
         }
-        float *red = sm.red[rb & 1];
+        // The four quarter sums meet in LDS; wave w finishes the block's rows 4 w .. 4 w + 3, lane l row 4 w + (l >> 4), hidden
+        // unit l & 15.  (The two buffers alternate: one is written again two blocks later, behind the next block's barrier.)
+        float *red = sm.red[b & 1];
 #pragma unroll
         for (int g = 0; g < NG; ++g) *reinterpret_cast<floatx4 *>(&red[((wave * NG + g) * 64 + lane) * 4]) = acc[g];
-        p_enode = enode;
-        p_cl = cl;
-        p_cr = cr;
-        p_erow = erow;
+        __syncthreads();
+        if (sm.gave_up != 0) return;
+        float gate[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            float p[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = red[((k * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
+            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], w.scale[g], w.bias[g]);
+        }
+        if (e.x >= 0) {
+            float cc = 0.f, hh = 0.f;
+            if (hu_ok) {
+                const float cl = flow_wait_c<true>(f, rs_c, (unsigned)e.y * row_b + hu_b, cl0);     // a child's c element may arrive after its h row
+                const float cr = flow_wait_c<true>(f, rs_c, (unsigned)e.z * row_b + hu_b, cr0);
+                if (__builtin_expect(w.plain, 0)) {
+                    split_gates_plain<NG>(f, f.xi, e.y, e.z, hu, gate);
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) gate[g] += w.bias[g];
+                }
+                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, e.x, hu), H);
+            }
+            const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
+            if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)e.x * hx_row_b + split_word_off(hu), __uint_as_float(word));
+            if (hu_ok) {
+                const unsigned o = (unsigned)e.x * row_b + hu_b;
+                buf_st_f<true>(rs_c, o, cc);
+                buf_st_f<true>(rs_h, o, hh);
+                const int t = (e.w & 0x7FFFFFFF) - 1;           // a root's tree
+                if (t >= 0) {
+                    if (f.h_root) f.h_root[(size_t)t * H + hu] = hh;
+                    if (f.c_root) f.c_root[(size_t)t * H + hu] = cc;
+                }
+            }
+        }
+        if (late && !last) {
+#pragma unroll
+            for (int s = 0; s < S; ++s) request(rs_x, s, std::false_type{});
+        }
+        q_next = q_ahead;
+        e = e_next;
     }
-    hook(-2);
-    __syncthreads();
-    if (nrb > 0) finish(sm.red[(nrb - 1) & 1], p_enode, p_cl, p_cr, p_erow);
-    __syncthreads();                                            // row tables and LDS may be rewritten after this call
 }
 
 }  // namespace tl

@@ -108,8 +108,7 @@ struct Gemm {
 struct SplitGemm {
     const void *wp;         // packed terms, see pack.hpp
     const float *scale;     // [n_cg][NG][HU]: what a sum of scaled products is multiplied by
-    const float *w;         // the matrix as given (used where `special` says so)
-    const int *special;     // [n_cg][NG]: not 0 where a column holds an infinity and has no split
+    const float *w;         // the matrix as given
 };
 constexpr float SPLIT_H_SCALE = 16384.f;    // power of two by which h (|h| <= 1) is scaled before it is split
 
@@ -159,6 +158,9 @@ struct Fwd {
     int32_t *flow_seen;
     int4 *flow_list;
     int flow_roots;                   // data-flow scheduler: roots are found and their states copied out by the cell kernels (no separate passes)
+    int4 *sched;                      // ... and of the split cell: blocks of 16 entries {node, left, right, flags}, see flow_schedule
+    int4 *sched_head;                 // per slot {first block, blocks, trees [from, to) among which some have one node}
+    int n_slots;                      // slots (sets of workgroups that cover all column groups) of its kernel
     int flow;                         // data-flow scheduler: who fills the rows of internal nodes with the "not written" pattern: 1 the reset kernel, 2 the leaf kernel
     int gang_parts;                   // ready scheduler, RNTN cell: workgroups per tile and column group (each adds up a part of the slices), 1 or RNTN_PARTS
     int pick;                         // batch of few large trees, both internal-node kernels launched: 1 this one runs if the trees are narrow, 2 if they are not (see internal_kernel_skipped)

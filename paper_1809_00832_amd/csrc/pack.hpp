@@ -122,13 +122,12 @@ __global__ void k_pack_many(PackList pl)
 // The two fp16 terms of a matrix for the split cell (cell_split.hpp): [column group][k-step of 32][gate][hi, lo][lane][8].
 // The K axis is SEG segments of `steps` k-steps (L rows, zero padded), then zeros up to n_steps k-steps.  Every column is
 // scaled by the power of two that brings its largest magnitude into [2^13, 2^14) (exponents beyond what fp32 can undo are cut
-// off); `scale` receives what a sum of products is to be multiplied by.  One workgroup per column group and gate: it looks
+// off); `scale` receives what a sum of products is to be multiplied by (NaN: the column holds an infinity, which has no two terms).  One workgroup per column group and gate: it looks
 // for the largest magnitudes of its 16 columns first, then packs them.
 struct SplitPackJob {
     const float *w;
     _Float16 *wp;
     float *scale;
-    int *special;           // [n_cg][NG]: the columns hold an infinity
     int NG, H, SEG, L, steps, n_steps, n_cg;
     float operand_scale;    // of the other side
 };
@@ -139,7 +138,7 @@ struct SplitPackList {
 };
 __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
 {
-    __shared__ unsigned s_max[16];
+    __shared__ unsigned s_max[16], s_inf[16];
     int b = blockIdx.x, a = 0;
     while (a + 1 < pl.n && b >= pl.job[a].n_cg * pl.job[a].NG) {
         b -= pl.job[a].n_cg * pl.job[a].NG;
@@ -151,7 +150,7 @@ __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
     const int col = tid & 15, hu = cg * HU + col;
     const size_t ld = (size_t)j.NG * j.H;
     const float *w = j.w + (size_t)g * j.H + hu;
-    if (tid < 16) s_max[tid] = 0u;
+    if (tid < 16) s_max[tid] = s_inf[tid] = 0u;
     __syncthreads();
     unsigned m = 0u;                                            // largest finite magnitude, as bits
     bool inf = false;
@@ -162,11 +161,11 @@ __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
             else if (v == 0x7F800000u) inf = true;
         }
     atomicMax(&s_max[col], m);
-    const int any_inf = __syncthreads_or(inf ? 1 : 0);
-    if (tid == 0) j.special[cg * j.NG + g] = any_inf;
+    if (inf) s_inf[col] = 1u;
+    __syncthreads();
     const int top = (int)(s_max[col] >> 23);                    // biased exponent of the column's largest magnitude
     const int e = min(13 - (top - 127), 100);                   // the column is scaled by 2^e
-    if (tid < 16) j.scale[(cg * j.NG + g) * HU + col] = hu < j.H ? ldexpf(1.f / j.operand_scale, -e) : 0.f;
+    if (tid < 16) j.scale[(cg * j.NG + g) * HU + col] = s_inf[col] ? __uint_as_float(0x7FC00000u) : hu < j.H ? ldexpf(1.f / j.operand_scale, -e) : 0.f;
     const int total = j.n_steps * 64 * 8;
     for (int i = tid; i < total; i += 256) {
         const int el = i & 7, c = i >> 3 & 15, kg = i >> 7 & 3, s = i >> 9;

@@ -530,21 +530,12 @@ __device__ inline void flow_append(int4 *list, int capacity, int *len, unsigned 
     }
 }
 
-// MODE: which cell evaluates the nodes.  FLOW_F32: fp32 matrix instructions (TreeRNN: its leaves are embedding rows of any
-// magnitude, which the split cell's fixed scale does not take); FLOW_BF16: bf16 operands; FLOW_SPLIT: fp32 operands as two
-// fp16 terms (TreeLSTM; SPW counts k-steps of 32 there, as with bf16).
-enum FlowMode { FLOW_F32 = 0, FLOW_BF16 = 1, FLOW_SPLIT = 2 };
-template <int NG, int SPW, int MODE>
-using FlowWeights = std::conditional_t<MODE == FLOW_SPLIT, SplitWeights<NG, SPW>, PersistentWeights<NG, SPW, MODE == FLOW_BF16>>;
-template <int SPW, int MODE>
-using FlowSmem = std::conditional_t<MODE == FLOW_SPLIT, SplitSmem, PersistentSmem<SPW, MODE == FLOW_BF16>>;
-
-template <int EPI, bool VEC4, int SPW, int MODE = FLOW_F32>
-__global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_persistent(Fwd f)
+template <int EPI, bool VEC4, int SPW, bool BF16 = false>
+__global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fwd f)
 {
     static_assert(SPW > 0, "the data-flow scheduler uses the weight-stationary cell");
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    using Smem = FlowSmem<SPW, MODE>;
+    using Smem = PersistentSmem<SPW, BF16>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     Ctl *ctl = f.ctl;
     if (batch_rejected(f) || internal_kernel_skipped(f)) return;
@@ -552,31 +543,10 @@ __global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_
     const int n_slots = gridDim.x / f.n_cg;
     const int member = blockIdx.x % f.n_cg, slot = blockIdx.x / f.n_cg;
     const int my_cg = member;
-    FlowWeights<EpiTraits<EPI>::NG, SPW, MODE> w;              // (loaded below, behind the first requests of the scan)
+    PersistentWeights<EpiTraits<EPI>::NG, SPW, BF16> w;        // (loaded below, behind the first requests of the scan)
 
-    // the slot's trees: [t_lo, t_hi), cut where the node count passes slot / n_slots of the batch.  Both cuts are
-    // looked for at once, lanes 0-31 of every wave for this slot's and lanes 32-63 for the next one's, 32 candidates per
-    // round trip (a bisection is one dependent load per halving).
     int t_lo, t_hi;
-    {
-        const int lane = tid & 63, half = lane >> 5, i = lane & 31;
-        const long long bound = ((long long)(slot + half) * f.n_nodes + n_slots - 1) / n_slots;
-        int lo = 0, hi = f.n_trees;                   // smallest t with tree_off[t] >= bound is in [lo, hi]; tree_off[n_trees] = n_nodes >= bound
-        while (__ballot(lo < hi) != 0ull) {
-            const int step = (hi - lo + 30) / 31;     // candidates lo, lo + step, ..., the last one clamped to hi
-            const int cand = min(lo + i * step, hi);
-            const bool ge = cand >= hi || f.tree_off[cand] >= bound;                    // (at hi it holds by the invariant)
-            const unsigned long long m = __ballot(ge) >> (32 * half) & 0xFFFFFFFFull;   // never empty: the last candidate is hi
-            const int k = __builtin_ctzll(m);         // first candidate at or above the cut
-            if (lo < hi) {
-                const int new_hi = min(lo + k * step, hi);
-                lo = k == 0 ? lo : min(lo + (k - 1) * step, hi) + 1;                    // (k == 0: the cut is lo itself)
-                hi = new_hi;
-            }
-        }
-        t_lo = __builtin_amdgcn_readlane(lo, 0);      // (scalar values, like everything derived from them)
-        t_hi = __builtin_amdgcn_readlane(lo, 32);
-    }
+    flow_cut(f, slot, n_slots, &t_lo, &t_hi);
     const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];
     const int slot_internal = ((ne - nb) - (t_hi - t_lo)) / 2;      // full binary trees
     if (ne <= nb) return;
@@ -608,8 +578,7 @@ __global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_
     // of up to 1 024 nodes then runs while the weights arrive, instead of behind them.
     scan_requests(nb);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (MODE == FLOW_SPLIT) split_load(w, f.xi, f.inner, my_cg, tid >> 6, tid & 63);
-    else if constexpr (MODE == FLOW_BF16) ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
+    if constexpr (BF16) ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
     else ws_load(w, f.inner, my_cg, tid >> 6, tid & 63);
     __builtin_amdgcn_sched_barrier(0);
     for (int n = nb + tid; n < ne; n += WG_THREADS) seen[n] = 0u;
@@ -712,8 +681,7 @@ __global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_
                 ticket.p = -1;
             }
         };
-        if constexpr (MODE == FLOW_SPLIT) split_tile<SPW>(sm, f, count, my_cg, w, hook);
-        else if constexpr (MODE == FLOW_BF16) ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
+        if constexpr (BF16) ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
         else ws_tile<EPI, true, SPW, !VEC4, true>(sm, f, f.inner, f.h, f.n_nodes, count, my_cg, w, hook);
         if (sm.cmd[7] != 0) return;                   // a wait was abandoned: everybody leaves
         pieces += 1;
@@ -741,6 +709,33 @@ __global__ __launch_bounds__(WG_THREADS, MODE == FLOW_BF16 ? 2 : 1) void k_flow_
                 if (f.parent[n] < 0) flow_copy_root(f, n, my_cg, t_lo, t_hi);
         }
     }
+}
+
+// The same scheduler with the split cell (fp32 TreeLSTM), on the schedule that flow_schedule has prepared.
+template <int S>
+__global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SplitSmem &sm = *reinterpret_cast<SplitSmem *>(smem_raw);
+    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
+    const int tid = threadIdx.x;
+    int member, slot;
+    split_place(f, &slot, &member);
+    if (tid == 0) sm.gave_up = 0;
+    SplitWeights<EpiTraits<EPI_LSTM_INNER>::NG, S> w;
+    split_load(w, f.xi, f.inner, member, tid >> 6, tid & 63);
+    const int4 head = f.sched_head[slot];
+    if (f.flow_roots) {                           // trees of one node: the leaf is the root
+        const int hu = member * HU + (tid & 15);
+        for (int t = head.z + (tid >> 4); t < head.w && hu < f.H; t += WG_THREADS / 16) {
+            const int n = f.tree_off[t];
+            if (f.tree_off[t + 1] - n != 1) continue;
+            if (f.h_root) f.h_root[(size_t)t * f.H + hu] = f.h[(size_t)n * f.H + hu];
+            if (f.c_root) f.c_root[(size_t)t * f.H + hu] = f.c[(size_t)n * f.H + hu];
+        }
+    }
+    __syncthreads();
+    if (head.y > 0) split_run<S>(sm, f, f.sched + (size_t)head.x * 16, head.y, member, w);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -381,4 +381,203 @@ __global__ void k_root_gather(Fwd f)
     }
 }
 
+// ---- schedule of the data-flow kernel ------------------------------------------------------------
+// The trees of the batch are dealt to the slots (sets of workgroups that cover all column groups) in contiguous ranges of
+// about equal node count.  For every slot one workgroup orders the internal nodes of its trees with the ready
+// counters of Section 4.1: it starts with the nodes over two leaves; handing a node out counts it at its parent, and a
+// parent whose internal children have all been handed out goes to the end of the list.  The list is cut into blocks of up to
+// 16 nodes whose children all lie in earlier blocks: rounds of whole blocks as long as enough nodes wait, what is left of the
+// list (at most 16) otherwise.  A block is `late` if a node of it became ready with the block right before it.
+// The order depends on the trees alone, so one workgroup prepares it for all, beside the leaf cells; the cell kernel then
+// walks finished blocks and knows two blocks ahead what it will need.  The rounds are a chain of LDS accesses of one wave
+// (0.2 us each), the lists of a slot in LDS (5 bytes per node) or, for slots of more nodes than fit, in the workspace.
+constexpr unsigned SCHED_LATE = 0x80000000u;
+__host__ __device__ constexpr size_t sched_lds_bytes(size_t n) { return 16 + ((2 * n + 3) & ~(size_t)3) + ((n + 3) & ~(size_t)3) + 2 * (2 * (n / 2 + 1) + 2); }
+
+template <bool IN_LDS> struct SchedLists;
+template <> struct SchedLists<true> {
+    typedef unsigned short T;
+    static constexpr unsigned NONE = 0xFFFFu, LATE = 0x8000u;
+    T *par, *pool, *start;              // parent and (list position ->) node, relative to the slot's first node; first list position of a block
+    unsigned *cnt;                      // internal children not handed out yet, one byte per node
+    __device__ inline void carve(const Fwd &, unsigned char *lds, int n, int, int)
+    {
+        cnt = reinterpret_cast<unsigned *>(lds);
+        par = reinterpret_cast<T *>(lds + ((n + 3) & ~3));
+        pool = reinterpret_cast<T *>(lds + ((n + 3) & ~3) + ((2 * n + 3) & ~3));
+        start = pool + (n / 2 + 1);
+    }
+    __device__ inline void set_node(int i, int p, int pend)
+    {
+        par[i] = p < 0 ? (T)NONE : (T)p;
+        reinterpret_cast<unsigned char *>(cnt)[i] = (unsigned char)pend;
+    }
+    __device__ inline int parent(int i) const { return par[i] == (T)NONE ? -1 : (int)par[i]; }
+    __device__ inline int count_down(int i) { return (int)(atomicSub(&cnt[i >> 2], 1u << (8 * (i & 3))) >> (8 * (i & 3)) & 0xFFu); }
+    __device__ inline int node(int pos) const { return pool[pos]; }
+    __device__ inline void list(int pos, int i) { pool[pos] = (T)i; }
+    __device__ inline void block(int b, int pos, bool late) { start[b] = (T)((unsigned)pos | (late ? LATE : 0u)); }
+    __device__ inline int block_start(int b) const { return start[b] & 0x7FFF; }
+    __device__ inline bool block_late(int b) const { return (start[b] & LATE) != 0u; }
+    __device__ inline void settle() const { __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront"); }
+};
+template <> struct SchedLists<false> {
+    int32_t *par, *pool, *cnt;
+    unsigned *start;
+    int nb;
+    __device__ inline void carve(const Fwd &f, unsigned char *, int, int nb_, int first)
+    {
+        nb = nb_;
+        par = f.parent + nb;
+        cnt = f.arrive + nb;
+        pool = f.level_nodes + first;
+        start = reinterpret_cast<unsigned *>(f.level_fill) + first;
+    }
+    __device__ inline void set_node(int i, int, int pend) { st_dev(&cnt[i], pend); }
+    __device__ inline int parent(int i) const { const int p = par[i]; return p < 0 ? -1 : p - nb; }
+    __device__ inline int count_down(int i) { return add_dev(&cnt[i], -1); }
+    __device__ inline int node(int pos) const { return ld_dev(&pool[pos]); }
+    __device__ inline void list(int pos, int i) { st_dev(&pool[pos], (int32_t)i); }
+    __device__ inline void block(int b, int pos, bool late) { st_dev(&start[b], (unsigned)pos | (late ? SCHED_LATE : 0u)); }
+    __device__ inline int block_start(int b) const { return (int)(ld_dev(&start[b]) & ~SCHED_LATE); }
+    __device__ inline bool block_late(int b) const { return (ld_dev(&start[b]) & SCHED_LATE) != 0u; }
+    __device__ inline void settle() const { wait_mem(); }
+};
+
+// The part of the batch that belongs to a slot: trees [t_lo, t_hi), cut where the node count passes slot / n_slots of the batch.
+// Both cuts are looked for at once, lanes 0-31 of every wave for this slot's and lanes 32-63 for the next one's, 32
+// candidates per round trip (a bisection is one dependent load per halving).
+__device__ inline void flow_cut(const Fwd &f, int slot, int n_slots, int *t_lo, int *t_hi)
+{
+    const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
+    const long long bound = ((long long)(slot + half) * f.n_nodes + n_slots - 1) / n_slots;
+    int lo = 0, hi = f.n_trees;                   // smallest t with tree_off[t] >= bound is in [lo, hi]; tree_off[n_trees] = n_nodes >= bound
+    while (__ballot(lo < hi) != 0ull) {
+        const int step = (hi - lo + 30) / 31;     // candidates lo, lo + step, ..., the last one clamped to hi
+        const int cand = min(lo + i * step, hi);
+        const bool ge = cand >= hi || f.tree_off[cand] >= bound;                    // (at hi it holds by the invariant)
+        const unsigned long long m = __ballot(ge) >> (32 * half) & 0xFFFFFFFFull;   // never empty: the last candidate is hi
+        const int k = __builtin_ctzll(m);         // first candidate at or above the cut
+        if (lo < hi) {
+            const int new_hi = min(lo + k * step, hi);
+            lo = k == 0 ? lo : min(lo + (k - 1) * step, hi) + 1;                    // (k == 0: the cut is lo itself)
+            hi = new_hi;
+        }
+    }
+    *t_lo = __builtin_amdgcn_readlane(lo, 0);     // (scalar values, like everything derived from them)
+    *t_hi = __builtin_amdgcn_readlane(lo, 32);
+}
+
+template <bool IN_LDS>
+__device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int t_hi, int nb, int ne, unsigned char *lds)
+{
+    const int tid = threadIdx.x, lane = tid & 63, n = ne - nb, first = (nb - t_lo) / 2;
+    const int cap = (n - (t_hi - t_lo)) / 2;      // internal nodes (full binary trees)
+    int *s_ctl = reinterpret_cast<int *>(lds);    // seeds | roots, later nodes handed out | blocks | a tree of one node exists
+    SchedLists<IN_LDS> q;
+    q.carve(f, lds + 16, n, nb, first);
+    if (tid < 4) s_ctl[tid] = 0;
+    __syncthreads();
+    constexpr int Q = 4;
+    for (int base = 0; base < n; base += WG_THREADS * Q) {
+        int l[Q], up[Q], pend[Q];
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const int i = min(base + j * WG_THREADS + tid, n - 1);
+            l[j] = f.left[nb + i];
+            up[j] = f.parent[nb + i];
+            pend[j] = f.pending[nb + i];
+        }
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const int i = base + j * WG_THREADS + tid;
+            const bool here = i < n;
+            if (here) q.set_node(i, up[j] < 0 ? -1 : up[j] - nb, pend[j]);
+            const bool seed = here && l[j] >= 0 && pend[j] == 0;
+            const unsigned long long m = __ballot(seed);
+            int pos = 0;
+            if (m != 0ull && lane == __builtin_ctzll(m)) pos = atomicAdd(&s_ctl[0], __popcll(m));
+            if (m != 0ull) pos = __shfl(pos, __builtin_ctzll(m)) + __popcll(m & ((1ull << lane) - 1ull));
+            if (seed && pos < cap) q.list(pos, i);
+            if (f.flow_roots && here && up[j] < 0) {
+                // a root: one per tree (a second one of a tree is found here, a missing one by the count)
+                atomicAdd(&s_ctl[1], 1);
+                const int t = t_lo + tree_of(f.tree_off + t_lo, t_hi - t_lo, nb + i);
+                f.depth_root[nb + i] = t;
+                if (f.root_out) f.root_out[t] = nb + i;
+                if (l[j] < 0) atomicOr(&s_ctl[3], 1);
+                if (atomicCAS(&f.root_ws[t], -1, nb + i) != -1) latch_error(f.ctl, TL_ESTRUCT);
+            }
+        }
+    }
+    wait_mem();
+    __syncthreads();
+    if (tid < 64) {
+        int head = 0, tail = min(s_ctl[0], cap), blocks = 0, rounds = 0;
+        int fresh = cap;                          // list positions from here on became ready in the round before
+        while (head < tail) {
+            int take = min(tail - head, 64);
+            if (take > 16) take &= ~15;
+            const bool mine = lane < take;
+            int p = -1;
+            if (mine) p = q.parent(q.node(head + lane));
+            bool ready = false;
+            if (p >= 0) ready = q.count_down(p) == 1;
+            const unsigned long long m = __ballot(ready);
+            const int pos = tail + __popcll(m & ((1ull << lane) - 1ull));
+            if (ready && pos < cap) q.list(pos, p);
+            if (lane * 16 < take) q.block(blocks + lane, head + lane * 16, lane == 0 && head + min(take, 16) > fresh);
+            fresh = tail;
+            blocks += (take + 15) >> 4;
+            head += take;
+            tail = min(tail + __popcll(m), cap);
+            rounds += 1;
+            q.settle();
+        }
+        if (lane == 0) {
+            s_ctl[2] = blocks;
+            f.sched_head[slot] = int4{first, blocks, t_lo, s_ctl[3] != 0 ? t_hi : t_lo};
+            atomicMax(&f.ctl->n_levels, rounds + 1);
+            // nodes that never became ready (a cycle), or a tree without a root
+            if (head < cap || (f.flow_roots && s_ctl[1] != t_hi - t_lo)) latch_error(f.ctl, TL_ESTRUCT);
+            s_ctl[1] = head;
+        }
+    }
+    __syncthreads();
+    // the blocks' entries; rows beyond a block's nodes stand in with the sources of its first row: they are requested like
+    // the others (a request needs no test), so they must be rows that do become valid
+    const int blocks = s_ctl[2], handed = s_ctl[1];
+    int4 *out = f.sched + (size_t)first * 16;
+#pragma unroll 4
+    for (int i = tid; i < blocks * 16; i += WG_THREADS) {
+        const int b = i >> 4, r = i & 15;
+        const int st = q.block_start(b), end = b + 1 < blocks ? q.block_start(b + 1) : handed;
+        const bool here = st + r < end;
+        const int node = nb + q.node(here ? st + r : st);
+        int w = q.block_late(b) ? (int)SCHED_LATE : 0;
+        if (f.flow_roots && here && f.parent[node] < 0) w |= ld_dev(&f.depth_root[node]) + 1;
+        out[i] = int4{here ? node : -1, f.left[node], f.right[node], w};
+    }
+}
+__device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds, size_t lds_bytes)
+{
+    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
+    int t_lo, t_hi;
+    flow_cut(f, slot, f.n_slots, &t_lo, &t_hi);
+    const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];
+    if (ne <= nb) {
+        if (threadIdx.x == 0) f.sched_head[slot] = int4{0, 0, 0, 0};
+        return;
+    }
+    if (ne - nb < 0xFFFF && sched_lds_bytes((size_t)(ne - nb)) <= lds_bytes) flow_schedule_slot<true>(f, slot, t_lo, t_hi, nb, ne, lds);
+    else flow_schedule_slot<false>(f, slot, t_lo, t_hi, nb, ne, lds);
+}
+// As a launch of its own, where the leaves are evaluated by a kernel that does not do it on the side.
+constexpr size_t SCHED_LDS_BYTES = 60 * 1024;
+__global__ __launch_bounds__(WG_THREADS) void k_flow_schedule(Fwd f)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    flow_schedule(f, blockIdx.x, smem_raw, SCHED_LDS_BYTES);
+}
+
 }  // namespace tl

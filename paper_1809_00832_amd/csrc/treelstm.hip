@@ -71,9 +71,10 @@ struct tl_ctx {
     int hx_steps = 0;                 // 128-byte lines per row of the split copy of h
     int flow_grid = 0;                // workgroups of the data-flow kernel
     unsigned *hx = nullptr;           // split copy of h, cap_nodes rows
-    _Float16 *xp_inner = nullptr;     // its packed weights, their scales and flags
+    int4 *sched = nullptr;            // schedule of its kernel: blocks of 16 entries, as many blocks as internal nodes at most
+    int4 *sched_head = nullptr;       // first block, number of blocks and trees of every slot
+    _Float16 *xp_inner = nullptr;     // its packed weights and their scales
     float *xs_inner = nullptr;
-    int *xf_inner = nullptr;
     // backward pass (TreeLSTM, fp32): transposed weights packed like the forward ones, workspace
     void *wp_bwd_inner = nullptr, *wp_bwd_leaf = nullptr, *wp_bwd_inner1 = nullptr;
     float *bp_bwd_inner = nullptr, *bp_bwd_leaf = nullptr, *bp_bwd_inner1 = nullptr;
@@ -199,12 +200,12 @@ fwd_kernel flow_kernel_bf16(int cell, int s)
 {
     const bool lstm = cell == TL_TREELSTM;
     switch (s) {
-    case 1: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 1, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 1, FLOW_BF16>;
-    case 2: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 2, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 2, FLOW_BF16>;
-    case 3: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 3, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 3, FLOW_BF16>;
-    case 4: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 4, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 4, FLOW_BF16>;
-    case 6: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 6, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 6, FLOW_BF16>;
-    default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 8, FLOW_BF16> : k_flow_persistent<EPI_RNN_INNER, true, 8, FLOW_BF16>;
+    case 1: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 1, true> : k_flow_persistent<EPI_RNN_INNER, true, 1, true>;
+    case 2: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 2, true> : k_flow_persistent<EPI_RNN_INNER, true, 2, true>;
+    case 3: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 3, true> : k_flow_persistent<EPI_RNN_INNER, true, 3, true>;
+    case 4: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 4, true> : k_flow_persistent<EPI_RNN_INNER, true, 4, true>;
+    case 6: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 6, true> : k_flow_persistent<EPI_RNN_INNER, true, 6, true>;
+    default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 8, true> : k_flow_persistent<EPI_RNN_INNER, true, 8, true>;
     }
 }
 // fp32 TreeRNN
@@ -223,14 +224,14 @@ fwd_kernel flow_kernel_rnn(bool vec4, int spw)
 fwd_kernel flow_kernel_split(int s)
 {
     switch (s) {
-    case 1: return k_flow_persistent<EPI_LSTM_INNER, true, 1, FLOW_SPLIT>;
-    case 2: return k_flow_persistent<EPI_LSTM_INNER, true, 2, FLOW_SPLIT>;
-    case 3: return k_flow_persistent<EPI_LSTM_INNER, true, 3, FLOW_SPLIT>;
-    case 4: return k_flow_persistent<EPI_LSTM_INNER, true, 4, FLOW_SPLIT>;
-    case 5: return k_flow_persistent<EPI_LSTM_INNER, true, 5, FLOW_SPLIT>;
-    case 6: return k_flow_persistent<EPI_LSTM_INNER, true, 6, FLOW_SPLIT>;
-    case 7: return k_flow_persistent<EPI_LSTM_INNER, true, 7, FLOW_SPLIT>;
-    default: return k_flow_persistent<EPI_LSTM_INNER, true, 8, FLOW_SPLIT>;
+    case 1: return k_flow_split<1>;
+    case 2: return k_flow_split<2>;
+    case 3: return k_flow_split<3>;
+    case 4: return k_flow_split<4>;
+    case 5: return k_flow_split<5>;
+    case 6: return k_flow_split<6>;
+    case 7: return k_flow_split<7>;
+    default: return k_flow_split<8>;
     }
 }
 // The data-flow kernel: split > 0 the split cell with that many k-steps per wave, else spw > 0 and not the RNTN cell
@@ -408,10 +409,9 @@ int pack_split(tl_ctx *ctx, hipStream_t st)
     const int H = ctx->cfg.hidden, n_cg = ctx->n_cg, n_steps = 4 * ctx->split;
     if (!ctx->xp_inner) TL_HIP(hipMalloc(&ctx->xp_inner, (size_t)n_cg * n_steps * 5 * 2 * 64 * 8 * sizeof(_Float16)));
     if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)n_cg * 5 * HU * sizeof(float)));
-    if (!ctx->xf_inner) TL_HIP(hipMalloc(&ctx->xf_inner, (size_t)n_cg * 5 * sizeof(int)));
     SplitPackList pl{};
     SplitPackJob &j = pl.job[0];
-    j.w = ctx->m_u; j.wp = ctx->xp_inner; j.scale = ctx->xs_inner; j.special = ctx->xf_inner;
+    j.w = ctx->m_u; j.wp = ctx->xp_inner; j.scale = ctx->xs_inner;
     j.NG = 5; j.H = H; j.SEG = 2; j.L = H; j.steps = ctx->hx_steps; j.n_steps = n_steps; j.n_cg = n_cg;
     j.operand_scale = SPLIT_H_SCALE;
     pl.n = 1;
@@ -573,6 +573,7 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     if (ctx->ws) { TL_HIP(hipFree(ctx->ws)); ctx->ws = nullptr; }
     if (ctx->hb) { TL_HIP(hipFree(ctx->hb)); ctx->hb = nullptr; }
     if (ctx->hx) { TL_HIP(hipFree(ctx->hx)); ctx->hx = nullptr; }
+    if (ctx->sched) { TL_HIP(hipFree(ctx->sched)); ctx->sched = nullptr; }
     if (ctx->flow_ws) { TL_HIP(hipFree(ctx->flow_ws)); ctx->flow_ws = nullptr; }
     if (ctx->host_levels) { TL_HIP(hipHostFree(ctx->host_levels)); ctx->host_levels = nullptr; }
     ctx->cap_nodes = ctx->cap_trees = 0;
@@ -589,7 +590,8 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
         TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
         TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));   // the padding stays zero for good
     }
-    if ((ctx->spw > 0 || ctx->split > 0) && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
+    if (ctx->split > 0) TL_HIP(hipMalloc(&ctx->sched, ((size_t)N / 2 + 1) * 16 * sizeof(int4)));
+    else if (ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
         TL_HIP(hipMalloc(&ctx->flow_ws, flow_bytes(ctx->n_cg, (size_t)N)));
     TL_HIP(hipHostMalloc(&ctx->host_levels, (size_t)(N + 2) * 4, hipHostMallocDefault));
     ctx->ws_bytes = bytes;
@@ -632,9 +634,10 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->hb);
     (void)hipFree(ctx->flow_ws);
     (void)hipFree(ctx->hx);
+    (void)hipFree(ctx->sched);
+    (void)hipFree(ctx->sched_head);
     (void)hipFree(ctx->xp_inner);
     (void)hipFree(ctx->xs_inner);
-    (void)hipFree(ctx->xf_inner);
     (void)hipFree(ctx->embb);
     (void)hipFree(ctx->wp_bwd_inner);
     (void)hipFree(ctx->wp_bwd_inner1);
@@ -886,6 +889,12 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             if (o < o_min) o_min = o;
         }
         ctx->flow_grid = o_min * ctx->n_cu;
+        if (ctx->split > 0) {
+            const int per_domain = ctx->flow_grid / N_XCD / ctx->n_cg * N_XCD, slots = ctx->flow_grid / ctx->n_cg;
+            if (10 * per_domain >= 9 * slots) ctx->flow_grid = per_domain * ctx->n_cg;      // slots inside L2 domains (see split_place)
+            if ((rc = allow_lds(k_flow_schedule, SCHED_LDS_BYTES)) != TL_OK) return rc;
+            TL_HIP(hipMalloc(&ctx->sched_head, (size_t)(slots + 1) * sizeof(int4)));
+        }
         if (ctx->flow_grid < ctx->n_cg) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
     }
     if (ctx->spw_leaf > 0) {
@@ -1043,7 +1052,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     // cell does not take, the fixed workspace) the level scheduler on the device stands in.
     const bool split_range = n_nodes < (1 << 24) && (unsigned long long)n_nodes * ctx->hx_steps * 128ull < (1ull << 32);
     const int split = split_range ? ctx->split : 0;
-    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_ws != nullptr && ctx->flow_grid > 0 &&
+    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_grid > 0 &&
                       (cfg.cell == TL_TREELSTM && !bf16 ? split > 0 : spw > 0);
     // A batch of few large trees: the data-flow scheduler deals whole trees to its sets of workgroups, so with fewer
     // trees than sets the others stay idle: one bushy tree of 16 384 leaves takes 3.5 ms on one set against 0.34 ms
@@ -1060,7 +1069,8 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (flow && split > 0) {
         f.hx = ctx->hx;
         f.hx_steps = ctx->hx_steps;
-        f.xi.wp = ctx->xp_inner; f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u; f.xi.special = ctx->xf_inner;
+        f.sched = ctx->sched; f.sched_head = ctx->sched_head;
+        f.xi.wp = ctx->xp_inner; f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u;
     }
     // The persistent kernels' workgroups wait for each other, so all of them must be resident at once: the grid is
     // cut to what the device holds of the very kernel that is launched (the figure taken at tl_create is that of one
@@ -1118,6 +1128,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         f.flow = (cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range) ? 2 : 1;
         // (with no internal node the data-flow kernel is not launched; where the level kernel may run instead, the root passes do)
         f.flow_roots = f.n_int > 0 && !need_levels && !flow_or_levels ? 1 : 0;
+        f.n_slots = grid_p / ctx->n_cg;
         f.flow_seen = reinterpret_cast<int32_t *>(ctx->flow_ws);
         f.flow_list = reinterpret_cast<int4 *>(ctx->flow_ws + align256((size_t)ctx->n_cg * ctx->cap_nodes * sizeof(int32_t)));
     }
@@ -1166,6 +1177,11 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (prof) TL_HIP(hipEventRecord(ev[1], st));
 
     // ---- leaves ------------------------------------------------------------------------
+    if (flow && split > 0 && f.n_int > 0) {
+        Fwd g = f;
+        g.pick = flow_or_levels ? 1 : 0;
+        hipLaunchKernelGGL(k_flow_schedule, dim3(f.n_slots), dim3(WG_THREADS), SCHED_LDS_BYTES, st, g);
+    }
     if (cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range) {          // (its cell addresses h and c with 32-bit offsets)
         hipLaunchKernelGGL(bf16 ? leaf_ws_bf_kernel(ctx->spw_leaf) : leaf_ws_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid),
                            dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16), st, f);
