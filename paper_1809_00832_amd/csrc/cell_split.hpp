@@ -262,4 +262,138 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
     }
 }
 
+// ---- leaves ----------------------------------------------------------------------------------------
+// Lane l of a wave holds, for row l & 15, the eight embedding values k = 32 step + 8 (l >> 4) ... + 7 of each of its wave's S
+// steps: 16-byte loads (rows need 4-byte alignment only), straight into the registers that become the A operands.  An
+// embedding may have any magnitude, so every row is scaled for itself, and for each quarter of the K axis: by the power of two
+// that brings the quarter's largest magnitude into [2^14, 2^15); the wave scales its partial sums back before they meet.
+// What lies beyond the row's end counts as zero.  A row that holds an infinity or a NaN (and a column of weights that holds an
+// infinity) comes out as NaN here; its sums are then taken in fp32.
+struct SplitLeafSmem {
+    static constexpr int NG = 3;
+    float red[2][4 * NG * 64 * 4];
+    float row_scale[4][16];
+};
+
+__device__ inline float max_across_quarters(float m)
+{
+    // lanes l, l ^ 16, l ^ 32, l ^ 48
+    m = fmaxf(m, __shfl_xor(m, 16));
+    return fmaxf(m, __shfl_xor(m, 32));
+}
+
+// Leaves [lo, hi) of the leaf list for column group cg; every workgroup keeps its slice of W_leaf.
+template <int S>
+__device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int hi, int cg, const SplitWeights<3, S> &w)
+{
+    constexpr int NG = 3;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int H = f.H, E = f.E;
+    const int hu = cg * HU + (lane & 15);
+    const bool hu_ok = hu < H;
+    const unsigned row_b = (unsigned)H * 4u, hu_b = (unsigned)(hu_ok ? hu : 0) * 4u, hx_row_b = (unsigned)f.hx_steps * 128u, emb_row_b = (unsigned)E * 4u;
+    const __amdgpu_buffer_rsrc_t rs_h = buf_of(f.h, (unsigned long long)f.n_nodes * H * 4), rs_c = buf_of(f.c, (unsigned long long)f.n_nodes * H * 4),
+                                 rs_x = buf_of(f.hx, (unsigned long long)f.n_nodes * hx_row_b),
+                                 rs_e = buf_of(f.emb, (unsigned long long)f.vocab * emb_row_b);
+    const int k0 = wave * S * 32 + 8 * (lane >> 4);             // this lane's first k of step 0
+    const bool whole = (wave + 1) * S * 32 <= E;                // no step of this wave reaches beyond the row
+    uintx4_t rows[S][2];
+    auto request = [&](int word) {
+        const unsigned base = (unsigned)word * emb_row_b;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                const int k = k0 + 32 * s + 4 * t;
+                rows[s][t] = __builtin_amdgcn_raw_buffer_load_b128(rs_e, (int)(base + 4u * (unsigned)min(k, E)), 0, 0);
+            }
+    };
+    const int n_blocks = (hi - lo + 15) >> 4;
+    if (n_blocks <= 0) return;
+    // node of row l & 15 three blocks ahead, its word two, its values one
+    auto node_of = [&](int b) { return f.leaf_list[min(lo + b * 16 + (lane & 15), hi - 1)]; };
+    int node0 = node_of(0), node1 = node_of(1), node2 = node_of(2);
+    int word1 = f.word[node1];
+    request(f.word[node0]);
+    for (int b = 0; b < n_blocks; ++b) {
+        const int node3 = node_of(b + 3), word2 = f.word[node2];
+        float x[S][8], m = 0.f;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                float v = __uint_as_float(rows[s][i >> 2][i & 3]);
+                if (!whole && k0 + 32 * s + i >= E) v = 0.f;
+                x[s][i] = v;
+                m = fmaxf(m, fabsf(v));
+            }
+        request(word1);                                         // (behind the last block: the last leaf's row again)
+        m = max_across_quarters(m);
+        const unsigned eb = max(__float_as_uint(m) >> 23, 15u);
+        const float scale = __uint_as_float((268u - eb) << 23), back = __uint_as_float((eb - 14u) << 23);
+        if (lane < 16) sm.row_scale[wave][lane] = back;
+        floatx4 acc[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            halfx8 vh, vl;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float v = x[s][i] * scale;
+                vh[i] = (_Float16)v;
+                vl[i] = (_Float16)(v - (float)vh[i]);
+            }
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, w.hi[s][g], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vh, w.lo[s][g], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(vl, w.hi[s][g], acc[g], 0, 0, 0);
+        }
+        float *red = sm.red[b & 1];
+        const floatx4 r4 = *reinterpret_cast<const floatx4 *>(&sm.row_scale[wave][4 * (lane >> 4)]);    // this wave's own writes
+#pragma unroll
+        for (int g = 0; g < NG; ++g) *reinterpret_cast<floatx4 *>(&red[((wave * NG + g) * 64 + lane) * 4]) = acc[g] * r4;
+        const int fin_row = 4 * wave + (lane >> 4);
+        const int node = __shfl(node0, fin_row);
+        __syncthreads();
+        float gate[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            float p[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = red[((k * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
+            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], w.scale[g], w.bias[g]);
+        }
+        if (lo + b * 16 + fin_row < hi) {
+            float cc = 0.f, hh = 0.f;
+            if (hu_ok) {
+                if (__builtin_expect(__builtin_isnan(gate[0] + gate[1] + gate[2]), 0)) {
+                    const float *xr = f.emb + (size_t)f.word[node] * E;
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) gate[g] = 0.f;
+                    for (int k = 0; k < E; ++k)
+#pragma unroll
+                        for (int g = 0; g < NG; ++g) gate[g] = __builtin_fmaf(xr[k], f.xl.w[(size_t)k * (NG * H) + (size_t)g * H + hu], gate[g]);
+#pragma unroll
+                    for (int g = 0; g < NG; ++g) gate[g] += w.bias[g];
+                }
+                lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, kept_gates(f, node, hu), H);
+                const unsigned o = (unsigned)node * row_b + hu_b;
+                buf_st_f<false>(rs_c, o, cc);
+                buf_st_f<false>(rs_h, o, hh);
+            }
+            if (f.hx) {
+                const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
+                if ((hu & ~1) < H) buf_st_f<false>(rs_x, (unsigned)node * hx_row_b + split_word_off(hu), __uint_as_float(word));
+            }
+        }
+        node0 = node1;
+        node1 = node2;
+        node2 = node3;
+        word1 = word2;
+    }
+}
+
 }  // namespace tl

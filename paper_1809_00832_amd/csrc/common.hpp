@@ -127,7 +127,7 @@ struct Fwd {
     const unsigned short *embb; // bf16 copy, rows of es elements (zero padded), for the bf16 weight-stationary leaf kernel
     int es;
     Gemm leaf, inner;
-    SplitGemm xi;               // inner weights for the split cell
+    SplitGemm xi, xl;           // inner and leaf weights for the split cells
     unsigned *hx;               // split copy of h that the split cell gathers from (cell_split.hpp), hx_steps lines of 128 bytes a row; else null
     int hx_steps;
     // workspace

@@ -45,36 +45,32 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_tiles_static(Fwd f, const int
     cell_tile<EPI, VEC4, false, BF16>(sm, f, gm, table, count, cg);
 }
 
-// Leaves with the weight-stationary cell (fp32): the leaf matrix is small (E x 3H), so a column
-// group's slice takes few registers, two workgroups fit on a CU, and every workgroup keeps its
-// slice while it walks a contiguous share of the leaf list in pieces of up to WS_TABLE_ROWS rows.
-template <int SPW>
-__global__ __launch_bounds__(WG_THREADS, 2) void k_leaf_ws(Fwd f)
+// fp32 leaves: the leaf matrix is small (E x 3H), so every workgroup keeps its column group's slice and walks a contiguous
+// share of the leaf list.  Under the data-flow scheduler with the split cell the first n_sched workgroups prepare the schedule of
+// the internal nodes instead, beside the leaves' cells.
+template <int S>
+__global__ __launch_bounds__(WG_THREADS, S <= 4 ? 2 : 1) void k_leaf_split(Fwd f, int n_sched)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    WsSmemT<SPW> &sm = *reinterpret_cast<WsSmemT<SPW> *>(smem_raw);
+    if ((int)blockIdx.x < n_sched) {
+        flow_schedule(f, blockIdx.x, smem_raw, SCHED_LDS_BYTES);
+        return;
+    }
+    SplitLeafSmem &sm = *reinterpret_cast<SplitLeafSmem *>(smem_raw);
     if (batch_rejected(f)) return;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, wg = blockIdx.x - n_sched, n_wg = gridDim.x - n_sched;
     // (data-flow scheduler: the stores that mark the internal nodes' rows go out first and complete beside the cells)
-    if (f.flow == 2) flow_fill(f, (size_t)blockIdx.x * 4 + (tid >> 6), (size_t)gridDim.x * 4);
-    const int cg = gang_cg(blockIdx.x % f.n_cg, f.n_cg, f.n_cg);
-    const int slot = blockIdx.x / f.n_cg, n_slots = gridDim.x / f.n_cg;
-    WsWeights<EpiTraits<EPI_LSTM_LEAF>::NG, SPW> w;
-    ws_load(w, f.leaf, cg, tid >> 6, tid & 63);
+    if (f.flow == 2) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
+    const int cg = gang_cg(wg % f.n_cg, f.n_cg, f.n_cg);
+    const int slot = wg / f.n_cg, n_slots = n_wg / f.n_cg;
+    SplitWeights<EpiTraits<EPI_LSTM_LEAF>::NG, S> w;
+    split_load(w, f.xl, f.leaf, cg, tid >> 6, tid & 63);
     const int share = ((f.n_leaf + n_slots - 1) / n_slots + 15) & ~15;
     const int lo = slot * share, hi = min(f.n_leaf, lo + share);
-    for (int piece = lo; piece < hi; piece += WS_TABLE_ROWS) {
-        const int count = min(hi - piece, WS_TABLE_ROWS);
-        const int node = tid < count ? f.leaf_list[piece + tid] : -1;
-        sm.node[tid] = node;
-        sm.src0[tid] = node >= 0 ? f.word[node] : 0;
-        sm.src1[tid] = 0;
-        __syncthreads();
-        ws_tile<EPI_LSTM_LEAF, false, SPW>(sm, f, f.leaf, f.emb, f.vocab, count, cg, w);
-    }
+    split_leaves<S>(sm, f, lo, hi, cg, w);
 }
 
-// The same with bf16 operands: rows come from a bf16 copy of the embedding table (rows padded with
+// Leaves with bf16 operands (weight-stationary cell): rows come from a bf16 copy of the embedding table (rows padded with
 // zeros to a multiple of 8 elements).
 // (Four workgroups per CU: the matrix instructions of a block of leaves take 0.1 us, the block's phases - rows, park,
 // barrier, gates - 1.2 us.)

@@ -392,6 +392,7 @@ __global__ void k_root_gather(Fwd f)
 // walks finished blocks and knows two blocks ahead what it will need.  The rounds are a chain of LDS accesses of one wave
 // (0.2 us each), the lists of a slot in LDS (5 bytes per node) or, for slots of more nodes than fit, in the workspace.
 constexpr unsigned SCHED_LATE = 0x80000000u;
+constexpr size_t SCHED_LDS_BYTES = 52 * 1024;     // three workgroups of the kernel that does it beside its own work fit on a CU
 __host__ __device__ constexpr size_t sched_lds_bytes(size_t n) { return 16 + ((2 * n + 3) & ~(size_t)3) + ((n + 3) & ~(size_t)3) + 2 * (2 * (n / 2 + 1) + 2); }
 
 template <bool IN_LDS> struct SchedLists;
@@ -573,7 +574,7 @@ __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds,
     else flow_schedule_slot<false>(f, slot, t_lo, t_hi, nb, ne, lds);
 }
 // As a launch of its own, where the leaves are evaluated by a kernel that does not do it on the side.
-constexpr size_t SCHED_LDS_BYTES = 60 * 1024;
+
 __global__ __launch_bounds__(WG_THREADS) void k_flow_schedule(Fwd f)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];

@@ -75,6 +75,8 @@ struct tl_ctx {
     int4 *sched_head = nullptr;       // first block, number of blocks and trees of every slot
     _Float16 *xp_inner = nullptr;     // its packed weights and their scales
     float *xs_inner = nullptr;
+    _Float16 *xp_leaf = nullptr;      // the same of the leaf matrix (fp32 TreeLSTM, spw_leaf > 0)
+    float *xs_leaf = nullptr;
     // backward pass (TreeLSTM, fp32): transposed weights packed like the forward ones, workspace
     void *wp_bwd_inner = nullptr, *wp_bwd_leaf = nullptr, *wp_bwd_inner1 = nullptr;
     float *bp_bwd_inner = nullptr, *bp_bwd_leaf = nullptr, *bp_bwd_inner1 = nullptr;
@@ -250,16 +252,18 @@ fwd_kernel levels_kernel(int cell, bool vec4, int spw, bool bf16)
     if (cell == TL_RNTN) return vec4 ? k_levels_persistent<EPI_RNTN_INNER, true, 0> : k_levels_persistent<EPI_RNTN_INNER, false, 0>;
     return cell == TL_TREELSTM ? levels_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16) : levels_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
 }
-fwd_kernel leaf_ws_kernel(int spw)
+typedef void (*leaf_kernel)(Fwd, int);
+leaf_kernel leaf_split_kernel(int s)
 {
-    switch (spw) {
-    case 1: return k_leaf_ws<1>;
-    case 2: return k_leaf_ws<2>;
-    case 4: return k_leaf_ws<4>;
-    case 5: return k_leaf_ws<5>;
-    case 8: return k_leaf_ws<8>;
-    case 16: return k_leaf_ws<16>;
-    default: return nullptr;
+    switch (s) {
+    case 1: return k_leaf_split<1>;
+    case 2: return k_leaf_split<2>;
+    case 3: return k_leaf_split<3>;
+    case 4: return k_leaf_split<4>;
+    case 5: return k_leaf_split<5>;
+    case 6: return k_leaf_split<6>;
+    case 7: return k_leaf_split<7>;
+    default: return k_leaf_split<8>;
     }
 }
 fwd_kernel leaf_ws_bf_kernel(int s)
@@ -300,7 +304,7 @@ size_t ws_lds_bytes(int spw, bool bf16)
 }
 size_t leaf_lds_bytes(int spw, bool bf16)
 {
-    if (!bf16) return ws_lds_bytes(spw, false);
+    if (!bf16) return sizeof(SplitLeafSmem) > SCHED_LDS_BYTES ? sizeof(SplitLeafSmem) : SCHED_LDS_BYTES;
     switch (spw) {
     case 1: return sizeof(LeafSmemBf<1>);
     case 2: return sizeof(LeafSmemBf<2>);
@@ -378,7 +382,7 @@ int pack_gemm(const float *w, const float *b, int NG, int H, int SEG, int L, int
 int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim;
-    int rc = pack_gemm(ctx->m_w_leaf, ctx->m_b_leaf, 3, H, 1, E, ctx->n_cg, 4 * ctx->spw_leaf, false, &ctx->g_leaf, &ctx->wp_leaf,
+    int rc = pack_gemm(ctx->m_w_leaf, ctx->m_b_leaf, 3, H, 1, E, ctx->n_cg, 0, false, &ctx->g_leaf, &ctx->wp_leaf,
                        &ctx->bp_leaf, st);
     if (rc != TL_OK) return rc;
     rc = pack_gemm(ctx->m_u, ctx->m_b, 5, H, 2, H, ctx->n_cg, ctx->ws_steps16, false, &ctx->g_inner, &ctx->wp_inner, &ctx->bp_inner, st);
@@ -402,20 +406,27 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
     return TL_OK;
 }
 
-// The split cell's weights (fp32 TreeLSTM contexts of the data-flow scheduler), from the parameters kept in the context.
+// The split cells' weights (fp32 TreeLSTM contexts: leaves; under the data-flow scheduler internal nodes too), from the parameters kept in the context.
 int pack_split(tl_ctx *ctx, hipStream_t st)
 {
-    if (ctx->split == 0) return TL_OK;
-    const int H = ctx->cfg.hidden, n_cg = ctx->n_cg, n_steps = 4 * ctx->split;
-    if (!ctx->xp_inner) TL_HIP(hipMalloc(&ctx->xp_inner, (size_t)n_cg * n_steps * 5 * 2 * 64 * 8 * sizeof(_Float16)));
-    if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)n_cg * 5 * HU * sizeof(float)));
+    const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim, n_cg = ctx->n_cg;
     SplitPackList pl{};
-    SplitPackJob &j = pl.job[0];
-    j.w = ctx->m_u; j.wp = ctx->xp_inner; j.scale = ctx->xs_inner;
-    j.NG = 5; j.H = H; j.SEG = 2; j.L = H; j.steps = ctx->hx_steps; j.n_steps = n_steps; j.n_cg = n_cg;
-    j.operand_scale = SPLIT_H_SCALE;
-    pl.n = 1;
-    hipLaunchKernelGGL(k_pack_split, dim3(n_cg * 5), dim3(256), 0, st, pl);
+    int grid = 0;
+    auto add = [&](const float *m, int NG, int SEG, int L, int S, float operand_scale, _Float16 **wp, float **scale) -> int {
+        if (!*wp) TL_HIP(hipMalloc(wp, (size_t)n_cg * 4 * S * NG * 2 * 64 * 8 * sizeof(_Float16)));
+        if (!*scale) TL_HIP(hipMalloc(scale, (size_t)n_cg * NG * HU * sizeof(float)));
+        SplitPackJob &j = pl.job[pl.n++];
+        j.w = m; j.wp = *wp; j.scale = *scale;
+        j.NG = NG; j.H = H; j.SEG = SEG; j.L = L; j.steps = (L + 31) / 32; j.n_steps = 4 * S; j.n_cg = n_cg;
+        j.operand_scale = operand_scale;
+        grid += n_cg * NG;
+        return TL_OK;
+    };
+    int rc;
+    if (ctx->split > 0 && (rc = add(ctx->m_u, 5, 2, H, ctx->split, SPLIT_H_SCALE, &ctx->xp_inner, &ctx->xs_inner)) != TL_OK) return rc;
+    if (ctx->spw_leaf > 0 && (rc = add(ctx->m_w_leaf, 3, 1, E, ctx->spw_leaf, 1.f, &ctx->xp_leaf, &ctx->xs_leaf)) != TL_OK) return rc;
+    if (grid == 0) return TL_OK;
+    hipLaunchKernelGGL(k_pack_split, dim3(grid), dim3(256), 0, st, pl);
     TL_HIP(hipGetLastError());
     return TL_OK;
 }
@@ -638,6 +649,8 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->sched_head);
     (void)hipFree(ctx->xp_inner);
     (void)hipFree(ctx->xs_inner);
+    (void)hipFree(ctx->xp_leaf);
+    (void)hipFree(ctx->xs_leaf);
     (void)hipFree(ctx->embb);
     (void)hipFree(ctx->wp_bwd_inner);
     (void)hipFree(ctx->wp_bwd_inner1);
@@ -735,10 +748,8 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             const int needed = round_up(ctx->es, 128) / 128;
             for (int sz : WSB_SIZES)
                 if (sz >= needed) { ctx->spw_leaf = sz; break; }
-        } else if (E % 4 == 0) {
-            const int needed = round_up(E, KC) / STEP_K / 4;
-            for (int sz : WS_SIZES)
-                if (sz >= needed) { ctx->spw_leaf = sz; break; }
+        } else if (round_up(E, 128) / 128 <= SPLIT_MAX_S) {
+            ctx->spw_leaf = round_up(E, 128) / 128;
         }
     }
     if (bf16 && ctx->spw_leaf > 0) {
@@ -899,11 +910,11 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     }
     if (ctx->spw_leaf > 0) {
         const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16);
-        const fwd_kernel lk = bf16 ? leaf_ws_bf_kernel(ctx->spw_leaf) : leaf_ws_kernel(ctx->spw_leaf);
-        if ((rc = allow_lds(lk, lds)) != TL_OK) return rc;
+        const void *lk = bf16 ? reinterpret_cast<const void *>(leaf_ws_bf_kernel(ctx->spw_leaf)) : reinterpret_cast<const void *>(leaf_split_kernel(ctx->spw_leaf));
+        TL_HIP(hipFuncSetAttribute(lk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         int o = 0;
-        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(lk), WG_THREADS, lds));
-        const int o_max = bf16 ? 4 : 2;      // fp32: bound by its instruction stream, a third workgroup brings nothing; bf16: by latency
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, lk, WG_THREADS, lds));
+        const int o_max = bf16 ? 4 : 2;      // bf16: bound by latency, gains from every workgroup
         if (o > o_max) o = o_max;
         ctx->leaf_grid = o * ctx->n_cu / ctx->n_cg * ctx->n_cg;
         if (ctx->leaf_grid < ctx->n_cg) ctx->spw_leaf = 0;
@@ -1025,6 +1036,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     f.cell = cfg.cell; f.H = cfg.hidden; f.E = cfg.embed_dim; f.vocab = cfg.vocab; f.n_cg = ctx->n_cg; f.bf16 = cfg.precision == TL_BF16_IN;
     f.emb = ctx->emb; f.embb = ctx->embb; f.es = ctx->es;
     f.leaf = ctx->g_leaf; f.inner = ctx->g_inner;
+    f.xl.wp = ctx->xp_leaf; f.xl.scale = ctx->xs_leaf; f.xl.w = ctx->m_w_leaf;
     if (static_ws) carve_workspace(ctx->scratch, TL_NOALLOC_MAX_NODES, TL_NOALLOC_MAX_NODES, &f);
     else carve_workspace(ctx->ws, ctx->cap_nodes, ctx->cap_trees, &f);
     ctx->gates_nodes = 0;
@@ -1177,14 +1189,17 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (prof) TL_HIP(hipEventRecord(ev[1], st));
 
     // ---- leaves ------------------------------------------------------------------------
-    if (flow && split > 0 && f.n_int > 0) {
-        Fwd g = f;
-        g.pick = flow_or_levels ? 1 : 0;
-        hipLaunchKernelGGL(k_flow_schedule, dim3(f.n_slots), dim3(WG_THREADS), SCHED_LDS_BYTES, st, g);
-    }
-    if (cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range) {          // (its cell addresses h and c with 32-bit offsets)
-        hipLaunchKernelGGL(bf16 ? leaf_ws_bf_kernel(ctx->spw_leaf) : leaf_ws_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid),
-                           dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16), st, f);
+    const int n_sched = flow && split > 0 && f.n_int > 0 ? f.n_slots : 0;      // workgroups that prepare the split cell's schedule
+    Fwd fl = f;
+    fl.pick = flow_or_levels ? 1 : 0;
+    const bool leaf_ws = cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range;      // (its cell addresses h and c with 32-bit offsets)
+    if (n_sched > 0 && !leaf_ws)
+        hipLaunchKernelGGL(k_flow_schedule, dim3(n_sched), dim3(WG_THREADS), SCHED_LDS_BYTES, st, fl);
+    if (leaf_ws && bf16) {
+        hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16), st, f);
+    } else if (leaf_ws) {
+        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16),
+                           st, fl, n_sched);
     } else if (cfg.cell == TL_TREELSTM) {
         const LevelPlan plan = plan_level(f.n_leaf, f.cap_tiles);
         hipLaunchKernelGGL(static_kernel(EPI_LSTM_LEAF, vec4_leaf, bf16), dim3(plan.n_tiles * ctx->n_cg), dim3(WG_THREADS),
