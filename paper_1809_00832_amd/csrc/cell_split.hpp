@@ -32,19 +32,27 @@ constexpr int SPLIT_MAX_S = 8;
 
 struct SplitSmem {
     float red[2][4 * MAX_GATES * 64 * 4];   // K-split partial sums, alternating per block: [wave][gate][lane][v]
+    float sum_of[MAX_GATES * HU * 2];       // scale and bias of every column (registers are short)
     int gave_up;
 };
 
 template <int NG, int S> struct SplitWeights {
     halfx8 hi[S][NG], lo[S][NG];
-    float bias[NG], scale[NG];
     bool plain;                                                 // some unit of the column group has a weight that is infinite
 };
 
-// k-steps [wave * S, (wave + 1) * S) of column group cg; the packed matrix has exactly 4 * S of them.
+// k-steps [wave * S, (wave + 1) * S) of column group cg; the packed matrix has exactly 4 * S of them.  sum_of: [gate][unit] {scale,
+// bias} in LDS.  Called by all threads; a barrier must be passed before the first use.
 template <int NG, int S>
-__device__ inline void split_load(SplitWeights<NG, S> &w, const SplitGemm &x, const Gemm &gm, int cg, int wave, int lane)
+__device__ inline void split_load(SplitWeights<NG, S> &w, float *sum_of, const SplitGemm &x, const Gemm &gm, int cg, int wave, int lane)
 {
+    const int t = wave * 64 + lane;
+    float scale = 0.f, bias = 0.f;                              // requested first: nothing is waited for but themselves
+    if (t < NG * HU) {
+        scale = x.scale[cg * NG * HU + t];
+        bias = gm.bp[cg * NG * HU + t];
+    }
+    __builtin_amdgcn_sched_barrier(0);
     const halfx8 *wp = reinterpret_cast<const halfx8 *>(x.wp) + ((size_t)cg * 4 * S + (size_t)wave * S) * NG * 2 * 64 + lane;
 #pragma unroll
     for (int s = 0; s < S; ++s)
@@ -53,14 +61,13 @@ __device__ inline void split_load(SplitWeights<NG, S> &w, const SplitGemm &x, co
             w.hi[s][g] = wp[(size_t)((s * NG + g) * 2) * 64];
             w.lo[s][g] = wp[(size_t)((s * NG + g) * 2 + 1) * 64];
         }
-#pragma unroll
-    for (int g = 0; g < NG; ++g) {
-        w.bias[g] = gm.bp[(cg * NG + g) * HU + (lane & 15)];
-        w.scale[g] = x.scale[(cg * NG + g) * HU + (lane & 15)];
+    if (t < NG * HU) {
+        sum_of[2 * t] = scale;
+        sum_of[2 * t + 1] = bias;
     }
     float scales = 0.f;
 #pragma unroll
-    for (int g = 0; g < NG; ++g) scales += w.scale[g];
+    for (int g = 0; g < NG; ++g) scales += x.scale[(cg * NG + g) * HU + (lane & 15)];
     w.plain = __ballot(__builtin_isnan(scales)) != 0ull;
     // With more weights than fit into the vector registers beside the rows in flight, say which of them live in the
     // accumulation registers (a matrix instruction reads either; see ws_load).
@@ -223,10 +230,11 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
         float gate[NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
+            const float *sb = &sm.sum_of[(g * HU + (lane & 15)) * 2];
             float p[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) p[k] = red[((k * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
-            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], w.scale[g], w.bias[g]);
+            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], sb[0], sb[1]);
         }
         if (e.x >= 0) {
             float cc = 0.f, hh = 0.f;
@@ -236,7 +244,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
                 if (__builtin_expect(w.plain, 0)) {
                     split_gates_plain<NG>(f, f.xi, e.y, e.z, hu, gate);
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) gate[g] += w.bias[g];
+                    for (int g = 0; g < NG; ++g) gate[g] += sm.sum_of[(g * HU + (lane & 15)) * 2 + 1];
                 }
                 lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, e.x, hu), H);
             }
@@ -272,6 +280,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 struct SplitLeafSmem {
     static constexpr int NG = 3;
     float red[2][4 * NG * 64 * 4];
+    float sum_of[NG * HU * 2];
     float row_scale[4][16];
 };
 
@@ -282,8 +291,8 @@ __device__ inline float max_across_quarters(float m)
     return fmaxf(m, __shfl_xor(m, 32));
 }
 
-// Leaves [lo, hi) of the leaf list for column group cg; every workgroup keeps its slice of W_leaf.
-template <int S>
+// Leaves [lo, hi) of the leaf list for column group cg; every workgroup keeps its slice of W_leaf.  (Stores: see split_run.)
+template <int S, bool KEEP>
 __device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int hi, int cg, const SplitWeights<3, S> &w)
 {
     constexpr int NG = 3;
@@ -299,7 +308,7 @@ __device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int
     const bool whole = (wave + 1) * S * 32 <= E;                // no step of this wave reaches beyond the row
     uintx4_t rows[S][2];
     auto request = [&](int word) {
-        const unsigned base = (unsigned)word * emb_row_b;
+        const unsigned base = __umul24((unsigned)word, emb_row_b);
 #pragma unroll
         for (int s = 0; s < S; ++s)
 #pragma unroll
@@ -361,34 +370,34 @@ __device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int
         float gate[NG];
 #pragma unroll
         for (int g = 0; g < NG; ++g) {
+            const float *sb = &sm.sum_of[(g * HU + (lane & 15)) * 2];
             float p[4];
 #pragma unroll
             for (int k = 0; k < 4; ++k) p[k] = red[((k * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
-            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], w.scale[g], w.bias[g]);
+            gate[g] = __builtin_fmaf(((p[0] + p[1]) + p[2]) + p[3], sb[0], sb[1]);
         }
-        if (lo + b * 16 + fin_row < hi) {
-            float cc = 0.f, hh = 0.f;
-            if (hu_ok) {
-                if (__builtin_expect(__builtin_isnan(gate[0] + gate[1] + gate[2]), 0)) {
-                    const float *xr = f.emb + (size_t)f.word[node] * E;
+        if (__builtin_expect(__ballot(__builtin_isnan(gate[0] + gate[1] + gate[2])) != 0ull, 0)) {
+            if (__builtin_isnan(gate[0] + gate[1] + gate[2])) {
+                const float *xr = f.emb + (size_t)f.word[node] * E, *wr = f.xl.w + (hu_ok ? hu : 0);
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) gate[g] = 0.f;
-                    for (int k = 0; k < E; ++k)
+                for (int g = 0; g < NG; ++g) gate[g] = 0.f;
+                for (int k = 0; k < E; ++k)
 #pragma unroll
-                        for (int g = 0; g < NG; ++g) gate[g] = __builtin_fmaf(xr[k], f.xl.w[(size_t)k * (NG * H) + (size_t)g * H + hu], gate[g]);
+                    for (int g = 0; g < NG; ++g) gate[g] = __builtin_fmaf(xr[k], wr[(size_t)k * (NG * H) + (size_t)g * H], gate[g]);
 #pragma unroll
-                    for (int g = 0; g < NG; ++g) gate[g] += w.bias[g];
-                }
-                lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, kept_gates(f, node, hu), H);
-                const unsigned o = (unsigned)node * row_b + hu_b;
-                buf_st_f<false>(rs_c, o, cc);
-                buf_st_f<false>(rs_h, o, hh);
+                for (int g = 0; g < NG; ++g) gate[g] += sm.sum_of[(g * HU + (lane & 15)) * 2 + 1];
             }
-            if (f.hx) {
-                const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
-                if ((hu & ~1) < H) buf_st_f<false>(rs_x, (unsigned)node * hx_row_b + split_word_off(hu), __uint_as_float(word));
-            }
+            __builtin_amdgcn_s_waitcnt(0);
         }
+        const bool here = lo + b * 16 + fin_row < hi, ok = here && hu_ok;
+        float cc, hh;
+        lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, KEEP ? (ok ? f.gates + (size_t)node * (5 * H) + hu : f.sink + (lane & 15)) : nullptr, H);
+        const unsigned o = ok ? __umul24((unsigned)node, row_b) + hu_b : ~0u;
+        const unsigned word = split_word(hu_ok ? hh * SPLIT_H_SCALE : 0.f, hu);
+        buf_st_f<false>(rs_c, o, cc);
+        buf_st_f<false>(rs_h, o, hh);
+        // (without a split copy its table has no bytes and the store is dropped)
+        buf_st_f<false>(rs_x, here && (hu & ~1) < H ? __umul24((unsigned)node, hx_row_b) + split_word_off(hu) : ~0u, __uint_as_float(word));
         node0 = node1;
         node1 = node2;
         node2 = node3;

@@ -130,6 +130,7 @@ struct Fwd {
     SplitGemm xi, xl;           // inner and leaf weights for the split cells
     unsigned *hx;               // split copy of h that the split cell gathers from (cell_split.hpp), hx_steps lines of 128 bytes a row; else null
     int hx_steps;
+    float *sink;                // [5H + 16]: where lanes without a node put the gate activations they do not have
     // workspace
     int32_t *parent, *pending, *leaf_list, *root_ws;
     int32_t *height, *arrive, *level_cnt, *level_off, *level_fill, *level_nodes;

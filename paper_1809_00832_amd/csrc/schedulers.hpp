@@ -48,7 +48,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_tiles_static(Fwd f, const int
 // fp32 leaves: the leaf matrix is small (E x 3H), so every workgroup keeps its column group's slice and walks a contiguous
 // share of the leaf list.  Under the data-flow scheduler with the split cell the first n_sched workgroups prepare the schedule of
 // the internal nodes instead, beside the leaves' cells.
-template <int S>
+template <int S, bool KEEP>
 __global__ __launch_bounds__(WG_THREADS, S <= 4 ? 2 : 1) void k_leaf_split(Fwd f, int n_sched)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -59,15 +59,16 @@ __global__ __launch_bounds__(WG_THREADS, S <= 4 ? 2 : 1) void k_leaf_split(Fwd f
     SplitLeafSmem &sm = *reinterpret_cast<SplitLeafSmem *>(smem_raw);
     if (batch_rejected(f)) return;
     const int tid = threadIdx.x, wg = blockIdx.x - n_sched, n_wg = gridDim.x - n_sched;
-    // (data-flow scheduler: the stores that mark the internal nodes' rows go out first and complete beside the cells)
-    if (f.flow == 2) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
     const int cg = gang_cg(wg % f.n_cg, f.n_cg, f.n_cg);
     const int slot = wg / f.n_cg, n_slots = n_wg / f.n_cg;
     SplitWeights<EpiTraits<EPI_LSTM_LEAF>::NG, S> w;
-    split_load(w, f.xl, f.leaf, cg, tid >> 6, tid & 63);
+    split_load(w, sm.sum_of, f.xl, f.leaf, cg, tid >> 6, tid & 63);
     const int share = ((f.n_leaf + n_slots - 1) / n_slots + 15) & ~15;
     const int lo = slot * share, hi = min(f.n_leaf, lo + share);
-    split_leaves<S>(sm, f, lo, hi, cg, w);
+    __syncthreads();
+    split_leaves<S, KEEP>(sm, f, lo, hi, cg, w);
+    // data-flow scheduler: the stores that mark the internal nodes' rows (last: a load behind them would wait for them)
+    if (f.flow == 2) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
 }
 
 // Leaves with bf16 operands (weight-stationary cell): rows come from a bf16 copy of the embedding table (rows padded with
@@ -719,7 +720,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
     split_place(f, &slot, &member);
     if (tid == 0) sm.gave_up = 0;
     SplitWeights<EpiTraits<EPI_LSTM_INNER>::NG, S> w;
-    split_load(w, f.xi, f.inner, member, tid >> 6, tid & 63);
+    split_load(w, sm.sum_of, f.xi, f.inner, member, tid >> 6, tid & 63);
     const int4 head = f.sched_head[slot];
     if (f.flow_roots) {                           // trees of one node: the leaf is the root
         const int hu = member * HU + (tid & 15);

@@ -60,8 +60,12 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
     const bool quad = (H & 3) == 0 && (((uintptr_t)f.h | (uintptr_t)f.c) & 15) == 0;
     const float ones = __uint_as_float(0xFFFFFFFFu);
     const floatx4 ones4 = floatx4{ones, ones, ones, ones};
-    for (size_t n = wave; n < (size_t)f.n_nodes; n += n_waves) {
-        if (f.left[n] < 0) continue;
+    // the kinds of up to 64 nodes in one load, then their rows one after the other (a load per row would make every row a round trip)
+    const size_t share = (f.n_nodes + n_waves - 1) / n_waves, chunk = share < 64 ? share : 64;
+    for (size_t n0 = wave * chunk; n0 < (size_t)f.n_nodes; n0 += n_waves * chunk)
+    for (unsigned long long todo = __ballot((size_t)lane < chunk && n0 + lane < (size_t)f.n_nodes && f.left[min(n0 + lane, (size_t)f.n_nodes - 1)] >= 0);
+         todo != 0ull; todo &= todo - 1ull) {
+        const size_t n = n0 + __builtin_ctzll(todo);
         float *c = f.c ? f.c + n * H : nullptr, *h = f.hb || f.hx ? nullptr : f.h + n * H;
         if (quad) {
             for (int e = lane * 4; e < H; e += 256) {
@@ -393,7 +397,7 @@ __global__ void k_root_gather(Fwd f)
 // (0.2 us each), the lists of a slot in LDS (5 bytes per node) or, for slots of more nodes than fit, in the workspace.
 constexpr unsigned SCHED_LATE = 0x80000000u;
 constexpr size_t SCHED_LDS_BYTES = 52 * 1024;     // three workgroups of the kernel that does it beside its own work fit on a CU
-__host__ __device__ constexpr size_t sched_lds_bytes(size_t n) { return 16 + ((2 * n + 3) & ~(size_t)3) + ((n + 3) & ~(size_t)3) + 2 * (2 * (n / 2 + 1) + 2); }
+__host__ __device__ constexpr size_t sched_lds_bytes(size_t n) { return 16 + 64 + ((2 * n + 3) & ~(size_t)3) + ((n + 3) & ~(size_t)3) + 2 * (2 * (n / 2 + 1) + 2); }
 
 template <bool IN_LDS> struct SchedLists;
 template <> struct SchedLists<true> {
@@ -474,14 +478,17 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
 {
     const int tid = threadIdx.x, lane = tid & 63, n = ne - nb, first = (nb - t_lo) / 2;
     const int cap = (n - (t_hi - t_lo)) / 2;      // internal nodes (full binary trees)
-    int *s_ctl = reinterpret_cast<int *>(lds);    // seeds | roots, later nodes handed out | blocks | a tree of one node exists
+    int *s_ctl = reinterpret_cast<int *>(lds);    // - | roots, later nodes handed out | blocks | a tree of one node exists
     SchedLists<IN_LDS> q;
-    q.carve(f, lds + 16, n, nb, first);
+    constexpr int Q = 4;
+    int *s_cnt = s_ctl + 4;                       // seeds of a pass, [Q][waves]
+    q.carve(f, lds + 16 + 4 * Q * 4, n, nb, first);
     if (tid < 4) s_ctl[tid] = 0;
     __syncthreads();
-    constexpr int Q = 4;
+    int n_seeds = 0;
     for (int base = 0; base < n; base += WG_THREADS * Q) {
         int l[Q], up[Q], pend[Q];
+        unsigned seeds = 0u;
 #pragma unroll
         for (int j = 0; j < Q; ++j) {
             const int i = min(base + j * WG_THREADS + tid, n - 1);
@@ -495,11 +502,9 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
             const bool here = i < n;
             if (here) q.set_node(i, up[j] < 0 ? -1 : up[j] - nb, pend[j]);
             const bool seed = here && l[j] >= 0 && pend[j] == 0;
+            seeds |= (seed ? 1u : 0u) << j;
             const unsigned long long m = __ballot(seed);
-            int pos = 0;
-            if (m != 0ull && lane == __builtin_ctzll(m)) pos = atomicAdd(&s_ctl[0], __popcll(m));
-            if (m != 0ull) pos = __shfl(pos, __builtin_ctzll(m)) + __popcll(m & ((1ull << lane) - 1ull));
-            if (seed && pos < cap) q.list(pos, i);
+            if (lane == 0) s_cnt[j * 4 + (tid >> 6)] = __popcll(m);
             if (f.flow_roots && here && up[j] < 0) {
                 // a root: one per tree (a second one of a tree is found here, a missing one by the count)
                 atomicAdd(&s_ctl[1], 1);
@@ -510,21 +515,56 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
                 if (atomicCAS(&f.root_ws[t], -1, nb + i) != -1) latch_error(f.ctl, TL_ESTRUCT);
             }
         }
+        __syncthreads();
+        // in node order, so that the schedule is the same every time
+#pragma unroll
+        for (int j = 0; j < Q; ++j) {
+            const unsigned long long m = __ballot(seeds >> j & 1u);
+            int pos = n_seeds + __popcll(m & ((1ull << lane) - 1ull));
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = s_cnt[j * 4 + k];
+                if (k < (tid >> 6)) pos += c;
+                n_seeds += c;
+            }
+            if ((seeds >> j & 1u) && pos < cap) q.list(pos, base + j * WG_THREADS + tid);
+        }
+        __syncthreads();
     }
     wait_mem();
     __syncthreads();
     if (tid < 64) {
-        int head = 0, tail = min(s_ctl[0], cap), blocks = 0, rounds = 0;
+        int head = 0, tail = min(n_seeds, cap), blocks = 0, rounds = 0;
         int fresh = cap;                          // list positions from here on became ready in the round before
+        // hands out this lane's node: does its parent p become ready with it (said by one of two siblings)?
+        auto hand_out = [&](int p) {
+            bool ready = false;
+            int old = 0;
+            if (p >= 0) {
+                old = q.count_down(p);
+                ready = old == 1;
+            }
+            if constexpr (!IN_LDS) {
+                // Siblings handed out together: which of them memory counts second is not fixed, the higher lane lists the parent.
+                // (In LDS the lanes of one instruction are served in order.)
+                unsigned long long first_of_two = __ballot(old == 2);
+                while (first_of_two != 0ull) {
+                    const int k = __builtin_ctzll(first_of_two);
+                    first_of_two &= first_of_two - 1ull;
+                    const unsigned long long pair = __ballot(p >= 0 && p == __shfl(p, k));
+                    if (__popcll(pair) == 2 && (pair >> lane & 1ull)) ready = lane == 63 - __builtin_clzll(pair);
+                }
+            }
+            return ready;
+        };
         while (head < tail) {
             int take = min(tail - head, 64);
             if (take > 16) take &= ~15;
             const bool mine = lane < take;
             int p = -1;
             if (mine) p = q.parent(q.node(head + lane));
-            bool ready = false;
-            if (p >= 0) ready = q.count_down(p) == 1;
-            const unsigned long long m = __ballot(ready);
+            bool ready = hand_out(p);
+            unsigned long long m = __ballot(ready);
             const int pos = tail + __popcll(m & ((1ull << lane) - 1ull));
             if (ready && pos < cap) q.list(pos, p);
             if (lane * 16 < take) q.block(blocks + lane, head + lane * 16, lane == 0 && head + min(take, 16) > fresh);
@@ -533,6 +573,26 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
             head += take;
             tail = min(tail + __popcll(m), cap);
             rounds += 1;
+            if (head == fresh && __popcll(m) <= 16) {
+                // Nothing waits but the few nodes that this round made ready: the rounds of a deep tree.  They stay in the lanes
+                // that found them, and a node's parent is looked up beside the count that makes the node ready: a round is one
+                // LDS access deep.
+                int up = ready ? q.parent(p) : -1;
+                while (m != 0ull && __popcll(m) <= 16 && head < tail) {
+                    if (lane == 0) q.block(blocks, head, true);
+                    const int above = up >= 0 ? q.parent(up) : -1;
+                    ready = hand_out(up);
+                    m = __ballot(ready);
+                    const int at = tail + __popcll(m & ((1ull << lane) - 1ull));
+                    if (ready && at < cap) q.list(at, up);
+                    fresh = tail;
+                    blocks += 1;
+                    head = tail;
+                    tail = min(tail + __popcll(m), cap);
+                    rounds += 1;
+                    up = ready ? above : -1;
+                }
+            }
             q.settle();
         }
         if (lane == 0) {

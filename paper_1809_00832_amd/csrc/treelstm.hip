@@ -253,19 +253,20 @@ fwd_kernel levels_kernel(int cell, bool vec4, int spw, bool bf16)
     return cell == TL_TREELSTM ? levels_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16) : levels_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
 }
 typedef void (*leaf_kernel)(Fwd, int);
-leaf_kernel leaf_split_kernel(int s)
+template <bool KEEP> leaf_kernel leaf_split_kernel_k(int s)
 {
     switch (s) {
-    case 1: return k_leaf_split<1>;
-    case 2: return k_leaf_split<2>;
-    case 3: return k_leaf_split<3>;
-    case 4: return k_leaf_split<4>;
-    case 5: return k_leaf_split<5>;
-    case 6: return k_leaf_split<6>;
-    case 7: return k_leaf_split<7>;
-    default: return k_leaf_split<8>;
+    case 1: return k_leaf_split<1, KEEP>;
+    case 2: return k_leaf_split<2, KEEP>;
+    case 3: return k_leaf_split<3, KEEP>;
+    case 4: return k_leaf_split<4, KEEP>;
+    case 5: return k_leaf_split<5, KEEP>;
+    case 6: return k_leaf_split<6, KEEP>;
+    case 7: return k_leaf_split<7, KEEP>;
+    default: return k_leaf_split<8, KEEP>;
     }
 }
+leaf_kernel leaf_split_kernel(int s, bool keep) { return keep ? leaf_split_kernel_k<true>(s) : leaf_split_kernel_k<false>(s); }
 fwd_kernel leaf_ws_bf_kernel(int s)
 {
     switch (s) {
@@ -910,12 +911,14 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     }
     if (ctx->spw_leaf > 0) {
         const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16);
-        const void *lk = bf16 ? reinterpret_cast<const void *>(leaf_ws_bf_kernel(ctx->spw_leaf)) : reinterpret_cast<const void *>(leaf_split_kernel(ctx->spw_leaf));
-        TL_HIP(hipFuncSetAttribute(lk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        int o = 0;
-        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, lk, WG_THREADS, lds));
-        const int o_max = bf16 ? 4 : 2;      // bf16: bound by latency, gains from every workgroup
-        if (o > o_max) o = o_max;
+        int o = bf16 ? 4 : 2;                // bf16: bound by latency, gains from every workgroup
+        for (int v = 0; v < 2; ++v) {        // fp32: without and with gate activations kept
+            const void *lk = bf16 ? reinterpret_cast<const void *>(leaf_ws_bf_kernel(ctx->spw_leaf)) : reinterpret_cast<const void *>(leaf_split_kernel(ctx->spw_leaf, v != 0));
+            int o1 = 0;
+            TL_HIP(hipFuncSetAttribute(lk, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+            TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, lk, WG_THREADS, lds));
+            if (o1 < o) o = o1;
+        }
         ctx->leaf_grid = o * ctx->n_cu / ctx->n_cg * ctx->n_cg;
         if (ctx->leaf_grid < ctx->n_cg) ctx->spw_leaf = 0;
     }
@@ -1045,10 +1048,11 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
             TL_HIP(hipDeviceSynchronize());
             if (ctx->gates) { TL_HIP(hipFree(ctx->gates)); ctx->gates = nullptr; }
             ctx->gates_cap = 0;
-            TL_HIP(hipMalloc(&ctx->gates, (size_t)ctx->cap_nodes * 5 * cfg.hidden * sizeof(float)));
+            TL_HIP(hipMalloc(&ctx->gates, ((size_t)(ctx->cap_nodes + 1) * 5 * cfg.hidden + HU) * sizeof(float)));      // (one row more: the sink)
             ctx->gates_cap = ctx->cap_nodes;
         }
         f.gates = ctx->gates;
+        f.sink = ctx->gates + (size_t)ctx->gates_cap * 5 * cfg.hidden;
         ctx->gates_nodes = n_nodes;
         ctx->gates_h = h;
     }
@@ -1198,7 +1202,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (leaf_ws && bf16) {
         hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16), st, f);
     } else if (leaf_ws) {
-        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16),
+        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf, f.gates != nullptr), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16),
                            st, fl, n_sched);
     } else if (cfg.cell == TL_TREELSTM) {
         const LevelPlan plan = plan_level(f.n_leaf, f.cap_tiles);
