@@ -296,133 +296,136 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 // Weight gradient: out[k][j] += sum_q a_q[k] * dg[q][j] over the n_rows nodes of `list` (dg rows by
 // list position), a_q = [h[left]; h[right]] (SEG 2, L = H) or the embedding row of the leaf's
 // word (SEG 1, L = E).  K_out = SEG * L rows, n_cols columns, row-major; `out` is zero beforehand.
-// One workgroup per 64 x 64 tile of the output and slice of the nodes (blockIdx.z; the slices'
+// One workgroup per 128 x 128 tile of the output and slice of the nodes (blockIdx.z; the slices'
 // partial tiles are added with atomics: the node axis is long and the output small, so without
 // slices there are too few workgroups to hide the latency of the gathers), wave w on the
-// 32 x 32 quarter (w / 2, w % 2).  The contraction runs over the nodes, 16 at a time through LDS,
-// on v_mfma_f32_16x16x4_f32 with the node index as the k of the instruction; the next 16 nodes'
-// operands are requested into registers before the current ones are multiplied.
-constexpr int WG_TILE = 64, WG_Q = 16, WG_LD = WG_TILE + 4;
+// 64 x 64 quarter (w / 2, w % 2).
+// The contraction runs over the nodes on the 16-bit matrix unit with fp32 operands: a value is the sum of three bf16 terms
+// (8 bits each and the range of fp32, so gradients of any magnitude need no scaling), and of the nine products the six
+// that reach 2^-24 of the whole are taken, accumulated in fp32: 6/16 of the fp32 instruction's time, beside which vector
+// instructions run.  (An infinity has no such terms: where a sum was infinite it comes out as NaN.)
+// A thread loads one column of 16 of a step's 32 nodes (a wave: 256 consecutive bytes a row), splits them and parks each term's
+// eight neighbours as the 16 bytes that are an operand of v_mfma_f32_16x16x32_bf16; the next 32 nodes' values are
+// requested before the current ones are multiplied.  Bound by the reads of the rows, each of which goes to every
+// tile: hence the tile of 128 (64 x 64 tiles with fp32 instructions took 371 us for U at H = 512 and 6 658 nodes).
+constexpr int WG_TILE = 128, WG_Q = 32, WG_LD = WG_Q + 8, WG_SRC = 512;
+struct WgSmem {
+    unsigned short a[3][WG_TILE][WG_LD], b[3][WG_TILE][WG_LD];      // [term][column][node]
+    int src[2][WG_SRC];                                             // source rows of the slice's next nodes
+};
 
-template <int SEG, bool VEC4>
-__global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
-                                                     const float *__restrict__ table, int L, const float *__restrict__ dg,
-                                                     int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+// Eight values as three vectors of bf16 terms, parked as [term][.. 8 neighbours ..].
+__device__ inline void wg_park(unsigned short (*dst)[WG_TILE][WG_LD], int col, int q, const float *x)
 {
-    __shared__ __align__(16) float as[2][WG_Q][WG_LD];         // two buffers each: a step's operands are parked while the
-    __shared__ __align__(16) float bs[2][WG_Q][WG_LD];         // step before is still being multiplied (one barrier per step)
+    bf16x8 hi, mid, lo;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        hi[i] = (__bf16)x[i];
+        const float r = x[i] - (float)hi[i];
+        mid[i] = (__bf16)r;
+        lo[i] = (__bf16)(r - (float)mid[i]);
+    }
+    *reinterpret_cast<bf16x8 *>(&dst[0][col][q]) = hi;
+    *reinterpret_cast<bf16x8 *>(&dst[1][col][q]) = mid;
+    *reinterpret_cast<bf16x8 *>(&dst[2][col][q]) = lo;
+}
+
+template <int SEG>
+__global__ __launch_bounds__(256, 2) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
+                                                        const float *__restrict__ table, int L, const float *__restrict__ dg,
+                                                        int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+{
+    __shared__ __align__(16) WgSmem sm;
+    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * WG_TILE, j0 = blockIdx.y * WG_TILE;
     const int K_out = SEG * L;
-    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+    const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
     const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WG_Q - 1) / WG_Q * WG_Q;
     const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
     if (q_lo >= q_hi) return;
-    floatx4 acc[2][2];
+    floatx4 acc[4][4];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
-    const int lq = tid >> 4, lk = (tid & 15) * 4;             // this thread stages 4 consecutive columns of row lq
-    float ra[4], rb[4];
+        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // this thread stages column `col` of nodes half, half + 1, ... half + 15 of a step; columns beyond the matrix repeat its last one
+    // (their results are not stored)
+    const int col = tid & (WG_TILE - 1), half = (tid >> 7) * 16;
+    const int k = min(k0 + col, K_out - 1), j = min(j0 + col, n_cols - 1);
+    const int seg = (SEG == 2 && k >= L) ? 1 : 0, k_in = k - seg * L;
+    float ra[16], rb[16];
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
     const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
-    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
-    // The operands of a step (16 nodes) hang on a chain of three loads: the node from the list, its source rows from
-    // the child (or word) arrays, the data from those rows.  A step has only 16 MFMAs per wave to hide it, so the chain
-    // is spread over three steps: step i requests the data of step i + 1, the source rows of step i + 2 and the node
-    // of step i + 3, each from what the step before has requested.
-    auto node_of = [&](int q0) {                              // stage 1
-        const int q = q0 + lq;
-        return q < q_hi ? list[q] : -1;
-    };
-    auto sources_of = [&](int node, int *s0, int *s1) {       // stage 2
-        *s0 = *s1 = 0;
-        if (node >= 0) {
-            if (SEG == 2) { *s0 = f.left[node]; *s1 = f.right[node]; } else { *s0 = f.word[node]; }
+    float bsum = 0.f;
+    auto request = [&](int q0, int chunk) {                   // operands of nodes q0 ... q0 + 31 into registers
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int q = q0 + half + i;
+            const bool live = q < q_hi;
+            const int src = sm.src[seg][min(q, q_hi - 1) - chunk];
+            ra[i] = live ? table[(size_t)src * L + k_in] : 0.f;
+            rb[i] = live ? dg[(size_t)q * n_cols + j] : 0.f;
         }
     };
-    auto request = [&](int q0, int node, int s0, int s1) {    // stage 3: operands of nodes q0 .. q0 + 15 into registers
-        const int q = q0 + lq;
-        const bool live = node >= 0;
-        if constexpr (VEC4) {      // L and n_cols multiples of 4, rows 16-byte aligned: 4 consecutive columns never leave a segment
-            const int k = k0 + lk, j = j0 + lk;
-            const int seg = (SEG == 2 && k >= L) ? 1 : 0;
-            floatx4 a = floatx4{0.f, 0.f, 0.f, 0.f}, b = a;
-            if (live && k < K_out) a = *reinterpret_cast<const floatx4 *>(table + (size_t)(seg ? s1 : s0) * L + (k - seg * L));
-            if (live && j < n_cols) b = *reinterpret_cast<const floatx4 *>(dg + (size_t)q * n_cols + j);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) { ra[e] = a[e]; rb[e] = b[e]; }
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                const int k = k0 + lk + e, j = j0 + lk + e;
-                const int seg = (SEG == 2 && k >= L) ? 1 : 0;
-                ra[e] = (live && k < K_out) ? table[(size_t)(seg ? s1 : s0) * L + (k - seg * L)] : 0.f;
-                rb[e] = (live && j < n_cols) ? dg[(size_t)q * n_cols + j] : 0.f;
+    for (int chunk = q_lo; chunk < q_hi; chunk += WG_SRC) {
+        const int end = min(q_hi, chunk + WG_SRC);
+        for (int i = tid; i < end - chunk; i += 256) {
+            const int node = list[chunk + i];
+            if (SEG == 2) {
+                sm.src[0][i] = f.left[node];
+                sm.src[1][i] = f.right[node];
+            } else {
+                sm.src[0][i] = f.word[node];
             }
         }
-    };
-    int node1 = node_of(q_lo), s0_1, s1_1;                    // step q_lo: all three stages at once
-    sources_of(node1, &s0_1, &s1_1);
-    request(q_lo, node1, s0_1, s1_1);
-    node1 = node_of(q_lo + WG_Q);                             // step q_lo + 16: node and source rows
-    sources_of(node1, &s0_1, &s1_1);
-    int node2 = node_of(q_lo + 2 * WG_Q);                     // step q_lo + 32: node
-    auto park = [&](int buf) {
-        *reinterpret_cast<floatx4 *>(&as[buf][lq][lk]) = floatx4{ra[0], ra[1], ra[2], ra[3]};
-        *reinterpret_cast<floatx4 *>(&bs[buf][lq][lk]) = floatx4{rb[0], rb[1], rb[2], rb[3]};
-        if (with_bias) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) bsum[e] += rb[e];
-        }
-    };
-    park(0);
-    __syncthreads();
-    int buf = 0;
-    for (int q0 = q_lo; q0 < q_hi; q0 += WG_Q) {
-        request(q0 + WG_Q, node1, s0_1, s1_1);                // (beyond the end: node -1, nothing is loaded)
-        node1 = node2;
-        sources_of(node1, &s0_1, &s1_1);
-        node2 = node_of(q0 + 3 * WG_Q);
-#pragma unroll
-        for (int kk = 0; kk < WG_Q / 4; ++kk) {
-            const int qq = kk * 4 + (lane >> 4);
-            float a[2], b[2];
-#pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = as[buf][qq][wr + t * 16 + (lane & 15)];
-                b[t] = bs[buf][qq][wc + t * 16 + (lane & 15)];
-            }
-#pragma unroll
-            for (int ta = 0; ta < 2; ++ta)
-#pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
-                    acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
-        }
-        // the other buffer was read in the step before this one, and every wave has passed the barrier since
-        if (q0 + WG_Q < q_hi) park(buf ^ 1);
         __syncthreads();
-        buf ^= 1;
+        request(chunk, chunk);
+        for (int q0 = chunk; q0 < end; q0 += WG_Q) {
+            wg_park(sm.a, col, half, ra);
+            wg_park(sm.a, col, half + 8, ra + 8);
+            wg_park(sm.b, col, half, rb);
+            wg_park(sm.b, col, half + 8, rb + 8);
+            if (with_bias) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) bsum += rb[i];
+            }
+            __syncthreads();
+            if (q0 + WG_Q < end) request(q0 + WG_Q, chunk);
+            bf16x8 vb[4][3];
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+#pragma unroll
+                for (int m = 0; m < 3; ++m) vb[t][m] = *reinterpret_cast<const bf16x8 *>(&sm.b[m][wc + t * 16 + (lane & 15)][8 * (lane >> 4)]);
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) {
+                bf16x8 va[3];
+#pragma unroll
+                for (int m = 0; m < 3; ++m) va[m] = *reinterpret_cast<const bf16x8 *>(&sm.a[m][wr + ta * 16 + (lane & 15)][8 * (lane >> 4)]);
+                constexpr int TERM[6][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};       // smallest first
+#pragma unroll
+                for (int p = 0; p < 6; ++p)
+#pragma unroll
+                    for (int tb = 0; tb < 4; ++tb)
+                        acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+            }
+            __syncthreads();
+        }
     }
 #pragma unroll
-    for (int ta = 0; ta < 2; ++ta)
+    for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb)
+        for (int tb = 0; tb < 4; ++tb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int k = k0 + wr + ta * 16 + (lane >> 4) * 4 + v, j = j0 + wc + tb * 16 + (lane & 15);
-                if (k < K_out && j < n_cols) atomicAdd(&out[(size_t)k * n_cols + j], acc[ta][tb][v]);
+                const int ko = k0 + wr + ta * 16 + (lane >> 4) * 4 + v, jo = j0 + wc + tb * 16 + (lane & 15);
+                if (ko < K_out && jo < n_cols) atomicAdd(&out[(size_t)ko * n_cols + jo], acc[ta][tb][v]);
             }
     if (with_bias) {                                          // uniform per workgroup; the loop ended with a barrier
-        *reinterpret_cast<floatx4 *>(&bs[0][lq][lk]) = floatx4{bsum[0], bsum[1], bsum[2], bsum[3]};
+        float *part = reinterpret_cast<float *>(sm.src[0]);
+        if (tid >= WG_TILE) part[col] = bsum;
         __syncthreads();
-        if (tid < WG_TILE && j0 + tid < n_cols) {
-            float t = 0.f;
-#pragma unroll
-            for (int q = 0; q < WG_Q; ++q) t += bs[0][q][tid];
-            atomicAdd(&bias_out[j0 + tid], t);
-        }
+        if (tid < WG_TILE && j0 + col < n_cols) atomicAdd(&bias_out[j0 + col], bsum + part[col]);
     }
 }
 

@@ -145,7 +145,6 @@ inline int round_up(int x, int m) { return (x + m - 1) / m * m; }
 
 typedef void (*fwd_kernel)(Fwd);
 typedef void (*tiles_kernel)(Fwd, const int32_t *, int, LevelPlan);
-typedef void (*wgrad_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, float *, float *);
 
 // Steps per wave that the weight-stationary cell is instantiated for; 0 = streaming cell.
 const int WS_SIZES[] = {1, 2, 4, 5, 8, 16};
@@ -1534,17 +1533,15 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // weight and bias gradients: contractions over all nodes, the node axis cut into slices so that a few
     // thousand workgroups are in flight
     auto slices = [&](int tiles, int rows) {
-        int z = (8 * ctx->n_cu + tiles - 1) / tiles;
-        const int max_z = (rows + 4 * WG_Q - 1) / (4 * WG_Q);
+        int z = (4 * ctx->n_cu + tiles - 1) / tiles;          // two workgroups per CU at a time
+        const int max_z = (rows + 2 * WG_Q - 1) / (2 * WG_Q);
         if (z > max_z) z = max_z;
         return z < 1 ? 1 : z;
     };
     if (n_int > 0) {
         const dim3 grid((2 * H + WG_TILE - 1) / WG_TILE, (dg_cols + WG_TILE - 1) / WG_TILE, 1);
-        const bool v4 = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0);
-        const wgrad_kernel wk = v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>);
         float *acc = rntn ? ctx->rntn_acc : d_u, *colsum = rntn ? ctx->rntn_acc + (size_t)2 * H * rntn_row : d_b;
-        hipLaunchKernelGGL(wk, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_int)), dim3(256), 0, st, f,
+        hipLaunchKernelGGL(k_weight_grad<2>, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_int)), dim3(256), 0, st, f,
                            (const int32_t *)f.level_nodes, n_int, (const float *)h, H, (const float *)dg_int, dg_cols, acc, colsum);
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
@@ -1552,9 +1549,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
                            (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H);
     if (lstm) {
         const dim3 grid((E + WG_TILE - 1) / WG_TILE, (3 * H + WG_TILE - 1) / WG_TILE, 1);
-        const bool v4 = E % 4 == 0 && H % 4 == 0;
-        const wgrad_kernel wk = v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>);
-        hipLaunchKernelGGL(wk, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_leaf)), dim3(256), 0, st, f,
+        hipLaunchKernelGGL(k_weight_grad<1>, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_leaf)), dim3(256), 0, st, f,
                            (const int32_t *)f.leaf_list, n_leaf, (const float *)ctx->emb, E, (const float *)dg_leaf, 3 * H, d_w_leaf,
                            d_b_leaf);
     }
