@@ -122,8 +122,8 @@ __global__ void k_pack_many(PackList pl)
 // The two fp16 terms of a matrix for the split cell (cell_split.hpp): [column group][k-step of 32][gate][hi, lo][lane][8].
 // The K axis is SEG segments of `steps` k-steps (L rows, zero padded), then zeros up to n_steps k-steps.  Every column is
 // scaled by the power of two that brings its largest magnitude into [2^13, 2^14) (exponents beyond what fp32 can undo are cut
-// off); `scale` receives what a sum of products is to be multiplied by (NaN: the column holds an infinity, which has no two terms).  One workgroup per column group and gate: it looks
-// for the largest magnitudes of its 16 columns first, then packs them.
+// off); `scale` receives what a sum of products is to be multiplied by (NaN: the column holds an infinity, which has no two terms).  One workgroup per column group and gate holds
+// its 16 columns in registers, looks for their largest magnitudes and packs them.
 struct SplitPackJob {
     const float *w;
     _Float16 *wp;
@@ -131,7 +131,7 @@ struct SplitPackJob {
     int NG, H, SEG, L, steps, n_steps, n_cg;
     float operand_scale;    // of the other side
 };
-constexpr int SPLIT_PACK_JOBS = 2;
+constexpr int SPLIT_PACK_JOBS = 2, SPLIT_PACK_T = 8;      // n_steps <= 4 * SPLIT_PACK_T
 struct SplitPackList {
     SplitPackJob job[SPLIT_PACK_JOBS];
     int n;
@@ -147,16 +147,29 @@ __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
     const SplitPackJob &j = pl.job[a];
     if (b >= j.n_cg * j.NG) return;
     const int g = b % j.NG, cg = b / j.NG, tid = threadIdx.x;
-    const int col = tid & 15, hu = cg * HU + col;
+    const int col = tid & 15, unit = cg * HU + col, kg = tid >> 4 & 3;
     const size_t ld = (size_t)j.NG * j.H;
-    const float *w = j.w + (size_t)g * j.H + hu;
+    const float *w = j.w + (size_t)g * j.H + unit;
     if (tid < 16) s_max[tid] = s_inf[tid] = 0u;
     __syncthreads();
+    // thread: eight consecutive k of its column in every fourth k-step, all requested together
+    float x[SPLIT_PACK_T][8];
     unsigned m = 0u;                                            // largest finite magnitude, as bits
     bool inf = false;
-    if (hu < j.H)
-        for (int k = tid >> 4; k < j.SEG * j.L; k += 16) {
-            const unsigned v = __float_as_uint(w[(size_t)k * ld]) & 0x7FFFFFFFu;
+#pragma unroll
+    for (int t = 0; t < SPLIT_PACK_T; ++t) {
+        const int s = 4 * t + (tid >> 6), seg = s / j.steps, off = (s - seg * j.steps) * 32 + 8 * kg;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            x[t][i] = 0.f;
+            if (seg < j.SEG && off + i < j.L && unit < j.H) x[t][i] = w[(size_t)(seg * j.L + off + i) * ld];
+        }
+    }
+#pragma unroll
+    for (int t = 0; t < SPLIT_PACK_T; ++t)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const unsigned v = __float_as_uint(x[t][i]) & 0x7FFFFFFFu;
             if (v < 0x7F800000u) m = max(m, v);
             else if (v == 0x7F800000u) inf = true;
         }
@@ -165,18 +178,22 @@ __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
     __syncthreads();
     const int top = (int)(s_max[col] >> 23);                    // biased exponent of the column's largest magnitude
     const int e = min(13 - (top - 127), 100);                   // the column is scaled by 2^e
-    if (tid < 16) j.scale[(cg * j.NG + g) * HU + col] = s_inf[col] ? __uint_as_float(0x7FC00000u) : hu < j.H ? ldexpf(1.f / j.operand_scale, -e) : 0.f;
-    const int total = j.n_steps * 64 * 8;
-    for (int i = tid; i < total; i += 256) {
-        const int el = i & 7, c = i >> 3 & 15, kg = i >> 7 & 3, s = i >> 9;
-        const int ec = min(13 - ((int)(s_max[c] >> 23) - 127), 100);
-        const int seg = s / j.steps, off = (s - seg * j.steps) * 32 + 8 * kg + el, unit = cg * HU + c;
-        float x = 0.f;
-        if (seg < j.SEG && off < j.L && unit < j.H) x = ldexpf(j.w[(size_t)(seg * j.L + off) * ld + (size_t)g * j.H + unit], ec);
-        const _Float16 hi = (_Float16)x, lo = (_Float16)(x - (float)hi);
-        _Float16 *dst = j.wp + ((((size_t)cg * j.n_steps + s) * j.NG + g) * 2 * 64 + kg * 16 + c) * 8 + el;
+    if (tid < 16) j.scale[(cg * j.NG + g) * HU + col] = s_inf[col] ? __uint_as_float(0x7FC00000u) : unit < j.H ? ldexpf(1.f / j.operand_scale, -e) : 0.f;
+#pragma unroll
+    for (int t = 0; t < SPLIT_PACK_T; ++t) {
+        const int s = 4 * t + (tid >> 6);
+        if (s >= j.n_steps) continue;
+        typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+        half8 hi, lo;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float v = ldexpf(x[t][i], e);
+            hi[i] = (_Float16)v;
+            lo[i] = (_Float16)(v - (float)hi[i]);
+        }
+        half8 *dst = reinterpret_cast<half8 *>(j.wp) + (((size_t)cg * j.n_steps + s) * j.NG + g) * 2 * 64 + kg * 16 + col;
         dst[0] = hi;
-        dst[64 * 8] = lo;
+        dst[64] = lo;
     }
 }
 
