@@ -363,11 +363,6 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
                 lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, kept_gates(f, enode, hu), H);
                 buf_st_f<COH>(rs_c, o, cc);
                 buf_st_f<COH>(rs_h, o, hh);
-            } else if constexpr (EPI == EPI_LSTM_LEAF) {
-                float cc, hh;
-                lstm_leaf_out(gate[0], gate[1], gate[NG - 1], &cc, &hh, kept_gates(f, enode, hu), H);
-                buf_st_f<COH>(rs_c, o, cc);
-                buf_st_f<COH>(rs_h, o, hh);
             } else if constexpr (EPI == EPI_TD_CHILD) {     // gates i, f, o, u of an LSTM step along the edge (as in cell_tile.hpp)
                 const float i = sigmoid_f(gate[0]), fg = sigmoid_f(gate[1]), og = sigmoid_f(gate[2]), u = tanh_f(gate[3]);
                 const float cc = __builtin_fmaf(fg, cl, i * u);
@@ -500,13 +495,6 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
                     if constexpr (EPI == EPI_LSTM_INNER) {
                         float cc, hh;
                         lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, writer ? kept_gates(f, enode, n_hu) : nullptr, H);
-                        if (writer) {
-                            buf_st_f<COH>(rs_c, o, cc);
-                            buf_st_f<COH>(rs_h, o, hh);
-                        }
-                    } else if constexpr (EPI == EPI_LSTM_LEAF) {
-                        float cc, hh;
-                        lstm_leaf_out(gate[0], gate[1], gate[NG - 1], &cc, &hh, writer ? kept_gates(f, enode, n_hu) : nullptr, H);
                         if (writer) {
                             buf_st_f<COH>(rs_c, o, cc);
                             buf_st_f<COH>(rs_h, o, hh);

@@ -60,12 +60,7 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
     const bool quad = (H & 3) == 0 && (((uintptr_t)f.h | (uintptr_t)f.c) & 15) == 0;
     const float ones = __uint_as_float(0xFFFFFFFFu);
     const floatx4 ones4 = floatx4{ones, ones, ones, ones};
-    // the kinds of up to 64 nodes in one load, then their rows one after the other (a load per row would make every row a round trip)
-    const size_t share = (f.n_nodes + n_waves - 1) / n_waves, chunk = share < 64 ? share : 64;
-    for (size_t n0 = wave * chunk; n0 < (size_t)f.n_nodes; n0 += n_waves * chunk)
-    for (unsigned long long todo = __ballot((size_t)lane < chunk && n0 + lane < (size_t)f.n_nodes && f.left[min(n0 + lane, (size_t)f.n_nodes - 1)] >= 0);
-         todo != 0ull; todo &= todo - 1ull) {
-        const size_t n = n0 + __builtin_ctzll(todo);
+    auto fill_row = [&](size_t n) {
         float *c = f.c ? f.c + n * H : nullptr, *h = f.hb || f.hx ? nullptr : f.h + n * H;
         if (quad) {
             for (int e = lane * 4; e < H; e += 256) {
@@ -93,6 +88,19 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
                 else for (int k = 0; k < 4; ++k) if (unit + 2 * k < H) hx[4 * q + k] = 0xFFFFFFFFu;
             }
         }
+    };
+    const size_t N = (size_t)f.n_nodes;
+    if (n_waves >= N) {
+        if (wave < N && f.left[wave] >= 0) fill_row(wave);
+        return;
+    }
+    // fewer waves than nodes: the kinds of up to 64 nodes in one load, then their rows one after the other (a load per row
+    // would make every row a round trip)
+    const size_t share = (N + n_waves - 1) / n_waves, chunk = share < 64 ? share : 64;
+    for (size_t n0 = wave * chunk; n0 < N; n0 += n_waves * chunk) {
+        const size_t n = n0 + lane;
+        unsigned long long todo = __ballot((size_t)lane < chunk && n < N && f.left[n < N ? n : N - 1] >= 0);
+        for (; todo != 0ull; todo &= todo - 1ull) fill_row(n0 + __builtin_ctzll(todo));
     }
 }
 

@@ -280,7 +280,7 @@ fwd_kernel leaf_ws_bf_kernel(int s)
 }
 // LDS bytes of the weight-stationary kernels
 // LDS of the leaf kernel: the bf16 form has a leaner layout of its own (three gates, no scheduler tables)
-size_t leaf_lds_bytes(int spw, bool bf16);
+size_t leaf_lds_bytes(int spw, bool bf16, bool sched);
 size_t ws_lds_bytes(int spw, bool bf16)
 {
     if (bf16) {
@@ -302,9 +302,9 @@ size_t ws_lds_bytes(int spw, bool bf16)
     default: return sizeof(WsSmemT<16>);
     }
 }
-size_t leaf_lds_bytes(int spw, bool bf16)
+size_t leaf_lds_bytes(int spw, bool bf16, bool sched)
 {
-    if (!bf16) return sizeof(SplitLeafSmem) > SCHED_LDS_BYTES ? sizeof(SplitLeafSmem) : SCHED_LDS_BYTES;
+    if (!bf16) return sched && SCHED_LDS_BYTES > sizeof(SplitLeafSmem) ? SCHED_LDS_BYTES : sizeof(SplitLeafSmem);     // (the schedule's lists)
     switch (spw) {
     case 1: return sizeof(LeafSmemBf<1>);
     case 2: return sizeof(LeafSmemBf<2>);
@@ -909,7 +909,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         if (ctx->flow_grid < ctx->n_cg) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
     }
     if (ctx->spw_leaf > 0) {
-        const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16);
+        const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16, ctx->split > 0);
         int o = bf16 ? 4 : 2;                // bf16: bound by latency, gains from every workgroup
         for (int v = 0; v < 2; ++v) {        // fp32: without and with gate activations kept
             const void *lk = bf16 ? reinterpret_cast<const void *>(leaf_ws_bf_kernel(ctx->spw_leaf)) : reinterpret_cast<const void *>(leaf_split_kernel(ctx->spw_leaf, v != 0));
@@ -1199,9 +1199,9 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (n_sched > 0 && !leaf_ws)
         hipLaunchKernelGGL(k_flow_schedule, dim3(n_sched), dim3(WG_THREADS), SCHED_LDS_BYTES, st, fl);
     if (leaf_ws && bf16) {
-        hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16), st, f);
+        hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, false), st, f);
     } else if (leaf_ws) {
-        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf, f.gates != nullptr), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16),
+        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf, f.gates != nullptr), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, n_sched > 0),
                            st, fl, n_sched);
     } else if (cfg.cell == TL_TREELSTM) {
         const LevelPlan plan = plan_level(f.n_leaf, f.cap_tiles);

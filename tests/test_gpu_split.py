@@ -1,0 +1,92 @@
+"""The fp32 TreeLSTM cells that split their operands into two fp16 terms (data-flow scheduler; leaves of every scheduler),
+at the sizes where their tiles, paddings and scales can go wrong.
+
+Tolerance: two terms hold a value to 2^-24 of itself and a sum of at most 1 024 products of order one carries an
+error of about 1e-6; 2e-5 relative + 2e-6 absolute leaves an order of magnitude (the figures the schedulers are
+compared with elsewhere)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1809_00832_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+RTOL, ATOL = 2e-5, 2e-6
+
+
+def run(params, trees, sched):
+    net = binding.TreeNet(params, scheduler=sched)
+    try:
+        out = net.run(trees)
+        for _ in range(2):
+            net.batch["h"].fill_(float("nan"))
+            net.batch["c"].fill_(float("nan"))
+            net.forward()
+            assert binding.tl_status(net.ctx) == 0
+            assert np.array_equal(net.batch["h"].cpu().numpy(), out["h"], equal_nan=True)
+        return out
+    finally:
+        net.close()
+
+
+def same(a, b, what):
+    for key in ("h", "c", "h_root", "c_root"):
+        np.testing.assert_allclose(a[key], b[key], rtol=RTOL, atol=ATOL, err_msg="%s %s" % (what, key))
+    assert np.array_equal(a["root"], b["root"])
+
+
+@pytest.mark.parametrize("H,E", [(1, 1), (15, 3), (16, 31), (17, 32), (31, 33), (32, 4), (33, 127), (63, 129), (65, 300), (97, 257),
+                                 (129, 385), (193, 513), (301, 99), (449, 641), (511, 1023), (512, 1024)])
+def test_sizes_at_the_edges_of_the_tiles(H, E):
+    print("case split sizes", H, E, flush=True)
+    params = synth.make_treelstm_params(900 + H, 70, E, H, "xavier")
+    trees = synth.make_trees(901, [1, 2, 3, 1, 17, 40, 9, 33], ["random", "chain"] * 4, 70)
+    got = run(params, trees, "dataflow")
+    ref = oracle.forward_params(params, trees, n_threads=8)
+    for key in ("h", "c"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+    same(got, run(params, trees, "ready"), "dataflow / ready")
+
+
+def test_columns_and_rows_of_very_different_size():
+    """Every column of the weights and every embedding row is scaled for itself: sizes from 1e-25 to 1e20 side by side."""
+    print("case split scales", flush=True)
+    H, E = 48, 40
+    p = synth.make_treelstm_params(910, 60, E, H, "xavier")
+    rng = np.random.default_rng(1)
+    p.u *= (10.0 ** rng.uniform(-25, 0.5, p.u.shape[1])).astype(np.float32)
+    p.w_leaf *= (10.0 ** rng.uniform(-3, 0.5, p.w_leaf.shape[1])).astype(np.float32)
+    size = 10.0 ** rng.uniform(-25, 1, p.emb.shape[0])
+    size[::7] = 1e20                                    # (gates saturate)
+    p.emb *= size.astype(np.float32)[:, None]
+    trees = synth.make_trees(911, [30, 8, 1, 21], ["random", "chain", "random", "balanced"], 60)
+    got = run(p, trees, "dataflow")
+    ref = oracle.forward_params(p, trees, n_threads=8)
+    for key in ("h", "c"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+
+
+@pytest.mark.parametrize("where", ["u", "w_leaf", "emb"])
+def test_infinities_are_summed_in_fp32(where):
+    """An infinity has no two terms; its sums are taken from the parameters as given, as with fp32 instructions."""
+    print("case split infinity", where, flush=True)
+    H, E = 40, 24
+    p = synth.make_treelstm_params(920, 30, E, H, "xavier")
+    a = getattr(p, where)
+    a[3, 5] = np.inf
+    trees = synth.make_trees(921, [12, 5, 1, 20], ["random"] * 4, 30)
+    with np.errstate(all="ignore"):
+        ref = oracle.forward_params(p, trees, n_threads=8)
+    got = run(p, trees, "dataflow")
+    for key in ("h", "c"):
+        assert np.array_equal(np.isnan(got[key]), np.isnan(ref[key])), key
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key, equal_nan=True)
+
+
+@pytest.mark.parametrize("shape", ["random", "chain"])
+def test_slots_whose_lists_do_not_fit_into_lds(shape):
+    """More nodes per set of workgroups than the schedule's lists have room for in LDS: they move to the workspace."""
+    print("case split large slots", shape, flush=True)
+    params = synth.make_treelstm_params(930, 300, 16, 500, "xavier")
+    trees = synth.make_trees(931, [1200] * 40, [shape] * 40, 300)
+    same(run(params, trees, "dataflow"), run(params, trees, "level_device"), shape)
