@@ -265,14 +265,17 @@ __device__ inline unsigned split_word(float scaled, int hu)
     const unsigned other = (unsigned)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);      // quad_perm [1, 0, 3, 2]
     return (hu & 1) ? (other >> 16 | (own & 0xFFFF0000u)) : ((own & 0xFFFFu) | other << 16);
 }
-// One unit by itself, for writers that do not hold neighbouring units in neighbouring lanes.  (A pad unit beside the last one
-// keeps its zero.)
+// One unit by itself, for writers that do not hold neighbouring units in neighbouring lanes.  The last unit of an odd number is
+// stored with the zero of the pad unit beside it: the row may have been an internal node's in an earlier batch, whose marks
+// ("not written", whole words) nobody replaced - the level kernel was picked, or the batch was rejected - and a mark that
+// is left in half a word is a NaN that shows no pattern.
 __device__ inline void split_store_one(const Fwd &f, int node, int hu, float h)
 {
     const unsigned b = split_bits(h * SPLIT_H_SCALE);
     unsigned short *row = reinterpret_cast<unsigned short *>(f.hx) + (size_t)node * f.hx_steps * 64 + (hu >> 5) * 64 + (hu & 31);
     row[0] = (unsigned short)b;
     row[32] = (unsigned short)(b >> 16);
+    if (hu + 1 == f.H && (hu & 1) == 0) row[1] = row[33] = 0;
 }
 
 __device__ inline unsigned long long pack2(unsigned lo32, unsigned hi32) { return (unsigned long long)hi32 << 32 | lo32; }

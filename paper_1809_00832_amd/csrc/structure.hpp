@@ -81,7 +81,7 @@ __device__ inline void flow_fill(const Fwd &f, size_t wave, size_t n_waves)
             }
         }
         if (f.hx) {
-            unsigned *hx = f.hx + n * (size_t)(f.hx_steps * 32);        // rows of whole 128-byte lines; words of pad units stay zero
+            unsigned *hx = f.hx + n * (size_t)(f.hx_steps * 32);        // rows of whole 128-byte lines; words of pad units alone stay zero
             for (int q = lane; q < f.hx_steps * 8; q += 64) {
                 const int unit = (q >> 3) * 32 + (q & 3) * 8;           // first of the 8 units of these 16 bytes
                 if (unit + 8 <= H) *reinterpret_cast<floatx4 *>(hx + 4 * q) = ones4;

@@ -599,7 +599,7 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     if (ctx->split > 0) {
         const size_t hx_bytes = (size_t)N * ctx->hx_steps * 128;
         TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
-        TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));   // the padding stays zero for good
+        TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));   // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
     }
     if (ctx->split > 0) TL_HIP(hipMalloc(&ctx->sched, ((size_t)N / 2 + 1) * 16 * sizeof(int4)));
     else if (ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)

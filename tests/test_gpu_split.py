@@ -90,3 +90,29 @@ def test_slots_whose_lists_do_not_fit_into_lds(shape):
     params = synth.make_treelstm_params(930, 300, 16, 500, "xavier")
     trees = synth.make_trees(931, [1200] * 40, [shape] * 40, 300)
     same(run(params, trees, "dataflow"), run(params, trees, "level_device"), shape)
+
+
+@pytest.mark.parametrize("first", ["level kernel picked", "rejected"])
+@pytest.mark.parametrize("H,E", [(33, 1025), (1, 1025), (47, 1030)])
+def test_rows_that_were_internal_nodes_before_become_leaves(H, E, first):
+    """The split copy of h outlives a batch.  Rows that a batch marked and nobody wrote (the level kernel was picked; the batch
+    was rejected) are leaves in the next one, evaluated by the leaf kernel for long embeddings: with an odd hidden size
+    the pad unit beside the last one must read as zero again."""
+    print("case split reused rows", H, E, first, flush=True)
+    params = synth.make_treelstm_params(940, 40, E, H, "xavier")
+    before = synth.make_trees(941, [256] * 3, ["balanced"] * 3, 40)
+    if first == "rejected":
+        before.word[np.flatnonzero(before.left < 0)[7]] = 40
+    after = synth.make_trees(942, [30, 1, 200], ["random", "chain", "random"], 40)       # (no larger in any way: the workspace stays)
+    assert ((before.left[:after.n_nodes] >= 0) & (after.left < 0)).sum() > 50
+    ref = oracle.forward_params(params, after, n_threads=8)
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        net.load(before)
+        net.forward()
+        assert binding.tl_status(net.ctx) == (binding.TL_ESTRUCT if first == "rejected" else binding.TL_OK)
+        got = net.run(after)
+    finally:
+        net.close()
+    for key in ("h", "c"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
