@@ -488,8 +488,8 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_backward_heights(Fwd f, BwdHe
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     TileSmem &sm = *reinterpret_cast<TileSmem *>(smem_raw);
-    if (batch_rejected(f)) return;
     const int tid = threadIdx.x;
+    if (decided_to_leave(&sm.cmd[7], tid == 0 && batch_rejected(f))) return;
     const int H = f.H;
     const int n_levels = f.ctl->n_levels;
     const long long first = (long long)blockIdx.x * blockDim.x + tid, stride = (long long)gridDim.x * blockDim.x;
@@ -551,7 +551,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
     extern __shared__ __align__(16) unsigned char smem_raw[];
     using Smem = OperandWsSmem<SPW2>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
-    if (batch_rejected(f)) return;
+    if (decided_to_leave(&sm.cmd[7], threadIdx.x == 0 && batch_rejected(f))) return;
     constexpr int NLB = SPW2;                               // row loads per lane and half: 16 rows x 4 SPW2 pieces / 64 lanes
     constexpr int PPR = 4 * SPW2;                           // 16-byte pieces of a row in one half of a wave's quarter
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;

@@ -34,7 +34,7 @@ constexpr int SPLIT_MAX_S = 8;
 struct SplitSmem {
     float red[2][4 * MAX_GATES * 64 * 4];   // K-split partial sums, alternating per block: [wave][gate][lane][v]
     float sum_of[MAX_GATES * HU * 2];       // scale and bias of every column (registers are short)
-    int gave_up;
+    int gave_up, leave;
 };
 
 template <int NG, int S> struct SplitWeights {
@@ -291,6 +291,7 @@ struct SplitLeafSmem {
     float red[2][4 * NG * 64 * 4];
     float sum_of[NG * HU * 2];
     float row_scale[4][16];
+    int leave;
 };
 
 __device__ inline float max_across_quarters(float m)

@@ -310,6 +310,18 @@ __device__ inline bool batch_rejected(const Fwd &f)
     return f.ctl->status != 0 || (f.flow_roots ? f.ctl->n_leaf_seen != f.n_leaf : f.ctl->n_roots != f.n_trees);
 }
 
+// A workgroup leaves as a whole or not at all.  Where other workgroups of the same launch may latch an error (a schedule that
+// finds a second root, a wait that gives up), every wave reading the status for itself would let some waves leave and the
+// rest go on with row tables and counts in LDS that the departed ones never wrote.  So one thread decides for all: it leaves
+// its answer in LDS in front of a barrier the kernel has anyway, or of this one.
+// `word` must not be written again before a further barrier.
+__device__ inline bool decided_to_leave(int *word, bool leave)
+{
+    if (threadIdx.x == 0) *word = leave ? 1 : 0;
+    __syncthreads();
+    return *word != 0;
+}
+
 __device__ inline void backoff() { __builtin_amdgcn_s_sleep(2); }
 
 // A batch of fewer trees than the device has sets of workgroups, of large trees: the data-flow scheduler keeps a tree on

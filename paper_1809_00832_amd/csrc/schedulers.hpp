@@ -57,15 +57,15 @@ __global__ __launch_bounds__(WG_THREADS, S <= 4 ? 2 : 1) void k_leaf_split(Fwd f
         return;
     }
     SplitLeafSmem &sm = *reinterpret_cast<SplitLeafSmem *>(smem_raw);
-    if (batch_rejected(f)) return;
     const int tid = threadIdx.x, wg = blockIdx.x - n_sched, n_wg = gridDim.x - n_sched;
+    const bool leave = tid == 0 && batch_rejected(f);         // (the schedule's workgroups may latch an error meanwhile)
     const int cg = gang_cg(wg % f.n_cg, f.n_cg, f.n_cg);
     const int slot = wg / f.n_cg, n_slots = n_wg / f.n_cg;
     SplitWeights<EpiTraits<EPI_LSTM_LEAF>::NG, S> w;
     split_load(w, sm.sum_of, f.xl, f.leaf, cg, tid >> 6, tid & 63);
     const int share = ((f.n_leaf + n_slots - 1) / n_slots + 15) & ~15;
     const int lo = slot * share, hi = min(f.n_leaf, lo + share);
-    __syncthreads();
+    if (decided_to_leave(&sm.leave, leave)) return;
     split_leaves<S, KEEP>(sm, f, lo, hi, cg, w);
     // data-flow scheduler: the stores that mark the internal nodes' rows (last: a load behind them would wait for them)
     if (f.flow == 2) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
@@ -267,8 +267,8 @@ __global__ __launch_bounds__(WG_THREADS, (SPW > 0 && !BF16) ? 1 : 2) void k_leve
     using Smem = PersistentSmem<SPW, BF16>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     Ctl *ctl = f.ctl;
-    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
     const int tid = threadIdx.x;
+    if (decided_to_leave(&sm.cmd[7], tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f)))) return;
     // A slot is a set of workgroups that covers all column groups; the workgroups of a slot gather the same child rows.
     // (Putting every slot on one L2 domain, so that its rows cross the fabric once instead of once per domain that
     // holds some of its column groups, was measured and is not done: no faster on the H=512 batch, whose fabric
@@ -535,8 +535,8 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     using Smem = PersistentSmem<SPW, BF16>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     Ctl *ctl = f.ctl;
-    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
     const int tid = threadIdx.x;
+    const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));      // (a slot's workgroup latches what it finds)
     const int n_slots = gridDim.x / f.n_cg;
     const int member = blockIdx.x % f.n_cg, slot = blockIdx.x / f.n_cg;
     const int my_cg = member;
@@ -546,7 +546,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     flow_cut(f, slot, n_slots, &t_lo, &t_hi);
     const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];
     const int slot_internal = ((ne - nb) - (t_hi - t_lo)) / 2;      // full binary trees
-    if (ne <= nb) return;
+    if (ne <= nb) return;                             // (the same for all waves: nothing writes the offsets)
     unsigned *seen = reinterpret_cast<unsigned *>(f.flow_seen) + (size_t)member * f.n_nodes;   // this workgroup's own: [nb, ne) of it
     int4 *list = f.flow_list + (size_t)member * f.n_int + (nb - t_lo) / 2;
     int *len = &sm.cmd[4];
@@ -554,7 +554,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
         sm.cmd[6] = 0;                                // roots found
         sm.cmd[7] = 0;                                // a wait was abandoned
     }
-    __syncthreads();
+    if (decided_to_leave(&sm.cmd[4], leave)) return;  // (cmd[4] is written again when the scan is over)
     // the list starts with the slot's nodes over two leaves, in node order.  The same pass over the slot's nodes counts
     // the roots (nodes without a parent): there must be one per tree (a second one in a tree is caught where the roots
     // are copied out, after the last piece).  A thread looks at four consecutive nodes per round, all their loads in
@@ -714,14 +714,15 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     SplitSmem &sm = *reinterpret_cast<SplitSmem *>(smem_raw);
-    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
     const int tid = threadIdx.x;
+    const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));      // (a workgroup that gives up latches that)
     int member, slot;
     split_place(f, &slot, &member);
     if (tid == 0) sm.gave_up = 0;
     SplitWeights<EpiTraits<EPI_LSTM_INNER>::NG, S> w;
     split_load(w, sm.sum_of, f.xi, f.inner, member, tid >> 6, tid & 63);
-    const int4 head = f.sched_head[slot];
+    const int4 head = f.sched_head[slot];         // (of an earlier batch where this one is rejected: not used then)
+    if (decided_to_leave(&sm.leave, leave)) return;
     if (f.flow_roots) {                           // trees of one node: the leaf is the root
         const int hu = member * HU + (tid & 15);
         for (int t = head.z + (tid >> 4); t < head.w && hu < f.H; t += WG_THREADS / 16) {
@@ -731,7 +732,6 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
             if (f.c_root) f.c_root[(size_t)t * f.H + hu] = f.c[(size_t)n * f.H + hu];
         }
     }
-    __syncthreads();
     if (head.y > 0) split_run<S>(sm, f, f.sched + (size_t)head.x * 16, head.y, member, w);
 }
 
@@ -937,8 +937,8 @@ __global__ __launch_bounds__(WG_THREADS, (SPW > 0 && !BF16) ? 1 : 2) void k_read
     extern __shared__ __align__(16) unsigned char smem_raw[];
     using Smem = PersistentSmem<SPW, BF16>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
-    if (batch_rejected(f)) return;
     const int tid = threadIdx.x;
+    if (decided_to_leave(&sm.cmd[7], tid == 0 && batch_rejected(f))) return;
     const int n_compute = f.n_gangs * f.gang_size;
     if ((int)blockIdx.x >= n_compute) {           // scheduler workgroups come after all compute workgroups
         ready_scheduler(f, &f.gangs[blockIdx.x - n_compute]);

@@ -486,13 +486,11 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
 {
     const int tid = threadIdx.x, lane = tid & 63, n = ne - nb, first = (nb - t_lo) / 2;
     const int cap = (n - (t_hi - t_lo)) / 2;      // internal nodes (full binary trees)
-    int *s_ctl = reinterpret_cast<int *>(lds);    // - | roots, later nodes handed out | blocks | a tree of one node exists
+    int *s_ctl = reinterpret_cast<int *>(lds);    // leave (read) | roots, later nodes handed out | blocks | a tree of one node exists
     SchedLists<IN_LDS> q;
     constexpr int Q = 4;
     int *s_cnt = s_ctl + 4;                       // seeds of a pass, [Q][waves]
     q.carve(f, lds + 16 + 4 * Q * 4, n, nb, first);
-    if (tid < 4) s_ctl[tid] = 0;
-    __syncthreads();
     int n_seeds = 0;
     for (int base = 0; base < n; base += WG_THREADS * Q) {
         int l[Q], up[Q], pend[Q];
@@ -630,7 +628,10 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
 }
 __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds, size_t lds_bytes)
 {
-    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
+    // (workgroups of other slots may latch an error meanwhile)
+    int *s_ctl = reinterpret_cast<int *>(lds);
+    if (threadIdx.x >= 1 && threadIdx.x < 4) s_ctl[threadIdx.x] = 0;
+    if (decided_to_leave(&s_ctl[0], threadIdx.x == 0 && (batch_rejected(f) || internal_kernel_skipped(f)))) return;
     int t_lo, t_hi;
     flow_cut(f, slot, f.n_slots, &t_lo, &t_hi);
     const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];

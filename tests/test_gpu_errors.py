@@ -227,3 +227,44 @@ def test_many_forwards_give_the_same_bits(name, iters, sched, precision):
         assert bad == 0, "%d of %d checked forwards differ from the first" % (bad, checked)
     finally:
         net.close()
+
+
+def batch_with_wrong_roots(n_good, leaves, vocab):
+    """Good trees around two ranges whose counts add up while neither is a tree: 6 nodes with two roots, and 4 nodes that
+    form a cycle and have none (every node has one parent at most, leaves and internal nodes are as many as they should be).
+    What is wrong is found by whoever looks for the roots: under the data-flow scheduler workgroups of one slot, beside the others."""
+    good = synth.make_trees(7, [leaves] * n_good, ["random", "balanced"] * (n_good // 2), vocab)
+    two = (np.array([1, -1, -1, 4, -1, -1]), np.array([2, -1, -1, 5, -1, -1]))
+    ring = (np.array([1, 0, -1, -1]), np.array([2, 3, -1, -1]))
+    off, left, right, word = [0], [], [], []
+
+    def add(l, r, w):
+        base = off[-1]
+        left.append(np.where(l >= 0, l + base, -1))
+        right.append(np.where(r >= 0, r + base, -1))
+        word.append(w)
+        off.append(base + len(l))
+
+    for t in range(n_good):
+        if t == n_good // 3: add(*two, np.where(two[0] < 0, 3, -1))
+        if t == 2 * n_good // 3: add(*ring, np.where(ring[0] < 0, 4, -1))
+        lo, hi = int(good.tree_off[t]), int(good.tree_off[t + 1])
+        rel = lambda a: np.where(a[lo:hi] >= 0, a[lo:hi] - lo, -1)
+        add(rel(good.left), rel(good.right), good.word[lo:hi])
+    cat = lambda a: np.concatenate(a).astype(np.int32)
+    return TreeBatch(np.array(off, np.int32), cat(left), cat(right), cat(word))
+
+
+@pytest.mark.parametrize("what", ["lstm", "lstm, large slots", "lstm bf16", "rnn", "rnn bf16"])
+def test_errors_found_by_one_slot_beside_the_others(what):
+    """A workgroup leaves as a whole: an error that another slot latches while a workgroup starts must not part its waves
+    (their shares of the tables in LDS would be missing).  The batch is rejected, again and again, and the context goes on."""
+    print("case errors beside other slots", what, flush=True)
+    large = "large" in what
+    H = 500 if large else 16
+    p = synth.make_rnn_params(5, synth.CELL_TREERNN, 50, H, scale=0.4) if "rnn" in what else synth.make_treelstm_params(5, 50, 8, H, "xavier")
+    bad = batch_with_wrong_roots(40 if large else 300, 1200 if large else 20, 50)
+    assert (bad.n_nodes + bad.n_trees) % 2 == 0 and (bad.left < 0).sum() * 2 == bad.n_nodes + bad.n_trees
+    kw = dict(precision=binding.TL_BF16_IN) if "bf16" in what else {}
+    for _ in range(2 if large else 6):
+        run_expect(p, bad, "dataflow", binding.TL_ESTRUCT, **kw)
