@@ -248,9 +248,12 @@ template <bool COH> __device__ inline void buf_st_h(__amdgpu_buffer_rsrc_t r, un
 }
 
 // ---- two fp16 terms of a value, and the split copy of h (cell_split.hpp) ------------------
-// hi | lo << 16 of a value that has been scaled already
+// hi | lo << 16 of a value that has been scaled already.  (A NaN is stored as the one without payload: converted as it is, a
+// negative one whose upper mantissa bits are ones would be all ones in fp16, and two of them side by side the word that
+// says "not written", for which only a NaN of 32 ones may stand.)
 __device__ inline unsigned split_bits(float x)
 {
+    if (__builtin_isnan(x)) x = __uint_as_float(0x7FC00000u);
     const _Float16 hi = (_Float16)x;
     const _Float16 lo = (_Float16)(x - (float)hi);
     return (unsigned)__builtin_bit_cast(unsigned short, hi) | (unsigned)__builtin_bit_cast(unsigned short, lo) << 16;

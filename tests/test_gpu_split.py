@@ -116,3 +116,28 @@ def test_rows_that_were_internal_nodes_before_become_leaves(H, E, first):
         net.close()
     for key in ("h", "c"):
         np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+
+
+@pytest.mark.parametrize("bits", [0xFFFFE000, 0x7FFFE000, 0xFFFFFFFE, 0x7FC00000])
+@pytest.mark.parametrize("where", ["b_leaf", "b", "emb"])
+def test_a_nan_is_a_result_whatever_its_payload(where, bits):
+    """NaNs in neighbouring units whose fp16 halves would be all ones: rows that hold them count as written.  (Only a NaN
+    of 32 ones may end a forward with TL_ESTALL.)"""
+    print("case split nan", where, hex(bits), flush=True)
+    H, E = 34, 20
+    p = synth.make_treelstm_params(950, 30, E, H, "xavier")
+    a = getattr(p, where)
+    at = (slice(4, 8), slice(0, 2)) if where == "emb" else slice(a.shape[0] // H * H - 2 * H + 6, a.shape[0] // H * H - 2 * H + 10)     # output gate
+    a.view(np.uint32)[at] = bits
+    trees = synth.make_trees(951, [12, 5, 1, 20], ["random"] * 4, 30)
+    with np.errstate(all="ignore"):
+        ref = oracle.forward_params(p, trees, n_threads=8)
+    net = binding.TreeNet(p, scheduler="dataflow", spin_limit=20000)
+    try:
+        got = net.run(trees)
+    finally:
+        net.close()
+    for key in ("h", "c"):
+        assert np.isnan(ref[key]).any() or (where != "emb" and key == "c")
+        assert np.array_equal(np.isnan(got[key]), np.isnan(ref[key])), key
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key, equal_nan=True)
