@@ -303,7 +303,11 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 // The contraction runs over the nodes on the 16-bit matrix unit with fp32 operands: a value is the sum of three bf16 terms
 // (8 bits each and the range of fp32, so gradients of any magnitude need no scaling), and of the nine products the six
 // that reach 2^-24 of the whole are taken, accumulated in fp32: 6/16 of the fp32 instruction's time, beside which vector
-// instructions run.  (An infinity has no such terms: where a sum was infinite it comes out as NaN.)
+// instructions run.
+// An infinity has no such terms (x - hi is a NaN), a finite value above the largest bf16 number rounds to one, and below 2^-109
+// the last term runs out of exponents.  A wave that ends with a sum that is not finite, or is below 2^-100 and not zero, therefore takes
+// its sums again with fp32 instructions (wg_sums_again): what comes out is what those give.  (A sum above 2^-100 of values
+// below 2^-109 keeps their upper 16 bits at least.)
 // A thread loads one column of 16 of a step's 32 nodes (a wave: 256 consecutive bytes a row), splits them and parks each term's
 // eight neighbours as the 16 bytes that are an operand of v_mfma_f32_16x16x32_bf16; the next 32 nodes' values are
 // requested before the current ones are multiplied.  Bound by the reads of the rows, each of which goes to every
@@ -328,6 +332,37 @@ __device__ inline void wg_park(unsigned short (*dst)[WG_TILE][WG_LD], int col, i
     *reinterpret_cast<bf16x8 *>(&dst[0][col][q]) = hi;
     *reinterpret_cast<bf16x8 *>(&dst[1][col][q]) = mid;
     *reinterpret_cast<bf16x8 *>(&dst[2][col][q]) = lo;
+}
+
+// The sums of a wave's 64 x 64 quarter at (k0, j0) over nodes [q_lo, q_hi) with fp32 instructions, straight from memory (rare, and
+// slow: every four nodes are a chain of three loads).
+template <int SEG>
+__device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list, const float *table, int L, const float *dg, int n_cols, int k0,
+                                                        int j0, int q_lo, int q_hi, floatx4 (&acc)[4][4])
+{
+    const int lane = threadIdx.x & 63, K_out = SEG * L;
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int q0 = q_lo; q0 < q_hi; q0 += 4) {
+        const bool live = q0 + (lane >> 4) < q_hi;
+        const int q = live ? q0 + (lane >> 4) : q_hi - 1, node = list[q];
+        const int s0 = SEG == 2 ? f.left[node] : f.word[node], s1 = SEG == 2 ? f.right[node] : 0;
+        float a[4], b[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+            const int k = min(k0 + t * 16 + (lane & 15), K_out - 1), j = min(j0 + t * 16 + (lane & 15), n_cols - 1);
+            const bool second = SEG == 2 && k >= L;
+            a[t] = live ? table[(size_t)(second ? s1 : s0) * L + (second ? k - L : k)] : 0.f;
+            b[t] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+        }
+#pragma unroll
+        for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+            for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
+    }
 }
 
 template <int SEG>
@@ -412,6 +447,17 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad(Fwd f, const int32_t *__
             __syncthreads();
         }
     }
+    bool again = false;
+#pragma unroll
+    for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const float m = fabsf(acc[ta][tb][v]);
+                again |= !(m == 0.f || (m >= 0x1p-100f && m < __builtin_inff()));
+            }
+    if (__builtin_expect(__ballot(again) != 0ull, 0)) wg_sums_again<SEG>(f, list, table, L, dg, n_cols, k0 + wr, j0 + wc, q_lo, q_hi, acc);
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)
 #pragma unroll

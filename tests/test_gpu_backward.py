@@ -489,3 +489,77 @@ def test_rntn_backward_matches_oracle():
         assert np.array_equal(fresh.run(sub)["h"], h_after)
     finally:
         fresh.close()
+
+
+def rnn_gate_gradients(p, trees, h, g_h):
+    """dg of every internal node, in 64 bits: dg = dh (1 - h^2), dh[child] += dg W^T, parents first."""
+    dh, dg = g_h.astype(np.float64), np.zeros(g_h.shape)
+    h, u, d = h.astype(np.float64), p.u.astype(np.float64), p.hidden
+    stack = sorted(set(range(trees.n_nodes)) - set(trees.left.tolist()) - set(trees.right.tolist()))
+    while stack:
+        n = stack.pop()
+        if trees.left[n] < 0: continue
+        dg[n] = dh[n] * (1 - h[n] * h[n])
+        back = u @ dg[n]
+        dh[trees.left[n]] += back[:d]
+        dh[trees.right[n]] += back[d:]
+        stack += [int(trees.left[n]), int(trees.right[n])]
+    return dg
+
+
+@pytest.mark.parametrize("d", [33, 130])
+@pytest.mark.parametrize("what", ["infinite", "near the largest", "small"])
+def test_weight_gradient_outside_the_ordinary_range(what, d):
+    """An upstream gradient that is infinite, beyond the largest bf16 number, or far below one: the sums are those of fp32
+    instructions.  TreeRNN; the gradient enters at a node over two leaves, so one column of d_u holds it and the others are
+    ordinary.  Tolerance: 54 terms of at most |dg| each (|h| <= 1), each dg a sum over d products before that, so
+    (54 + 2 d) 2^-24 of the largest |dg| (of the column itself where that is the one with the large value)."""
+    print("case weight gradient, upstream", what, d, flush=True)
+    p = synth.make_rnn_params(140, synth.CELL_TREERNN, 50, d, scale=0.1)
+    p.emb *= np.float32(0.02 if what == "near the largest" else 8)
+    trees = synth.make_trees(141, [9, 2, 30, 1, 17], ["random"] * 5, 50)
+    inner = np.flatnonzero(trees.left >= 0)
+    assert len(inner) == 54
+    rng = np.random.default_rng(142)
+    g_h = rng.standard_normal((trees.n_nodes, d)).astype(np.float32)
+    special = np.zeros(d, bool)
+    if what == "small":
+        g_h *= np.float32(1e-37)
+    else:
+        at = inner[(trees.left[trees.left[inner]] < 0) & (trees.left[trees.right[inner]] < 0)][2]
+        g_h[at, 5] = np.inf if what == "infinite" else np.float32(3.4e38)
+        special[5] = True
+    net = binding.TreeNet(p, scheduler="level_device")
+    try:
+        b = net.load(trees)
+        net.forward()
+        got = binding.tl_backward(net.ctx, b, torch.from_numpy(g_h).cuda(), d)
+        got = {k: v.cpu().numpy() for k, v in got.items()}
+        h = b["h"].cpu().numpy()
+    finally:
+        net.close()
+    with np.errstate(all="ignore"):
+        ref = oracle.backward(p, trees, h, None, g_h)
+        dg = np.abs(rnn_gate_gradients(p, trees, h, g_h))
+    scale = np.where(special, np.where(np.isfinite(dg), dg, 0.0).max(axis=0), dg[:, ~special].max())
+    assert np.isinf(ref["d_u"]).any() == (what == "infinite")
+    for k in ("d_u", "d_b"):
+        r, g = ref[k].astype(np.float64), got[k].astype(np.float64)
+        assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(np.isinf(g), np.isinf(r)), k
+        assert np.array_equal(np.sign(g[np.isinf(r)]), np.sign(r[np.isinf(r)])), k
+        fin = np.isfinite(r)
+        err = np.abs(np.where(fin, g, 0.0) - np.where(fin, r, 0.0)) / scale
+        print("   ", k, "largest error / scale %.1e" % err.max(), flush=True)
+        assert err.max() <= (54 + 2 * d) * 2.0 ** -24, k
+
+
+def test_weight_gradient_of_rows_beyond_the_largest_bf16_number():
+    """TreeLSTM leaves: an embedding value above the largest bf16 number saturates its gates, whose gradients are zero;
+    d_w_leaf is finite."""
+    print("case weight gradient, embedding", flush=True)
+    p = synth.make_treelstm_params(150, 20, 24, 40, "xavier")
+    p.emb[3, 7] = np.float32(3.4e38)
+    trees = synth.make_trees(151, [12, 30, 5], ["random"] * 3, 20)
+    assert (trees.word[trees.left < 0] == 3).any()
+    run_case(p, trees, 152, "embedding 3.4e38")
+    run_case(p, trees, 152, "embedding 3.4e38 kept", keep=True, scheduler="dataflow")
