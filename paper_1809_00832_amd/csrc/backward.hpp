@@ -296,9 +296,140 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 // Weight gradient: out[k][j] += sum_q a_q[k] * dg[q][j] over the n_rows nodes of `list` (dg rows by
 // list position), a_q = [h[left]; h[right]] (SEG 2, L = H) or the embedding row of the leaf's
 // word (SEG 1, L = E).  K_out = SEG * L rows, n_cols columns, row-major; `out` is zero beforehand.
-// One workgroup per 128 x 128 tile of the output and slice of the nodes (blockIdx.z; the slices'
-// partial tiles are added with atomics: the node axis is long and the output small, so without
-// slices there are too few workgroups to hide the latency of the gathers), wave w on the
+// Two kernels; wg_plan() says which, and why the line lies where it does.  Both cut the node axis into slices (blockIdx.z; the
+// slices' partial tiles are added with atomics: the node axis is long and the output small, so without
+// slices there are too few workgroups to hide the latency of the gathers).
+//
+// The one for small outputs and few nodes: one workgroup per 64 x 64 tile of the output and slice, wave w on the
+// 32 x 32 quarter (w / 2, w % 2).  The contraction runs over the nodes, 16 at a time through LDS,
+// on v_mfma_f32_16x16x4_f32 with the node index as the k of the instruction; the next 16 nodes'
+// operands are requested into registers before the current ones are multiplied.
+constexpr int WN_TILE = 64, WN_Q = 16, WN_LD = WN_TILE + 4;
+
+template <int SEG, bool VEC4>
+__global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
+                                                     const float *__restrict__ table, int L, const float *__restrict__ dg,
+                                                     int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+{
+    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
+    __shared__ __align__(16) float as[2][WN_Q][WN_LD];         // two buffers each: a step's operands are parked while the
+    __shared__ __align__(16) float bs[2][WN_Q][WN_LD];         // step before is still being multiplied (one barrier per step)
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int k0 = blockIdx.x * WN_TILE, j0 = blockIdx.y * WN_TILE;
+    const int K_out = SEG * L;
+    const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
+    const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WN_Q - 1) / WN_Q * WN_Q;
+    const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
+    if (q_lo >= q_hi) return;
+    floatx4 acc[2][2];
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+    const int lq = tid >> 4, lk = (tid & 15) * 4;             // this thread stages 4 consecutive columns of row lq
+    float ra[4], rb[4];
+    // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
+    const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
+    float bsum[4] = {0.f, 0.f, 0.f, 0.f};
+    // The operands of a step (16 nodes) hang on a chain of three loads: the node from the list, its source rows from
+    // the child (or word) arrays, the data from those rows.  A step has only 16 MFMAs per wave to hide it, so the chain
+    // is spread over three steps: step i requests the data of step i + 1, the source rows of step i + 2 and the node
+    // of step i + 3, each from what the step before has requested.
+    auto node_of = [&](int q0) {                              // stage 1
+        const int q = q0 + lq;
+        return q < q_hi ? list[q] : -1;
+    };
+    auto sources_of = [&](int node, int *s0, int *s1) {       // stage 2
+        *s0 = *s1 = 0;
+        if (node >= 0) {
+            if (SEG == 2) { *s0 = f.left[node]; *s1 = f.right[node]; } else { *s0 = f.word[node]; }
+        }
+    };
+    auto request = [&](int q0, int node, int s0, int s1) {    // stage 3: operands of nodes q0 .. q0 + 15 into registers
+        const int q = q0 + lq;
+        const bool live = node >= 0;
+        if constexpr (VEC4) {      // L and n_cols multiples of 4, rows 16-byte aligned: 4 consecutive columns never leave a segment
+            const int k = k0 + lk, j = j0 + lk;
+            const int seg = (SEG == 2 && k >= L) ? 1 : 0;
+            floatx4 a = floatx4{0.f, 0.f, 0.f, 0.f}, b = a;
+            if (live && k < K_out) a = *reinterpret_cast<const floatx4 *>(table + (size_t)(seg ? s1 : s0) * L + (k - seg * L));
+            if (live && j < n_cols) b = *reinterpret_cast<const floatx4 *>(dg + (size_t)q * n_cols + j);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) { ra[e] = a[e]; rb[e] = b[e]; }
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int k = k0 + lk + e, j = j0 + lk + e;
+                const int seg = (SEG == 2 && k >= L) ? 1 : 0;
+                ra[e] = (live && k < K_out) ? table[(size_t)(seg ? s1 : s0) * L + (k - seg * L)] : 0.f;
+                rb[e] = (live && j < n_cols) ? dg[(size_t)q * n_cols + j] : 0.f;
+            }
+        }
+    };
+    int node1 = node_of(q_lo), s0_1, s1_1;                    // step q_lo: all three stages at once
+    sources_of(node1, &s0_1, &s1_1);
+    request(q_lo, node1, s0_1, s1_1);
+    node1 = node_of(q_lo + WN_Q);                             // step q_lo + 16: node and source rows
+    sources_of(node1, &s0_1, &s1_1);
+    int node2 = node_of(q_lo + 2 * WN_Q);                     // step q_lo + 32: node
+    auto park = [&](int buf) {
+        *reinterpret_cast<floatx4 *>(&as[buf][lq][lk]) = floatx4{ra[0], ra[1], ra[2], ra[3]};
+        *reinterpret_cast<floatx4 *>(&bs[buf][lq][lk]) = floatx4{rb[0], rb[1], rb[2], rb[3]};
+        if (with_bias) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) bsum[e] += rb[e];
+        }
+    };
+    park(0);
+    __syncthreads();
+    int buf = 0;
+    for (int q0 = q_lo; q0 < q_hi; q0 += WN_Q) {
+        request(q0 + WN_Q, node1, s0_1, s1_1);                // (beyond the end: node -1, nothing is loaded)
+        node1 = node2;
+        sources_of(node1, &s0_1, &s1_1);
+        node2 = node_of(q0 + 3 * WN_Q);
+#pragma unroll
+        for (int kk = 0; kk < WN_Q / 4; ++kk) {
+            const int qq = kk * 4 + (lane >> 4);
+            float a[2], b[2];
+#pragma unroll
+            for (int t = 0; t < 2; ++t) {
+                a[t] = as[buf][qq][wr + t * 16 + (lane & 15)];
+                b[t] = bs[buf][qq][wc + t * 16 + (lane & 15)];
+            }
+#pragma unroll
+            for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+                for (int tb = 0; tb < 2; ++tb)
+                    acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[ta], b[tb], acc[ta][tb], 0, 0, 0);
+        }
+        // the other buffer was read in the step before this one, and every wave has passed the barrier since
+        if (q0 + WN_Q < q_hi) park(buf ^ 1);
+        __syncthreads();
+        buf ^= 1;
+    }
+#pragma unroll
+    for (int ta = 0; ta < 2; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < 2; ++tb)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = k0 + wr + ta * 16 + (lane >> 4) * 4 + v, j = j0 + wc + tb * 16 + (lane & 15);
+                if (k < K_out && j < n_cols) atomicAdd(&out[(size_t)k * n_cols + j], acc[ta][tb][v]);
+            }
+    if (with_bias) {                                          // uniform per workgroup; the loop ended with a barrier
+        *reinterpret_cast<floatx4 *>(&bs[0][lq][lk]) = floatx4{bsum[0], bsum[1], bsum[2], bsum[3]};
+        __syncthreads();
+        if (tid < WN_TILE && j0 + tid < n_cols) {
+            float t = 0.f;
+#pragma unroll
+            for (int q = 0; q < WN_Q; ++q) t += bs[0][q][tid];
+            atomicAdd(&bias_out[j0 + tid], t);
+        }
+    }
+}
+
+// The one for large outputs and many nodes: one workgroup per 128 x 128 tile of the output and slice, wave w on the
 // 64 x 64 quarter (w / 2, w % 2).
 // The contraction runs over the nodes on the 16-bit matrix unit with fp32 operands: a value is the sum of three bf16 terms
 // (8 bits each and the range of fp32, so gradients of any magnitude need no scaling), and of the nine products the six
@@ -306,13 +437,47 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 // instructions run.
 // An infinity has no such terms (x - hi is a NaN), a finite value above the largest bf16 number rounds to one, and below 2^-109
 // the last term runs out of exponents.  A wave that ends with a sum that is not finite, or is below 2^-100 and not zero, therefore takes
-// its sums again with fp32 instructions (wg_sums_again): what comes out is what those give.  (A sum above 2^-100 of values
-// below 2^-109 keeps their upper 16 bits at least.)
+// its sums again with fp32 instructions (wg_sums_again): what comes out is what those give.  (In a larger sum a
+// value below 2^-109 is off by 2^-134 at most.)
 // A thread loads one column of 16 of a step's 32 nodes (a wave: 256 consecutive bytes a row), splits them and parks each term's
 // eight neighbours as the 16 bytes that are an operand of v_mfma_f32_16x16x32_bf16; the next 32 nodes' values are
 // requested before the current ones are multiplied.  Bound by the reads of the rows, each of which goes to every
-// tile: hence the tile of 128 (64 x 64 tiles with fp32 instructions took 371 us for U at H = 512 and 6 658 nodes).
+// tile: hence the tile of 128.
 constexpr int WG_TILE = 128, WG_Q = 32, WG_LD = WG_Q + 8, WG_SRC = 512;
+
+// Which of the two kernels, and its grid.  A workgroup of the wide form starts with a longer chain (source rows, 64 KB of LDS,
+// no second buffer), ends with four times the atomics, and does the products of a whole tile wherever the output ends; per
+// product it needs half the reads and 6/16 of the matrix time.  Measured on 202 outputs and node counts (TreeLSTM H = 16 ... 512,
+// TreeRNN d = 16 ... 512, RNTN d = 8 ... 96; 1 to 4 096 trees of 5 to 50 leaves), time of the 64 x 64 form over that of the wide one:
+//   tiles filled to less than 62 % by the output (86)       0.48 ... 1.00, one at 1.09
+//   nodes per slice x filled share below 340 (94)           0.44 ... 0.99, and 1.01 ... 1.22 for six outputs close below that line
+//   above (22)                                              1.06 ... 1.88
+// (U at H = 512: 387 -> 303 us for 6 772 nodes, 104 -> 112 us for 1 682; W of TreeRNN at d = 256: 39 -> 57 us for 6 772,
+// 306 -> 224 us for 108 536; U at H = 48: 17 -> 19 us for 6 772.)
+struct WgPlan {
+    bool wide;
+    unsigned tiles_k, tiles_j, slices;
+};
+inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu)
+{
+    WgPlan p{};
+    auto cut = [&](int tile, int per_cu, int min_nodes) {
+        p.tiles_k = (unsigned)((K_out + tile - 1) / tile);
+        p.tiles_j = (unsigned)((n_cols + tile - 1) / tile);
+        const long long tiles = (long long)p.tiles_k * p.tiles_j;
+        long long z = ((long long)per_cu * n_cu + tiles - 1) / tiles;             // that many workgroups per CU in all
+        const long long max_z = ((long long)n_rows + min_nodes - 1) / min_nodes;
+        if (z > max_z) z = max_z;
+        p.slices = (unsigned)(z < 1 ? 1 : z);
+        return tiles;
+    };
+    const double tiles = (double)cut(WG_TILE, 4, 2 * WG_Q);                       // two resident at a time
+    const double filled = (double)K_out * n_cols / (tiles * WG_TILE * WG_TILE);
+    p.wide = filled >= 0.62 && (double)n_rows / p.slices * filled >= 340.0;
+    if (!p.wide) cut(WN_TILE, 8, 4 * WN_Q);
+    return p;
+}
+
 struct WgSmem {
     unsigned short a[3][WG_TILE][WG_LD], b[3][WG_TILE][WG_LD];      // [term][column][node]
     int src[2][WG_SRC];                                             // source rows of the slice's next nodes
@@ -366,9 +531,9 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
 }
 
 template <int SEG>
-__global__ __launch_bounds__(256, 2) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
-                                                        const float *__restrict__ table, int L, const float *__restrict__ dg,
-                                                        int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+__global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
+                                                             const float *__restrict__ table, int L, const float *__restrict__ dg,
+                                                             int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
 {
     __shared__ __align__(16) WgSmem sm;
     if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)

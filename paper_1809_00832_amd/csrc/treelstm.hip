@@ -1530,28 +1530,27 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
                            dim3(plan_op.n_tiles * g.n_cg), dim3(WG_THREADS),
                            TILE_SMEM_BYTES, st, g, (const int32_t *)f.leaf_list, n_leaf, plan_op);
     }
-    // weight and bias gradients: contractions over all nodes, the node axis cut into slices so that a few
-    // thousand workgroups are in flight
-    auto slices = [&](int tiles, int rows) {
-        int z = (4 * ctx->n_cu + tiles - 1) / tiles;          // two workgroups per CU at a time
-        const int max_z = (rows + 2 * WG_Q - 1) / (2 * WG_Q);
-        if (z > max_z) z = max_z;
-        return z < 1 ? 1 : z;
+    // weight and bias gradients: contractions over all nodes
+    typedef void (*wgrad_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, float *, float *);
+    auto weight_grad = [&](wgrad_kernel wide, wgrad_kernel small, int K_out, const int32_t *list, int rows, const float *table, int L,
+                           const float *dg, int cols, float *out, float *bias_out) {
+        const WgPlan p = wg_plan(K_out, cols, rows, ctx->n_cu);
+        hipLaunchKernelGGL(p.wide ? wide : small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, cols, out,
+                           bias_out);
     };
     if (n_int > 0) {
-        const dim3 grid((2 * H + WG_TILE - 1) / WG_TILE, (dg_cols + WG_TILE - 1) / WG_TILE, 1);
+        const bool v4 = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0);
         float *acc = rntn ? ctx->rntn_acc : d_u, *colsum = rntn ? ctx->rntn_acc + (size_t)2 * H * rntn_row : d_b;
-        hipLaunchKernelGGL(k_weight_grad<2>, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_int)), dim3(256), 0, st, f,
-                           (const int32_t *)f.level_nodes, n_int, (const float *)h, H, (const float *)dg_int, dg_cols, acc, colsum);
+        weight_grad(k_weight_grad_wide<2>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
+                    f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,
                            (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H);
     if (lstm) {
-        const dim3 grid((E + WG_TILE - 1) / WG_TILE, (3 * H + WG_TILE - 1) / WG_TILE, 1);
-        hipLaunchKernelGGL(k_weight_grad<1>, dim3(grid.x, grid.y, slices(grid.x * grid.y, n_leaf)), dim3(256), 0, st, f,
-                           (const int32_t *)f.leaf_list, n_leaf, (const float *)ctx->emb, E, (const float *)dg_leaf, 3 * H, d_w_leaf,
-                           d_b_leaf);
+        const bool v4 = E % 4 == 0 && H % 4 == 0;
+        weight_grad(k_weight_grad_wide<1>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
+                    n_leaf, ctx->emb, E, dg_leaf, 3 * H, d_w_leaf, d_b_leaf);
     }
     TL_HIP(hipGetLastError());
     if (status_pending) {

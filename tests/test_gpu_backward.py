@@ -507,26 +507,32 @@ def rnn_gate_gradients(p, trees, h, g_h):
     return dg
 
 
-@pytest.mark.parametrize("d", [33, 130])
+@pytest.mark.parametrize("d,more", [(33, 0), (130, 0), (250, 1800)])
 @pytest.mark.parametrize("what", ["infinite", "near the largest", "small"])
-def test_weight_gradient_outside_the_ordinary_range(what, d):
+def test_weight_gradient_outside_the_ordinary_range(what, d, more):
     """An upstream gradient that is infinite, beyond the largest bf16 number, or far below one: the sums are those of fp32
     instructions.  TreeRNN; the gradient enters at a node over two leaves, so one column of d_u holds it and the others are
-    ordinary.  Tolerance: 54 terms of at most |dg| each (|h| <= 1), each dg a sum over d products before that, so
-    (54 + 2 d) 2^-24 of the largest |dg| (of the column itself where that is the one with the large value)."""
-    print("case weight gradient, upstream", what, d, flush=True)
+    ordinary.  `more` trees without any gradient take the batch to the kernel for many nodes.  Tolerance: 54 terms of at
+    most |dg| each (|h| <= 1), each dg a sum over d products before that, so (54 + 2 d) 2^-24 of the largest |dg| (of the
+    column itself where that is the one with the large value)."""
+    print("case weight gradient, upstream", what, d, more, flush=True)
     p = synth.make_rnn_params(140, synth.CELL_TREERNN, 50, d, scale=0.1)
     p.emb *= np.float32(0.02 if what == "near the largest" else 8)
-    trees = synth.make_trees(141, [9, 2, 30, 1, 17], ["random"] * 5, 50)
-    inner = np.flatnonzero(trees.left >= 0)
+    leaves = [9, 2, 30, 1, 17] + [5 + (29 * t) % 46 for t in range(more)]
+    trees = synth.make_trees(141, leaves, ["random"] * len(leaves), 50)
+    n = int(trees.tree_off[5])                             # the nodes that have a gradient
+    first, _ = synth.subset(trees, list(range(5)))
+    assert np.array_equal(first.left, trees.left[:n])
+    inner = np.flatnonzero(first.left >= 0)
     assert len(inner) == 54
     rng = np.random.default_rng(142)
-    g_h = rng.standard_normal((trees.n_nodes, d)).astype(np.float32)
+    g_h = np.zeros((trees.n_nodes, d), np.float32)
+    g_h[:n] = rng.standard_normal((n, d))
     special = np.zeros(d, bool)
     if what == "small":
         g_h *= np.float32(1e-37)
     else:
-        at = inner[(trees.left[trees.left[inner]] < 0) & (trees.left[trees.right[inner]] < 0)][2]
+        at = inner[(first.left[first.left[inner]] < 0) & (first.left[first.right[inner]] < 0)][2]
         g_h[at, 5] = np.inf if what == "infinite" else np.float32(3.4e38)
         special[5] = True
     net = binding.TreeNet(p, scheduler="level_device")
@@ -534,17 +540,18 @@ def test_weight_gradient_outside_the_ordinary_range(what, d):
         b = net.load(trees)
         net.forward()
         got = binding.tl_backward(net.ctx, b, torch.from_numpy(g_h).cuda(), d)
-        got = {k: v.cpu().numpy() for k, v in got.items()}
-        h = b["h"].cpu().numpy()
+        got = {k: v.cpu().numpy().astype(np.float64) for k, v in got.items()}
+        h = b["h"].cpu().numpy()[:n]
     finally:
         net.close()
     with np.errstate(all="ignore"):
-        ref = oracle.backward(p, trees, h, None, g_h)
-        dg = np.abs(rnn_gate_gradients(p, trees, h, g_h))
-    scale = np.where(special, np.where(np.isfinite(dg), dg, 0.0).max(axis=0), dg[:, ~special].max())
+        dg = rnn_gate_gradients(p, first, h, g_h[:n])
+        a = np.concatenate([h[first.left[inner]], h[first.right[inner]]], axis=1).astype(np.float64)
+        ref = dict(d_u=(a[:, :, None] * dg[inner][:, None, :]).sum(axis=0), d_b=dg[inner].sum(axis=0))
+    scale = np.where(special, np.where(np.isfinite(dg), np.abs(dg), 0.0).max(axis=0), np.abs(dg[:, ~special]).max())
     assert np.isinf(ref["d_u"]).any() == (what == "infinite")
     for k in ("d_u", "d_b"):
-        r, g = ref[k].astype(np.float64), got[k].astype(np.float64)
+        r, g = ref[k], got[k]
         assert np.array_equal(np.isnan(g), np.isnan(r)) and np.array_equal(np.isinf(g), np.isinf(r)), k
         assert np.array_equal(np.sign(g[np.isinf(r)]), np.sign(r[np.isinf(r)])), k
         fin = np.isfinite(r)
@@ -563,3 +570,21 @@ def test_weight_gradient_of_rows_beyond_the_largest_bf16_number():
     assert (trees.word[trees.left < 0] == 3).any()
     run_case(p, trees, 152, "embedding 3.4e38")
     run_case(p, trees, 152, "embedding 3.4e38 kept", keep=True, scheduler="dataflow")
+
+
+@pytest.mark.parametrize("cell,d,n_trees", [("lstm", 400, 190), ("lstm", 260, 320), ("lstm", 264, 330), ("rnn", 250, 1650), ("rnn", 250, 1800),
+                                            ("rntn", 47, 470), ("rntn", 48, 500), ("rntn", 48, 440)])
+def test_weight_gradient_on_both_sides_of_the_rule(cell, d, n_trees):
+    """Outputs whose last tiles of 128 (wide form) or 64 are partly filled, with node counts on both sides of the line between the two
+    kernels; slices of a few hundred nodes that are no multiple of 32."""
+    print("case weight gradient", cell, d, n_trees, flush=True)
+    leaves = [5 + (29 * t) % 46 for t in range(n_trees)]
+    trees = synth.make_trees(160, leaves, ["random"] * n_trees, 300)
+    what = "%s %d, %d trees" % (cell, d, n_trees)
+    if cell == "lstm":
+        params = synth.make_treelstm_params(161, 300, 290, d, "xavier")
+        run_case(params, trees, 162, what, keep=True, scheduler="dataflow", whole_batch=True)
+    elif cell == "rnn":
+        run_rnn_case(synth.make_rnn_params(161, synth.CELL_TREERNN, 300, d, scale=0.05), trees, 162, what, whole_batch=True)
+    else:
+        run_rntn_case(synth.make_rnn_params(161, synth.CELL_RNTN, 300, d, scale=0.05), trees, 162, what, whole_batch=True)
