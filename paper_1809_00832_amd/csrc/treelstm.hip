@@ -70,7 +70,8 @@ struct tl_ctx {
     int split = 0;                    // k-steps per wave of the split cell (data-flow scheduler, fp32 TreeLSTM), 0 = not used
     int hx_steps = 0;                 // 128-byte lines per row of the split copy of h
     int flow_grid = 0;                // workgroups of the data-flow kernel
-    unsigned *hx = nullptr;           // split copy of h, cap_nodes rows
+    unsigned *hx = nullptr;           // split copy of h, cap_split rows
+    int cap_split = 0;                // nodes that hx and sched have room for
     int4 *sched = nullptr;            // schedule of its kernel: blocks of 16 entries, as many blocks as internal nodes at most
     int4 *sched_head = nullptr;       // first block, number of blocks and trees of every slot
     _Float16 *xp_inner = nullptr;     // its packed weights and their scales
@@ -583,8 +584,6 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     const int B = n_trees > ctx->cap_trees ? n_trees : ctx->cap_trees;
     if (ctx->ws) { TL_HIP(hipFree(ctx->ws)); ctx->ws = nullptr; }
     if (ctx->hb) { TL_HIP(hipFree(ctx->hb)); ctx->hb = nullptr; }
-    if (ctx->hx) { TL_HIP(hipFree(ctx->hx)); ctx->hx = nullptr; }
-    if (ctx->sched) { TL_HIP(hipFree(ctx->sched)); ctx->sched = nullptr; }
     if (ctx->flow_ws) { TL_HIP(hipFree(ctx->flow_ws)); ctx->flow_ws = nullptr; }
     if (ctx->host_levels) { TL_HIP(hipHostFree(ctx->host_levels)); ctx->host_levels = nullptr; }
     ctx->cap_nodes = ctx->cap_trees = 0;
@@ -596,18 +595,34 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
         TL_HIP(hipMalloc(&ctx->hb, hb_bytes));
         TL_HIP(hipMemset(ctx->hb, 0, hb_bytes));   // the padding at the end of each row stays zero for good
     }
-    if (ctx->split > 0) {
-        const size_t hx_bytes = (size_t)N * ctx->hx_steps * 128;
-        TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
-        TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));   // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
-    }
-    if (ctx->split > 0) TL_HIP(hipMalloc(&ctx->sched, ((size_t)N / 2 + 1) * 16 * sizeof(int4)));
-    else if (ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
+    if (ctx->split == 0 && ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
         TL_HIP(hipMalloc(&ctx->flow_ws, flow_bytes(ctx->n_cg, (size_t)N)));
     TL_HIP(hipHostMalloc(&ctx->host_levels, (size_t)(N + 2) * 4, hipHostMallocDefault));
     ctx->ws_bytes = bytes;
     ctx->cap_nodes = N;
     ctx->cap_trees = B;
+    return TL_OK;
+}
+
+// The split cell addresses nodes and rows of the split copy of h with 24-bit row numbers and 32-bit byte offsets.
+bool in_split_range(const tl_ctx *ctx, int n_nodes)
+{
+    return n_nodes < (1 << 24) && (unsigned long long)n_nodes * ctx->hx_steps * 128ull < (1ull << 32);
+}
+// What the split cell needs beside the workspace: its copy of h and its schedule.  Only where it runs: a batch beyond its range
+// goes to the level scheduler, and would leave as much memory idle as h takes.  Called behind ensure_workspace.
+int ensure_split(tl_ctx *ctx, int n_nodes)
+{
+    if (n_nodes <= ctx->cap_split) return TL_OK;
+    TL_HIP(hipDeviceSynchronize());
+    if (ctx->hx) { TL_HIP(hipFree(ctx->hx)); ctx->hx = nullptr; }
+    if (ctx->sched) { TL_HIP(hipFree(ctx->sched)); ctx->sched = nullptr; }
+    ctx->cap_split = 0;
+    const size_t N = (size_t)(in_split_range(ctx, ctx->cap_nodes) ? ctx->cap_nodes : n_nodes), hx_bytes = N * ctx->hx_steps * 128;
+    TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
+    TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));       // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
+    TL_HIP(hipMalloc(&ctx->sched, (N / 2 + 1) * 16 * sizeof(int4)));
+    ctx->cap_split = (int)N;
     return TL_OK;
 }
 
@@ -1065,8 +1080,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool persistent = cfg.scheduler != TL_SCHED_LEVEL_HOST;
     // the data-flow scheduler needs the weight-stationary cell and its private lists; without them (RNTN, sizes the
     // cell does not take, the fixed workspace) the level scheduler on the device stands in.
-    const bool split_range = n_nodes < (1 << 24) && (unsigned long long)n_nodes * ctx->hx_steps * 128ull < (1ull << 32);
-    const int split = split_range ? ctx->split : 0;
+    const int split = in_split_range(ctx, n_nodes) ? ctx->split : 0;
     const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_grid > 0 &&
                       (cfg.cell == TL_TREELSTM && !bf16 ? split > 0 : spw > 0);
     // A batch of few large trees: the data-flow scheduler deals whole trees to its sets of workgroups, so with fewer
@@ -1082,6 +1096,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         f.hs = ctx->hs;
     }
     if (flow && split > 0) {
+        if ((rc = ensure_split(ctx, n_nodes)) != TL_OK) return rc;
         f.hx = ctx->hx;
         f.hx_steps = ctx->hx_steps;
         f.sched = ctx->sched; f.sched_head = ctx->sched_head;

@@ -6,6 +6,7 @@ error of about 1e-6; 2e-5 relative + 2e-6 absolute leaves an order of magnitude 
 compared with elsewhere)."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_1809_00832_amd import binding, synth
@@ -141,3 +142,38 @@ def test_a_nan_is_a_result_whatever_its_payload(where, bits):
         assert np.isnan(ref[key]).any() or (where != "emb" and key == "c")
         assert np.array_equal(np.isnan(got[key]), np.isnan(ref[key])), key
         np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key, equal_nan=True)
+
+
+def test_batches_beyond_the_range_of_the_split_cell_cost_no_copy_of_h():
+    """2^24 nodes and more go to the level scheduler: nothing is allocated for a cell that does not run, results are those of
+    the checker, and the next batch in range is evaluated as always."""
+    print("case split range", flush=True)
+    H, V = 2, 50
+    p = synth.make_treelstm_params(960, V, 8, H, "xavier")
+    B = (1 << 24) // 3 + 5
+    node = np.arange(3 * B, dtype=np.int32)
+    root = node % 3 == 0
+    trees = synth.TreeBatch(np.arange(0, 3 * B + 1, 3, dtype=np.int32), np.where(root, node + 1, -1).astype(np.int32),
+                            np.where(root, node + 2, -1).astype(np.int32), np.where(root, -1, (node * 7) % V).astype(np.int32))
+    assert trees.n_nodes >= 1 << 24
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        net.load(trees)
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        net.forward()
+        assert binding.tl_status(net.ctx) == 0
+        used = free - torch.cuda.mem_get_info()[0]
+        # 48 bytes of parents, counters and lists a node; a copy of h would take 128 more, a schedule as many again
+        assert used < 64 * trees.n_nodes, used / trees.n_nodes
+        some = np.concatenate([np.arange(40), np.arange(B - 40, B)])
+        sub, orig = synth.subset(trees, [int(t) for t in some])
+        ref = oracle.forward_params(p, sub, n_threads=8)
+        for key in ("h", "c"):
+            np.testing.assert_allclose(net.batch[key].cpu().numpy()[orig], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+        small = synth.make_trees(961, [5, 1, 90, 33], ["random"] * 4, V)
+        got, ref = net.run(small), oracle.forward_params(p, small, n_threads=8)
+        for key in ("h", "c"):
+            np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+    finally:
+        net.close()
