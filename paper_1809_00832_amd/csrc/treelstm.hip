@@ -598,6 +598,7 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     if (ctx->split == 0 && ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
         TL_HIP(hipMalloc(&ctx->flow_ws, flow_bytes(ctx->n_cg, (size_t)N)));
     TL_HIP(hipHostMalloc(&ctx->host_levels, (size_t)(N + 2) * 4, hipHostMallocDefault));
+    TL_HIP(hipStreamSynchronize(nullptr));     // the caller's stream need not be ordered behind the null stream's memsets
     ctx->ws_bytes = bytes;
     ctx->cap_nodes = N;
     ctx->cap_trees = B;
@@ -622,6 +623,7 @@ int ensure_split(tl_ctx *ctx, int n_nodes)
     TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
     TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));       // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
     TL_HIP(hipMalloc(&ctx->sched, (N / 2 + 1) * 16 * sizeof(int4)));
+    TL_HIP(hipStreamSynchronize(nullptr));         // as in ensure_workspace
     ctx->cap_split = (int)N;
     return TL_OK;
 }
@@ -953,6 +955,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     }
     TL_HIP(hipHostMalloc(&ctx->host_ctl, sizeof(Ctl), hipHostMallocDefault));
     if ((rc = scratch_address(ctx->device, &ctx->scratch)) != TL_OK) return rc;
+    TL_HIP(hipDeviceSynchronize());
     return TL_OK;
 }
 

@@ -177,3 +177,25 @@ def test_batches_beyond_the_range_of_the_split_cell_cost_no_copy_of_h():
             np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
     finally:
         net.close()
+
+
+def test_first_call_on_a_stream_of_its_own():
+    """A stream that does not wait for the null stream: what a context clears when it allocates is clear before the call's
+    kernels run, also when the workspace grows."""
+    print("case split, stream of its own", flush=True)
+    H, E = 33, 1025
+    p = synth.make_treelstm_params(970, 40, E, H, "xavier")
+    batches = [synth.make_trees(971, [30, 7, 1], ["random"] * 3, 40), synth.make_trees(972, [50] * 400, ["random"] * 400, 40)]
+    stream = torch.cuda.Stream()
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        for trees in batches:
+            net.load(trees)
+            torch.cuda.synchronize()
+            net.forward(stream.cuda_stream)
+            assert binding.tl_status(net.ctx) == 0
+            ref = oracle.forward_params(p, trees, n_threads=8)
+            for key in ("h", "c"):
+                np.testing.assert_allclose(net.batch[key].cpu().numpy(), ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+    finally:
+        net.close()
