@@ -67,8 +67,9 @@ __global__ __launch_bounds__(WG_THREADS, S <= 4 ? 2 : 1) void k_leaf_split(Fwd f
     const int lo = slot * share, hi = min(f.n_leaf, lo + share);
     if (decided_to_leave(&sm.leave, leave)) return;
     split_leaves<S, KEEP>(sm, f, lo, hi, cg, w);
-    // data-flow scheduler: the stores that mark the internal nodes' rows (last: a load behind them would wait for them)
-    if (f.flow == 2) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
+    // data-flow scheduler: the stores that mark the internal nodes' rows (last: a load behind them would wait for them).  Where the
+    // level kernel will run instead nobody reads the marks (three balanced trees of 2 000 leaves, H = 64: 93.5 -> 91.4 us)
+    if (f.flow == 2 && !internal_kernel_skipped(f)) flow_fill(f, (size_t)wg * 4 + (tid >> 6), (size_t)n_wg * 4);
 }
 
 // Leaves with bf16 operands (weight-stationary cell): rows come from a bf16 copy of the embedding table (rows padded with

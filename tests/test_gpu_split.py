@@ -199,3 +199,20 @@ def test_first_call_on_a_stream_of_its_own():
                 np.testing.assert_allclose(net.batch[key].cpu().numpy(), ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
     finally:
         net.close()
+
+
+@pytest.mark.parametrize("H", [35, 64])
+def test_few_large_trees_of_either_kind_one_after_the_other(H):
+    """Both kernels of the internal nodes are launched for few large trees, the marks are set only for the one that waits
+    for them: bushy trees, then deep ones, then bushy ones again through one context."""
+    print("case split, few large trees", H, flush=True)
+    p = synth.make_treelstm_params(980, 40, 50, H, "xavier")
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        for i, shape in enumerate(["balanced", "chain", "random", "chain"]):
+            trees = synth.make_trees(981 + i, [300, 200, 400], [shape] * 3, 40)
+            got, ref = net.run(trees), oracle.forward_params(p, trees, n_threads=8)
+            for key in ("h", "c", "h_root", "c_root"):
+                np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg="%s %s" % (shape, key))
+    finally:
+        net.close()
