@@ -109,20 +109,6 @@ __device__ inline void split_gates_plain(const Fwd &f, const SplitGemm &x, int s
     }
 }
 
-// Slot and column group of a workgroup.  Workgroups are dealt to the L2 domains round-robin; where whole slots fit into the
-// domains, a slot is kept inside one, so that its rows cross the fabric once and its dependent rows not at all.
-__device__ inline void split_place(const Fwd &f, int *slot, int *member)
-{
-    const int i = blockIdx.x / N_XCD;
-    if (f.n_slots % N_XCD == 0) {
-        *member = i % f.n_cg;
-        *slot = (i / f.n_cg) * N_XCD + blockIdx.x % N_XCD;
-    } else {
-        *member = blockIdx.x % f.n_cg;
-        *slot = blockIdx.x / f.n_cg;
-    }
-}
-
 // Evaluates the blocks of one slot's schedule (structure.hpp, flow_schedule) for column group cg: 16 internal nodes a block,
 // every node's children in earlier blocks, the rows of a block requested while the block before is computed - or,
 // where a row of it comes out of that very block, once its results are stored.

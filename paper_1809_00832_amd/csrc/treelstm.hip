@@ -918,10 +918,8 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         }
         ctx->flow_grid = o_min * ctx->n_cu;
         if (ctx->split > 0) {
-            const int per_domain = ctx->flow_grid / N_XCD / ctx->n_cg * N_XCD, slots = ctx->flow_grid / ctx->n_cg;
-            if (10 * per_domain >= 9 * slots) ctx->flow_grid = per_domain * ctx->n_cg;      // slots inside L2 domains (see split_place)
             if ((rc = allow_lds(k_flow_schedule, SCHED_LDS_BYTES)) != TL_OK) return rc;
-            TL_HIP(hipMalloc(&ctx->sched_head, (size_t)(slots + 1) * sizeof(int4)));
+            TL_HIP(hipMalloc(&ctx->sched_head, (size_t)(ctx->flow_grid / ctx->n_cg + 1) * sizeof(int4)));
         }
         if (ctx->flow_grid < ctx->n_cg) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
     }
