@@ -296,6 +296,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
     constexpr int NG = EpiTraits<EPI>::NG;
     constexpr int SEG = EpiTraits<EPI>::SEG;
     constexpr int NL = WsLoadGeom<SPW>::NL;
+    static_assert(!(FLOW && EPI == EPI_LSTM_INNER), "the fp32 TreeLSTM has a cell of its own under the data-flow scheduler (cell_split.hpp)");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nrb = (count + 15) >> 4;
     const int H = f.H;
@@ -354,10 +355,6 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
         }
         if (ev) {
             const unsigned o = (unsigned)enode * row_b + hu_b;
-            if constexpr (FLOW && EPI == EPI_LSTM_INNER) {      // a child's c element may arrive after its h row
-                cl = flow_wait_c<COH>(f, rs_c, (unsigned)sm.src0[erow & (WS_TABLE_ROWS - 1)] * row_b + hu_b, cl);
-                cr = flow_wait_c<COH>(f, rs_c, (unsigned)sm.src1[erow & (WS_TABLE_ROWS - 1)] * row_b + hu_b, cr);
-            }
             if constexpr (EPI == EPI_LSTM_INNER) {
                 float cc, hh;
                 lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, kept_gates(f, enode, hu), H);
@@ -389,11 +386,12 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
     float p_cl = 0.f, p_cr = 0.f;
     int p_erow = 0;
     constexpr int FINISH_AFTER = SPW > 1 ? 1 : 0;               // k-step after which the previous block is finished
-    // A piece's last block with few rows takes the narrow form below the loop (data-flow scheduler only).
-    constexpr int NARROW_MAX_RG = NG >= 3 ? 3 : 2;              // groups of four rows up to which that form is the faster one
+    // A piece's last block with few rows takes the narrow form below the loop (TreeRNN under the data-flow scheduler only: in
+    // top-down generation the place of a node in a tile depends on timing, and its bits must not).
+    constexpr bool NARROW_FORM = FLOW && EPI != EPI_TD_CHILD;
+    constexpr int NARROW_MAX_RG = 2;                            // groups of four rows up to which that form is the faster one
     const int n_rg = (count - (nrb - 1) * 16 + 3) >> 2;         // groups of four rows in the last block
-    // (not in top-down generation: there the place of a node in a tile depends on timing, and its bits must not)
-    const bool last_narrow = FLOW && EPI != EPI_TD_CHILD && nrb > 0 && n_rg <= NARROW_MAX_RG;
+    const bool last_narrow = NARROW_FORM && nrb > 0 && n_rg <= NARROW_MAX_RG;
     const int nrb_full = last_narrow ? nrb - 1 : nrb;
     for (int rb = 0; rb < nrb_full; ++rb) {
         float *red = sm.red[rb & 1];
@@ -457,7 +455,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
         // rb + 2, after every wave has passed the barrier inside block rb + 2, hence after it has
         // read this buffer (inside block rb + 1)
     }
-    if constexpr (FLOW) {
+    if constexpr (NARROW_FORM) {
         // The 16x16x4 instruction takes 32 cycles however many of its 16 rows exist, and the dependent steps of a deep tree
         // are blocks of one to four rows.  The 4x4x1 instruction (16 independent 4x4 products, 8 cycles) takes the same B
         // operands - lane l holds U[k(l >> 4)][l & 15] - when its 16 products are read as (k class l >> 4) x (four hidden
@@ -477,7 +475,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
             const int n_hu = cg * HU + (nl >> 2);
             const bool n_hu_ok = n_hu < H;
             const unsigned n_hu_b = (unsigned)(n_hu_ok ? n_hu : 0) * 4u;
-            auto finish_narrow = [&](const float *red, int enode, bool ev, float cl, float cr, int erow, const float (&bias)[NG]) {
+            auto finish_narrow = [&](const float *red, int enode, bool ev, const float (&bias)[NG]) {
                 float gate[NG];
 #pragma unroll
                 for (int g = 0; g < NG; ++g) {
@@ -485,62 +483,31 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
                     const float q = ((p.x + p.y) + p.z) + p.w;
                     gate[g] = (((quad_bcast<0>(q) + quad_bcast<1>(q)) + quad_bcast<2>(q)) + quad_bcast<3>(q)) + bias[g];
                 }
-                if (ev) {
-                    const unsigned o = (unsigned)enode * row_b + n_hu_b;
-                    if constexpr (FLOW && EPI == EPI_LSTM_INNER) {
-                        cl = flow_wait_c<COH>(f, rs_c, (unsigned)sm.src0[erow & (WS_TABLE_ROWS - 1)] * row_b + n_hu_b, cl);
-                        cr = flow_wait_c<COH>(f, rs_c, (unsigned)sm.src1[erow & (WS_TABLE_ROWS - 1)] * row_b + n_hu_b, cr);
-                    }
-                    const bool writer = (nl & 3) == 0;               // the four lanes of a quad hold the same result
-                    if constexpr (EPI == EPI_LSTM_INNER) {
-                        float cc, hh;
-                        lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, writer ? kept_gates(f, enode, n_hu) : nullptr, H);
-                        if (writer) {
-                            buf_st_f<COH>(rs_c, o, cc);
-                            buf_st_f<COH>(rs_h, o, hh);
-                        }
-                    } else if constexpr (EPI == EPI_TD_CHILD) {
-                        const float i = sigmoid_f(gate[0]), fg = sigmoid_f(gate[1]), og = sigmoid_f(gate[2]), u = tanh_f(gate[3]);
-                        const float cc = __builtin_fmaf(fg, cl, i * u);
-                        if (writer) {
-                            buf_st_f<COH>(rs_c, o, cc);
-                            buf_st_f<COH>(rs_h, o, og * tanh_f(cc));
-                        }
-                    } else {
-                        if (writer) buf_st_f<COH>(rs_h, o, tanh_f(gate[0]));
-                    }
-                }
+                // (the four lanes of a quad hold the same result)
+                if (ev && (nl & 3) == 0) buf_st_f<COH>(rs_h, (unsigned)enode * row_b + n_hu_b, tanh_f(gate[0]));
             };
 
-            int n_enode = -1, n_erow = 0;
+            int n_enode = -1;
             bool n_ev = false;
-            float n_cl = 0.f, n_cr = 0.f, n_bias[NG];
-            // the row a lane finishes in group rg, and its c operands (a value that shows "not written" is asked for again
-            // when the row is finished)
-            auto request_c = [&](int rg) {
-                n_erow = rb * 16 + rg * 4 + wave;
-                n_enode = n_erow < count ? sm.node[n_erow] : -1;
+            float n_bias[NG];
+            auto row_to_finish = [&](int rg) {                  // of this lane in group rg
+                const int erow = rb * 16 + rg * 4 + wave;
+                n_enode = erow < count ? sm.node[erow] : -1;
                 n_ev = n_enode >= 0 && n_hu_ok;
-                if (EPI == EPI_LSTM_INNER) {
-                    n_cl = buf_ld_f<COH>(rs_c, (unsigned)sm.src0[n_erow & (WS_TABLE_ROWS - 1)] * row_b + n_hu_b);
-                    n_cr = buf_ld_f<COH>(rs_c, (unsigned)sm.src1[n_erow & (WS_TABLE_ROWS - 1)] * row_b + n_hu_b);
-                } else if (EPI == EPI_TD_CHILD) {
-                    n_cl = buf_ld_f<COH>(rs_c, (unsigned)sm.src0[n_erow & (WS_TABLE_ROWS - 1)] * row_b + n_hu_b);
-                }
             };
             if (!flow_wait_rows<float, COH, WsRowRequest<SEG, SPW, float, TAIL>, NL, WsLoadGeom<SPW>::RPL>(f, req, rows, req.sub))
                 sm.cmd[7] = 1;
             ws_park_rows<SPW>(sm, rows, wave, lane);
             hook(rb);
-            request_c(0);
+            row_to_finish(0);
 #pragma unroll
             for (int g = 0; g < NG; ++g) n_bias[g] = __shfl(w.bias[g], nl >> 2);
 #pragma unroll 1
             for (int rg = 0; rg < n_rg; ++rg) {
                 if (rg > 0) {
                     __syncthreads();                        // every wave has written its partial sums of group rg - 1
-                    finish_narrow(sm.red[(rb + rg - 1) & 1], n_enode, n_ev, n_cl, n_cr, n_erow, n_bias);
-                    request_c(rg);
+                    finish_narrow(sm.red[(rb + rg - 1) & 1], n_enode, n_ev, n_bias);
+                    row_to_finish(rg);
                 }
                 __builtin_amdgcn_sched_barrier(0);
                 floatx4 acc[NG];
@@ -573,7 +540,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
             }
             hook(-2);
             __syncthreads();
-            finish_narrow(sm.red[(rb + n_rg - 1) & 1], n_enode, n_ev, n_cl, n_cr, n_erow, n_bias);
+            finish_narrow(sm.red[(rb + n_rg - 1) & 1], n_enode, n_ev, n_bias);
             __syncthreads();
             return;
         }
