@@ -4,7 +4,7 @@
 One step = one tl_forward over one batch: structure pass, leaf cells, internal cells (scheduling
 included) and root gather, with the batch and the parameters already resident in device memory.
 
-Prints ONE JSON line.  `value` is trees/s of the whole step; `roofline` is about the dominant
+Prints ONE short JSON line on stdout (and before it, on stderr, one with everything else that was measured).  `value` is trees/s of the whole step; `roofline` is about the dominant
 kernel (the internal-node kernel) with its duration taken from HIP events recorded by the library on
 the stream it launches on; `cpu_baseline` is the CPU checker timed on this host.
 """
@@ -439,6 +439,15 @@ def copy_calibration(mib=1024, reps=3):
                       "launches": reps}))
 
 
+HEADLINE_LEAVES_OUT = ("comparison", "other_configs", "training", "topdown", "backward", "head", "span_bound")
+
+
+def headline(out):
+    """The fields of the line on stdout: the metric, its configuration and how the time is made up.  Short enough for a
+    reader that keeps the end of the output only; what is left out goes to stderr."""
+    return {k: v for k, v in out.items() if k not in HEADLINE_LEAVES_OUT}
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -553,7 +562,9 @@ def main():
         out["topdown"] = {"rows": topdown_rows(min(args.steps, 20), min(args.warmup, 5), False), "note": TOPDOWN_NOTE}
     if not args.no_cpu:
         out["cpu_baseline"] = cpu_baseline(w)
-    print(json.dumps(out))
+    # One short JSON line on stdout, last; everything measured (the other schedulers, workloads, training) on stderr before it.
+    print(json.dumps(out), file=sys.stderr, flush=True)
+    print(json.dumps(headline(out)), flush=True)
 
 
 if __name__ == "__main__":

@@ -21,3 +21,20 @@ def test_cpu_baseline_sample_is_bounded():
     assert small["kind"] == "oracle" and small["unit"] == "trees/s" and small["value"] > 0 and "all 4 trees" in small["sample"]
     big = bench.cpu_baseline(synth.workload("sentence"), max_nodes=300)
     assert "of the 25 trees" in big["sample"] and big["cores"] >= 1
+
+
+def test_the_line_on_stdout_is_short_and_complete():
+    """What other schedulers, workloads and training steps were measured at does not go into the headline line."""
+    import json
+    sys.path.insert(0, ROOT)
+    import bench
+    keys = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data",
+            "config", "roofline", "stage_ms", "cpu_baseline")
+    out = {k: 0.123456789012345 for k in keys}
+    out["roofline"] = {"k%d" % i: 0.123456789012345 for i in range(12)}
+    out["cpu_baseline"] = bench.cpu_baseline(__import__("paper_1809_00832_amd.synth", fromlist=["x"]).workload("tiny"))
+    for k in bench.HEADLINE_LEAVES_OUT:
+        out[k] = ["x" * 100] * 100
+    line = json.dumps(bench.headline(out))
+    assert len(line) < 3000
+    assert set(keys) == set(json.loads(line))
