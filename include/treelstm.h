@@ -62,7 +62,11 @@ typedef struct tl_ctx tl_ctx;
 
 enum tl_cell { TL_TREELSTM = 0, TL_TREERNN = 1, TL_RNTN = 2 };
 
-/* TL_F32: fp32 operands, fp32 accumulation.  TL_BF16_IN: weights, embeddings and the
+/* TL_F32: fp32 operands, fp32 accumulation.  (The leaves of TL_TREELSTM up to embed_dim 1024, and its internal nodes under
+ * TL_SCHED_DATAFLOW, form their products on the 16-bit matrix unit with every operand as two fp16 terms and fp32
+ * accumulation: an operand is met to 2^-23 of itself, or to 2^-38 of the largest of its weight column or embedding row where
+ * it is far below that one; a product to 2^-21.  The gate functions, good to about 1e-7 absolute in every path, hide the
+ * difference: against 64 bits the states' errors are the same.)  TL_BF16_IN: weights, embeddings and the
  * gathered child h are rounded to bfloat16 (nearest even) as matrix operands;
  * accumulation, gate functions, c and the stored h stay fp32. */
 enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
@@ -107,8 +111,10 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  *                        this is the fastest choice for deep or narrow batches and as fast as
  *                        TL_SCHED_LEVEL_DEVICE on wide ones.  Consequence: if the parameters or
  *                        embeddings hold NaNs whose bits are all ones, a forward ends with
- *                        TL_ESTALL instead of NaN results.  Where the weight-stationary cell is not
- *                        used (TL_RNTN, hidden > 512, odd hidden in TL_F32, tl_forward_noalloc)
+ *                        TL_ESTALL instead of NaN results.  (TL_TREELSTM in TL_F32: one workgroup per
+ *                        set works out the order of the nodes for all of them, beside the leaves' cells.)
+ *                        Where its cells are not used (TL_RNTN, hidden > 512, odd hidden of TL_TREERNN in
+ *                        TL_F32, tl_forward_noalloc, batches of 2^24 nodes or 4 GiB of h and more)
  *                        TL_SCHED_LEVEL_DEVICE stands in.  Whole trees are dealt to the sets, so a
  *                        batch of fewer trees than the device has sets leaves sets idle; if its trees
  *                        have 256 nodes or more on average, both this kernel and that of
@@ -117,13 +123,16 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  *                        level on all sets; otherwise deep narrow ones, data-flow).  A batch in which
  *                        one large bushy tree stands beside many small ones is better served by
  *                        TL_SCHED_LEVEL_DEVICE.  Unreachable nodes: TL_ESTRUCT.
- * Results do not depend on the scheduler: all paths of one precision sum a node's
- * contraction in the same order, so all of them agree bit for bit and repeat their bits from
- * run to run.  One exception: in TL_F32, TL_SCHED_DATAFLOW evaluates the dependent steps of few
- * rows (the last block of up to 12 rows of each piece of its lists) with a narrower matrix
- * instruction that rounds the same sum in another order; which nodes those are is fixed by the
- * batch, so it repeats its own bits from run to run and agrees with the other schedulers to
- * rounding (relative 2e-5 in the tests). */
+ * All paths repeat their bits from run to run, and TL_SCHED_READY, _READY_PRIORITY, _LEVEL_DEVICE and
+ * _LEVEL_HOST of one precision agree bit for bit: they sum a node's contraction in the same
+ * order.  So does TL_SCHED_DATAFLOW in TL_BF16_IN.  In TL_F32 it agrees with them to rounding (relative
+ * 2e-5 in the tests): a TL_TREELSTM's internal nodes are summed from split operands (above), and a
+ * TL_TREERNN's dependent steps of few rows (the last block of up to 8 rows of each piece of its
+ * lists) with a narrower matrix instruction that rounds the same sum in another order; which nodes
+ * those are is fixed by the batch.  A node's bits do not depend on the rest of the batch, with two
+ * exceptions: those narrow blocks, and a TL_F32 TL_TREELSTM batch of 2^24 nodes or 4 GiB of h and more, whose
+ * leaves are summed by fp32 instructions (as all leaves are with embed_dim > 1024 or a table of 2^24 words or 4 GiB and
+ * more). */
 enum tl_scheduler { TL_SCHED_READY = 0, TL_SCHED_LEVEL_DEVICE = 1, TL_SCHED_LEVEL_HOST = 2, TL_SCHED_READY_PRIORITY = 3,
                     TL_SCHED_DATAFLOW = 4 };
 
@@ -208,7 +217,8 @@ int tl_forward(tl_ctx *ctx, int n_trees, int n_nodes,
 /*
  * tl_forward for callers that cannot allocate device memory while they run: code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels and
- * the same results bit for bit as tl_forward, but the scheduler state (parent links, ready
+ * the same results bit for bit as tl_forward (TL_SCHED_DATAFLOW: as tl_forward under TL_SCHED_LEVEL_DEVICE, which
+ * stands in), but the scheduler state (parent links, ready
  * counters, ready queue, mailboxes, control block, and the bf16 copy of h that TL_BF16_IN gathers
  * from) lives in one fixed array that is part of the library's device code - about 17.2 MiB of
  * every GPU the library is used on, held until the process ends - instead of a workspace that the

@@ -2,14 +2,18 @@
 //
 // v_mfma_f32_16x16x4_f32 does 32 multiply-adds per clock and SIMD and occupies the vector pipe while it runs; the 16-bit
 // instruction v_mfma_f32_16x16x32_f16 does 512 and runs beside vector instructions.  A value x is split into
-// hi = fp16(x) and lo = fp16(x - hi), 11 bits each and a sign between them: hi + lo misses x by at most 2^-24 |x|, as much as
-// rounding to fp32 does.  x w = hi hi' + hi lo' + lo hi' (+ lo lo', below 2^-24 of the product, left out): three instructions,
-// exact products, fp32 accumulation, 3/16 of the fp32 instruction's time.  (Relative 2-norm error of h and c
+// hi = fp16(x) and lo = fp16(x - hi), 11 bits each and a sign between them: hi + lo misses x by at most 2^-23 |x| (three quarters of
+// all fp32 values are met exactly).  x w = hi hi' + hi lo' + lo hi' (+ lo lo', up to 2^-22 of the product, left out): three
+// instructions, exact products, fp32 accumulation, 3/16 of the fp32 instruction's time; a product is off by 2^-21 at most,
+// where the fp32 instruction rounds it to 2^-24.  (Relative 2-norm error of h and c
 // against 64 bits, with fp32 instructions / with the split: 256 parse trees at H = 512 1.1e-6 / 1.1e-6, 25 at H = 150 8.9e-7 /
-// 8.9e-7, chains of 1 024 leaves at H = 256 8.1e-7 / 8.1e-7: the gate functions decide it.)
+// 8.9e-7, chains of 1 024 leaves at H = 256 8.1e-7 / 8.1e-7: the gate functions decide it, whose absolute error of about
+// 1e-7 is that of all paths.)
 // fp16 has five exponent bits, so both sides are scaled by powers of two: h (|h| <= 1) by 2^14, every column of the weights to
-// a largest magnitude in [2^13, 2^14); a gate's sum is scaled back when its partial sums meet.  What lies more than
-// 2^28 below the largest value of its kind keeps an absolute error of 2^-39 of that value.
+// a largest magnitude in [2^13, 2^14); a gate's sum is scaled back when its partial sums meet.  The lower term of what lies
+// more than 2^15 below the largest value of its kind runs out of exponents: from there on the error is absolute, 2^-38 of that
+// largest value (2^-39 for h), so 2^-22 of a value 2^-16 of the largest, 2^-18 of one 2^-20, 2^-10 of one 2^-28.  Embedding
+// values of 1e-1 ... 1e-8 (h down to 1e-9; 25 trees, H = 150, no biases) give the errors of the fp32 instructions to two digits.
 //
 // Layout of the split copy of h (`hx`, workspace): row n holds hx_steps groups of 32 hidden units, a group is one 128-byte line
 // [32 hi][32 lo], pads zero.  It is written next to h by whoever computes a node, and lane l of a wave reads the A operand
