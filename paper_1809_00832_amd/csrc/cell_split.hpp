@@ -121,10 +121,10 @@ __device__ inline void split_gates_plain(const Fwd &f, const SplitGemm &x, int s
 // products in the order hi hi, hi lo, lo hi; the four quarter sums are added in wave order.  A node's result so depends neither
 // on its place in a block nor on the batch.
 // Measured (H = 512, 256 parse trees, kernel): 388 us with fp32 instructions and lists taken in pieces, 236 with these instructions
-// and the same lists, 173 on finished blocks.  A full block takes 2.0 us, of which 0.95 matrix instructions (2 300 clocks for
-// 120 of 16 clocks), 0.6 exchange of the quarters, gates and stores, 0.4 waiting for rows (a wave's requests of 16 rows x 64 bytes
-// leave the CU at about 25 bytes per clock); a dependent block of few rows takes 3.5 to 4 us, most of it the way of its
-// children's rows through the L2.
+// and the same lists, 173 on finished blocks, 151 with the slots spread over all L2 domains.  A wave's block is 120 matrix
+// instructions of 16 clocks and 171 other vector instructions in 6 700 clocks (matrix unit 29 % busy): products, exchange of
+// the quarters, gates and stores follow each other, and the dependent blocks at the top of the trees wait for their children's
+// rows (a dependent block of few rows takes 2.3 us at H = 256, most of it the way of those rows through the L2).
 template <int S>
 __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__restrict__ entries, int n_blocks, int cg, const SplitWeights<5, S> &w)
 {
@@ -273,7 +273,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 // that brings the quarter's largest magnitude into [2^14, 2^15); the wave scales its partial sums back before they meet.
 // What lies beyond the row's end counts as zero.  A row that holds an infinity or a NaN (and a column of weights that holds an
 // infinity) comes out as NaN here; its sums are then taken in fp32.
-// Measured (6 914 leaves, E = 300, H = 512): 81 us with fp32 instructions, 70 with these and the schedule prepared on the side; tiny
+// Measured (6 914 leaves, E = 300, H = 512): 81 us with fp32 instructions, 64 with these and the schedule prepared on the side; tiny
 // and ragged batches gain most.  What bounds it now is not the matrix unit (27 instructions a block) but the chain of a
 // block: row maximum across lanes, conversion, exchange, gates, three rows of stores.
 struct SplitLeafSmem {
