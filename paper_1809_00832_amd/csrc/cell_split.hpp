@@ -113,6 +113,22 @@ __device__ inline void split_gates_plain(const Fwd &f, const SplitGemm &x, int s
     }
 }
 
+// Slot and column group of a workgroup.  Workgroups are dealt to the L2 domains round-robin; with f.place the slots are taken from
+// one domain each as far as whole slots fit (a multiple of N_XCD of them; what is left over lies on all domains), so that a
+// slot's rows cross the fabric once and its dependent rows not at all - and its requests queue at one L2.
+__device__ inline void split_place(const Fwd &f, int *slot, int *member)
+{
+    const int b = blockIdx.x, inside = f.place ? f.n_slots / N_XCD * N_XCD : 0, first = inside * f.n_cg;
+    if (b < first) {
+        const int i = b / N_XCD;
+        *member = i % f.n_cg;
+        *slot = i / f.n_cg * N_XCD + b % N_XCD;
+    } else {
+        *member = (b - first) % f.n_cg;
+        *slot = inside + (b - first) / f.n_cg;
+    }
+}
+
 // Evaluates the blocks of one slot's schedule (structure.hpp, flow_schedule) for column group cg: 16 internal nodes a block,
 // every node's children in earlier blocks, the rows of a block requested while the block before is computed - or,
 // where a row of it comes out of that very block, once its results are stored.

@@ -162,6 +162,7 @@ struct Fwd {
     int4 *sched;                      // ... and of the split cell: blocks of 16 entries {node, left, right, flags}, see flow_schedule
     int4 *sched_head;                 // per slot {first block, blocks, trees [from, to) among which some have one node}
     int n_slots;                      // slots (sets of workgroups that cover all column groups) of its kernel
+    int place;                        // a slot's workgroups lie on one L2 domain (see split_place)
     int flow;                         // data-flow scheduler: who fills the rows of internal nodes with the "not written" pattern: 1 the reset kernel, 2 the leaf kernel
     int gang_parts;                   // ready scheduler, RNTN cell: workgroups per tile and column group (each adds up a part of the slices), 1 or RNTN_PARTS
     int pick;                         // batch of few large trees, both internal-node kernels launched: 1 this one runs if the trees are narrow, 2 if they are not (see internal_kernel_skipped)

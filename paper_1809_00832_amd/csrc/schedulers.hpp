@@ -717,11 +717,8 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
     SplitSmem &sm = *reinterpret_cast<SplitSmem *>(smem_raw);
     const int tid = threadIdx.x;
     const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));      // (a workgroup that gives up latches that)
-    // (The workgroups of a slot lie on all L2 domains, as they come.  Slots kept inside one domain, with a tenth of the sets given up for
-    // it where they do not divide evenly, were measured: 234 against 229 us at H = 512, 256 parse trees, 81.6 against 71.9 for 25 of
-    // them, 78 against 74 at H = 256, 100 trees, 47.1 against 44.6 at H = 150, 25 trees, 2 869 against 2 760 on deep trees; better
-    // only at H = 48, 44.9 against 46.2.)
-    const int member = blockIdx.x % f.n_cg, slot = blockIdx.x / f.n_cg;
+    int member, slot;
+    split_place(f, &slot, &member);
     if (tid == 0) sm.gave_up = 0;
     SplitWeights<EpiTraits<EPI_LSTM_INNER>::NG, S> w;
     split_load(w, sm.sum_of, f.xi, f.inner, member, tid >> 6, tid & 63);

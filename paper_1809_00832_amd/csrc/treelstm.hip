@@ -1163,6 +1163,16 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         // (with no internal node the data-flow kernel is not launched; where the level kernel may run instead, the root passes do)
         f.flow_roots = f.n_int > 0 && !need_levels && !flow_or_levels ? 1 : 0;
         f.n_slots = grid_p / ctx->n_cg;
+        // Slots inside one L2 domain each (split_place): the dependent steps are shorter, the requests of a slot queue at one L2.  Pays
+        // where few workgroups gather the same rows, or where a slot has no more than a tree or so and is one dependent chain.
+        // Forward, slots on all domains -> inside: H = 48, 24 chains of 100 to 300 leaves 463 -> 416 us, 64 parse trees 39.6 -> 37.6, 1 500 of
+        // them 100.8 -> 98.9; H = 80, 24 chains 512 -> 471, 12 parse trees 38.4 -> 37.0, 256 of them 53.9 -> 55.7; H = 112, 12 parse trees 40.0 ->
+        // 38.9, 60 of them 44.7 -> 45.2; H = 150, 25 parse trees (one a slot) 44.6 -> 46.1; H = 200, 24 chains 655 -> 642; H = 100, 200 chains of
+        // 60 leaves 140 -> 158; H = 256, 100 parse trees 73.6 -> 78.1, 64 trees of 1 024 leaves 2 760 -> 2 869; H = 512, one chain 468 -> 507, 25 parse
+        // trees 71.9 -> 81.6.
+        const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
+        f.place = ctx->n_cg <= 3 || (ctx->n_cg <= 10 && 4ll * n_trees <= 3ll * f.n_slots) ||
+                  (ctx->n_cg <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
         f.flow_seen = reinterpret_cast<int32_t *>(ctx->flow_ws);
         f.flow_list = reinterpret_cast<int4 *>(ctx->flow_ws + align256((size_t)ctx->n_cg * ctx->cap_nodes * sizeof(int32_t)));
     }

@@ -264,3 +264,17 @@ def test_entries_of_one_column_or_row_that_differ_by_2_to_the_30(where):
     got, ref = run(p, trees, "dataflow"), oracle.forward_params(p, trees, n_threads=8)
     for key in ("h", "c"):
         np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+
+
+@pytest.mark.parametrize("H,n_trees,leaves,shape", [(48, 90, 9, "random"), (50, 20, 9, "random"), (65, 38, 9, "random"), (65, 39, 9, "random"), (112, 27, 9, "random"),
+                                                    (150, 18, 9, "random"), (150, 19, 9, "random"), (150, 37, 70, "chain"), (177, 31, 70, "chain"),
+                                                    (250, 24, 70, "chain"), (260, 24, 70, "chain"), (250, 25, 70, "chain")])
+def test_slots_inside_one_domain_or_on_all_of_them(H, n_trees, leaves, shape):
+    """Both ways of placing the slots, on both sides of the lines between them, with numbers of slots that eight divides and
+    that it does not (what is left over lies on all domains): every slot is evaluated once, by all of its column groups."""
+    print("case split placement", H, n_trees, leaves, shape, flush=True)
+    params = synth.make_treelstm_params(1000 + H, 70, 20, H, "xavier")
+    trees = synth.make_trees(1001, [leaves - t % 5 for t in range(n_trees)], [shape] * n_trees, 70)
+    got, ref = run(params, trees, "dataflow"), oracle.forward_params(params, trees, n_threads=8)
+    for key in ("h", "c", "h_root", "c_root"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
