@@ -91,12 +91,12 @@ struct PackList {
     PackJob job[PACK_JOBS];
     int n;
 };
-__global__ void k_pack_many(PackList pl)
+__device__ inline void pack_many(const PackList &pl, size_t first, size_t stride)
 {
     for (int a = 0; a < pl.n; ++a) {
         const PackJob &j = pl.job[a];
         const size_t total = (size_t)j.n_cg * j.n_steps * j.NG * 64 * 4;
-        for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
+        for (size_t e = first; e < total; e += stride) {
             const int i = (int)(e & 3), lane = (int)((e >> 2) & 63);
             size_t r = e >> 8;
             const int g = (int)(r % j.NG);
@@ -109,9 +109,9 @@ __global__ void k_pack_many(PackList pl)
             j.wp[e] = v;
         }
         if (j.b) {
-            const int nb = j.n_cg * j.NG * HU;
-            for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < nb; e += gridDim.x * blockDim.x) {
-                const int q = e % HU, g = (e / HU) % j.NG, cg = e / (HU * j.NG);
+            const size_t nb = (size_t)j.n_cg * j.NG * HU;
+            for (size_t at = first; at < nb; at += stride) {
+                const int e = (int)at, q = e % HU, g = (e / HU) % j.NG, cg = e / (HU * j.NG);
                 const int hu = cg * HU + q;
                 j.bp[e] = hu < j.H ? j.b[g * j.H + hu] : 0.f;
             }
@@ -136,10 +136,10 @@ struct SplitPackList {
     SplitPackJob job[SPLIT_PACK_JOBS];
     int n;
 };
-__global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
+__device__ inline void pack_split_block(const SplitPackList &pl, int b)
 {
     __shared__ unsigned s_max[16], s_inf[16];
-    int b = blockIdx.x, a = 0;
+    int a = 0;
     while (a + 1 < pl.n && b >= pl.job[a].n_cg * pl.job[a].NG) {
         b -= pl.job[a].n_cg * pl.job[a].NG;
         a += 1;
@@ -195,6 +195,14 @@ __global__ __launch_bounds__(256) void k_pack_split(SplitPackList pl)
         dst[0] = hi;
         dst[64] = lo;
     }
+}
+
+// Both, side by side: the first n_split workgroups pack the split weights, the others the rest (one launch after an update; the
+// split weights' workgroups are a chain of loads, maximum and stores, 7 to 12 us, and few).
+__global__ __launch_bounds__(256) void k_repack(PackList pl, SplitPackList sl, int n_split)
+{
+    if ((int)blockIdx.x < n_split) pack_split_block(sl, blockIdx.x);
+    else pack_many(pl, (size_t)(blockIdx.x - n_split) * blockDim.x + threadIdx.x, (size_t)(gridDim.x - n_split) * blockDim.x);
 }
 
 // bf16 copy of a row-major table with rows padded to Ls elements (pads zero)

@@ -408,7 +408,8 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
 }
 
 // The split cells' weights (fp32 TreeLSTM contexts: leaves; under the data-flow scheduler internal nodes too), from the parameters kept in the context.
-int pack_split(tl_ctx *ctx, hipStream_t st)
+// In one launch with the jobs of `many`, if there are any.
+int pack_split(tl_ctx *ctx, const PackList &many, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim, n_cg = ctx->n_cg;
     SplitPackList pl{};
@@ -426,13 +427,14 @@ int pack_split(tl_ctx *ctx, hipStream_t st)
     int rc;
     if (ctx->split > 0 && (rc = add(ctx->m_u, 5, 2, H, ctx->split, SPLIT_H_SCALE, &ctx->xp_inner, &ctx->xs_inner)) != TL_OK) return rc;
     if (ctx->spw_leaf > 0 && (rc = add(ctx->m_w_leaf, 3, 1, E, ctx->spw_leaf, 1.f, &ctx->xp_leaf, &ctx->xs_leaf)) != TL_OK) return rc;
-    if (grid == 0) return TL_OK;
-    hipLaunchKernelGGL(k_pack_split, dim3(grid), dim3(256), 0, st, pl);
+    const int rest = many.n > 0 ? 2048 : 0;
+    if (grid + rest == 0) return TL_OK;
+    hipLaunchKernelGGL(k_repack, dim3(grid + rest), dim3(256), 0, st, many, pl, grid);
     TL_HIP(hipGetLastError());
     return TL_OK;
 }
 
-// One job of k_pack_many for a matrix that pack_gemm has packed before (g says how): [SEG * L x NG * H], from w as it is
+// One job of k_repack for a matrix that pack_gemm has packed before (g says how): [SEG * L x NG * H], from w as it is
 // stored (row-major) or, transposed = true, from the stored [NG * H x SEG * L] matrix whose transpose it is.
 PackJob repack_job(const Gemm &g, const float *w, const float *b, float *bp, int NG, int H, int SEG, int n_cg, bool transposed)
 {
@@ -465,9 +467,7 @@ int repack_f32(tl_ctx *ctx, hipStream_t st)
         pl.job[n++] = repack_job(ctx->g_bwd_leaf, ctx->m_w_leaf, nullptr, nullptr, ctx->ng_bwd_leaf, E / ctx->ng_bwd_leaf, 1,
                                  (E / ctx->ng_bwd_leaf + HU - 1) / HU, true);
     pl.n = n;
-    hipLaunchKernelGGL(k_pack_many, dim3(2048), dim3(256), 0, st, pl);
-    TL_HIP(hipGetLastError());
-    return lstm ? pack_split(ctx, st) : TL_OK;
+    return pack_split(ctx, pl, st);
 }
 
 // The same for an fp32 TreeRNN context: forward weights and W^T of the backward pass.
@@ -797,7 +797,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             ctx->ng_bwd_leaf = E % 4 == 0 ? 4 : 1;
             ctx->ws_steps16 = ws_steps16;
             rc = pack_treelstm_f32(ctx, nullptr);
-            if (rc == TL_OK) rc = pack_split(ctx, nullptr);
+            if (rc == TL_OK) rc = pack_split(ctx, PackList{}, nullptr);
             TL_HIP(hipDeviceSynchronize());
             if (rc != TL_OK) return rc;
         } else {
