@@ -579,10 +579,11 @@ __device__ inline void cell_tile_staged_bf16(TileSmem &sm, const Fwd &f, const G
 //   table : source rows of the gather (embedding table, or h)
 //   count : rows in use (1..TILE_ROWS);  cg : column group
 template <bool VEC4, bool COH>
-__device__ inline void rntn_tile_any(TileSmem &sm, const Fwd &f, const Gemm &gm, int count, int cg);   // cell_rntn.hpp
+__device__ __forceinline__ void rntn_tile_any(TileSmem &sm, const Fwd &f, const Gemm &gm, int count, int cg);   // cell_rntn.hpp
 
+// (always inlined: a call would copy the kernel's parameters to memory to pass them)
 template <int EPI, bool VEC4, bool COH, bool BF16 = false>
-__device__ inline void cell_tile(TileSmem &sm, const Fwd &f, const Gemm &gm, const float *__restrict__ table,
+__device__ __forceinline__ void cell_tile(TileSmem &sm, const Fwd &f, const Gemm &gm, const float *__restrict__ table,
                                  int count, int cg)
 {
     if constexpr (EPI == EPI_RNTN_INNER) rntn_tile_any<VEC4, COH>(sm, f, gm, count, cg);

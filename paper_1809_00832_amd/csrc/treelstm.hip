@@ -498,11 +498,13 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
     const int Lp = round_up(H, 4);
     int Kp = round_up(2 * Lp, KC);
     if (Kp > 128) Kp = 256;
-    const size_t n_v = (size_t)ctx->n_cg * (Kp + 1) * (Kp / STEP_K) * 256;
-    if (!ctx->wp_inner) TL_HIP(hipMalloc(&ctx->wp_inner, n_v * sizeof(float)));
+    const int n_steps = Kp / 32, slices = ctx->n_cg * (Kp + 1);
+    if (!ctx->wp_inner) TL_HIP(hipMalloc(&ctx->wp_inner, (size_t)ctx->n_cg * rntn_units_of(n_steps) * 2 * 64 * 16));
+    if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)slices * HU * sizeof(float)));
     if (!ctx->bp_inner) TL_HIP(hipMalloc(&ctx->bp_inner, (size_t)ctx->n_cg * HU * sizeof(float)));
-    hipLaunchKernelGGL(k_pack_rntn, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, (float *)ctx->wp_inner,
-                       H, Lp, Kp, ctx->n_cg);
+    hipLaunchKernelGGL(k_rntn_build_s, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, ctx->t_scratch, H);
+    hipLaunchKernelGGL(k_pack_rntn, dim3((slices + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, (_Float16 *)ctx->wp_inner, ctx->xs_inner,
+                       H, Lp, n_steps, ctx->n_cg);
     hipLaunchKernelGGL(k_pack_bias, dim3(64), dim3(256), 0, st, (const float *)ctx->m_b, ctx->bp_inner, 1, H, ctx->n_cg);
     TL_HIP(hipGetLastError());
     ctx->g_inner.wp = ctx->wp_inner;
@@ -510,7 +512,6 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
     ctx->g_inner.L = H;
     ctx->g_inner.Lp = Lp;
     ctx->g_inner.n_chunks = Kp / KC;
-    hipLaunchKernelGGL(k_rntn_build_s, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, ctx->t_scratch, H);
     int rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, ctx->ng_bwd_inner, D2 / ctx->ng_bwd_inner, 1, L,
                        (D2 / ctx->ng_bwd_inner + HU - 1) / HU, 0, false, &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
     if (rc != TL_OK) return rc;
@@ -1133,6 +1134,10 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         if (grid_l2 < (spw > 0 ? ctx->n_cg : 1)) return TL_EHIP;
     }
     f.cap_tiles = grid_p / ctx->n_cg > 0 ? grid_p / ctx->n_cg : 1;
+    if (cfg.cell == TL_RNTN) {
+        f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u;
+        f.rntn_v = ctx->m_v;
+    }
     // RNTN: a frontier of at most rntn_units tiles is cut into RNTN_PARTS workgroups per tile and column group
     f.rntn_part = ctx->rntn_part; f.rntn_done = ctx->rntn_done;
     f.rntn_units = cfg.cell == TL_RNTN ? (2 * grid_p / ctx->n_cg < ctx->rntn_units ? 2 * grid_p / ctx->n_cg : ctx->rntn_units) : 0;

@@ -1,0 +1,84 @@
+"""The fp32 RNTN cell, whose operands are split into two fp16 terms, at the sizes where its tiles, slices, paddings and scales
+can go wrong.
+
+Tolerance: two terms hold a value to 2^-23 of itself (2^-38 of the largest of its row or column where it is far below that), a
+product of two is off by 2^-21 at most; the sums of at most 2d (2d + 1) / 2 products here are of order one.  2e-5 relative + 2e-6
+absolute is what the split TreeLSTM cells are tested with."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1809_00832_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+RTOL, ATOL = 2e-5, 2e-6
+
+
+def run(params, trees, sched):
+    net = binding.TreeNet(params, scheduler=sched)
+    try:
+        out = net.run(trees)
+        for _ in range(2):
+            net.batch["h"].fill_(float("nan"))
+            net.forward()
+            assert binding.tl_status(net.ctx) == 0
+            assert np.array_equal(net.batch["h"].cpu().numpy(), out["h"], equal_nan=True)
+        return out
+    finally:
+        net.close()
+
+
+def check(got, ref):
+    for key in ("h", "h_root"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+
+
+@pytest.mark.parametrize("sched", ["dataflow", "level_device", "ready", "level_host"])
+@pytest.mark.parametrize("d", [1, 7, 8, 16, 17, 31, 32, 33, 48, 49, 63, 64, 65, 95, 96, 97, 128])
+def test_sizes_at_the_edges_of_the_slices(d, sched):
+    print("case rntn split sizes", d, sched, flush=True)
+    params = synth.make_rnn_params(700 + d, synth.CELL_RNTN, 60, d, scale=0.7 / d ** 0.5)
+    trees = synth.make_trees(701, [1, 2, 3, 1, 18, 40, 9, 33, 64], ["random", "chain", "balanced"] * 3, 60)
+    check(run(params, trees, sched), oracle.forward_params(params, trees, n_threads=8))
+
+
+@pytest.mark.parametrize("sched", ["dataflow", "level_device"])
+def test_rows_and_columns_of_very_different_size(sched):
+    """Every embedding row and every column of a slice is scaled for itself: sizes four powers of ten apart side by side (the
+    sums of absolute products reach 100, of which 2^-21 is left uncertain per product: hence the absolute tolerance)."""
+    print("case rntn split scales", sched, flush=True)
+    d = 40
+    p = synth.make_rnn_params(710, synth.CELL_RNTN, 60, d, scale=0.1)
+    rng = np.random.default_rng(1)
+    p.v *= (10.0 ** rng.uniform(-3, 0, (d, 1, 1))).astype(np.float32)
+    p.u *= (10.0 ** rng.uniform(-3, 0.5, d)).astype(np.float32)
+    p.emb *= (10 * 10.0 ** rng.uniform(-4, 0.3, p.emb.shape[0])).astype(np.float32)[:, None]
+    trees = synth.make_trees(711, [30, 8, 1, 21], ["random", "chain", "random", "balanced"], 60)
+    got, ref = run(p, trees, sched), oracle.forward_params(p, trees, n_threads=8)
+    assert np.abs(ref["h"][trees.left >= 0]).max() > 0.5
+    np.testing.assert_allclose(got["h"], ref["h"], rtol=RTOL, atol=1e-5)
+
+
+@pytest.mark.parametrize("sched", ["dataflow", "level_device", "ready"])
+@pytest.mark.parametrize("where", ["v", "u", "emb"])
+def test_infinities_are_summed_in_fp32(where, sched):
+    """An infinity has no two terms; its sums are taken from the parameters as given."""
+    print("case rntn infinity", where, sched, flush=True)
+    d = 24
+    p = synth.make_rnn_params(720, synth.CELL_RNTN, 30, d, scale=0.02)       # (sums of absolute products of order one)
+    p.emb[:] = np.abs(p.emb) + 0.1                      # (no sum of infinities of both signs, which is a NaN)
+    if where == "v":
+        p.v[5, 3, 30] = np.inf
+    elif where == "u":
+        p.u[3, 5] = np.inf
+    else:
+        p.emb[::3, 5] = np.inf
+        p.v[:] = np.abs(p.v)
+        p.u[:] = np.abs(p.u)
+    trees = synth.make_trees(721, [12, 5, 1, 20], ["random"] * 4, 30)
+    with np.errstate(all="ignore"):
+        ref = oracle.forward_params(p, trees, n_threads=8)
+    got = run(p, trees, sched)
+    ok = ~np.isnan(ref["h"])
+    assert (np.abs(ref["h"][trees.left >= 0][:, 5]) == 1).any()
+    np.testing.assert_allclose(got["h"][ok], ref["h"][ok], rtol=RTOL, atol=ATOL)
