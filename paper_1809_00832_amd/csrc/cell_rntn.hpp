@@ -29,55 +29,62 @@ namespace tl {
 __host__ __device__ constexpr int rntn_unit(int q) { return 16 * (q >> 5) * ((q >> 5) + 1) + (q & 31) * ((q >> 5) + 1); }
 __host__ __device__ constexpr int rntn_units_of(int n_steps) { return rntn_unit(32 * n_steps) + n_steps; }
 
-// From the matrix of k_rntn_build_s (backward.hpp): s[(k, q)][p] = V[k][p][q] + V[k][q][p], s[d * 2d + k][p] = W[p][k].  One wave per column
-// group and slice: a lane holds its column's values, eight neighbours of every k-step.
+// One column of a slice (q < Q, unit k; q = Q: the linear term) from the matrix of k_rntn_build_s (backward.hpp): s[(k, q)][p] = V[k][p][q] +
+// V[k][q][p], s[d * 2d + k][p] = W[p][k].  A lane holds, of the column of lane % 16, eight neighbours of every k-step.
 constexpr int RNTN_MAX_STEPS = 8;
-__global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, _Float16 *__restrict__ vp, float *__restrict__ scale, int d, int Lp,
-                                                   int n_steps, int n_cg)
+struct RntnColumn {
+    halfx8 hi[RNTN_MAX_STEPS], lo[RNTN_MAX_STEPS];
+    float scale;            // what a sum of products is multiplied by
+};
+__device__ inline RntnColumn rntn_column(const float *__restrict__ s, int d, int Lp, int Q, int q, int k, int lane)
 {
-    const int lane = threadIdx.x & 63, Q = 32 * n_steps, D2 = 2 * d;
-    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (item >= n_cg * (Q + 1)) return;
-    const int cg = item / (Q + 1), q = item - cg * (Q + 1);
-    const int k = cg * HU + (lane & 15);
+    const int D2 = 2 * d;
     const bool linear = q == Q;
     const int qseg = q / Lp, ql = qseg * d + (q - qseg * Lp);       // logical index of a_q
     const bool live = k < d && (linear || (qseg < 2 && q - qseg * Lp < d));
     const float *row = s + (linear ? (size_t)d * D2 + k : (size_t)k * D2 + ql) * D2;
-    const int steps = linear ? n_steps : (q >> 5) + 1;
     float x[RNTN_MAX_STEPS][8];
     unsigned m = 0u;
-    bool inf = false;
 #pragma unroll
     for (int t = 0; t < RNTN_MAX_STEPS; ++t)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const int p = 32 * t + 8 * (lane >> 4) + i, pseg = p / Lp, off = p - pseg * Lp;
             float v = 0.f;
-            if (live && t < steps && pseg < 2 && off < d && (linear || p <= q)) v = row[pseg * d + off] * (!linear && p == q ? 0.5f : 1.f);
+            if (live && pseg < 2 && off < d && (linear || p <= q)) v = row[pseg * d + off] * (!linear && p == q ? 0.5f : 1.f);
             x[t][i] = v;
             const unsigned u = __float_as_uint(v) & 0x7FFFFFFFu;
-            if (u < 0x7F800000u) m = max(m, u); else inf = true;
+            if (u < 0x7F800000u) m = max(m, u);                     // (an infinity or a NaN is packed as NaN terms: lo = inf - inf)
         }
     m = max(m, (unsigned)__shfl_xor((int)m, 16));
     m = max(m, (unsigned)__shfl_xor((int)m, 32));
-    (void)inf;                                                      // (an infinity or a NaN is packed as NaN terms: lo = inf - inf)
     const int e = min(13 - ((int)(m >> 23) - 127), 100);            // the column is scaled by 2^e
-    if (lane < 16) scale[((size_t)cg * (Q + 1) + q) * HU + lane] = k < d ? ldexpf(1.f, -e) : 0.f;
-    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-    half8 *dst = reinterpret_cast<half8 *>(vp) + ((size_t)cg * rntn_units_of(n_steps) + rntn_unit(q)) * 2 * 64 + lane;
+    RntnColumn c;
+    c.scale = k < d ? ldexpf(1.f, -e) : 0.f;
 #pragma unroll
-    for (int t = 0; t < RNTN_MAX_STEPS; ++t) {
-        if (t >= steps) break;
-        half8 hi, lo;
+    for (int t = 0; t < RNTN_MAX_STEPS; ++t)
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
             const float v = ldexpf(x[t][i], e);
-            hi[i] = (_Float16)v;
-            lo[i] = (_Float16)(v - (float)hi[i]);
+            c.hi[t][i] = (_Float16)v;
+            c.lo[t][i] = (_Float16)(v - (float)c.hi[t][i]);
         }
-        dst[(size_t)t * 128] = hi;
-        dst[(size_t)t * 128 + 64] = lo;
+    return c;
+}
+// One wave per column group and slice.
+__device__ inline void pack_rntn_tile(const float *__restrict__ s, _Float16 *__restrict__ vp, float *__restrict__ scale, int d, int Lp, int n_steps,
+                                      int item, int lane)
+{
+    const int Q = 32 * n_steps, cg = item / (Q + 1), q = item - cg * (Q + 1);
+    const int steps = q == Q ? n_steps : (q >> 5) + 1;
+    const RntnColumn c = rntn_column(s, d, Lp, Q, q, cg * HU + (lane & 15), lane);
+    if (lane < 16) scale[((size_t)cg * (Q + 1) + q) * HU + lane] = c.scale;
+    halfx8 *dst = reinterpret_cast<halfx8 *>(vp) + ((size_t)cg * rntn_units_of(n_steps) + rntn_unit(q)) * 2 * 64 + lane;
+#pragma unroll
+    for (int t = 0; t < RNTN_MAX_STEPS; ++t) {
+        if (t >= steps) break;
+        dst[(size_t)t * 128] = c.hi[t];
+        dst[(size_t)t * 128 + 64] = c.lo[t];
     }
 }
 
@@ -123,7 +130,7 @@ template <int NS> struct RntnSmem {
 };
 
 // The k-steps of a class as one stream of units: slice j of the class is q = class + 16 j with j / 2 + 1 k-steps.
-constexpr int rntn_first(int j) { return (j >> 1) * ((j >> 1) + 1) + (j & 1) * ((j >> 1) + 1); }
+__host__ __device__ constexpr int rntn_first(int j) { return (j >> 1) * ((j >> 1) + 1) + (j & 1) * ((j >> 1) + 1); }
 constexpr int rntn_slice_of(int u) { int j = 0; while (rntn_first(j + 1) <= u) ++j; return j; }
 
 // Row blocks rb0 .. rb0 + RB - 1 of a tile: sums of this wave's class of part pp, accumulated into out.  RING units of the packed matrix

@@ -282,6 +282,172 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
     }
 }
 
+// ---- TreeRNN ---------------------------------------------------------------------------------------
+// The same blocks for h = tanh(a W + b): NG column groups side by side in a workgroup take the place of the gates, and waves 0, 1 hold the
+// left child's K axis, waves 2, 3 the right one's (S k-steps of 32 each).  Leaves are embedding rows of any magnitude, so every row of the
+// split copy has a scale of its own, and f.hx_back[node] says what its sums are multiplied by (2^-14 for internal nodes).
+// Few weights (32 registers per column group at H = 256), so two workgroups a CU.  One group per workgroup where every tree then still
+// has a slot of its own, two that share the rows they gather otherwise (forward, NG = 1 / 2 / 4): 25 trees at H = 50 30.8 / 35.7 / 40.3 us, at
+// H = 150 39.6 / 39.8 / 48.5, at H = 256 43.6 / 44.1 / 47.8; 100 trees at H = 200 55.7 / 54.4 / 59.9; 256 trees at H = 256 80.4 / 71.9 / 74.6.
+// (Before, with fp32 instructions and lists taken in pieces: 41.7, 50.4, 49.7, 59.4, 86.0; with rows of h scaled, split and left in LDS
+// for four waves of 16 units each: 34.6, 54.9, 56.1, -, 79.6, and 82 instead of 50 for 10 trees at H = 512.)
+template <int NG> struct SplitRnnSmem {
+    float red[2][4 * NG * 64 * 4];
+    float sum_of[NG * HU * 2];
+    float row_scale[4][16];
+    int gave_up, leave;
+};
+
+// A node's sum in fp32 from the parameters as given (rare, and slow).  Leaves' rows are those of h; the rest of h may not be there yet
+// when the split copy is, whose values are finite (or NaN).
+__device__ __forceinline__ float split_rnn_plain(const Fwd &f, int l, int r, int hu)
+{
+    const int H = f.H;
+    float sum = 0.f;
+#pragma unroll 1
+    for (int k = 0; k < 2 * H; ++k) {
+        const int u = k < H ? k : k - H, n = k < H ? l : r;
+        float a;
+        if (f.left[n] < 0) {
+            a = f.h[(size_t)n * H + u];
+        } else {
+            const unsigned short *p = reinterpret_cast<const unsigned short *>(f.hx) + (size_t)n * f.hx_steps * 64 + (u >> 5) * 64 + (u & 31);
+            a = ((float)__builtin_bit_cast(_Float16, ld_dev(p)) + (float)__builtin_bit_cast(_Float16, ld_dev(p + 32))) * (1.f / SPLIT_H_SCALE);
+        }
+        sum = __builtin_fmaf(a, f.xi.w[(size_t)k * H + hu], sum);
+    }
+    return sum;
+}
+
+// The packed matrix is [column group][4 S k-steps][hi, lo][lane][8] whatever NG; groups beyond the last are zeros up to an even number.
+template <int NG, int S>
+__device__ __forceinline__ void split_rnn_load(SplitWeights<NG, S> &w, float *sum_of, const Fwd &f, int cg, int wave, int lane)
+{
+    const int t = wave * 64 + lane, u = cg * NG * HU + t;
+    if (t < NG * HU) {
+        sum_of[2 * t] = u < f.H ? f.xi.scale[u] : 0.f;
+        sum_of[2 * t + 1] = u < f.H ? f.inner.bp[u] : 0.f;
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+        const halfx8 *wp = reinterpret_cast<const halfx8 *>(f.xi.wp) + ((size_t)(cg * NG + g) * 4 * S + (size_t)wave * S) * 2 * 64 + lane;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            w.hi[s][g] = wp[(size_t)(s * 2) * 64];
+            w.lo[s][g] = wp[(size_t)(s * 2 + 1) * 64];
+        }
+    }
+}
+
+template <int NG, int S>
+__device__ __forceinline__ void split_rnn_run(SplitRnnSmem<NG> &sm, const Fwd &f, const int4 *__restrict__ entries, int n_blocks, int cg, const SplitWeights<NG, S> &w)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int H = f.H, steps = f.hx_steps, hu0 = cg * NG * HU + (lane & 15);
+    const unsigned row_b = (unsigned)H * 4u, hx_row_b = (unsigned)steps * 128u;
+    const unsigned long long hx_bytes = (unsigned long long)f.n_nodes * hx_row_b;
+    const __amdgpu_buffer_rsrc_t rs_h = buf_of(f.h, (unsigned long long)f.n_nodes * row_b), rs_x = buf_of(f.hx, hx_bytes);
+    const unsigned lane_off = (unsigned)(lane >> 4) * 16u;
+    unsigned base = 0;                                          // this lane's row in the split copy: of its wave's child
+    float back = 0.f;
+    uintx4_t rows[S][2];
+    auto prepare = [&](const int4 &q) __attribute__((always_inline)) {
+        const int child = wave < 2 ? q.y : q.z;
+        base = __umul24((unsigned)child, hx_row_b) + lane_off;
+        return f.hx_back[child];
+    };
+    auto request = [&](auto past_caches) __attribute__((always_inline)) {
+        constexpr int POLICY = decltype(past_caches)::value ? 16 : 0;
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int kk = min((wave & 1) * S + s, steps - 1);  // (beyond the row: its last step again, against zero weights)
+            rows[s][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, (int)base, kk * 128, POLICY);
+            rows[s][1] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, (int)base + 64, kk * 128, POLICY);
+        }
+    };
+    auto shows_pattern = [&]() __attribute__((always_inline)) {
+        unsigned m = 0u;
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int t = 0; t < 2; ++t) m = max(max(m, max(rows[s][t].x, rows[s][t].y)), max(rows[s][t].z, rows[s][t].w));
+        return __ballot(m == FLOW_SENTINEL) != 0ull;
+    };
+    const int my_row = lane & 15, fin_row = 4 * wave + (lane >> 4);
+    int4 q = entries[my_row], e = entries[fin_row];
+    int4 q_next = n_blocks > 1 ? entries[16 + my_row] : q;
+    back = prepare(q);
+    request(std::false_type{});
+#pragma unroll 1
+    for (int b = 0; b < n_blocks; ++b) {
+        const bool last = b + 1 >= n_blocks;
+        const bool late = last || __builtin_amdgcn_readfirstlane(q_next.w) < 0;     // the next block waits for this one
+        const int4 q_ahead = entries[(size_t)min(b + 2, n_blocks - 1) * 16 + my_row];
+        const int4 e_next = entries[(size_t)min(b + 1, n_blocks - 1) * 16 + fin_row];
+        if (shows_pattern()) {
+            int spins = 0;
+            unsigned aborted = 0u;
+            do {                                                // bounded by the spin budget and the abort flag
+                if (++spins > f.spin_limit || aborted != 0u) {
+                    flow_give_up(f);
+                    sm.gave_up = 1;
+                    break;
+                }
+                __builtin_amdgcn_s_sleep(1);
+                request(std::true_type{});
+                aborted = ld_dev(&f.ctl->abort.v);              // arrives with the rows
+            } while (shows_pattern());
+        }
+        if (lane < 16) sm.row_scale[wave][lane] = back;
+        floatx4 acc[NG];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const halfx8 hi = __builtin_bit_cast(halfx8, rows[s][0]), lo = __builtin_bit_cast(halfx8, rows[s][1]);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, w.hi[s][g], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, w.lo[s][g], acc[g], 0, 0, 0);
+#pragma unroll
+            for (int g = 0; g < NG; ++g) acc[g] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, w.hi[s][g], acc[g], 0, 0, 0);
+        }
+        const float back_next = prepare(q_next);
+        if (!late) request(std::false_type{});
+        // the four quarter sums meet in LDS, as in split_run
+        float *red = sm.red[b & 1];
+        const floatx4 r4 = *reinterpret_cast<const floatx4 *>(&sm.row_scale[wave][4 * (lane >> 4)]);    // this wave's own writes
+#pragma unroll
+        for (int g = 0; g < NG; ++g) *reinterpret_cast<floatx4 *>(&red[((wave * NG + g) * 64 + lane) * 4]) = acc[g] * r4;
+        __syncthreads();
+        if (sm.gave_up != 0) return;
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
+            const float *sb = &sm.sum_of[(g * HU + (lane & 15)) * 2];
+            float p[4];
+#pragma unroll
+            for (int k = 0; k < 4; ++k) p[k] = red[((k * NG + g) * 64 + 16 * wave + (lane & 15)) * 4 + (lane >> 4)];
+            const int hu = hu0 + g * HU;
+            float sum = (((p[0] + p[1]) + p[2]) + p[3]) * sb[0];
+            if (e.x >= 0) {
+                if (__builtin_expect(__builtin_isnan(sum) && hu < H, 0)) sum = split_rnn_plain(f, e.y, e.z, hu);
+                const float hh = hu < H ? tanh_f(sum + sb[1]) : 0.f;
+                const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
+                if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)e.x * hx_row_b + split_word_off(hu), __uint_as_float(word));
+                if (hu < H) {
+                    buf_st_f<true>(rs_h, (unsigned)e.x * row_b + (unsigned)hu * 4u, hh);
+                    const int t = (e.w & 0x7FFFFFFF) - 1;       // a root's tree
+                    if (t >= 0 && f.h_root) f.h_root[(size_t)t * H + hu] = hh;
+                }
+            }
+        }
+        if (late && !last) request(std::true_type{});           // (past the caches: what they hold of these rows is too old)
+        back = back_next;
+        q_next = q_ahead;
+        e = e_next;
+    }
+}
+
 // ---- leaves ----------------------------------------------------------------------------------------
 // Lane l of a wave holds, for row l & 15, the eight embedding values k = 32 step + 8 (l >> 4) ... + 7 of each of its wave's S
 // steps: 16-byte loads (rows need 4-byte alignment only), straight into the registers that become the A operands.  An

@@ -130,6 +130,7 @@ struct Fwd {
     SplitGemm xi, xl;           // inner and leaf weights for the split cells
     unsigned *hx;               // split copy of h that the split cell gathers from (cell_split.hpp), hx_steps lines of 128 bytes a row; else null
     int hx_steps;
+    float *hx_back;             // TreeRNN: what sums over a row of the split copy are multiplied by (its leaves' rows have scales of their own)
     float *sink;                // [5H + 16]: where lanes without a node put the gate activations they do not have
     // workspace
     int32_t *parent, *pending, *leaf_list, *root_ws;
@@ -162,6 +163,7 @@ struct Fwd {
     int flow_roots;                   // data-flow scheduler: roots are found and their states copied out by the cell kernels (no separate passes)
     int4 *sched;                      // ... and of the split cell: blocks of 16 entries {node, left, right, flags}, see flow_schedule
     int4 *sched_head;                 // per slot {first block, blocks, trees [from, to) among which some have one node}
+    int seg_chunks;                   // RNTN cell that gathers rows (cell_rows.hpp): groups of eight values per segment of the K axis
     int n_slots;                      // slots (sets of workgroups that cover all column groups) of its kernel
     int place;                        // a slot's workgroups lie on one L2 domain (see split_place)
     int flow;                         // data-flow scheduler: who fills the rows of internal nodes with the "not written" pattern: 1 the reset kernel, 2 the leaf kernel

@@ -7,6 +7,7 @@
 #include "cell_ws.hpp"
 #include "cell_split.hpp"
 #include "cell_rntn.hpp"
+#include "cell_rows.hpp"
 
 namespace tl {
 
@@ -101,18 +102,67 @@ __global__ __launch_bounds__(WG_THREADS, 4) void k_leaf_ws_bf(Fwd f)
     }
 }
 
-// Leaves of TreeRNN / RNTN: h = embedding row.
-__global__ void k_leaf_copy(Fwd f)
+// Leaves of TreeRNN / RNTN: h = embedding row.  One wave per node and step; under the data-flow scheduler the waves that meet an
+// internal node mark its row as not written, the split copy (TreeRNN) receives a leaf's row scaled so that its largest magnitude lies in
+// [2^14, 2^15), and the first n_sched workgroups prepare the schedule of the internal nodes beside them.
+__global__ __launch_bounds__(WG_THREADS) void k_leaf_copy(Fwd f, int n_sched, int lds_bytes)
 {
-    if (batch_rejected(f)) return;
-    const int i = blockIdx.x;
-    if (i >= f.n_leaf) return;
-    const int n = f.leaf_list[i];
-    const int w = f.word[n];
-    for (int j = threadIdx.x; j < f.H; j += blockDim.x) {
-        const float x = f.emb[(size_t)w * f.E + j];
-        f.h[(size_t)n * f.H + j] = x;
-        if (f.hb) f.hb[(size_t)n * f.hs + j] = bf16_bits(x);
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ int s_leave;
+    if ((int)blockIdx.x < n_sched) {
+        flow_schedule(f, blockIdx.x, smem_raw, (size_t)lds_bytes);
+        return;
+    }
+    // (the schedule's workgroups may latch an error meanwhile)
+    if (decided_to_leave(&s_leave, threadIdx.x == 0 && batch_rejected(f))) return;
+    const int lane = threadIdx.x & 63, H = f.H;
+    const int wave = (blockIdx.x - n_sched) * 4 + (threadIdx.x >> 6), n_waves = (gridDim.x - n_sched) * 4;
+    const bool mark = f.flow == 2 && !internal_kernel_skipped(f);
+    const unsigned ones = 0xFFFFFFFFu;
+    const bool all = n_sched > 0;                           // (without marks there are only leaves to look after)
+    for (int i = wave; i < (all ? f.n_nodes : f.n_leaf); i += n_waves) {
+        const int n = all ? i : f.leaf_list[i];
+        const int w = !all || f.left[n] < 0 ? f.word[n] : -1;
+        if (w < 0 && !mark) continue;
+        const float *src = f.emb + (size_t)max(w, 0) * f.E;
+        if (f.hx) {
+            // a lane takes pairs of units: one word of hi halves, one of lo halves
+            constexpr int PAIRS = SPLIT_MAX_S * 64 / 128;       // H <= 512
+            unsigned *row = f.hx + (size_t)n * (f.hx_steps * 32);
+            float x[PAIRS][2], m = 0.f;
+#pragma unroll
+            for (int i = 0; i < PAIRS; ++i)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) {
+                    const int u = 2 * (lane + 64 * i) + e;
+                    x[i][e] = w >= 0 && u < H ? src[u] : 0.f;
+                    m = fmaxf(m, fabsf(x[i][e]));
+                }
+#pragma unroll
+            for (int d = 1; d < 64; d *= 2) m = fmaxf(m, __shfl_xor(m, d));
+            const unsigned eb = max(__float_as_uint(m) >> 23, 15u);
+            const float scale = __uint_as_float((268u - eb) << 23);
+            if (lane == 0) f.hx_back[n] = w >= 0 ? __uint_as_float((eb - 14u) << 23) : 1.f / SPLIT_H_SCALE;
+#pragma unroll
+            for (int i = 0; i < PAIRS; ++i) {
+                const int u = 2 * (lane + 64 * i);
+                if (u >= H) continue;                           // (words of pad units alone stay zero)
+                const unsigned b0 = split_bits(x[i][0] * scale), b1 = split_bits(x[i][1] * scale);
+                unsigned *word = row + (u >> 5) * 32 + ((u & 31) >> 1);
+                word[0] = w >= 0 ? (b0 & 0xFFFFu) | b1 << 16 : ones;
+                word[16] = w >= 0 ? b0 >> 16 | (b1 & 0xFFFF0000u) : ones;
+                if (w >= 0) {
+                    f.h[(size_t)n * H + u] = x[i][0];
+                    if (u + 1 < H) f.h[(size_t)n * H + u + 1] = x[i][1];
+                }
+            }
+        } else {
+            for (int j = lane; j < H; j += 64) {
+                const float x = w >= 0 ? src[j] : __uint_as_float(ones);
+                f.h[(size_t)n * H + j] = x;
+                if (f.hb && w >= 0) f.hb[(size_t)n * f.hs + j] = bf16_bits(x);
+            }
+        }
     }
 }
 
@@ -543,9 +593,8 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     const int my_cg = member;
     PersistentWeights<EpiTraits<EPI>::NG, SPW, BF16> w;        // (loaded below, behind the first requests of the scan)
 
-    int t_lo, t_hi;
-    flow_cut(f, slot, n_slots, &t_lo, &t_hi);
-    const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];
+    int t_lo, t_hi, nb, ne;
+    flow_cut(f, slot, n_slots, &t_lo, &t_hi, &nb, &ne);
     const int slot_internal = ((ne - nb) - (t_hi - t_lo)) / 2;      // full binary trees
     if (ne <= nb) return;                             // (the same for all waves: nothing writes the offsets)
     unsigned *seen = reinterpret_cast<unsigned *>(f.flow_seen) + (size_t)member * f.n_nodes;   // this workgroup's own: [nb, ne) of it
@@ -734,6 +783,30 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_flow_split(Fwd f)
         }
     }
     if (head.y > 0) split_run<S>(sm, f, f.sched + (size_t)head.x * 16, head.y, member, w);
+}
+
+// ... with the split TreeRNN cell: f.n_cg workgroups of NG column groups.
+template <int NG, int S>
+__global__ __launch_bounds__(WG_THREADS, 2) void k_flow_split_rnn(Fwd f)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    SplitRnnSmem<NG> &sm = *reinterpret_cast<SplitRnnSmem<NG> *>(smem_raw);
+    const int tid = threadIdx.x;
+    const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));      // (a workgroup that gives up latches that)
+    int member, slot;
+    split_place(f, &slot, &member);
+    if (tid == 0) sm.gave_up = 0;
+    SplitWeights<NG, S> w;
+    split_rnn_load(w, sm.sum_of, f, member, tid >> 6, tid & 63);
+    const int4 head = f.sched_head[slot];         // (of an earlier batch where this one is rejected: not used then)
+    if (decided_to_leave(&sm.leave, leave)) return;
+    if (f.flow_roots && f.h_root) {               // trees of one node: the leaf is the root
+        for (int i = tid; i < (head.w - head.z) * (NG * HU); i += WG_THREADS) {
+            const int t = head.z + i / (NG * HU), hu = member * (NG * HU) + i % (NG * HU), n = f.tree_off[t];
+            if (hu < f.H && f.tree_off[t + 1] - n == 1) f.h_root[(size_t)t * f.H + hu] = f.h[(size_t)n * f.H + hu];
+        }
+    }
+    if (head.y > 0) split_rnn_run<NG, S>(sm, f, f.sched + (size_t)head.x * 16, head.y, member, w);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -459,26 +459,32 @@ template <> struct SchedLists<false> {
 
 // The part of the batch that belongs to a slot: trees [t_lo, t_hi), cut where the node count passes slot / n_slots of the batch.
 // Both cuts are looked for at once, lanes 0-31 of every wave for this slot's and lanes 32-63 for the next one's, 32
-// candidates per round trip (a bisection is one dependent load per halving).
-__device__ inline void flow_cut(const Fwd &f, int slot, int n_slots, int *t_lo, int *t_hi)
+// candidates per round trip (a bisection is one dependent load per halving).  The offsets at the cuts are among what has been read.
+__device__ inline void flow_cut(const Fwd &f, int slot, int n_slots, int *t_lo, int *t_hi, int *n_lo, int *n_hi)
 {
     const int lane = threadIdx.x & 63, half = lane >> 5, i = lane & 31;
     const long long bound = ((long long)(slot + half) * f.n_nodes + n_slots - 1) / n_slots;
     int lo = 0, hi = f.n_trees;                   // smallest t with tree_off[t] >= bound is in [lo, hi]; tree_off[n_trees] = n_nodes >= bound
+    int at_hi = f.n_nodes;                        // tree_off[hi]
     while (__ballot(lo < hi) != 0ull) {
         const int step = (hi - lo + 30) / 31;     // candidates lo, lo + step, ..., the last one clamped to hi
         const int cand = min(lo + i * step, hi);
-        const bool ge = cand >= hi || f.tree_off[cand] >= bound;                    // (at hi it holds by the invariant)
+        const int off = cand >= hi ? at_hi : f.tree_off[cand];
+        const bool ge = cand >= hi || off >= bound;                                 // (at hi it holds by the invariant)
         const unsigned long long m = __ballot(ge) >> (32 * half) & 0xFFFFFFFFull;   // never empty: the last candidate is hi
         const int k = __builtin_ctzll(m);         // first candidate at or above the cut
+        const int off_k = __shfl(off, 32 * half + k);
         if (lo < hi) {
             const int new_hi = min(lo + k * step, hi);
             lo = k == 0 ? lo : min(lo + (k - 1) * step, hi) + 1;                    // (k == 0: the cut is lo itself)
             hi = new_hi;
+            at_hi = off_k;
         }
     }
     *t_lo = __builtin_amdgcn_readlane(lo, 0);     // (scalar values, like everything derived from them)
     *t_hi = __builtin_amdgcn_readlane(lo, 32);
+    *n_lo = __builtin_amdgcn_readlane(at_hi, 0);
+    *n_hi = __builtin_amdgcn_readlane(at_hi, 32);
 }
 
 template <bool IN_LDS>
@@ -622,7 +628,9 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
         const bool here = st + r < end;
         const int node = nb + q.node(here ? st + r : st);
         int w = q.block_late(b) ? (int)SCHED_LATE : 0;
-        if (f.flow_roots && here && f.parent[node] < 0) w |= ld_dev(&f.depth_root[node]) + 1;
+        // (asked for together: only a root's tree is there)
+        const int up = f.parent[node], tree = f.flow_roots ? ld_dev(&f.depth_root[node]) : 0;
+        if (f.flow_roots && here && up < 0) w |= tree + 1;
         out[i] = int4{here ? node : -1, f.left[node], f.right[node], w};
     }
 }
@@ -631,10 +639,11 @@ __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds,
     // (workgroups of other slots may latch an error meanwhile)
     int *s_ctl = reinterpret_cast<int *>(lds);
     if (threadIdx.x >= 1 && threadIdx.x < 4) s_ctl[threadIdx.x] = 0;
-    if (decided_to_leave(&s_ctl[0], threadIdx.x == 0 && (batch_rejected(f) || internal_kernel_skipped(f)))) return;
-    int t_lo, t_hi;
-    flow_cut(f, slot, f.n_slots, &t_lo, &t_hi);
-    const int nb = f.tree_off[t_lo], ne = f.tree_off[t_hi];
+    // the cuts first: what they read of a batch that is rejected is not used, and the status arrives beside it
+    const bool leave = threadIdx.x == 0 && (batch_rejected(f) || internal_kernel_skipped(f));
+    int t_lo, t_hi, nb, ne;
+    flow_cut(f, slot, f.n_slots, &t_lo, &t_hi, &nb, &ne);
+    if (decided_to_leave(&s_ctl[0], leave)) return;
     if (ne <= nb) {
         if (threadIdx.x == 0) f.sched_head[slot] = int4{0, 0, 0, 0};
         return;

@@ -69,6 +69,13 @@ struct tl_ctx {
     unsigned short *hb = nullptr;     // bf16 copy of h, cap_nodes rows (bf16 weight-stationary cell only)
     int split = 0;                    // k-steps per wave of the split cell (data-flow scheduler, fp32 TreeLSTM), 0 = not used
     int hx_steps = 0;                 // 128-byte lines per row of the split copy of h
+    int flow_set = 0;                 // workgroups of the data-flow kernel that cover all hidden units (TreeRNN: with one column group each)
+    float *hx_back = nullptr;         // TreeRNN: scales of the rows of hx
+    // fp32 RNTN under the data-flow scheduler (cell_rows.hpp): k-steps of the K axis (0: not used), groups of eight values per
+    // segment, packed matrices and their scales
+    int rows_steps = 0, rows_seg = 0;
+    _Float16 *rows_wp = nullptr;
+    float *rows_scale = nullptr;
     int flow_grid = 0;                // workgroups of the data-flow kernel
     unsigned *hx = nullptr;           // split copy of h, cap_split rows
     int cap_split = 0;                // nodes that hx and sched have room for
@@ -210,16 +217,41 @@ fwd_kernel flow_kernel_bf16(int cell, int s)
     default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 8, true> : k_flow_persistent<EPI_RNN_INNER, true, 8, true>;
     }
 }
-// fp32 TreeRNN
-fwd_kernel flow_kernel_rnn(bool vec4, int spw)
+// fp32 RNTN: the k-steps there are kernels for, the kernel and its LDS
+constexpr int ROWS_MAX_STEPS = 6;
+template <int NS> fwd_kernel rows_kernel_of(size_t *lds)
 {
-    switch (spw) {
-    case 1: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 1> : k_flow_persistent<EPI_RNN_INNER, false, 1>;
-    case 2: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 2> : k_flow_persistent<EPI_RNN_INNER, false, 2>;
-    case 4: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 4> : k_flow_persistent<EPI_RNN_INNER, false, 4>;
-    case 5: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 5> : k_flow_persistent<EPI_RNN_INNER, false, 5>;
-    case 8: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 8> : k_flow_persistent<EPI_RNN_INNER, false, 8>;
-    default: return vec4 ? k_flow_persistent<EPI_RNN_INNER, true, 16> : k_flow_persistent<EPI_RNN_INNER, false, 16>;
+    *lds = sizeof(RowsSmem<NS>);
+    return k_flow_rows<NS>;
+}
+fwd_kernel rows_kernel(int steps, size_t *lds)
+{
+    switch (steps) {
+    case 1: return rows_kernel_of<1>(lds);
+    case 2: return rows_kernel_of<2>(lds);
+    case 3: return rows_kernel_of<3>(lds);
+    case 4: return rows_kernel_of<4>(lds);
+    case 5: return rows_kernel_of<5>(lds);
+    default: return rows_kernel_of<6>(lds);
+    }
+}
+// fp32 TreeRNN, s k-steps of 32 per wave, one or two column groups per workgroup
+template <int S> fwd_kernel rnn_kernel_of(int groups, size_t *lds)
+{
+    *lds = groups == 1 ? sizeof(SplitRnnSmem<1>) : sizeof(SplitRnnSmem<2>);
+    return groups == 1 ? k_flow_split_rnn<1, S> : k_flow_split_rnn<2, S>;
+}
+fwd_kernel flow_kernel_rnn(int s, int groups, size_t *lds)
+{
+    switch (s) {
+    case 1: return rnn_kernel_of<1>(groups, lds);
+    case 2: return rnn_kernel_of<2>(groups, lds);
+    case 3: return rnn_kernel_of<3>(groups, lds);
+    case 4: return rnn_kernel_of<4>(groups, lds);
+    case 5: return rnn_kernel_of<5>(groups, lds);
+    case 6: return rnn_kernel_of<6>(groups, lds);
+    case 7: return rnn_kernel_of<7>(groups, lds);
+    default: return rnn_kernel_of<8>(groups, lds);
     }
 }
 // fp32 TreeLSTM, s k-steps of 32 per wave (1 ... SPLIT_MAX_S)
@@ -236,11 +268,13 @@ fwd_kernel flow_kernel_split(int s)
     default: return k_flow_split<8>;
     }
 }
-// The data-flow kernel: split > 0 the split cell with that many k-steps per wave, else spw > 0 and not the RNTN cell
-fwd_kernel flow_kernel(int cell, bool vec4, int spw, int split, bool bf16)
+// The data-flow kernel of a context (and its LDS): the RNTN cell that gathers rows, the split cells, or bf16 operands
+fwd_kernel flow_kernel(const tl_ctx *ctx, int rnn_groups, size_t *lds)
 {
-    if (split > 0) return flow_kernel_split(split);
-    return bf16 ? flow_kernel_bf16(cell, spw) : flow_kernel_rnn(vec4, spw);
+    if (ctx->rows_steps > 0) return rows_kernel(ctx->rows_steps, lds);
+    if (ctx->split > 0 && ctx->cfg.cell == TL_TREERNN) return flow_kernel_rnn(ctx->split, rnn_groups, lds);
+    *lds = ctx->split > 0 ? sizeof(SplitSmem) : ctx->ws_lds;
+    return ctx->split > 0 ? flow_kernel_split(ctx->split) : flow_kernel_bf16(ctx->cfg.cell, ctx->spw);
 }
 fwd_kernel ready_kernel(int cell, bool vec4, int spw, bool bf16)
 {
@@ -411,22 +445,26 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
 // In one launch with the jobs of `many`, if there are any.
 int pack_split(tl_ctx *ctx, const PackList &many, hipStream_t st)
 {
-    const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim, n_cg = ctx->n_cg;
+    const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim;
     SplitPackList pl{};
     int grid = 0;
-    auto add = [&](const float *m, int NG, int SEG, int L, int S, float operand_scale, _Float16 **wp, float **scale) -> int {
+    auto add = [&](const float *m, int NG, int SEG, int L, int S, float operand_scale, _Float16 **wp, float **scale, int steps, int n_cg) -> int {
         if (!*wp) TL_HIP(hipMalloc(wp, (size_t)n_cg * 4 * S * NG * 2 * 64 * 8 * sizeof(_Float16)));
         if (!*scale) TL_HIP(hipMalloc(scale, (size_t)n_cg * NG * HU * sizeof(float)));
         SplitPackJob &j = pl.job[pl.n++];
         j.w = m; j.wp = *wp; j.scale = *scale;
-        j.NG = NG; j.H = H; j.SEG = SEG; j.L = L; j.steps = (L + 31) / 32; j.n_steps = 4 * S; j.n_cg = n_cg;
+        j.NG = NG; j.H = H; j.SEG = SEG; j.L = L; j.steps = steps; j.n_steps = 4 * S; j.n_cg = n_cg;
         j.operand_scale = operand_scale;
         grid += n_cg * NG;
         return TL_OK;
     };
     int rc;
-    if (ctx->split > 0 && (rc = add(ctx->m_u, 5, 2, H, ctx->split, SPLIT_H_SCALE, &ctx->xp_inner, &ctx->xs_inner)) != TL_OK) return rc;
-    if (ctx->spw_leaf > 0 && (rc = add(ctx->m_w_leaf, 3, 1, E, ctx->spw_leaf, 1.f, &ctx->xp_leaf, &ctx->xs_leaf)) != TL_OK) return rc;
+    const bool rnn = ctx->cfg.cell == TL_TREERNN;
+    const int n_cg = ctx->n_cg, steps_h = (H + 31) / 32;
+    // (TreeRNN: half the waves for either child, an even number of column groups)
+    if (ctx->split > 0 && rnn && (rc = add(ctx->m_u, 1, 2, H, ctx->split, 1.f, &ctx->xp_inner, &ctx->xs_inner, 2 * ctx->split, round_up(n_cg, 2))) != TL_OK) return rc;
+    if (ctx->split > 0 && !rnn && (rc = add(ctx->m_u, 5, 2, H, ctx->split, SPLIT_H_SCALE, &ctx->xp_inner, &ctx->xs_inner, steps_h, n_cg)) != TL_OK) return rc;
+    if (ctx->spw_leaf > 0 && (rc = add(ctx->m_w_leaf, 3, 1, E, ctx->spw_leaf, 1.f, &ctx->xp_leaf, &ctx->xs_leaf, (E + 31) / 32, n_cg)) != TL_OK) return rc;
     const int rest = many.n > 0 ? 2048 : 0;
     if (grid + rest == 0) return TL_OK;
     hipLaunchKernelGGL(k_repack, dim3(grid + rest), dim3(256), 0, st, many, pl, grid);
@@ -495,16 +533,19 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
 int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, D2 = 2 * H, L = H * D2 + H;
-    const int Lp = round_up(H, 4);
+    const int Lp = round_up(H, 8);         // (the cells that gather rows take them eight values at a time)
     int Kp = round_up(2 * Lp, KC);
     if (Kp > 128) Kp = 256;
-    const int n_steps = Kp / 32, slices = ctx->n_cg * (Kp + 1);
+    const int n_steps = Kp / 32, slices = ctx->n_cg * (Kp + 1), rs = ctx->rows_steps;
     if (!ctx->wp_inner) TL_HIP(hipMalloc(&ctx->wp_inner, (size_t)ctx->n_cg * rntn_units_of(n_steps) * 2 * 64 * 16));
     if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)slices * HU * sizeof(float)));
     if (!ctx->bp_inner) TL_HIP(hipMalloc(&ctx->bp_inner, (size_t)ctx->n_cg * HU * sizeof(float)));
+    if (rs > 0 && !ctx->rows_wp) TL_HIP(hipMalloc(&ctx->rows_wp, (size_t)H * (rs * (rs + 1) + 1) * 2 * 64 * 16));
+    if (rs > 0 && !ctx->rows_scale) TL_HIP(hipMalloc(&ctx->rows_scale, (size_t)H * (2 * rs + 1) * HU * sizeof(float)));
     hipLaunchKernelGGL(k_rntn_build_s, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, ctx->t_scratch, H);
-    hipLaunchKernelGGL(k_pack_rntn, dim3((slices + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, (_Float16 *)ctx->wp_inner, ctx->xs_inner,
-                       H, Lp, n_steps, ctx->n_cg);
+    const int waves = slices + (rs > 0 ? H * (2 * rs + 1) : 0);
+    hipLaunchKernelGGL(k_pack_rntn, dim3((waves + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, (_Float16 *)ctx->wp_inner, ctx->xs_inner,
+                       H, Lp, n_steps, ctx->n_cg, ctx->rows_wp, ctx->rows_scale, rs);
     hipLaunchKernelGGL(k_pack_bias, dim3(64), dim3(256), 0, st, (const float *)ctx->m_b, ctx->bp_inner, 1, H, ctx->n_cg);
     TL_HIP(hipGetLastError());
     ctx->g_inner.wp = ctx->wp_inner;
@@ -596,7 +637,7 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
         TL_HIP(hipMalloc(&ctx->hb, hb_bytes));
         TL_HIP(hipMemset(ctx->hb, 0, hb_bytes));   // the padding at the end of each row stays zero for good
     }
-    if (ctx->split == 0 && ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
+    if (ctx->split == 0 && ctx->rows_steps == 0 && ctx->spw > 0 && ctx->cfg.scheduler == TL_SCHED_DATAFLOW)
         TL_HIP(hipMalloc(&ctx->flow_ws, flow_bytes(ctx->n_cg, (size_t)N)));
     TL_HIP(hipHostMalloc(&ctx->host_levels, (size_t)(N + 2) * 4, hipHostMallocDefault));
     TL_HIP(hipStreamSynchronize(nullptr));     // the caller's stream need not be ordered behind the null stream's memsets
@@ -606,12 +647,14 @@ int ensure_workspace(tl_ctx *ctx, int n_nodes, int n_trees)
     return TL_OK;
 }
 
-// The split cell addresses nodes and rows of the split copy of h with 24-bit row numbers and 32-bit byte offsets.
+// The cells of a prepared schedule address nodes and rows (of the split copy of h, or of h itself) with 24-bit row numbers and 32-bit
+// byte offsets.
 bool in_split_range(const tl_ctx *ctx, int n_nodes)
 {
-    return n_nodes < (1 << 24) && (unsigned long long)n_nodes * ctx->hx_steps * 128ull < (1ull << 32);
+    const unsigned long long row = ctx->rows_steps > 0 ? ctx->cfg.hidden * 4ull : ctx->hx_steps * 128ull;
+    return n_nodes < (1 << 24) && (unsigned long long)n_nodes * row < (1ull << 32);
 }
-// What the split cell needs beside the workspace: its copy of h and its schedule.  Only where it runs: a batch beyond its range
+// What the cells of a prepared schedule need beside the workspace: the schedule, and the split cell its copy of h.  Only where it runs: a batch beyond its range
 // goes to the level scheduler, and would leave as much memory idle as h takes.  Called behind ensure_workspace.
 int ensure_split(tl_ctx *ctx, int n_nodes)
 {
@@ -620,9 +663,11 @@ int ensure_split(tl_ctx *ctx, int n_nodes)
     if (ctx->hx) { TL_HIP(hipFree(ctx->hx)); ctx->hx = nullptr; }
     if (ctx->sched) { TL_HIP(hipFree(ctx->sched)); ctx->sched = nullptr; }
     ctx->cap_split = 0;
-    const size_t N = (size_t)(in_split_range(ctx, ctx->cap_nodes) ? ctx->cap_nodes : n_nodes), hx_bytes = N * ctx->hx_steps * 128;
-    TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
-    TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));       // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
+    const size_t N = (size_t)(in_split_range(ctx, ctx->cap_nodes) ? ctx->cap_nodes : n_nodes), hx_bytes = ctx->split > 0 ? N * ctx->hx_steps * 128 : 0;
+    if (hx_bytes > 0) TL_HIP(hipMalloc(&ctx->hx, hx_bytes));
+    if (ctx->hx_back) { TL_HIP(hipFree(ctx->hx_back)); ctx->hx_back = nullptr; }
+    if (hx_bytes > 0 && ctx->cfg.cell == TL_TREERNN) TL_HIP(hipMalloc(&ctx->hx_back, N * sizeof(float)));
+    if (hx_bytes > 0) TL_HIP(hipMemset(ctx->hx, 0, hx_bytes));       // words of pad units alone stay zero for good; that beside an odd last unit is stored with it
     TL_HIP(hipMalloc(&ctx->sched, (N / 2 + 1) * 16 * sizeof(int4)));
     TL_HIP(hipStreamSynchronize(nullptr));         // as in ensure_workspace
     ctx->cap_split = (int)N;
@@ -665,6 +710,9 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->hx);
     (void)hipFree(ctx->sched);
     (void)hipFree(ctx->sched_head);
+    (void)hipFree(ctx->hx_back);
+    (void)hipFree(ctx->rows_wp);
+    (void)hipFree(ctx->rows_scale);
     (void)hipFree(ctx->xp_inner);
     (void)hipFree(ctx->xs_inner);
     (void)hipFree(ctx->xp_leaf);
@@ -757,6 +805,14 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     ctx->hx_steps = (H + 31) / 32;
     if (cfg->cell == TL_TREELSTM && !bf16 && cfg->scheduler == TL_SCHED_DATAFLOW && (2 * ctx->hx_steps + 3) / 4 <= SPLIT_MAX_S)
         ctx->split = (2 * ctx->hx_steps + 3) / 4;
+    // (TreeRNN: whole waves for either child)
+    if (cfg->cell == TL_TREERNN && !bf16 && cfg->scheduler == TL_SCHED_DATAFLOW && (ctx->hx_steps + 1) / 2 <= SPLIT_MAX_S) ctx->split = (ctx->hx_steps + 1) / 2;
+    // RNTN under the data-flow scheduler: the matrix of a hidden unit in a wave's registers, d <= 96
+    if (cfg->cell == TL_RNTN && cfg->scheduler == TL_SCHED_DATAFLOW && 2 * round_up(H, 8) <= 32 * ROWS_MAX_STEPS) {
+        ctx->rows_steps = (2 * round_up(H, 8) + 31) / 32;
+        ctx->rows_seg = round_up(H, 8) / 8;
+    }
+    ctx->flow_set = ctx->rows_steps > 0 ? (H + ROWS_UNITS - 1) / ROWS_UNITS : ctx->n_cg;
     const int ws_steps16 = bf16 ? 8 * ctx->spw : 4 * ctx->spw;   // K axis of the weight-stationary cell in k-steps of 16
     ctx->spw_leaf = 0;
     ctx->es = round_up(E, 8);
@@ -819,6 +875,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         ctx->ng_bwd_inner = (2 * H) % 4 == 0 ? 4 : 1;
         ctx->ws_steps16 = ws_steps16;
         rc = pack_treernn_f32(ctx, nullptr);
+        if (rc == TL_OK) rc = pack_split(ctx, PackList{}, nullptr);
         TL_HIP(hipDeviceSynchronize());
         if (rc != TL_OK) return rc;
     } else if (cfg->cell == TL_TREERNN) {
@@ -908,21 +965,24 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         if (o1 < 1 || ctx->ws_grid < ctx->n_cg + 1) ctx->spw = 0;
     }
 
-    if (cfg->scheduler == TL_SCHED_DATAFLOW && (ctx->spw > 0 || ctx->split > 0)) {
-        const size_t lds = ctx->split > 0 ? sizeof(SplitSmem) : ctx->ws_lds;
-        int o = 0, o_min = bf16 ? 2 : 1;
-        for (int v = 0; v < 2; ++v) {
-            const fwd_kernel fk = flow_kernel(cfg->cell, v != 0, ctx->spw, ctx->split, bf16);
+    if (cfg->scheduler == TL_SCHED_DATAFLOW && (ctx->spw > 0 || ctx->split > 0 || ctx->rows_steps > 0)) {
+        const int set = ctx->flow_set;
+        size_t lds = 0;
+        int o_min = bf16 || cfg->cell != TL_TREELSTM ? 2 : 1;
+        for (int groups = 1; groups <= 2; ++groups) {      // (TreeRNN: two kernels)
+            const fwd_kernel fk = flow_kernel(ctx, groups, &lds);
             if ((rc = allow_lds(fk, lds)) != TL_OK) return rc;
+            int o = 0;
             TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(fk), WG_THREADS, lds));
             if (o < o_min) o_min = o;
         }
         ctx->flow_grid = o_min * ctx->n_cu;
-        if (ctx->split > 0) {
+        if (ctx->split > 0 || ctx->rows_steps > 0) {
             if ((rc = allow_lds(k_flow_schedule, SCHED_LDS_BYTES)) != TL_OK) return rc;
-            TL_HIP(hipMalloc(&ctx->sched_head, (size_t)(ctx->flow_grid / ctx->n_cg + 1) * sizeof(int4)));
+            if ((rc = allow_lds(k_leaf_copy, SCHED_LDS_BYTES)) != TL_OK) return rc;
+            TL_HIP(hipMalloc(&ctx->sched_head, (size_t)(ctx->flow_grid / ((set + 1) / 2) + 1) * sizeof(int4)));
         }
-        if (ctx->flow_grid < ctx->n_cg) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
+        if (ctx->flow_grid < set) ctx->flow_grid = 0;       // not even one set of workgroups: the level scheduler stands in
     }
     if (ctx->spw_leaf > 0) {
         const size_t lds = leaf_lds_bytes(ctx->spw_leaf, bf16, ctx->split > 0);
@@ -1082,9 +1142,11 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool persistent = cfg.scheduler != TL_SCHED_LEVEL_HOST;
     // the data-flow scheduler needs the weight-stationary cell and its private lists; without them (RNTN, sizes the
     // cell does not take, the fixed workspace) the level scheduler on the device stands in.
-    const int split = in_split_range(ctx, n_nodes) ? ctx->split : 0;
-    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_grid > 0 &&
-                      (cfg.cell == TL_TREELSTM && !bf16 ? split > 0 : spw > 0);
+    const bool sched_range = in_split_range(ctx, n_nodes);
+    const int split = sched_range ? ctx->split : 0;
+    const bool rows = ctx->rows_steps > 0 && sched_range;      // the cells that gather rows (cell_rows.hpp)
+    const bool flow = cfg.scheduler == TL_SCHED_DATAFLOW && !static_ws && ctx->flow_grid > 0 && (bf16 ? spw > 0 : split > 0 || rows);
+    const bool scheduled = flow && (split > 0 || rows);        // ... and prepared blocks
     // A batch of few large trees: the data-flow scheduler deals whole trees to its sets of workgroups, so with fewer
     // trees than sets the others stay idle: one bushy tree of 16 384 leaves takes 3.5 ms on one set against 0.34 ms
     // level by level on all of them, while a deep chain of 2 048 leaves takes 6.4 ms data-flow and 11.8 ms level by
@@ -1094,35 +1156,42 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     // (What the kernel that is not picked costs, its launch: with an odd hidden size, H = 35, one to eight bushy trees of 200 to 400 leaves
     // take 84 ... 105 us level by level alone and 88 ... 108 with both launched, chains of those sizes 1 555 ... 3 324 against
     // 342 ... 567.)
-    const int flow_sets = ctx->n_cg > 0 ? ctx->flow_grid / ctx->n_cg : 0;
+    // (TreeRNN: one column group per workgroup if every tree then has a set of its own, else two; cell_split.hpp)
+    const int rnn_groups = n_trees <= ctx->flow_grid / ctx->flow_set ? 1 : 2;
+    const int flow_set = cfg.cell == TL_TREERNN && split > 0 && rnn_groups == 2 ? (ctx->flow_set + 1) / 2 : ctx->flow_set;
+    const int flow_sets = ctx->flow_grid / flow_set;
     const bool flow_or_levels = flow && n_trees < flow_sets && n_nodes / (n_trees > 0 ? n_trees : 1) >= FLOW_LARGE_TREE_NODES;
     if (persistent && spw > 0 && bf16) {
         f.hb = static_ws ? reinterpret_cast<unsigned short *>(ctx->scratch + NOALLOC_WS_BYTES) : ctx->hb;
         f.hs = ctx->hs;
     }
-    if (flow && split > 0) {
+    if (scheduled) {
         if ((rc = ensure_split(ctx, n_nodes)) != TL_OK) return rc;
+        f.sched = ctx->sched; f.sched_head = ctx->sched_head;
+    }
+    if (flow && split > 0) {
         f.hx = ctx->hx;
         f.hx_steps = ctx->hx_steps;
-        f.sched = ctx->sched; f.sched_head = ctx->sched_head;
         f.xi.wp = ctx->xp_inner; f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u;
+        f.hx_back = ctx->hx_back;
     }
     // The persistent kernels' workgroups wait for each other, so all of them must be resident at once: the grid is
     // cut to what the device holds of the very kernel that is launched (the figure taken at tl_create is that of one
     // variant), and a kernel of which not even one set of workgroups fits is refused here, not found out by a stall.
     const bool ready_sched = cfg.scheduler == TL_SCHED_READY || cfg.scheduler == TL_SCHED_READY_PRIORITY;
+    size_t flow_lds = 0;
     const fwd_kernel kern = !persistent ? nullptr
                             : ready_sched ? ready_kernel(cfg.cell, vec4_inner, spw, bf16)
-                            : flow ? flow_kernel(cfg.cell, vec4_inner, spw, split, bf16) : levels_kernel(cfg.cell, vec4_inner, spw, bf16);
+                            : flow ? flow_kernel(ctx, rnn_groups, &flow_lds) : levels_kernel(cfg.cell, vec4_inner, spw, bf16);
     const size_t level_lds = spw > 0 ? ctx->ws_lds : TILE_SMEM_BYTES;
-    const size_t kern_lds = flow && split > 0 ? sizeof(SplitSmem) : level_lds;
+    const size_t kern_lds = flow ? flow_lds : level_lds;
     const bool whole_sets = spw > 0 || flow;          // every workgroup of the kernel is tied to one column group
     int grid_p = flow ? ctx->flow_grid : (persistent && spw > 0) ? ctx->ws_grid : ctx->persistent_grid;
     if (kern) {
         int per_cu = 0;
         if ((rc = resident_per_cu(ctx, kern, kern_lds, &per_cu)) != TL_OK) return rc;
         if (per_cu * ctx->n_cu < grid_p) grid_p = per_cu * ctx->n_cu;
-        if (grid_p < (whole_sets ? ctx->n_cg : 1) + (ready_sched ? 1 : 0)) return TL_EHIP;
+        if (grid_p < (flow ? flow_set : whole_sets ? ctx->n_cg : 1) + (ready_sched ? 1 : 0)) return TL_EHIP;
     }
     int grid_l2 = 0;                                  // grid of the level kernel where it is launched beside the data-flow kernel
     if (flow_or_levels) {
@@ -1133,14 +1202,15 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         if (spw > 0) grid_l2 = grid_l2 / ctx->n_cg * ctx->n_cg;
         if (grid_l2 < (spw > 0 ? ctx->n_cg : 1)) return TL_EHIP;
     }
-    f.cap_tiles = grid_p / ctx->n_cg > 0 ? grid_p / ctx->n_cg : 1;
+    const int grid_tiles = flow_or_levels ? grid_l2 : grid_p;      // (of the kernel that works in tiles)
+    f.cap_tiles = grid_tiles / ctx->n_cg > 0 ? grid_tiles / ctx->n_cg : 1;
     if (cfg.cell == TL_RNTN) {
         f.xi.scale = ctx->xs_inner; f.xi.w = ctx->m_u;
         f.rntn_v = ctx->m_v;
     }
     // RNTN: a frontier of at most rntn_units tiles is cut into RNTN_PARTS workgroups per tile and column group
     f.rntn_part = ctx->rntn_part; f.rntn_done = ctx->rntn_done;
-    f.rntn_units = cfg.cell == TL_RNTN ? (2 * grid_p / ctx->n_cg < ctx->rntn_units ? 2 * grid_p / ctx->n_cg : ctx->rntn_units) : 0;
+    f.rntn_units = cfg.cell == TL_RNTN ? (2 * grid_tiles / ctx->n_cg < ctx->rntn_units ? 2 * grid_tiles / ctx->n_cg : ctx->rntn_units) : 0;
     // ready scheduler: gangs of gang_size compute workgroups plus one scheduler workgroup each
     f.gang_size = ctx->n_cg + 1 <= grid_p ? ctx->n_cg : grid_p - 1;
     f.n_gangs = grid_p / (f.gang_size + 1) < MAX_GANGS ? grid_p / (f.gang_size + 1) : MAX_GANGS;
@@ -1164,10 +1234,10 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool need_levels = cfg.scheduler == TL_SCHED_LEVEL_HOST || cfg.validate != 0;
     f.priority = cfg.scheduler == TL_SCHED_READY_PRIORITY ? 1 : 0;
     if (flow) {
-        f.flow = (cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range) ? 2 : 1;
+        f.flow = (scheduled && cfg.cell != TL_TREELSTM) || (cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range) ? 2 : 1;
         // (with no internal node the data-flow kernel is not launched; where the level kernel may run instead, the root passes do)
         f.flow_roots = f.n_int > 0 && !need_levels && !flow_or_levels ? 1 : 0;
-        f.n_slots = grid_p / ctx->n_cg;
+        f.n_slots = grid_p / flow_set;
         // Slots inside one L2 domain each (split_place): the dependent steps are shorter, the requests of a slot queue at one L2.  Pays
         // where few workgroups gather the same rows, or where a slot has no more than a tree or so and is one dependent chain.
         // Forward, slots on all domains -> inside: H = 48, 24 chains of 100 to 300 leaves 463 -> 416 us, 64 parse trees 39.6 -> 37.6, 1 500 of
@@ -1176,8 +1246,8 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         // 60 leaves 140 -> 158; H = 256, 100 parse trees 73.6 -> 78.1, 64 trees of 1 024 leaves 2 760 -> 2 869; H = 512, one chain 468 -> 507, 25 parse
         // trees 71.9 -> 81.6.
         const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
-        f.place = ctx->n_cg <= 3 || (ctx->n_cg <= 10 && 4ll * n_trees <= 3ll * f.n_slots) ||
-                  (ctx->n_cg <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
+        f.place = flow_set <= 3 || (flow_set <= 10 && 4ll * n_trees <= 3ll * f.n_slots) ||
+                  (flow_set <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
         f.flow_seen = reinterpret_cast<int32_t *>(ctx->flow_ws);
         f.flow_list = reinterpret_cast<int4 *>(ctx->flow_ws + align256((size_t)ctx->n_cg * ctx->cap_nodes * sizeof(int32_t)));
     }
@@ -1226,11 +1296,11 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (prof) TL_HIP(hipEventRecord(ev[1], st));
 
     // ---- leaves ------------------------------------------------------------------------
-    const int n_sched = flow && split > 0 && f.n_int > 0 ? f.n_slots : 0;      // workgroups that prepare the split cell's schedule
+    const int n_sched = scheduled && f.n_int > 0 ? f.n_slots : 0;      // workgroups that prepare the schedule
     Fwd fl = f;
     fl.pick = flow_or_levels ? 1 : 0;
     const bool leaf_ws = cfg.cell == TL_TREELSTM && ctx->spw_leaf > 0 && ws_range;      // (its cell addresses h and c with 32-bit offsets)
-    if (n_sched > 0 && !leaf_ws)
+    if (n_sched > 0 && !leaf_ws && cfg.cell == TL_TREELSTM)
         hipLaunchKernelGGL(k_flow_schedule, dim3(n_sched), dim3(WG_THREADS), SCHED_LDS_BYTES, st, fl);
     if (leaf_ws && bf16) {
         hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, false), st, f);
@@ -1242,7 +1312,13 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         hipLaunchKernelGGL(static_kernel(EPI_LSTM_LEAF, vec4_leaf, bf16), dim3(plan.n_tiles * ctx->n_cg), dim3(WG_THREADS),
                            TILE_SMEM_BYTES, st, f, (const int32_t *)f.leaf_list, f.n_leaf, plan);
     } else {
-        hipLaunchKernelGGL(k_leaf_copy, dim3(f.n_leaf), dim3(128), 0, st, f);
+        // (a wave per node, in as many workgroups as are resident at once)
+        const int copies = n_sched > 0 ? n_nodes : f.n_leaf, copy_grid = (copies + 3) / 4 < 8 * ctx->n_cu ? (copies + 3) / 4 : 8 * ctx->n_cu;
+        // All workgroups of a launch have the LDS of those that prepare the schedule: with 52 KB three fit on a CU, and the copies of 256 parse
+        // trees (8 workgroups per CU) went in three rounds, 15.6 us; so little of it where the slots are small that all are resident.
+        const size_t small = 16 * 1024;
+        const size_t lds = n_sched == 0 ? 0 : sched_lds_bytes(4 * (size_t)(n_nodes / n_sched) + 256) <= small ? small : SCHED_LDS_BYTES;
+        hipLaunchKernelGGL(k_leaf_copy, dim3(n_sched + copy_grid), dim3(WG_THREADS), lds, st, fl, n_sched, (int)lds);
     }
     TL_HIP(hipGetLastError());
     if (prof) TL_HIP(hipEventRecord(ev[2], st));
@@ -1255,15 +1331,22 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
             ctx->last_grid = grid_r;
         } else if (cfg.scheduler == TL_SCHED_LEVEL_DEVICE || cfg.scheduler == TL_SCHED_DATAFLOW) {
             // weight-stationary cell: every workgroup is tied to one column group, so whole sets only
-            const int grid_l = whole_sets ? grid_p / ctx->n_cg * ctx->n_cg : grid_p;
+            const int grid_l = flow ? grid_p / flow_set * flow_set : whole_sets ? grid_p / ctx->n_cg * ctx->n_cg : grid_p;
+            Fwd fk = f;
+            if (flow) fk.n_cg = flow_set;
+            if (rows && flow) {
+                fk.xi.wp = ctx->rows_wp; fk.xi.scale = ctx->rows_scale;
+                fk.seg_chunks = ctx->rows_seg;
+            }
             if (flow_or_levels) {                     // both kernels; every workgroup of the one that is not picked returns at once
-                Fwd g = f;
+                Fwd g = fk;
                 g.pick = 1;
                 hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, g);
+                g = f;
                 g.pick = 2;
                 hipLaunchKernelGGL(levels_kernel(cfg.cell, vec4_inner, spw, bf16), dim3(grid_l2), dim3(WG_THREADS), level_lds, st, g);
             } else {
-                hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, f);
+                hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, fk);
             }
             ctx->last_grid = grid_l;
         } else {

@@ -82,3 +82,60 @@ def test_infinities_are_summed_in_fp32(where, sched):
     ok = ~np.isnan(ref["h"])
     assert (np.abs(ref["h"][trees.left >= 0][:, 5]) == 1).any()
     np.testing.assert_allclose(got["h"][ok], ref["h"][ok], rtol=RTOL, atol=ATOL)
+
+
+# ---- TreeRNN under the data-flow scheduler: the split cell with rows of any scale ------------------------------------
+@pytest.mark.parametrize("n_trees", [9, 700])           # one column group per workgroup, and two
+@pytest.mark.parametrize("H", [1, 15, 16, 17, 33, 64, 65, 129, 256, 301, 479, 512])
+def test_treernn_sizes_at_the_edges_of_the_tiles(H, n_trees):
+    print("case rnn split sizes", H, n_trees, flush=True)
+    params = synth.make_rnn_params(740 + H, synth.CELL_TREERNN, 60, H, scale=1.0 / H ** 0.5)
+    params.emb *= np.float32(H ** 0.5)
+    trees = synth.make_trees(741, ([1, 2, 3, 1, 18, 40, 9, 33, 64] * 78)[:n_trees], (["random", "chain", "balanced"] * 234)[:n_trees], 60)
+    got, ref = run(params, trees, "dataflow"), oracle.forward_params(params, trees, n_threads=8)
+    # (sums of up to 1 024 products of which those of leaves reach 1)
+    for key in ("h", "h_root"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=4e-6, err_msg=key)
+
+
+def test_treernn_rows_and_columns_of_very_different_size():
+    """Leaves keep the scale of their embedding row: sizes from 1e-3 to 1e3 side by side, columns of the weights from 1e-6 to 1."""
+    print("case rnn split scales", flush=True)
+    H = 72
+    p = synth.make_rnn_params(750, synth.CELL_TREERNN, 60, H, scale=0.1)
+    rng = np.random.default_rng(2)
+    p.u *= (10.0 ** rng.uniform(-6, 0, H)).astype(np.float32)
+    p.emb *= (10.0 ** rng.uniform(-3, 1, p.emb.shape[0])).astype(np.float32)[:, None]
+    p.emb[::9] *= 1e3
+    trees = synth.make_trees(751, [30, 8, 1, 21], ["random", "chain", "random", "balanced"], 60)
+    got, ref = run(p, trees, "dataflow"), oracle.forward_params(p, trees, n_threads=8)
+    # a sum over a row of 1e3 carries 2^-21 of its absolute products (144 of up to 100): 7e-3 where it does not saturate
+    big = np.abs(ref["h"]).max(axis=1) > 20
+    inner = trees.left >= 0
+    over_big = np.zeros(trees.n_nodes, dtype=bool)
+    over_big[inner] = big[trees.left[inner]] | big[trees.right[inner]]
+    tainted = over_big.copy()                           # and what stands on such a node
+    for _ in range(40):
+        tainted[inner] |= tainted[trees.left[inner]] | tainted[trees.right[inner]]
+    assert tainted.any() and not tainted[inner].all()
+    np.testing.assert_allclose(got["h"][~tainted], ref["h"][~tainted], rtol=RTOL, atol=4e-6)
+    np.testing.assert_allclose(got["h"][tainted], ref["h"][tainted], rtol=RTOL, atol=7e-3)
+
+
+@pytest.mark.parametrize("where", ["u", "emb"])
+def test_treernn_infinities_are_summed_in_fp32(where):
+    print("case rnn infinity", where, flush=True)
+    H = 40
+    p = synth.make_rnn_params(760, synth.CELL_TREERNN, 30, H, scale=0.1)
+    p.emb[:] = np.abs(p.emb) + 0.1
+    p.u[:] = np.abs(p.u)
+    if where == "u":
+        p.u[3, 5] = np.inf
+    else:
+        p.emb[::3, 5] = np.inf
+    trees = synth.make_trees(761, [12, 5, 1, 20], ["random"] * 4, 30)
+    with np.errstate(all="ignore"):
+        ref = oracle.forward_params(p, trees, n_threads=8)
+    got = run(p, trees, "dataflow")
+    assert not np.isnan(ref["h"]).any() and (ref["h"][trees.left >= 0][:, 5] == 1).any()
+    np.testing.assert_allclose(got["h"], ref["h"], rtol=RTOL, atol=4e-6)
