@@ -104,10 +104,11 @@ template <int SPW> struct WsLoadGeom {
 // NaN).  Rows that do not exist (-1 in the row table) read row 0 instead: every MFMA output row
 // depends on its own A row only, and the results of such rows are never stored.
 // The caller guarantees rows < 2^24 and table bytes < 2^32.
-// TAIL: fp32 rows whose length is even but not a multiple of 4 (so rows are 8-byte, not 16-byte
-// aligned, which the two 8-byte loads of a device-scope request tolerate).  The last request of
-// a row then covers two elements of the row and two of whatever follows it in memory; the lanes
-// concerned take their second 8 bytes from a block of zeros instead.
+// TAIL: fp32 rows of any length and alignment (a buffer load of 16 bytes needs 4-byte alignment only).  The last request of a row
+// then covers up to three elements of whatever follows it in memory, which are replaced by zeros when they arrive
+// (three selects a request; two 8-byte loads and a block of zeros, for even lengths only, were no faster: 25 trees at H = 150
+// 114 us either way.  Odd lengths went to the streaming cell: 57 trees at H = 301 369 -> 184 us, 20 at H = 37 144 -> 95, TreeRNN 50
+// at d = 257 202 -> 125, all under the ready scheduler).
 template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowRequest {
     using G = WsLoadGeom<SPW>;
     static constexpr int EPL = 16 / (int)sizeof(T);             // elements per lane and load
@@ -116,8 +117,7 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     unsigned lane_off, row_bytes;
     int sub;
     unsigned off[G::NL];
-    const char *hi_base;                                        // TAIL only: where the second 8 bytes come from
-    unsigned hi_mask;
+    int valid;                                                  // TAIL only: elements of this lane's request that belong to the row
     __amdgpu_buffer_rsrc_t rsrc;                                // the table as a raw buffer (device-scope requests)
 
     // rows of `table` are `stride` elements apart; what a row holds between its data and `stride`
@@ -138,9 +138,7 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
         else src = sm.src0;
         lane_off = (unsigned)o * (unsigned)sizeof(T);
         row_bytes = (unsigned)stride * (unsigned)sizeof(T);
-        const bool tail = TAIL && o + EPL > stride;
-        hi_base = tail ? reinterpret_cast<const char *>(f.zeros) : table + 8;
-        hi_mask = tail ? 0u : ~0u;
+        valid = stride - o;
     }
     // byte offsets of the requests of block [row0, row0 + 16): one batch of row-table reads
     __device__ inline void prepare(int row0)
@@ -153,29 +151,30 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     }
     template <bool COH> __device__ inline floatx4 issue(int j) const
     {
-        if constexpr (!TAIL && COH) {
+        if constexpr (COH || TAIL) {
             // one 16-byte device-scope load (buffer_load_dwordx4 ... sc1)
             typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-            const uintx4 u = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off[j], 0, 16);
+            const uintx4 u = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off[j], 0, COH ? 16 : 0);
             floatx4 v;
             v.x = __uint_as_float(u.x);
             v.y = __uint_as_float(u.y);
             v.z = __uint_as_float(u.z);
             v.w = __uint_as_float(u.w);
             return v;
-        } else if constexpr (!TAIL) {
-            return ld_f4<COH>(reinterpret_cast<const float *>(table + off[j]));
         } else {
-            static_assert(sizeof(T) == 4, "tail handling is for fp32 rows");
-            const unsigned long long a = ld_dev(reinterpret_cast<const unsigned long long *>(table + off[j]));
-            const unsigned long long b = ld_dev(reinterpret_cast<const unsigned long long *>(hi_base + (off[j] & hi_mask)));
-            floatx4 v;
-            v.x = __uint_as_float((unsigned)a);
-            v.y = __uint_as_float((unsigned)(a >> 32));
-            v.z = __uint_as_float((unsigned)b);
-            v.w = __uint_as_float((unsigned)(b >> 32));
-            return v;
+            return ld_f4<COH>(reinterpret_cast<const float *>(table + off[j]));
         }
+    }
+    // what issue() has brought, without what does not belong to the row
+    __device__ inline floatx4 whole(floatx4 v) const
+    {
+        if constexpr (TAIL) {
+            static_assert(sizeof(T) == 4, "tail handling is for fp32 rows");
+            v.y = valid > 1 ? v.y : 0.f;
+            v.z = valid > 2 ? v.z : 0.f;
+            v.w = valid > 3 ? v.w : 0.f;
+        }
+        return v;
     }
 };
 
@@ -296,7 +295,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
     constexpr int NG = EpiTraits<EPI>::NG;
     constexpr int SEG = EpiTraits<EPI>::SEG;
     constexpr int NL = WsLoadGeom<SPW>::NL;
-    static_assert(!(FLOW && EPI == EPI_LSTM_INNER), "the fp32 TreeLSTM has a cell of its own under the data-flow scheduler (cell_split.hpp)");
+    static_assert(!FLOW || EPI == EPI_TD_CHILD, "the fp32 cells of the data-flow scheduler are those of cell_split.hpp and cell_rows.hpp");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int nrb = (count + 15) >> 4;
     const int H = f.H;
@@ -386,18 +385,15 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
     float p_cl = 0.f, p_cr = 0.f;
     int p_erow = 0;
     constexpr int FINISH_AFTER = SPW > 1 ? 1 : 0;               // k-step after which the previous block is finished
-    // A piece's last block with few rows takes the narrow form below the loop (TreeRNN under the data-flow scheduler only: in
-    // top-down generation the place of a node in a tile depends on timing, and its bits must not).
-    constexpr bool NARROW_FORM = FLOW && EPI != EPI_TD_CHILD;
-    constexpr int NARROW_MAX_RG = 2;                            // groups of four rows up to which that form is the faster one
-    const int n_rg = (count - (nrb - 1) * 16 + 3) >> 2;         // groups of four rows in the last block
-    const bool last_narrow = NARROW_FORM && nrb > 0 && n_rg <= NARROW_MAX_RG;
-    const int nrb_full = last_narrow ? nrb - 1 : nrb;
-    for (int rb = 0; rb < nrb_full; ++rb) {
+    for (int rb = 0; rb < nrb; ++rb) {
         float *red = sm.red[rb & 1];
         if constexpr (FLOW) {                               // the rows are there only when their producers have stored them
             if (!flow_wait_rows<float, COH, WsRowRequest<SEG, SPW, float, TAIL>, NL, WsLoadGeom<SPW>::RPL>(f, req, rows, req.sub))
                 sm.cmd[7] = 1;
+        }
+        if constexpr (TAIL) {
+#pragma unroll
+            for (int j = 0; j < NL; ++j) rows[j] = req.whole(rows[j]);
         }
         ws_park_rows<SPW>(sm, rows, wave, lane);            // waits for the requested rows
         // the next block's rows are requested between the k-steps below, one row load per step: the
@@ -454,96 +450,6 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
         // the two reduction buffers alternate: buffer rb & 1 is written again at the end of block
         // rb + 2, after every wave has passed the barrier inside block rb + 2, hence after it has
         // read this buffer (inside block rb + 1)
-    }
-    if constexpr (NARROW_FORM) {
-        // The 16x16x4 instruction takes 32 cycles however many of its 16 rows exist, and the dependent steps of a deep tree
-        // are blocks of one to four rows.  The 4x4x1 instruction (16 independent 4x4 products, 8 cycles) takes the same B
-        // operands - lane l holds U[k(l >> 4)][l & 15] - when its 16 products are read as (k class l >> 4) x (four hidden
-        // units): with A = a[4 rg + (l & 3)][k(l >> 4)] it accumulates, for rows 4 rg .. 4 rg + 3, the sum over the k of
-        // class l >> 4.  A group of four rows so costs a quarter of a block (measured: 4.1 ns per instruction against
-        // 14.6), and the four class sums of a wave are added when the row is finished.  A node's sum is then rounded in
-        // another order than in a full block; which form evaluates a node depends on its place in the list alone, which
-        // does not change from run to run.
-        if (last_narrow) {
-            const int rb = nrb - 1;
-            // Lane l of wave w finishes row w of a group of four rows for hidden unit l >> 2, from wave (l & 3)'s four class
-            // sums; the four lanes of a quad then add theirs in wave order.  (What is computed from the lane number here starts
-            // from a copy the compiler cannot see through: held in registers across the whole kernel, these few values made it
-            // spill others in the loop above.)
-            int nl = lane;
-            asm volatile("" : "+v"(nl));
-            const int n_hu = cg * HU + (nl >> 2);
-            const bool n_hu_ok = n_hu < H;
-            const unsigned n_hu_b = (unsigned)(n_hu_ok ? n_hu : 0) * 4u;
-            auto finish_narrow = [&](const float *red, int enode, bool ev, const float (&bias)[NG]) {
-                float gate[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g) {
-                    const floatx4 p = *reinterpret_cast<const floatx4 *>(&red[(((((nl & 3) * NG + g) * 4 + wave) * 16) + (nl >> 2)) * 4]);
-                    const float q = ((p.x + p.y) + p.z) + p.w;
-                    gate[g] = (((quad_bcast<0>(q) + quad_bcast<1>(q)) + quad_bcast<2>(q)) + quad_bcast<3>(q)) + bias[g];
-                }
-                // (the four lanes of a quad hold the same result)
-                if (ev && (nl & 3) == 0) buf_st_f<COH>(rs_h, (unsigned)enode * row_b + n_hu_b, tanh_f(gate[0]));
-            };
-
-            int n_enode = -1;
-            bool n_ev = false;
-            float n_bias[NG];
-            auto row_to_finish = [&](int rg) {                  // of this lane in group rg
-                const int erow = rb * 16 + rg * 4 + wave;
-                n_enode = erow < count ? sm.node[erow] : -1;
-                n_ev = n_enode >= 0 && n_hu_ok;
-            };
-            if (!flow_wait_rows<float, COH, WsRowRequest<SEG, SPW, float, TAIL>, NL, WsLoadGeom<SPW>::RPL>(f, req, rows, req.sub))
-                sm.cmd[7] = 1;
-            ws_park_rows<SPW>(sm, rows, wave, lane);
-            hook(rb);
-            row_to_finish(0);
-#pragma unroll
-            for (int g = 0; g < NG; ++g) n_bias[g] = __shfl(w.bias[g], nl >> 2);
-#pragma unroll 1
-            for (int rg = 0; rg < n_rg; ++rg) {
-                if (rg > 0) {
-                    __syncthreads();                        // every wave has written its partial sums of group rg - 1
-                    finish_narrow(sm.red[(rb + rg - 1) & 1], n_enode, n_ev, n_bias);
-                    row_to_finish(rg);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                floatx4 acc[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g) acc[g] = floatx4{0.f, 0.f, 0.f, 0.f};
-                const float *a4 = &sm.a[wave][(rg * 4 + (nl & 3)) * WsSmemT<SPW>::A_LD + (nl >> 4) * 4];
-                floatx4 av_next = *reinterpret_cast<const floatx4 *>(a4);
-#pragma unroll
-                for (int s = 0; s < SPW; ++s) {
-                    const floatx4 av = av_next;
-                    if (s + 1 < SPW) av_next = *reinterpret_cast<const floatx4 *>(a4 + (s + 1) * STEP_K);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-#pragma unroll
-                        for (int g = 0; g < NG; ++g)
-                            acc[g] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[i], w.b[s][g][i], acc[g], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                    if (s == FINISH_AFTER && rg == 0 && rb > 0) {
-                        __syncthreads();                    // every wave has written its partial sums of block rb - 1
-                        finish(sm.red[(rb - 1) & 1], p_enode, p_ev, p_cl, p_cr, p_erow);
-                        __builtin_amdgcn_sched_barrier(0);
-                    }
-                }
-                // [wave][gate][row][hidden unit][k class]: the four class sums of an element lie side by side
-                float *nred = sm.red[(rb + rg) & 1];
-#pragma unroll
-                for (int g = 0; g < NG; ++g)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) nred[((((wave * NG + g) * 4 + v) * 16) + (nl & 15)) * 4 + (nl >> 4)] = acc[g][v];
-            }
-            hook(-2);
-            __syncthreads();
-            finish_narrow(sm.red[(rb + n_rg - 1) & 1], n_enode, n_ev, n_bias);
-            __syncthreads();
-            return;
-        }
     }
     hook(-2);
     __syncthreads();

@@ -578,12 +578,13 @@ __device__ inline void flow_append(int4 *list, int capacity, int *len, unsigned 
     }
 }
 
-template <int EPI, bool VEC4, int SPW, bool BF16 = false>
-__global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fwd f)
+// (bf16 operands; the fp32 cells work on prepared blocks, see below)
+template <int EPI, int SPW>
+__global__ __launch_bounds__(WG_THREADS, 2) void k_flow_persistent(Fwd f)
 {
     static_assert(SPW > 0, "the data-flow scheduler uses the weight-stationary cell");
     extern __shared__ __align__(16) unsigned char smem_raw[];
-    using Smem = PersistentSmem<SPW, BF16>;
+    using Smem = PersistentSmem<SPW, true>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     Ctl *ctl = f.ctl;
     const int tid = threadIdx.x;
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     const int n_slots = gridDim.x / f.n_cg;
     const int member = blockIdx.x % f.n_cg, slot = blockIdx.x / f.n_cg;
     const int my_cg = member;
-    PersistentWeights<EpiTraits<EPI>::NG, SPW, BF16> w;        // (loaded below, behind the first requests of the scan)
+    PersistentWeights<EpiTraits<EPI>::NG, SPW, true> w;        // (loaded below, behind the first requests of the scan)
 
     int t_lo, t_hi, nb, ne;
     flow_cut(f, slot, n_slots, &t_lo, &t_hi, &nb, &ne);
@@ -625,8 +626,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
     // of up to 1 024 nodes then runs while the weights arrive, instead of behind them.
     scan_requests(nb);
     __builtin_amdgcn_sched_barrier(0);
-    if constexpr (BF16) ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
-    else ws_load(w, f.inner, my_cg, tid >> 6, tid & 63);
+    ws_load(w, sm, f.inner, my_cg, tid >> 6, tid & 63);
     __builtin_amdgcn_sched_barrier(0);
     for (int n = nb + tid; n < ne; n += WG_THREADS) seen[n] = 0u;
     int n_listed = 0, n_roots = 0;
@@ -728,8 +728,7 @@ __global__ __launch_bounds__(WG_THREADS, BF16 ? 2 : 1) void k_flow_persistent(Fw
                 ticket.p = -1;
             }
         };
-        if constexpr (BF16) ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
-        else ws_tile<EPI, true, SPW, !VEC4, true>(sm, f, f.inner, f.h, f.n_nodes, count, my_cg, w, hook);
+        ws_tile<EPI, true, SPW, true>(sm, f, f.inner, f.hb, f.n_nodes, f.hs, count, my_cg, w, hook);
         if (sm.cmd[7] != 0) return;                   // a wait was abandoned: everybody leaves
         pieces += 1;
         begin += count;

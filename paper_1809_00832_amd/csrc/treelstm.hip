@@ -155,7 +155,7 @@ typedef void (*fwd_kernel)(Fwd);
 typedef void (*tiles_kernel)(Fwd, const int32_t *, int, LevelPlan);
 
 // Steps per wave that the weight-stationary cell is instantiated for; 0 = streaming cell.
-const int WS_SIZES[] = {1, 2, 4, 5, 8, 16};
+const int WS_SIZES[] = {1, 2, 4, 5, 8, 10, 12, 16}, TD_SIZES[] = {1, 2, 4, 5, 8, 16};      // (forward, top-down generation)
 // Same for bf16 operands, in k-steps of 32.
 const int WSB_SIZES[] = {1, 2, 3, 4, 6, 8};
 
@@ -178,6 +178,8 @@ template <int EPI> fwd_kernel ready_kernel_epi(bool vec4, int spw, bool bf16)
     case 4: return vec4 ? k_ready_persistent<EPI, true, 4> : k_ready_persistent<EPI, false, 4>;
     case 5: return vec4 ? k_ready_persistent<EPI, true, 5> : k_ready_persistent<EPI, false, 5>;
     case 8: return vec4 ? k_ready_persistent<EPI, true, 8> : k_ready_persistent<EPI, false, 8>;
+    case 10: return vec4 ? k_ready_persistent<EPI, true, 10> : k_ready_persistent<EPI, false, 10>;
+    case 12: return vec4 ? k_ready_persistent<EPI, true, 12> : k_ready_persistent<EPI, false, 12>;
     case 16: return vec4 ? k_ready_persistent<EPI, true, 16> : k_ready_persistent<EPI, false, 16>;
     default: return vec4 ? k_ready_persistent<EPI, true, 0> : k_ready_persistent<EPI, false, 0>;
     }
@@ -201,6 +203,8 @@ template <int EPI> fwd_kernel levels_kernel_epi(bool vec4, int spw, bool bf16)
     case 4: return vec4 ? k_levels_persistent<EPI, true, 4> : k_levels_persistent<EPI, false, 4>;
     case 5: return vec4 ? k_levels_persistent<EPI, true, 5> : k_levels_persistent<EPI, false, 5>;
     case 8: return vec4 ? k_levels_persistent<EPI, true, 8> : k_levels_persistent<EPI, false, 8>;
+    case 10: return vec4 ? k_levels_persistent<EPI, true, 10> : k_levels_persistent<EPI, false, 10>;
+    case 12: return vec4 ? k_levels_persistent<EPI, true, 12> : k_levels_persistent<EPI, false, 12>;
     case 16: return vec4 ? k_levels_persistent<EPI, true, 16> : k_levels_persistent<EPI, false, 16>;
     default: return vec4 ? k_levels_persistent<EPI, true, 0> : k_levels_persistent<EPI, false, 0>;
     }
@@ -209,12 +213,12 @@ fwd_kernel flow_kernel_bf16(int cell, int s)
 {
     const bool lstm = cell == TL_TREELSTM;
     switch (s) {
-    case 1: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 1, true> : k_flow_persistent<EPI_RNN_INNER, true, 1, true>;
-    case 2: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 2, true> : k_flow_persistent<EPI_RNN_INNER, true, 2, true>;
-    case 3: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 3, true> : k_flow_persistent<EPI_RNN_INNER, true, 3, true>;
-    case 4: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 4, true> : k_flow_persistent<EPI_RNN_INNER, true, 4, true>;
-    case 6: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 6, true> : k_flow_persistent<EPI_RNN_INNER, true, 6, true>;
-    default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, true, 8, true> : k_flow_persistent<EPI_RNN_INNER, true, 8, true>;
+    case 1: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 1> : k_flow_persistent<EPI_RNN_INNER, 1>;
+    case 2: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 2> : k_flow_persistent<EPI_RNN_INNER, 2>;
+    case 3: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 3> : k_flow_persistent<EPI_RNN_INNER, 3>;
+    case 4: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 4> : k_flow_persistent<EPI_RNN_INNER, 4>;
+    case 6: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 6> : k_flow_persistent<EPI_RNN_INNER, 6>;
+    default: return lstm ? k_flow_persistent<EPI_LSTM_INNER, 8> : k_flow_persistent<EPI_RNN_INNER, 8>;
     }
 }
 // fp32 RNTN: the k-steps there are kernels for, the kernel and its LDS
@@ -334,6 +338,8 @@ size_t ws_lds_bytes(int spw, bool bf16)
     case 4: return sizeof(WsSmemT<4>);
     case 5: return sizeof(WsSmemT<5>);
     case 8: return sizeof(WsSmemT<8>);
+    case 10: return sizeof(WsSmemT<10>);
+    case 12: return sizeof(WsSmemT<12>);
     default: return sizeof(WsSmemT<16>);
     }
 }
@@ -785,8 +791,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     TL_HIP(hipMalloc(&ctx->emb, emb_bytes));
     TL_HIP(hipMemcpy(ctx->emb, cfg->emb, emb_bytes, hipMemcpyDeviceToDevice));
 
-    // Weight-stationary cell.  fp32: needs 16-byte aligned rows (H % 4 == 0) and at most 16 k-steps of
-    // 16 per wave; bf16: at most 8 k-steps of 32 per wave (its rows come from a padded bf16 copy of h).
+    // Weight-stationary cell.  fp32: at most 16 k-steps of 16 per wave (H <= 512); bf16: at most 8 k-steps of 32 per wave (its rows come from a padded bf16 copy of h).
     const bool bf16 = cfg->precision == TL_BF16_IN;
     ctx->spw = 0;
     ctx->hs = round_up(H, 8);
@@ -795,7 +800,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             const int needed = round_up(2 * ctx->hs, 128) / 128;
             for (int sz : WSB_SIZES)
                 if (sz >= needed) { ctx->spw = sz; break; }
-        } else if (H % 2 == 0) {      // rows of h must be 8-byte aligned at least
+        } else {
             const int needed = round_up(2 * round_up(H, 4), KC) / STEP_K / 4;
             for (int sz : WS_SIZES)
                 if (sz >= needed) { ctx->spw = sz; break; }
@@ -1137,8 +1142,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool bf16 = cfg.precision == TL_BF16_IN;
     // the weight-stationary cell addresses rows with 24-bit row numbers and 32-bit byte offsets
     const bool ws_range = n_nodes < (1 << 24) && (unsigned long long)n_nodes * cfg.hidden * 4ull < (1ull << 32);
-    const bool pair_inner = (cfg.hidden % 2 == 0) && (((uintptr_t)h & 7) == 0);      // rows 8-byte aligned
-    const int spw = ((bf16 || pair_inner) && ws_range) ? ctx->spw : 0;     // weight-stationary cell in the persistent kernels
+    const int spw = ws_range ? ctx->spw : 0;     // weight-stationary cell in the persistent kernels
     const bool persistent = cfg.scheduler != TL_SCHED_LEVEL_HOST;
     // the data-flow scheduler needs the weight-stationary cell and its private lists; without them (RNTN, sizes the
     // cell does not take, the fixed workspace) the level scheduler on the device stands in.
@@ -1845,7 +1849,7 @@ int tl_td_create(int hidden, const float *u_td, const float *b_td, const float *
         ctx->spw = 0;
         if (H % 4 == 0 && ctx->n_cu >= 2 * ctx->n_cg) {
             const int needed = round_up(H, KC) / STEP_K / 4;
-            for (int sz : WS_SIZES)
+            for (int sz : TD_SIZES)
                 if (sz >= needed) { ctx->spw = sz; break; }
         }
         // one side's [H x 4H] block of u_td, made contiguous for the packer
