@@ -739,10 +739,9 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_backward_heights(Fwd f, BwdHe
     }
 }
 
-// The same walk with the operand gradient on weight-stationary workgroups (TreeLSTM from kept activations, 5 H a
-// multiple of 128).  U^T is the one matrix that every height multiplies, so a workgroup owns 16 of the 2 H output
-// columns for the whole call and keeps its slice of U^T in registers: the K axis (5 H) in four quarters, one per wave,
-// 5 H / 64 k-steps x 4 registers each (160 at H = 512).  The rows of dG are long (5 H floats), so a block of 16 rows
+// The same walk with the operand gradient on weight-stationary workgroups (TreeLSTM from kept activations, TreeRNN; H <= 512).  U^T is the one matrix that every height multiplies, so a workgroup owns 16 of the 2 H output
+// columns for the whole call and keeps its slice of U^T in registers: the K axis (5 H, padded to 128 SPW2) in four quarters, one per wave,
+// 2 SPW2 k-steps x 4 registers each (160 at H = 512).  The rows of dG are long (5 H floats), so a block of 16 rows
 // passes through LDS in two halves of each wave's quarter: while the matrix instructions of one half run, the other
 // half (or the next block's first) is on its way.  A wave adds up its quarter in k order on one accumulator, the four
 // quarters meet in LDS and are added in wave order: the order of every other data path, so the same bits.  Sets of
@@ -755,8 +754,9 @@ template <int SPW2> struct OperandWsSmem {
     int cmd[8];
 };
 
-// (LSTM = false: TreeRNN, whose rows of dG have H values, so K = H: a multiple of 128, SPW2 = H / 128.)
-template <int SPW2, bool LSTM = true>
+// (LSTM = false: TreeRNN, whose rows of dG have H values.)
+// EXACT: rows of exactly 128 SPW2 values, all tables 16-byte aligned.
+template <int SPW2, bool LSTM, bool EXACT>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, BwdHeights b)
 {
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
     constexpr int PPR = 4 * SPW2;                           // 16-byte pieces of a row in one half of a wave's quarter
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int H = f.H, K = (LSTM ? 5 : 1) * H;
-    const int n_cg = 2 * H / HU;
+    const int n_cg = (2 * H + HU - 1) / HU;
     const int cg = (int)blockIdx.x % n_cg, slot = (int)blockIdx.x / n_cg, n_slots = (int)gridDim.x / n_cg;
     const int n_levels = f.ctl->n_levels;
     const long long first = (long long)blockIdx.x * blockDim.x + tid, stride = (long long)gridDim.x * blockDim.x;
@@ -810,11 +810,22 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
             c %= PPR;
         }
     };
-    auto park = [&](const floatx4 (&rows)[NLB]) {
+    // (What lies behind the end of a row - the next row, or nothing - meets zero weights, but it need not be finite:
+    // zeros stand in for it.)
+    auto park = [&](const floatx4 (&rows)[NLB], int half) __attribute__((always_inline)) {
         int r = lane / PPR, c = lane % PPR;
+        const int left = K - (wave * 2 + half) * SPW2 * STEP_K;
 #pragma unroll
         for (int j = 0; j < NLB; ++j) {
-            *reinterpret_cast<floatx4 *>(&a_w[r * Smem::A_LD + c * 4]) = rows[j];
+            float *dst = &a_w[r * Smem::A_LD + c * 4];
+            if (EXACT || left >= SPW2 * STEP_K || c * 4 + 4 <= left) {
+                *reinterpret_cast<floatx4 *>(dst) = rows[j];
+            } else {
+                dst[0] = c * 4 < left ? rows[j].x : 0.f;
+                dst[1] = c * 4 + 1 < left ? rows[j].y : 0.f;
+                dst[2] = c * 4 + 2 < left ? rows[j].z : 0.f;
+                dst[3] = 0.f;
+            }
             c += 64;
             r += c / PPR;
             c %= PPR;
@@ -827,9 +838,13 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
     for (int lvl = n_levels - 1; lvl >= 1; --lvl) {
         const int lo = f.level_off[lvl], n_rows = f.level_off[lvl + 1] - lo;
         const int32_t *list = f.level_nodes + lo;
-        // (H % 128 == 0; the host has checked the alignment)
-        if constexpr (LSTM) gate_grad_kept_rows<true, 4, true>(g, list, n_rows, lo, first, stride);
-        else rnn_gate_grad_rows<4, true>(g, list, n_rows, lo, first, stride);
+        if constexpr (LSTM) {
+            if (EXACT || b.kept_v4) gate_grad_kept_rows<true, 4, true>(g, list, n_rows, lo, first, stride);
+            else gate_grad_kept_rows<true, 1, true>(g, list, n_rows, lo, first, stride);
+        } else {
+            if (EXACT || b.kept_v4) rnn_gate_grad_rows<4, true>(g, list, n_rows, lo, first, stride);
+            else rnn_gate_grad_rows<1, true>(g, list, n_rows, lo, first, stride);
+        }
         if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
         const int n_blocks = (n_rows + 15) >> 4;
         if (slot < n_blocks) {
@@ -849,10 +864,10 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
             for (int half = 0; half < 2; ++half) {
                 // (the last block asks for rows that nobody uses: past the end of the table they read as zero)
                 if (half == 0) {
-                    park(rows0);
+                    park(rows0, 0);
                     request(rows0, lo + (blk + n_slots) * 16, 0);
                 } else {
-                    park(rows1);
+                    park(rows1, 1);
                     request(rows1, lo + (blk + n_slots) * 16, 1);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -877,7 +892,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
                 sum += sm.red[(3 * 4 + wave) * 64 + lane];
                 const int row = (lane >> 4) * 4 + wave, oc = cg * HU + (lane & 15);
                 const int child = sm.child[oc < H ? 0 : 1][row];
-                if (child >= 0) {
+                if (child >= 0 && oc < 2 * H) {
                     // (one contribution per element, from the node's only parent: an addition at the memory side gives the bits
                     // of load, add, store, and the wave does not wait for a load behind the rows it has requested ahead)
                     float *p = f.dh + (size_t)child * H + (oc < H ? oc : oc - H);

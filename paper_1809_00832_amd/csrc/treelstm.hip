@@ -431,11 +431,11 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
     // backward pass: U^T [5H x 2H] and W_leaf^T [3H x E] as contractions with a zero bias
     float *t = ctx->t_scratch, *zb = ctx->zero_bias;
     hipLaunchKernelGGL(k_transpose, dim3(1024), dim3(256), 0, st, (const float *)ctx->m_u, t, 2 * H, 5 * H);
-    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, 5 * H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 0, false,
+    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, 5 * H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 8 * ctx->bw_spw2, false,
                    &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
     if (rc != TL_OK) return rc;
     if (ctx->ng_bwd_inner == 4) {
-        rc = pack_gemm(t, zb, 1, 2 * H, 1, 5 * H, (2 * H + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
+        rc = pack_gemm(t, zb, 1, 2 * H, 1, 5 * H, (2 * H + HU - 1) / HU, 8 * ctx->bw_spw2, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
                        &ctx->bp_bwd_inner1, st);
         if (rc != TL_OK) return rc;
     }
@@ -522,11 +522,11 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
     if (rc != TL_OK) return rc;
     float *t = ctx->t_scratch, *zb = ctx->zero_bias;
     hipLaunchKernelGGL(k_transpose, dim3(1024), dim3(256), 0, st, (const float *)ctx->m_u, t, 2 * H, H);
-    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 0, false,
+    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 8 * ctx->bw_spw2, false,
                    &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
     if (rc != TL_OK) return rc;
     if (ctx->ng_bwd_inner == 4) {
-        rc = pack_gemm(t, zb, 1, 2 * H, 1, H, (2 * H + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
+        rc = pack_gemm(t, zb, 1, 2 * H, 1, H, (2 * H + HU - 1) / HU, 8 * ctx->bw_spw2, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
                        &ctx->bp_bwd_inner1, st);
         if (rc != TL_OK) return rc;
     }
@@ -751,30 +751,45 @@ void free_all(tl_ctx *ctx)
     delete ctx;
 }
 
-// The persistent backward kernel with the weight-stationary operand gradient, and the LDS it takes: TreeLSTM with
-// 5 H / 128 = spw2 (H = 128, 256, 384, 512), TreeRNN with H / 128 = spw2 (the same sizes).
+// The persistent backward kernel with the weight-stationary operand gradient, and the LDS it takes: rows of dG (5 H values, TreeRNN: H)
+// of at most 128 spw2 values, H <= 512.
 typedef void (*bwh_ws_kernel)(Fwd, BwdHeights);
-bwh_ws_kernel backward_ws_kernel(bool lstm, int spw2, size_t *lds)
+const int BW_STEPS[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 15, 16, 18, 20};
+template <int SPW2, bool LSTM> bwh_ws_kernel backward_ws_kernel_of(bool exact, size_t *lds)
+{
+    *lds = sizeof(OperandWsSmem<SPW2>);
+    // (rows of exactly 128 spw2 values: H a multiple of 128)
+    if constexpr (!LSTM || SPW2 % 5 == 0)
+        if (exact) return k_backward_heights_ws<SPW2, LSTM, true>;
+    return k_backward_heights_ws<SPW2, LSTM, false>;
+}
+bwh_ws_kernel backward_ws_kernel(bool lstm, int spw2, bool exact, size_t *lds)
 {
     if (lstm) {
         switch (spw2) {
-        case 5:  *lds = sizeof(OperandWsSmem<5>);  return bwh_ws_kernel(k_backward_heights_ws<5, true>);
-        case 10: *lds = sizeof(OperandWsSmem<10>); return bwh_ws_kernel(k_backward_heights_ws<10, true>);
-        case 15: *lds = sizeof(OperandWsSmem<15>); return bwh_ws_kernel(k_backward_heights_ws<15, true>);
-        case 20: *lds = sizeof(OperandWsSmem<20>); return bwh_ws_kernel(k_backward_heights_ws<20, true>);
-        default: break;
-        }
-    } else {
-        switch (spw2) {
-        case 1: *lds = sizeof(OperandWsSmem<1>); return bwh_ws_kernel(k_backward_heights_ws<1, false>);
-        case 2: *lds = sizeof(OperandWsSmem<2>); return bwh_ws_kernel(k_backward_heights_ws<2, false>);
-        case 3: *lds = sizeof(OperandWsSmem<3>); return bwh_ws_kernel(k_backward_heights_ws<3, false>);
-        case 4: *lds = sizeof(OperandWsSmem<4>); return bwh_ws_kernel(k_backward_heights_ws<4, false>);
-        default: break;
+        case 1:  return backward_ws_kernel_of<1, true>(exact, lds);
+        case 2:  return backward_ws_kernel_of<2, true>(exact, lds);
+        case 3:  return backward_ws_kernel_of<3, true>(exact, lds);
+        case 4:  return backward_ws_kernel_of<4, true>(exact, lds);
+        case 5:  return backward_ws_kernel_of<5, true>(exact, lds);
+        case 6:  return backward_ws_kernel_of<6, true>(exact, lds);
+        case 7:  return backward_ws_kernel_of<7, true>(exact, lds);
+        case 8:  return backward_ws_kernel_of<8, true>(exact, lds);
+        case 10: return backward_ws_kernel_of<10, true>(exact, lds);
+        case 12: return backward_ws_kernel_of<12, true>(exact, lds);
+        case 14: return backward_ws_kernel_of<14, true>(exact, lds);
+        case 15: return backward_ws_kernel_of<15, true>(exact, lds);
+        case 16: return backward_ws_kernel_of<16, true>(exact, lds);
+        case 18: return backward_ws_kernel_of<18, true>(exact, lds);
+        default: return backward_ws_kernel_of<20, true>(exact, lds);
         }
     }
-    *lds = 0;
-    return nullptr;
+    switch (spw2) {
+    case 1:  return backward_ws_kernel_of<1, false>(exact, lds);
+    case 2:  return backward_ws_kernel_of<2, false>(exact, lds);
+    case 3:  return backward_ws_kernel_of<3, false>(exact, lds);
+    default: return backward_ws_kernel_of<4, false>(exact, lds);
+    }
 }
 
 int create_impl(const tl_config *cfg, tl_ctx *ctx)
@@ -818,6 +833,12 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         ctx->rows_seg = round_up(H, 8) / 8;
     }
     ctx->flow_set = ctx->rows_steps > 0 ? (H + ROWS_UNITS - 1) / ROWS_UNITS : ctx->n_cg;
+    // Backward pass: k-steps of 16 in half a wave's quarter of a row of gate gradients
+    if (!bf16 && cfg->cell != TL_RNTN && H <= 512) {
+        const int needed = ((cfg->cell == TL_TREELSTM ? 5 : 1) * H + 127) / 128;
+        for (int sz : BW_STEPS)
+            if (sz >= needed) { ctx->bw_spw2 = sz; break; }
+    }
     const int ws_steps16 = bf16 ? 8 * ctx->spw : 4 * ctx->spw;   // K axis of the weight-stationary cell in k-steps of 16
     ctx->spw_leaf = 0;
     ctx->es = round_up(E, 8);
@@ -939,16 +960,19 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             if (o < o_min) o_min = o;
         }
         ctx->bw_grid = o_min * ctx->n_cu;
-        // weight-stationary operand gradient: 5 H / 128 k-steps per wave and half of its quarter of the K axis
+        // weight-stationary operand gradient
         ctx->bw_ws_grid = 0;
-        const int H_ = cfg->hidden, n_cg_b = 2 * H_ / HU;
-        if ((cfg->cell == TL_TREELSTM || cfg->cell == TL_TREERNN) && H_ % 128 == 0 && H_ <= 512 && ctx->n_cu >= n_cg_b) {
-            ctx->bw_spw2 = (cfg->cell == TL_TREELSTM ? 5 : 1) * H_ / 128;
-            size_t lds = 0;
-            const bwh_ws_kernel k = backward_ws_kernel(cfg->cell == TL_TREELSTM, ctx->bw_spw2, &lds);
-            if ((rc = allow_lds(k, lds)) != TL_OK) return rc;
-            int o = 0;
-            TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(k), WG_THREADS, lds));
+        const int n_cg_b = (2 * H + HU - 1) / HU;
+        if (ctx->bw_spw2 > 0 && ctx->n_cu >= n_cg_b) {
+            int o = 1;
+            for (int exact = 0; exact < 2; ++exact) {
+                size_t lds = 0;
+                const bwh_ws_kernel k = backward_ws_kernel(cfg->cell == TL_TREELSTM, ctx->bw_spw2, exact != 0, &lds);
+                if ((rc = allow_lds(k, lds)) != TL_OK) return rc;
+                int o1 = 0;
+                TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, reinterpret_cast<const void *>(k), WG_THREADS, lds));
+                if (o1 < o) o = o1;
+            }
             if (o >= 1) ctx->bw_ws_grid = ctx->n_cu / n_cg_b * n_cg_b;
         }
     }
@@ -1534,24 +1558,30 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // On request (tl_set_async_backward), gate gradients that need no contraction (kept activations; TreeRNN): all heights in
     // one persistent kernel, which finds the per-height lists on the device.  Nothing is read back, the call does not wait;
     // what the structure pass finds wrong with the batch is latched for tl_status, and every kernel below leaves at once.
+    const bool kept_or_rnn_v4 = lstm ? kept_v4 : vec4;
     const bool persistent_ok = ctx->bw_grid > 0 && !rntn && (kept || !lstm) && n_int > 0;
-    // TreeLSTM with H = 128, 256, 384 or 512: the operand gradient on weight-stationary workgroups (row offsets of dG in 32 bits)
-    // (TreeRNN: the same sizes, K = H)
-    const bool ws = persistent_ok && (lstm ? kept_v4 : vec4) && ctx->bw_ws_grid > 0 && ctx->ng_bwd_inner == 4 &&
+    // H <= 512: the operand gradient on weight-stationary workgroups (row offsets of dG in 32 bits).  Not for many nodes where rows of more
+    // than 2 304 values leave no registers for the general form (H = 500, training step, launches / this: 64 trees 836 / 831 us, 128
+    // 1 127 / 1 181, 256 1 667 / 1 818) or whole sets of workgroups leave a seventh of the CUs idle (H = 340, 256 trees 1 196 / 1 224; 64 666 / 605).
+    // Elsewhere it is the faster one: H = 16, 3 trees 221 / 172; H = 150, 25 373 / 277; H = 301, 57 668 / 537, 256 1 380 / 1 111; H = 450, 128
+    // 1 210 / 1 099; TreeRNN d = 50, 25 trees 265 / 183, d = 450, 250 833 / 714.
+    const bool exact_rows = kept_or_rnn_v4 && dg_cols == 128 * ctx->bw_spw2;
+    const bool many = !exact_rows && ((ctx->bw_spw2 > 18 && n_int > 2000) || (100 * ctx->bw_ws_grid < 86 * ctx->n_cu && n_int > 4000));
+    const bool ws = persistent_ok && ctx->bw_ws_grid > 0 && !many &&
                     (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
     const bool heights_on_device = ctx->async_backward > 0 && persistent_ok;
     auto launch_all_heights = [&]() {
         BwdHeights b{};
-        b.bwd4 = ctx->g_bwd_inner; b.bwd1 = ctx->g_bwd_inner1; b.ng_inner = ctx->ng_bwd_inner;
+        b.bwd4 = ctx->g_bwd_inner; b.bwd1 = ctx->ng_bwd_inner == 4 ? ctx->g_bwd_inner1 : ctx->g_bwd_inner; b.ng_inner = ctx->ng_bwd_inner;
         b.dg_int = dg_int;
-        b.kept_v4 = lstm ? (kept_v4 ? 1 : 0) : (vec4 ? 1 : 0);
+        b.kept_v4 = kept_or_rnn_v4 ? 1 : 0;
         const bool v4 = vec4 && dg_cols % 4 == 0;
         typedef void (*bwh_kernel)(Fwd, BwdHeights);
         const bwh_kernel k = lstm ? (v4 ? bwh_kernel(k_backward_heights<true, true>) : bwh_kernel(k_backward_heights<true, false>))
                                   : (v4 ? bwh_kernel(k_backward_heights<false, true>) : bwh_kernel(k_backward_heights<false, false>));
         if (ws) {
             size_t lds = 0;
-            const bwh_ws_kernel kw = backward_ws_kernel(lstm, ctx->bw_spw2, &lds);
+            const bwh_ws_kernel kw = backward_ws_kernel(lstm, ctx->bw_spw2, exact_rows, &lds);
             hipLaunchKernelGGL(kw, dim3(ctx->bw_ws_grid), dim3(WG_THREADS), lds, st, f, b);
         } else {
             hipLaunchKernelGGL(k, dim3(ctx->bw_grid), dim3(WG_THREADS), TILE_SMEM_BYTES, st, f, b);

@@ -36,3 +36,37 @@ def test_odd_sizes_give_the_same_bits_everywhere(H, cell):
         if first is None:
             first = got["h"]
         assert np.array_equal(got["h"], first), sched
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", h) for h in (1, 3, 16, 25, 26, 51, 77, 150, 205, 308, 359, 411, 461, 510)] +
+                         [("rnn", h) for h in (1, 50, 127, 129, 255, 301, 450)])
+def test_backward_in_one_kernel_at_any_size(cell, H):
+    """The weight-stationary operand gradient pads rows of gate gradients to a multiple of 128 values; what lies behind a row's end
+    does not matter: the gradients that reach the leaves are those of the launches per height bit for bit, and agree with
+    the checker (sums of at most 2 600 products of order one)."""
+    import torch
+    print("case backward sizes", cell, H, flush=True)
+    if cell == "lstm":
+        params = synth.make_treelstm_params(820 + H, 50, 21, H, "xavier")
+    else:
+        params = synth.make_rnn_params(820 + H, synth.CELL_TREERNN, 50, H, scale=0.5 / H ** 0.5)
+    trees = synth.make_trees(821, [1, 2, 30, 1, 7, 65, 3, 18], ["random", "chain"] * 4, 50)
+    g_h = torch.from_numpy(np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)).cuda()
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, True)
+        net.forward()
+        out = {}
+        for mode in (-1, 0, 1):
+            binding.tl_set_async_backward(net.ctx, mode)
+            out[mode] = {k: v.cpu().numpy() for k, v in binding.tl_backward(net.ctx, b, g_h, params.embed_dim).items()}
+            assert binding.tl_status(net.ctx) == 0
+        h, c = b["h"].cpu().numpy(), b["c"].cpu().numpy() if b["c"] is not None else None
+    finally:
+        net.close()
+    ref = oracle.backward(params, trees, h, c, g_h.cpu().numpy())
+    for mode in (0, 1):
+        assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
+    for k in ref:
+        np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
