@@ -306,7 +306,19 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 // operands are requested into registers before the current ones are multiplied.
 constexpr int WN_TILE = 64, WN_Q = 16, WN_LD = WN_TILE + 4;
 
-template <int SEG, bool VEC4>
+// RNTN: the rows contracted with are y = [dz_k a_q for all (k, q) | dz] (see k_rntn_rows), made from dz (d values a node) and the children's rows
+// where they are needed: column j is (k, q), its value dz[k] times element q of [h_left ; h_right].
+struct RntnY {
+    int k, seg, in;         // seg < 0: a column of dz itself
+};
+__device__ inline RntnY rntn_y(int j, int d)
+{
+    const int k = j / (2 * d), q = j - k * 2 * d;
+    if (k >= d) return RntnY{j - 2 * d * d, -1, 0};
+    return RntnY{k, q >= d ? 1 : 0, q >= d ? q - d : q};
+}
+
+template <int SEG, bool VEC4, bool RNTN = false>
 __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
                                                      const float *__restrict__ table, int L, const float *__restrict__ dg,
                                                      int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
@@ -353,7 +365,16 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
             const int seg = (SEG == 2 && k >= L) ? 1 : 0;
             floatx4 a = floatx4{0.f, 0.f, 0.f, 0.f}, b = a;
             if (live && k < K_out) a = *reinterpret_cast<const floatx4 *>(table + (size_t)(seg ? s1 : s0) * L + (k - seg * L));
-            if (live && j < n_cols) b = *reinterpret_cast<const floatx4 *>(dg + (size_t)q * n_cols + j);
+            if constexpr (RNTN) {                               // (four neighbouring columns of one k, or of dz)
+                if (live && j < n_cols) {
+                    const RntnY y = rntn_y(j, L);
+                    const float *z = dg + (size_t)q * L + y.k;
+                    if (y.seg < 0) b = *reinterpret_cast<const floatx4 *>(z);
+                    else b = *reinterpret_cast<const floatx4 *>(table + (size_t)(y.seg ? s1 : s0) * L + y.in) * *z;
+                }
+            } else if (live && j < n_cols) {
+                b = *reinterpret_cast<const floatx4 *>(dg + (size_t)q * n_cols + j);
+            }
 #pragma unroll
             for (int e = 0; e < 4; ++e) { ra[e] = a[e]; rb[e] = b[e]; }
         } else {
@@ -362,7 +383,16 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
                 const int k = k0 + lk + e, j = j0 + lk + e;
                 const int seg = (SEG == 2 && k >= L) ? 1 : 0;
                 ra[e] = (live && k < K_out) ? table[(size_t)(seg ? s1 : s0) * L + (k - seg * L)] : 0.f;
-                rb[e] = (live && j < n_cols) ? dg[(size_t)q * n_cols + j] : 0.f;
+                if constexpr (RNTN) {
+                    rb[e] = 0.f;
+                    if (live && j < n_cols) {
+                        const RntnY y = rntn_y(j, L);
+                        rb[e] = dg[(size_t)q * L + y.k];
+                        if (y.seg >= 0) rb[e] *= table[(size_t)(y.seg ? s1 : s0) * L + y.in];
+                    }
+                } else {
+                    rb[e] = (live && j < n_cols) ? dg[(size_t)q * n_cols + j] : 0.f;
+                }
             }
         }
     };
@@ -501,7 +531,7 @@ __device__ inline void wg_park(unsigned short (*dst)[WG_TILE][WG_LD], int col, i
 
 // The sums of a wave's 64 x 64 quarter at (k0, j0) over nodes [q_lo, q_hi) with fp32 instructions, straight from memory (rare, and
 // slow: every four nodes are a chain of three loads).
-template <int SEG>
+template <int SEG, bool RNTN>
 __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list, const float *table, int L, const float *dg, int n_cols, int k0,
                                                         int j0, int q_lo, int q_hi, floatx4 (&acc)[4][4])
 {
@@ -521,7 +551,13 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
             const int k = min(k0 + t * 16 + (lane & 15), K_out - 1), j = min(j0 + t * 16 + (lane & 15), n_cols - 1);
             const bool second = SEG == 2 && k >= L;
             a[t] = live ? table[(size_t)(second ? s1 : s0) * L + (second ? k - L : k)] : 0.f;
-            b[t] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+            if constexpr (RNTN) {
+                const RntnY y = rntn_y(j, L);
+                b[t] = live ? dg[(size_t)q * L + y.k] : 0.f;
+                if (live && y.seg >= 0) b[t] *= table[(size_t)(y.seg ? s1 : s0) * L + y.in];
+            } else {
+                b[t] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+            }
         }
 #pragma unroll
         for (int ta = 0; ta < 4; ++ta)
@@ -530,7 +566,7 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
     }
 }
 
-template <int SEG>
+template <int SEG, bool RNTN = false>
 __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
                                                              const float *__restrict__ table, int L, const float *__restrict__ dg,
                                                              int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
@@ -554,6 +590,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     const int col = tid & (WG_TILE - 1), half = (tid >> 7) * 16;
     const int k = min(k0 + col, K_out - 1), j = min(j0 + col, n_cols - 1);
     const int seg = (SEG == 2 && k >= L) ? 1 : 0, k_in = k - seg * L;
+    const RntnY y = RNTN ? rntn_y(j, L) : RntnY{0, 0, 0};
     float ra[16], rb[16];
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
     const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
@@ -565,7 +602,13 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
             const bool live = q < q_hi;
             const int src = sm.src[seg][min(q, q_hi - 1) - chunk];
             ra[i] = live ? table[(size_t)src * L + k_in] : 0.f;
-            rb[i] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+            if constexpr (RNTN) {
+                rb[i] = live ? dg[(size_t)q * L + y.k] : 0.f;
+                const int src_y = sm.src[y.seg > 0 ? 1 : 0][min(q, q_hi - 1) - chunk];
+                rb[i] *= live && y.seg >= 0 ? table[(size_t)src_y * L + y.in] : 1.f;
+            } else {
+                rb[i] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+            }
         }
     };
     for (int chunk = q_lo; chunk < q_hi; chunk += WG_SRC) {
@@ -622,7 +665,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
                 const float m = fabsf(acc[ta][tb][v]);
                 again |= !(m == 0.f || (m >= 0x1p-100f && m < __builtin_inff()));
             }
-    if (__builtin_expect(__ballot(again) != 0ull, 0)) wg_sums_again<SEG>(f, list, table, L, dg, n_cols, k0 + wr, j0 + wc, q_lo, q_hi, acc);
+    if (__builtin_expect(__ballot(again) != 0ull, 0)) wg_sums_again<SEG, RNTN>(f, list, table, L, dg, n_cols, k0 + wr, j0 + wc, q_lo, q_hi, acc);
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
@@ -900,6 +943,198 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, Bw
                 }
             }
             __syncthreads();                                // red and child are free again
+        }
+        if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
+    }
+}
+
+// RNTN (d <= 96): the same walk, one phase and one grid barrier per height.  The gradient of the operand,
+//     da_p = sum_k dz_k (sum_q S[(k, q)][p] a_q + W[p][k]),    dz = dh (1 - h^2),
+// has the shape of the forward's bilinear form (cell_rows.hpp): a wave keeps the whole matrix of ONE p - 16 k side by side in d / 16 blocks, the
+// contraction over q - as two fp16 terms in registers (128 at d = 64), multiplies the gathered rows [h_left ; h_right] of 16 nodes
+// with it, scales the products by dz_k where they are and adds them up across the lanes.  Nothing of the d (2d + 1) values per node
+// that the gradient is a contraction of is ever written (33 KB a node at d = 64); dz is (f.dg, by list position), for the weight gradient.
+// A child's dh has one contribution, added at the memory side.
+// Measured (training step; before: rows written, then contracted by the streaming cell with fp32 instructions, two launches per height): 256 parse
+// trees at d = 64 1 311 -> 580 us (operand gradient, rows and launches 880 -> 150), 200 at d = 48 1 037 -> 397, 150 at d = 96 2 877 -> 984, 8 at d = 64
+// 591 -> 243, 4 at d = 8 306 -> 161 (the last three with the forward's own change).  Error against 64 bits unchanged.
+template <int NS> struct RntnBwdSmem {
+    static constexpr int LDZ = 16 * NS + 4;
+    halfx8 split[2][NS * 2 * 64];                           // as in RowsSmem
+    float dz[2][16 * LDZ];
+    float back[2][16];
+    int child[2][2][16];
+    int cmd[8];
+};
+constexpr int rntn_bwd_sets_per_cu(int ns) { return ns <= 4 ? 2 : 1; }
+
+template <int NS>
+__global__ __launch_bounds__(WG_THREADS, (rntn_bwd_sets_per_cu(NS))) void k_backward_rntn(Fwd f, int n_sets)
+{
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    using Smem = RntnBwdSmem<NS>;
+    Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
+    constexpr int CPT = (NS + 3) / 4, LDZ = Smem::LDZ;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int d = f.H, seg = f.seg_chunks;
+    const int set_size = (int)gridDim.x / n_sets, member = (int)blockIdx.x % set_size, slot = (int)blockIdx.x / set_size;
+    if (decided_to_leave(&sm.cmd[7], tid == 0 && batch_rejected(f))) return;
+    const int p = member * ROWS_UNITS + wave, pp = p < 2 * d ? p : 0;      // (a wave beyond the last p computes the first one's sums and adds nothing)
+    halfx8 w[NS][NS][2];                                    // [k / 16][k-step over q]
+    float sc[NS], lin[NS];
+    {
+        const halfx8 *wp = reinterpret_cast<const halfx8 *>(f.xi.wp) + (size_t)pp * NS * NS * 128 + lane;
+#pragma unroll
+        for (int j = 0; j < NS; ++j)
+#pragma unroll
+            for (int t = 0; t < NS; ++t)
+#pragma unroll
+                for (int e = 0; e < 2; ++e) w[j][t][e] = wp[(size_t)((j * NS + t) * 2 + e) * 64];
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            sc[j] = f.xi.scale[((size_t)pp * 2 * NS + j) * HU + (lane & 15)];
+            lin[j] = f.xi.scale[((size_t)pp * 2 * NS + NS + j) * HU + (lane & 15)];
+        }
+    }
+    const unsigned row_b = (unsigned)d * 4u;
+    const __amdgpu_buffer_rsrc_t rs_h = buf_of(f.h, (unsigned long long)f.n_nodes * row_b);
+    const int my_row = tid >> 4, t16 = tid & 15;
+    const bool ragged = d != seg * 8;
+    uintx4_t rows[CPT][2];
+    float dh[NS], hn[NS];
+    int left = 0, right = 0;
+    auto request = [&](int node) __attribute__((always_inline)) {
+        left = f.left[node];
+        right = f.right[node];
+        const unsigned base0 = __umul24((unsigned)left, row_b), base1 = __umul24((unsigned)right, row_b);
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const int c = t16 + 16 * i;
+            const unsigned off = c < 2 * seg ? (c >= seg ? base1 + (unsigned)(c - seg) * 32u : base0 + (unsigned)c * 32u) : ~0u - 63u;
+            rows[i][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_h, (int)off, 0, 0);
+            rows[i][1] = __builtin_amdgcn_raw_buffer_load_b128(rs_h, (int)off + 16, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < NS; ++i) {
+            const int k = min(t16 + 16 * i, d - 1);
+            hn[i] = f.h[(size_t)node * d + k];
+            dh[i] = ld_dev(f.dh + (size_t)node * d + k);
+        }
+    };
+    unsigned epoch = 0, unused = 0;
+    int buf = 0;
+    const int n_levels = f.ctl->n_levels;
+#pragma unroll 1
+    for (int lvl = n_levels - 1; lvl >= 1; --lvl) {         // roots first: a parent is always higher than its children
+        const int lo = f.level_off[lvl], n_rows = f.level_off[lvl + 1] - lo, n_blocks = (n_rows + 15) >> 4;
+        const int32_t *list = f.level_nodes + lo;
+        // (rows beyond the height's last one stand in with that one: they are computed and not stored)
+        auto node_of = [&](int blk) __attribute__((always_inline)) { return list[min(blk * 16 + my_row, n_rows - 1)]; };
+        int node_next = 0;
+        if (slot < n_blocks) {
+            request(node_of(slot));
+            node_next = node_of(slot + n_sets);
+        }
+#pragma unroll 1
+        for (int blk = slot; blk < n_blocks; blk += n_sets, buf ^= 1) {
+            const bool here = blk * 16 + my_row < n_rows;
+            float m = 0.f;
+#pragma unroll
+            for (int i = 0; i < CPT; ++i) {
+                const int c = t16 + 16 * i, in = (c >= seg ? c - seg : c) * 8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    if (ragged && in + e >= d) rows[i][e >> 2][e & 3] = 0u;      // the next row's, or nothing's
+                    m = fmaxf(m, fabsf(__uint_as_float(rows[i][e >> 2][e & 3])));
+                }
+            }
+            m = fmaxf(m, dpp<DPP_XOR1>(m));
+            m = fmaxf(m, dpp<DPP_XOR2>(m));
+            m = fmaxf(m, dpp<DPP_HALF_MIRROR>(m));
+            m = fmaxf(m, dpp<DPP_MIRROR>(m));
+            const unsigned eb = max(__float_as_uint(m) >> 23, 15u);
+            const float scale = __uint_as_float((268u - eb) << 23);
+            if (t16 == 0) {
+                sm.back[buf][my_row] = __uint_as_float((eb - 14u) << 23);
+                sm.child[buf][0][my_row] = here ? left : -1;
+                sm.child[buf][1][my_row] = here ? right : -1;
+            }
+#pragma unroll
+            for (int i = 0; i < CPT; ++i) {
+                const int c = t16 + 16 * i, s = c >> 2, quarter = c & 3;
+                if (NS % 4 != 0 && c >= 4 * NS) continue;
+                halfx8 hi, lo8;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const float v = __uint_as_float(rows[i][e >> 2][e & 3]) * scale;
+                    hi[e] = (_Float16)v;
+                    lo8[e] = (_Float16)(v - (float)hi[e]);
+                }
+                halfx8 *dst = &sm.split[buf][s * 128 + rows_slot(s, quarter, my_row)];
+                dst[0] = hi;
+                dst[64] = lo8;
+            }
+#pragma unroll
+            for (int i = 0; i < NS; ++i) {
+                const int k = t16 + 16 * i;
+                const float dz = k < d ? dh[i] * (1.f - hn[i] * hn[i]) : 0.f;
+                sm.dz[buf][my_row * LDZ + k] = dz;
+                if (member == 0 && here && k < d) f.dg[(size_t)(lo + blk * 16 + my_row) * d + k] = dz;
+            }
+            if (blk + n_sets < n_blocks) {
+                request(node_next);
+                node_next = node_of(blk + 2 * n_sets);
+            }
+            __syncthreads();
+            const halfx8 *op = sm.split[buf];
+            floatx4 t[NS];
+#pragma unroll
+            for (int j = 0; j < NS; ++j) t[j] = floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const halfx8 *o = &op[s * 128 + rows_slot(s, lane >> 4, lane & 15)];
+                const halfx8 hi = o[0], lo8 = o[64];
+#pragma unroll
+                for (int j = 0; j < NS; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, w[j][s][0], t[j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < NS; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, w[j][s][1], t[j], 0, 0, 0);
+#pragma unroll
+                for (int j = 0; j < NS; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo8, w[j][s][0], t[j], 0, 0, 0);
+            }
+            const floatx4 back = *reinterpret_cast<const floatx4 *>(&sm.back[buf][4 * (lane >> 4)]);
+            const float *z = &sm.dz[buf][4 * (lane >> 4) * LDZ + (lane & 15)];
+            float sum = 0.f;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                float x = 0.f;
+#pragma unroll
+                for (int j = 0; j < NS; ++j) x = __builtin_fmaf(z[v * LDZ + 16 * j], __builtin_fmaf(t[j][v] * sc[j], back[v], lin[j]), x);
+                x += dpp<DPP_XOR1>(x);
+                x += dpp<DPP_XOR2>(x);
+                x += dpp<DPP_HALF_MIRROR>(x);
+                x += dpp<DPP_MIRROR>(x);
+                if ((lane & 3) == v) sum = x;
+            }
+            const int row = 4 * (lane >> 4) + (lane & 3), child = sm.child[buf][p < d ? 0 : 1][row];
+            if ((lane & 15) < 4 && child >= 0 && p < 2 * d) {
+                bool again = __builtin_isnan(sum);
+                if (__builtin_expect(again, 0))
+                    for (int k = 0; k < d; ++k) again = again && !__builtin_isnan(sm.dz[buf][row * LDZ + k]);      // (nothing to gain there)
+                if (__builtin_expect(again, 0)) {
+                    // (an infinity has no two terms: in fp32 from the parameters as given)
+                    const float *hl = f.h + (size_t)sm.child[buf][0][row] * d, *hr = f.h + (size_t)sm.child[buf][1][row] * d;
+                    sum = 0.f;
+#pragma unroll 1
+                    for (int k = 0; k < d; ++k) {
+                        const float *v = f.rntn_v + (size_t)k * 4 * d * d;
+                        float x = f.xi.w[(size_t)p * d + k];
+#pragma unroll 1
+                        for (int q = 0; q < 2 * d; ++q) x = __builtin_fmaf(v[(size_t)p * 2 * d + q] + v[(size_t)q * 2 * d + p], q < d ? hl[q] : hr[q - d], x);
+                        sum = __builtin_fmaf(sm.dz[buf][row * LDZ + k], x, sum);
+                    }
+                }
+                (void)add_dev(f.dh + (size_t)child * d + (p < d ? p : p - d), sum);
+            }
         }
         if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
     }

@@ -36,7 +36,8 @@ struct RntnColumn {
     halfx8 hi[RNTN_MAX_STEPS], lo[RNTN_MAX_STEPS];
     float scale;            // what a sum of products is multiplied by
 };
-__device__ inline RntnColumn rntn_column(const float *__restrict__ s, int d, int Lp, int Q, int q, int k, int lane)
+// (full: all rows p, as they stand in s - the operand gradient's matrix)
+__device__ inline RntnColumn rntn_column(const float *__restrict__ s, int d, int Lp, int Q, int q, int k, int lane, bool full = false)
 {
     const int D2 = 2 * d;
     const bool linear = q == Q;
@@ -51,7 +52,7 @@ __device__ inline RntnColumn rntn_column(const float *__restrict__ s, int d, int
         for (int i = 0; i < 8; ++i) {
             const int p = 32 * t + 8 * (lane >> 4) + i, pseg = p / Lp, off = p - pseg * Lp;
             float v = 0.f;
-            if (live && pseg < 2 && off < d && (linear || p <= q)) v = row[pseg * d + off] * (!linear && p == q ? 0.5f : 1.f);
+            if (live && pseg < 2 && off < d && (linear || full || p <= q)) v = row[pseg * d + off] * (!linear && !full && p == q ? 0.5f : 1.f);
             x[t][i] = v;
             const unsigned u = __float_as_uint(v) & 0x7FFFFFFFu;
             if (u < 0x7F800000u) m = max(m, u);                     // (an infinity or a NaN is packed as NaN terms: lo = inf - inf)

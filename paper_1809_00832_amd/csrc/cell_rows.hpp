@@ -65,14 +65,43 @@ __device__ inline void pack_rntn_rows(const float *__restrict__ s, _Float16 *__r
     if (linear && (lane & 15) >= n_steps) dst[0] = dst[64] = halfx8{};
 }
 
-// Both packed forms of the RNTN parameters in one launch: the first n_tiles waves those of the tiles, the rest those of the rows.
-__global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, _Float16 *__restrict__ vp, float *__restrict__ scale, int d, int Lp, int n_steps,
-                                                   int n_cg, _Float16 *__restrict__ rows_wp, float *__restrict__ rows_scale, int rows_steps)
+// The matrices of the operand gradient (backward.hpp): [p][k / 16][k-step over q][hi, lo][lane][8], scales and linear terms [p][2 n_steps][16].
+// One wave per p and 16 of the k.
+__device__ inline void pack_rntn_operand(const float *__restrict__ s, _Float16 *__restrict__ wp, float *__restrict__ scale, int d, int Lp, int n_steps,
+                                         int item, int lane)
 {
-    const int lane = threadIdx.x & 63, n_tiles = n_cg * (32 * n_steps + 1);
-    const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (item < n_tiles) pack_rntn_tile(s, vp, scale, d, Lp, n_steps, item, lane);
-    else if (item - n_tiles < d * (2 * rows_steps + 1) && rows_steps > 0) pack_rntn_rows(s, rows_wp, rows_scale, d, Lp, rows_steps, item - n_tiles, lane);
+    const int p = item / n_steps, j = item - p * n_steps, k = 16 * j + (lane & 15);
+    const RntnColumn c = rntn_column(s, d, Lp, 32 * RNTN_MAX_STEPS, (p >= d ? Lp - d : 0) + p, k, lane, true);
+    if (lane < 16) {
+        scale[((size_t)p * 2 * n_steps + j) * HU + lane] = c.scale;
+        scale[((size_t)p * 2 * n_steps + n_steps + j) * HU + lane] = k < d ? s[((size_t)d * 2 * d + k) * 2 * d + p] : 0.f;
+    }
+    halfx8 *dst = reinterpret_cast<halfx8 *>(wp) + (((size_t)p * n_steps + j) * n_steps) * 128 + lane;
+#pragma unroll
+    for (int t = 0; t < RNTN_MAX_STEPS; ++t) {
+        if (t >= n_steps) break;
+        dst[(size_t)t * 128] = c.hi[t];
+        dst[(size_t)t * 128 + 64] = c.lo[t];
+    }
+}
+
+// The packed forms of the RNTN parameters in one launch, a wave per item: those of the tiles, of the rows (rows.steps > 0) and of the operand
+// gradient (operand.steps > 0).
+struct RntnPack {
+    _Float16 *wp;
+    float *scale;
+    int steps;
+};
+__global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, int d, int Lp, int n_cg, RntnPack tile, RntnPack rows, RntnPack operand)
+{
+    const int lane = threadIdx.x & 63;
+    int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    const int n_tiles = n_cg * (32 * tile.steps + 1), n_rows = rows.steps > 0 ? d * (2 * rows.steps + 1) : 0, n_operand = 2 * d * operand.steps;
+    if (item < n_tiles) return pack_rntn_tile(s, tile.wp, tile.scale, d, Lp, tile.steps, item, lane);
+    item -= n_tiles;
+    if (item < n_rows) return pack_rntn_rows(s, rows.wp, rows.scale, d, Lp, rows.steps, item, lane);
+    item -= n_rows;
+    if (item < n_operand) pack_rntn_operand(s, operand.wp, operand.scale, d, Lp, operand.steps, item, lane);
 }
 
 template <int CTRL> __device__ inline float dpp(float x)

@@ -74,6 +74,10 @@ struct tl_ctx {
     // fp32 RNTN under the data-flow scheduler (cell_rows.hpp): k-steps of the K axis (0: not used), groups of eight values per
     // segment, packed matrices and their scales
     int rows_steps = 0, rows_seg = 0;
+    // fp32 RNTN, backward pass in one kernel (d <= 96): workgroups, sets of them, packed matrices and scales
+    int rb_steps = 0, rb_grid = 0, rb_sets = 0;
+    _Float16 *rb_wp = nullptr;
+    float *rb_scale = nullptr;
     _Float16 *rows_wp = nullptr;
     float *rows_scale = nullptr;
     int flow_grid = 0;                // workgroups of the data-flow kernel
@@ -549,9 +553,12 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
     if (rs > 0 && !ctx->rows_wp) TL_HIP(hipMalloc(&ctx->rows_wp, (size_t)H * (rs * (rs + 1) + 1) * 2 * 64 * 16));
     if (rs > 0 && !ctx->rows_scale) TL_HIP(hipMalloc(&ctx->rows_scale, (size_t)H * (2 * rs + 1) * HU * sizeof(float)));
     hipLaunchKernelGGL(k_rntn_build_s, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, ctx->t_scratch, H);
-    const int waves = slices + (rs > 0 ? H * (2 * rs + 1) : 0);
-    hipLaunchKernelGGL(k_pack_rntn, dim3((waves + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, (_Float16 *)ctx->wp_inner, ctx->xs_inner,
-                       H, Lp, n_steps, ctx->n_cg, ctx->rows_wp, ctx->rows_scale, rs);
+    const int bs = ctx->rb_steps, waves = slices + (rs > 0 ? H * (2 * rs + 1) : 0) + D2 * bs;
+    if (bs > 0 && !ctx->rb_wp) TL_HIP(hipMalloc(&ctx->rb_wp, (size_t)D2 * bs * bs * 2 * 64 * 16));
+    if (bs > 0 && !ctx->rb_scale) TL_HIP(hipMalloc(&ctx->rb_scale, (size_t)D2 * 2 * bs * HU * sizeof(float)));
+    hipLaunchKernelGGL(k_pack_rntn, dim3((waves + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, H, Lp, ctx->n_cg,
+                       RntnPack{(_Float16 *)ctx->wp_inner, ctx->xs_inner, n_steps}, RntnPack{ctx->rows_wp, ctx->rows_scale, rs},
+                       RntnPack{ctx->rb_wp, ctx->rb_scale, bs});
     hipLaunchKernelGGL(k_pack_bias, dim3(64), dim3(256), 0, st, (const float *)ctx->m_b, ctx->bp_inner, 1, H, ctx->n_cg);
     TL_HIP(hipGetLastError());
     ctx->g_inner.wp = ctx->wp_inner;
@@ -717,6 +724,8 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->sched);
     (void)hipFree(ctx->sched_head);
     (void)hipFree(ctx->hx_back);
+    (void)hipFree(ctx->rb_wp);
+    (void)hipFree(ctx->rb_scale);
     (void)hipFree(ctx->rows_wp);
     (void)hipFree(ctx->rows_scale);
     (void)hipFree(ctx->xp_inner);
@@ -792,6 +801,25 @@ bwh_ws_kernel backward_ws_kernel(bool lstm, int spw2, bool exact, size_t *lds)
     }
 }
 
+// RNTN: the backward pass over all heights, for d <= 96
+typedef void (*bwh_rntn_kernel)(Fwd, int);
+template <int NS> bwh_rntn_kernel backward_rntn_kernel_of(size_t *lds)
+{
+    *lds = sizeof(RntnBwdSmem<NS>);
+    return k_backward_rntn<NS>;
+}
+bwh_rntn_kernel backward_rntn_kernel(int steps, size_t *lds)
+{
+    switch (steps) {
+    case 1: return backward_rntn_kernel_of<1>(lds);
+    case 2: return backward_rntn_kernel_of<2>(lds);
+    case 3: return backward_rntn_kernel_of<3>(lds);
+    case 4: return backward_rntn_kernel_of<4>(lds);
+    case 5: return backward_rntn_kernel_of<5>(lds);
+    default: return backward_rntn_kernel_of<6>(lds);
+    }
+}
+
 int create_impl(const tl_config *cfg, tl_ctx *ctx)
 {
     ctx->cfg = *cfg;
@@ -831,6 +859,19 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     if (cfg->cell == TL_RNTN && cfg->scheduler == TL_SCHED_DATAFLOW && 2 * round_up(H, 8) <= 32 * ROWS_MAX_STEPS) {
         ctx->rows_steps = (2 * round_up(H, 8) + 31) / 32;
         ctx->rows_seg = round_up(H, 8) / 8;
+    }
+    if (cfg->cell == TL_RNTN && 2 * round_up(H, 8) <= 32 * ROWS_MAX_STEPS) {
+        ctx->rb_steps = (2 * round_up(H, 8) + 31) / 32;
+        ctx->rows_seg = round_up(H, 8) / 8;
+        size_t lds = 0;
+        const bwh_rntn_kernel k = backward_rntn_kernel(ctx->rb_steps, &lds);
+        int o = 0;
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(k), WG_THREADS, lds));
+        if (o > rntn_bwd_sets_per_cu(ctx->rb_steps)) o = rntn_bwd_sets_per_cu(ctx->rb_steps);
+        const int set = (2 * H + ROWS_UNITS - 1) / ROWS_UNITS;
+        ctx->rb_sets = o * ctx->n_cu / set;
+        ctx->rb_grid = ctx->rb_sets * set;
+        if (ctx->rb_sets < 1) ctx->rb_steps = 0;
     }
     ctx->flow_set = ctx->rows_steps > 0 ? (H + ROWS_UNITS - 1) / ROWS_UNITS : ctx->n_cg;
     // Backward pass: k-steps of 16 in half a wave's quarter of a row of gate gradients
@@ -1496,13 +1537,16 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // workspace of the backward pass: dh, dc [N x H], gate gradients [n_int x 5H] and [n_leaf x 3H]
     // (RNTN: rows of d * 2d + d values per internal node, see backward.hpp)
     const size_t rntn_row = (size_t)H * 2 * H + H;
+    // RNTN: rows of d * 2d + d values per node, or of d where the one kernel takes them (24-bit row numbers, 32-bit byte offsets)
+    auto rntn_wide = [&](size_t nodes) { return rntn && (ctx->rb_steps == 0 || nodes >= ((size_t)1 << 24) || nodes * H * 4 >= ((size_t)1 << 32)); };
+    const bool rntn_rows = rntn_wide((size_t)n_nodes);
     if (n_nodes > ctx->bw_nodes) {
         TL_HIP(hipDeviceSynchronize());
         if (ctx->bw) { TL_HIP(hipFree(ctx->bw)); ctx->bw = nullptr; }
         ctx->bw_nodes = 0;
         const size_t cap = (size_t)ctx->cap_nodes;
         size_t floats = 2 * cap * H + cap * 5 * H;                                   // n_int*5H + n_leaf*3H <= N*5H
-        if (rntn) floats = 2 * cap * H + (cap / 2 + 1) * rntn_row;
+        if (rntn) floats = 2 * cap * H + (cap / 2 + 1) * (rntn_wide(cap) ? rntn_row : (size_t)H);
         if (floats * sizeof(float) > ((size_t)64 << 30)) return TL_ENOMEM;
         TL_HIP(hipMalloc(&ctx->bw, floats * sizeof(float)));
         ctx->bw_nodes = ctx->cap_nodes;
@@ -1569,8 +1613,21 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const bool many = !exact_rows && ((ctx->bw_spw2 > 18 && n_int > 2000) || (100 * ctx->bw_ws_grid < 86 * ctx->n_cu && n_int > 4000));
     const bool ws = persistent_ok && ctx->bw_ws_grid > 0 && !many &&
                     (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
-    const bool heights_on_device = ctx->async_backward > 0 && persistent_ok;
+    // RNTN: in one kernel wherever its matrices fit into registers and the rows' addresses into 32 bits (nothing else is left for those sizes)
+    const bool rntn_one = rntn && !rntn_rows && n_int > 0;
+    const bool heights_on_device = ctx->async_backward > 0 && (persistent_ok || rntn_one);
     auto launch_all_heights = [&]() {
+        if (rntn_one) {
+            Fwd g = f;
+            g.dg = dg_int;
+            g.seg_chunks = ctx->rows_seg;
+            g.xi.wp = ctx->rb_wp; g.xi.scale = ctx->rb_scale; g.xi.w = ctx->m_u;
+            g.rntn_v = ctx->m_v;
+            size_t lds = 0;
+            const bwh_rntn_kernel k = backward_rntn_kernel(ctx->rb_steps, &lds);
+            hipLaunchKernelGGL(k, dim3(ctx->rb_grid), dim3(WG_THREADS), lds, st, g, ctx->rb_sets);
+            return;
+        }
         BwdHeights b{};
         b.bwd4 = ctx->g_bwd_inner; b.bwd1 = ctx->ng_bwd_inner == 4 ? ctx->g_bwd_inner1 : ctx->g_bwd_inner; b.ng_inner = ctx->ng_bwd_inner;
         b.dg_int = dg_int;
@@ -1592,7 +1649,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     bool status_pending = false;
     if (heights_on_device) {
         launch_all_heights();
-    } else if (ws && ctx->async_backward == 0) {
+    } else if ((ws && ctx->async_backward == 0) || rntn_one) {
         // The weight-stationary form is the faster one whatever the number of heights, and needs nothing from the host: the
         // structure pass's status is copied out in front of it, everything is enqueued, and the call then waits for that copy
         // alone (the device works on meanwhile) to return that status as it always has.
@@ -1692,8 +1749,12 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     if (n_int > 0) {
         const bool v4 = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0);
         float *acc = rntn ? ctx->rntn_acc : d_u, *colsum = rntn ? ctx->rntn_acc + (size_t)2 * H * rntn_row : d_b;
-        weight_grad(k_weight_grad_wide<2>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
-                    f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
+        if (rntn_one)
+            weight_grad(k_weight_grad_wide<2, true>, v4 ? wgrad_kernel(k_weight_grad<2, true, true>) : wgrad_kernel(k_weight_grad<2, false, true>), 2 * H,
+                        f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
+        else
+            weight_grad(k_weight_grad_wide<2>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
+                        f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,

@@ -139,3 +139,66 @@ def test_treernn_infinities_are_summed_in_fp32(where):
     got = run(p, trees, "dataflow")
     assert not np.isnan(ref["h"]).any() and (ref["h"][trees.left >= 0][:, 5] == 1).any()
     np.testing.assert_allclose(got["h"], ref["h"], rtol=RTOL, atol=4e-6)
+
+
+# ---- RNTN: the backward pass in one kernel (d <= 96) -------------------------------------------------------------------
+def rntn_gradients(params, trees, g_h, modes=(0, 1)):
+    import torch
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        net.forward()
+        out = {}
+        for mode in modes:
+            binding.tl_set_async_backward(net.ctx, mode)
+            got = binding.tl_backward(net.ctx, b, torch.from_numpy(g_h).cuda(), params.embed_dim, rntn=True)
+            torch.cuda.synchronize()
+            assert binding.tl_status(net.ctx) == 0
+            out[mode] = {k: v.cpu().numpy() for k, v in got.items()}
+        h = b["h"].cpu().numpy()
+    finally:
+        net.close()
+    with np.errstate(all="ignore"):
+        ref = oracle.backward(params, trees, h, None, g_h)
+    ref["d_w_leaf"] = ref.pop("d_v")
+    return out, ref
+
+
+@pytest.mark.parametrize("d,n_trees", [(d, 9) for d in (1, 7, 8, 16, 17, 31, 32, 33, 48, 49, 64, 65, 80, 95, 96, 97)] + [(16, 150), (33, 150), (64, 40)])
+def test_rntn_gradients_at_the_edges_of_the_blocks(d, n_trees):
+    """Against the checker: products to 2^-21, sums of at most 2d d of them of order one, carried down up to 33 heights (1e-4 of the
+    largest, the figure that the other gradients are tested with)."""
+    print("case rntn backward sizes", d, n_trees, flush=True)
+    params = synth.make_rnn_params(770 + d, synth.CELL_RNTN, 60, d, scale=0.3 / d ** 0.5)
+    trees = synth.make_trees(771, ([1, 2, 3, 1, 18, 30, 9, 33, 16] * 17)[:n_trees], (["random", "chain", "balanced"] * 51)[:n_trees], 60)
+    g_h = np.random.default_rng(d).standard_normal((trees.n_nodes, d)).astype(np.float32)
+    out, ref = rntn_gradients(params, trees, g_h)
+    assert np.array_equal(out[0]["d_x"], out[1]["d_x"])
+    for k in ref:
+        np.testing.assert_allclose(out[0][k], ref[k].reshape(out[0][k].shape), rtol=1e-4, atol=1e-4 * max(1e-3, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+@pytest.mark.parametrize("what", ["scales", "infinite weight", "nan gradient"])
+def test_rntn_gradients_outside_the_ordinary_range(what):
+    """Gradients are factors as they are, of any magnitude; an infinite operand is met in fp32; a NaN stays where it belongs."""
+    print("case rntn backward range", what, flush=True)
+    d = 24
+    params = synth.make_rnn_params(780, synth.CELL_RNTN, 40, d, scale=0.05)
+    params.emb[:] = np.abs(params.emb) + 0.1
+    trees = synth.make_trees(781, [12, 5, 1, 20], ["random", "chain", "random", "balanced"], 40)
+    rng = np.random.default_rng(3)
+    g_h = rng.standard_normal((trees.n_nodes, d)).astype(np.float32)
+    tree = np.searchsorted(trees.tree_off, np.arange(trees.n_nodes), side="right") - 1
+    if what == "scales":
+        g_h *= np.array([1e-25, 1e12, 1.0, 1e-8], dtype=np.float32)[tree][:, None]       # (a tree's gradients do not meet another's in d_x)
+    elif what == "infinite weight":
+        params.v[5, 3, 30] = np.inf
+    else:
+        g_h[trees.tree_off[1], 7] = np.nan
+    out, ref = rntn_gradients(params, trees, g_h)
+    got, want = out[0]["d_x"], ref["d_x"]
+    assert np.array_equal(np.isnan(got), np.isnan(want))
+    for t in range(4):
+        m = (tree == t)[:, None] & np.isfinite(want)
+        if m.any():
+            np.testing.assert_allclose(got[m], want[m], rtol=1e-4, atol=1e-4 * float(np.abs(want[m]).max()), err_msg="tree %d" % t)
