@@ -271,7 +271,8 @@ __global__ void k_rntn_unpack(const float *__restrict__ acc, const float *__rest
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
         if (e < n_v) {
             const int q = (int)(e % D2), p = (int)((e / D2) % D2), k = (int)(e / ((size_t)D2 * D2));
-            d_v[e] = acc[(size_t)p * L + (size_t)k * D2 + q];
+            // (symmetric: the weight gradient may have computed p <= q alone)
+            d_v[e] = acc[(size_t)min(p, q) * L + (size_t)k * D2 + max(p, q)];
         } else if (e < n_v + (size_t)D2 * d) {
             const size_t r = e - n_v;
             const int k = (int)(r % d), p = (int)(r / d);
@@ -548,7 +549,7 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
         float a[4], b[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            const int k = min(k0 + t * 16 + (lane & 15), K_out - 1), j = min(j0 + t * 16 + (lane & 15), n_cols - 1);
+            const int k = min(k0 + t * (RNTN ? 32 : 16) + (lane & 15), K_out - 1), j = min(j0 + t * (RNTN ? 32 : 16) + (lane & 15), n_cols - 1);
             const bool second = SEG == 2 && k >= L;
             a[t] = live ? table[(size_t)(second ? s1 : s0) * L + (second ? k - L : k)] : 0.f;
             if constexpr (RNTN) {
@@ -576,7 +577,20 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int k0 = blockIdx.x * WG_TILE, j0 = blockIdx.y * WG_TILE;
     const int K_out = SEG * L;
-    const int wr = (wave >> 1) * 64, wc = (wave & 1) * 64;
+    // RNTN: dV is symmetric, so only tiles of 16 x 16 that hold a p <= q are computed; the tiles of the four waves are interleaved, so that
+    // each has at most ten of its sixteen (36 of 64 in all).
+    constexpr int TS = RNTN ? 32 : 16;                        // distance of a wave's tiles
+    const int wr = (wave >> 1) * (RNTN ? 16 : 64), wc = (wave & 1) * (RNTN ? 16 : 64);
+    bool live_tile[4][4];
+    if constexpr (RNTN) {
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb) {
+            const int c = j0 + wc + tb * TS, q0 = c % (2 * L);
+            const int top = c + 15 >= 2 * L * L || q0 + 15 >= 2 * L ? K_out : q0 + 15;      // largest q among the columns (the linear ones: all rows)
+#pragma unroll
+            for (int ta = 0; ta < 4; ++ta) live_tile[ta][tb] = k0 + wr + ta * TS <= top;
+        }
+    }
     const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WG_Q - 1) / WG_Q * WG_Q;
     const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
     if (q_lo >= q_hi) return;
@@ -639,18 +653,28 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
 #pragma unroll
             for (int t = 0; t < 4; ++t)
 #pragma unroll
-                for (int m = 0; m < 3; ++m) vb[t][m] = *reinterpret_cast<const bf16x8 *>(&sm.b[m][wc + t * 16 + (lane & 15)][8 * (lane >> 4)]);
+                for (int m = 0; m < 3; ++m) vb[t][m] = *reinterpret_cast<const bf16x8 *>(&sm.b[m][wc + t * TS + (lane & 15)][8 * (lane >> 4)]);
 #pragma unroll
             for (int ta = 0; ta < 4; ++ta) {
                 bf16x8 va[3];
 #pragma unroll
-                for (int m = 0; m < 3; ++m) va[m] = *reinterpret_cast<const bf16x8 *>(&sm.a[m][wr + ta * 16 + (lane & 15)][8 * (lane >> 4)]);
+                for (int m = 0; m < 3; ++m) va[m] = *reinterpret_cast<const bf16x8 *>(&sm.a[m][wr + ta * TS + (lane & 15)][8 * (lane >> 4)]);
                 constexpr int TERM[6][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};       // smallest first
-#pragma unroll
-                for (int p = 0; p < 6; ++p)
+                if constexpr (RNTN) {
 #pragma unroll
                     for (int tb = 0; tb < 4; ++tb)
-                        acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+                        if (live_tile[ta][tb]) {
+#pragma unroll
+                            for (int p = 0; p < 6; ++p)
+                                acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+                        }
+                } else {
+#pragma unroll
+                    for (int p = 0; p < 6; ++p)
+#pragma unroll
+                        for (int tb = 0; tb < 4; ++tb)
+                            acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+                }
             }
             __syncthreads();
         }
@@ -672,8 +696,8 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
         for (int tb = 0; tb < 4; ++tb)
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int ko = k0 + wr + ta * 16 + (lane >> 4) * 4 + v, jo = j0 + wc + tb * 16 + (lane & 15);
-                if (ko < K_out && jo < n_cols) atomicAdd(&out[(size_t)ko * n_cols + jo], acc[ta][tb][v]);
+                const int ko = k0 + wr + ta * TS + (lane >> 4) * 4 + v, jo = j0 + wc + tb * TS + (lane & 15);
+                if (ko < K_out && jo < n_cols && (!RNTN || live_tile[ta][tb])) atomicAdd(&out[(size_t)ko * n_cols + jo], acc[ta][tb][v]);
             }
     if (with_bias) {                                          // uniform per workgroup; the loop ended with a barrier
         float *part = reinterpret_cast<float *>(sm.src[0]);

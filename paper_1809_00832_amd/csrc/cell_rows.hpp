@@ -85,17 +85,19 @@ __device__ inline void pack_rntn_operand(const float *__restrict__ s, _Float16 *
     }
 }
 
-// The packed forms of the RNTN parameters in one launch, a wave per item: those of the tiles, of the rows (rows.steps > 0) and of the operand
+// The packed forms of the RNTN parameters (and the bias) in one launch, a wave per item: those of the tiles, of the rows (rows.steps > 0) and of the operand
 // gradient (operand.steps > 0).
 struct RntnPack {
     _Float16 *wp;
     float *scale;
     int steps;
 };
-__global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, int d, int Lp, int n_cg, RntnPack tile, RntnPack rows, RntnPack operand)
+__global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, int d, int Lp, int n_cg, RntnPack tile, RntnPack rows, RntnPack operand,
+                                                   const float *__restrict__ b, float *__restrict__ bp)
 {
     const int lane = threadIdx.x & 63;
     int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+    for (int u = blockIdx.x * blockDim.x + threadIdx.x; u < n_cg * HU; u += gridDim.x * blockDim.x) bp[u] = u < d ? b[u] : 0.f;
     const int n_tiles = n_cg * (32 * tile.steps + 1), n_rows = rows.steps > 0 ? d * (2 * rows.steps + 1) : 0, n_operand = 2 * d * operand.steps;
     if (item < n_tiles) return pack_rntn_tile(s, tile.wp, tile.scale, d, Lp, tile.steps, item, lane);
     item -= n_tiles;

@@ -538,11 +538,28 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
     return TL_OK;
 }
 
-// The same for an fp32 RNTN context: the forward's packed tensor slices, and the matrix S of the operand gradient
-// (see backward.hpp) packed like transposed weights.
-int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
+// RNTN: the matrix S of the operand gradient (backward.hpp, in t_scratch since pack_rntn_f32) packed like transposed weights, for the sizes
+// and batches that the one kernel does not take.
+int pack_rntn_wide(tl_ctx *ctx, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, D2 = 2 * H, L = H * D2 + H;
+    int rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, ctx->ng_bwd_inner, D2 / ctx->ng_bwd_inner, 1, L,
+                       (D2 / ctx->ng_bwd_inner + HU - 1) / HU, 0, false, &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
+    if (rc != TL_OK) return rc;
+    if (ctx->ng_bwd_inner == 4) {
+        rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, 1, D2, 1, L, (D2 + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
+                       &ctx->bp_bwd_inner1, st);
+        if (rc != TL_OK) return rc;
+    }
+    TL_HIP(hipGetLastError());
+    return TL_OK;
+}
+
+// The same for an fp32 RNTN context: the packed forms of the forward and of the one backward kernel, all from the matrix S
+// of the operand gradient (backward.hpp).
+int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
+{
+    const int H = ctx->cfg.hidden, D2 = 2 * H;
     const int Lp = round_up(H, 8);         // (the cells that gather rows take them eight values at a time)
     int Kp = round_up(2 * Lp, KC);
     if (Kp > 128) Kp = 256;
@@ -558,24 +575,14 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
     if (bs > 0 && !ctx->rb_scale) TL_HIP(hipMalloc(&ctx->rb_scale, (size_t)D2 * 2 * bs * HU * sizeof(float)));
     hipLaunchKernelGGL(k_pack_rntn, dim3((waves + 3) / 4), dim3(256), 0, st, (const float *)ctx->t_scratch, H, Lp, ctx->n_cg,
                        RntnPack{(_Float16 *)ctx->wp_inner, ctx->xs_inner, n_steps}, RntnPack{ctx->rows_wp, ctx->rows_scale, rs},
-                       RntnPack{ctx->rb_wp, ctx->rb_scale, bs});
-    hipLaunchKernelGGL(k_pack_bias, dim3(64), dim3(256), 0, st, (const float *)ctx->m_b, ctx->bp_inner, 1, H, ctx->n_cg);
+                       RntnPack{ctx->rb_wp, ctx->rb_scale, bs}, (const float *)ctx->m_b, ctx->bp_inner);
     TL_HIP(hipGetLastError());
     ctx->g_inner.wp = ctx->wp_inner;
     ctx->g_inner.bp = ctx->bp_inner;
     ctx->g_inner.L = H;
     ctx->g_inner.Lp = Lp;
     ctx->g_inner.n_chunks = Kp / KC;
-    int rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, ctx->ng_bwd_inner, D2 / ctx->ng_bwd_inner, 1, L,
-                       (D2 / ctx->ng_bwd_inner + HU - 1) / HU, 0, false, &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
-    if (rc != TL_OK) return rc;
-    if (ctx->ng_bwd_inner == 4) {
-        rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, 1, D2, 1, L, (D2 + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
-                       &ctx->bp_bwd_inner1, st);
-        if (rc != TL_OK) return rc;
-    }
-    TL_HIP(hipGetLastError());
-    return TL_OK;
+    return bs > 0 ? TL_OK : pack_rntn_wide(ctx, st);
 }
 
 // Workgroups of `kernel` (with `lds` bytes of dynamic LDS) that one compute unit holds at a time; asked of the runtime
@@ -1540,6 +1547,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // RNTN: rows of d * 2d + d values per node, or of d where the one kernel takes them (24-bit row numbers, 32-bit byte offsets)
     auto rntn_wide = [&](size_t nodes) { return rntn && (ctx->rb_steps == 0 || nodes >= ((size_t)1 << 24) || nodes * H * 4 >= ((size_t)1 << 32)); };
     const bool rntn_rows = rntn_wide((size_t)n_nodes);
+    if (rntn_rows && ctx->rb_steps > 0 && (rc = pack_rntn_wide(ctx, st)) != TL_OK) return rc;
     if (n_nodes > ctx->bw_nodes) {
         TL_HIP(hipDeviceSynchronize());
         if (ctx->bw) { TL_HIP(hipFree(ctx->bw)); ctx->bw = nullptr; }
