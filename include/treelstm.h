@@ -62,8 +62,8 @@ typedef struct tl_ctx tl_ctx;
 
 enum tl_cell { TL_TREELSTM = 0, TL_TREERNN = 1, TL_RNTN = 2 };
 
-/* TL_F32: fp32 operands, fp32 accumulation.  (The leaves of TL_TREELSTM up to embed_dim 1024, and its internal nodes under
- * TL_SCHED_DATAFLOW, form their products on the 16-bit matrix unit with every operand as two fp16 terms and fp32
+/* TL_F32: fp32 operands, fp32 accumulation.  (The leaves of TL_TREELSTM up to embed_dim 1024, its internal nodes and those of
+ * TL_TREERNN under TL_SCHED_DATAFLOW, and all sums of TL_RNTN form their products on the 16-bit matrix unit with every operand as two fp16 terms and fp32
  * accumulation: an operand is met to 2^-23 of itself, or to 2^-38 of the largest of its weight column or embedding row where
  * it is far below that one; a product to 2^-21.  The gate functions, good to about 1e-7 absolute in every path, hide the
  * difference: against 64 bits the states' errors are the same.)  TL_BF16_IN: weights, embeddings and the
@@ -111,10 +111,10 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  *                        this is the fastest choice for deep or narrow batches and as fast as
  *                        TL_SCHED_LEVEL_DEVICE on wide ones.  Consequence: if the parameters or
  *                        embeddings hold NaNs whose bits are all ones, a forward ends with
- *                        TL_ESTALL instead of NaN results.  (TL_TREELSTM in TL_F32: one workgroup per
+ *                        TL_ESTALL instead of NaN results.  (In TL_F32 one workgroup per
  *                        set works out the order of the nodes for all of them, beside the leaves' cells.)
- *                        Where its cells are not used (TL_RNTN, hidden > 512, odd hidden of TL_TREERNN in
- *                        TL_F32, tl_forward_noalloc, batches of 2^24 nodes or 4 GiB of h and more)
+ *                        Where its cells are not used (hidden > 512, TL_RNTN with hidden > 96,
+ *                        tl_forward_noalloc, batches of 2^24 nodes or 4 GiB of h and more)
  *                        TL_SCHED_LEVEL_DEVICE stands in.  Whole trees are dealt to the sets, so a
  *                        batch of fewer trees than the device has sets leaves sets idle; if its trees
  *                        have 256 nodes or more on average, both this kernel and that of
@@ -126,11 +126,9 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  * All paths repeat their bits from run to run, and TL_SCHED_READY, _READY_PRIORITY, _LEVEL_DEVICE and
  * _LEVEL_HOST of one precision agree bit for bit: they sum a node's contraction in the same
  * order.  So does TL_SCHED_DATAFLOW in TL_BF16_IN.  In TL_F32 it agrees with them to rounding (relative
- * 2e-5 in the tests): a TL_TREELSTM's internal nodes are summed from split operands (above), and a
- * TL_TREERNN's dependent steps of few rows (the last block of up to 8 rows of each piece of its
- * lists) with a narrower matrix instruction that rounds the same sum in another order; which nodes
- * those are is fixed by the batch.  A node's bits do not depend on the rest of the batch, with two
- * exceptions: those narrow blocks, and a TL_F32 TL_TREELSTM batch of 2^24 nodes or 4 GiB of h and more, whose
+ * 2e-5 in the tests) for TL_TREELSTM and TL_TREERNN, whose internal nodes are summed from split operands (above); for
+ * TL_RNTN, split under every scheduler, bit for bit where hidden is a multiple of 16.  A node's bits do not depend on the rest of the
+ * batch, with one exception: a TL_F32 TL_TREELSTM batch of 2^24 nodes or 4 GiB of h and more, whose
  * leaves are summed by fp32 instructions (as all leaves are with embed_dim > 1024 or a table of 2^24 words or 4 GiB and
  * more). */
 enum tl_scheduler { TL_SCHED_READY = 0, TL_SCHED_LEVEL_DEVICE = 1, TL_SCHED_LEVEL_HOST = 2, TL_SCHED_READY_PRIORITY = 3,
@@ -339,7 +337,7 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
  * For callers that must not be held up by tl_backward (the recursion of Section 4.2.2 walked without the host):
  * with on > 0, a tl_backward that needs no contraction for its gate gradients - TreeLSTM from kept gate
  * activations (tl_set_keep_gates), TreeRNN - walks all heights in one persistent kernel that finds the
- * per-height lists on the device (TreeLSTM and TreeRNN with H = 128, 256, 384 or 512: the operand gradient on weight-stationary
+ * per-height lists on the device (TreeLSTM and TreeRNN with H <= 512: the operand gradient on weight-stationary
  * workgroups).  Nothing is read back and the call returns without waiting; a malformed batch is then reported
  * by tl_status (TL_ESTRUCT, gradients undefined), not by tl_backward.  Same results as the per-height launches
  * (same contractions in the same order).

@@ -1849,7 +1849,9 @@ int tl_classify(tl_ctx *ctx, int n_rows, const float *h, const float *w_s, const
     const size_t lds = (size_t)n_classes * Hp * sizeof(float);
     if (lds > 96 * 1024) return TL_EINVAL;
     typedef void (*cls_kernel)(const float *, const float *, const float *, float *, int, int, int);
-    const cls_kernel k = n_classes <= 2 ? k_classify<2> : n_classes <= 8 ? k_classify<8> : n_classes <= 16 ? k_classify<16> : k_classify<32>;
+    // (up to eight classes: a kernel of exactly that many, without tests between its multiply-adds)
+    constexpr cls_kernel exact[8] = {k_classify<1>, k_classify<2>, k_classify<3>, k_classify<4>, k_classify<5>, k_classify<6>, k_classify<7>, k_classify<8>};
+    const cls_kernel k = n_classes <= 8 ? exact[n_classes - 1] : n_classes <= 16 ? k_classify<16> : k_classify<32>;
     TL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(k), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     long long blocks = ((long long)n_rows + 15) / 16;
     const long long cap = (long long)ctx->n_cu * 8;
@@ -1874,8 +1876,9 @@ int tl_classify_backward(tl_ctx *ctx, int n_rows, const float *h, const float *w
     if (n_rows == 0) return TL_OK;
     typedef void (*bwd_kernel)(const float *, const float *, const float *, const int32_t *, float *, float *, float *, int, int, int);
     typedef void (*wg_kernel)(const float *, const float *, float *, float *, int, int, int);
-    const bwd_kernel kb = C <= 2 ? k_classify_backward<2> : C <= 8 ? k_classify_backward<8> : C <= 16 ? k_classify_backward<16>
-                                                                                                     : k_classify_backward<32>;
+    constexpr bwd_kernel exact[8] = {k_classify_backward<1>, k_classify_backward<2>, k_classify_backward<3>, k_classify_backward<4>,
+                                     k_classify_backward<5>, k_classify_backward<6>, k_classify_backward<7>, k_classify_backward<8>};
+    const bwd_kernel kb = C <= 8 ? exact[C - 1] : C <= 16 ? k_classify_backward<16> : k_classify_backward<32>;
     const wg_kernel kw = C <= 2 ? k_head_weight_grad<2> : C <= 8 ? k_head_weight_grad<8> : C <= 16 ? k_head_weight_grad<16>
                                                                                                   : k_head_weight_grad<32>;
     TL_HIP(hipFuncSetAttribute(reinterpret_cast<const void *>(kb), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
