@@ -1216,8 +1216,9 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool ws_range = n_nodes < (1 << 24) && (unsigned long long)n_nodes * cfg.hidden * 4ull < (1ull << 32);
     const int spw = ws_range ? ctx->spw : 0;     // weight-stationary cell in the persistent kernels
     const bool persistent = cfg.scheduler != TL_SCHED_LEVEL_HOST;
-    // the data-flow scheduler needs the weight-stationary cell and its private lists; without them (RNTN, sizes the
-    // cell does not take, the fixed workspace) the level scheduler on the device stands in.
+    // The data-flow scheduler works on prepared blocks (fp32: split cells of TreeLSTM and TreeRNN, RNTN up to d = 96) or on lists of its own
+    // (bf16); without them (larger sizes, the fixed workspace, batches beyond the cells' address range) the level scheduler on
+    // the device stands in.
     const bool sched_range = in_split_range(ctx, n_nodes);
     const int split = sched_range ? ctx->split : 0;
     const bool rows = ctx->rows_steps > 0 && sched_range;      // the cells that gather rows (cell_rows.hpp)
