@@ -280,14 +280,16 @@ int tl_last_stats(tl_ctx *ctx, int *n_levels, int *n_tiles, int *n_workgroups);
  *   d_x       [n_nodes x E] fp32 out: row n = dL/d(embedding row used by leaf n);
  *             rows of internal nodes are zero (the caller scatter-adds by word)    DEVICE
  * fp32 arithmetic; the TreeLSTM gate activations are recomputed from h / c unless the forward
- * kept them (tl_set_keep_gates); TreeRNN and RNTN need nothing but h.  The RNTN path is a first
- * version: it materialises a row of d * 2d + d values per internal node (workspace of that size).
+ * kept them (tl_set_keep_gates); TreeRNN and RNTN need nothing but h.  RNTN with d <= 96 walks all heights in one
+ * persistent kernel; with d > 96, in batches of 2^24 nodes or 4 GiB of h and more, and under
+ * tl_set_async_backward(ctx, -1) it takes launches per height and a row of d * 2d + d values per internal node
+ * (workspace of that size).
  * Work is enqueued on hip_stream, but the call waits for the structure pass and returns the deferred
  * structure status: TL_OK, TL_ESTRUCT, ... (where the heights are walked by launches, one pair per height,
  * it needs their number and sizes first; where one persistent kernel walks them, it has enqueued all its
- * work by then and the device is not held up).  With tl_set_async_backward(ctx, 1) it does not wait.
- * The first call for a larger batch than any before allocates workspace (TL_ENOMEM if the RNTN
- * rows would take more than 64 GiB).  TL_BF16_IN: TL_EINVAL.
+ * work by then and the device is not held up).  With tl_set_async_backward(ctx, 1) it does not wait (RNTN: it does).
+ * The first call for a larger batch than any before (RNTN: or the first that needs those rows) allocates workspace
+ * (TL_ENOMEM if the RNTN rows would take more than 64 GiB).  TL_BF16_IN: TL_EINVAL.
  */
 int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, const int32_t *left,
                 const int32_t *right, const int32_t *word, const float *h, const float *c, const float *g_h,
@@ -348,8 +350,10 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
  * kernel.  Otherwise (other hidden sizes: the persistent kernel with the streaming cell is 5 % slower
  * than the launches on shallow batches and faster on deep ones) the call waits for the number of heights and
  * takes the persistent kernel for more than 64 of them, launches per height up to there.
- * on < 0: always launches per height.  Like the persistent schedulers of tl_forward, the kernel needs all its
- * workgroups resident.  Recomputed gates and TL_RNTN always take the launches per height and wait.
+ * on < 0: always launches per height.  Like the persistent schedulers of tl_forward, the persistent kernels need all their
+ * workgroups resident: a caller that cannot keep the device to itself takes on < 0 (a wait that gives up is
+ * reported by tl_status, TL_ESTALL).  Recomputed gates always take the launches per height and wait.  TL_RNTN returns the
+ * structure pass's status in every mode; d <= 96 takes its persistent kernel with on >= 0, larger d always the launches.
  */
 int tl_set_async_backward(tl_ctx *ctx, int on);
 

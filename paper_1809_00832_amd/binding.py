@@ -218,7 +218,8 @@ def tl_set_keep_gates(ctx, on: bool) -> None:
 
 
 def tl_set_async_backward(ctx, on) -> None:
-    """True / 1: never waits; False / 0: the default (picks by the number of heights); -1: always launches per height."""
+    """True / 1: TreeLSTM and TreeRNN do not wait (RNTN returns the structure pass's status all the same); False / 0: the default;
+    -1: always launches per height, which need no workgroups resident together."""
     _check(lib().tl_set_async_backward(ctx, int(on)), "tl_set_async_backward")
 
 

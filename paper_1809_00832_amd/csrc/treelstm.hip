@@ -99,6 +99,8 @@ struct tl_ctx {
     int ng_bwd_inner = 1, ng_bwd_leaf = 1;    // blocks of output columns per column group of the operand-gradient contractions
     float *bw = nullptr;              // dh | dc | gate gradients of internal nodes | of leaves
     int bw_nodes = 0;
+    bool bw_rows = false;             // RNTN: bw has room for rows of d * 2d + d values
+    bool rntn_wide_packed = false;    // RNTN: the matrix of the launches per height belongs to the current parameters
     float *m_u = nullptr, *m_b = nullptr, *m_w_leaf = nullptr, *m_b_leaf = nullptr;   // fp32 TreeLSTM: the parameters themselves
     float *t_scratch = nullptr, *zero_bias = nullptr;
     float *m_v = nullptr;             // fp32 RNTN: the tensor V as given
@@ -108,7 +110,7 @@ struct tl_ctx {
     float *rntn_acc = nullptr;        // RNTN backward: [2d x (d * 2d + d)] weight-gradient contraction and its column sums
     int ws_steps16 = 0;
     bool keep_gates = false;          // tl_set_keep_gates
-    int async_backward = 0;           // tl_set_async_backward: 1 never waits, -1 always launches per height, 0 picks by the number of heights
+    int async_backward = 0;           // tl_set_async_backward: 1 does not wait, -1 always launches per height, 0 picks
     float *gates = nullptr;           // [gates_cap x 5H] gate activations of the last forward that kept them
     int gates_cap = 0;
     int gates_nodes = 0;              // nodes of that forward, 0: nothing kept
@@ -539,9 +541,10 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
 }
 
 // RNTN: the matrix S of the operand gradient (backward.hpp, in t_scratch since pack_rntn_f32) packed like transposed weights, for the sizes
-// and batches that the one kernel does not take.
+// and batches that the one kernel does not take and for callers that ask for launches per height.
 int pack_rntn_wide(tl_ctx *ctx, hipStream_t st)
 {
+    if (ctx->rntn_wide_packed) return TL_OK;
     const int H = ctx->cfg.hidden, D2 = 2 * H, L = H * D2 + H;
     int rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, ctx->ng_bwd_inner, D2 / ctx->ng_bwd_inner, 1, L,
                        (D2 / ctx->ng_bwd_inner + HU - 1) / HU, 0, false, &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
@@ -552,6 +555,7 @@ int pack_rntn_wide(tl_ctx *ctx, hipStream_t st)
         if (rc != TL_OK) return rc;
     }
     TL_HIP(hipGetLastError());
+    ctx->rntn_wide_packed = true;
     return TL_OK;
 }
 
@@ -569,6 +573,7 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
     if (!ctx->bp_inner) TL_HIP(hipMalloc(&ctx->bp_inner, (size_t)ctx->n_cg * HU * sizeof(float)));
     if (rs > 0 && !ctx->rows_wp) TL_HIP(hipMalloc(&ctx->rows_wp, (size_t)H * (rs * (rs + 1) + 1) * 2 * 64 * 16));
     if (rs > 0 && !ctx->rows_scale) TL_HIP(hipMalloc(&ctx->rows_scale, (size_t)H * (2 * rs + 1) * HU * sizeof(float)));
+    ctx->rntn_wide_packed = false;
     hipLaunchKernelGGL(k_rntn_build_s, dim3(2048), dim3(256), 0, st, (const float *)ctx->m_v, (const float *)ctx->m_u, ctx->t_scratch, H);
     const int bs = ctx->rb_steps, waves = slices + (rs > 0 ? H * (2 * rs + 1) : 0) + D2 * bs;
     if (bs > 0 && !ctx->rb_wp) TL_HIP(hipMalloc(&ctx->rb_wp, (size_t)D2 * bs * bs * 2 * 64 * 16));
@@ -1545,20 +1550,21 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // workspace of the backward pass: dh, dc [N x H], gate gradients [n_int x 5H] and [n_leaf x 3H]
     // (RNTN: rows of d * 2d + d values per internal node, see backward.hpp)
     const size_t rntn_row = (size_t)H * 2 * H + H;
-    // RNTN: rows of d * 2d + d values per node, or of d where the one kernel takes them (24-bit row numbers, 32-bit byte offsets)
-    auto rntn_wide = [&](size_t nodes) { return rntn && (ctx->rb_steps == 0 || nodes >= ((size_t)1 << 24) || nodes * H * 4 >= ((size_t)1 << 32)); };
-    const bool rntn_rows = rntn_wide((size_t)n_nodes);
-    if (rntn_rows && ctx->rb_steps > 0 && (rc = pack_rntn_wide(ctx, st)) != TL_OK) return rc;
-    if (n_nodes > ctx->bw_nodes) {
+    // RNTN: rows of d * 2d + d values per node and launches per height, or rows of d where the one kernel takes them (24-bit row numbers,
+    // 32-bit byte offsets) and the caller has not asked for launches
+    const bool rntn_rows = rntn && (ctx->rb_steps == 0 || ctx->async_backward < 0 || n_nodes >= (1 << 24) || (size_t)n_nodes * H * 4 >= ((size_t)1 << 32));
+    if (rntn_rows && (rc = pack_rntn_wide(ctx, st)) != TL_OK) return rc;
+    if (n_nodes > ctx->bw_nodes || (rntn_rows && !ctx->bw_rows)) {
         TL_HIP(hipDeviceSynchronize());
         if (ctx->bw) { TL_HIP(hipFree(ctx->bw)); ctx->bw = nullptr; }
         ctx->bw_nodes = 0;
         const size_t cap = (size_t)ctx->cap_nodes;
         size_t floats = 2 * cap * H + cap * 5 * H;                                   // n_int*5H + n_leaf*3H <= N*5H
-        if (rntn) floats = 2 * cap * H + (cap / 2 + 1) * (rntn_wide(cap) ? rntn_row : (size_t)H);
+        if (rntn) floats = 2 * cap * H + (cap / 2 + 1) * (rntn_rows ? rntn_row : (size_t)H);
         if (floats * sizeof(float) > ((size_t)64 << 30)) return TL_ENOMEM;
         TL_HIP(hipMalloc(&ctx->bw, floats * sizeof(float)));
         ctx->bw_nodes = ctx->cap_nodes;
+        ctx->bw_rows = rntn_rows;
     }
     Fwd f{};
     f.n_trees = n_trees; f.n_nodes = n_nodes; f.n_leaf = n_leaf; f.n_int = n_int;
@@ -1622,9 +1628,10 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const bool many = !exact_rows && ((ctx->bw_spw2 > 18 && n_int > 2000) || (100 * ctx->bw_ws_grid < 86 * ctx->n_cu && n_int > 4000));
     const bool ws = persistent_ok && ctx->bw_ws_grid > 0 && !many &&
                     (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
-    // RNTN: in one kernel wherever its matrices fit into registers and the rows' addresses into 32 bits (nothing else is left for those sizes)
+    // RNTN: in one kernel wherever its matrices fit into registers and the rows' addresses into 32 bits; the call returns the structure
+    // pass's status in every mode
     const bool rntn_one = rntn && !rntn_rows && n_int > 0;
-    const bool heights_on_device = ctx->async_backward > 0 && (persistent_ok || rntn_one);
+    const bool heights_on_device = ctx->async_backward > 0 && persistent_ok;
     auto launch_all_heights = [&]() {
         if (rntn_one) {
             Fwd g = f;

@@ -178,6 +178,48 @@ def test_rntn_gradients_at_the_edges_of_the_blocks(d, n_trees):
         np.testing.assert_allclose(out[0][k], ref[k].reshape(out[0][k].shape), rtol=1e-4, atol=1e-4 * max(1e-3, float(np.abs(ref[k]).max())), err_msg=k)
 
 
+@pytest.mark.parametrize("d", [20, 48, 96])
+def test_rntn_backward_in_every_mode(d):
+    """tl_set_async_backward and RNTN: -1 takes launches per height (fp32 instructions, another order of summation: the same
+    gradients to rounding, other bits), 0 and 1 the one kernel, and a malformed batch is reported by the call in every mode.
+    Modes alternate on one context, with an update in between: each finds its packed matrix and its workspace."""
+    import torch
+    print("case rntn backward modes", d, flush=True)
+    params = synth.make_rnn_params(790 + d, synth.CELL_RNTN, 60, d, scale=0.3 / d ** 0.5)
+    trees = synth.make_trees(791, [1, 2, 30, 1, 18, 33, 9], ["random", "chain", "balanced", "random", "chain", "random", "balanced"], 60)
+    g_h = np.random.default_rng(d).standard_normal((trees.n_nodes, d)).astype(np.float32)
+    dev_g = torch.from_numpy(g_h).cuda()
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        bad = dict(b)
+        bad["left"] = b["left"].clone()
+        bad["left"][trees.n_nodes - 1] = 0              # the last leaf gets one child, and that in another tree
+        for step in range(2):
+            net.forward()
+            out = {}
+            for mode in (0, -1, 1):
+                binding.tl_set_async_backward(net.ctx, mode)
+                out[mode] = {k: v.cpu().numpy() for k, v in binding.tl_backward(net.ctx, b, dev_g, d, rntn=True).items()}
+                assert binding.tl_status(net.ctx) == 0
+                with pytest.raises(binding.TLError) as e:
+                    binding.tl_backward(net.ctx, bad, dev_g, d, rntn=True)
+                assert e.value.code == binding.TL_ESTRUCT and binding.tl_status(net.ctx) == binding.TL_ESTRUCT
+            p = binding.tl_get_params(net.ctx, 60, d, d, cell=params.cell)
+            ref = oracle.backward(synth.Params(params.cell, 60, d, d, p["emb"].cpu().numpy(), None, None, p["u"].cpu().numpy(), p["b"].cpu().numpy(),
+                                               p["w_leaf"].cpu().numpy()), trees, b["h"].cpu().numpy(), None, g_h)
+            ref["d_w_leaf"] = ref.pop("d_v")
+            assert np.array_equal(out[0]["d_x"], out[1]["d_x"])
+            assert not np.array_equal(out[-1]["d_x"], out[0]["d_x"]), "launches per height were expected to run"
+            for mode in out:
+                for k in ref:
+                    np.testing.assert_allclose(out[mode][k], ref[k].reshape(out[mode][k].shape), rtol=1e-4, atol=1e-4 * max(1e-3, float(np.abs(ref[k]).max())),
+                                               err_msg="step %d mode %d %s" % (step, mode, k))
+            binding.tl_sgd_update(net.ctx, 1e-2, b, {k: torch.from_numpy(v).cuda() for k, v in out[0].items()})
+    finally:
+        net.close()
+
+
 @pytest.mark.parametrize("what", ["scales", "infinite weight", "nan gradient"])
 def test_rntn_gradients_outside_the_ordinary_range(what):
     """Gradients are factors as they are, of any magnitude; an infinite operand is met in fp32; a NaN stays where it belongs."""
