@@ -110,8 +110,9 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  *                        round trip instead of an acknowledgement, a barrier and a queue read, so
  *                        this is the fastest choice for deep or narrow batches and as fast as
  *                        TL_SCHED_LEVEL_DEVICE on wide ones.  Consequence: if the parameters or
- *                        embeddings hold NaNs whose bits are all ones, a forward ends with
- *                        TL_ESTALL instead of NaN results.  (In TL_F32 one workgroup per
+ *                        embeddings hold NaNs whose bits are all ones, a forward of TL_TREELSTM, or
+ *                        with TL_BF16_IN, may end with TL_ESTALL instead of results (TL_RNTN, and
+ *                        TL_TREERNN in TL_F32, give them).  (In TL_F32 one workgroup per
  *                        set works out the order of the nodes for all of them, beside the leaves' cells.)
  *                        Where its cells are not used (hidden > 512, TL_RNTN with hidden > 96,
  *                        tl_forward_noalloc, batches of 2^24 nodes or 4 GiB of h and more)

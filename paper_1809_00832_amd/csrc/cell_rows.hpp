@@ -8,7 +8,8 @@
 // (cell_rntn.hpp), 16 side by side, with rows p <= q only; the products are scaled by a_q where they are and added up across the lanes
 // at the end.  So no sums are exchanged between waves or workgroups.  Lane q mod 16 holds what the other schedulers
 // call a class, and classes are added in their order: the same bits.
-// Rows that are not written yet show the pattern of cell_ws.hpp (validity carried by the data).
+// Rows that are not written yet show the pattern of cell_ws.hpp (validity carried by the data); no NaN of the parameters or embeddings is
+// taken for it.
 // d <= 96: 21 units of 8 registers at d = 64, 43 at d = 96 (above, the matrix does not fit and the level kernel stands in).
 // Measured (whole forward; level kernel with this cell's products / with fp32 instructions): 256 parse trees at d = 64 229 / 329 -> 108 us, 150
 // at d = 96 317 / 841 -> 160, 8 at d = 64 157 / 209 -> 60, 4 at d = 8 119 / 116 -> 30.  Of the kernel's 88 us at d = 64 the products are 22, the rest
@@ -21,6 +22,7 @@
 namespace tl {
 
 constexpr int ROWS_UNITS = 4;     // hidden units of a workgroup, one per wave
+constexpr int ROWS_SETTLE_SPINS = 16;   // unsuccessful requests after which a wave asks whether the pattern stands in a leaf's row
 
 template <int NS> struct RowsSmem {
     static constexpr int LD = 32 * NS + 4;
@@ -172,6 +174,17 @@ __device__ __forceinline__ void rows_run(RowsSmem<NS> &sm, const Fwd &f, const i
             for (int t = 0; t < 2; ++t) m = max(max(m, max(rows[i][t].x, rows[i][t].y)), max(rows[i][t].z, rows[i][t].w));
         return __ballot(m == FLOW_SENTINEL) != 0ull;
     };
+    // A leaf's row was there before the kernel: a word of it that shows the pattern is a NaN of the embedding's own, and any other NaN
+    // stands for it.  Asked only when a wait lasts (legitimate ones are mostly shorter).
+    auto settle_leaves = [&](bool leaf0, bool leaf1) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < CPT; ++i) {
+            const bool leaf = t16 + 16 * i >= seg ? leaf1 : leaf0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                if (leaf && rows[i][e >> 2][e & 3] == FLOW_SENTINEL) rows[i][e >> 2][e & 3] = 0x7FC00000u;
+        }
+    };
     auto prepare = [&](const int4 &q) __attribute__((always_inline)) {
         base0 = __umul24((unsigned)q.y, row_b);
         base1 = __umul24((unsigned)q.z, row_b);
@@ -201,6 +214,7 @@ __device__ __forceinline__ void rows_run(RowsSmem<NS> &sm, const Fwd &f, const i
                 request(std::true_type{});
                 aborted = ld_dev(&f.ctl->abort.v);              // arrives with the rows
                 cut();
+                if (spins >= min(ROWS_SETTLE_SPINS, f.spin_limit)) settle_leaves(f.left[q.y] < 0, f.left[q.z] < 0);
             } while (shows_pattern());
         }
         // ---- split ---------------------------------------------------------------------
