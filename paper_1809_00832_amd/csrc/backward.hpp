@@ -986,7 +986,7 @@ template <int NS> struct RntnBwdSmem {
     static constexpr int LDZ = 16 * NS + 4;
     halfx8 split[2][NS * 2 * 64];                           // as in RowsSmem
     float dz[2][16 * LDZ];
-    float back[2][16];
+    int back[2][16];                                        // a row's sums are multiplied by two to this
     int child[2][2][16];
     int cmd[8];
 };
@@ -1005,7 +1005,8 @@ __global__ __launch_bounds__(WG_THREADS, (rntn_bwd_sets_per_cu(NS))) void k_back
     if (decided_to_leave(&sm.cmd[7], tid == 0 && batch_rejected(f))) return;
     const int p = member * ROWS_UNITS + wave, pp = p < 2 * d ? p : 0;      // (a wave beyond the last p computes the first one's sums and adds nothing)
     halfx8 w[NS][NS][2];                                    // [k / 16][k-step over q]
-    float sc[NS], lin[NS];
+    int sc[NS];                                             // ... and a column's by two to this
+    float lin[NS];
     {
         const halfx8 *wp = reinterpret_cast<const halfx8 *>(f.xi.wp) + (size_t)pp * NS * NS * 128 + lane;
 #pragma unroll
@@ -1016,7 +1017,7 @@ __global__ __launch_bounds__(WG_THREADS, (rntn_bwd_sets_per_cu(NS))) void k_back
                 for (int e = 0; e < 2; ++e) w[j][t][e] = wp[(size_t)((j * NS + t) * 2 + e) * 64];
 #pragma unroll
         for (int j = 0; j < NS; ++j) {
-            sc[j] = f.xi.scale[((size_t)pp * 2 * NS + j) * HU + (lane & 15)];
+            sc[j] = (int)(__float_as_uint(f.xi.scale[((size_t)pp * 2 * NS + j) * HU + (lane & 15)]) >> 23) - 127;      // (columns beyond the last: products are zero)
             lin[j] = f.xi.scale[((size_t)pp * 2 * NS + NS + j) * HU + (lane & 15)];
         }
     }
@@ -1079,7 +1080,7 @@ __global__ __launch_bounds__(WG_THREADS, (rntn_bwd_sets_per_cu(NS))) void k_back
             const unsigned eb = max(__float_as_uint(m) >> 23, 15u);
             const float scale = __uint_as_float((268u - eb) << 23);
             if (t16 == 0) {
-                sm.back[buf][my_row] = __uint_as_float((eb - 14u) << 23);
+                sm.back[buf][my_row] = (int)eb - 14 - 127;
                 sm.child[buf][0][my_row] = here ? left : -1;
                 sm.child[buf][1][my_row] = here ? right : -1;
             }
@@ -1125,14 +1126,16 @@ __global__ __launch_bounds__(WG_THREADS, (rntn_bwd_sets_per_cu(NS))) void k_back
 #pragma unroll
                 for (int j = 0; j < NS; ++j) t[j] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo8, w[j][s][0], t[j], 0, 0, 0);
             }
-            const floatx4 back = *reinterpret_cast<const floatx4 *>(&sm.back[buf][4 * (lane >> 4)]);
+            const int *back = &sm.back[buf][4 * (lane >> 4)];
             const float *z = &sm.dz[buf][4 * (lane >> 4) * LDZ + (lane & 15)];
             float sum = 0.f;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 float x = 0.f;
+                const int back_v = back[v];
+                // (both scales at once: t times the column's alone may be infinite where the product with both is not)
 #pragma unroll
-                for (int j = 0; j < NS; ++j) x = __builtin_fmaf(z[v * LDZ + 16 * j], __builtin_fmaf(t[j][v] * sc[j], back[v], lin[j]), x);
+                for (int j = 0; j < NS; ++j) x = __builtin_fmaf(z[v * LDZ + 16 * j], __builtin_amdgcn_ldexpf(t[j][v], sc[j] + back_v) + lin[j], x);
                 x += dpp<DPP_XOR1>(x);
                 x += dpp<DPP_XOR2>(x);
                 x += dpp<DPP_HALF_MIRROR>(x);

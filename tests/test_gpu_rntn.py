@@ -276,3 +276,19 @@ def test_rntn_gradients_outside_the_ordinary_range(what):
         m = (tree == t)[:, None] & np.isfinite(want)
         if m.any():
             np.testing.assert_allclose(got[m], want[m], rtol=1e-4, atol=1e-4 * float(np.abs(want[m]).max()), err_msg="tree %d" % t)
+
+
+def test_rntn_gradients_of_weights_near_the_largest_number():
+    """Weights of up to 2e34 beside states of 5e-18: a product of scaled terms and the column's scale alone would be infinite, the
+    gradient of an operand (sums of 2d d such products, up to 1e17) is not."""
+    print("case rntn backward, largest weights", flush=True)
+    d = 16
+    params = synth.make_rnn_params(795, synth.CELL_RNTN, 40, d, scale=0.05)
+    params.v *= np.float32(4e35)
+    params.emb *= np.float32(1e-16)
+    trees = synth.make_trees(796, [2] * 40, ["random"] * 40, 40)
+    g_h = np.random.default_rng(4).standard_normal((trees.n_nodes, d)).astype(np.float32)
+    out, ref = rntn_gradients(params, trees, g_h)
+    want = ref["d_x"]
+    assert np.isfinite(want).all() and np.abs(want).max() > 1e16
+    np.testing.assert_allclose(out[0]["d_x"], want, rtol=1e-4, atol=1e-4 * float(np.abs(want).max()))
