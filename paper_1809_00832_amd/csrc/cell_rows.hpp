@@ -305,7 +305,7 @@ __device__ __forceinline__ void rows_run(RowsSmem<NS> &sm, const Fwd &f, const i
             }
             const int row = 4 * (lane >> 4) + (lane & 3), node = sm.node[buf][row];
             if ((lane & 15) < 4 && node >= 0 && hu < H) {
-                if (__builtin_expect(__builtin_isnan(sum), 0)) sum = rntn_sum_plain(f, f.inner, &sm.a[buf][row * LD], hu);
+                if (__builtin_expect(!__builtin_isfinite(sum), 0)) sum = rntn_sum_plain(f, f.inner, &sm.a[buf][row * LD], hu);
                 const float h = tanh_f(sum + bias);
                 buf_st_f<true>(rs_h, __umul24((unsigned)node, row_b) + (unsigned)hu * 4u, h);
                 const int t = sm.tree[buf][row];

@@ -430,7 +430,7 @@ __device__ __forceinline__ void split_rnn_run(SplitRnnSmem<NG> &sm, const Fwd &f
             const int hu = hu0 + g * HU;
             float sum = (((p[0] + p[1]) + p[2]) + p[3]) * sb[0];
             if (e.x >= 0) {
-                if (__builtin_expect(__builtin_isnan(sum) && hu < H, 0)) sum = split_rnn_plain(f, e.y, e.z, hu);
+                if (__builtin_expect(!__builtin_isfinite(sum) && hu < H, 0)) sum = split_rnn_plain(f, e.y, e.z, hu);
                 const float hh = hu < H ? tanh_f(sum + sb[1]) : 0.f;
                 const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
                 if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)e.x * hx_row_b + split_word_off(hu), __uint_as_float(word));

@@ -84,6 +84,31 @@ def test_infinities_are_summed_in_fp32(where, sched):
     np.testing.assert_allclose(got["h"][ok], ref["h"][ok], rtol=RTOL, atol=ATOL)
 
 
+@pytest.mark.parametrize("cell,sched", [("rntn", "dataflow"), ("rntn", "level_device"), ("rntn", "level_host"), ("rnn", "dataflow")])
+def test_sums_that_overflow_only_when_scaled(cell, sched):
+    """3e34 - 1.9e34 - 1.9e34: the first term is beyond the largest number once it is scaled by 2^14, the others are not.  The sum
+    is negative, so every internal node over two leaves is -1 there."""
+    print("case scaled overflow", cell, sched, flush=True)
+    d = 64 if cell == "rnn" else 16
+    p = synth.make_rnn_params(735, synth.CELL_RNTN if cell == "rntn" else synth.CELL_TREERNN, 2, d, scale=0.01)
+    if cell == "rntn":
+        p.emb[:] = 1
+        p.v[3, 0, 0], p.v[3, 1, 1], p.v[3, 2, 2] = 3e34, -1.9e34, -1.9e34
+    else:                                               # three different quarters of the K axis
+        p.emb[:, 0] = 6e34, 3.9e34
+        p.emb[1, 40] = 3.9e34
+        p.u[:] = 0
+        p.u[0, 3], p.u[d, 3], p.u[d + 40, 3] = 1, -1, -1
+    trees = synth.make_trees(736, [2] * 20, ["random"] * 20, 2)
+    trees.word[trees.left[trees.left >= 0]], trees.word[trees.right[trees.left >= 0]] = 0, 1
+    ref = oracle.forward_params(p, trees, n_threads=4)
+    got = run(p, trees, sched)
+    inner = trees.left >= 0
+    assert (ref["h"][inner, 3] == -1).all()
+    assert (got["h"][inner, 3] == -1).all()
+    np.testing.assert_allclose(got["h"][~inner], ref["h"][~inner])
+
+
 @pytest.mark.parametrize("where", ["emb", "v", "u", "b"])
 @pytest.mark.parametrize("cell,d", [("rntn", 24), ("rntn", 33), ("rnn", 40)])
 def test_a_nan_of_32_ones_ends_no_forward(cell, d, where):
