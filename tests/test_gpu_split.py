@@ -119,6 +119,23 @@ def test_rows_that_were_internal_nodes_before_become_leaves(H, E, first):
         np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
 
 
+def test_leaf_sums_that_overflow_only_when_scaled():
+    """6e34 - 3.9e34 - 3.9e34 over three quarters of the embedding row: the first partial sum is beyond the largest number once it is
+    scaled by 2^13, the others are not.  The input gate is closed, so c is zero there."""
+    print("case split scaled overflow", flush=True)
+    H, E = 20, 300
+    p = synth.make_treelstm_params(955, 4, E, H, "xavier")
+    p.emb[:, 0], p.emb[:, 100], p.emb[:, 200] = 6e34, 3.9e34, 3.9e34
+    p.w_leaf[:] = 0
+    p.w_leaf[0, 3], p.w_leaf[100, 3], p.w_leaf[200, 3] = 1, -1, -1
+    p.b_leaf[2 * H:] = 1
+    trees = synth.make_trees(956, [12, 5, 1, 20], ["random"] * 4, 4)
+    ref, got = oracle.forward_params(p, trees, n_threads=4), run(p, trees, "dataflow")
+    assert (ref["c"][trees.left < 0, 3] == 0).all()
+    for key in ("h", "c"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=ATOL, err_msg=key)
+
+
 @pytest.mark.parametrize("bits", [0xFFFFE000, 0x7FFFE000, 0xFFFFFFFE, 0x7FC00000])
 @pytest.mark.parametrize("where", ["b_leaf", "b", "emb"])
 def test_a_nan_is_a_result_whatever_its_payload(where, bits):
