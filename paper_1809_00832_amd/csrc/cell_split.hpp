@@ -286,11 +286,11 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 // The same blocks for h = tanh(a W + b): NG column groups side by side in a workgroup take the place of the gates, and waves 0, 1 hold the
 // left child's K axis, waves 2, 3 the right one's (S k-steps of 32 each).  Leaves are embedding rows of any magnitude, so every row of the
 // split copy has a scale of its own, and f.hx_back[node] says what its sums are multiplied by (2^-14 for internal nodes).
-// Few weights (32 registers per column group at H = 256), so two workgroups a CU.  One group per workgroup where every tree then still
-// has a slot of its own, two that share the rows they gather otherwise (forward, NG = 1 / 2 / 4): 25 trees at H = 50 30.8 / 35.7 / 40.3 us, at
-// H = 150 39.6 / 39.8 / 48.5, at H = 256 43.6 / 44.1 / 47.8; 100 trees at H = 200 55.7 / 54.4 / 59.9; 256 trees at H = 256 80.4 / 71.9 / 74.6.
-// (Before, with fp32 instructions and lists taken in pieces: 41.7, 50.4, 49.7, 59.4, 86.0; with rows of h scaled, split and left in LDS
-// for four waves of 16 units each: 34.6, 54.9, 56.1, -, 79.6, and 82 instead of 50 for 10 trees at H = 512.)
+// Few weights (32 registers per column group at H = 256), so that two workgroups fit on a CU; where one a CU is the faster way, and where a
+// workgroup takes one column group or two that share the rows they gather, is decided in forward_impl, with the figures.  (NG = 1 / 2 / 4, two a
+// CU, forward: 25 trees at H = 50 30.8 / 35.7 / 40.3 us, at H = 256 43.6 / 44.1 / 47.8, 256 trees there 80.4 / 71.9 / 74.6.  Before, with fp32
+// instructions and lists taken in pieces: 41.7, 49.7, 86.0; with rows of h scaled, split and left in LDS for four waves of 16 units each: 34.6,
+// 56.1, 79.6.)
 template <int NG> struct SplitRnnSmem {
     float red[2][4 * NG * 64 * 4];
     float sum_of[NG * HU * 2];

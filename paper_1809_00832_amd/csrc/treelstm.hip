@@ -1238,11 +1238,23 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     // (What the kernel that is not picked costs, its launch: with an odd hidden size, H = 35, one to eight bushy trees of 200 to 400 leaves
     // take 84 ... 105 us level by level alone and 88 ... 108 with both launched, chains of those sizes 1 555 ... 3 324 against
     // 342 ... 567.)
-    // (TreeRNN: one column group per workgroup if every tree then has a set of its own, else two; cell_split.hpp)
-    const int rnn_groups = n_trees <= ctx->flow_grid / ctx->flow_set ? 1 : 2;
-    const int flow_set = cfg.cell == TL_TREERNN && split > 0 && rnn_groups == 2 ? (ctx->flow_set + 1) / 2 : ctx->flow_set;
-    const int flow_sets = ctx->flow_grid / flow_set;
-    const bool flow_or_levels = flow && n_trees < flow_sets && n_nodes / (n_trees > 0 ? n_trees : 1) >= FLOW_LARGE_TREE_NODES;
+    // From which size on is a cell's own: where a bushy tree on one set takes as long as level by level.  Nodes a tree, one bushy tree
+    // a set, level by level / data-flow: TreeRNN H = 100, 799 79 / 53 us, H = 256 78 / 65, 1 599 97 / 142 (of 8 trees each); RNTN d = 48, 1 599
+    // 168 / 136, 2 999 215 / 225 (8 trees), d = 96, 1 599 200 / 220, 799 179 / 129 (one tree).
+    const bool fp32_rnn = cfg.cell == TL_TREERNN && split > 0;
+    const int large_tree = fp32_rnn ? 1024 : rows ? (ctx->n_cg <= 4 ? 2048 : 1536) : FLOW_LARGE_TREE_NODES;
+    // fp32 TreeRNN and RNTN: two workgroups fit on a CU.  One a CU is the faster way unless there is much work a set: workgroups that share a CU
+    // slow each other down, and with trees on every other set half of the CUs have two and the others none.  TreeRNN: one column group per
+    // workgroup if every tree then has a set of its own, or with few column groups, else two (cell_split.hpp).  Two a CU / one, us: TreeRNN
+    // H = 256, 16 random trees of 200 leaves 80 / 66, 100 chains of 60 168 / 151, 100 random trees of 200 (39 900 nodes) 133 / 148; H = 512, 8 trees
+    // 120 / 85, 256 chains of 60 leaves (30 464 nodes) 361 / 278, 160 balanced trees of 100 (31 840) 188 / 201; RNTN d = 48, 40 parse trees 62 / 49, d = 32,
+    // 64 chains of 60 185 / 154, 100 balanced trees of 100 (19 900) 57 / 68.
+    const int rnn_groups = ctx->flow_set <= 5 || n_trees <= ctx->n_cu / ctx->flow_set ? 1 : 2;
+    const int flow_set = fp32_rnn && rnn_groups == 2 ? (ctx->flow_set + 1) / 2 : ctx->flow_set;
+    const long long flow_light = (fp32_rnn ? 120ll : 72ll) * ctx->n_cu;
+    const bool one_per_cu = (fp32_rnn || rows) && flow_set <= ctx->n_cu && (n_trees <= ctx->n_cu / flow_set || n_nodes <= flow_light);
+    const int flow_sets = (bf16 ? ctx->flow_grid : ctx->n_cu) / ctx->flow_set;
+    const bool flow_or_levels = flow && n_trees < flow_sets && n_nodes / (n_trees > 0 ? n_trees : 1) >= large_tree;
     if (persistent && spw > 0 && bf16) {
         f.hb = static_ws ? reinterpret_cast<unsigned short *>(ctx->scratch + NOALLOC_WS_BYTES) : ctx->hb;
         f.hs = ctx->hs;
@@ -1268,7 +1280,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const size_t level_lds = spw > 0 ? ctx->ws_lds : TILE_SMEM_BYTES;
     const size_t kern_lds = flow ? flow_lds : level_lds;
     const bool whole_sets = spw > 0 || flow;          // every workgroup of the kernel is tied to one column group
-    int grid_p = flow ? ctx->flow_grid : (persistent && spw > 0) ? ctx->ws_grid : ctx->persistent_grid;
+    int grid_p = flow ? (one_per_cu && ctx->n_cu < ctx->flow_grid ? ctx->n_cu : ctx->flow_grid) : (persistent && spw > 0) ? ctx->ws_grid : ctx->persistent_grid;
     if (kern) {
         int per_cu = 0;
         if ((rc = resident_per_cu(ctx, kern, kern_lds, &per_cu)) != TL_OK) return rc;
@@ -1330,6 +1342,18 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
         f.place = flow_set <= 3 || (flow_set <= 10 && 4ll * n_trees <= 3ll * f.n_slots) ||
                   (flow_set <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
+        // fp32 TreeRNN and RNTN have lines of their own: all domains -> inside, one workgroup a CU, us: TreeRNN H = 48, 40 chains of 60 leaves 95 -> 91, H = 100, 8
+        // of them 109 -> 88, 24 random trees of 200 57.4 -> 54.8, H = 200, 4 chains 114 -> 109, H = 256, 4 random trees of 200 59.5 -> 63.5, H = 512 80 -> 83;
+        // RNTN d = 16, 64 chains of 60 133 -> 124, d = 32 154 -> 144, d = 40, 40 parse trees 47 -> 52, d = 48 50 -> 53.  Two a CU: d = 32, 64 balanced trees of 100
+        // leaves 48 -> 67.
+        if (fp32_rnn) f.place = flow_set <= 3 || (rnn_groups == 1 && flow_set <= (one_per_cu ? 13 : 5));
+        if (rows) f.place = flow_set <= 3 || (one_per_cu && (flow_set <= 8 || (flow_set <= 10 && n_trees <= 8)));
+        // (sets left over on all domains are the slower ones, and the call waits for them: not used where the others are enough.  H = 100, 24 chains of 300 leaves
+        // 482 -> 396 us)
+        if ((fp32_rnn || rows) && f.place && n_trees <= f.n_slots / N_XCD * N_XCD) {
+            f.n_slots = f.n_slots / N_XCD * N_XCD;
+            grid_p = f.n_slots * flow_set;
+        }
         f.flow_seen = reinterpret_cast<int32_t *>(ctx->flow_ws);
         f.flow_list = reinterpret_cast<int4 *>(ctx->flow_ws + align256((size_t)ctx->n_cg * ctx->cap_nodes * sizeof(int32_t)));
     }

@@ -198,6 +198,52 @@ def test_treernn_infinities_are_summed_in_fp32(where):
     np.testing.assert_allclose(got["h"], ref["h"], rtol=RTOL, atol=4e-6)
 
 
+# ---- both cells: sets of workgroups, their places, and the choice of the kernel ---------------------------------------
+def small_params(cell, d, seed):
+    p = synth.make_rnn_params(seed, synth.CELL_RNTN if cell == "rntn" else synth.CELL_TREERNN, 60, d, scale=(0.7 if cell == "rntn" else 1.0) / d ** 0.5)
+    return p
+
+
+@pytest.mark.parametrize("cell,d,n_trees,leaves", [("rnn", 80, 51, 9), ("rnn", 80, 52, 9), ("rnn", 96, 42, 9), ("rnn", 96, 43, 9), ("rnn", 96, 86, 9), ("rnn", 208, 19, 20),
+                                                   ("rnn", 208, 20, 20), ("rnn", 224, 18, 20), ("rnn", 100, 380, 40), ("rnn", 100, 400, 40), ("rnn", 40, 380, 40), ("rnn", 40, 400, 40),
+                                                   ("rntn", 20, 51, 9), ("rntn", 20, 52, 9), ("rntn", 20, 51, 190), ("rntn", 20, 52, 190), ("rntn", 32, 33, 9), ("rntn", 36, 29, 9),
+                                                   ("rntn", 12, 90, 90), ("rntn", 12, 110, 90)])
+def test_sets_of_workgroups_on_both_sides_of_the_lines(cell, d, n_trees, leaves):
+    """One workgroup a CU or two, one column group per workgroup or two, sets inside one domain or on all of them: as many trees as
+    there are sets and one more, batches on both sides of the line in nodes.  Every node is evaluated once, by all of its columns."""
+    print("case sets", cell, d, n_trees, leaves, flush=True)
+    p = small_params(cell, d, 900 + d)
+    trees = synth.make_trees(901, [leaves - t % 5 for t in range(n_trees)], (["random", "chain", "balanced"] * n_trees)[:n_trees], 60)
+    got, ref = run(p, trees, "dataflow"), oracle.forward_params(p, trees, n_threads=8)
+    for key in ("h", "h_root"):
+        np.testing.assert_allclose(got[key], ref[key], rtol=RTOL, atol=4e-6, err_msg=key)
+
+
+@pytest.mark.parametrize("cell,d,line", [("rnn", 33, 1024), ("rnn", 100, 1024), ("rntn", 24, 2048), ("rntn", 72, 1536)])
+def test_few_large_trees_of_either_kind_one_after_the_other(cell, d, line):
+    """Few trees of more nodes than the line: both kernels are launched and the device picks.  Bushy trees, then deep ones, then bushy
+    ones again through one context (rows marked for a kernel that did not run become leaves and the other way round), and
+    trees just below the line, against the checker.  TreeRNN, whose two kernels sum in different orders: bushy trees have the
+    level scheduler's bits, deep ones and those below the line have not."""
+    print("case few large trees", cell, d, flush=True)
+    p = small_params(cell, d, 910 + d)
+    L = line // 2 + 1                                   # 2 L - 1 nodes, one more than the line
+    nets = {s: binding.TreeNet(p, scheduler=s) for s in ("dataflow", "level_device")}
+    try:
+        for i, (shape, leaves) in enumerate([("balanced", L + 9), ("chain", L), ("random", L + 60), ("balanced", L - 1), ("balanced", L)]):
+            trees = synth.make_trees(911 + i, [leaves] * 3, [shape] * 3, 60)
+            ref = oracle.forward_params(p, trees, n_threads=8)
+            got = {s: n.run(trees) for s, n in nets.items()}
+            for s in got:
+                for key in ("h", "h_root"):
+                    np.testing.assert_allclose(got[s][key], ref[key], rtol=RTOL, atol=4e-6, err_msg="%s %s %s" % (s, shape, key))
+            if cell == "rnn":
+                assert np.array_equal(got["dataflow"]["h"], got["level_device"]["h"]) == (shape != "chain" and leaves >= L), (shape, leaves)
+    finally:
+        for n in nets.values():
+            n.close()
+
+
 # ---- RNTN: the backward pass in one kernel (d <= 96) -------------------------------------------------------------------
 def rntn_gradients(params, trees, g_h, modes=(0, 1)):
     import torch
