@@ -12,7 +12,7 @@
 // embedding rows of any magnitude - and every column of a slice to [2^13, 2^14).  The factor a_q is the fp32 value itself.  A sum
 // that does not come out finite (an infinite operand has no two terms, and scaled sums overflow 2^15 earlier) is taken again in fp32 from the parameters
 // as given.
-// Measured (level kernel, whole forward; before: fp32 instructions, all products): 256 parse trees at d = 64 330 -> 229 us, 150 at d = 96 784 -> 317,
+// Measured (level kernel, whole forward; before: fp32 instructions, all products): 256 parse trees at d = 64 330 -> 205 us, 150 at d = 96 784 -> 317,
 // 8 at d = 64 190 -> 157; error against 64 bits unchanged (1.4e-6 to 1.7e-6).  What is left is the chain of a frontier (records, rows,
 // parts, barrier), about 12 us each.
 #pragma once
@@ -259,8 +259,10 @@ template <int NS, int RB, bool VEC4, bool COH>
 __device__ __forceinline__ void rntn_blocks(RntnSmem<NS> &s, const TileSmem &sm, const Fwd &f, const Gemm &gm, int nrb, int rb0, int cg, float (&mine)[4])
 {
     constexpr int LD = RntnSmem<NS>::LD, UNITS = NS * (NS + 1);
-    // what is left of 256 registers beside the operands of the rows
-    constexpr int RING = RB * NS <= 8 ? (UNITS < 12 ? UNITS : 12) : 4;
+    // Beside the operands of few rows there are registers for many units.  Four row blocks at NS = 4 (two at 8) take 128 of the 256 for
+    // operands, and with more than two units the kernels that walk all heights spill (4 / 3 / 2 units: 21 / 10 / 4 registers; 256 parse trees at
+    // d = 64, level by level 219 / 210 / 205 us, 6 chains of 250 leaves 2 842 / 2 752 / 2 670).
+    constexpr int RING = RB * NS <= 8 ? (UNITS < 12 ? UNITS : 12) : 2;
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int part = __builtin_amdgcn_readfirstlane(sm.cmd[5]);             // written by the caller before its barrier
     constexpr unsigned CG_BYTES = rntn_units_of(NS) * 2048u, CG_SLICES = 32 * NS + 1;
@@ -411,16 +413,6 @@ __device__ __forceinline__ void rntn_tile(TileSmem &sm, const Fwd &f, const Gemm
 #pragma unroll
         for (int v = 0; v < 4; ++v) rntn_finish<NS, COH>(s, sm, f, gm, count, hu, rb * 16 + (lane >> 4) * 4 + v, ((e[v][0] + e[v][1]) + e[v][2]) + e[v][3], bias);
     }
-}
-
-// Dispatch on the padded K length (k-steps of 32): d <= 32, 64, 128.
-template <bool VEC4, bool COH>
-__device__ __forceinline__ void rntn_tile_any(TileSmem &sm, const Fwd &f, const Gemm &gm, int count, int cg)
-{
-    const int ns = gm.n_chunks * (KC / 32);
-    if (ns == 2) rntn_tile<2, VEC4, COH>(sm, f, gm, count, cg);
-    else if (ns == 4) rntn_tile<4, VEC4, COH>(sm, f, gm, count, cg);
-    else rntn_tile<8, VEC4, COH>(sm, f, gm, count, cg);
 }
 
 }  // namespace tl

@@ -23,7 +23,9 @@
 namespace tl {
 
 enum Epi {
-    EPI_LSTM_LEAF = 0, EPI_LSTM_INNER = 1, EPI_RNN_INNER = 2, EPI_RNTN_INNER = 3,
+    EPI_LSTM_LEAF = 0, EPI_LSTM_INNER = 1, EPI_RNN_INNER = 2,
+    // RNTN (cell_rntn.hpp), by its k-steps of 32: kernels of their own, so that the larger ones' registers cost the smaller ones nothing
+    EPI_RNTN_2 = 3, EPI_RNTN_4 = 11, EPI_RNTN_8 = 12,
     // backward pass (backward.hpp): gate gradients of internal nodes / leaves (the forward contraction is
     // recomputed), and the gradient sent to the operand rows (gate gradients times transposed weights)
     EPI_BWD_INNER_GATES = 4, EPI_BWD_INNER_OPERAND = 5, EPI_BWD_LEAF_GATES = 6, EPI_BWD_LEAF_OPERAND = 7,
@@ -33,6 +35,7 @@ enum Epi {
     // one (output widths that are multiples of 4): every gathered row is reused four times as often
     EPI_BWD_INNER_OPERAND4 = 9, EPI_BWD_LEAF_OPERAND4 = 10
 };
+constexpr int epi_rntn_steps(int epi) { return epi == EPI_RNTN_2 ? 2 : epi == EPI_RNTN_4 ? 4 : epi == EPI_RNTN_8 ? 8 : 0; }
 constexpr bool epi_is_backward(int epi)
 {
     return (epi >= EPI_BWD_INNER_GATES && epi <= EPI_BWD_LEAF_OPERAND) || epi == EPI_BWD_INNER_OPERAND4 || epi == EPI_BWD_LEAF_OPERAND4;
@@ -46,7 +49,9 @@ template <int EPI> struct EpiTraits;
 template <> struct EpiTraits<EPI_LSTM_LEAF>  { static constexpr int NG = 3, SEG = 1; };
 template <> struct EpiTraits<EPI_LSTM_INNER> { static constexpr int NG = 5, SEG = 2; };
 template <> struct EpiTraits<EPI_RNN_INNER>  { static constexpr int NG = 1, SEG = 2; };
-template <> struct EpiTraits<EPI_RNTN_INNER> { static constexpr int NG = 1, SEG = 2; };
+template <> struct EpiTraits<EPI_RNTN_2>     { static constexpr int NG = 1, SEG = 2; };
+template <> struct EpiTraits<EPI_RNTN_4>     { static constexpr int NG = 1, SEG = 2; };
+template <> struct EpiTraits<EPI_RNTN_8>     { static constexpr int NG = 1, SEG = 2; };
 template <> struct EpiTraits<EPI_BWD_INNER_GATES>   { static constexpr int NG = 5, SEG = 2; };
 template <> struct EpiTraits<EPI_BWD_INNER_OPERAND> { static constexpr int NG = 1, SEG = 1; };
 template <> struct EpiTraits<EPI_BWD_LEAF_GATES>    { static constexpr int NG = 3, SEG = 1; };
@@ -578,15 +583,15 @@ __device__ inline void cell_tile_staged_bf16(TileSmem &sm, const Fwd &f, const G
 // the rows (see tile_set_rows) and a __syncthreads() has been passed since they were written.
 //   table : source rows of the gather (embedding table, or h)
 //   count : rows in use (1..TILE_ROWS);  cg : column group
-template <bool VEC4, bool COH>
-__device__ __forceinline__ void rntn_tile_any(TileSmem &sm, const Fwd &f, const Gemm &gm, int count, int cg);   // cell_rntn.hpp
+template <int NS, bool VEC4, bool COH>
+__device__ __forceinline__ void rntn_tile(TileSmem &sm, const Fwd &f, const Gemm &gm, int count, int cg);   // cell_rntn.hpp
 
 // (always inlined: a call would copy the kernel's parameters to memory to pass them)
 template <int EPI, bool VEC4, bool COH, bool BF16 = false>
 __device__ __forceinline__ void cell_tile(TileSmem &sm, const Fwd &f, const Gemm &gm, const float *__restrict__ table,
                                  int count, int cg)
 {
-    if constexpr (EPI == EPI_RNTN_INNER) rntn_tile_any<VEC4, COH>(sm, f, gm, count, cg);
+    if constexpr (epi_rntn_steps(EPI) > 0) rntn_tile<epi_rntn_steps(EPI), VEC4, COH>(sm, f, gm, count, cg);
     else if constexpr (BF16) cell_tile_staged_bf16<EPI, VEC4, COH>(sm, f, gm, table, count, cg);
     else if (count <= 32) cell_tile_direct<EPI, VEC4, COH>(sm, f, gm, table, count, cg);
     else cell_tile_staged<EPI, VEC4, COH>(sm, f, gm, table, count, cg);

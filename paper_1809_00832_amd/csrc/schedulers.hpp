@@ -25,7 +25,7 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_tiles_static(Fwd f, const int
     TileSmem &sm = *reinterpret_cast<TileSmem *>(smem_raw);
     if (batch_rejected(f)) return;
     // RNTN cell, frontier of few tiles: RNTN_PARTS workgroups per tile and column group, one part of the sums each
-    const int parts = (EPI == EPI_RNTN_INNER && plan.n_tiles <= f.rntn_units) ? RNTN_PARTS : 1;
+    const int parts = (epi_rntn_steps(EPI) > 0 && plan.n_tiles <= f.rntn_units) ? RNTN_PARTS : 1;
     const int tile = blockIdx.x / (f.n_cg * parts), rem = blockIdx.x % (f.n_cg * parts);
     const int cg = rem % f.n_cg, part = rem / f.n_cg;
     int start, count;
@@ -392,10 +392,10 @@ __global__ __launch_bounds__(WG_THREADS, (SPW > 0 && !BF16) ? 1 : 2) void k_leve
                 if (j_mine >= 0) appended += frontier_push(f, ticket);
             }
         } else {
-            const LevelPlan plan = plan_level(rows, EPI == EPI_RNTN_INNER ? rntn_cap_tiles(f.cap_tiles, f.rntn_units) : f.cap_tiles);
+            const LevelPlan plan = plan_level(rows, epi_rntn_steps(EPI) > 0 ? rntn_cap_tiles(f.cap_tiles, f.rntn_units) : f.cap_tiles);
             // tile T of a frontier: its rows' parents are looked after by the workgroup that computes
             // column group T % n_cg of it
-            const int parts = (EPI == EPI_RNTN_INNER && plan.n_tiles <= f.rntn_units) ? RNTN_PARTS : 1;
+            const int parts = (epi_rntn_steps(EPI) > 0 && plan.n_tiles <= f.rntn_units) ? RNTN_PARTS : 1;
             const int items = plan.n_tiles * f.n_cg * parts;
             for (int item = blockIdx.x; item < items; item += gridDim.x) {
                 const int tile = item / (f.n_cg * parts), rem = item % (f.n_cg * parts);

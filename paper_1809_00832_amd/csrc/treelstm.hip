@@ -74,6 +74,7 @@ struct tl_ctx {
     // fp32 RNTN under the data-flow scheduler (cell_rows.hpp): k-steps of the K axis (0: not used), groups of eight values per
     // segment, packed matrices and their scales
     int rows_steps = 0, rows_seg = 0;
+    int rntn_steps = 0;               // k-steps of 32 of the RNTN tiles (cell_rntn.hpp): 2, 4 or 8
     // fp32 RNTN, backward pass in one kernel (d <= 96): workgroups, sets of them, packed matrices and scales
     int rb_steps = 0, rb_grid = 0, rb_sets = 0;
     _Float16 *rb_wp = nullptr;
@@ -286,15 +287,33 @@ fwd_kernel flow_kernel(const tl_ctx *ctx, int rnn_groups, size_t *lds)
     *lds = ctx->split > 0 ? sizeof(SplitSmem) : ctx->ws_lds;
     return ctx->split > 0 ? flow_kernel_split(ctx->split) : flow_kernel_bf16(ctx->cfg.cell, ctx->spw);
 }
-fwd_kernel ready_kernel(int cell, bool vec4, int spw, bool bf16)
+// The cell of a context's internal nodes under the level and ready schedulers.
+int inner_epi(const tl_ctx *ctx)
 {
-    if (cell == TL_RNTN) return vec4 ? k_ready_persistent<EPI_RNTN_INNER, true, 0> : k_ready_persistent<EPI_RNTN_INNER, false, 0>;
-    return cell == TL_TREELSTM ? ready_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16) : ready_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
+    if (ctx->cfg.cell == TL_RNTN) return ctx->rntn_steps == 2 ? EPI_RNTN_2 : ctx->rntn_steps == 4 ? EPI_RNTN_4 : EPI_RNTN_8;
+    return ctx->cfg.cell == TL_TREELSTM ? EPI_LSTM_INNER : EPI_RNN_INNER;
 }
-fwd_kernel levels_kernel(int cell, bool vec4, int spw, bool bf16)
+fwd_kernel ready_kernel(const tl_ctx *ctx, bool vec4, int spw)
 {
-    if (cell == TL_RNTN) return vec4 ? k_levels_persistent<EPI_RNTN_INNER, true, 0> : k_levels_persistent<EPI_RNTN_INNER, false, 0>;
-    return cell == TL_TREELSTM ? levels_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16) : levels_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
+    const bool bf16 = ctx->cfg.precision == TL_BF16_IN;
+    switch (inner_epi(ctx)) {
+    case EPI_RNTN_2: return vec4 ? k_ready_persistent<EPI_RNTN_2, true, 0> : k_ready_persistent<EPI_RNTN_2, false, 0>;
+    case EPI_RNTN_4: return vec4 ? k_ready_persistent<EPI_RNTN_4, true, 0> : k_ready_persistent<EPI_RNTN_4, false, 0>;
+    case EPI_RNTN_8: return vec4 ? k_ready_persistent<EPI_RNTN_8, true, 0> : k_ready_persistent<EPI_RNTN_8, false, 0>;
+    case EPI_LSTM_INNER: return ready_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16);
+    default: return ready_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
+    }
+}
+fwd_kernel levels_kernel(const tl_ctx *ctx, bool vec4, int spw)
+{
+    const bool bf16 = ctx->cfg.precision == TL_BF16_IN;
+    switch (inner_epi(ctx)) {
+    case EPI_RNTN_2: return vec4 ? k_levels_persistent<EPI_RNTN_2, true, 0> : k_levels_persistent<EPI_RNTN_2, false, 0>;
+    case EPI_RNTN_4: return vec4 ? k_levels_persistent<EPI_RNTN_4, true, 0> : k_levels_persistent<EPI_RNTN_4, false, 0>;
+    case EPI_RNTN_8: return vec4 ? k_levels_persistent<EPI_RNTN_8, true, 0> : k_levels_persistent<EPI_RNTN_8, false, 0>;
+    case EPI_LSTM_INNER: return levels_kernel_epi<EPI_LSTM_INNER>(vec4, spw, bf16);
+    default: return levels_kernel_epi<EPI_RNN_INNER>(vec4, spw, bf16);
+    }
 }
 typedef void (*leaf_kernel)(Fwd, int);
 template <bool KEEP> leaf_kernel leaf_split_kernel_k(int s)
@@ -382,7 +401,9 @@ tiles_kernel backward_kernel(int epi, bool vec4)
 }
 tiles_kernel static_kernel(int epi, bool vec4, bool bf16)
 {
-    if (epi == EPI_RNTN_INNER) return vec4 ? k_tiles_static<EPI_RNTN_INNER, true, false> : k_tiles_static<EPI_RNTN_INNER, false, false>;
+    if (epi == EPI_RNTN_2) return vec4 ? k_tiles_static<EPI_RNTN_2, true, false> : k_tiles_static<EPI_RNTN_2, false, false>;
+    if (epi == EPI_RNTN_4) return vec4 ? k_tiles_static<EPI_RNTN_4, true, false> : k_tiles_static<EPI_RNTN_4, false, false>;
+    if (epi == EPI_RNTN_8) return vec4 ? k_tiles_static<EPI_RNTN_8, true, false> : k_tiles_static<EPI_RNTN_8, false, false>;
     return bf16 ? static_kernel_p<true>(epi, vec4) : static_kernel_p<false>(epi, vec4);
 }
 
@@ -565,9 +586,7 @@ int pack_rntn_f32(tl_ctx *ctx, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, D2 = 2 * H;
     const int Lp = round_up(H, 8);         // (the cells that gather rows take them eight values at a time)
-    int Kp = round_up(2 * Lp, KC);
-    if (Kp > 128) Kp = 256;
-    const int n_steps = Kp / 32, slices = ctx->n_cg * (Kp + 1), rs = ctx->rows_steps;
+    const int n_steps = ctx->rntn_steps, Kp = 32 * n_steps, slices = ctx->n_cg * (Kp + 1), rs = ctx->rows_steps;
     if (!ctx->wp_inner) TL_HIP(hipMalloc(&ctx->wp_inner, (size_t)ctx->n_cg * rntn_units_of(n_steps) * 2 * 64 * 16));
     if (!ctx->xs_inner) TL_HIP(hipMalloc(&ctx->xs_inner, (size_t)slices * HU * sizeof(float)));
     if (!ctx->bp_inner) TL_HIP(hipMalloc(&ctx->bp_inner, (size_t)ctx->n_cg * HU * sizeof(float)));
@@ -867,6 +886,7 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         ctx->split = (2 * ctx->hx_steps + 3) / 4;
     // (TreeRNN: whole waves for either child)
     if (cfg->cell == TL_TREERNN && !bf16 && cfg->scheduler == TL_SCHED_DATAFLOW && (ctx->hx_steps + 1) / 2 <= SPLIT_MAX_S) ctx->split = (ctx->hx_steps + 1) / 2;
+    if (cfg->cell == TL_RNTN) ctx->rntn_steps = 2 * round_up(H, 8) <= 64 ? 2 : 2 * round_up(H, 8) <= 128 ? 4 : 8;
     // RNTN under the data-flow scheduler: the matrix of a hidden unit in a wave's registers, d <= 96
     if (cfg->cell == TL_RNTN && cfg->scheduler == TL_SCHED_DATAFLOW && 2 * round_up(H, 8) <= 32 * ROWS_MAX_STEPS) {
         ctx->rows_steps = (2 * round_up(H, 8) + 31) / 32;
@@ -982,18 +1002,18 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
 
     // every kernel that stages tiles needs more than the default LDS limit
     for (int v = 0; v < 2; ++v) {
-        if ((rc = allow_lds(ready_kernel(cfg->cell, v, 0, bf16))) != TL_OK) return rc;
-        if ((rc = allow_lds(levels_kernel(cfg->cell, v, 0, bf16))) != TL_OK) return rc;
-        for (int epi = 0; epi < 4; ++epi)
+        if ((rc = allow_lds(ready_kernel(ctx, v, 0))) != TL_OK) return rc;
+        if ((rc = allow_lds(levels_kernel(ctx, v, 0))) != TL_OK) return rc;
+        for (const int epi : {(int)EPI_LSTM_LEAF, inner_epi(ctx)})
             if ((rc = allow_lds(static_kernel(epi, v, bf16))) != TL_OK) return rc;
         for (int epi = EPI_BWD_INNER_GATES; epi <= EPI_BWD_LEAF_OPERAND4; ++epi)
             if (epi_is_backward(epi) && (rc = allow_lds(backward_kernel(epi, v))) != TL_OK) return rc;
     }
     int occ = 0;
-    TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void *>(ready_kernel(cfg->cell, true, 0, bf16)),
+    TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, reinterpret_cast<const void *>(ready_kernel(ctx, true, 0)),
                                                         WG_THREADS, TILE_SMEM_BYTES));
     int occ2 = 0;
-    TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ2, reinterpret_cast<const void *>(levels_kernel(cfg->cell, false, 0, bf16)),
+    TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ2, reinterpret_cast<const void *>(levels_kernel(ctx, false, 0)),
                                                         WG_THREADS, TILE_SMEM_BYTES));
     if (occ2 < occ) occ = occ2;
     if (occ < 1) return TL_EHIP;
@@ -1032,13 +1052,13 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
     if (ctx->spw > 0) {
         ctx->ws_lds = ws_lds_bytes(ctx->spw, bf16);
         for (int v = 0; v < 2; ++v) {   // fp32: rows 16-byte aligned / 8-byte aligned
-            if ((rc = allow_lds(ready_kernel(cfg->cell, v != 0, ctx->spw, bf16), ctx->ws_lds)) != TL_OK) return rc;
-            if ((rc = allow_lds(levels_kernel(cfg->cell, v != 0, ctx->spw, bf16), ctx->ws_lds)) != TL_OK) return rc;
+            if ((rc = allow_lds(ready_kernel(ctx, v != 0, ctx->spw), ctx->ws_lds)) != TL_OK) return rc;
+            if ((rc = allow_lds(levels_kernel(ctx, v != 0, ctx->spw), ctx->ws_lds)) != TL_OK) return rc;
         }
         int o1 = 0, o2 = 0;
-        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, reinterpret_cast<const void *>(ready_kernel(cfg->cell, true, ctx->spw, bf16)),
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, reinterpret_cast<const void *>(ready_kernel(ctx, true, ctx->spw)),
                                                             WG_THREADS, ctx->ws_lds));
-        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o2, reinterpret_cast<const void *>(levels_kernel(cfg->cell, true, ctx->spw, bf16)),
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o2, reinterpret_cast<const void *>(levels_kernel(ctx, true, ctx->spw)),
                                                             WG_THREADS, ctx->ws_lds));
         if (o2 < o1) o1 = o2;
         const int want = bf16 ? 2 : 1;   // fp32: the register file of a CU holds one workgroup's weights; bf16: two
@@ -1275,8 +1295,8 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     const bool ready_sched = cfg.scheduler == TL_SCHED_READY || cfg.scheduler == TL_SCHED_READY_PRIORITY;
     size_t flow_lds = 0;
     const fwd_kernel kern = !persistent ? nullptr
-                            : ready_sched ? ready_kernel(cfg.cell, vec4_inner, spw, bf16)
-                            : flow ? flow_kernel(ctx, rnn_groups, &flow_lds) : levels_kernel(cfg.cell, vec4_inner, spw, bf16);
+                            : ready_sched ? ready_kernel(ctx, vec4_inner, spw)
+                            : flow ? flow_kernel(ctx, rnn_groups, &flow_lds) : levels_kernel(ctx, vec4_inner, spw);
     const size_t level_lds = spw > 0 ? ctx->ws_lds : TILE_SMEM_BYTES;
     const size_t kern_lds = flow ? flow_lds : level_lds;
     const bool whole_sets = spw > 0 || flow;          // every workgroup of the kernel is tied to one column group
@@ -1290,7 +1310,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     int grid_l2 = 0;                                  // grid of the level kernel where it is launched beside the data-flow kernel
     if (flow_or_levels) {
         int per_cu = 0;
-        if ((rc = resident_per_cu(ctx, levels_kernel(cfg.cell, vec4_inner, spw, bf16), level_lds, &per_cu)) != TL_OK) return rc;
+        if ((rc = resident_per_cu(ctx, levels_kernel(ctx, vec4_inner, spw), level_lds, &per_cu)) != TL_OK) return rc;
         grid_l2 = spw > 0 ? ctx->ws_grid : ctx->persistent_grid;
         if (per_cu * ctx->n_cu < grid_l2) grid_l2 = per_cu * ctx->n_cu;
         if (spw > 0) grid_l2 = grid_l2 / ctx->n_cg * ctx->n_cg;
@@ -1358,7 +1378,6 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
         f.flow_list = reinterpret_cast<int4 *>(ctx->flow_ws + align256((size_t)ctx->n_cg * ctx->cap_nodes * sizeof(int32_t)));
     }
     const bool vec4_leaf = cfg.embed_dim % 4 == 0;
-    const int inner_epi = cfg.cell == TL_TREELSTM ? EPI_LSTM_INNER : (cfg.cell == TL_TREERNN ? EPI_RNN_INNER : EPI_RNTN_INNER);
     const bool prof = ctx->profiling != 0 && !static_ws;      // (recording may have to create events)
     const int nb_nodes = (n_nodes + 1 + 255) / 256;
     const int nb_big = (n_nodes + 1 + NODE_BLOCK - 1) / NODE_BLOCK;
@@ -1450,7 +1469,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
                 hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, g);
                 g = f;
                 g.pick = 2;
-                hipLaunchKernelGGL(levels_kernel(cfg.cell, vec4_inner, spw, bf16), dim3(grid_l2), dim3(WG_THREADS), level_lds, st, g);
+                hipLaunchKernelGGL(levels_kernel(ctx, vec4_inner, spw), dim3(grid_l2), dim3(WG_THREADS), level_lds, st, g);
             } else {
                 hipLaunchKernelGGL(kern, dim3(grid_l), dim3(WG_THREADS), kern_lds, st, fk);
             }
@@ -1471,7 +1490,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
                     if (rows <= 0 || lo < 0 || lo + rows > f.n_int) return TL_EHIP;
                     const LevelPlan plan = plan_level(rows, cfg.cell == TL_RNTN ? rntn_cap_tiles(f.cap_tiles, f.rntn_units) : f.cap_tiles);
                     const int parts = plan.n_tiles <= f.rntn_units ? RNTN_PARTS : 1;
-                    hipLaunchKernelGGL(static_kernel(inner_epi, vec4_inner, bf16), dim3(plan.n_tiles * ctx->n_cg * parts), dim3(WG_THREADS),
+                    hipLaunchKernelGGL(static_kernel(inner_epi(ctx), vec4_inner, bf16), dim3(plan.n_tiles * ctx->n_cg * parts), dim3(WG_THREADS),
                                        TILE_SMEM_BYTES, st, f, (const int32_t *)(f.level_nodes + lo), rows, plan);
                     if (plan.n_tiles * ctx->n_cg * parts > max_grid) max_grid = plan.n_tiles * ctx->n_cg * parts;
                 }
