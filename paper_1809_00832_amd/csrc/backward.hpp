@@ -262,17 +262,18 @@ __global__ __launch_bounds__(256) void k_rntn_rows(Fwd f, const int32_t *__restr
     }
 }
 
-// acc [2d x (d * 2d + d)] = sum_n a_n^T y_n, colsum [d * 2d + d] = sum_n y_n  ->  d_v [d][2d][2d], d_w [2d][d], d_b [d]
+// acc [2d x (d * 2d + d)] = sum_n a_n^T y_n, colsum [d * 2d + d] = sum_n y_n  ->  d_v [d][2d][2d], d_w [2d][d], d_b [d].  upper: of the symmetric part
+// only p <= q has been computed (else it is not read that way: half of the reads go down columns, d = 128 27 -> 50 us).
 __global__ void k_rntn_unpack(const float *__restrict__ acc, const float *__restrict__ colsum, float *__restrict__ d_v,
-                              float *__restrict__ d_w, float *__restrict__ d_b, int d)
+                              float *__restrict__ d_w, float *__restrict__ d_b, int d, int upper)
 {
     const int D2 = 2 * d, L = d * D2 + d;
     const size_t n_v = (size_t)d * D2 * D2, total = n_v + (size_t)D2 * d + d;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
         if (e < n_v) {
             const int q = (int)(e % D2), p = (int)((e / D2) % D2), k = (int)(e / ((size_t)D2 * D2));
-            // (symmetric: the weight gradient may have computed p <= q alone)
-            d_v[e] = acc[(size_t)min(p, q) * L + (size_t)k * D2 + max(p, q)];
+            const bool turn = upper && p > q;
+            d_v[e] = acc[(size_t)(turn ? q : p) * L + (size_t)k * D2 + (turn ? p : q)];
         } else if (e < n_v + (size_t)D2 * d) {
             const size_t r = e - n_v;
             const int k = (int)(r % d), p = (int)(r / d);

@@ -1817,7 +1817,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,
-                           (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H);
+                           (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H, rntn_one ? 1 : 0);
     if (lstm) {
         const bool v4 = E % 4 == 0 && H % 4 == 0;
         weight_grad(k_weight_grad_wide<1>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
