@@ -106,8 +106,7 @@ template <int SPW> struct WsLoadGeom {
 // The caller guarantees rows < 2^24 and table bytes < 2^32.
 // TAIL: fp32 rows of any length and alignment (a buffer load of 16 bytes needs 4-byte alignment only).  The last request of a row
 // then covers up to three elements of whatever follows it in memory, which are replaced by zeros when they arrive
-// (three selects a request; two 8-byte loads and a block of zeros, for even lengths only, were no faster: 25 trees at H = 150
-// 114 us either way.  Odd lengths went to the streaming cell: 57 trees at H = 301 369 -> 184 us, 20 at H = 37 144 -> 95, TreeRNN 50
+// (three selects a request; two 8-byte loads are no faster at any length.  Odd lengths went to the streaming cell: 57 trees at H = 301 369 -> 184 us, 20 at H = 37 144 -> 95, TreeRNN 50
 // at d = 257 202 -> 125, all under the ready scheduler).
 template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowRequest {
     using G = WsLoadGeom<SPW>;
@@ -385,6 +384,14 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
     float p_cl = 0.f, p_cr = 0.f;
     int p_erow = 0;
     constexpr int FINISH_AFTER = SPW > 1 ? 1 : 0;               // k-step after which the previous block is finished
+    if constexpr (TAIL && !FLOW && SPW <= 8) {
+        // The first block's rows are used here (no instruction), in front of the branch of the threads that park them: moved down into it, its
+        // requests would wait for one another.  (6 chains of 250 leaves, ready / level scheduler: TreeLSTM H = 150 1 426 / 1 369 -> 1 319 /
+        // 1 310 us, TreeRNN 960 / 1 038 -> 974 / 967.  With more k-steps a wave the requests are the longer part: TreeLSTM H = 301, ready
+        // 1 813 -> 1 877, 25 parse trees 126 -> 129.)
+#pragma unroll
+        for (int j = 0; j < NL; ++j) asm volatile("" : "+v"(rows[j].x), "+v"(rows[j].y), "+v"(rows[j].z), "+v"(rows[j].w));
+    }
     for (int rb = 0; rb < nrb; ++rb) {
         float *red = sm.red[rb & 1];
         if constexpr (FLOW) {                               // the rows are there only when their producers have stored them
