@@ -340,17 +340,17 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
  * For callers that must not be held up by tl_backward (the recursion of Section 4.2.2 walked without the host):
  * with on > 0, a tl_backward that needs no contraction for its gate gradients - TreeLSTM from kept gate
  * activations (tl_set_keep_gates), TreeRNN - walks all heights in one persistent kernel that finds the
- * per-height lists on the device (TreeLSTM and TreeRNN with H <= 512: the operand gradient on weight-stationary
- * workgroups).  Nothing is read back and the call returns without waiting; a malformed batch is then reported
+ * per-height lists on the device (H <= 512: the operand gradient on weight-stationary workgroups, but for shallow
+ * batches of more than 2 000 internal nodes at 460 < H < 512).  Nothing is read back and the call returns without waiting; a malformed batch is then reported
  * by tl_status (TL_ESTRUCT, gradients undefined), not by tl_backward.  Same results as the per-height launches
  * (same contractions in the same order).
- * on == 0, the default: tl_backward returns the structure pass's status itself, as described there.  Where the
- * weight-stationary form applies it is the fastest form whatever the shape of the trees (H = 512, 256 trees:
+ * on == 0, the default: tl_backward returns the structure pass's status itself, as described there.  With H <= 512 the
+ * weight-stationary form is mostly the fastest whatever the shape of the trees (H = 512, 256 trees:
  * 1.14 ms per call against 1.19 with launches per height; 64 trees of 1 024 heights: 13.5 against 16.8 ms), so
  * the call enqueues all its work and then waits only for the copy of that status, which sits in front of that
- * kernel.  Otherwise (other hidden sizes: the persistent kernel with the streaming cell is 5 % slower
- * than the launches on shallow batches and faster on deep ones) the call waits for the number of heights and
- * takes the persistent kernel for more than 64 of them, launches per height up to there.
+ * kernel.  Otherwise (H > 512; batches of some thousand internal nodes at sizes above 460 or whose workgroups leave a
+ * seventh of the compute units idle, H = 340 say, and that are no multiple of 128) the call waits for the number of
+ * heights and takes the persistent kernel for more than 64 of them, launches per height up to there.
  * on < 0: always launches per height.  Like the persistent schedulers of tl_forward, the persistent kernels need all their
  * workgroups resident: a caller that cannot keep the device to itself takes on < 0 (a wait that gives up is
  * reported by tl_status, TL_ESTALL).  Recomputed gates always take the launches per height and wait.  TL_RNTN returns the

@@ -1662,15 +1662,19 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // what the structure pass finds wrong with the batch is latched for tl_status, and every kernel below leaves at once.
     const bool kept_or_rnn_v4 = lstm ? kept_v4 : vec4;
     const bool persistent_ok = ctx->bw_grid > 0 && !rntn && (kept || !lstm) && n_int > 0;
-    // H <= 512: the operand gradient on weight-stationary workgroups (row offsets of dG in 32 bits).  Not for many nodes where rows of more
-    // than 2 304 values leave no registers for the general form (H = 500, training step, launches / this: 64 trees 836 / 831 us, 128
-    // 1 127 / 1 181, 256 1 667 / 1 818) or whole sets of workgroups leave a seventh of the CUs idle (H = 340, 256 trees 1 196 / 1 224; 64 666 / 605).
-    // Elsewhere it is the faster one: H = 16, 3 trees 221 / 172; H = 150, 25 373 / 277; H = 301, 57 668 / 537, 256 1 380 / 1 111; H = 450, 128
-    // 1 210 / 1 099; TreeRNN d = 50, 25 trees 265 / 183, d = 450, 250 833 / 714.
+    // H <= 512: the operand gradient on weight-stationary workgroups (row offsets of dG in 32 bits).  In launches per height the streaming
+    // cell is the faster one for many nodes where rows of more than 2 304 values leave no registers for the general form (H = 500, training
+    // step, launches / this: 64 trees 836 / 831 us, 128 1 127 / 1 181, 256 1 667 / 1 818) or whole sets of workgroups leave a seventh of the CUs idle
+    // (H = 340, 256 trees 1 196 / 1 224; 64 666 / 605): such batches wait for the number of heights.  Elsewhere this is the faster one: H = 16, 3 trees
+    // 221 / 172; H = 150, 25 373 / 277; H = 301, 57 668 / 537, 256 1 380 / 1 111; H = 450, 128 1 210 / 1 099; TreeRNN d = 50, 25 trees 265 / 183,
+    // d = 450, 250 833 / 714.
+    // Against the streaming cell in one kernel (deep trees; calls that do not wait) it is so at every size but the first of those two where the trees are
+    // shallow: backward, H = 500, 24 chains of 300 leaves 6 650 / 5 383, 256 parse trees 1 284 / 1 321; H = 340 5 787 / 3 943, 912 / 848.
     const bool exact_rows = kept_or_rnn_v4 && dg_cols == 128 * ctx->bw_spw2;
-    const bool many = !exact_rows && ((ctx->bw_spw2 > 18 && n_int > 2000) || (100 * ctx->bw_ws_grid < 86 * ctx->n_cu && n_int > 4000));
-    const bool ws = persistent_ok && ctx->bw_ws_grid > 0 && !many &&
-                    (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
+    const bool no_room = !exact_rows && ctx->bw_spw2 > 18 && n_int > 2000;
+    const bool ws_fits = persistent_ok && ctx->bw_ws_grid > 0 && (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
+    const bool ws = ws_fits && !no_room && (exact_rows || 100 * ctx->bw_ws_grid >= 86 * ctx->n_cu || n_int <= 4000);    // ... whatever the number of heights
+    const bool ws_walk = ws_fits && !(ctx->async_backward > 0 && no_room && n_nodes < 256ll * n_trees);                 // ... where one kernel walks them
     // RNTN: in one kernel wherever its matrices fit into registers and the rows' addresses into 32 bits; the call returns the structure
     // pass's status in every mode
     const bool rntn_one = rntn && !rntn_rows && n_int > 0;
@@ -1695,7 +1699,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         typedef void (*bwh_kernel)(Fwd, BwdHeights);
         const bwh_kernel k = lstm ? (v4 ? bwh_kernel(k_backward_heights<true, true>) : bwh_kernel(k_backward_heights<true, false>))
                                   : (v4 ? bwh_kernel(k_backward_heights<false, true>) : bwh_kernel(k_backward_heights<false, false>));
-        if (ws) {
+        if (ws_walk) {
             size_t lds = 0;
             const bwh_ws_kernel kw = backward_ws_kernel(lstm, ctx->bw_spw2, exact_rows, &lds);
             hipLaunchKernelGGL(kw, dim3(ctx->bw_ws_grid), dim3(WG_THREADS), lds, st, f, b);

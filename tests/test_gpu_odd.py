@@ -70,3 +70,32 @@ def test_backward_in_one_kernel_at_any_size(cell, H):
         assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
     for k in ref:
         np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+@pytest.mark.parametrize("H,n_trees,leaves,shape", [(500, 40, 50, "random"), (500, 42, 50, "random"), (500, 7, 300, "chain"), (340, 40, 98, "random"), (340, 42, 98, "random"),
+                                                    (340, 14, 300, "chain")])
+def test_backward_of_many_nodes_on_both_sides_of_the_lines(H, n_trees, leaves, shape):
+    """Sizes whose batches of many nodes take launches per height by default (2 000 internal nodes at H = 500, 4 000 at H = 340), deep
+    trees or calls that do not wait one kernel or the other: the same bits of d_x in every mode."""
+    import torch
+    print("case backward lines", H, n_trees, leaves, shape, flush=True)
+    params = synth.make_treelstm_params(830 + H, 50, 21, H, "xavier")
+    trees = synth.make_trees(831, [leaves + t % 3 for t in range(n_trees)], [shape] * n_trees, 50)
+    g_h = torch.from_numpy(np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)).cuda()
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, True)
+        net.forward()
+        out = {}
+        for mode in (-1, 0, 1):
+            binding.tl_set_async_backward(net.ctx, mode)
+            out[mode] = {k: v.cpu().numpy() for k, v in binding.tl_backward(net.ctx, b, g_h, params.embed_dim).items()}
+            assert binding.tl_status(net.ctx) == 0
+    finally:
+        net.close()
+    assert np.abs(out[-1]["d_x"]).max() > 0
+    for mode in (0, 1):
+        assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
+        for k in out[mode]:
+            np.testing.assert_allclose(out[mode][k], out[-1][k], rtol=1e-4, atol=2e-5 * float(np.abs(out[-1][k]).max()), err_msg=k)
