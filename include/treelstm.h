@@ -118,7 +118,8 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  *                        tl_forward_noalloc, batches of 2^24 nodes or 4 GiB of h and more)
  *                        TL_SCHED_LEVEL_DEVICE stands in.  Whole trees are dealt to the sets, so a
  *                        batch of fewer trees than the device has sets leaves sets idle; if its trees
- *                        have 256 nodes or more on average, both this kernel and that of
+ *                        have 256 nodes or more on average (TL_TREERNN in TL_F32 1 024, TL_RNTN 2 048,
+ *                        with hidden > 64 1 536), both this kernel and that of
  *                        TL_SCHED_LEVEL_DEVICE are launched and the device picks one by the width of
  *                        the first frontier (more than 16 ready nodes per tree: bushy trees, level by
  *                        level on all sets; otherwise deep narrow ones, data-flow).  A batch in which
@@ -128,9 +129,11 @@ enum tl_precision { TL_F32 = 0, TL_BF16_IN = 1 };
  * _LEVEL_HOST of one precision agree bit for bit: they sum a node's contraction in the same
  * order.  So does TL_SCHED_DATAFLOW in TL_BF16_IN.  In TL_F32 it agrees with them to rounding (relative
  * 2e-5 in the tests) for TL_TREELSTM and TL_TREERNN, whose internal nodes are summed from split operands (above); for
- * TL_RNTN, split under every scheduler, bit for bit where hidden is a multiple of 16.  A node's bits do not depend on the rest of the
- * batch, with one exception: a TL_F32 TL_TREELSTM batch of 2^24 nodes or 4 GiB of h and more, whose
- * leaves are summed by fp32 instructions (as all leaves are with embed_dim > 1024 or a table of 2^24 words or 4 GiB and
+ * TL_RNTN, split under every scheduler, bit for bit.  A node's bits do not depend on the rest of the
+ * batch, with two exceptions in TL_F32: in TL_TREELSTM and TL_TREERNN under TL_SCHED_DATAFLOW the number, size and shape of the
+ * trees decide whether the internal nodes are summed from split operands or level by level in fp32 (few large trees, see there), as
+ * does a batch of 2^24 nodes or 4 GiB of h and more, of which in TL_TREELSTM under any scheduler the
+ * leaves too are summed by fp32 instructions (as all leaves are with embed_dim > 1024 or a table of 2^24 words or 4 GiB and
  * more). */
 enum tl_scheduler { TL_SCHED_READY = 0, TL_SCHED_LEVEL_DEVICE = 1, TL_SCHED_LEVEL_HOST = 2, TL_SCHED_READY_PRIORITY = 3,
                     TL_SCHED_DATAFLOW = 4 };

@@ -12,8 +12,8 @@
 // embedding rows of any magnitude - and every column of a slice to [2^13, 2^14).  The factor a_q is the fp32 value itself.  A sum
 // that does not come out finite (an infinite operand has no two terms, and scaled sums overflow 2^15 earlier) is taken again in fp32 from the parameters
 // as given.
-// Measured (level kernel, whole forward; before: fp32 instructions, all products): 256 parse trees at d = 64 330 -> 205 us, 150 at d = 96 784 -> 317,
-// 8 at d = 64 190 -> 157; error against 64 bits unchanged (1.4e-6 to 1.7e-6).  What is left is the chain of a frontier (records, rows,
+// Measured (level kernel, whole forward; before: fp32 instructions, all products): 256 parse trees at d = 64 342 -> 205 us, 150 at d = 96 808 -> 288,
+// 8 at d = 64 201 -> 132, 4 at d = 8 101 -> 80; error against 64 bits unchanged (1.4e-6 to 1.7e-6).  What is left is the chain of a frontier (records, rows,
 // parts, barrier), about 12 us each.
 #pragma once
 

@@ -11,8 +11,8 @@
 // Rows that are not written yet show the pattern of cell_ws.hpp (validity carried by the data); no NaN of the parameters or embeddings is
 // taken for it.
 // d <= 96: 21 units of 8 registers at d = 64, 43 at d = 96 (above, the matrix does not fit and the level kernel stands in).
-// Measured (whole forward; level kernel with this cell's products / with fp32 instructions): 256 parse trees at d = 64 229 / 329 -> 108 us, 150
-// at d = 96 317 / 841 -> 160, 8 at d = 64 157 / 209 -> 60, 4 at d = 8 119 / 116 -> 30.  Of the kernel's 88 us at d = 64 the products are 22, the rest
+// Measured (whole forward; level kernel with fp32 instructions / with this cell's products -> this): 256 parse trees at d = 64 342 / 205 -> 105 us, 150 at
+// d = 96 808 / 288 -> 157, 8 at d = 64 201 / 132 -> 52, 4 at d = 8 101 / 80 -> 29.  Of the kernel's 80 us at d = 64 the products are 22, the rest
 // is the chain of its 33 blocks a slot: rows, split, barrier, store.  (Two workgroups per CU at d = 64, for 32 slots: 144 us, spills.)
 #pragma once
 
@@ -36,8 +36,8 @@ template <int NS> struct RowsSmem {
 // and quarter, and read by threads that differ in the row; turned like this both meet all banks.
 __device__ inline int rows_slot(int s, int quarter, int r) { return quarter * 16 + (r ^ ((4 * s + quarter) & 15)); }
 
-// Units of a wave's matrix: TreeRNN one per k-step; RNTN those of cell_rntn.hpp for one k - slice column q = 16 j + lane % 16, j / 2 + 1
-// k-steps - and one for the linear term, whose column s holds k-step s.
+// Units of a wave's matrix: those of cell_rntn.hpp for one k - slice column q = 16 j + lane % 16, j / 2 + 1 k-steps - and one for the linear term,
+// whose column s holds k-step s.
 template <int NS> struct RowsGeom {
     static constexpr int QUAD = NS * (NS + 1), UNITS = QUAD + 1;
     static constexpr int SCALES = 2 * NS + 1;               // [scale][lane % 16]

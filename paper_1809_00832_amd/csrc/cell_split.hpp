@@ -290,7 +290,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 // workgroup takes one column group or two that share the rows they gather, is decided in forward_impl, with the figures.  (NG = 1 / 2 / 4, two a
 // CU, forward: 25 trees at H = 50 30.8 / 35.7 / 40.3 us, at H = 256 43.6 / 44.1 / 47.8, 256 trees there 80.4 / 71.9 / 74.6.  Before, with fp32
 // instructions and lists taken in pieces: 41.7, 49.7, 86.0; with rows of h scaled, split and left in LDS for four waves of 16 units each: 34.6,
-// 56.1, 79.6.)
+// 56.1, 79.6.  One a CU: 29.2, 41.5, 67.2.)
 template <int NG> struct SplitRnnSmem {
     float red[2][4 * NG * 64 * 4];
     float sum_of[NG * HU * 2];

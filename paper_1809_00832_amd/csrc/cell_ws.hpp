@@ -177,12 +177,6 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     }
 };
 
-// Lane J of every group of four lanes, to all four.
-template <int J> __device__ inline float quad_bcast(float x)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), J * 0x55, 0xF, 0xF, true));
-}
-
 // ---- validity carried by the data itself (data-flow scheduler) -----------------------------
 // Before the kernel starts, every row that an internal node will produce (its c row and the h row
 // its parent gathers) is filled with a bit pattern that no cell ever stores: all ones, a NaN (h

@@ -44,8 +44,8 @@ __global__ __launch_bounds__(256) void k_classify(const float *__restrict__ h, c
         float acc[CT];
 #pragma unroll
         for (int c = 0; c < CT; ++c) acc[c] = 0.f;
-        // four 16-byte requests per lane are in flight before the first is used: with only a few
-        // waves per SIMD the kernel is otherwise bound by memory latency, not bandwidth
+        // (four requests of a lane for every 256 values.  They are not in flight together: what is asked about vec4 stands between them, and
+        // the compiled loop waits for one before it makes the next.)
         for (int kb = l16 * 4; kb < Hp; kb += 256) {
             floatx4 x[4];
 #pragma unroll

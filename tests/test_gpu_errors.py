@@ -129,10 +129,8 @@ def test_results_do_not_depend_on_the_schedule(name, precision):
     each in k order, added in quarter order), whatever rows share its tile.  So the schedulers agree bit
     for bit with each other and from run to run, although the ready scheduler forms different tiles every time.
     (Same recursion, different execution order, identical numbers: the claim of Section 5's numerical check.)
-    One exception: in fp32 the data-flow scheduler sums a TreeLSTM's internal nodes from operands split into two fp16
-    terms, and evaluates a piece's last block of up to 8 rows of a TreeRNN with the 4x4x1 matrix instruction, which sums
-    every quarter as four interleaved chains; which nodes those are is fixed by the batch, so it still repeats its own bits
-    from run to run, and agrees with the others to rounding."""
+    One exception: in fp32 the data-flow scheduler sums the internal nodes of a TreeLSTM or a TreeRNN from operands split into two
+    fp16 terms; it still repeats its own bits from run to run, and agrees with the others to rounding."""
     print("case determinism", name, precision, flush=True)
     w = synth.workload(name)
     outs = []

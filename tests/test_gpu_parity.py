@@ -269,7 +269,7 @@ def test_wide_frontiers_at_a_hidden_size_with_uneven_slots():
             check_against_oracle(params, trees, got, ref, "H=440/%s" % sched)
             if first is None:
                 first = got
-            if sched == "dataflow":      # narrow last blocks of its pieces sum in another order (fp32): equal to rounding
+            if sched == "dataflow":      # internal nodes are summed from operands split into two terms (fp32): equal to rounding
                 np.testing.assert_allclose(got["h"], first["h"], rtol=2e-5, atol=2e-6, err_msg=sched)
                 np.testing.assert_allclose(got["c"], first["c"], rtol=2e-5, atol=2e-6, err_msg=sched)
             else:
@@ -461,11 +461,11 @@ def test_two_contexts_on_two_streams_ordered_by_events(sched):
 
 @pytest.mark.parametrize("precision", ["f32", "bf16"])
 def test_dataflow_on_many_batch_shapes(precision):
-    """The data-flow scheduler cuts its private lists into pieces whose composition depends on the shapes of the trees,
-    their number and the hidden size (slots per device, rows per slot, narrow last blocks).  Thirty seeded batches that
+    """The data-flow scheduler works on blocks (bf16: pieces of private lists) whose composition depends on the shapes of the trees,
+    their number and the hidden size (slots per device, rows per slot).  Thirty seeded batches that
     vary all of these - single-node trees, chains, balanced and random trees, one tree or hundreds, nodes renumbered
     inside their trees - against the level scheduler on the same batch: identical bits with bf16 operands and in every
-    run of its own, equal to rounding in fp32 (narrow blocks sum in another order); a sample against the checker."""
+    run of its own, equal to rounding in fp32 (split operands); a sample against the checker."""
     import torch
     prec = binding.TL_F32 if precision == "f32" else binding.TL_BF16_IN
     pick = synth.Stream(977, "batch shapes")

@@ -42,6 +42,19 @@ def test_sizes_at_the_edges_of_the_slices(d, sched):
     check(run(params, trees, sched), oracle.forward_params(params, trees, n_threads=8))
 
 
+@pytest.mark.parametrize("d", [1, 7, 8, 12, 16, 17, 20, 28, 31, 32, 33, 36, 48, 49, 60, 63, 64, 65, 80, 95, 96, 97, 128])
+def test_every_scheduler_gives_the_same_bits(d):
+    """Classes, k-steps of the linear term and parts are added in one order, in tiles of any size and by one wave a unit."""
+    print("case rntn bits", d, flush=True)
+    params = synth.make_rnn_params(705 + d, synth.CELL_RNTN, 60, d, scale=0.7 / d ** 0.5)
+    trees = synth.make_trees(706, [1, 2, 40, 1, 18, 70, 9, 33, 64] * 6, ["random", "chain", "balanced"] * 18, 60)
+    first = run(params, trees, "level_device")
+    for sched in ("dataflow", "ready", "ready_priority", "level_host"):
+        got = run(params, trees, sched)
+        for key in ("h", "h_root"):
+            assert np.array_equal(got[key], first[key]), (sched, key)
+
+
 @pytest.mark.parametrize("sched", ["dataflow", "level_device"])
 def test_rows_and_columns_of_very_different_size(sched):
     """Every embedding row and every column of a slice is scaled for itself: sizes four powers of ten apart side by side (the
@@ -363,3 +376,48 @@ def test_rntn_gradients_of_weights_near_the_largest_number():
     want = ref["d_x"]
     assert np.isfinite(want).all() and np.abs(want).max() > 1e16
     np.testing.assert_allclose(out[0]["d_x"], want, rtol=1e-4, atol=1e-4 * float(np.abs(want).max()))
+
+
+# ---- both cells: after an update --------------------------------------------------------------------------------------
+@pytest.mark.parametrize("cell,d", [("rntn", 20), ("rntn", 64), ("rntn", 72), ("rntn", 100), ("rnn", 24), ("rnn", 150), ("rnn", 272)])
+def test_after_an_update_a_context_is_like_a_fresh_one(cell, d):
+    """tl_sgd_update rebuilds every packed form of the parameters: forward and operand gradient have the bits of a context made from the
+    updated parameters, with steps that change the largest magnitudes of columns by powers of ten."""
+    import torch
+    print("case update", cell, d, flush=True)
+    p = small_params(cell, d, 920 + d)
+    trees = synth.make_trees(921, [30, 8, 1, 21, 2, 60], ["random", "chain", "random", "balanced", "random", "chain"], 60)
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    rand = lambda *shape: torch.randn(*shape, device="cuda", generator=gen)
+    g_h = rand(trees.n_nodes, d)
+
+    def both(net):
+        net.forward()
+        g = binding.tl_backward(net.ctx, net.batch, g_h, d, rntn=cell == "rntn")
+        assert binding.tl_status(net.ctx) == 0
+        return {"h": net.batch["h"].cpu().numpy(), "h_root": net.batch["h_root"].cpu().numpy(), **{k: v.cpu().numpy() for k, v in g.items()}}
+
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        net.load(trees)
+        before = both(net)
+        grads = dict(d_u=rand(2 * d, d) * torch.logspace(-5, 0, d, device="cuda"), d_b=rand(d), d_x=rand(trees.n_nodes, d))
+        if cell == "rntn":
+            grads["d_w_leaf"] = rand(d, 2 * d, 2 * d) * torch.logspace(0, -5, d, device="cuda")[:, None, None]
+        binding.tl_sgd_update(net.ctx, 0.05, net.batch, grads)
+        new = {k: v.cpu().numpy() for k, v in binding.tl_get_params(net.ctx, 60, d, d, cell=p.cell).items()}
+        after = both(net)
+    finally:
+        net.close()
+    assert np.abs(after["h"] - before["h"]).max() > 1e-2
+    q = synth.Params(p.cell, 60, d, d, new["emb"], None, None, new["u"], new["b"], new.get("w_leaf"))
+    fresh = binding.TreeNet(q, scheduler="dataflow")
+    try:
+        fresh.load(trees)
+        want = both(fresh)
+    finally:
+        fresh.close()
+    for key in ("h", "h_root", "d_x"):
+        assert np.array_equal(after[key], want[key]), key
+    for key in ("d_u", "d_b") + (("d_w_leaf",) if cell == "rntn" else ()):      # (sums over the nodes by atomics)
+        np.testing.assert_allclose(after[key], want[key], rtol=1e-4, atol=2e-5 * float(np.abs(want[key]).max()), err_msg=key)
