@@ -21,9 +21,11 @@ PEAK_TFLOPS = {"f32": 157.3, "bf16": 2500.0}      # MI355X dense matrix peaks
 
 
 def matrix_peak(workload, scheduler, precision):
-    """Peak of the unit that the internal-node kernel's products run on: the fp32 TreeLSTM under the data-flow scheduler
-    forms a product of two fp32 numbers as three 16-bit ones (operands as two fp16 terms, fp32 accumulation)."""
-    if precision == "f32" and scheduler == "dataflow" and workload not in ("treernn", "rntn"):
+    """Peak of the unit that the internal-node kernel's products run on.  Where fp32 operands are taken as two fp16 terms
+    (TreeLSTM and TreeRNN under the data-flow scheduler, RNTN under all of them) a product of two fp32 numbers is three
+    16-bit ones with fp32 accumulation.  (The RNTN kernels form the products of p <= q only; its operations are counted
+    as the formula has them, all 4 d^2 pairs.)"""
+    if precision == "f32" and (scheduler == "dataflow" or workload == "rntn"):
         return PEAK_TFLOPS["bf16"] / 3
     return PEAK_TFLOPS[precision]
 HBM_GBS = 8000.0
@@ -229,8 +231,8 @@ def length_sweep(steps, warmup):
 
 
 def backward_stage(w, n_classes, reps=10):
-    """tl_backward on the states of one forward (TreeLSTM, fp32): mean wall time per call (the call waits for the
-    structure pass itself), with its algorithmic flops: 60 H^2 per internal node (gates recomputed, operand
+    """tl_backward on the states of one forward (fp32): mean wall time per call (the call waits for the
+    structure pass itself), with its algorithmic flops; TreeLSTM: 60 H^2 per internal node (gates recomputed, operand
     gradient, weight gradient: 20 H^2 each) and 18 E H per leaf.  With a head (n_classes > 0) also the head's
     backward on its own and one training step without the parameter update: forward, head backward (which
     recomputes the head's forward), tree backward, back to back on one stream."""
@@ -262,7 +264,8 @@ def backward_stage(w, n_classes, reps=10):
         else:                       # RNTN: both contractions run over rows of d * 2d + d values, 2d outputs
             flops = 2.0 * 2.0 * (H * 2 * H + H) * 2 * H * w.trees.n_internal
         out = {"ms": ms, "flops": flops, "tflops": flops / (ms * 1e-3) / 1e12,
-               "frac_mfma_peak": flops / (ms * 1e-3) / 1e12 / PEAK_TFLOPS["f32"]}
+               # (RNTN: both contractions run on the 16-bit unit, as two or three terms)
+               "frac_mfma_peak": flops / (ms * 1e-3) / 1e12 / (PEAK_TFLOPS["bf16"] / 3 if rntn else PEAK_TFLOPS["f32"])}
         # training mode: the forward keeps the gate activations, the backward does not recompute the contraction
         # (40 H^2 flops per internal node and 12 E H per leaf are left)
         if w.params.cell == 0:
@@ -293,7 +296,7 @@ def backward_stage(w, n_classes, reps=10):
                 net.forward()                                          # (the update above has made the kept activations stale)
                 out["ms_without_waiting"] = wall(lambda: binding.tl_backward(net.ctx, b, g_h, E), reps)
                 out["train_step_ms_without_waiting"] = wall(train_step, reps)
-                # and with launches per height whatever the number of heights (the default takes them up to 64 heights)
+                # and with launches per height whatever the size and the number of heights
                 binding.tl_set_async_backward(net.ctx, -1)
                 net.forward()
                 out["ms_launches_per_height"] = wall(lambda: binding.tl_backward(net.ctx, b, g_h, E), reps)
@@ -462,7 +465,7 @@ def main():
     ap.add_argument("--preheat-ms", type=float, default=PREHEAT_MS,
                     help="milliseconds of untimed forwards before the warm-up steps, so that the device has left its idle clock state (0: none)")
     ap.add_argument("--head", type=int, default=5, help="classes of the per-node classifier head timed as an extra stage (0: skip)")
-    ap.add_argument("--backward", action="store_true", help="also time tl_backward on the same batch (TreeLSTM, fp32)")
+    ap.add_argument("--backward", action="store_true", help="also time tl_backward on the same batch (fp32)")
     ap.add_argument("--length-sweep", action="store_true",
                     help="print only the latency of single trees of 2..1024 leaves (balanced, random, chain)")
     ap.add_argument("--graph", action="store_true",

@@ -3,6 +3,8 @@ import os
 import subprocess
 import sys
 
+import pytest
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
@@ -38,3 +40,14 @@ def test_the_line_on_stdout_is_short_and_complete():
     line = json.dumps(bench.headline(out))
     assert len(line) < 3000
     assert set(keys) == set(json.loads(line))
+
+
+@pytest.mark.parametrize("workload, scheduler, precision, terms", [
+    ("throughput", "dataflow", "f32", 3), ("throughput", "level_device", "f32", 0), ("treernn", "dataflow", "f32", 3),
+    ("treernn", "ready", "f32", 0), ("rntn", "dataflow", "f32", 3), ("rntn", "level_host", "f32", 3), ("treernn", "dataflow", "bf16", 1)])
+def test_rate_of_the_unit_that_does_the_products(workload, scheduler, precision, terms):
+    """The rate that a kernel's products are set against is that of the unit they run on: set against the fp32
+    instructions' rate, RNTN came out above it."""
+    import bench
+    want = bench.PEAK_TFLOPS["bf16"] / terms if terms else bench.PEAK_TFLOPS["f32"]
+    assert bench.matrix_peak(workload, scheduler, precision) == want
