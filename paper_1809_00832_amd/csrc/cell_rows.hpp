@@ -12,7 +12,7 @@
 // taken for it.
 // d <= 96: 21 units of 8 registers at d = 64, 43 at d = 96 (above, the matrix does not fit and the level kernel stands in).
 // Measured (whole forward; level kernel with fp32 instructions / with this cell's products -> this): 256 parse trees at d = 64 342 / 205 -> 105 us, 150 at
-// d = 96 808 / 288 -> 157, 8 at d = 64 201 / 132 -> 52, 4 at d = 8 101 / 80 -> 29.  Of the kernel's 80 us at d = 64 the products are 22, the rest
+// d = 96 808 / 288 -> 157, 8 at d = 64 201 / 132 -> 52, 4 at d = 8 101 / 80 -> 29.  Of the kernel's 84 us at d = 64 the products are 22, the rest
 // is the chain of its 33 blocks a slot: rows, split, barrier, store.  (Two workgroups per CU at d = 64, for 32 slots: 144 us, spills.)
 #pragma once
 
