@@ -106,7 +106,10 @@ template <int SPW> struct WsLoadGeom {
 // The caller guarantees rows < 2^24 and table bytes < 2^32.
 // TAIL: fp32 rows of any length and alignment (a buffer load of 16 bytes needs 4-byte alignment only).  The last request of a row
 // then covers up to three elements of whatever follows it in memory, which are replaced by zeros when they arrive
-// (three selects a request; two 8-byte loads are no faster at any length.  Odd lengths went to the streaming cell: 57 trees at H = 301 369 -> 184 us, 20 at H = 37 144 -> 95, TreeRNN 50
+// (three selects a request).  With one k-step a wave a block is the chain of its only request, and what stands behind that counts: there the four elements
+// are asked for one by one, and those behind the row's end beyond the table's, where a buffer load gives zero, so that no select follows.  (6 chains
+// of 250 leaves, level scheduler, before / now: TreeLSTM H = 18 1 063 -> 997 us, H = 21 1 073 -> 998, H = 30 1 033 -> 1 000; TreeRNN d = 22 892 -> 848.  With two
+// k-steps neither that nor two loads of 8 bytes is faster: H = 50 1 049 -> 1 053 and 1 141 -> 1 146 us.)  Odd lengths went to the streaming cell: 57 trees at H = 301 369 -> 184 us, 20 at H = 37 144 -> 95, TreeRNN 50
 // at d = 257 202 -> 125, all under the ready scheduler).
 template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowRequest {
     using G = WsLoadGeom<SPW>;
@@ -116,6 +119,8 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     unsigned lane_off, row_bytes;
     int sub;
     unsigned off[G::NL];
+    static constexpr bool SINGLES = TAIL && SPW == 1;           // an element per load
+    unsigned beyond[3];                                         // SINGLES only: what moves an element behind the row's end out of the table
     int valid;                                                  // TAIL only: elements of this lane's request that belong to the row
     __amdgpu_buffer_rsrc_t rsrc;                                // the table as a raw buffer (device-scope requests)
 
@@ -138,6 +143,8 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
         lane_off = (unsigned)o * (unsigned)sizeof(T);
         row_bytes = (unsigned)stride * (unsigned)sizeof(T);
         valid = stride - o;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) beyond[i] = i + 1 < valid ? 0u : ~3u;
     }
     // byte offsets of the requests of block [row0, row0 + 16): one batch of row-table reads
     __device__ inline void prepare(int row0)
@@ -150,7 +157,14 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     }
     template <bool COH> __device__ inline floatx4 issue(int j) const
     {
-        if constexpr (COH || TAIL) {
+        if constexpr (SINGLES) {
+            floatx4 v;
+            v.x = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)off[j], 0, COH ? 16 : 0));
+            v.y = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)((off[j] + 4u) | beyond[0]), 0, COH ? 16 : 0));
+            v.z = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)((off[j] + 8u) | beyond[1]), 0, COH ? 16 : 0));
+            v.w = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rsrc, (int)((off[j] + 12u) | beyond[2]), 0, COH ? 16 : 0));
+            return v;
+        } else if constexpr (COH || TAIL) {
             // one 16-byte device-scope load (buffer_load_dwordx4 ... sc1)
             typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
             const uintx4 u = __builtin_amdgcn_raw_buffer_load_b128(rsrc, (int)off[j], 0, COH ? 16 : 0);
@@ -167,7 +181,7 @@ template <int SEG, int SPW, typename T = float, bool TAIL = false> struct WsRowR
     // what issue() has brought, without what does not belong to the row
     __device__ inline floatx4 whole(floatx4 v) const
     {
-        if constexpr (TAIL) {
+        if constexpr (TAIL && !SINGLES) {
             static_assert(sizeof(T) == 4, "tail handling is for fp32 rows");
             v.y = valid > 1 ? v.y : 0.f;
             v.z = valid > 2 ? v.z : 0.f;

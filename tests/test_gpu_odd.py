@@ -38,6 +38,13 @@ def test_odd_sizes_give_the_same_bits_everywhere(H, cell):
         assert np.array_equal(got["h"], first), sched
 
 
+@pytest.mark.parametrize("cell", ["lstm", "rnn"])
+@pytest.mark.parametrize("H", [5, 18, 23, 30, 31])
+def test_rows_of_one_k_step(H, cell):
+    """Up to H = 32 the elements of a request are asked for one by one, those behind the row's end beyond the table."""
+    test_odd_sizes_give_the_same_bits_everywhere(H, cell)
+
+
 @pytest.mark.parametrize("cell,H", [("lstm", h) for h in (1, 3, 16, 25, 26, 51, 77, 150, 205, 308, 359, 411, 461, 510)] +
                          [("rnn", h) for h in (1, 50, 127, 129, 255, 301, 450)])
 def test_backward_in_one_kernel_at_any_size(cell, H):
