@@ -329,8 +329,8 @@ int tl_get_params(tl_ctx *ctx, float *u, float *b, float *w_leaf, float *b_leaf,
 /*
  * Training mode of tl_forward (Section 4.2.2: the backward pass of a recursive call looks up the
  * forward values of the same call instance).  With on != 0, every later tl_forward of a TreeLSTM /
- * TL_F32 context also keeps the gate activations of every node (5H floats per node, in a
- * workspace the context owns and grows like its others), and a tl_backward whose h argument and
+ * TL_F32 context also keeps what the gate gradients of every node are made of - products of its gate
+ * activations, tanh(c) and its children's c (8H floats per node, in a workspace the context owns and grows like its others), and a tl_backward whose h argument and
  * n_nodes are those of that forward takes them from there instead of recomputing the forward
  * contraction.  The caller must not change h, c or the batch between the two calls.  Results of
  * tl_forward are unchanged bit for bit; those of tl_backward agree with the recomputing path to
@@ -341,19 +341,15 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
 
 /*
  * For callers that must not be held up by tl_backward (the recursion of Section 4.2.2 walked without the host):
- * with on > 0, a tl_backward that needs no contraction for its gate gradients - TreeLSTM from kept gate
- * activations (tl_set_keep_gates), TreeRNN - walks all heights in one persistent kernel that finds the
- * per-height lists on the device (H <= 512: the operand gradient on weight-stationary workgroups, but for shallow
- * batches of more than 2 000 internal nodes at 460 < H < 512).  Nothing is read back and the call returns without waiting; a malformed batch is then reported
- * by tl_status (TL_ESTRUCT, gradients undefined), not by tl_backward.  Same results as the per-height launches
- * (same contractions in the same order).
- * on == 0, the default: tl_backward returns the structure pass's status itself, as described there.  With H <= 512 the
- * weight-stationary form is mostly the fastest whatever the shape of the trees (H = 512, 256 trees:
- * 1.14 ms per call against 1.19 with launches per height; 64 trees of 1 024 heights: 13.5 against 16.8 ms), so
- * the call enqueues all its work and then waits only for the copy of that status, which sits in front of that
- * kernel.  Otherwise (H > 512; batches of some thousand internal nodes at sizes above 460 or whose workgroups leave a
- * seventh of the compute units idle, H = 340 say, and that are no multiple of 128) the call waits for the number of
- * heights and takes the persistent kernel for more than 64 of them, launches per height up to there.
+ * with on > 0, a tl_backward that needs no contraction for its gate gradients - TreeLSTM from what the forward kept
+ * (tl_set_keep_gates), TreeRNN - walks the trees in one persistent kernel.  Nothing is read back and the call returns without
+ * waiting; a malformed batch is then reported by tl_status (TL_ESTRUCT, gradients undefined), not by tl_backward.  Same
+ * results as the launches per height (same contractions in the same order; with H <= 512 operands as two fp16 terms each in every mode, sums that are
+ * not finite taken again in fp32).
+ * on == 0, the default: tl_backward returns the structure pass's status itself, as described there.  With H <= 512 (and
+ * gates kept, or a TreeRNN) the call enqueues all its work and then waits only for the copy of that status, which sits in front of the
+ * persistent kernel (H = 512, 256 trees: 0.72 ms per call; 64 trees of 1 024 heights: 3.9 ms).  Otherwise it waits for the number of heights
+ * and takes the persistent kernel for more than 64 of them, launches per height up to there.
  * on < 0: always launches per height.  Like the persistent schedulers of tl_forward, the persistent kernels need all their
  * workgroups resident: a caller that cannot keep the device to itself takes on < 0 (a wait that gives up is
  * reported by tl_status, TL_ESTALL).  Recomputed gates always take the launches per height and wait.  TL_RNTN returns the

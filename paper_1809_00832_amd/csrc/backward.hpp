@@ -95,10 +95,9 @@ __device__ inline void bwd_epilogue(const TileSmem &sm, const Fwd &f, const Gemm
     }
 }
 
-// Gate gradients from gate activations that the forward kept (Fwd::gates): the elementwise part
-// of bwd_epilogue without the contraction in front of it.  One thread per (row of `list`, group of
-// V hidden units); same outputs as the EPI_BWD_*_GATES epilogues (dg rows by list position from
-// pos0 on, dc of the children).
+// Gate gradients from what the forward kept (Fwd::keep0, keep1): the elementwise part of bwd_epilogue without the
+// contraction in front of it.  One thread per (row of `list`, group of V hidden units); same outputs as the EPI_BWD_*_GATES
+// epilogues (dg rows by list position from pos0 on, dc of the children).
 // (COH: dh, dc and dg are exchanged between workgroups of one kernel, see the persistent form below.)
 template <bool INNER, int V, bool COH>
 __device__ inline void gate_grad_kept_rows(const Fwd &f, const int32_t *__restrict__ list, int n_rows, int pos0, long long first,
@@ -111,15 +110,11 @@ __device__ inline void gate_grad_kept_rows(const Fwd &f, const int32_t *__restri
         const int row = (int)(e / per_row), col = (int)(e - (long long)row * per_row) * V;
         const int node = list[row];
         const size_t o = (size_t)node * H + col;
-        const float *kept = f.gates + (size_t)node * (5 * H) + col;
         float *dg = f.dg + (size_t)(pos0 + row) * (NG * H) + col;
         int l = 0, r = 0;
         if (INNER) { l = f.left[node]; r = f.right[node]; }
-        float cn[V], dh[V], dc[V], g[5][V], cl[V], cr[V], out[5][V], dcl[V], dcr[V];
-        auto load = [&](float (&dst)[V], const float *src) {
-            if constexpr (V == 4) { const floatx4 t = *reinterpret_cast<const floatx4 *>(src); dst[0] = t.x; dst[1] = t.y; dst[2] = t.z; dst[3] = t.w; }
-            else dst[0] = *src;
-        };
+        float dh[V], dc[V], out[5][V], dcl[V], dcr[V];
+        floatx4 k0[V], k1[V];
         auto load_x = [&](float (&dst)[V], const float *src) {      // what another workgroup may have written
             if constexpr (V == 4) { const floatx4 t = ld_f4<COH>(src); dst[0] = t.x; dst[1] = t.y; dst[2] = t.z; dst[3] = t.w; }
             else dst[0] = ld_f<COH>(src);
@@ -134,30 +129,22 @@ __device__ inline void gate_grad_kept_rows(const Fwd &f, const int32_t *__restri
                 st_f<COH>(dst, src[0]);
             }
         };
-        load(cn, f.c + o); load_x(dh, f.dh + o); load_x(dc, f.dc + o);
-#pragma unroll
-        for (int q = 0; q < NG; ++q) load(g[q], kept + (size_t)q * H);
-        if (INNER) { load(cl, f.c + (size_t)l * H + col); load(cr, f.c + (size_t)r * H + col); }
+        load_x(dh, f.dh + o); load_x(dc, f.dc + o);
 #pragma unroll
         for (int v = 0; v < V; ++v) {
-            const float t = tanh_f(cn[v]);
-            if (INNER) {
-                const float i = g[0][v], fl = g[1][v], fr = g[2][v], og = g[3][v], u = g[4][v];
-                const float dct = dc[v] + dh[v] * og * (1.f - t * t);
-                out[0][v] = dct * u * i * (1.f - i);
-                out[1][v] = dct * cl[v] * fl * (1.f - fl);
-                out[2][v] = dct * cr[v] * fr * (1.f - fr);
-                out[3][v] = dh[v] * t * og * (1.f - og);
-                out[4][v] = dct * i * (1.f - u * u);
-                dcl[v] = dct * fl;
-                dcr[v] = dct * fr;
-            } else {
-                const float i = g[0][v], og = g[1][v], u = g[2][v];
-                const float dct = dc[v] + dh[v] * og * (1.f - t * t);
-                out[0][v] = dct * u * i * (1.f - i);
-                out[1][v] = dh[v] * t * og * (1.f - og);
-                out[2][v] = dct * i * (1.f - u * u);
-            }
+            k0[v] = f.keep0[o + v];
+            if (INNER) k1[v] = f.keep1[o + v];
+        }
+#pragma unroll
+        for (int v = 0; v < V; ++v) {
+            const float dct = __builtin_fmaf(dh[v], k0[v][0], dc[v]), d_i = dct * k0[v][1], d_o = dh[v] * k0[v][2], d_u = dct * k0[v][3];
+            out[0][v] = d_i;
+            out[1][v] = INNER ? dct * k1[v][0] : d_o;
+            out[2][v] = INNER ? dct * k1[v][1] : d_u;
+            out[3][v] = d_o;
+            out[4][v] = d_u;
+            dcl[v] = INNER ? dct * k1[v][2] : 0.f;
+            dcr[v] = INNER ? dct * k1[v][3] : 0.f;
         }
 #pragma unroll
         for (int q = 0; q < NG; ++q) store(dg + (size_t)q * H, out[q]);
@@ -296,7 +283,7 @@ __global__ void k_transpose(const float *__restrict__ in, float *__restrict__ ou
 }
 
 // Weight gradient: out[k][j] += sum_q a_q[k] * dg[q][j] over the n_rows nodes of `list` (dg rows by
-// list position), a_q = [h[left]; h[right]] (SEG 2, L = H) or the embedding row of the leaf's
+// list position; ld > 0: by node, ld values apart), a_q = [h[left]; h[right]] (SEG 2, L = H) or the embedding row of the leaf's
 // word (SEG 1, L = E).  K_out = SEG * L rows, n_cols columns, row-major; `out` is zero beforehand.
 // Two kernels; wg_plan() says which, and why the line lies where it does.  Both cut the node axis into slices (blockIdx.z; the
 // slices' partial tiles are added with atomics: the node axis is long and the output small, so without
@@ -323,7 +310,7 @@ __device__ inline RntnY rntn_y(int j, int d)
 template <int SEG, bool VEC4, bool RNTN = false>
 __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
                                                      const float *__restrict__ table, int L, const float *__restrict__ dg,
-                                                     int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+                                                     int ld, int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
 {
     if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
     __shared__ __align__(16) float as[2][WN_Q][WN_LD];         // two buffers each: a step's operands are parked while the
@@ -360,8 +347,8 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
         }
     };
     auto request = [&](int q0, int node, int s0, int s1) {    // stage 3: operands of nodes q0 .. q0 + 15 into registers
-        const int q = q0 + lq;
         const bool live = node >= 0;
+        const float *dg_row = ld > 0 ? dg + (size_t)max(node, 0) * ld : dg + (size_t)(q0 + lq) * (RNTN ? L : n_cols);
         if constexpr (VEC4) {      // L and n_cols multiples of 4, rows 16-byte aligned: 4 consecutive columns never leave a segment
             const int k = k0 + lk, j = j0 + lk;
             const int seg = (SEG == 2 && k >= L) ? 1 : 0;
@@ -370,12 +357,12 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
             if constexpr (RNTN) {                               // (four neighbouring columns of one k, or of dz)
                 if (live && j < n_cols) {
                     const RntnY y = rntn_y(j, L);
-                    const float *z = dg + (size_t)q * L + y.k;
+                    const float *z = dg_row + y.k;
                     if (y.seg < 0) b = *reinterpret_cast<const floatx4 *>(z);
                     else b = *reinterpret_cast<const floatx4 *>(table + (size_t)(y.seg ? s1 : s0) * L + y.in) * *z;
                 }
             } else if (live && j < n_cols) {
-                b = *reinterpret_cast<const floatx4 *>(dg + (size_t)q * n_cols + j);
+                b = *reinterpret_cast<const floatx4 *>(dg_row + j);
             }
 #pragma unroll
             for (int e = 0; e < 4; ++e) { ra[e] = a[e]; rb[e] = b[e]; }
@@ -389,11 +376,11 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
                     rb[e] = 0.f;
                     if (live && j < n_cols) {
                         const RntnY y = rntn_y(j, L);
-                        rb[e] = dg[(size_t)q * L + y.k];
+                        rb[e] = dg_row[y.k];
                         if (y.seg >= 0) rb[e] *= table[(size_t)(y.seg ? s1 : s0) * L + y.in];
                     }
                 } else {
-                    rb[e] = (live && j < n_cols) ? dg[(size_t)q * n_cols + j] : 0.f;
+                    rb[e] = (live && j < n_cols) ? dg_row[j] : 0.f;
                 }
             }
         }
@@ -513,6 +500,7 @@ inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu)
 struct WgSmem {
     unsigned short a[3][WG_TILE][WG_LD], b[3][WG_TILE][WG_LD];      // [term][column][node]
     int src[2][WG_SRC];                                             // source rows of the slice's next nodes
+    int row[WG_SRC];                                                // ... and their rows of dg
 };
 
 // Eight values as three vectors of bf16 terms, parked as [term][.. 8 neighbours ..].
@@ -535,7 +523,7 @@ __device__ inline void wg_park(unsigned short (*dst)[WG_TILE][WG_LD], int col, i
 // slow: every four nodes are a chain of three loads).
 template <int SEG, bool RNTN>
 __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list, const float *table, int L, const float *dg, int n_cols, int k0,
-                                                        int j0, int q_lo, int q_hi, floatx4 (&acc)[4][4])
+                                                        int j0, int q_lo, int q_hi, int ld, floatx4 (&acc)[4][4])
 {
     const int lane = threadIdx.x & 63, K_out = SEG * L;
 #pragma unroll
@@ -547,6 +535,7 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
         const bool live = q0 + (lane >> 4) < q_hi;
         const int q = live ? q0 + (lane >> 4) : q_hi - 1, node = list[q];
         const int s0 = SEG == 2 ? f.left[node] : f.word[node], s1 = SEG == 2 ? f.right[node] : 0;
+        const float *dg_row = ld > 0 ? dg + (size_t)node * ld : dg + (size_t)q * (RNTN ? L : n_cols);
         float a[4], b[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
@@ -555,10 +544,10 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
             a[t] = live ? table[(size_t)(second ? s1 : s0) * L + (second ? k - L : k)] : 0.f;
             if constexpr (RNTN) {
                 const RntnY y = rntn_y(j, L);
-                b[t] = live ? dg[(size_t)q * L + y.k] : 0.f;
+                b[t] = live ? dg_row[y.k] : 0.f;
                 if (live && y.seg >= 0) b[t] *= table[(size_t)(y.seg ? s1 : s0) * L + y.in];
             } else {
-                b[t] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+                b[t] = live ? dg_row[j] : 0.f;
             }
         }
 #pragma unroll
@@ -570,7 +559,7 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
 
 template <int SEG, bool RNTN = false>
 __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
-                                                             const float *__restrict__ table, int L, const float *__restrict__ dg,
+                                                             const float *__restrict__ table, int L, const float *__restrict__ dg, int ld,
                                                              int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
 {
     __shared__ __align__(16) WgSmem sm;
@@ -610,6 +599,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
     const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
     float bsum = 0.f;
+    const int n_row = ld > 0 ? ld : n_cols;
     auto request = [&](int q0, int chunk) {                   // operands of nodes q0 ... q0 + 31 into registers
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
@@ -622,7 +612,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
                 const int src_y = sm.src[y.seg > 0 ? 1 : 0][min(q, q_hi - 1) - chunk];
                 rb[i] *= live && y.seg >= 0 ? table[(size_t)src_y * L + y.in] : 1.f;
             } else {
-                rb[i] = live ? dg[(size_t)q * n_cols + j] : 0.f;
+                rb[i] = live ? dg[(size_t)sm.row[min(q, q_hi - 1) - chunk] * n_row + j] : 0.f;
             }
         }
     };
@@ -636,6 +626,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
             } else {
                 sm.src[0][i] = f.word[node];
             }
+            sm.row[i] = ld > 0 ? node : chunk + i;
         }
         __syncthreads();
         request(chunk, chunk);
@@ -645,8 +636,10 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
             wg_park(sm.b, col, half, rb);
             wg_park(sm.b, col, half + 8, rb + 8);
             if (with_bias) {
+                float pair[8];                                // (in pairs: an eighth of the roundings of a sum of one by one)
 #pragma unroll
-                for (int i = 0; i < 16; ++i) bsum += rb[i];
+                for (int i = 0; i < 8; ++i) pair[i] = rb[i] + rb[i + 8];
+                bsum += ((pair[0] + pair[4]) + (pair[2] + pair[6])) + ((pair[1] + pair[5]) + (pair[3] + pair[7]));
             }
             __syncthreads();
             if (q0 + WG_Q < end) request(q0 + WG_Q, chunk);
@@ -690,7 +683,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
                 const float m = fabsf(acc[ta][tb][v]);
                 again |= !(m == 0.f || (m >= 0x1p-100f && m < __builtin_inff()));
             }
-    if (__builtin_expect(__ballot(again) != 0ull, 0)) wg_sums_again<SEG, RNTN>(f, list, table, L, dg, n_cols, k0 + wr, j0 + wc, q_lo, q_hi, acc);
+    if (__builtin_expect(__ballot(again) != 0ull, 0)) wg_sums_again<SEG, RNTN>(f, list, table, L, dg, n_cols, k0 + wr, j0 + wc, q_lo, q_hi, ld, acc);
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)
 #pragma unroll
@@ -802,172 +795,6 @@ __global__ __launch_bounds__(WG_THREADS, 2) void k_backward_heights(Fwd f, BwdHe
             __syncthreads();
             if (ng == 4) cell_tile<EPI_BWD_INNER_OPERAND4, VEC4, true>(sm, g, g.bwd, g.dg, count, cg);
             else cell_tile<EPI_BWD_INNER_OPERAND, VEC4, true>(sm, g, g.bwd, g.dg, count, cg);
-        }
-        if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
-    }
-}
-
-// The same walk with the operand gradient on weight-stationary workgroups (TreeLSTM from kept activations, TreeRNN; H <= 512).  U^T is the one matrix that every height multiplies, so a workgroup owns 16 of the 2 H output
-// columns for the whole call and keeps its slice of U^T in registers: the K axis (5 H, padded to 128 SPW2) in four quarters, one per wave,
-// 2 SPW2 k-steps x 4 registers each (160 at H = 512).  The rows of dG are long (5 H floats), so a block of 16 rows
-// passes through LDS in two halves of each wave's quarter: while the matrix instructions of one half run, the other
-// half (or the next block's first) is on its way.  A wave adds up its quarter in k order on one accumulator, the four
-// quarters meet in LDS and are added in wave order: the order of every other data path, so the same bits.  Sets of
-// 2 H / 16 workgroups share the blocks of a height.
-template <int SPW2> struct OperandWsSmem {
-    static constexpr int A_LD = STEP_K * SPW2 + 4;          // LDS row stride of half a quarter of a row, floats
-    float a[4][16 * A_LD];
-    float red[4 * 4 * 64];                                  // [wave][v][lane]
-    int child[2][16];                                       // left / right child of the block's nodes
-    int cmd[8];
-};
-
-// (LSTM = false: TreeRNN, whose rows of dG have H values.)
-// EXACT: rows of exactly 128 SPW2 values, all tables 16-byte aligned.
-template <int SPW2, bool LSTM, bool EXACT>
-__global__ __launch_bounds__(WG_THREADS, 1) void k_backward_heights_ws(Fwd f, BwdHeights b)
-{
-    extern __shared__ __align__(16) unsigned char smem_raw[];
-    using Smem = OperandWsSmem<SPW2>;
-    Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
-    if (decided_to_leave(&sm.cmd[7], threadIdx.x == 0 && batch_rejected(f))) return;
-    constexpr int NLB = SPW2;                               // row loads per lane and half: 16 rows x 4 SPW2 pieces / 64 lanes
-    constexpr int PPR = 4 * SPW2;                           // 16-byte pieces of a row in one half of a wave's quarter
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int H = f.H, K = (LSTM ? 5 : 1) * H;
-    const int n_cg = (2 * H + HU - 1) / HU;
-    const int cg = (int)blockIdx.x % n_cg, slot = (int)blockIdx.x / n_cg, n_slots = (int)gridDim.x / n_cg;
-    const int n_levels = f.ctl->n_levels;
-    const long long first = (long long)blockIdx.x * blockDim.x + tid, stride = (long long)gridDim.x * blockDim.x;
-    WsWeights<1, 2 * SPW2> w;
-    {                                                       // (the grid is a whole number of sets)
-        ws_load(w, b.bwd1, cg, wave, lane);
-        // the weights live in the accumulation registers (a matrix instruction takes its B operand from either file), the
-        // vector registers are for the rows in flight
-#pragma unroll
-        for (int s = 0; s < 2 * SPW2; ++s)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                float x = w.b[s][0][i];
-                asm volatile("" : "+a"(x));                     // no instruction: a register-class constraint only
-                w.b[s][0][i] = x;
-            }
-    }
-    const unsigned row_b = (unsigned)K * 4u;
-    float *a_w = sm.a[wave];
-    const float *a_lane = &a_w[(lane & 15) * Smem::A_LD + (lane >> 4) * 4];
-    const __amdgpu_buffer_rsrc_t rs_dg = buf_of(b.dg_int, (unsigned long long)f.n_int * K * 4);
-    // Rows in flight: one set of registers per half, so that a half is requested a whole block (both halves' matrix
-    // instructions) before it is parked - the latency of a request is longer than one half's matrix instructions.
-    floatx4 rows0[NLB], rows1[NLB];
-    // 16 rows of dG from row `base` on, half `half` of this wave's quarter.  (Rows past the end of the height are other
-    // nodes' rows, past the end of the table they read as zero; every output row depends on its own row only, and the
-    // results of such rows are dropped.)
-    // Piece j * 64 + lane of a half is piece c of row r, PPR pieces to a row: (r, c) is walked along with j instead of
-    // being kept per piece (the registers are needed for the weights and the rows in flight).
-    auto request = [&](floatx4 (&rows)[NLB], int base, int half) {
-        const unsigned off = (unsigned)base * row_b + (unsigned)((wave * 2 + half) * SPW2 * STEP_K) * 4u;
-        int r = lane / PPR, c = lane % PPR;
-#pragma unroll
-        for (int j = 0; j < NLB; ++j) {
-            typedef unsigned int uintx4 __attribute__((ext_vector_type(4)));
-            const uintx4 u = __builtin_amdgcn_raw_buffer_load_b128(rs_dg, (int)(off + (unsigned)r * row_b + (unsigned)c * 16u), 0, 16);
-            rows[j] = floatx4{__uint_as_float(u.x), __uint_as_float(u.y), __uint_as_float(u.z), __uint_as_float(u.w)};
-            c += 64;
-            r += c / PPR;
-            c %= PPR;
-        }
-    };
-    // (What lies behind the end of a row - the next row, or nothing - meets zero weights, but it need not be finite:
-    // zeros stand in for it.)
-    auto park = [&](const floatx4 (&rows)[NLB], int half) __attribute__((always_inline)) {
-        int r = lane / PPR, c = lane % PPR;
-        const int left = K - (wave * 2 + half) * SPW2 * STEP_K;
-#pragma unroll
-        for (int j = 0; j < NLB; ++j) {
-            float *dst = &a_w[r * Smem::A_LD + c * 4];
-            if (EXACT || left >= SPW2 * STEP_K || c * 4 + 4 <= left) {
-                *reinterpret_cast<floatx4 *>(dst) = rows[j];
-            } else {
-                dst[0] = c * 4 < left ? rows[j].x : 0.f;
-                dst[1] = c * 4 + 1 < left ? rows[j].y : 0.f;
-                dst[2] = c * 4 + 2 < left ? rows[j].z : 0.f;
-                dst[3] = 0.f;
-            }
-            c += 64;
-            r += c / PPR;
-            c %= PPR;
-        }
-    };
-    unsigned epoch = 0, unused = 0;
-    Fwd g = f;
-    g.dg = b.dg_int;
-#pragma unroll 1
-    for (int lvl = n_levels - 1; lvl >= 1; --lvl) {
-        const int lo = f.level_off[lvl], n_rows = f.level_off[lvl + 1] - lo;
-        const int32_t *list = f.level_nodes + lo;
-        if constexpr (LSTM) {
-            if (EXACT || b.kept_v4) gate_grad_kept_rows<true, 4, true>(g, list, n_rows, lo, first, stride);
-            else gate_grad_kept_rows<true, 1, true>(g, list, n_rows, lo, first, stride);
-        } else {
-            if (EXACT || b.kept_v4) rnn_gate_grad_rows<4, true>(g, list, n_rows, lo, first, stride);
-            else rnn_gate_grad_rows<1, true>(g, list, n_rows, lo, first, stride);
-        }
-        if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
-        const int n_blocks = (n_rows + 15) >> 4;
-        if (slot < n_blocks) {
-            request(rows0, lo + slot * 16, 0);
-            request(rows1, lo + slot * 16, 1);
-        }
-#pragma unroll 1
-        for (int blk = slot; blk < n_blocks; blk += n_slots) {
-            const int cnt = min(16, n_rows - blk * 16);
-            if (tid < 32) {                                 // the children that this block's results are added to
-                const int r = tid & 15;
-                const int node = r < cnt ? list[blk * 16 + r] : -1;
-                sm.child[tid >> 4][r] = node < 0 ? -1 : (tid < 16 ? f.left[node] : f.right[node]);
-            }
-            floatx4 acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int half = 0; half < 2; ++half) {
-                // (the last block asks for rows that nobody uses: past the end of the table they read as zero)
-                if (half == 0) {
-                    park(rows0, 0);
-                    request(rows0, lo + (blk + n_slots) * 16, 0);
-                } else {
-                    park(rows1, 1);
-                    request(rows1, lo + (blk + n_slots) * 16, 1);
-                }
-                __builtin_amdgcn_sched_barrier(0);
-                floatx4 av_next = *reinterpret_cast<const floatx4 *>(a_lane);
-#pragma unroll
-                for (int s = 0; s < SPW2; ++s) {
-                    const floatx4 av = av_next;
-                    if (s + 1 < SPW2) av_next = *reinterpret_cast<const floatx4 *>(a_lane + (s + 1) * STEP_K);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(av[i], w.b[half * SPW2 + s][0][i], acc, 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) sm.red[(wave * 4 + v) * 64 + lane] = acc[v];
-            __syncthreads();
-            {
-                // wave w finishes accumulator row w of every group of four rows: the quarters in wave order
-                float sum = sm.red[(0 * 4 + wave) * 64 + lane];
-                sum += sm.red[(1 * 4 + wave) * 64 + lane];
-                sum += sm.red[(2 * 4 + wave) * 64 + lane];
-                sum += sm.red[(3 * 4 + wave) * 64 + lane];
-                const int row = (lane >> 4) * 4 + wave, oc = cg * HU + (lane & 15);
-                const int child = sm.child[oc < H ? 0 : 1][row];
-                if (child >= 0 && oc < 2 * H) {
-                    // (one contribution per element, from the node's only parent: an addition at the memory side gives the bits
-                    // of load, add, store, and the wave does not wait for a load behind the rows it has requested ahead)
-                    float *p = f.dh + (size_t)child * H + (oc < H ? oc : oc - H);
-                    (void)add_dev(p, sum);
-                }
-            }
-            __syncthreads();                                // red and child are free again
         }
         if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
     }

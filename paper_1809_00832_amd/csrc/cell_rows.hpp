@@ -108,11 +108,6 @@ __global__ __launch_bounds__(256) void k_pack_rntn(const float *__restrict__ s, 
     if (item < n_operand) pack_rntn_operand(s, operand.wp, operand.scale, d, Lp, operand.steps, item, lane);
 }
 
-template <int CTRL> __device__ inline float dpp(float x)
-{
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
-}
-constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
 template <int N> __device__ inline float from_lane_above(float x) { return dpp<0x100 + N>(x); }      // row_shl: lane i of 16 reads lane i + N
 
 template <int NS>

@@ -258,7 +258,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 #pragma unroll
                     for (int g = 0; g < NG; ++g) gate[g] += sm.sum_of[(g * HU + (lane & 15)) * 2 + 1];
                 }
-                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, e.x, hu), H);
+                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, e.x, hu));
             }
             const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
             if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)e.x * hx_row_b + split_word_off(hu), __uint_as_float(word));
@@ -577,7 +577,7 @@ __device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int
         }
         const bool here = lo + b * 16 + fin_row < hi, ok = here && hu_ok;
         float cc, hh;
-        lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, KEEP ? (ok ? f.gates + (size_t)node * (5 * H) + hu : f.sink + (lane & 15)) : nullptr, H);
+        lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, KEEP ? Keep{ok ? f.keep0 + ((size_t)node * H + hu) : f.keep0 - HU + (lane & 15), nullptr} : Keep());
         const unsigned o = ok ? __umul24((unsigned)node, row_b) + hu_b : ~0u;
         const unsigned word = split_word(hu_ok ? hh * SPLIT_H_SCALE : 0.f, hu);
         buf_st_f<false>(rs_c, o, cc);

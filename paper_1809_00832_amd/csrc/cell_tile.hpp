@@ -84,40 +84,43 @@ __device__ inline float tanh_f(float x)
 // calls these same functions, and the multiply-adds are spelled out as fused operations (left to
 // the compiler, the choice of which product to fuse differs between call sites), so that a
 // node's h and c do not depend on the path that made them.
-// `keep`, when not null, receives the gate activations for the backward pass (Section 4.2.2:
-// forward values are kept per call instance): i, o, u of a leaf at keep[0], keep[H], keep[2H];
-// i, f_l, f_r, o, u of an internal node at keep[0] .. keep[4H].
-__device__ inline void lstm_leaf_out(float gi, float go, float gu, float *c, float *h, float *keep = nullptr, int H = 0)
+// `keep`, when it points somewhere, receives what the backward pass makes the node's gate gradients of (Section 4.2.2: forward values
+// are kept per call instance), as two aligned vectors per hidden unit.  With dct = dc + dh A:
+//   k0 = { A = o (1 - tanh(c)^2), u i (1 - i), tanh(c) o (1 - o), i (1 - u^2) }     gradients of i, o, u are dct k0[1], dh k0[2], dct k0[3]
+//   k1 = { c_l f_l (1 - f_l), c_r f_r (1 - f_r), f_l, f_r }                         of f_l, f_r dct k1[0], dct k1[1]; the children's dc are dct k1[2], dct k1[3]
+// (k1 of internal nodes only).  Two stores here and two loads there in the place of five and nine.
+struct Keep {
+    floatx4 *k0 = nullptr, *k1 = nullptr;
+};
+__device__ inline void keep_leaf(floatx4 *k0, float i, float og, float u, float t)
+{
+    *k0 = floatx4{og * __builtin_fmaf(-t, t, 1.f), u * i * (1.f - i), t * og * (1.f - og), i * __builtin_fmaf(-u, u, 1.f)};
+}
+__device__ inline void lstm_leaf_out(float gi, float go, float gu, float *c, float *h, Keep keep = Keep())
 {
     const float i = sigmoid_f(gi), og = sigmoid_f(go), u = tanh_f(gu);
-    const float cc = i * u;
+    const float cc = i * u, t = tanh_f(cc);
     *c = cc;
-    *h = og * tanh_f(cc);
-    if (keep) {
-        keep[0] = i;
-        keep[H] = og;
-        keep[2 * H] = u;
-    }
+    *h = og * t;
+    if (keep.k0) keep_leaf(keep.k0, i, og, u, t);
 }
 __device__ inline void lstm_inner_out(float gi, float gfl, float gfr, float go, float gu, float cl, float cr, float *c,
-                                      float *h, float *keep = nullptr, int H = 0)
+                                      float *h, Keep keep = Keep())
 {
     const float i = sigmoid_f(gi), fl = sigmoid_f(gfl), fr = sigmoid_f(gfr), og = sigmoid_f(go), u = tanh_f(gu);
-    const float cc = __builtin_fmaf(fr, cr, __builtin_fmaf(fl, cl, i * u));
+    const float cc = __builtin_fmaf(fr, cr, __builtin_fmaf(fl, cl, i * u)), t = tanh_f(cc);
     *c = cc;
-    *h = og * tanh_f(cc);
-    if (keep) {
-        keep[0] = i;
-        keep[H] = fl;
-        keep[2 * H] = fr;
-        keep[3 * H] = og;
-        keep[4 * H] = u;
+    *h = og * t;
+    if (keep.k0) {
+        keep_leaf(keep.k0, i, og, u, t);
+        *keep.k1 = floatx4{cl * fl * (1.f - fl), cr * fr * (1.f - fr), fl, fr};
     }
 }
-// Where a node's kept gate activations start for hidden unit hu; null when they are not kept.
-__device__ inline float *kept_gates(const Fwd &f, int node, int hu)
+// Where a node's kept values are for hidden unit hu; nowhere when they are not kept.
+__device__ inline Keep kept_gates(const Fwd &f, int node, int hu)
 {
-    return f.gates ? f.gates + (size_t)node * (5 * f.H) + hu : nullptr;
+    const size_t at = (size_t)node * f.H + hu;
+    return f.keep0 ? Keep{f.keep0 + at, f.keep1 + at} : Keep();
 }
 
 // Fills node/src0/src1 of one row.  Rows without a node are marked unused.  Caller synchronises.
@@ -218,7 +221,7 @@ __device__ inline void tile_epilogue(const TileSmem &sm, const Fwd &f, const Gem
         const size_t o = (size_t)node * H + hu;
         if (EPI == EPI_LSTM_LEAF) {
             float cc, hh;
-            lstm_leaf_out(acc[0][v] + bias[0], acc[1][v] + bias[1], acc[2][v] + bias[2], &cc, &hh, kept_gates(f, node, hu), H);
+            lstm_leaf_out(acc[0][v] + bias[0], acc[1][v] + bias[1], acc[2][v] + bias[2], &cc, &hh, kept_gates(f, node, hu));
             st_f<COH>(f.c + o, cc);
             st_f<COH>(f.h + o, hh);
             if (f.hb) st_h<COH>(f.hb + (size_t)node * f.hs + hu, bf16_bits(hh));
@@ -228,7 +231,7 @@ __device__ inline void tile_epilogue(const TileSmem &sm, const Fwd &f, const Gem
             const float cr = ld_f<COH>(f.c + (size_t)sm.src1[row] * H + hu);
             float cc, hh;
             lstm_inner_out(acc[0][v] + bias[0], acc[1][v] + bias[1], acc[2][v] + bias[2], acc[3][v] + bias[3],
-                           acc[4][v] + bias[4], cl, cr, &cc, &hh, kept_gates(f, node, hu), H);
+                           acc[4][v] + bias[4], cl, cr, &cc, &hh, kept_gates(f, node, hu));
             st_f<COH>(f.c + o, cc);
             st_f<COH>(f.h + o, hh);
             if (f.hb) st_h<COH>(f.hb + (size_t)node * f.hs + hu, bf16_bits(hh));

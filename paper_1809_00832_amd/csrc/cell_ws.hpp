@@ -363,7 +363,7 @@ __device__ inline void ws_tile(WsSmemT<SPW> &sm, const Fwd &f, const Gemm &gm, c
             const unsigned o = (unsigned)enode * row_b + hu_b;
             if constexpr (EPI == EPI_LSTM_INNER) {
                 float cc, hh;
-                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, kept_gates(f, enode, hu), H);
+                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[NG - 1], cl, cr, &cc, &hh, kept_gates(f, enode, hu));
                 buf_st_f<COH>(rs_c, o, cc);
                 buf_st_f<COH>(rs_h, o, hh);
             } else if constexpr (EPI == EPI_TD_CHILD) {     // gates i, f, o, u of an LSTM step along the edge (as in cell_tile.hpp)

@@ -45,7 +45,8 @@ struct alignas(LINE) Ctl {
     int reached;                  // nodes reached bottom-up from the leaves
     int tiles_formed;             // ready scheduler: tiles of ready nodes formed
     int n_roots;                  // nodes without a parent found by the structure pass (one per tree in a valid batch)
-    int pad0[LINE / 4 - 8];
+    int n_int_seen;               // internal nodes listed (backward pass)
+    int pad0[LINE / 4 - 9];
     Line abort;                   // set when a waiting workgroup gives up; everybody leaves
     Line q_head;                  // ready-queue entries consumed into tiles
     Line q_tail;                  // ready-queue entries reserved by producers
@@ -112,6 +113,13 @@ struct SplitGemm {
 };
 constexpr float SPLIT_H_SCALE = 16384.f;    // power of two by which h (|h| <= 1) is scaled before it is split
 
+// Backward pass: what the structure pass leaves there beside the forward's.  (Not in Fwd: every launch copies its arguments.)
+struct SchedPlaces {
+    int4 *trees;                // per slot its trees [from, to), its number of internal nodes and the position of the first one
+    int4 *children;             // per entry of the schedule the places of its children
+    int2 *of;                   // where a node's gate gradients lie (back_flow.hpp): {position of its block's first node, nodes of the block | its row << 8}, leaves {-1, 0}
+};
+
 // Everything a forward kernel needs, passed by value.
 struct Fwd {
     int n_trees, n_nodes, n_leaf, n_int;
@@ -131,7 +139,6 @@ struct Fwd {
     unsigned *hx;               // split copy of h that the split cell gathers from (cell_split.hpp), hx_steps lines of 128 bytes a row; else null
     int hx_steps;
     float *hx_back;             // TreeRNN: what sums over a row of the split copy are multiplied by (its leaves' rows have scales of their own)
-    float *sink;                // [5H + 16]: where lanes without a node put the gate activations they do not have
     // workspace
     int32_t *parent, *pending, *leaf_list, *root_ws;
     int32_t *height, *arrive, *level_cnt, *level_off, *level_fill, *level_nodes;
@@ -146,7 +153,8 @@ struct Fwd {
     const float *zeros;               // 256 bytes of zeros (stand-in source for padded operand granules)
     Ctl *ctl;
     // backward pass only (null / zero in a forward)
-    float *gates;                     // null, or [n_nodes x 5H]: gate activations kept by the forward for the backward pass
+    floatx4 *keep0, *keep1;           // null, or [n_nodes x H] each: what the forward keeps for the backward pass (Keep, cell_tile.hpp); in front of keep0 [16]
+                                      // for lanes that have nothing to keep
     float *dh, *dc;                   // [n_nodes x H]: gradient arriving at each node's h and c
     float *dg;                        // rows of gate-pre-activation gradients: [n_int x 5H] or [n_leaf x 3H], by list position
     float *d_x;                       // [n_nodes x E] out: gradient of the embedding row each leaf used
@@ -250,6 +258,13 @@ template <bool COH> __device__ inline void buf_st_h(__amdgpu_buffer_rsrc_t r, un
 {
     __builtin_amdgcn_raw_buffer_store_b16(v, r, (int)off, 0, COH ? 16 : 0);
 }
+
+// A value from another lane of the same 16, by the data-parallel pattern CTRL.
+template <int CTRL> __device__ inline float dpp(float x)
+{
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xF, 0xF, true));
+}
+constexpr int DPP_XOR1 = 0xB1, DPP_XOR2 = 0x4E, DPP_HALF_MIRROR = 0x141, DPP_MIRROR = 0x140;
 
 // ---- two fp16 terms of a value, and the split copy of h (cell_split.hpp) ------------------
 // hi | lo << 16 of a value that has been scaled already.  (A NaN is stored as the one without payload: converted as it is, a

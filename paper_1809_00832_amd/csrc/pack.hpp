@@ -197,12 +197,96 @@ __device__ inline void pack_split_block(const SplitPackList &pl, int b)
     }
 }
 
-// Both, side by side: the first n_split workgroups pack the split weights, the others the rest (one launch after an update; the
-// split weights' workgroups are a chain of loads, maximum and stores, 7 to 12 us, and few).
-__global__ __launch_bounds__(256) void k_repack(PackList pl, SplitPackList sl, int n_split)
+// The two fp16 terms of a matrix whose rows are the columns of a contraction (the transposed matrices of the backward pass, read along their
+// rows): [column group][k-step of 32][side][hi, lo][lane][8].  Column (side, c) is row side * n + c of w, NG * K values; k-step s holds values
+// 32 (s / NG) ... + 31 of the (s % NG)th K of them.  Scales as above, for an operand whose own scale is not known here.  One workgroup
+// per column group and side, 16 threads a column.
+constexpr int ROWS_PACK_T = 20;     // n_steps <= 4 * ROWS_PACK_T
+struct RowsPackJob {
+    const float *w;
+    _Float16 *wp;
+    float *scale;
+    int NG, K, n, sides, n_steps, n_cg;
+};
+struct RowsPackList {
+    RowsPackJob job[2];
+    int n, blocks;
+};
+__device__ inline void pack_rows_block(const RowsPackList &pl, int b)
 {
-    if ((int)blockIdx.x < n_split) pack_split_block(sl, blockIdx.x);
-    else pack_many(pl, (size_t)(blockIdx.x - n_split) * blockDim.x + threadIdx.x, (size_t)(gridDim.x - n_split) * blockDim.x);
+    int a = 0;
+    while (a + 1 < pl.n && b >= pl.job[a].n_cg * pl.job[a].sides) {
+        b -= pl.job[a].n_cg * pl.job[a].sides;
+        a += 1;
+    }
+    const RowsPackJob &j = pl.job[a];
+    if (b >= j.n_cg * j.sides) return;
+    const int side = b % j.sides, cg = b / j.sides, col = threadIdx.x >> 4, t16 = threadIdx.x & 15, c = cg * HU + col, len = j.NG * j.K;
+    const bool here = c < j.n;
+    const float *w = j.w + (size_t)(side * j.n + (here ? c : 0)) * len;
+    // thread: every sixteenth piece of eight consecutive values of its column, all requested together
+    float x[ROWS_PACK_T][8];
+    const bool quad = (j.K & 3) == 0 && ((uintptr_t)j.w & 15) == 0;
+#pragma unroll
+    for (int t = 0; t < ROWS_PACK_T; ++t) {
+        const int i = t16 + 16 * t, s = i >> 2, k0 = s / j.NG * 32 + 8 * (i & 3);
+        const float *src = w + (size_t)(s % j.NG) * j.K + k0;
+        const bool piece = here && i < j.n_steps * 4;
+        if (quad) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const floatx4 v = piece && k0 + 4 * h < j.K ? *reinterpret_cast<const floatx4 *>(src + 4 * h) : floatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int q = 0; q < 4; ++q) x[t][4 * h + q] = v[q];
+            }
+        } else {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) x[t][q] = piece && k0 + q < j.K ? src[q] : 0.f;
+        }
+    }
+    unsigned m = 0u;                                            // largest finite magnitude, as bits
+    int inf = 0;
+#pragma unroll
+    for (int t = 0; t < ROWS_PACK_T; ++t)
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const unsigned v = __float_as_uint(x[t][q]) & 0x7FFFFFFFu;
+            if (v < 0x7F800000u) m = max(m, v);
+            else if (v == 0x7F800000u) inf = 1;
+        }
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+        m = max(m, (unsigned)__shfl_xor((int)m, o));
+        inf |= __shfl_xor(inf, o);
+    }
+    const int e = min(13 - ((int)(m >> 23) - 127), 100);
+    if (t16 == 0) j.scale[(cg * j.sides + side) * HU + col] = inf ? __uint_as_float(0x7FC00000u) : here ? ldexpf(1.f, -e) : 0.f;
+    typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+#pragma unroll
+    for (int t = 0; t < ROWS_PACK_T; ++t) {
+        const int i = t16 + 16 * t, s = i >> 2;
+        if (i >= j.n_steps * 4) continue;
+        half8 hi, lo;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const float v = ldexpf(x[t][q], e);
+            hi[q] = (_Float16)v;
+            lo[q] = (_Float16)(v - (float)hi[q]);
+        }
+        half8 *dst = reinterpret_cast<half8 *>(j.wp) + (((size_t)cg * j.n_steps + s) * j.sides + side) * 2 * 64 + (i & 3) * 16 + col;
+        dst[0] = hi;
+        dst[64] = lo;
+    }
+}
+
+// All of them, side by side: the first n_split workgroups pack the split weights, the next ones those of the backward pass, the others the rest (one launch
+// after an update; the split weights' workgroups are a chain of loads, maximum and stores, 7 to 12 us, and few).
+__global__ __launch_bounds__(256) void k_repack(PackList pl, SplitPackList sl, RowsPackList rl, int n_split)
+{
+    const int b = (int)blockIdx.x - n_split, rest = b - rl.blocks;
+    if (b < 0) pack_split_block(sl, blockIdx.x);
+    else if (rest < 0) pack_rows_block(rl, b);
+    else pack_many(pl, (size_t)rest * blockDim.x + threadIdx.x, (size_t)(gridDim.x - n_split - rl.blocks) * blockDim.x);
 }
 
 // bf16 copy of a row-major table with rows padded to Ls elements (pads zero)

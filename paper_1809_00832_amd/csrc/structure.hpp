@@ -134,7 +134,8 @@ __global__ void k_reset(Fwd f, int with_levels)
 // One thread per node: checks, parent scatter, leaf list, counters of unfinished children.
 // Leaves are evaluated by a kernel of their own before any internal node, so pending[] counts
 // internal children only, and an internal node whose children are both leaves starts ready.
-__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f)
+// int_list: null, or (backward pass) receives the internal nodes, in no particular order.
+__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f, int32_t *int_list)
 {
     __shared__ int s_cnt[APPEND_SCRATCH];
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -172,6 +173,11 @@ __global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f)
     if (is_leaf && leaf_slot < f.n_leaf) f.leaf_list[leaf_slot] = n;
     const int seed_slot = block_append(&ctl->q_tail.v, is_seed, s_cnt);
     if (is_seed && seed_slot < f.n_int) qrec_store<false>(&f.q_rec[seed_slot], n, l, r);
+    if (int_list) {
+        const bool inner = n < f.n_nodes && l >= 0;
+        const int slot = block_append(&ctl->n_int_seen, inner, s_cnt);
+        if (inner && slot < f.n_int) int_list[slot] = n;
+    }
 }
 
 // One thread per node: the node nobody points to is its tree's root; there must be exactly one.
@@ -269,7 +275,7 @@ __global__ __launch_bounds__(NODE_BLOCK) void k_seed_place(Fwd f)
 __global__ void k_climb(Fwd f)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (batch_rejected(f) || i >= f.n_leaf) return;
+    if (batch_rejected(f) || internal_kernel_skipped(f) || i >= f.n_leaf) return;
     int n = f.leaf_list[i];
     int hcur = 0;
     for (int guard = 0; guard < f.n_nodes; ++guard) {
@@ -293,7 +299,7 @@ __global__ void k_level_hist(Fwd f)
     __shared__ int s_hist[HIST_BINS];
     __shared__ int s_max;
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (batch_rejected(f)) return;
+    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
     for (int b = threadIdx.x; b < HIST_BINS; b += blockDim.x) s_hist[b] = 0;
     if (threadIdx.x == 0) s_max = 0;
     __syncthreads();
@@ -323,6 +329,7 @@ __global__ void k_scan_levels(Fwd f)
         }
         return;
     }
+    if (internal_kernel_skipped(f)) return;
     const int n_levels = ctl->max_height + 1;
     if (tid == 0) s_carry = 0;
     __syncthreads();
@@ -352,12 +359,13 @@ __global__ void k_scan_levels(Fwd f)
 }
 
 // One thread per node: append every reached internal node to the list of its height.
-__global__ void k_fill_levels(Fwd f)
+// place_of: null, or (backward pass) see SchedPlaces.
+__global__ void k_fill_levels(Fwd f, int2 *place_of)
 {
     __shared__ int s_hist[HIST_BINS];
     __shared__ int s_base[HIST_BINS];
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (batch_rejected(f)) return;
+    if (batch_rejected(f) || internal_kernel_skipped(f)) return;
     for (int b = threadIdx.x; b < HIST_BINS; b += blockDim.x) s_hist[b] = 0;
     __syncthreads();
     const bool mine = n < f.n_nodes && f.left[n] >= 0 && f.arrive[n] == 2;
@@ -373,6 +381,10 @@ __global__ void k_fill_levels(Fwd f)
     if (mine) {
         const int slot = f.level_off[hgt] + rank + (hgt < HIST_BINS ? s_base[hgt] : 0);
         if (slot < f.n_int) f.level_nodes[slot] = n;
+        if (place_of) {
+            const int lo = f.level_off[hgt], block = (slot - lo) & ~15;
+            place_of[n] = int2{lo + block, min(16, f.level_off[hgt + 1] - lo - block) | (slot - lo - block) << 8};
+        }
     }
 }
 
@@ -487,8 +499,8 @@ __device__ inline void flow_cut(const Fwd &f, int slot, int n_slots, int *t_lo, 
     *n_hi = __builtin_amdgcn_readlane(at_hi, 32);
 }
 
-template <bool IN_LDS>
-__device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int t_hi, int nb, int ne, unsigned char *lds)
+template <bool IN_LDS, bool PLACES>
+__device__ inline void flow_schedule_slot(const Fwd &f, const SchedPlaces &sp, int slot, int t_lo, int t_hi, int nb, int ne, unsigned char *lds)
 {
     const int tid = threadIdx.x, lane = tid & 63, n = ne - nb, first = (nb - t_lo) / 2;
     const int cap = (n - (t_hi - t_lo)) / 2;      // internal nodes (full binary trees)
@@ -632,9 +644,25 @@ __device__ inline void flow_schedule_slot(const Fwd &f, int slot, int t_lo, int 
         const int up = f.parent[node], tree = f.flow_roots ? ld_dev(&f.depth_root[node]) : 0;
         if (f.flow_roots && here && up < 0) w |= tree + 1;
         out[i] = int4{here ? node : -1, f.left[node], f.right[node], w};
+        if (PLACES && here) sp.of[node] = int2{first + st, (end - st) | r << 8};
+    }
+    if constexpr (!PLACES) return;
+    // (leaves' places are written by other workgroups)
+    wait_mem();
+    __syncthreads();
+    auto place = [&](int n) {
+        if (f.left[n] < 0) return pack2(0xFFFFFFFFu, 0u);
+        return ld_dev(reinterpret_cast<const unsigned long long *>(sp.of + n));
+    };
+    int4 *places = sp.children + (size_t)first * 16;
+#pragma unroll 4
+    for (int i = tid; i < blocks * 16; i += WG_THREADS) {
+        const unsigned long long l = place(out[i].y), r = place(out[i].z);      // (this thread's own entry)
+        places[i] = int4{(int)(unsigned)l, (int)(unsigned)(l >> 32), (int)(unsigned)r, (int)(unsigned)(r >> 32)};
     }
 }
-__device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds, size_t lds_bytes)
+template <bool PLACES = false>
+__device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds, size_t lds_bytes, const SchedPlaces &sp = SchedPlaces{})
 {
     // (workgroups of other slots may latch an error meanwhile)
     int *s_ctl = reinterpret_cast<int *>(lds);
@@ -645,11 +673,15 @@ __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds,
     flow_cut(f, slot, f.n_slots, &t_lo, &t_hi, &nb, &ne);
     if (decided_to_leave(&s_ctl[0], leave)) return;
     if (ne <= nb) {
-        if (threadIdx.x == 0) f.sched_head[slot] = int4{0, 0, 0, 0};
+        if (threadIdx.x == 0) {
+            f.sched_head[slot] = int4{0, 0, 0, 0};
+            if (PLACES) sp.trees[slot] = int4{0, 0, 0, 0};
+        }
         return;
     }
-    if (ne - nb < 0xFFFF && sched_lds_bytes((size_t)(ne - nb)) <= lds_bytes) flow_schedule_slot<true>(f, slot, t_lo, t_hi, nb, ne, lds);
-    else flow_schedule_slot<false>(f, slot, t_lo, t_hi, nb, ne, lds);
+    if (PLACES && threadIdx.x == 0) sp.trees[slot] = int4{t_lo, t_hi, (ne - nb - (t_hi - t_lo)) / 2, (nb - t_lo) / 2};
+    if (ne - nb < 0xFFFF && sched_lds_bytes((size_t)(ne - nb)) <= lds_bytes) flow_schedule_slot<true, PLACES>(f, sp, slot, t_lo, t_hi, nb, ne, lds);
+    else flow_schedule_slot<false, PLACES>(f, sp, slot, t_lo, t_hi, nb, ne, lds);
 }
 // As a launch of its own, where the leaves are evaluated by a kernel that does not do it on the side.
 

@@ -16,6 +16,7 @@
 #include "schedulers.hpp"
 #include "classify.hpp"
 #include "backward.hpp"
+#include "back_flow.hpp"
 #include "topdown.hpp"
 
 using namespace tl;
@@ -94,7 +95,15 @@ struct tl_ctx {
     void *wp_bwd_inner = nullptr, *wp_bwd_leaf = nullptr, *wp_bwd_inner1 = nullptr;
     float *bp_bwd_inner = nullptr, *bp_bwd_leaf = nullptr, *bp_bwd_inner1 = nullptr;
     int bw_grid = 0;                  // workgroups of the backward kernel that walks all heights (0: per-height launches)
-    int bw_ws_grid = 0, bw_spw2 = 0;  // ... of its form with the operand gradient on weight-stationary workgroups (0: none)
+    // one-kernel forms at H <= 512 (back_flow.hpp): pairs of column groups per wave (0: not used), pairs, workgroups, packed weights and their scales, and
+    // beside bw: marked rows, the schedule and the list of internal nodes for bf_nodes nodes
+    int bf_p = 0, bf_pairs = 0, bf_grid = 0;
+    _Float16 *bf_wp = nullptr, *bf_wp_leaf = nullptr;
+    float *bf_scale = nullptr, *bf_scale_leaf = nullptr;
+    int bf_leaf_s = 0, bf_leaf_grid = 0;      // leaves: k-steps per wave (0: not used), workgroups
+    unsigned char *bf = nullptr;
+    int bf_nodes = 0;
+    bool bwd_packed = true;           // the matrices of the other forms belong to the current parameters
     Gemm g_bwd_inner1{};              // U^T once more with one column block per group: more workgroups for heights of few rows
     Gemm g_bwd_inner{}, g_bwd_leaf{};
     int ng_bwd_inner = 1, ng_bwd_leaf = 1;    // blocks of output columns per column group of the operand-gradient contractions
@@ -112,7 +121,7 @@ struct tl_ctx {
     int ws_steps16 = 0;
     bool keep_gates = false;          // tl_set_keep_gates
     int async_backward = 0;           // tl_set_async_backward: 1 does not wait, -1 always launches per height, 0 picks
-    float *gates = nullptr;           // [gates_cap x 5H] gate activations of the last forward that kept them
+    floatx4 *gates = nullptr;         // [HU], [2][gates_cap x H]: what the last forward that did so kept for the backward pass
     int gates_cap = 0;
     int gates_nodes = 0;              // nodes of that forward, 0: nothing kept
     const float *gates_h = nullptr;   // its h argument: identifies the batch the activations belong to
@@ -458,11 +467,11 @@ int pack_treelstm_f32(tl_ctx *ctx, hipStream_t st)
     // backward pass: U^T [5H x 2H] and W_leaf^T [3H x E] as contractions with a zero bias
     float *t = ctx->t_scratch, *zb = ctx->zero_bias;
     hipLaunchKernelGGL(k_transpose, dim3(1024), dim3(256), 0, st, (const float *)ctx->m_u, t, 2 * H, 5 * H);
-    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, 5 * H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 8 * ctx->bw_spw2, false,
+    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, 5 * H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 0, false,
                    &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
     if (rc != TL_OK) return rc;
     if (ctx->ng_bwd_inner == 4) {
-        rc = pack_gemm(t, zb, 1, 2 * H, 1, 5 * H, (2 * H + HU - 1) / HU, 8 * ctx->bw_spw2, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
+        rc = pack_gemm(t, zb, 1, 2 * H, 1, 5 * H, (2 * H + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
                        &ctx->bp_bwd_inner1, st);
         if (rc != TL_OK) return rc;
     }
@@ -480,7 +489,15 @@ int pack_split(tl_ctx *ctx, const PackList &many, hipStream_t st)
 {
     const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim;
     SplitPackList pl{};
+    RowsPackList rl{};
     int grid = 0;
+    auto add_rows = [&](const float *m, int NG, int K, int n, int sides, int S, _Float16 **wp, float **scale, int n_cg) -> int {
+        if (!*wp) TL_HIP(hipMalloc(wp, (size_t)n_cg * 4 * S * sides * 2 * 64 * 8 * sizeof(_Float16)));
+        if (!*scale) TL_HIP(hipMalloc(scale, (size_t)n_cg * sides * HU * sizeof(float)));
+        rl.job[rl.n++] = RowsPackJob{m, *wp, *scale, NG, K, n, sides, 4 * S, n_cg};
+        rl.blocks += n_cg * sides;
+        return TL_OK;
+    };
     auto add = [&](const float *m, int NG, int SEG, int L, int S, float operand_scale, _Float16 **wp, float **scale, int steps, int n_cg) -> int {
         if (!*wp) TL_HIP(hipMalloc(wp, (size_t)n_cg * 4 * S * NG * 2 * 64 * 8 * sizeof(_Float16)));
         if (!*scale) TL_HIP(hipMalloc(scale, (size_t)n_cg * NG * HU * sizeof(float)));
@@ -498,9 +515,12 @@ int pack_split(tl_ctx *ctx, const PackList &many, hipStream_t st)
     if (ctx->split > 0 && rnn && (rc = add(ctx->m_u, 1, 2, H, ctx->split, 1.f, &ctx->xp_inner, &ctx->xs_inner, 2 * ctx->split, round_up(n_cg, 2))) != TL_OK) return rc;
     if (ctx->split > 0 && !rnn && (rc = add(ctx->m_u, 5, 2, H, ctx->split, SPLIT_H_SCALE, &ctx->xp_inner, &ctx->xs_inner, steps_h, n_cg)) != TL_OK) return rc;
     if (ctx->spw_leaf > 0 && (rc = add(ctx->m_w_leaf, 3, 1, E, ctx->spw_leaf, 1.f, &ctx->xp_leaf, &ctx->xs_leaf, (E + 31) / 32, n_cg)) != TL_OK) return rc;
+    const int ng = rnn ? 1 : 5;
+    if (ctx->bf_p > 0 && (rc = add_rows(ctx->m_u, ng, H, H, 2, ng * ctx->bf_p, &ctx->bf_wp, &ctx->bf_scale, n_cg)) != TL_OK) return rc;
+    if (ctx->bf_leaf_s > 0 && (rc = add_rows(ctx->m_w_leaf, 1, 3 * H, E, 1, ctx->bf_leaf_s, &ctx->bf_wp_leaf, &ctx->bf_scale_leaf, (E + HU - 1) / HU)) != TL_OK) return rc;
     const int rest = many.n > 0 ? 2048 : 0;
-    if (grid + rest == 0) return TL_OK;
-    hipLaunchKernelGGL(k_repack, dim3(grid + rest), dim3(256), 0, st, many, pl, grid);
+    if (grid + rest + rl.blocks == 0) return TL_OK;
+    hipLaunchKernelGGL(k_repack, dim3(grid + rl.blocks + rest), dim3(256), 0, st, many, pl, rl, grid);
     TL_HIP(hipGetLastError());
     return TL_OK;
 }
@@ -517,6 +537,20 @@ PackJob repack_job(const Gemm &g, const float *w, const float *b, float *bp, int
     return j;
 }
 
+// The jobs of the backward pass: U^T [ng_cell H x 2H] and W_leaf^T [3H x E].
+int bwd_jobs(const tl_ctx *ctx, PackList &pl, int n)
+{
+    const int H = ctx->cfg.hidden, E = ctx->cfg.embed_dim;
+    pl.job[n++] = repack_job(ctx->g_bwd_inner, ctx->m_u, nullptr, nullptr, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1,
+                             (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, true);
+    if (ctx->ng_bwd_inner == 4)
+        pl.job[n++] = repack_job(ctx->g_bwd_inner1, ctx->m_u, nullptr, nullptr, 1, 2 * H, 1, (2 * H + HU - 1) / HU, true);
+    if (ctx->cfg.cell == TL_TREELSTM)
+        pl.job[n++] = repack_job(ctx->g_bwd_leaf, ctx->m_w_leaf, nullptr, nullptr, ctx->ng_bwd_leaf, E / ctx->ng_bwd_leaf, 1,
+                                 (E / ctx->ng_bwd_leaf + HU - 1) / HU, true);
+    return n;
+}
+
 // After a parameter update of an fp32 TreeLSTM or TreeRNN context: everything pack_treelstm_f32 / pack_treernn_f32 derive
 // from the parameters, packed over in one launch.
 int repack_f32(tl_ctx *ctx, hipStream_t st)
@@ -529,16 +563,26 @@ int repack_f32(tl_ctx *ctx, hipStream_t st)
     int n = 0;
     if (lstm) pl.job[n++] = repack_job(ctx->g_leaf, ctx->m_w_leaf, ctx->m_b_leaf, ctx->bp_leaf, 3, H, 1, ctx->n_cg, false);
     pl.job[n++] = repack_job(ctx->g_inner, ctx->m_u, ctx->m_b, ctx->bp_inner, ng_cell, H, 2, ctx->n_cg, false);
-    // backward pass: U^T [ng_cell H x 2H] and W_leaf^T [3H x E]
-    pl.job[n++] = repack_job(ctx->g_bwd_inner, ctx->m_u, nullptr, nullptr, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1,
-                             (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, true);
-    if (ctx->ng_bwd_inner == 4)
-        pl.job[n++] = repack_job(ctx->g_bwd_inner1, ctx->m_u, nullptr, nullptr, 1, 2 * H, 1, (2 * H + HU - 1) / HU, true);
-    if (lstm)
-        pl.job[n++] = repack_job(ctx->g_bwd_leaf, ctx->m_w_leaf, nullptr, nullptr, ctx->ng_bwd_leaf, E / ctx->ng_bwd_leaf, 1,
-                                 (E / ctx->ng_bwd_leaf + HU - 1) / HU, true);
+    // (fp32 matrices of the backward pass: where its one-kernel forms have their own, packed over when something needs them)
+    if (ctx->bf_p > 0) ctx->bwd_packed = false;
+    else n = bwd_jobs(ctx, pl, n);
     pl.n = n;
     return pack_split(ctx, pl, st);
+}
+
+// ... in front of a backward pass in another form than those of back_flow.hpp
+int pack_bwd(tl_ctx *ctx, hipStream_t st)
+{
+    if (ctx->bwd_packed) return TL_OK;
+    PackList pl{};
+    pl.n = bwd_jobs(ctx, pl, 0);
+    hipLaunchKernelGGL(k_repack, dim3(2048), dim3(256), 0, st, pl, SplitPackList{}, RowsPackList{}, 0);
+    TL_HIP(hipGetLastError());
+    // (a launch that a capture records has not run yet)
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    TL_HIP(hipStreamIsCapturing(st, &capture));
+    ctx->bwd_packed = capture == hipStreamCaptureStatusNone;
+    return TL_OK;
 }
 
 // The same for an fp32 TreeRNN context: forward weights and W^T of the backward pass.
@@ -549,11 +593,11 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
     if (rc != TL_OK) return rc;
     float *t = ctx->t_scratch, *zb = ctx->zero_bias;
     hipLaunchKernelGGL(k_transpose, dim3(1024), dim3(256), 0, st, (const float *)ctx->m_u, t, 2 * H, H);
-    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 8 * ctx->bw_spw2, false,
+    rc = pack_gemm(t, zb, ctx->ng_bwd_inner, 2 * H / ctx->ng_bwd_inner, 1, H, (2 * H / ctx->ng_bwd_inner + HU - 1) / HU, 0, false,
                    &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
     if (rc != TL_OK) return rc;
     if (ctx->ng_bwd_inner == 4) {
-        rc = pack_gemm(t, zb, 1, 2 * H, 1, H, (2 * H + HU - 1) / HU, 8 * ctx->bw_spw2, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
+        rc = pack_gemm(t, zb, 1, 2 * H, 1, H, (2 * H + HU - 1) / HU, 0, false, &ctx->g_bwd_inner1, &ctx->wp_bwd_inner1,
                        &ctx->bp_bwd_inner1, st);
         if (rc != TL_OK) return rc;
     }
@@ -718,6 +762,53 @@ int ensure_split(tl_ctx *ctx, int n_nodes)
     return TL_OK;
 }
 
+// Backward pass of back_flow.hpp: rows of the copy it gathers (and of the gate activations) by 24-bit node numbers and 32-bit byte offsets.
+size_t back_row_bytes(const tl_ctx *ctx) { return (size_t)ctx->bf_pairs * (ctx->cfg.cell == TL_TREELSTM ? 5 : 1) * 128; }
+bool in_back_range(const tl_ctx *ctx, int n_nodes)
+{
+    return ctx->bf_p > 0 && n_nodes < (1 << 24) && (unsigned long long)(n_nodes / 2 + 1) * back_row_bytes(ctx) < (1ull << 32) - (1 << 16) &&
+           (unsigned long long)n_nodes * ctx->cfg.hidden * (ctx->cfg.cell == TL_TREELSTM ? 20 : 4) < (1ull << 32) &&
+           (unsigned long long)n_nodes * ctx->cfg.hidden * sizeof(floatx4) < (1ull << 32) &&
+           (unsigned long long)n_nodes * ctx->cfg.embed_dim * 4 < (1ull << 32);
+}
+struct BackSizes {
+    size_t gx, gs, sched, head, trees, list, place;
+};
+BackSizes back_sizes(const tl_ctx *ctx, size_t N)
+{
+    const size_t slots = (size_t)ctx->bf_grid / ctx->n_cg;
+    const size_t inner = N / 2 + 1;
+    return BackSizes{align256(inner * back_row_bytes(ctx)), align256(inner * ctx->n_cg * 4), align256(inner * 16 * sizeof(int4)), align256(slots * sizeof(int4)),
+                     align256(slots * sizeof(int4)), align256(inner * 4), align256((N + 1) * sizeof(int2))};
+}
+int ensure_back(tl_ctx *ctx, int n_nodes)
+{
+    if (n_nodes <= ctx->bf_nodes) return TL_OK;
+    TL_HIP(hipDeviceSynchronize());
+    if (ctx->bf) { TL_HIP(hipFree(ctx->bf)); ctx->bf = nullptr; }
+    ctx->bf_nodes = 0;
+    const size_t N = (size_t)(in_back_range(ctx, ctx->cap_nodes) ? ctx->cap_nodes : n_nodes);
+    const BackSizes z = back_sizes(ctx, N);
+    TL_HIP(hipMalloc(&ctx->bf, z.gx + z.gs + 2 * z.sched + z.head + z.trees + z.list + z.place));
+    ctx->bf_nodes = (int)N;
+    return TL_OK;
+}
+void carve_back(const tl_ctx *ctx, Fwd *f, BackFlow *b)
+{
+    const BackSizes z = back_sizes(ctx, (size_t)ctx->bf_nodes);
+    unsigned char *p = ctx->bf;
+    auto take = [&](size_t n) { unsigned char *r = p; p += n; return r; };
+    b->gx = (unsigned *)take(z.gx);
+    b->gs = (unsigned *)take(z.gs);
+    f->sched = (int4 *)take(z.sched);
+    b->at.children = (int4 *)take(z.sched);
+    f->sched_head = (int4 *)take(z.head);
+    b->at.trees = (int4 *)take(z.trees);
+    b->at.of = (int2 *)take(z.place);
+    b->int_list = (int32_t *)take(z.list);
+    b->wp = ctx->bf_wp; b->scale = ctx->bf_scale; b->u = ctx->m_u; b->n_pairs = ctx->bf_pairs;
+}
+
 // Cuts a workspace of workspace_bytes(cap_nodes, cap_trees) bytes at `base` into the arrays of a forward.
 void carve_workspace(unsigned char *base, int cap_nodes, int cap_trees, Fwd *f)
 {
@@ -756,6 +847,11 @@ void free_all(tl_ctx *ctx)
     (void)hipFree(ctx->sched_head);
     (void)hipFree(ctx->hx_back);
     (void)hipFree(ctx->rb_wp);
+    (void)hipFree(ctx->bf);
+    (void)hipFree(ctx->bf_wp);
+    (void)hipFree(ctx->bf_wp_leaf);
+    (void)hipFree(ctx->bf_scale);
+    (void)hipFree(ctx->bf_scale_leaf);
     (void)hipFree(ctx->rb_scale);
     (void)hipFree(ctx->rows_wp);
     (void)hipFree(ctx->rows_scale);
@@ -791,44 +887,48 @@ void free_all(tl_ctx *ctx)
     delete ctx;
 }
 
-// The persistent backward kernel with the weight-stationary operand gradient, and the LDS it takes: rows of dG (5 H values, TreeRNN: H)
-// of at most 128 spw2 values, H <= 512.
-typedef void (*bwh_ws_kernel)(Fwd, BwdHeights);
-const int BW_STEPS[] = {1, 2, 3, 4, 5, 6, 7, 8, 10, 12, 14, 15, 16, 18, 20};
-template <int SPW2, bool LSTM> bwh_ws_kernel backward_ws_kernel_of(bool exact, size_t *lds)
+// Backward pass of TreeLSTM and TreeRNN, H <= 512 (back_flow.hpp), p pairs of column groups per wave.
+typedef void (*back_flow_kernel)(Fwd, BackFlow);
+typedef void (*back_heights_kernel)(Fwd, BackFlow, int, int, int);
+template <int P> back_flow_kernel back_flow_of(bool lstm) { return lstm ? k_back_flow<5, P> : k_back_flow<1, P>; }
+template <int P> back_heights_kernel back_heights_of(bool lstm) { return lstm ? k_back_heights<5, P> : k_back_heights<1, P>; }
+back_flow_kernel back_flow(bool lstm, int p)
 {
-    *lds = sizeof(OperandWsSmem<SPW2>);
-    // (rows of exactly 128 spw2 values: H a multiple of 128)
-    if constexpr (!LSTM || SPW2 % 5 == 0)
-        if (exact) return k_backward_heights_ws<SPW2, LSTM, true>;
-    return k_backward_heights_ws<SPW2, LSTM, false>;
-}
-bwh_ws_kernel backward_ws_kernel(bool lstm, int spw2, bool exact, size_t *lds)
-{
-    if (lstm) {
-        switch (spw2) {
-        case 1:  return backward_ws_kernel_of<1, true>(exact, lds);
-        case 2:  return backward_ws_kernel_of<2, true>(exact, lds);
-        case 3:  return backward_ws_kernel_of<3, true>(exact, lds);
-        case 4:  return backward_ws_kernel_of<4, true>(exact, lds);
-        case 5:  return backward_ws_kernel_of<5, true>(exact, lds);
-        case 6:  return backward_ws_kernel_of<6, true>(exact, lds);
-        case 7:  return backward_ws_kernel_of<7, true>(exact, lds);
-        case 8:  return backward_ws_kernel_of<8, true>(exact, lds);
-        case 10: return backward_ws_kernel_of<10, true>(exact, lds);
-        case 12: return backward_ws_kernel_of<12, true>(exact, lds);
-        case 14: return backward_ws_kernel_of<14, true>(exact, lds);
-        case 15: return backward_ws_kernel_of<15, true>(exact, lds);
-        case 16: return backward_ws_kernel_of<16, true>(exact, lds);
-        case 18: return backward_ws_kernel_of<18, true>(exact, lds);
-        default: return backward_ws_kernel_of<20, true>(exact, lds);
-        }
+    switch (p) {
+    case 1: return back_flow_of<1>(lstm);
+    case 2: return back_flow_of<2>(lstm);
+    case 3: return back_flow_of<3>(lstm);
+    default: return back_flow_of<4>(lstm);
     }
-    switch (spw2) {
-    case 1:  return backward_ws_kernel_of<1, false>(exact, lds);
-    case 2:  return backward_ws_kernel_of<2, false>(exact, lds);
-    case 3:  return backward_ws_kernel_of<3, false>(exact, lds);
-    default: return backward_ws_kernel_of<4, false>(exact, lds);
+}
+back_heights_kernel back_heights(bool lstm, int p)
+{
+    switch (p) {
+    case 1: return back_heights_of<1>(lstm);
+    case 2: return back_heights_of<2>(lstm);
+    case 3: return back_heights_of<3>(lstm);
+    default: return back_heights_of<4>(lstm);
+    }
+}
+size_t back_lds(bool lstm, int p) { return lstm && p == 4 ? sizeof(BackSmem<5, 4>) : sizeof(BackSmem<1, 1>); }     // (weights in LDS in the largest one only)
+static_assert(sizeof(BackSmem<5, 3>) == sizeof(BackSmem<1, 1>) && sizeof(BackSmem<1, 4>) == sizeof(BackSmem<1, 1>), "one LDS layout for all but the largest");
+// ... its leaves, s k-steps of 32 per wave (3 H <= 1 536), BACK_LEAF_NC column groups of the embedding per workgroup
+constexpr int BACK_LEAF_NC = 3;
+const int BACK_LEAF_STEPS[] = {1, 2, 3, 4, 6, 8, 10, 12};
+typedef void (*back_leaf_kernel)(Fwd, const float *, int, const void *, const float *, const float *);
+size_t back_leaf_lds(int s) { return sizeof(BackLeafSmem<1, BACK_LEAF_NC>) + (size_t)(s - 1) * 4 * TURN_BYTES; }
+static_assert(sizeof(BackLeafSmem<12, BACK_LEAF_NC>) == sizeof(BackLeafSmem<1, BACK_LEAF_NC>) + 11 * 4 * TURN_BYTES, "back_leaf_lds");
+back_leaf_kernel back_leaf(int s)
+{
+    switch (s) {
+    case 1: return k_back_leaf<1, BACK_LEAF_NC>;
+    case 2: return k_back_leaf<2, BACK_LEAF_NC>;
+    case 3: return k_back_leaf<3, BACK_LEAF_NC>;
+    case 4: return k_back_leaf<4, BACK_LEAF_NC>;
+    case 6: return k_back_leaf<6, BACK_LEAF_NC>;
+    case 8: return k_back_leaf<8, BACK_LEAF_NC>;
+    case 10: return k_back_leaf<10, BACK_LEAF_NC>;
+    default: return k_back_leaf<12, BACK_LEAF_NC>;
     }
 }
 
@@ -906,11 +1006,31 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
         if (ctx->rb_sets < 1) ctx->rb_steps = 0;
     }
     ctx->flow_set = ctx->rows_steps > 0 ? (H + ROWS_UNITS - 1) / ROWS_UNITS : ctx->n_cg;
-    // Backward pass: k-steps of 16 in half a wave's quarter of a row of gate gradients
+    // Backward pass
     if (!bf16 && cfg->cell != TL_RNTN && H <= 512) {
-        const int needed = ((cfg->cell == TL_TREELSTM ? 5 : 1) * H + 127) / 128;
-        for (int sz : BW_STEPS)
-            if (sz >= needed) { ctx->bw_spw2 = sz; break; }
+        const bool lstm = cfg->cell == TL_TREELSTM;
+        const int p = ((H + 31) / 32 + 3) / 4;
+        int o = 0, o1 = 0, rc = allow_lds(back_flow(lstm, p), back_lds(lstm, p));
+        if (rc == TL_OK) rc = allow_lds(back_heights(lstm, p), back_lds(lstm, p));
+        if (rc == TL_OK) rc = allow_lds(k_back_prepare, SCHED_LDS_BYTES);
+        if (rc != TL_OK) return rc;
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(back_flow(lstm, p)), WG_THREADS, back_lds(lstm, p)));
+        TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, reinterpret_cast<const void *>(back_heights(lstm, p)), WG_THREADS, back_lds(lstm, p)));
+        if (o >= 1 && o1 >= 1 && ctx->n_cu >= ctx->n_cg) {      // one workgroup per CU; all of them wait for each other
+            ctx->bf_p = p;
+            ctx->bf_pairs = (H + 31) / 32;
+            ctx->bf_grid = ctx->n_cu / ctx->n_cg * ctx->n_cg;
+        }
+        if (lstm && ctx->bf_p > 0) {
+            for (int sz : BACK_LEAF_STEPS)
+                if (128 * sz >= 3 * H) { ctx->bf_leaf_s = sz; break; }
+            o = 0;
+            if ((rc = allow_lds(back_leaf(ctx->bf_leaf_s), back_leaf_lds(ctx->bf_leaf_s))) != TL_OK) return rc;
+            TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o, reinterpret_cast<const void *>(back_leaf(ctx->bf_leaf_s)), WG_THREADS, back_leaf_lds(ctx->bf_leaf_s)));
+            const int groups = ((E + HU - 1) / HU + BACK_LEAF_NC - 1) / BACK_LEAF_NC;
+            ctx->bf_leaf_grid = (o < 1 ? 1 : o > 2 ? 2 : o) * ctx->n_cu / (N_XCD * groups) * (N_XCD * groups);
+            if (ctx->bf_leaf_grid < N_XCD * groups) ctx->bf_leaf_grid = N_XCD * groups;
+        }
     }
     const int ws_steps16 = bf16 ? 8 * ctx->spw : 4 * ctx->spw;   // K axis of the weight-stationary cell in k-steps of 16
     ctx->spw_leaf = 0;
@@ -1033,21 +1153,6 @@ int create_impl(const tl_config *cfg, tl_ctx *ctx)
             if (o < o_min) o_min = o;
         }
         ctx->bw_grid = o_min * ctx->n_cu;
-        // weight-stationary operand gradient
-        ctx->bw_ws_grid = 0;
-        const int n_cg_b = (2 * H + HU - 1) / HU;
-        if (ctx->bw_spw2 > 0 && ctx->n_cu >= n_cg_b) {
-            int o = 1;
-            for (int exact = 0; exact < 2; ++exact) {
-                size_t lds = 0;
-                const bwh_ws_kernel k = backward_ws_kernel(cfg->cell == TL_TREELSTM, ctx->bw_spw2, exact != 0, &lds);
-                if ((rc = allow_lds(k, lds)) != TL_OK) return rc;
-                int o1 = 0;
-                TL_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&o1, reinterpret_cast<const void *>(k), WG_THREADS, lds));
-                if (o1 < o) o = o1;
-            }
-            if (o >= 1) ctx->bw_ws_grid = ctx->n_cu / n_cg_b * n_cg_b;
-        }
     }
     if (ctx->spw > 0) {
         ctx->ws_lds = ws_lds_bytes(ctx->spw, bf16);
@@ -1226,11 +1331,11 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
             TL_HIP(hipDeviceSynchronize());
             if (ctx->gates) { TL_HIP(hipFree(ctx->gates)); ctx->gates = nullptr; }
             ctx->gates_cap = 0;
-            TL_HIP(hipMalloc(&ctx->gates, ((size_t)(ctx->cap_nodes + 1) * 5 * cfg.hidden + HU) * sizeof(float)));      // (one row more: the sink)
+            TL_HIP(hipMalloc(&ctx->gates, ((size_t)ctx->cap_nodes * 2 * cfg.hidden + HU) * sizeof(floatx4)));          // (HU for lanes that have nothing to keep, and two planes)
             ctx->gates_cap = ctx->cap_nodes;
         }
-        f.gates = ctx->gates;
-        f.sink = ctx->gates + (size_t)ctx->gates_cap * 5 * cfg.hidden;
+        f.keep0 = ctx->gates + HU;
+        f.keep1 = f.keep0 + (size_t)ctx->gates_cap * cfg.hidden;
         ctx->gates_nodes = n_nodes;
         ctx->gates_h = h;
     }
@@ -1405,13 +1510,13 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     // (the data-flow scheduler's fill of the rows of internal nodes takes one wave per node)
     const int nb_reset = f.flow == 1 ? (n_nodes / 4 + 1 < 256 ? 256 : (n_nodes / 4 + 1 > 4096 ? 4096 : n_nodes / 4 + 1)) : 256;
     hipLaunchKernelGGL(k_reset, dim3(nb_reset), dim3(256), 0, st, f, need_levels ? 1 : 0);
-    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
+    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, (int32_t *)nullptr);
     if (!f.flow_roots) hipLaunchKernelGGL(k_roots, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
     if (need_levels) {
         hipLaunchKernelGGL(k_climb, dim3((f.n_leaf + 255) / 256), dim3(256), 0, st, f);
         hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, f);
         hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, f);
-        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, f);
+        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, f, (int2 *)nullptr);
     }
     if (f.priority && f.n_int > 0) {
         hipLaunchKernelGGL(k_depth_walk, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
@@ -1430,7 +1535,7 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     if (leaf_ws && bf16) {
         hipLaunchKernelGGL(leaf_ws_bf_kernel(ctx->spw_leaf), dim3(ctx->leaf_grid), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, false), st, f);
     } else if (leaf_ws) {
-        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf, f.gates != nullptr), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, n_sched > 0),
+        hipLaunchKernelGGL(leaf_split_kernel(ctx->spw_leaf, f.keep0 != nullptr), dim3(ctx->leaf_grid + n_sched), dim3(WG_THREADS), leaf_lds_bytes(ctx->spw_leaf, bf16, n_sched > 0),
                            st, fl, n_sched);
     } else if (cfg.cell == TL_TREELSTM) {
         const LevelPlan plan = plan_level(f.n_leaf, f.cap_tiles);
@@ -1595,8 +1700,15 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const size_t rntn_row = (size_t)H * 2 * H + H;
     // RNTN: rows of d * 2d + d values per node and launches per height, or rows of d where the one kernel takes them (24-bit row numbers,
     // 32-bit byte offsets) and the caller has not asked for launches
+    const int ng_cell = lstm ? 5 : 1;                         // gate blocks of an internal node
+    // gate activations of the forward that wrote these h rows, if it kept them: no contraction to recompute
+    const bool kept = lstm && ctx->gates_nodes == n_nodes && ctx->gates_h == h && ctx->gates != nullptr;
+    // gate gradients that need no contraction, H <= 512: the forms of back_flow.hpp (24-bit node numbers, 32-bit byte offsets)
+    const bool back = in_back_range(ctx, n_nodes) && (kept || !lstm);
     const bool rntn_rows = rntn && (ctx->rb_steps == 0 || ctx->async_backward < 0 || n_nodes >= (1 << 24) || (size_t)n_nodes * H * 4 >= ((size_t)1 << 32));
     if (rntn_rows && (rc = pack_rntn_wide(ctx, st)) != TL_OK) return rc;
+    if (!rntn && !back && (rc = pack_bwd(ctx, st)) != TL_OK) return rc;
+    if (back && (rc = ensure_back(ctx, n_nodes)) != TL_OK) return rc;
     if (n_nodes > ctx->bw_nodes || (rntn_rows && !ctx->bw_rows)) {
         TL_HIP(hipDeviceSynchronize());
         if (ctx->bw) { TL_HIP(hipFree(ctx->bw)); ctx->bw = nullptr; }
@@ -1622,25 +1734,61 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const size_t cap = (size_t)ctx->bw_nodes;
     f.dh = ctx->bw;
     f.dc = f.dh + cap * H;
-    const int ng_cell = lstm ? 5 : 1;                         // gate blocks of an internal node
     float *dg_int = f.dc + cap * H, *dg_leaf = dg_int + (size_t)n_int * ng_cell * H;
     const int dg_cols = rntn ? (int)rntn_row : ng_cell * H;   // length of a row of dg_int
     f.d_x = d_x;
+    if (kept) {
+        f.keep0 = ctx->gates + HU;
+        f.keep1 = f.keep0 + (size_t)ctx->gates_cap * H;
+    }
+    // Whole trees on sets of workgroups (k_back_flow); a batch of few large trees leaves the choice between that and height by height on
+    // all of them to the device, as the forward does (internal_kernel_skipped); launches per height on request.
+    const bool launches = ctx->async_backward < 0;
+    const int back_slots = back ? ctx->bf_grid / ctx->n_cg : 0;
+    const bool back_either = back && !launches && n_trees < back_slots && n_nodes / n_trees >= FLOW_LARGE_TREE_NODES;
+    BackFlow bk{};
+    if (back) {
+        carve_back(ctx, &f, &bk);
+        f.n_slots = back_slots;
+        f.flow_roots = !launches && !back_either ? 1 : 0;
+        const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
+        f.place = ctx->n_cg <= 3 || (ctx->n_cg <= 10 && 4ll * n_trees <= 3ll * f.n_slots) || (ctx->n_cg <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
+        bk.g_h = g_h; bk.dg = dg_int; bk.dc = lstm ? f.dh : nullptr;
+    }
     ctx->last = f;
     ctx->last_stream = st;
     ctx->ran = true;
     const int nb_nodes = (n_nodes + 1 + 255) / 256;
     const int nb_big = (n_nodes + 1 + NODE_BLOCK - 1) / NODE_BLOCK;
-    // structure pass with heights and per-height lists (as for the host-driven level scheduler)
-    hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, 1);
-    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
-    hipLaunchKernelGGL(k_roots, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
-    hipLaunchKernelGGL(k_climb, dim3((n_leaf + 255) / 256), dim3(256), 0, st, f);
-    hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, f);
-    hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, f);
-    hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, f);
-    // dh starts as the upstream gradient of every node, dc as zero; d_x rows of internal nodes stay zero
-    {
+    // structure pass; with heights and per-height lists (as for the host-driven level scheduler) where something walks the heights
+    const bool need_levels = !back || launches || back_either;
+    hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, need_levels ? 1 : 0);
+    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list);
+    if (need_levels) {
+        Fwd fl = f;
+        fl.pick = back_either ? 2 : 0;
+        hipLaunchKernelGGL(k_roots, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
+        hipLaunchKernelGGL(k_climb, dim3((n_leaf + 255) / 256), dim3(256), 0, st, fl);
+        hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, fl);
+        hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, fl);
+        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, fl, bk.at.of);
+    }
+    if (back) {
+        ClearList z{};
+        z.p[0] = d_b;      z.n[0] = (size_t)ng_cell * H;
+        z.p[1] = d_u;      z.n[1] = (size_t)2 * H * ng_cell * H;
+        z.p[2] = d_b_leaf; z.n[2] = lstm ? (size_t)3 * H : 0;
+        z.p[3] = d_w_leaf; z.n[3] = lstm ? (size_t)E * 3 * H : 0;
+        Fwd fs = f;
+        fs.pick = back_either ? 1 : 0;
+        const int n_sched = launches ? 0 : back_slots;
+        // (as many workgroups as are resident at once, a wave per node; LDS as in forward_impl)
+        const int rows = (n_nodes + 3) / 4 < 8 * ctx->n_cu ? (n_nodes + 3) / 4 : 8 * ctx->n_cu;
+        const size_t small = 16 * 1024;
+        const size_t lds = n_sched == 0 ? 0 : sched_lds_bytes(4 * (size_t)(n_nodes / n_sched) + 256) <= small ? small : SCHED_LDS_BYTES;
+        hipLaunchKernelGGL(k_back_prepare, dim3(n_sched + rows), dim3(WG_THREADS), lds, st, fs, bk, z, ng_cell, n_sched > 0 ? 1 : 0, n_sched, (int)lds);
+    } else {
+        // dh starts as the upstream gradient of every node, dc as zero; d_x rows of internal nodes stay zero
         ZeroList z{};
         z.src = g_h; z.dst = f.dh; z.n_copy = (size_t)n_nodes * H;
         z.p[0] = f.dc;     z.n[0] = lstm ? (size_t)n_nodes * H : 0;
@@ -1653,33 +1801,25 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     }
     TL_HIP(hipGetLastError());
     const bool vec4 = H % 4 == 0 && (((uintptr_t)h & 15) == 0);
-    // gate activations of the forward that wrote these h rows, if it kept them: no contraction to recompute
-    const bool kept = lstm && ctx->gates_nodes == n_nodes && ctx->gates_h == h && ctx->gates != nullptr;
     const bool kept_v4 = H % 4 == 0 && (((uintptr_t)h | (uintptr_t)c) & 15) == 0;
-    f.gates = kept ? ctx->gates : nullptr;
     // On request (tl_set_async_backward), gate gradients that need no contraction (kept activations; TreeRNN): all heights in
     // one persistent kernel, which finds the per-height lists on the device.  Nothing is read back, the call does not wait;
     // what the structure pass finds wrong with the batch is latched for tl_status, and every kernel below leaves at once.
     const bool kept_or_rnn_v4 = lstm ? kept_v4 : vec4;
     const bool persistent_ok = ctx->bw_grid > 0 && !rntn && (kept || !lstm) && n_int > 0;
-    // H <= 512: the operand gradient on weight-stationary workgroups (row offsets of dG in 32 bits).  In launches per height the streaming
-    // cell is the faster one for many nodes where rows of more than 2 304 values leave no registers for the general form (H = 500, training
-    // step, launches / this: 64 trees 836 / 831 us, 128 1 127 / 1 181, 256 1 667 / 1 818) or whole sets of workgroups leave a seventh of the CUs idle
-    // (H = 340, 256 trees 1 196 / 1 224; 64 666 / 605): such batches wait for the number of heights.  Elsewhere this is the faster one: H = 16, 3 trees
-    // 221 / 172; H = 150, 25 373 / 277; H = 301, 57 668 / 537, 256 1 380 / 1 111; H = 450, 128 1 210 / 1 099; TreeRNN d = 50, 25 trees 265 / 183,
-    // d = 450, 250 833 / 714.
-    // Against the streaming cell in one kernel (deep trees; calls that do not wait) it is so at every size but the first of those two where the trees are
-    // shallow: backward, H = 500, 24 chains of 300 leaves 6 650 / 5 383, 256 parse trees 1 284 / 1 321; H = 340 5 787 / 3 943, 912 / 848.
-    const bool exact_rows = kept_or_rnn_v4 && dg_cols == 128 * ctx->bw_spw2;
-    const bool no_room = !exact_rows && ctx->bw_spw2 > 18 && n_int > 2000;
-    const bool ws_fits = persistent_ok && ctx->bw_ws_grid > 0 && (unsigned long long)n_int * (unsigned long long)dg_cols * 4ull < (1ull << 32);
-    const bool ws = ws_fits && !no_room && (exact_rows || 100 * ctx->bw_ws_grid >= 86 * ctx->n_cu || n_int <= 4000);    // ... whatever the number of heights
-    const bool ws_walk = ws_fits && !(ctx->async_backward > 0 && no_room && n_nodes < 256ll * n_trees);                 // ... where one kernel walks them
     // RNTN: in one kernel wherever its matrices fit into registers and the rows' addresses into 32 bits; the call returns the structure
     // pass's status in every mode
     const bool rntn_one = rntn && !rntn_rows && n_int > 0;
-    const bool heights_on_device = ctx->async_backward > 0 && persistent_ok;
+    const bool heights_on_device = ctx->async_backward > 0 && (persistent_ok || back);
     auto launch_all_heights = [&]() {
+        if (back) {
+            Fwd g = f;
+            g.pick = back_either ? 1 : 0;
+            hipLaunchKernelGGL(back_flow(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk);
+            g.pick = 2;
+            if (back_either) hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk, BACK_ALL, 0, 0);
+            return;
+        }
         if (rntn_one) {
             Fwd g = f;
             g.dg = dg_int;
@@ -1699,22 +1839,15 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         typedef void (*bwh_kernel)(Fwd, BwdHeights);
         const bwh_kernel k = lstm ? (v4 ? bwh_kernel(k_backward_heights<true, true>) : bwh_kernel(k_backward_heights<true, false>))
                                   : (v4 ? bwh_kernel(k_backward_heights<false, true>) : bwh_kernel(k_backward_heights<false, false>));
-        if (ws_walk) {
-            size_t lds = 0;
-            const bwh_ws_kernel kw = backward_ws_kernel(lstm, ctx->bw_spw2, exact_rows, &lds);
-            hipLaunchKernelGGL(kw, dim3(ctx->bw_ws_grid), dim3(WG_THREADS), lds, st, f, b);
-        } else {
-            hipLaunchKernelGGL(k, dim3(ctx->bw_grid), dim3(WG_THREADS), TILE_SMEM_BYTES, st, f, b);
-        }
+        hipLaunchKernelGGL(k, dim3(ctx->bw_grid), dim3(WG_THREADS), TILE_SMEM_BYTES, st, f, b);
     };
     int n_levels = 0;
     const int levels_ahead = n_nodes + 2 < LEVELS_AHEAD ? n_nodes + 2 : LEVELS_AHEAD;   // offsets read back together with the control block
     bool status_pending = false;
     if (heights_on_device) {
         launch_all_heights();
-    } else if ((ws && ctx->async_backward == 0) || rntn_one) {
-        // The weight-stationary form is the faster one whatever the number of heights, and needs nothing from the host: the
-        // structure pass's status is copied out in front of it, everything is enqueued, and the call then waits for that copy
+    } else if ((back && !launches) || rntn_one) {
+        // These forms need nothing from the host: the structure pass's status is copied out in front of it, everything is enqueued, and the call then waits for that copy
         // alone (the device works on meanwhile) to return that status as it always has.
         if (!ctx->ev_ctl) TL_HIP(hipEventCreateWithFlags(&ctx->ev_ctl, hipEventDisableTiming));
         TL_HIP(hipMemcpyAsync(ctx->host_ctl, f.ctl, sizeof(Ctl), hipMemcpyDeviceToHost, st));
@@ -1740,6 +1873,8 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         if (blocks > 8LL * ctx->n_cu) blocks = 8LL * ctx->n_cu;
         hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(256), 0, st, g, list, rows, g.pos0);
     };
+    if (back && launches)
+        hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk, BACK_ROOTS, 0, 0);
     if (n_levels > 1) {
         if (n_levels + 1 > levels_ahead) {
             TL_HIP(hipMemcpyAsync(ctx->host_levels, f.level_off, (size_t)(n_levels + 1) * 4, hipMemcpyDeviceToHost, st));
@@ -1748,6 +1883,12 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         for (int lvl = n_levels - 1; lvl >= 1; --lvl) {     // roots first: a parent is always higher than its children
             const int lo = ctx->host_levels[lvl], rows = ctx->host_levels[lvl + 1] - lo;
             if (rows <= 0 || lo < 0 || lo + rows > n_int) return TL_EHIP;
+            if (back) {
+                const int blocks = (rows + 15) / 16;
+                hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3((blocks < back_slots ? blocks : back_slots) * ctx->n_cg), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f,
+                                   bk, BACK_HEIGHT, lo, rows);
+                continue;
+            }
             const LevelPlan plan = plan_level(rows, f.cap_tiles);
             Fwd g = f;
             g.dg = dg_int;
@@ -1779,7 +1920,11 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
                                TILE_SMEM_BYTES, st, g, (const int32_t *)(f.level_nodes + lo), rows, plan);
         }
     }
-    if (!lstm) {
+    if (back) {
+        if (lstm)      // (TreeRNN: the rows of d_x are there)
+            hipLaunchKernelGGL(back_leaf(ctx->bf_leaf_s), dim3(ctx->bf_leaf_grid), dim3(WG_THREADS), back_leaf_lds(ctx->bf_leaf_s), st, f, (const float *)dg_int, 5 * H,
+                               (const void *)ctx->bf_wp_leaf, (const float *)ctx->bf_scale_leaf, (const float *)ctx->m_w_leaf);
+    } else if (!lstm) {
         hipLaunchKernelGGL(k_rnn_leaf_grad, dim3(1024), dim3(256), 0, st, f);       // leaves: d_x = dh
     } else {
         const LevelPlan plan = plan_level(n_leaf, f.cap_tiles);
@@ -1802,11 +1947,12 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
                            TILE_SMEM_BYTES, st, g, (const int32_t *)f.leaf_list, n_leaf, plan_op);
     }
     // weight and bias gradients: contractions over all nodes
-    typedef void (*wgrad_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, float *, float *);
+    typedef void (*wgrad_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, int, float *, float *);
+    const int ld = back ? ng_cell * H : 0;                    // rows of dG by node, or by list position
     auto weight_grad = [&](wgrad_kernel wide, wgrad_kernel small, int K_out, const int32_t *list, int rows, const float *table, int L,
                            const float *dg, int cols, float *out, float *bias_out) {
         const WgPlan p = wg_plan(K_out, cols, rows, ctx->n_cu);
-        hipLaunchKernelGGL(p.wide ? wide : small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, cols, out,
+        hipLaunchKernelGGL(p.wide ? wide : small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, ld, cols, out,
                            bias_out);
     };
     if (n_int > 0) {
@@ -1817,7 +1963,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
                         f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
         else
             weight_grad(k_weight_grad_wide<2>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
-                        f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
+                        back ? bk.int_list : f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,
@@ -1825,7 +1971,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     if (lstm) {
         const bool v4 = E % 4 == 0 && H % 4 == 0;
         weight_grad(k_weight_grad_wide<1>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
-                    n_leaf, ctx->emb, E, dg_leaf, 3 * H, d_w_leaf, d_b_leaf);
+                    n_leaf, ctx->emb, E, back ? dg_int : dg_leaf, 3 * H, d_w_leaf, d_b_leaf);
     }
     TL_HIP(hipGetLastError());
     if (status_pending) {

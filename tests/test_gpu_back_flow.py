@@ -1,0 +1,142 @@
+"""The backward pass that mirrors the data-flow forward (csrc/back_flow.hpp: TreeLSTM from kept activations and TreeRNN at H <= 512), at the
+edges of its layout, against the CPU checker and in all modes of tl_set_async_backward, whose gradients of the leaves must agree bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1809_00832_amd import binding, synth
+
+pytestmark = pytest.mark.gpu
+
+
+def make(cell, H, seed, counts, shapes, E=21):
+    if cell == "lstm":
+        params = synth.make_treelstm_params(seed, 50, E, H, "xavier")
+    else:
+        params = synth.make_rnn_params(seed, synth.CELL_TREERNN, 50, H, scale=0.5 / H ** 0.5)
+    return params, synth.make_trees(seed + 1, counts, shapes, 50)
+
+
+def backward(params, trees, g_h, modes=(0,), keep=True):
+    """{mode: gradients} and the states of one forward."""
+    net = binding.TreeNet(params, scheduler="dataflow")
+    out = {}
+    try:
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, keep)
+        net.forward()
+        g = torch.from_numpy(g_h).cuda()
+        for mode in modes:
+            binding.tl_set_async_backward(net.ctx, mode)
+            out[mode] = {k: v.cpu().numpy() for k, v in binding.tl_backward(net.ctx, b, g, params.embed_dim).items()}
+            assert binding.tl_status(net.ctx) == 0
+        h = b["h"].cpu().numpy()
+        c = b["c"].cpu().numpy() if b["c"] is not None else None
+    finally:
+        net.close()
+    return out, h, c
+
+
+# H: one unit, one and two column groups, an odd number of them, whole and ragged pairs, the largest of each number of pairs per wave and the size behind it;
+# E: leaves' columns in one group of three and beyond
+@pytest.mark.parametrize("cell,H,E", [("lstm", h, e) for h, e in ((2, 1), (17, 16), (32, 48), (33, 49), (48, 300), (128, 300), (129, 21), (256, 257), (257, 64), (384, 96), (385, 7), (512, 97))] +
+                         [("rnn", h, h) for h in (2, 31, 33, 128, 130, 257, 512)])
+def test_sizes_at_the_edges_of_the_layout(cell, H, E):
+    print("case back sizes", cell, H, E, flush=True)
+    params, trees = make(cell, H, 900 + H, [1, 2, 40, 1, 9, 70, 3, 18, 33], ["random", "chain", "balanced"] * 3, E)
+    g_h = np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1))
+    for mode in (0, 1):
+        assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
+    ref = oracle.backward(params, trees, h, c, g_h)
+    for k in ref:                                             # sums of at most 2 600 products of order one (fp32: 2600 * 2^-24 = 1.5e-4 of the largest at worst)
+        np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", 40), ("lstm", 150), ("rnn", 64)])
+@pytest.mark.parametrize("shape", ["balanced", "chain"])
+def test_few_large_trees_of_either_kind(cell, H, shape):
+    """Fewer trees than sets of workgroups, 256 nodes a tree and more: bushy trees are walked height by height by all workgroups, narrow ones stay with one
+    set each; the device picks."""
+    print("case back few large", cell, H, shape, flush=True)
+    params, trees = make(cell, H, 950 + H, [300, 301, 290], [shape] * 3)
+    g_h = np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1, 0))
+    for mode in (0, 1):
+        assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
+    ref = oracle.backward(params, trees, h, c, g_h)
+    for k in ref:
+        np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", 150), ("rnn", 100)])
+def test_gradients_of_any_size(cell, H):
+    """A row of gate gradients is scaled by itself, and so are its pieces of 16 units: trees whose upstream gradients are 2^-60 ... 2^60 times those of others, and within
+    one tree units 16 ... 31 2^12 times the others.  d_x of every tree against the checker, relative to the tree's largest value (an operand is met to 2^-22 of its
+    piece's largest value, a product to 2^-21: sums of some hundred of them, over at most 12 heights, to 1e-4)."""
+    print("case back scales", cell, H, flush=True)
+    params, trees = make(cell, H, 970, [30] * 13, ["random"] * 13)
+    rng = np.random.default_rng(5)
+    g_h = rng.standard_normal((trees.n_nodes, H))
+    off = trees.tree_off
+    for t in range(12):
+        g_h[off[t]:off[t + 1]] *= 2.0 ** (10 * t - 60)
+    g_h[off[12]:, 16:32] *= 2.0 ** 12
+    g_h = g_h.astype(np.float32)
+    out, h, c = backward(params, trees, g_h)
+    ref = oracle.backward(params, trees, h, c, g_h)["d_x"]
+    for t in range(13):
+        rows = slice(off[t], off[t + 1])
+        err, top = np.abs(out[0]["d_x"][rows] - ref[rows]).max(), np.abs(ref[rows]).max()
+        assert top > 0 and err <= 1e-4 * top, (t, err / top)
+
+
+@pytest.mark.parametrize("bits", [0x7F800000, 0xFF800000, 0x7FC00000, 0xFFFFFFFF])
+@pytest.mark.parametrize("H", [40, 150])
+def test_infinities_and_nans_upstream(H, bits):
+    """An upstream infinity or NaN - the NaN of 32 ones, which marks rows that are not written yet, among them - comes out as the checker's, and the call ends; trees without one are
+    as they were."""
+    print("case back non-finite", H, hex(bits), flush=True)
+    params, trees = make("lstm", H, 990, [20, 21, 22, 1], ["random", "chain", "random", "random"])
+    g_h = np.random.default_rng(7).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    clean, _, _ = backward(params, trees, g_h)
+    bad = g_h.copy()
+    node = int(trees.tree_off[1]) + 3                         # below the root of the chain
+    bad.view(np.uint32)[node, 17] = bits
+    out, h, c = backward(params, trees, bad, (-1, 0, 1))
+    ref = oracle.backward(params, trees, h, c, bad)["d_x"]
+    hit = slice(trees.tree_off[1], trees.tree_off[2])
+    for mode in (-1, 0, 1):
+        got = out[mode]["d_x"]
+        assert np.array_equal(np.isfinite(got[hit]), np.isfinite(ref[hit])), mode
+        assert not np.isfinite(got[hit]).all()
+        mask = np.ones(trees.n_nodes, bool)
+        mask[hit] = False
+        assert np.array_equal(got[mask], clean[0]["d_x"][mask]), mode
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", 72), ("rnn", 96)])
+@pytest.mark.parametrize("keep", [True, False])
+def test_backward_after_an_update_is_that_of_a_fresh_context(cell, H, keep):
+    """tl_sgd_update rebuilds the packed transposed matrices (those of the other forms when they are next used)."""
+    print("case back update", cell, H, keep, flush=True)
+    params, trees = make(cell, H, 1010, [12, 30, 1, 7], ["random"] * 4)
+    g_h = np.random.default_rng(9).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    g = torch.from_numpy(g_h).cuda()
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, keep)
+        for _ in range(2):
+            net.forward()
+            grads = binding.tl_backward(net.ctx, b, g, params.embed_dim)
+            binding.tl_sgd_update(net.ctx, 0.05, b, grads)
+        net.forward()
+        after = binding.tl_backward(net.ctx, b, g, params.embed_dim)["d_x"].cpu().numpy()
+        new = {k: v.cpu().numpy() for k, v in binding.tl_get_params(net.ctx, params.vocab, params.embed_dim, params.hidden, params.cell).items()}
+    finally:
+        net.close()
+    q = synth.Params(params.cell, params.vocab, params.embed_dim, params.hidden, new["emb"], new.get("w_leaf"), new.get("b_leaf"), new["u"], new["b"], None)
+    fresh, _, _ = backward(q, trees, g_h, keep=keep)
+    assert np.array_equal(fresh[0]["d_x"], after)
