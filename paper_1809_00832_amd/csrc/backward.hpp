@@ -499,9 +499,10 @@ inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu)
 
 struct WgSmem {
     unsigned short a[3][WG_TILE][WG_LD], b[3][WG_TILE][WG_LD];      // [term][column][node]
-    int src[2][WG_SRC];                                             // source rows of the slice's next nodes
-    int row[WG_SRC];                                                // ... and their rows of dg
+    unsigned src[2][WG_SRC];                                        // source rows of the slice's next nodes, as byte offsets (BIG: row numbers)
+    unsigned row[WG_SRC];                                           // ... and their rows of dg
 };
+constexpr unsigned WG_NOWHERE = 0xFFFF0000u;
 
 // Eight values as three vectors of bf16 terms, parked as [term][.. 8 neighbours ..].
 __device__ inline void wg_park(unsigned short (*dst)[WG_TILE][WG_LD], int col, int q, const float *x)
@@ -557,10 +558,13 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
     }
 }
 
-template <int SEG, bool RNTN = false>
+// BIG: tables of 4 GiB and more, or rows of 60 000 bytes (addresses in 64 bits: some 250 of a step's vector instructions, which the conversion leaves
+// no room for; else the byte offsets of a slice's rows lie in LDS, and rows beyond its end are beyond the end of the table and read as zeros).
+template <int SEG, bool RNTN, bool BIG>
 __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
                                                              const float *__restrict__ table, int L, const float *__restrict__ dg, int ld,
-                                                             int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+                                                             int n_cols, float *__restrict__ out, float *__restrict__ bias_out, unsigned long long table_bytes,
+                                                             unsigned long long dg_bytes)
 {
     __shared__ __align__(16) WgSmem sm;
     if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
@@ -584,53 +588,63 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WG_Q - 1) / WG_Q * WG_Q;
     const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
     if (q_lo >= q_hi) return;
-    floatx4 acc[4][4];
+    // The five lower products have sums of their own: a step rounds a large sum once, not six times (error of dU against 64 bits, H = 512, 6 772
+    // nodes: 5.7e-7 -> 5.6e-7, and 6.5e-7 without it for the nodes in the order that the lists now have).
+    floatx4 acc[4][4], low[4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 4; ++b) acc[a][b] = low[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
     // this thread stages column `col` of nodes half, half + 1, ... half + 15 of a step; columns beyond the matrix repeat its last one
     // (their results are not stored)
     const int col = tid & (WG_TILE - 1), half = (tid >> 7) * 16;
     const int k = min(k0 + col, K_out - 1), j = min(j0 + col, n_cols - 1);
     const int seg = (SEG == 2 && k >= L) ? 1 : 0, k_in = k - seg * L;
     const RntnY y = RNTN ? rntn_y(j, L) : RntnY{0, 0, 0};
-    float ra[16], rb[16];
+    float ra[16], rb[16], ry[RNTN ? 16 : 1];                 // (ry: the other factor of an RNTN column)
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
     const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
     float bsum = 0.f;
-    const int n_row = ld > 0 ? ld : n_cols;
+    const int n_row = ld > 0 ? ld : RNTN ? L : n_cols;
+    const __amdgpu_buffer_rsrc_t rs_t = buf_of(table, BIG ? 0ull : table_bytes), rs_dg = buf_of(dg, BIG ? 0ull : dg_bytes);
+    const unsigned a_off = (unsigned)k_in * 4u, b_off = (unsigned)(RNTN ? y.k : j) * 4u, y_off = (unsigned)y.in * 4u;
     auto request = [&](int q0, int chunk) {                   // operands of nodes q0 ... q0 + 31 into registers
+        if constexpr (!BIG) {
+            const unsigned *src = &sm.src[seg][q0 - chunk + half], *row = &sm.row[q0 - chunk + half], *src_y = &sm.src[y.seg > 0 ? 1 : 0][q0 - chunk + half];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            const int q = q0 + half + i;
-            const bool live = q < q_hi;
-            const int src = sm.src[seg][min(q, q_hi - 1) - chunk];
-            ra[i] = live ? table[(size_t)src * L + k_in] : 0.f;
-            if constexpr (RNTN) {
-                rb[i] = live ? dg[(size_t)q * L + y.k] : 0.f;
-                const int src_y = sm.src[y.seg > 0 ? 1 : 0][min(q, q_hi - 1) - chunk];
-                rb[i] *= live && y.seg >= 0 ? table[(size_t)src_y * L + y.in] : 1.f;
-            } else {
-                rb[i] = live ? dg[(size_t)sm.row[min(q, q_hi - 1) - chunk] * n_row + j] : 0.f;
+            for (int i = 0; i < 16; ++i) {
+                ra[i] = buf_ld_f<false>(rs_t, src[i] + a_off);
+                rb[i] = buf_ld_f<false>(rs_dg, row[i] + b_off);
+                if constexpr (RNTN) ry[i] = buf_ld_f<false>(rs_t, src_y[i] + y_off);
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int q = q0 + half + i, at = min(q, q_hi - 1) - chunk;
+                const bool live = q < q_hi;
+                ra[i] = live ? table[(size_t)sm.src[seg][at] * L + k_in] : 0.f;
+                rb[i] = live ? dg[(size_t)sm.row[at] * n_row + (RNTN ? y.k : j)] : 0.f;
+                if constexpr (RNTN) ry[i] = live ? table[(size_t)sm.src[y.seg > 0 ? 1 : 0][at] * L + y.in] : 0.f;
             }
         }
     };
     for (int chunk = q_lo; chunk < q_hi; chunk += WG_SRC) {
         const int end = min(q_hi, chunk + WG_SRC);
-        for (int i = tid; i < end - chunk; i += 256) {
-            const int node = list[chunk + i];
-            if (SEG == 2) {
-                sm.src[0][i] = f.left[node];
-                sm.src[1][i] = f.right[node];
-            } else {
-                sm.src[0][i] = f.word[node];
-            }
-            sm.row[i] = ld > 0 ? node : chunk + i;
+        for (int i = tid; i < (end - chunk + WG_Q - 1) / WG_Q * WG_Q; i += 256) {
+            const bool live = chunk + i < end;
+            const int node = list[live ? chunk + i : end - 1];
+            const unsigned unit = BIG ? 1u : (unsigned)L * 4u, row = (unsigned)(ld > 0 ? node : chunk + i) * (BIG ? 1u : (unsigned)n_row * 4u);
+            sm.src[0][i] = live ? (unsigned)(SEG == 2 ? f.left[node] : f.word[node]) * unit : WG_NOWHERE;
+            if (SEG == 2) sm.src[1][i] = live ? (unsigned)f.right[node] * unit : WG_NOWHERE;
+            sm.row[i] = live ? row : WG_NOWHERE;
         }
         __syncthreads();
         request(chunk, chunk);
         for (int q0 = chunk; q0 < end; q0 += WG_Q) {
+            if constexpr (RNTN) {                             // (here, where they are waited for anyway)
+#pragma unroll
+                for (int i = 0; i < 16; ++i) rb[i] *= y.seg >= 0 ? ry[i] : 1.f;
+            }
             wg_park(sm.a, col, half, ra);
             wg_park(sm.a, col, half + 8, ra + 8);
             wg_park(sm.b, col, half, rb);
@@ -653,26 +667,33 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
                 bf16x8 va[3];
 #pragma unroll
                 for (int m = 0; m < 3; ++m) va[m] = *reinterpret_cast<const bf16x8 *>(&sm.a[m][wr + ta * TS + (lane & 15)][8 * (lane >> 4)]);
-                constexpr int TERM[6][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};       // smallest first
+                constexpr int TERM[5][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}};       // smallest first
                 if constexpr (RNTN) {
 #pragma unroll
                     for (int tb = 0; tb < 4; ++tb)
                         if (live_tile[ta][tb]) {
 #pragma unroll
-                            for (int p = 0; p < 6; ++p)
+                            for (int p = 0; p < 5; ++p)
                                 acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+                            acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0], vb[tb][0], acc[ta][tb], 0, 0, 0);
                         }
                 } else {
 #pragma unroll
-                    for (int p = 0; p < 6; ++p)
+                    for (int p = 0; p < 5; ++p)
 #pragma unroll
-                        for (int tb = 0; tb < 4; ++tb)
-                            acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
+                        for (int tb = 0; tb < 4; ++tb) low[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], low[ta][tb], 0, 0, 0);
+#pragma unroll
+                    for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0], vb[tb][0], acc[ta][tb], 0, 0, 0);
                 }
             }
             __syncthreads();
         }
     }
+#pragma unroll
+    for (int ta = 0; ta < 4; ++ta)
+#pragma unroll
+        for (int tb = 0; tb < 4; ++tb)
+            if (!RNTN) acc[ta][tb] += low[ta][tb];
     bool again = false;
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)

@@ -1948,30 +1948,36 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     }
     // weight and bias gradients: contractions over all nodes
     typedef void (*wgrad_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, int, float *, float *);
+    typedef void (*wgrad_wide_kernel)(Fwd, const int32_t *, int, const float *, int, const float *, int, int, float *, float *, unsigned long long, unsigned long long);
     const int ld = back ? ng_cell * H : 0;                    // rows of dG by node, or by list position
-    auto weight_grad = [&](wgrad_kernel wide, wgrad_kernel small, int K_out, const int32_t *list, int rows, const float *table, int L,
-                           const float *dg, int cols, float *out, float *bias_out) {
+    auto weight_grad = [&](wgrad_wide_kernel wide, wgrad_wide_kernel big, wgrad_kernel small, int K_out, const int32_t *list, int rows, const float *table, size_t table_rows,
+                           int L, const float *dg, int dg_row, int cols, float *out, float *bias_out) {
         const WgPlan p = wg_plan(K_out, cols, rows, ctx->n_cu);
-        hipLaunchKernelGGL(p.wide ? wide : small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, ld, cols, out,
-                           bias_out);
+        const unsigned long long table_bytes = (unsigned long long)table_rows * L * 4, dg_bytes = (unsigned long long)(ld > 0 ? n_nodes : rows) * dg_row * 4;
+        const bool is_big = table_bytes >= WG_NOWHERE || dg_bytes >= WG_NOWHERE || L > 15000 || dg_row > 15000;
+        if (p.wide)
+            hipLaunchKernelGGL(is_big ? big : wide, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, ld, cols, out, bias_out, table_bytes,
+                               dg_bytes);
+        else
+            hipLaunchKernelGGL(small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, ld, cols, out, bias_out);
     };
     if (n_int > 0) {
         const bool v4 = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0);
         float *acc = rntn ? ctx->rntn_acc : d_u, *colsum = rntn ? ctx->rntn_acc + (size_t)2 * H * rntn_row : d_b;
         if (rntn_one)
-            weight_grad(k_weight_grad_wide<2, true>, v4 ? wgrad_kernel(k_weight_grad<2, true, true>) : wgrad_kernel(k_weight_grad<2, false, true>), 2 * H,
-                        f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
+            weight_grad(k_weight_grad_wide<2, true, false>, k_weight_grad_wide<2, true, true>, v4 ? wgrad_kernel(k_weight_grad<2, true, true>) : wgrad_kernel(k_weight_grad<2, false, true>), 2 * H,
+                        f.level_nodes, n_int, h, n_nodes, H, dg_int, H, dg_cols, acc, colsum);
         else
-            weight_grad(k_weight_grad_wide<2>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
-                        back ? bk.int_list : f.level_nodes, n_int, h, H, dg_int, dg_cols, acc, colsum);
+            weight_grad(k_weight_grad_wide<2, false, false>, k_weight_grad_wide<2, false, true>, v4 ? wgrad_kernel(k_weight_grad<2, true>) : wgrad_kernel(k_weight_grad<2, false>), 2 * H,
+                        back ? bk.int_list : f.level_nodes, n_int, h, n_nodes, H, dg_int, dg_cols, dg_cols, acc, colsum);
     }
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,
                            (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H, rntn_one ? 1 : 0);
     if (lstm) {
         const bool v4 = E % 4 == 0 && H % 4 == 0;
-        weight_grad(k_weight_grad_wide<1>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
-                    n_leaf, ctx->emb, E, back ? dg_int : dg_leaf, 3 * H, d_w_leaf, d_b_leaf);
+        weight_grad(k_weight_grad_wide<1, false, false>, k_weight_grad_wide<1, false, true>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
+                    n_leaf, ctx->emb, cfg.vocab, E, back ? dg_int : dg_leaf, back ? 5 * H : 3 * H, 3 * H, d_w_leaf, d_b_leaf);
     }
     TL_HIP(hipGetLastError());
     if (status_pending) {
