@@ -417,7 +417,7 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
         // (requests that are not to be made yet go beyond the end of the table: they return at once and read nothing)
         request_ex(!late, first_policy{});
         __builtin_amdgcn_sched_barrier(0);
-        // The matrix instruction drops what does not fit downwards, and a column sum over all nodes adds that up (d_b of 2000 trees at H = 512: off by
+        // The matrix instruction drops what does not fit downwards, and a column sum over all nodes adds that up (d_b of 256 parse trees at H = 512: off by
         // 3.2e-7 of its norm): every other k-step is taken with its rows negated, into a sum of its own that is subtracted.
         floatx4 acc[2][2] = {};
         halfx8 wl[2][2] = {};                           // the next k-step's weights, where they are in LDS

@@ -466,34 +466,46 @@ constexpr int WG_TILE = 128, WG_Q = 32, WG_LD = WG_Q + 8, WG_SRC = 512;
 
 // Which of the two kernels, and its grid.  A workgroup of the wide form starts with a longer chain (source rows, 64 KB of LDS,
 // no second buffer), ends with four times the atomics, and does the products of a whole tile wherever the output ends; per
-// product it needs half the reads and 6/16 of the matrix time.  Measured on 202 outputs and node counts (TreeLSTM H = 16 ... 512,
-// TreeRNN d = 16 ... 512, RNTN d = 8 ... 96; 1 to 4 096 trees of 5 to 50 leaves), time of the 64 x 64 form over that of the wide one:
-//   tiles filled to less than 62 % by the output (86)       0.48 ... 1.00, one at 1.09
-//   nodes per slice x filled share below 340 (94)           0.44 ... 0.99, and 1.01 ... 1.22 for six outputs close below that line
-//   above (22)                                              1.06 ... 1.88
-// (U at H = 512: 387 -> 303 us for 6 772 nodes, 104 -> 112 us for 1 682; W of TreeRNN at d = 256: 39 -> 57 us for 6 772,
-// 306 -> 224 us for 108 536; U at H = 48: 17 -> 19 us for 6 772.)
+// product it needs half the reads and 6/16 of the matrix time.
+// Slices of the wide form: two workgroups are resident per CU, so the grid is a number of whole rounds of 2 n_cu or of half a round (one per CU:
+// 0.72 of a full round's time), whichever is shortest when a workgroup costs its nodes and 256 more for its start and its atomics.
+// Measured (profiler, 1 / 2 / 3 / 4 / 6 / 7 slices, U of TreeLSTM at H = 512 and 6 772 nodes, 160 tiles): 454, 313, 236, 287, 261, 271 us;
+// four workgroups per CU in all, rounded up, were 7 slices, a third round for the last 96 of 1 120 workgroups.
+// RNTN takes two rounds at least: a tile's sums are one chain there, whose error grows with the nodes of a slice (d = 64, 6 772 nodes, error of d_u
+// against 64 bits: 1.00e-6 with 7 slices, 0.96e-6 with 15; 106 and 108 us).
+// The 64 x 64 form where slices of 64 nodes don't give every CU a workgroup of the wide one.  Measured on 73 outputs and node counts (TreeLSTM H = 32 ...
+// 700, TreeRNN d = 64 ... 512, RNTN d = 16 ... 96; 25 to 1 000 trees of 5 to 50 leaves), time of the 64 x 64 form over that of the wide one:
+//   fewer workgroups of the wide form than CUs (24)        0.59 ... 0.99
+//   more (49)                                              1.00 ... 2.69
 struct WgPlan {
     bool wide;
     unsigned tiles_k, tiles_j, slices;
 };
-inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu)
+inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu, bool rntn)
 {
     WgPlan p{};
-    auto cut = [&](int tile, int per_cu, int min_nodes) {
+    auto tiles_of = [&](int tile) {
         p.tiles_k = (unsigned)((K_out + tile - 1) / tile);
         p.tiles_j = (unsigned)((n_cols + tile - 1) / tile);
-        const long long tiles = (long long)p.tiles_k * p.tiles_j;
-        long long z = ((long long)per_cu * n_cu + tiles - 1) / tiles;             // that many workgroups per CU in all
-        const long long max_z = ((long long)n_rows + min_nodes - 1) / min_nodes;
-        if (z > max_z) z = max_z;
-        p.slices = (unsigned)(z < 1 ? 1 : z);
-        return tiles;
+        return (long long)p.tiles_k * p.tiles_j;
     };
-    const double tiles = (double)cut(WG_TILE, 4, 2 * WG_Q);                       // two resident at a time
-    const double filled = (double)K_out * n_cols / (tiles * WG_TILE * WG_TILE);
-    p.wide = filled >= 0.62 && (double)n_rows / p.slices * filled >= 340.0;
-    if (!p.wide) cut(WN_TILE, 8, 4 * WN_Q);
+    const auto most = [&](int nodes) { return std::max(1ll, ((long long)n_rows + nodes - 1) / nodes); };   // slices of no fewer nodes
+    const long long tiles = tiles_of(WG_TILE), max_z = most(2 * WG_Q);
+    p.wide = tiles * max_z >= n_cu;
+    if (!p.wide) {
+        const long long small = tiles_of(WN_TILE);
+        p.slices = (unsigned)std::min((8ll * n_cu + small - 1) / small, most(4 * WN_Q));
+        return p;
+    }
+    double best = 0.0;
+    for (int half = rntn ? 4 : 0; half <= 8; ++half) {                                      // (0: one slice, however many tiles there are)
+        const long long z = std::min(std::max((long long)half * n_cu / tiles, 1ll), max_z), halves = (tiles * z + n_cu - 1) / n_cu;
+        const double rounds = (double)(halves / 2) + (halves % 2 != 0 ? 0.72 : 0.0), cost = rounds * ((double)n_rows / (double)z + 256.0);
+        if (p.slices == 0 || cost < best) {
+            best = cost;
+            p.slices = (unsigned)z;
+        }
+    }
     return p;
 }
 
@@ -590,11 +602,11 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     if (q_lo >= q_hi) return;
     // The five lower products have sums of their own: a step rounds a large sum once, not six times (error of dU against 64 bits, H = 512, 6 772
     // nodes: 5.7e-7 -> 5.6e-7, and 6.5e-7 without it for the nodes in the order that the lists now have).
-    floatx4 acc[4][4], low[4][4];
+    floatx4 acc[4][4];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) acc[a][b] = low[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int b = 0; b < 4; ++b) acc[a][b] = floatx4{0.f, 0.f, 0.f, 0.f};
     // this thread stages column `col` of nodes half, half + 1, ... half + 15 of a step; columns beyond the matrix repeat its last one
     // (their results are not stored)
     const int col = tid & (WG_TILE - 1), half = (tid >> 7) * 16;
@@ -667,33 +679,29 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
                 bf16x8 va[3];
 #pragma unroll
                 for (int m = 0; m < 3; ++m) va[m] = *reinterpret_cast<const bf16x8 *>(&sm.a[m][wr + ta * TS + (lane & 15)][8 * (lane >> 4)]);
-                constexpr int TERM[5][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}};       // smallest first
+                constexpr int TERM[6][2] = {{1, 1}, {0, 2}, {2, 0}, {0, 1}, {1, 0}, {0, 0}};
                 if constexpr (RNTN) {
 #pragma unroll
                     for (int tb = 0; tb < 4; ++tb)
                         if (live_tile[ta][tb]) {
 #pragma unroll
-                            for (int p = 0; p < 5; ++p)
-                                acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
-                            acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0], vb[tb][0], acc[ta][tb], 0, 0, 0);
+                            for (int p = 0; p < 6; ++p) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], acc[ta][tb], 0, 0, 0);
                         }
                 } else {
+                    // a step's products are summed from zero, smallest first, and added to the whole with one rounding to nearest (four chains of RNTN's
+                    // tiles spill registers, and one by one they wait for each other: 101 -> 111 us)
+                    floatx4 sum[4] = {};
 #pragma unroll
-                    for (int p = 0; p < 5; ++p)
+                    for (int p = 0; p < 6; ++p)
 #pragma unroll
-                        for (int tb = 0; tb < 4; ++tb) low[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], low[ta][tb], 0, 0, 0);
+                        for (int tb = 0; tb < 4; ++tb) sum[tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[TERM[p][0]], vb[tb][TERM[p][1]], sum[tb], 0, 0, 0);
 #pragma unroll
-                    for (int tb = 0; tb < 4; ++tb) acc[ta][tb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(va[0], vb[tb][0], acc[ta][tb], 0, 0, 0);
+                    for (int tb = 0; tb < 4; ++tb) acc[ta][tb] += sum[tb];
                 }
             }
             __syncthreads();
         }
     }
-#pragma unroll
-    for (int ta = 0; ta < 4; ++ta)
-#pragma unroll
-        for (int tb = 0; tb < 4; ++tb)
-            if (!RNTN) acc[ta][tb] += low[ta][tb];
     bool again = false;
 #pragma unroll
     for (int ta = 0; ta < 4; ++ta)

@@ -1952,7 +1952,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const int ld = back ? ng_cell * H : 0;                    // rows of dG by node, or by list position
     auto weight_grad = [&](wgrad_wide_kernel wide, wgrad_wide_kernel big, wgrad_kernel small, int K_out, const int32_t *list, int rows, const float *table, size_t table_rows,
                            int L, const float *dg, int dg_row, int cols, float *out, float *bias_out) {
-        const WgPlan p = wg_plan(K_out, cols, rows, ctx->n_cu);
+        const WgPlan p = wg_plan(K_out, cols, rows, ctx->n_cu, rntn);
         const unsigned long long table_bytes = (unsigned long long)table_rows * L * 4, dg_bytes = (unsigned long long)(ld > 0 ? n_nodes : rows) * dg_row * 4;
         const bool is_big = table_bytes >= WG_NOWHERE || dg_bytes >= WG_NOWHERE || L > 15000 || dg_row > 15000;
         if (p.wide)
