@@ -307,20 +307,21 @@ __device__ inline RntnY rntn_y(int j, int d)
     return RntnY{k, q >= d ? 1 : 0, q >= d ? q - d : q};
 }
 
-template <int SEG, bool VEC4, bool RNTN = false>
-__global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows,
-                                                     const float *__restrict__ table, int L, const float *__restrict__ dg,
-                                                     int ld, int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+struct WnSmem {
+    float as[2][WN_Q][WN_LD], bs[2][WN_Q][WN_LD];               // two buffers each: a step's operands are parked while the
+};                                                              // step before is still being multiplied (one barrier per step)
+template <int SEG, bool VEC4, bool RNTN>
+__device__ __forceinline__ void weight_grad_tile(WnSmem &sm, int bx, int by, int bz, int nz, const Fwd &f, const int32_t *__restrict__ list, int n_rows,
+                                                 const float *__restrict__ table, int L, const float *__restrict__ dg, int ld, int n_cols,
+                                                 float *__restrict__ out, float *__restrict__ bias_out)
 {
-    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
-    __shared__ __align__(16) float as[2][WN_Q][WN_LD];         // two buffers each: a step's operands are parked while the
-    __shared__ __align__(16) float bs[2][WN_Q][WN_LD];         // step before is still being multiplied (one barrier per step)
+    auto &as = sm.as, &bs = sm.bs;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k0 = blockIdx.x * WN_TILE, j0 = blockIdx.y * WN_TILE;
+    const int k0 = bx * WN_TILE, j0 = by * WN_TILE;
     const int K_out = SEG * L;
     const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32;
-    const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WN_Q - 1) / WN_Q * WN_Q;
-    const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
+    const int per = ((n_rows + nz - 1) / nz + WN_Q - 1) / WN_Q * WN_Q;
+    const int q_lo = bz * per, q_hi = min(n_rows, q_lo + per);
     if (q_lo >= q_hi) return;
     floatx4 acc[2][2];
 #pragma unroll
@@ -330,7 +331,7 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
     const int lq = tid >> 4, lk = (tid & 15) * 4;             // this thread stages 4 consecutive columns of row lq
     float ra[4], rb[4];
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
-    const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
+    const bool with_bias = bias_out != nullptr && bx == 0;
     float bsum[4] = {0.f, 0.f, 0.f, 0.f};
     // The operands of a step (16 nodes) hang on a chain of three loads: the node from the list, its source rows from
     // the child (or word) arrays, the data from those rows.  A step has only 16 MFMAs per wave to hide it, so the chain
@@ -448,6 +449,15 @@ __global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__res
     }
 }
 
+template <int SEG, bool VEC4, bool RNTN = false>
+__global__ __launch_bounds__(256) void k_weight_grad(Fwd f, const int32_t *__restrict__ list, int n_rows, const float *__restrict__ table, int L,
+                                                     const float *__restrict__ dg, int ld, int n_cols, float *__restrict__ out, float *__restrict__ bias_out)
+{
+    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
+    __shared__ __align__(16) WnSmem sm;
+    weight_grad_tile<SEG, VEC4, RNTN>(sm, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, f, list, n_rows, table, L, dg, ld, n_cols, out, bias_out);
+}
+
 // The one for large outputs and many nodes: one workgroup per 128 x 128 tile of the output and slice, wave w on the
 // 64 x 64 quarter (w / 2, w % 2).
 // The contraction runs over the nodes on the 16-bit matrix unit with fp32 operands: a value is the sum of three bf16 terms
@@ -481,30 +491,67 @@ struct WgPlan {
     bool wide;
     unsigned tiles_k, tiles_j, slices;
 };
+inline long long wg_slices(int n_rows, int nodes) { return std::max(1ll, ((long long)n_rows + nodes - 1) / nodes); }       // of no fewer nodes
+inline long long wg_tiles(WgPlan &p, int K_out, int n_cols, int tile)
+{
+    p.tiles_k = (unsigned)((K_out + tile - 1) / tile);
+    p.tiles_j = (unsigned)((n_cols + tile - 1) / tile);
+    return (long long)p.tiles_k * p.tiles_j;
+}
+// slices of the wide form for that many tiles, and what they cost (in nodes)
+inline double wg_rounds(long long tiles, int n_rows, long long max_z, int n_cu, bool rntn, unsigned *slices)
+{
+    double best = 0.0;
+    *slices = 0;
+    for (int half = rntn ? 4 : 0; half <= 8; ++half) {                            // (0: one slice, however many tiles there are)
+        const long long z = std::min(std::max((long long)half * n_cu / tiles, 1ll), max_z), halves = (tiles * z + n_cu - 1) / n_cu;
+        const double rounds = (double)(halves / 2) + (halves % 2 != 0 ? 0.72 : 0.0), cost = rounds * ((double)n_rows / (double)z + 256.0);
+        if (*slices == 0 || cost < best) {
+            best = cost;
+            *slices = (unsigned)z;
+        }
+    }
+    return best;
+}
+inline void wg_small(WgPlan &p, int K_out, int n_cols, int n_rows, int n_cu)
+{
+    const long long small = wg_tiles(p, K_out, n_cols, WN_TILE);
+    p.wide = false;
+    p.slices = (unsigned)std::min((8ll * n_cu + small - 1) / small, wg_slices(n_rows, 4 * WN_Q));
+}
 inline WgPlan wg_plan(int K_out, int n_cols, int n_rows, int n_cu, bool rntn)
 {
     WgPlan p{};
-    auto tiles_of = [&](int tile) {
-        p.tiles_k = (unsigned)((K_out + tile - 1) / tile);
-        p.tiles_j = (unsigned)((n_cols + tile - 1) / tile);
-        return (long long)p.tiles_k * p.tiles_j;
-    };
-    const auto most = [&](int nodes) { return std::max(1ll, ((long long)n_rows + nodes - 1) / nodes); };   // slices of no fewer nodes
-    const long long tiles = tiles_of(WG_TILE), max_z = most(2 * WG_Q);
+    const long long tiles = wg_tiles(p, K_out, n_cols, WG_TILE), max_z = wg_slices(n_rows, 2 * WG_Q);
     p.wide = tiles * max_z >= n_cu;
-    if (!p.wide) {
-        const long long small = tiles_of(WN_TILE);
-        p.slices = (unsigned)std::min((8ll * n_cu + small - 1) / small, most(4 * WN_Q));
-        return p;
-    }
-    double best = 0.0;
-    for (int half = rntn ? 4 : 0; half <= 8; ++half) {                                      // (0: one slice, however many tiles there are)
-        const long long z = std::min(std::max((long long)half * n_cu / tiles, 1ll), max_z), halves = (tiles * z + n_cu - 1) / n_cu;
-        const double rounds = (double)(halves / 2) + (halves % 2 != 0 ? 0.72 : 0.0), cost = rounds * ((double)n_rows / (double)z + 256.0);
-        if (p.slices == 0 || cost < best) {
-            best = cost;
-            p.slices = (unsigned)z;
-        }
+    if (p.wide) wg_rounds(tiles, n_rows, max_z, n_cu, rntn, &p.slices);
+    else wg_small(p, K_out, n_cols, n_rows, n_cu);
+    return p;
+}
+// The two gradients of TreeLSTM (U's: 2 H x 5 H over n_int nodes, W_leaf's: E x 3 H over n_leaf) in one launch: in the wide form, with the same number
+// of slices, where the tiles of both fill the chip and one launch's rounds are no longer than those of two; in the 64 x 64 form where not
+// even both together fill it.  Measured (profiler): 25 parse trees at H = 150 22 + 15 us apart (64 x 64), 34 in one launch of that form, 26.7 of
+// the wide one; 256 at H = 512 226 + 65 us apart, which one launch's rounds would exceed.
+struct WgPair {
+    bool one;
+    WgPlan u, w;
+};
+inline WgPair wg_pair(int H, int E, int n_int, int n_leaf, int n_cu)
+{
+    WgPair p{};
+    const long long tiles_u = wg_tiles(p.u, 2 * H, 5 * H, WG_TILE), tiles_w = wg_tiles(p.w, E, 3 * H, WG_TILE);
+    const long long z_u = wg_slices(n_int, 2 * WG_Q), z_w = wg_slices(n_leaf, 2 * WG_Q), max_z = std::min(z_u, z_w);
+    const long long tiles = tiles_u + tiles_w;
+    if (tiles * max_z >= n_cu) {
+        unsigned z = 0, zu = 0, zw = 0;
+        const double apart = wg_rounds(tiles_u, n_int, z_u, n_cu, false, &zu) + wg_rounds(tiles_w, n_leaf, z_w, n_cu, false, &zw);
+        p.one = wg_rounds(tiles, std::max(n_int, n_leaf), max_z, n_cu, false, &z) <= apart;
+        p.u.wide = p.w.wide = true;
+        p.u.slices = p.w.slices = z;
+    } else {
+        wg_small(p.u, 2 * H, 5 * H, n_int, n_cu);
+        wg_small(p.w, E, 3 * H, n_leaf, n_cu);
+        p.one = tiles_u * z_u < n_cu && tiles_w * z_w < n_cu;
     }
     return p;
 }
@@ -573,15 +620,13 @@ __device__ __forceinline__ void wg_sums_again(const Fwd &f, const int32_t *list,
 // BIG: tables of 4 GiB and more, or rows of 60 000 bytes (addresses in 64 bits: some 250 of a step's vector instructions, which the conversion leaves
 // no room for; else the byte offsets of a slice's rows lie in LDS, and rows beyond its end are beyond the end of the table and read as zeros).
 template <int SEG, bool RNTN, bool BIG>
-__global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
-                                                             const float *__restrict__ table, int L, const float *__restrict__ dg, int ld,
-                                                             int n_cols, float *__restrict__ out, float *__restrict__ bias_out, unsigned long long table_bytes,
-                                                             unsigned long long dg_bytes)
+__device__ __forceinline__ void weight_grad_wide_tile(WgSmem &sm, int bx, int by, int bz, int nz, const Fwd &f, const int32_t *__restrict__ list, int n_rows,
+                                                      const float *__restrict__ table, int L, const float *__restrict__ dg, int ld,
+                                                      int n_cols, float *__restrict__ out, float *__restrict__ bias_out, unsigned long long table_bytes,
+                                                      unsigned long long dg_bytes)
 {
-    __shared__ __align__(16) WgSmem sm;
-    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int k0 = blockIdx.x * WG_TILE, j0 = blockIdx.y * WG_TILE;
+    const int k0 = bx * WG_TILE, j0 = by * WG_TILE;
     const int K_out = SEG * L;
     // RNTN: dV is symmetric, so only tiles of 16 x 16 that hold a p <= q are computed; the tiles of the four waves are interleaved, so that
     // each has at most ten of its sixteen (36 of 64 in all).
@@ -597,8 +642,8 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
             for (int ta = 0; ta < 4; ++ta) live_tile[ta][tb] = k0 + wr + ta * TS <= top;
         }
     }
-    const int per = ((n_rows + (int)gridDim.z - 1) / (int)gridDim.z + WG_Q - 1) / WG_Q * WG_Q;
-    const int q_lo = blockIdx.z * per, q_hi = min(n_rows, q_lo + per);
+    const int per = ((n_rows + nz - 1) / nz + WG_Q - 1) / WG_Q * WG_Q;
+    const int q_lo = bz * per, q_hi = min(n_rows, q_lo + per);
     if (q_lo >= q_hi) return;
     // The five lower products have sums of their own: a step rounds a large sum once, not six times (error of dU against 64 bits, H = 512, 6 772
     // nodes: 5.7e-7 -> 5.6e-7, and 6.5e-7 without it for the nodes in the order that the lists now have).
@@ -615,7 +660,7 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
     const RntnY y = RNTN ? rntn_y(j, L) : RntnY{0, 0, 0};
     float ra[16], rb[16], ry[RNTN ? 16 : 1];                 // (ry: the other factor of an RNTN column)
     // the workgroups of the first row of output tiles also sum the columns of dg they pass over (bias gradient)
-    const bool with_bias = bias_out != nullptr && blockIdx.x == 0;
+    const bool with_bias = bias_out != nullptr && bx == 0;
     float bsum = 0.f;
     const int n_row = ld > 0 ? ld : RNTN ? L : n_cols;
     const __amdgpu_buffer_rsrc_t rs_t = buf_of(table, BIG ? 0ull : table_bytes), rs_dg = buf_of(dg, BIG ? 0ull : dg_bytes);
@@ -727,6 +772,55 @@ __global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_
         if (tid >= WG_TILE) part[col] = bsum;
         __syncthreads();
         if (tid < WG_TILE && j0 + col < n_cols) atomicAdd(&bias_out[j0 + col], bsum + part[col]);
+    }
+}
+
+template <int SEG, bool RNTN, bool BIG>
+__global__ __launch_bounds__(256, 2) void k_weight_grad_wide(Fwd f, const int32_t *__restrict__ list, int n_rows,
+                                                             const float *__restrict__ table, int L, const float *__restrict__ dg, int ld,
+                                                             int n_cols, float *__restrict__ out, float *__restrict__ bias_out, unsigned long long table_bytes,
+                                                             unsigned long long dg_bytes)
+{
+    if (batch_rejected(f)) return;
+    __shared__ __align__(16) WgSmem sm;
+    weight_grad_wide_tile<SEG, RNTN, BIG>(sm, blockIdx.x, blockIdx.y, blockIdx.z, gridDim.z, f, list, n_rows, table, L, dg, ld, n_cols, out, bias_out, table_bytes, dg_bytes);
+}
+
+// Both gradients of TreeLSTM, U's and W_leaf's, in one launch: they need nothing of each other (WgPair says when).
+struct WgradArgs {
+    const int32_t *list;
+    const float *table, *dg;
+    float *out, *bias_out;
+    int n_rows, L, n_cols, tiles_k, tiles_j, slices;
+    unsigned long long table_bytes, dg_bytes;
+};
+template <bool VEC4>
+__global__ __launch_bounds__(256) void k_weight_grad_both(Fwd f, WgradArgs u, WgradArgs w, int ld)
+{
+    if (batch_rejected(f)) return;
+    __shared__ __align__(16) WnSmem sm;
+    const int n_u = u.tiles_k * u.tiles_j * u.slices, b = (int)blockIdx.x < n_u ? (int)blockIdx.x : (int)blockIdx.x - n_u;
+    if ((int)blockIdx.x < n_u) {
+        const int t = b / u.tiles_k;
+        weight_grad_tile<2, VEC4, false>(sm, b - t * u.tiles_k, t % u.tiles_j, t / u.tiles_j, u.slices, f, u.list, u.n_rows, u.table, u.L, u.dg, ld, u.n_cols, u.out, u.bias_out);
+    } else {
+        const int t = b / w.tiles_k;
+        weight_grad_tile<1, VEC4, false>(sm, b - t * w.tiles_k, t % w.tiles_j, t / w.tiles_j, w.slices, f, w.list, w.n_rows, w.table, w.L, w.dg, ld, w.n_cols, w.out, w.bias_out);
+    }
+}
+__global__ __launch_bounds__(256, 2) void k_weight_grad_wide_both(Fwd f, WgradArgs u, WgradArgs w, int ld)
+{
+    if (batch_rejected(f)) return;
+    __shared__ __align__(16) WgSmem sm;
+    const int n_u = u.tiles_k * u.tiles_j * u.slices, b = (int)blockIdx.x < n_u ? (int)blockIdx.x : (int)blockIdx.x - n_u;
+    if ((int)blockIdx.x < n_u) {
+        const int t = b / u.tiles_k;
+        weight_grad_wide_tile<2, false, false>(sm, b - t * u.tiles_k, t % u.tiles_j, t / u.tiles_j, u.slices, f, u.list, u.n_rows, u.table, u.L, u.dg, ld, u.n_cols, u.out,
+                                               u.bias_out, u.table_bytes, u.dg_bytes);
+    } else {
+        const int t = b / w.tiles_k;
+        weight_grad_wide_tile<1, false, false>(sm, b - t * w.tiles_k, t % w.tiles_j, t / w.tiles_j, w.slices, f, w.list, w.n_rows, w.table, w.L, w.dg, ld, w.n_cols, w.out,
+                                               w.bias_out, w.table_bytes, w.dg_bytes);
     }
 }
 

@@ -1961,8 +1961,24 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         else
             hipLaunchKernelGGL(small, dim3(p.tiles_k, p.tiles_j, p.slices), dim3(256), 0, st, f, list, rows, table, L, dg, ld, cols, out, bias_out);
     };
-    if (n_int > 0) {
-        const bool v4 = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0);
+    const bool v4_u = H % 4 == 0 && dg_cols % 4 == 0 && (((uintptr_t)h & 15) == 0), v4_leaf = E % 4 == 0 && H % 4 == 0;
+    bool both = false;
+    if (lstm && n_int > 0) {
+        const WgPair p = wg_pair(H, E, n_int, n_leaf, ctx->n_cu);
+        auto args = [&](const WgPlan &q, const int32_t *list, const float *table, size_t table_rows, const float *dg, float *out, float *bias_out, int rows, int L, int cols, int dg_row) {
+            return WgradArgs{list, table, dg, out, bias_out, rows, L, cols, (int)q.tiles_k, (int)q.tiles_j, (int)q.slices,
+                             (unsigned long long)table_rows * L * 4, (unsigned long long)(ld > 0 ? n_nodes : rows) * dg_row * 4};
+        };
+        const WgradArgs u = args(p.u, back ? bk.int_list : f.level_nodes, h, n_nodes, dg_int, d_u, d_b, n_int, H, 5 * H, 5 * H);
+        const WgradArgs w = args(p.w, f.leaf_list, ctx->emb, cfg.vocab, back ? dg_int : dg_leaf, d_w_leaf, d_b_leaf, n_leaf, E, 3 * H, back ? 5 * H : 3 * H);
+        const unsigned long long grid = (unsigned long long)p.u.tiles_k * p.u.tiles_j * p.u.slices + (unsigned long long)p.w.tiles_k * p.w.tiles_j * p.w.slices;
+        const bool is_big = std::max(std::max(u.table_bytes, u.dg_bytes), std::max(w.table_bytes, w.dg_bytes)) >= WG_NOWHERE || std::max(E, 5 * H) > 15000;
+        both = p.one && grid < 0x80000000ull && (p.u.wide ? !is_big : v4_u == v4_leaf);
+        if (both && p.u.wide) hipLaunchKernelGGL(k_weight_grad_wide_both, dim3((unsigned)grid), dim3(256), 0, st, f, u, w, ld);
+        else if (both) hipLaunchKernelGGL(v4_u ? k_weight_grad_both<true> : k_weight_grad_both<false>, dim3((unsigned)grid), dim3(256), 0, st, f, u, w, ld);
+    }
+    if (n_int > 0 && !both) {
+        const bool v4 = v4_u;
         float *acc = rntn ? ctx->rntn_acc : d_u, *colsum = rntn ? ctx->rntn_acc + (size_t)2 * H * rntn_row : d_b;
         if (rntn_one)
             weight_grad(k_weight_grad_wide<2, true, false>, k_weight_grad_wide<2, true, true>, v4 ? wgrad_kernel(k_weight_grad<2, true, true>) : wgrad_kernel(k_weight_grad<2, false, true>), 2 * H,
@@ -1974,8 +1990,8 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     if (rntn)      // back into the layouts of V, W and b (all zero when the batch has no internal node)
         hipLaunchKernelGGL(k_rntn_unpack, dim3(1024), dim3(256), 0, st, (const float *)ctx->rntn_acc,
                            (const float *)(ctx->rntn_acc + (size_t)2 * H * rntn_row), d_w_leaf, d_u, d_b, H, rntn_one ? 1 : 0);
-    if (lstm) {
-        const bool v4 = E % 4 == 0 && H % 4 == 0;
+    if (lstm && !both) {
+        const bool v4 = v4_leaf;
         weight_grad(k_weight_grad_wide<1, false, false>, k_weight_grad_wide<1, false, true>, v4 ? wgrad_kernel(k_weight_grad<1, true>) : wgrad_kernel(k_weight_grad<1, false>), E, f.leaf_list,
                     n_leaf, ctx->emb, cfg.vocab, E, back ? dg_int : dg_leaf, back ? 5 * H : 3 * H, 3 * H, d_w_leaf, d_b_leaf);
     }

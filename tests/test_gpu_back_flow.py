@@ -140,3 +140,17 @@ def test_backward_after_an_update_is_that_of_a_fresh_context(cell, H, keep):
     q = synth.Params(params.cell, params.vocab, params.embed_dim, params.hidden, new["emb"], new.get("w_leaf"), new.get("b_leaf"), new["u"], new["b"], None)
     fresh, _, _ = backward(q, trees, g_h, keep=keep)
     assert np.array_equal(fresh[0]["d_x"], after)
+
+
+# (H, E, trees of 20 leaves): both products in one launch of the 64 x 64 form with and without 16-byte loads, apart in that form (only one has them), just below and above the
+# line from which one launch of the wide form fills the chip (slices of 64 nodes times 30 tiles: from 9 on), and well above with ragged tiles of either matrix
+@pytest.mark.parametrize("H,E,n_trees", [(40, 24, 3), (41, 23, 3), (40, 23, 3), (150, 300, 26), (150, 300, 28), (131, 129, 60), (200, 31, 60)])
+def test_weight_gradients_of_both_matrices(H, E, n_trees):
+    print("case both weight gradients", H, E, n_trees, flush=True)
+    params, trees = make("lstm", H, 700 + H + n_trees, [20] * n_trees, ["random"] * n_trees, E)
+    g_h = np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    for keep in (True, False):                                # (rows of gate gradients by node, and by list position)
+        out, h, c = backward(params, trees, g_h, keep=keep)
+        ref = oracle.backward(params, trees, h, c, g_h)
+        for k in ref:                                         # sums of at most 1 200 products, fp32: 1200 * 2^-24 = 7e-5 of the largest at worst
+            np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
