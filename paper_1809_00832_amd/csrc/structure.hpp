@@ -135,7 +135,7 @@ __global__ void k_reset(Fwd f, int with_levels)
 // Leaves are evaluated by a kernel of their own before any internal node, so pending[] counts
 // internal children only, and an internal node whose children are both leaves starts ready.
 // int_list: null, or (backward pass) receives the internal nodes, in no particular order.
-__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f, int32_t *int_list)
+__device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list)
 {
     __shared__ int s_cnt[APPEND_SCRATCH];
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -179,6 +179,9 @@ __global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f, int32_t *int_list
         if (inner && slot < f.n_int) int_list[slot] = n;
     }
 }
+// (two kernels: a second argument behind Fwd costs a launch-bound forward 1 us of 20)
+__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f) { scatter_nodes(f, nullptr); }
+__global__ __launch_bounds__(NODE_BLOCK) void k_scatter_list(Fwd f, int32_t *int_list) { scatter_nodes(f, int_list); }
 
 // One thread per node: the node nobody points to is its tree's root; there must be exactly one.
 __global__ __launch_bounds__(NODE_BLOCK) void k_roots(Fwd f)
@@ -360,7 +363,7 @@ __global__ void k_scan_levels(Fwd f)
 
 // One thread per node: append every reached internal node to the list of its height.
 // place_of: null, or (backward pass) see SchedPlaces.
-__global__ void k_fill_levels(Fwd f, int2 *place_of)
+__device__ __forceinline__ void fill_levels(const Fwd &f, int2 *place_of)
 {
     __shared__ int s_hist[HIST_BINS];
     __shared__ int s_base[HIST_BINS];
@@ -387,6 +390,8 @@ __global__ void k_fill_levels(Fwd f, int2 *place_of)
         }
     }
 }
+__global__ void k_fill_levels(Fwd f) { fill_levels(f, nullptr); }
+__global__ void k_fill_places(Fwd f, int2 *place_of) { fill_levels(f, place_of); }
 
 // h_root / c_root / root outputs.
 __global__ void k_root_gather(Fwd f)

@@ -1510,13 +1510,13 @@ int forward_impl(tl_ctx *ctx, bool static_ws, int n_trees, int n_nodes, const in
     // (the data-flow scheduler's fill of the rows of internal nodes takes one wave per node)
     const int nb_reset = f.flow == 1 ? (n_nodes / 4 + 1 < 256 ? 256 : (n_nodes / 4 + 1 > 4096 ? 4096 : n_nodes / 4 + 1)) : 256;
     hipLaunchKernelGGL(k_reset, dim3(nb_reset), dim3(256), 0, st, f, need_levels ? 1 : 0);
-    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, (int32_t *)nullptr);
+    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
     if (!f.flow_roots) hipLaunchKernelGGL(k_roots, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
     if (need_levels) {
         hipLaunchKernelGGL(k_climb, dim3((f.n_leaf + 255) / 256), dim3(256), 0, st, f);
         hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, f);
         hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, f);
-        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, f, (int2 *)nullptr);
+        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, f);
     }
     if (f.priority && f.n_int > 0) {
         hipLaunchKernelGGL(k_depth_walk, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
@@ -1763,7 +1763,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // structure pass; with heights and per-height lists (as for the host-driven level scheduler) where something walks the heights
     const bool need_levels = !back || launches || back_either;
     hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, need_levels ? 1 : 0);
-    hipLaunchKernelGGL(k_scatter, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list);
+    hipLaunchKernelGGL(k_scatter_list, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list);
     if (need_levels) {
         Fwd fl = f;
         fl.pick = back_either ? 2 : 0;
@@ -1771,7 +1771,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         hipLaunchKernelGGL(k_climb, dim3((n_leaf + 255) / 256), dim3(256), 0, st, fl);
         hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, fl);
         hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, fl);
-        hipLaunchKernelGGL(k_fill_levels, dim3(nb_nodes), dim3(256), 0, st, fl, bk.at.of);
+        hipLaunchKernelGGL(k_fill_places, dim3(nb_nodes), dim3(256), 0, st, fl, bk.at.of);
     }
     if (back) {
         ClearList z{};
