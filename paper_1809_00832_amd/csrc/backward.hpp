@@ -154,6 +154,7 @@ __device__ inline void gate_grad_kept_rows(const Fwd &f, const int32_t *__restri
 template <bool INNER, int V>
 __global__ __launch_bounds__(256) void k_gate_grad_kept(Fwd f, const int32_t *__restrict__ list, int n_rows, int pos0)
 {
+    if (batch_rejected(f)) return;                            // (the lists of a malformed batch are not complete)
     gate_grad_kept_rows<INNER, V, false>(f, list, n_rows, pos0, (long long)blockIdx.x * blockDim.x + threadIdx.x,
                                          (long long)gridDim.x * blockDim.x);
 }
@@ -196,6 +197,7 @@ __global__ __launch_bounds__(256) void k_rnn_gate_grad(Fwd f, const int32_t *__r
 // TreeRNN leaves: the embedding row is the state itself, so its gradient is the row of dh.
 __global__ void k_rnn_leaf_grad(Fwd f)
 {
+    if (batch_rejected(f)) return;                            // (its leaf list is not complete)
     const size_t total = (size_t)f.n_leaf * f.H;
     for (size_t e = (size_t)blockIdx.x * blockDim.x + threadIdx.x; e < total; e += (size_t)gridDim.x * blockDim.x) {
         const int i = (int)(e / f.H), j = (int)(e - (size_t)i * f.H);

@@ -267,3 +267,31 @@ def test_errors_found_by_one_slot_beside_the_others(what):
     kw = dict(precision=binding.TL_BF16_IN) if "bf16" in what else {}
     for _ in range(2 if large else 6):
         run_expect(p, bad, "dataflow", binding.TL_ESTRUCT, **kw)
+
+
+@pytest.mark.parametrize("cell,H,mode", [("rntn", 16, 0), ("rntn", 16, 1), ("rnn", 520, 1), ("lstm", 520, 1)])
+def test_backward_without_a_leaf_list(cell, H, mode):
+    """No leaf has a valid word, so the leaf list holds nothing: where the call does not wait for the structure pass, no kernel behind it may look there."""
+    print("case backward without a leaf list", cell, H, mode, flush=True)
+    if cell == "lstm":
+        p = synth.make_treelstm_params(1, 50, 8, H, "xavier")
+    else:
+        p = synth.make_rnn_params(5, synth.CELL_RNTN if cell == "rntn" else synth.CELL_TREERNN, 50, H, scale=0.02)
+    t = good_trees()
+    bad = TreeBatch(t.tree_off, t.left, t.right, np.full_like(t.word, 50))
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        b = net.load(bad)
+        binding.tl_set_keep_gates(net.ctx, True)
+        binding.tl_set_async_backward(net.ctx, mode)
+        net.forward()
+        g_h = torch.ones((b["N"], H), device="cuda")
+        code = binding.TL_OK
+        try:
+            binding.tl_backward(net.ctx, b, g_h, p.embed_dim, rntn=cell == "rntn")
+        except binding.TLError as e:
+            code = e.code
+        assert code == (binding.TL_ESTRUCT if cell == "rntn" else binding.TL_OK)
+        assert binding.tl_status(net.ctx) == binding.TL_ESTRUCT
+    finally:
+        net.close()
