@@ -1238,6 +1238,15 @@ void td_free(tl_td_ctx *ctx)
     delete ctx;
 }
 
+// What a copy of the control block says about the batch of `f`, beyond the status that a kernel latched.  Where nobody counts the roots beforehand
+// (flow_roots) every kernel behind the structure pass leaves a batch whose leaves are not as many as N and B say (batch_rejected), the one that looks for the
+// roots among them; elsewhere a tree without a root shows as a root count below the number of trees.
+int batch_status(const Ctl *ctl, const Fwd &f)
+{
+    if (ctl->status != 0) return ctl->status;
+    return (f.flow_roots ? ctl->n_leaf_seen != f.n_leaf : ctl->n_roots != f.n_trees) ? TL_ESTRUCT : TL_OK;
+}
+
 // levels > 0: the first `levels` offsets of the per-height lists come along in the same wait (shallow batches then need no
 // second round trip for them).
 int read_ctl(tl_ctx *ctx, int levels = 0)
@@ -1246,8 +1255,7 @@ int read_ctl(tl_ctx *ctx, int levels = 0)
     if (levels > 0)
         TL_HIP(hipMemcpyAsync(ctx->host_levels, ctx->last.level_off, (size_t)levels * 4, hipMemcpyDeviceToHost, ctx->last_stream));
     TL_HIP(hipStreamSynchronize(ctx->last_stream));
-    // a tree without a root shows as a root count below the number of trees
-    if (ctx->host_ctl->status == 0 && !ctx->last.flow_roots && ctx->host_ctl->n_roots != ctx->last.n_trees) ctx->host_ctl->status = TL_ESTRUCT;
+    ctx->host_ctl->status = batch_status(ctx->host_ctl, ctx->last);
     return TL_OK;
 }
 
@@ -1998,8 +2006,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     TL_HIP(hipGetLastError());
     if (status_pending) {
         TL_HIP(hipEventSynchronize(ctx->ev_ctl));
-        if (ctx->host_ctl->status == 0 && !f.flow_roots && ctx->host_ctl->n_roots != n_trees) ctx->host_ctl->status = TL_ESTRUCT;
-        if (ctx->host_ctl->status != 0) return ctx->host_ctl->status;
+        if ((rc = batch_status(ctx->host_ctl, f)) != TL_OK) return rc;
     }
     return TL_OK;
 }

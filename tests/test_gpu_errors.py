@@ -295,3 +295,64 @@ def test_backward_without_a_leaf_list(cell, H, mode):
         assert binding.tl_status(net.ctx) == binding.TL_ESTRUCT
     finally:
         net.close()
+
+
+def batch_with_too_many_leaves(n_good):
+    """Good trees around a range of three leaves without a parent: N + B stays even, and nothing but the number of leaves is wrong."""
+    if n_good == 0:
+        return TreeBatch(np.array([0, 3], np.int32), np.full(3, -1, np.int32), np.full(3, -1, np.int32), np.full(3, 7, np.int32))
+    t = synth.make_trees(11, [6] * n_good, ["random"] * n_good, 50)
+    cut = int(t.tree_off[n_good // 2])
+    move = lambda a: np.where(a >= cut, a + 3, a)
+    put = lambda a, v: np.concatenate([a[:cut], np.full(3, v), a[cut:]]).astype(np.int32)
+    off = np.concatenate([t.tree_off[:n_good // 2 + 1], t.tree_off[n_good // 2:] + 3]).astype(np.int32)
+    return TreeBatch(off, put(move(t.left), -1), put(move(t.right), -1), put(t.word, 7))
+
+
+@pytest.mark.parametrize("n_good", [0, 40])
+@pytest.mark.parametrize("what", ["lstm", "lstm bf16", "rnn", "rnn bf16", "rntn"])
+def test_too_many_leaves(what, n_good):
+    """Every kernel leaves such a batch; the status says so although none of them has latched anything."""
+    print("case too many leaves", what, n_good, flush=True)
+    if "lstm" in what:
+        p = small_params()
+    else:
+        p = synth.make_rnn_params(5, synth.CELL_RNTN if what == "rntn" else synth.CELL_TREERNN, 50, 16, scale=0.4)
+    bad = batch_with_too_many_leaves(n_good)
+    assert (bad.n_nodes + bad.n_trees) % 2 == 0 and (bad.left < 0).sum() * 2 == bad.n_nodes + bad.n_trees + 2
+    kw = dict(precision=binding.TL_BF16_IN) if "bf16" in what else {}
+    for sched in SCHEDULERS:
+        run_expect(p, bad, sched, binding.TL_ESTRUCT, **kw)
+
+
+@pytest.mark.parametrize("make_bad", [lambda: batch_with_too_many_leaves(0), lambda: batch_with_too_many_leaves(40), cyclic_batch, lambda: batch_with_wrong_roots(40, 20, 50)],
+                         ids=["three leaves", "three leaves among trees", "cycle", "roots"])
+@pytest.mark.parametrize("cell", ["lstm", "rnn", "rntn"])
+@pytest.mark.parametrize("keep", [True, False])
+def test_backward_of_a_malformed_batch(cell, keep, make_bad):
+    """tl_backward returns TL_ESTRUCT (modes -1 and 0), or tl_status does afterwards (mode 1, where the call does not wait)."""
+    print("case backward of a malformed batch", cell, keep, flush=True)
+    bad = make_bad()
+    if cell == "lstm":
+        p = small_params()
+    else:
+        p = synth.make_rnn_params(5, synth.CELL_RNTN if cell == "rntn" else synth.CELL_TREERNN, 50, 16, scale=0.4)
+    net = binding.TreeNet(p, scheduler="dataflow")
+    try:
+        for mode in (0, 1, -1):
+            b = net.load(bad)
+            binding.tl_set_keep_gates(net.ctx, keep)
+            binding.tl_set_async_backward(net.ctx, mode)
+            net.forward()                                     # (rejected as well: what it would keep is never read)
+            g_h = torch.ones((b["N"], p.hidden), device="cuda")
+            code = binding.TL_OK
+            try:
+                binding.tl_backward(net.ctx, b, g_h, p.embed_dim, rntn=cell == "rntn")
+            except binding.TLError as e:
+                code = e.code
+            if code == binding.TL_OK and mode == 1:
+                code = binding.tl_status(net.ctx)
+            assert code == binding.TL_ESTRUCT, (mode, binding.tl_strerror(code))
+            assert binding.tl_status(net.ctx) == binding.TL_ESTRUCT, mode
+    finally:
+        net.close()
