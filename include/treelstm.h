@@ -307,7 +307,9 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
  * are those tl_backward wrote (DEVICE, read-only); left / word / n_nodes are the batch's arrays.
  * d_x may be NULL: the embedding table then stays as it is.  Afterwards everything derived from
  * the parameters (packed weights of the forward and backward kernels) is rebuilt; all of it is
- * enqueued on hip_stream and nothing is allocated.  Dense parameters change exactly as the
+ * enqueued on hip_stream and nothing is allocated.  (What only some backward passes read - the fp32
+ * matrices where H <= 512, those of RNTN's launches per height - is rebuilt by the next one that needs it;
+ * a captured backward pass always records that.)  Dense parameters change exactly as the
  * formula says in fp32 (product rounded, then difference); embedding rows shared by several
  * leaves are updated with atomics.  Calls on one context must be ordered with its forwards
  * and backwards (same stream, or synchronised).  TL_F32 only, else TL_EINVAL; TL_TREERNN has

@@ -103,7 +103,8 @@ struct tl_ctx {
     int bf_leaf_s = 0, bf_leaf_grid = 0;      // leaves: k-steps per wave (0: not used), workgroups
     unsigned char *bf = nullptr;
     int bf_nodes = 0;
-    bool bwd_packed = true;           // the matrices of the other forms belong to the current parameters
+    bool bwd_packed = true;           // the matrices of the other forms belong to the current parameters (see still_packed)
+    bool update_recorded = false;     // a capture has recorded a tl_sgd_update of this context
     Gemm g_bwd_inner1{};              // U^T once more with one column block per group: more workgroups for heights of few rows
     Gemm g_bwd_inner{}, g_bwd_leaf{};
     int ng_bwd_inner = 1, ng_bwd_leaf = 1;    // blocks of output columns per column group of the operand-gradient contractions
@@ -570,18 +571,29 @@ int repack_f32(tl_ctx *ctx, hipStream_t st)
     return pack_split(ctx, pl, st);
 }
 
+// Is a capture under way on this stream?  (The legacy stream refuses the question while another one is captured: yes, as far as anybody relies on the answer.)
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
+// Matrices that an update does not rebuild are packed when a backward pass needs them.  Whether they belong to the current parameters is known on the host
+// only as long as nothing runs that the host does not enqueue: a captured backward pass always records its packing (an update may come between two
+// replays), and once an update has been recorded - a replay changes the parameters without a call - nobody relies on what was packed before.
+bool still_packed(const tl_ctx *ctx, bool packed, hipStream_t st) { return packed && !ctx->update_recorded && !capturing(st); }
+
 // ... in front of a backward pass in another form than those of back_flow.hpp
 int pack_bwd(tl_ctx *ctx, hipStream_t st)
 {
-    if (ctx->bwd_packed) return TL_OK;
+    if (ctx->bf_p == 0 || still_packed(ctx, ctx->bwd_packed, st)) return TL_OK;      // (elsewhere the update packs them)
     PackList pl{};
     pl.n = bwd_jobs(ctx, pl, 0);
     hipLaunchKernelGGL(k_repack, dim3(2048), dim3(256), 0, st, pl, SplitPackList{}, RowsPackList{}, 0);
     TL_HIP(hipGetLastError());
-    // (a launch that a capture records has not run yet)
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    TL_HIP(hipStreamIsCapturing(st, &capture));
-    ctx->bwd_packed = capture == hipStreamCaptureStatusNone;
+    if (!capturing(st)) ctx->bwd_packed = true;               // (a launch that a capture records has not run yet)
     return TL_OK;
 }
 
@@ -609,7 +621,7 @@ int pack_treernn_f32(tl_ctx *ctx, hipStream_t st)
 // and batches that the one kernel does not take and for callers that ask for launches per height.
 int pack_rntn_wide(tl_ctx *ctx, hipStream_t st)
 {
-    if (ctx->rntn_wide_packed) return TL_OK;
+    if (still_packed(ctx, ctx->rntn_wide_packed, st)) return TL_OK;
     const int H = ctx->cfg.hidden, D2 = 2 * H, L = H * D2 + H;
     int rc = pack_gemm(ctx->t_scratch, ctx->zero_bias, ctx->ng_bwd_inner, D2 / ctx->ng_bwd_inner, 1, L,
                        (D2 / ctx->ng_bwd_inner + HU - 1) / HU, 0, false, &ctx->g_bwd_inner, &ctx->wp_bwd_inner, &ctx->bp_bwd_inner, st);
@@ -620,7 +632,7 @@ int pack_rntn_wide(tl_ctx *ctx, hipStream_t st)
         if (rc != TL_OK) return rc;
     }
     TL_HIP(hipGetLastError());
-    ctx->rntn_wide_packed = true;
+    if (!capturing(st)) ctx->rntn_wide_packed = true;
     return TL_OK;
 }
 
@@ -2032,6 +2044,7 @@ int tl_sgd_update(tl_ctx *ctx, float lr, int n_nodes, const int32_t *left, const
     if (d_x) hipLaunchKernelGGL(k_sgd_embedding, dim3(1024), dim3(256), 0, st, ctx->emb, d_x, left, word, n_nodes, E, cfg.vocab, lr);
     TL_HIP(hipGetLastError());
     ctx->gates_nodes = 0;             // what a forward kept belongs to the old parameters
+    if (capturing(st)) ctx->update_recorded = true;
     return rntn ? pack_rntn_f32(ctx, st) : repack_f32(ctx, st);
 }
 

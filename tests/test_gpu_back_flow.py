@@ -154,3 +154,145 @@ def test_weight_gradients_of_both_matrices(H, E, n_trees):
         ref = oracle.backward(params, trees, h, c, g_h)
         for k in ref:                                         # sums of at most 1 200 products, fp32: 1200 * 2^-24 = 7e-5 of the largest at worst
             np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+def replayed(step):
+    """A graph of `step`, recorded on a stream of its own; what step returned in it."""
+    graph, side = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.graph(graph, stream=side):
+        out = step()
+    return graph, out
+
+
+def params_of(net, params):
+    new = {k: v.cpu().numpy() for k, v in binding.tl_get_params(net.ctx, params.vocab, params.embed_dim, params.hidden, params.cell).items()}
+    rntn = params.cell == synth.CELL_RNTN
+    return synth.Params(params.cell, params.vocab, params.embed_dim, params.hidden, new["emb"], None if rntn else new.get("w_leaf"), new.get("b_leaf"), new["u"], new["b"],
+                        new["w_leaf"] if rntn else None)
+
+
+def test_replayed_training_step():
+    """Forward, backward (which does not wait) and update as one graph: three replays, eager work between them, are three eager steps."""
+    print("case back replayed step", flush=True)
+    params, trees = make("lstm", 72, 1100, [12, 30, 1, 7], ["random"] * 4)
+    g = torch.from_numpy(np.random.default_rng(3).standard_normal((trees.n_nodes, 72)).astype(np.float32)).cuda()
+    states = []
+    for graphed in (False, True):
+        net = binding.TreeNet(params, scheduler="dataflow")
+        try:
+            b = net.load(trees)
+            binding.tl_set_keep_gates(net.ctx, True)
+            binding.tl_set_async_backward(net.ctx, 1)
+
+            def step():
+                net.forward()
+                grads = binding.tl_backward(net.ctx, b, g, params.embed_dim)
+                binding.tl_sgd_update(net.ctx, 0.05, b, grads)
+                return grads
+            step()                                            # eager: sizes the workspaces
+            torch.cuda.synchronize()
+            if graphed:
+                graph, grads = replayed(step)
+            for _ in range(3):
+                if graphed:
+                    graph.replay()
+                else:
+                    grads = step()
+                torch.cuda.synchronize()
+                assert torch.isfinite(torch.randn(1 << 16, device="cuda").sum())
+            assert binding.tl_status(net.ctx) == 0
+            states.append((grads["d_x"].cpu().numpy(), params_of(net, params)))
+        finally:
+            net.close()
+    (dx0, p0), (dx1, p1) = states
+    top = np.abs(dx0).max()
+    assert np.abs(dx1 - dx0).max() <= 1e-5 * top              # (embedding rows and weight gradients are summed with atomics: last bits)
+    assert np.abs(p1.u - p0.u).max() <= 1e-5 * np.abs(p0.u).max() and np.abs(p0.u - params.u).max() > 1e-3
+
+
+@pytest.mark.parametrize("cell", ["lstm", "rntn"])
+def test_eager_backward_after_replayed_updates(cell):
+    """A replay changes the parameters without a call: matrices that an update does not rebuild itself, packed by an eager backward pass before, are packed again.
+    (TreeLSTM: gates recomputed; RNTN: launches per height.)"""
+    print("case back after replayed updates", cell, flush=True)
+    H = 48
+    if cell == "lstm":
+        params, trees = make("lstm", H, 1110, [12, 30, 1, 7], ["random"] * 4)
+    else:
+        params = synth.make_rnn_params(1110, synth.CELL_RNTN, 50, H, scale=0.3 / H)
+        trees = synth.make_trees(1111, [12, 30, 1, 7], ["random"] * 4, 50)
+    rntn = cell == "rntn"
+    g = torch.from_numpy(np.random.default_rng(4).standard_normal((trees.n_nodes, H)).astype(np.float32)).cuda()
+
+    def gradients(net):
+        net.forward()
+        return binding.tl_backward(net.ctx, net.batch, g, params.embed_dim, rntn=rntn)
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        b = net.load(trees)
+        binding.tl_set_async_backward(net.ctx, -1)
+        grads = gradients(net)
+        torch.cuda.synchronize()
+        graph, _ = replayed(lambda: binding.tl_sgd_update(net.ctx, 0.05, b, grads))
+        for _ in range(2):
+            gradients(net)                                    # packs them
+            graph.replay()
+            torch.cuda.synchronize()
+            after = gradients(net)["d_x"].cpu().numpy()
+            q = params_of(net, params)
+            assert np.abs(q.u - params.u).max() > 1e-3
+            fresh = binding.TreeNet(q, scheduler="dataflow")
+            try:
+                fresh.load(trees)
+                binding.tl_set_async_backward(fresh.ctx, -1)
+                want = gradients(fresh)["d_x"].cpu().numpy()
+            finally:
+                fresh.close()
+            assert np.array_equal(after, want)
+    finally:
+        net.close()
+
+
+def test_replayed_backward_of_a_batch_beyond_the_tables():
+    """A batch whose rows need more than 32-bit offsets takes the fp32 matrices: a recorded backward pass packs them, whatever was packed when it was recorded."""
+    H, E = 512, 16
+    params, trees = make("lstm", H, 1120, [4096] * 52, ["balanced"] * 52, E)
+    assert trees.n_nodes * H * 20 >= 1 << 32
+    print("case back beyond the tables", trees.n_nodes, flush=True)
+    torch.manual_seed(5)
+    g = torch.randn((trees.n_nodes, H), device="cuda")
+
+    def prepared(p):
+        net = binding.TreeNet(p, scheduler="dataflow")
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, True)
+        binding.tl_set_async_backward(net.ctx, 1)
+        return net, b
+
+    def gradients(net, b):
+        net.forward()
+        return binding.tl_backward(net.ctx, b, g, E)
+    net, b = prepared(params)
+    try:
+        grads = gradients(net, b)
+        torch.cuda.synchronize()
+        graph, recorded = replayed(lambda: gradients(net, b))
+        step = 0.02 / float(grads["d_u"].abs().max())
+        for _ in range(2):
+            binding.tl_sgd_update(net.ctx, step, b, grads, with_embedding=False)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+        assert binding.tl_status(net.ctx) == 0
+        q = params_of(net, params)
+    finally:
+        net.close()
+    assert np.abs(q.u - params.u).max() > 1e-2
+    fresh, b = prepared(q)
+    try:
+        want = gradients(fresh, b)
+        assert binding.tl_status(fresh.ctx) == 0
+        assert torch.equal(recorded["d_x"], want["d_x"])
+    finally:
+        fresh.close()
