@@ -329,9 +329,9 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
         // (beyond the last pair, and in the second half of the last one of an odd number of column groups: zeros)
         const bool none = pair >= b.n_pairs, half = 2 * pair + 1 >= f.n_cg;
         const unsigned o = !wanted || none || (half && lane >= 32) ? NOWHERE : lane_off;
-        const int base = start * (int)unit.gx_row_b + line * 128 * m;
-        rows[s][0] = __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)o, base, POLICY);
-        rows[s][1] = __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)o, base + 64 * m, POLICY);
+        const unsigned base = (unsigned)start * unit.gx_row_b + (unsigned)(line * 128 * m);       // (beyond 2^31 in tables of less than 4 GiB)
+        rows[s][0] = __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)o, (int)base, POLICY);
+        rows[s][1] = __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)o, (int)(base + 64u * (unsigned)m), POLICY);
     };
     auto request_ex = [&](bool wanted, auto policy) __attribute__((always_inline)) {
         constexpr int POLICY = decltype(policy)::value;

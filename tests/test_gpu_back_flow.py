@@ -296,3 +296,33 @@ def test_replayed_backward_of_a_batch_beyond_the_tables():
         assert torch.equal(recorded["d_x"], want["d_x"])
     finally:
         fresh.close()
+
+
+def test_rows_beyond_two_gib():
+    """The copy that the blocks read may be of nearly 4 GiB: offsets of its upper half (TreeLSTM, H = 2: 640 bytes a row, 3.5 million internal nodes).
+    The same tree over and over: every copy's d_x has the bits of a batch of two."""
+    L, n_trees, H, E = 64, 56000, 2, 3
+    params, two = make("lstm", H, 1130, [L] * 2, ["random"] * 2, E)
+    n = int(two.tree_off[1])
+    one = [a[:n] for a in (two.left, two.right, two.word)]
+
+    def repeated(count):
+        base = (np.arange(count, dtype=np.int32) * n)[:, None]
+        child = lambda a: np.where(a >= 0, a + base, -1).astype(np.int32).ravel()
+        return synth.TreeBatch((np.arange(count + 1) * n).astype(np.int32), child(one[0]), child(one[1]), np.tile(one[2], count))
+    g = np.random.default_rng(11).standard_normal((n, H)).astype(np.float32)
+    got = {}
+    for count in (2, n_trees):
+        trees = repeated(count)
+        print("case back beyond 2 GiB", trees.n_nodes, flush=True)
+        net = binding.TreeNet(params, scheduler="dataflow")
+        try:
+            b = net.load(trees)
+            binding.tl_set_keep_gates(net.ctx, True)
+            net.forward()
+            got[count] = binding.tl_backward(net.ctx, b, torch.from_numpy(g).cuda().repeat(count, 1), E)["d_x"].view(count, n, E)
+            assert binding.tl_status(net.ctx) == 0
+        finally:
+            net.close()
+    assert (n_trees * (L - 1)) * 640 > 1 << 31
+    assert bool((got[n_trees] == got[2][0]).all()) and bool((got[2][1] == got[2][0]).all())
