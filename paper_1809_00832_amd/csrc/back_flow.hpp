@@ -56,10 +56,13 @@ template <int NG, int P> struct BackGeom {
     // that the block before could have asked for.
     static constexpr int IN_LDS = S > 16 ? 7 : 0;
     static_assert(S <= 16 || S == 20, "places of the weights");
-    static constexpr bool in_lds(int s) { return S > 16 && (s % 3 == 2 || s == 19); }
+    static constexpr bool in_lds(int s) { return S > 16 && s < S && (s % 3 == 2 || s == 19); }
     static constexpr int lds(int s) { return s == 19 ? 6 : s / 3; }         // place there
     static constexpr int reg(int s) { return S > 16 ? s - s / 3 : s; }      // ... in registers
+    // (a k-step's weights are read while the step before is computed, into registers that this one must not need)
+    static constexpr bool apart() { for (int s = 0; s < S; ++s) if (in_lds(s) && in_lds(s + 1)) return false; return true; }
 };
+static_assert(BackGeom<5, 4>::apart(), "weights in LDS");
 template <int L> struct BackSmemT {
     unsigned char stage[4][16 * 320 + 128];             // see BackUnit::finish
     int4 ring[4][32];                                   // entries of four blocks: {node, left, right, flags} of 16 rows, their children's places
