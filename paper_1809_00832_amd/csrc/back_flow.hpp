@@ -121,6 +121,7 @@ typedef unsigned int uintx2_t __attribute__((ext_vector_type(2)));
 // node's piece.
 template <int NG> struct BackUnit {
     static constexpr bool LSTM = NG == 5;
+    static constexpr unsigned HOLDS_NAN = 256u;         // in the place of an exponent
     static constexpr int PIECE = NG * 64, CHUNKS = 8 * NG * 4, STORES = (CHUNKS + 63) / 64;      // bytes of a piece; of 8 pieces, in 16 bytes and in wave-wide stores
     const Fwd &f;
     const BackFlow &b;
@@ -202,7 +203,8 @@ template <int NG> struct BackUnit {
             m = max(m, __float_as_uint(dpp<DPP_MIRROR>(__uint_as_float(m))));
             eb[d] = max(m >> 23, 15u);
             const float scale = __uint_as_float((268u - eb[d]) << 23);
-            if (__builtin_expect(__ballot(eb[d] == 255u) != 0ull, 0)) {         // no NaN may look like "not written"
+            if (__builtin_expect(__ballot(eb[d] == 255u) != 0ull, 0)) {         // no NaN may look like "not written"; a piece with one says so
+                if (m > 0x7F800000u) eb[d] = HOLDS_NAN;
 #pragma unroll
                 for (int q = 0; q < NG; ++q) out[d][q] = __builtin_isnan(out[d][q]) ? __uint_as_float(0x7FC00000u) : out[d][q];
 #pragma unroll
@@ -263,6 +265,13 @@ template <int NG> struct BackUnit {
                 }
             }
         }
+    }
+    // Does a gate gradient of row `row` of the block of m nodes at position start hold a NaN?  (Then so do its sums.)  Called by the 16 lanes of a row together.
+    __device__ __forceinline__ bool row_has_nan(int start, int m, int row) const
+    {
+        bool nan = false;
+        for (int c = lane & 15; c < f.n_cg; c += 16) nan |= ld_dev(b.gs + ((size_t)start * f.n_cg + (size_t)c * m + row)) == HOLDS_NAN;
+        return (__ballot(nan) >> (lane & 48) & 0xFFFFull) != 0ull;
     }
     // A sum of the operand gradient in fp32 from the parameters as given (rare, and slow): row `row` of the block of m nodes at position start,
     // whose copy is complete.
@@ -460,7 +469,8 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
         }
         const bool again = e.x >= 0 && unit.hu_ok && !(__builtin_isfinite(da[0]) && __builtin_isfinite(da[1]));
         if (__builtin_expect(__ballot(again) != 0ull, 0)) {
-            if (again) {
+            // (a row beyond the block's nodes has none of its own)
+            if (!unit.row_has_nan(here_start, here_m, min(fin_row, here_m - 1)) && again) {
                 da[0] = unit.plain(here_start, here_m, fin_row, 0);
                 da[1] = unit.plain(here_start, here_m, fin_row, 1);
             }
@@ -734,8 +744,11 @@ __global__ __launch_bounds__(WG_THREADS, S * NC * 8 <= 96 ? 2 : 1) void k_back_l
             const int col = (group * NC + g) * HU + (lane & 15);
             const bool here = col < E && lo + blk * 16 + fin_row < hi, again = here && !__builtin_isfinite(sum);
             if (__builtin_expect(__ballot(again) != 0ull, 0)) {
-                if (again) {                                                // in fp32 from the parameters as given
-                    const float *a = dg + (size_t)node * stride, *wr = w_leaf + (size_t)col * K;
+                const float *a = dg + (size_t)node * stride;
+                bool nan = false;                                           // (a NaN among the row's values: the sum stays one)
+                for (int k = lane & 15; k < K; k += 16) nan |= __builtin_isnan(a[k]);
+                if (again && (__ballot(nan) >> (lane & 48) & 0xFFFFull) == 0ull) {      // in fp32 from the parameters as given
+                    const float *wr = w_leaf + (size_t)col * K;
                     sum = 0.f;
 #pragma unroll 1
                     for (int k = 0; k < K; ++k) sum = __builtin_fmaf(a[k], wr[k], sum);

@@ -326,3 +326,33 @@ def test_rows_beyond_two_gib():
             net.close()
     assert (n_trees * (L - 1)) * 640 > 1 << 31
     assert bool((got[n_trees] == got[2][0]).all()) and bool((got[2][1] == got[2][0]).all())
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", 150), ("lstm", 512), ("rnn", 512)])
+def test_a_diverged_step_is_not_slow(cell, H):
+    """Sums that are not finite are taken again, one by one; those of a row that holds a NaN are not, they would stay NaN.  Time of a backward pass whose upstream gradients
+    are all NaN against that of ordinary ones (taken again throughout: some hundred times as long; the weight gradients' share of it is below twice the whole)."""
+    print("case back diverged", cell, H, flush=True)
+    params, trees = make(cell, H, 1140, [20] * 60, ["random"] * 60, 200)
+    clean = torch.from_numpy(np.random.default_rng(13).standard_normal((trees.n_nodes, H)).astype(np.float32)).cuda()
+    net = binding.TreeNet(params, scheduler="dataflow")
+    us = []
+    try:
+        b = net.load(trees)
+        binding.tl_set_keep_gates(net.ctx, True)
+        for g in (clean, torch.full_like(clean, float("nan"))):
+            times = []
+            for _ in range(8):
+                net.forward()
+                begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                begin.record()
+                d_x = binding.tl_backward(net.ctx, b, g, params.embed_dim)["d_x"]
+                end.record()
+                torch.cuda.synchronize()
+                times.append(begin.elapsed_time(end) * 1e3)
+            us.append(sorted(times)[4])
+        leaf = torch.from_numpy(trees.left < 0).cuda()
+        assert bool(torch.isnan(d_x[leaf]).all())
+    finally:
+        net.close()
+    assert us[1] < 4 * us[0] + 200, us
