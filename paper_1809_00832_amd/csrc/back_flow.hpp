@@ -121,7 +121,6 @@ typedef unsigned int uintx2_t __attribute__((ext_vector_type(2)));
 // node's piece.
 template <int NG> struct BackUnit {
     static constexpr bool LSTM = NG == 5;
-    static constexpr unsigned HOLDS_NAN = 256u;         // in the place of an exponent
     static constexpr int PIECE = NG * 64, CHUNKS = 8 * NG * 4, STORES = (CHUNKS + 63) / 64;      // bytes of a piece; of 8 pieces, in 16 bytes and in wave-wide stores
     const Fwd &f;
     const BackFlow &b;
@@ -203,8 +202,7 @@ template <int NG> struct BackUnit {
             m = max(m, __float_as_uint(dpp<DPP_MIRROR>(__uint_as_float(m))));
             eb[d] = max(m >> 23, 15u);
             const float scale = __uint_as_float((268u - eb[d]) << 23);
-            if (__builtin_expect(__ballot(eb[d] == 255u) != 0ull, 0)) {         // no NaN may look like "not written"; a piece with one says so
-                if (m > 0x7F800000u) eb[d] = HOLDS_NAN;
+            if (__builtin_expect(__ballot(eb[d] == 255u) != 0ull, 0)) {         // no NaN may look like "not written"
 #pragma unroll
                 for (int q = 0; q < NG; ++q) out[d][q] = __builtin_isnan(out[d][q]) ? __uint_as_float(0x7FC00000u) : out[d][q];
 #pragma unroll
@@ -266,15 +264,8 @@ template <int NG> struct BackUnit {
             }
         }
     }
-    // Does a gate gradient of row `row` of the block of m nodes at position start hold a NaN?  (Then so do its sums.)  Called by the 16 lanes of a row together.
-    __device__ __forceinline__ bool row_has_nan(int start, int m, int row) const
-    {
-        bool nan = false;
-        for (int c = lane & 15; c < f.n_cg; c += 16) nan |= ld_dev(b.gs + ((size_t)start * f.n_cg + (size_t)c * m + row)) == HOLDS_NAN;
-        return (__ballot(nan) >> (lane & 48) & 0xFFFFull) != 0ull;
-    }
     // A sum of the operand gradient in fp32 from the parameters as given (rare, and slow): row `row` of the block of m nodes at position start,
-    // whose copy is complete.
+    // whose copy is complete.  A sum that is a NaN stays one: a step that has diverged, all of whose rows hold nothing else, does not get here value by value.
     __device__ __forceinline__ float plain(int start, int m, int row, int side) const
     {
         const int H = f.H;
@@ -285,7 +276,7 @@ template <int NG> struct BackUnit {
 #pragma unroll 1
         for (int q = 0; q < NG; ++q)
 #pragma unroll 1
-            for (int u = 0; u < H; ++u) {
+            for (int u = 0; u < H && !__builtin_isnan(sum); ++u) {
                 const unsigned short *p = gx + ((((u >> 5) * NG + q) * 8 + (u >> 3 & 3)) * m + row) * 8 + (u & 7);
                 const float hi = (float)__builtin_bit_cast(_Float16, ld_dev(p)), lo = (float)__builtin_bit_cast(_Float16, ld_dev(p + 4 * m * 8));
                 const int e = (int)ld_dev(gs + (u >> 4) * m + row) - 141;
@@ -469,8 +460,7 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
         }
         const bool again = e.x >= 0 && unit.hu_ok && !(__builtin_isfinite(da[0]) && __builtin_isfinite(da[1]));
         if (__builtin_expect(__ballot(again) != 0ull, 0)) {
-            // (a row beyond the block's nodes has none of its own)
-            if (!unit.row_has_nan(here_start, here_m, min(fin_row, here_m - 1)) && again) {
+            if (again) {
                 da[0] = unit.plain(here_start, here_m, fin_row, 0);
                 da[1] = unit.plain(here_start, here_m, fin_row, 1);
             }
@@ -744,14 +734,11 @@ __global__ __launch_bounds__(WG_THREADS, S * NC * 8 <= 96 ? 2 : 1) void k_back_l
             const int col = (group * NC + g) * HU + (lane & 15);
             const bool here = col < E && lo + blk * 16 + fin_row < hi, again = here && !__builtin_isfinite(sum);
             if (__builtin_expect(__ballot(again) != 0ull, 0)) {
-                const float *a = dg + (size_t)node * stride;
-                bool nan = false;                                           // (a NaN among the row's values: the sum stays one)
-                for (int k = lane & 15; k < K; k += 16) nan |= __builtin_isnan(a[k]);
-                if (again && (__ballot(nan) >> (lane & 48) & 0xFFFFull) == 0ull) {      // in fp32 from the parameters as given
-                    const float *wr = w_leaf + (size_t)col * K;
+                if (again) {                                                // in fp32 from the parameters as given (a NaN stays one, as in BackUnit::plain)
+                    const float *a = dg + (size_t)node * stride, *wr = w_leaf + (size_t)col * K;
                     sum = 0.f;
 #pragma unroll 1
-                    for (int k = 0; k < K; ++k) sum = __builtin_fmaf(a[k], wr[k], sum);
+                    for (int k = 0; k < K && !__builtin_isnan(sum); ++k) sum = __builtin_fmaf(a[k], wr[k], sum);
                 }
                 __builtin_amdgcn_s_waitcnt(0);
             }
