@@ -577,7 +577,7 @@ __device__ inline void split_leaves(SplitLeafSmem &sm, const Fwd &f, int lo, int
         }
         const bool here = lo + b * 16 + fin_row < hi, ok = here && hu_ok;
         float cc, hh;
-        lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, KEEP ? Keep{f.keep0, nullptr, ok ? (long long)node * H + hu : (lane & 15) - HU} : Keep());
+        lstm_leaf_out(gate[0], gate[1], gate[2], &cc, &hh, KEEP ? Keep{ok ? f.keep0 + ((size_t)node * H + hu) : f.keep0 - HU + (lane & 15), nullptr, 0} : Keep());
         const unsigned o = ok ? __umul24((unsigned)node, row_b) + hu_b : ~0u;
         const unsigned word = split_word(hu_ok ? hh * SPLIT_H_SCALE : 0.f, hu);
         buf_st_f<false>(rs_c, o, cc);

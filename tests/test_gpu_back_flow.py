@@ -356,3 +356,31 @@ def test_a_diverged_step_is_not_slow(cell, H):
     finally:
         net.close()
     assert us[1] < 4 * us[0] + 200, us
+
+
+@pytest.mark.parametrize("cell,H", [("lstm", h) for h in (96, 150, 300, 512)] + [("rnn", h) for h in (31, 130, 512)])
+def test_pieces_far_apart(cell, H):
+    """A block-diagonal U (16 units a block, as many as share a power of two) keeps the units' groups apart, and each group's upstream gradients have a size of their own, up to
+    2^50 apart: a group's gradients are met to a share of its own largest value, beside larger groups in the same quarter of a row too.  TreeLSTM: d_u and d_b (d_x mixes
+    the groups of a quarter of a row, which share a scale there); TreeRNN: d_x.  Tolerance as for gradients of any size."""
+    print("case back pieces far apart", cell, H, flush=True)
+    params, trees = make(cell, H, 1150, [20, 31, 2, 1], ["random"] * 4)
+    group = np.arange(H) // 16
+    ng = 5 if cell == "lstm" else 1
+    same = np.tile(group[:, None] == group[None, :], (2, ng))
+    params.u = np.where(same, params.u * 3, 0).astype(np.float32)
+    size = 2.0 ** -np.array([0, 13, 14, 15, 16, 25, 31, 50])[group % 8]
+    g_h = (np.random.default_rng(17).standard_normal((trees.n_nodes, H)) * size).astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1))
+    ref = oracle.backward(params, trees, h, c, g_h)
+    for mode in (-1, 0, 1):
+        for q in range(group[-1] + 1):
+            units = np.flatnonzero(group == q)
+            if cell == "lstm":
+                cols = (np.arange(ng)[:, None] * H + units).ravel()
+                pairs = [(out[mode]["d_b"][cols], ref["d_b"][cols]), (out[mode]["d_u"][:, cols], ref["d_u"][:, cols])]
+            else:
+                pairs = [(out[mode]["d_x"][:, units], ref["d_x"][:, units])]
+            for got, want in pairs:
+                top = np.abs(want).max()
+                assert top > 0 and np.abs(got - want).max() <= 1e-4 * top, (mode, q, np.abs(got - want).max() / top)
