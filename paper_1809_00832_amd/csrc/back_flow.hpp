@@ -12,8 +12,8 @@
 // Contraction: operands as two fp16 terms, as in cell_split.hpp (three 16-bit products, fp32 accumulation).  A row of dG (NG H
 // values, any magnitude) is written by n_cg workgroups, each of which knows its own 16 units only; so every piece (a
 // node's NG x 16 values of one workgroup) has a power of two of its own, which brings its largest magnitude into [2^14, 2^15).  The
-// reader of a quarter of a row multiplies the pieces by powers of two that bring them to the largest of its quarter (exact; a piece 2^25
-// and more below it counts as zero) and its partial sums by that one's.
+// reader of a quarter of a row multiplies the pieces by powers of two that bring them to the largest of its quarter, down to 2^-14 (which keeps a piece to 2^-25 of its
+// own largest value), and its partial sums by that one's; pieces further below are summed apart (far_bands).
 // Sums that are not finite (an infinity has no two terms, and a scaled sum may overflow) are taken again in fp32.
 //
 // Layout of the copy that the blocks read (`gx`): a node's row is read once, in a block and a row of it that the schedule knows beforehand, so
@@ -121,6 +121,7 @@ typedef unsigned int uintx2_t __attribute__((ext_vector_type(2)));
 // node's piece.
 template <int NG> struct BackUnit {
     static constexpr bool LSTM = NG == 5;
+    static constexpr unsigned ALL_ZERO = 15u;           // in the place of an exponent
     static constexpr int PIECE = NG * 64, CHUNKS = 8 * NG * 4, STORES = (CHUNKS + 63) / 64;      // bytes of a piece; of 8 pieces, in 16 bytes and in wave-wide stores
     const Fwd &f;
     const BackFlow &b;
@@ -200,7 +201,7 @@ template <int NG> struct BackUnit {
             m = max(m, __float_as_uint(dpp<DPP_XOR2>(__uint_as_float(m))));
             m = max(m, __float_as_uint(dpp<DPP_HALF_MIRROR>(__uint_as_float(m))));
             m = max(m, __float_as_uint(dpp<DPP_MIRROR>(__uint_as_float(m))));
-            eb[d] = max(m >> 23, 15u);
+            eb[d] = max(m >> 23, ALL_ZERO + min(m, 1u));
             const float scale = __uint_as_float((268u - eb[d]) << 23);
             if (__builtin_expect(__ballot(eb[d] == 255u) != 0ull, 0)) {         // no NaN may look like "not written"
 #pragma unroll
@@ -311,6 +312,7 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
     constexpr int S = G::S;
     constexpr bool LSTM = NG == 5;
     constexpr int COH = FLOW ? 0 : 16;                  // (of the first requests)
+    constexpr int FAR = 14;                             // 2^-14 is the smallest number that fp16 holds with all its bits
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr unsigned NOWHERE = ~0u - 0xFFFFu;         // beyond the end of every table
     uintx4_t rows[S][2];
@@ -361,6 +363,51 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
     };
     typedef std::integral_constant<int, COH> first_policy;
     typedef std::integral_constant<int, 16> past_caches;
+    // Pieces further below their quarter's largest than FAR bits: brought there they would lose bits of their own, or all of them.  Rare: their rows are asked
+    // for again and summed band by band.  (Block of m nodes at position start; top: the largest of this lane's row's quarter.)
+    auto far_bands = [&](int start, int m, unsigned top, floatx4 *own) __attribute__((always_inline)) {
+        const unsigned off = (unsigned)((lane >> 4) * m + min(lane & 15, m - 1)) * 16u;
+        unsigned limit = top < 255u ? top : 0u;         // a band begins below limit - FAR (none in a row with an infinity, a NaN, or whose wait was given up)
+        for (;;) {
+            unsigned next = 0u;
+            auto piece = [&](int p) __attribute__((always_inline)) {
+                const int c = min(2 * min(wave * P + p, b.n_pairs - 1) + (lane >> 5), f.n_cg - 1);
+                return (unsigned)__builtin_amdgcn_raw_buffer_load_b32(unit.rs_gs, (c * m + min(lane & 15, m - 1)) * 4, start * f.n_cg * 4, 16);
+            };
+#pragma unroll 1
+            for (int p = 0; p < P; ++p) {
+                const unsigned e = piece(p);
+                if (e != BackUnit<NG>::ALL_ZERO && e + FAR < limit) next = max(next, e);
+            }
+            next = max(next, (unsigned)__shfl_xor((int)next, 32));
+            if (__ballot(next != 0u) == 0ull) break;
+            floatx4 acc[2] = {};
+#pragma unroll
+            for (int s = 0; s < S; ++s) {
+                const int pair = wave * P + s / NG, line = min(pair, b.n_pairs - 1) * NG + s % NG;
+                const unsigned e = piece(s / NG), base = (unsigned)start * unit.gx_row_b + (unsigned)(line * 128 * m);
+                const bool none = pair >= b.n_pairs || (2 * pair + 1 >= f.n_cg && lane >= 32), band = e + FAR < limit && next - e <= (unsigned)FAR;
+                const _Float16 by = __builtin_bit_cast(_Float16, (unsigned short)(band ? (FAR + 1 + e - next) << 10 : 0u));
+                const halfx8 hi = __builtin_bit_cast(halfx8, __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)(none ? NOWHERE : off), (int)base, 16)) * by,
+                             lo = __builtin_bit_cast(halfx8, __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)(none ? NOWHERE : off), (int)(base + 64u * (unsigned)m), 16)) * by;
+#pragma unroll
+                for (int d = 0; d < 2; ++d) {
+                    halfx8 wt[2];
+#pragma unroll
+                    for (int t = 0; t < 2; ++t) wt[t] = G::in_lds(s) ? sm.w[(((wave * G::IN_LDS + G::lds(s)) * 2 + d) * 2 + t) * 64 + lane] : w.t[G::reg(s)][d][t];
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[0], acc[d], 0, 0, 0);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[1], acc[d], 0, 0, 0);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, wt[0], acc[d], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            if (lane < 16) sm.row_scale[wave][lane] = __uint_as_float((max(next, 15u) - 14u) << 23);
+            const floatx4 r4 = *reinterpret_cast<const floatx4 *>(&sm.row_scale[wave][4 * (lane >> 4)]);
+#pragma unroll
+            for (int d = 0; d < 2; ++d) own[64 * d] += acc[d] * r4;
+            limit = next;
+        }
+    };
     const int fin_row = 4 * wave + (lane >> 4), last_b = n_blocks - 1;
     typename BackUnit<NG>::In in[2] = {};
     auto load_children = [&](int blk, typename BackUnit<NG>::In (&in)[2]) __attribute__((always_inline)) {
@@ -411,9 +458,13 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
 #pragma unroll
         for (int p = 1; p < P; ++p) top = max(top, ex[p]);
         top = max(top, (unsigned)__shfl_xor((int)top, 32));
-        _Float16 factor[P];
+        _Float16 factor[P];                             // (beyond FAR bits: zero)
+        unsigned ex_now[P];
 #pragma unroll
-        for (int p = 0; p < P; ++p) factor[p] = (_Float16)__uint_as_float((unsigned)max(127 + (int)ex[p] - (int)top, 0) << 23);
+        for (int p = 0; p < P; ++p) {
+            factor[p] = __builtin_bit_cast(_Float16, (unsigned short)((unsigned)max(FAR + 1 + (int)ex[p] - (int)top, 0) << 10));
+            ex_now[p] = ex[p];
+        }
         const float back = __uint_as_float((top - 14u) << 23);
         const int here_start = start, here_m = m;
         if (!last) prepare(blk + 1);
@@ -423,6 +474,7 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
         // The matrix instruction drops what does not fit downwards, and a column sum over all nodes adds that up (d_b of 256 parse trees at H = 512: off by
         // 3.2e-7 of its norm): every other k-step is taken with its rows negated, into a sum of its own that is subtracted.
         floatx4 acc[2][2] = {};
+        bool far = false;
         halfx8 wl[2][2] = {};                           // the next k-step's weights, where they are in LDS
 #pragma unroll
         for (int s = 0; s < S; ++s) {
@@ -435,6 +487,12 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
             const _Float16 by = (s & 1) != 0 ? -factor[s / NG] : factor[s / NG];
             const halfx8 hi = __builtin_bit_cast(halfx8, rows[s][0]) * by, lo = __builtin_bit_cast(halfx8, rows[s][1]) * by;
             request(!late, s, first_policy{});
+            if (s == 0) {                                   // is there a piece, not of zeros, that the factors leave out?  (Here, beside the matrix instructions.)
+                unsigned least = 0x7FFFu;
+#pragma unroll
+                for (int p = 0; p < P; ++p) least = min(least, ex_now[p] - (BackUnit<NG>::ALL_ZERO + 1));       // (a piece of zeros: the largest number)
+                far = __ballot(least + (BackUnit<NG>::ALL_ZERO + 1 + FAR) < top && top < 255u) != 0ull;
+            }
 #pragma unroll
             for (int d = 0; d < 2; ++d) acc[s & 1][d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, G::in_lds(s) ? wl[d][0] : w.t[G::reg(s)][d][0], acc[s & 1][d], 0, 0, 0);
 #pragma unroll
@@ -444,10 +502,12 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
             __builtin_amdgcn_sched_barrier(0);
         }
         if (lane < 16) sm.row_scale[wave][lane] = back;
-        float *red = sm.red[blk & 1];
         const floatx4 r4 = *reinterpret_cast<const floatx4 *>(&sm.row_scale[wave][4 * (lane >> 4)]);    // this wave's own writes
+        float *red = sm.red[blk & 1];
+        floatx4 *const own = reinterpret_cast<floatx4 *>(&red[(wave * 2 * 64 + lane) * 4]);             // [side] 64 apart
 #pragma unroll
-        for (int d = 0; d < 2; ++d) *reinterpret_cast<floatx4 *>(&red[((wave * 2 + d) * 64 + lane) * 4]) = (acc[0][d] - acc[1][d]) * r4;
+        for (int d = 0; d < 2; ++d) own[64 * d] = (acc[0][d] - acc[1][d]) * r4;
+        if (__builtin_expect(far, 0)) far_bands(here_start, here_m, top, own);
         __syncthreads();
         if (FLOW && sm.gave_up != 0) return;
         float da[2];

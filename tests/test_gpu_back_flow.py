@@ -384,3 +384,52 @@ def test_pieces_far_apart(cell, H):
             for got, want in pairs:
                 top = np.abs(want).max()
                 assert top > 0 and np.abs(got - want).max() <= 1e-4 * top, (mode, q, np.abs(got - want).max() / top)
+
+
+@pytest.mark.parametrize("H", [40, 150, 512])
+@pytest.mark.parametrize("where", ["u", "w_leaf"])
+def test_infinite_weights(where, H):
+    """A column with an infinity has no two terms: its sums are taken in fp32 and are finite, infinite or NaN where the checker's are.  (The infinity is an output gate's, whose
+    sigmoid is 0 or 1, so that the states stay finite.)"""
+    print("case back infinite weights", where, H, flush=True)
+    params, trees = make("lstm", H, 1160, [20, 31, 2, 1], ["random"] * 4)
+    if where == "u":
+        params.u = params.u.copy()
+        params.u[H + 3, 3 * H + 7] = np.inf
+    else:
+        params.w_leaf = params.w_leaf.copy()
+        params.w_leaf[5, H + 9] = np.inf
+    g_h = np.random.default_rng(19).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1))
+    assert np.isfinite(h).all() and np.isfinite(c).all()
+    ref = oracle.backward(params, trees, h, c, g_h)["d_x"]
+    assert not np.isfinite(ref).all() and (where == "u" or np.isfinite(ref).any())
+    for mode in (-1, 0, 1):
+        got = out[mode]["d_x"]
+        assert np.array_equal(np.isfinite(got), np.isfinite(ref)), mode
+        good = np.isfinite(ref)
+        np.testing.assert_allclose(got[good], ref[good], rtol=1e-4, atol=1e-4)
+
+
+@pytest.mark.parametrize("cell,H", [("rnn", 48), ("rnn", 300), ("lstm", 48), ("lstm", 512)])
+def test_sums_that_overflow_only_when_scaled(cell, H):
+    """Gradients of 2^120 against weights of 2^-60: the sums are of order 2^60, the scaled ones beyond fp32, and taken again.  TreeRNN: U (only the roots have an upstream
+    gradient, so that a leaf's d_x is such a sum or a sum of such); TreeLSTM: W_leaf."""
+    print("case back scaled overflow", cell, H, flush=True)
+    params, trees = make(cell, H, 1170, [2, 3, 2, 1], ["random"] * 4)
+    tiny = np.float32(2.0 ** -60)
+    if cell == "rnn":
+        params.u = (params.u * tiny).astype(np.float32)
+    else:
+        params.w_leaf = (params.w_leaf * tiny).astype(np.float32)
+    g_h = np.zeros((trees.n_nodes, H))
+    roots = np.setdiff1d(np.arange(trees.n_nodes), np.concatenate([trees.left, trees.right]))
+    rows = roots if cell == "rnn" else np.flatnonzero(trees.left < 0)
+    g_h[rows] = np.random.default_rng(23).standard_normal((len(rows), H)) * 2.0 ** 120
+    g_h = g_h.astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1))
+    ref = oracle.backward(params, trees, h, c, g_h)["d_x"]
+    for mode in (-1, 0, 1):
+        for n in np.flatnonzero(trees.left < 0):
+            top = np.abs(ref[n]).max()
+            assert 0 < top < 2.0 ** 127 and np.abs(out[mode]["d_x"][n] - ref[n]).max() <= 1e-4 * top, (mode, n)
