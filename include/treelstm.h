@@ -344,7 +344,8 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
 /*
  * For callers that must not be held up by tl_backward (the recursion of Section 4.2.2 walked without the host):
  * with on > 0, a tl_backward that needs no contraction for its gate gradients - TreeLSTM from what the forward kept
- * (tl_set_keep_gates), TreeRNN - walks the trees in one persistent kernel.  Nothing is read back and the call returns without
+ * (tl_set_keep_gates), TreeRNN - walks the trees in one persistent kernel (H <= 512: whole trees on sets of workgroups, or, where the structure pass finds
+ * trees that are bushy and much larger than a set's share of the batch, height by height on all of them).  Nothing is read back and the call returns without
  * waiting; a malformed batch is then reported by tl_status (TL_ESTRUCT, gradients undefined), not by tl_backward.  Same
  * results as the launches per height (same contractions in the same order; with H <= 512 operands as two fp16 terms each in every mode, sums that are
  * not finite taken again in fp32).

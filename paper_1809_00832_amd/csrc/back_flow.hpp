@@ -550,7 +550,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_flow(Fwd f, BackFlow b)
     using Smem = BackSmem<NG, P>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     const int tid = threadIdx.x;
-    const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));      // (a workgroup that gives up latches that)
+    const bool leave = tid == 0 && (batch_rejected(f) || back_flow_skipped(f));      // (a workgroup that gives up latches that)
     int member, slot;
     split_place(f, &slot, &member);
     member = gang_cg(member, f.n_cg, f.n_cg);     // (neighbouring units from one L2 domain)
@@ -570,9 +570,101 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_flow(Fwd f, BackFlow b)
                              [end = trees.z + trees.w](int, int m) mutable { return end -= m; });
 }
 
+// A batch with trees that are large beside the others (back_by_heights): the host does not know whether it is one, and the five launches that list the heights
+// elsewhere would leave at once for almost all batches, at 2 us each.  So the work is done beside other work.  Here, in k_back_prepare: the roots, the heights, how many nodes have each.
+// (Counters in LDS first, HIST_BINS of them: some thousand additions to one address from all over the chip are 50 us.)
+__device__ __forceinline__ void back_heights_of(const Fwd &f, int *hist, size_t first, size_t stride)
+{
+    Ctl *ctl = f.ctl;
+    for (int i = threadIdx.x; i < HIST_BINS; i += WG_THREADS) hist[i] = 0;
+    if (decided_to_leave(hist + HIST_BINS, threadIdx.x == 0 && batch_rejected(f))) return;
+    for (size_t n = first; n < (size_t)f.n_nodes; n += stride)
+        if (f.parent[n] < 0) {
+            if (atomicCAS(&f.root_ws[tree_of(f.tree_off, f.n_trees, (int)n)], -1, (int)n) != -1) latch_error(ctl, TL_ESTRUCT);      // a second root of the same tree
+            atomicAdd(&ctl->n_roots, 1);
+        }
+    for (size_t i = first; i < (size_t)f.n_leaf; i += stride) {
+        int top = 0, count = 0;
+        climb_from(f, f.leaf_list[i], [&](int height) {
+            atomicAdd(height < HIST_BINS ? &hist[height] : &f.level_cnt[height], 1);
+            top = height;
+            count += 1;
+        });
+        if (count > 0) {
+            atomicMax(&ctl->max_height, top);
+            atomicAdd(&ctl->reached, count);
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < HIST_BINS; i += WG_THREADS)
+        if (hist[i] != 0) atomicAdd(&f.level_cnt[i], hist[i]);
+}
+// ... before any row is computed: a tree without a root, or nodes that no leaf leads to (a cycle)?  (Counts that are final; the host's copy of them says the same.)
+__device__ inline bool back_rejected(const Fwd &f)
+{
+    if (f.ctl->n_roots == f.n_trees && f.ctl->reached == f.n_int) return false;
+    latch_error(f.ctl, TL_ESTRUCT);
+    return true;
+}
+// ... and from these counts the lists of all heights and the places of all nodes.  False where a wait was given up.
+template <typename Smem> __device__ __forceinline__ bool back_lists(Smem &sm, const Fwd &f, const BackFlow &b, unsigned &epoch)
+{
+    static_assert(sizeof(sm.red) >= 2 * HIST_BINS * sizeof(int), "counters");
+    const int tid = threadIdx.x, n_levels = f.ctl->max_height + 1;
+    unsigned unused = 0;
+    if (blockIdx.x == 0) {                                  // exclusive sums of the counts, a share of the heights per thread
+        int *sums = reinterpret_cast<int *>(sm.red);
+        const int share = (n_levels + WG_THREADS - 1) / WG_THREADS, lo = min(tid * share, n_levels), hi = min(lo + share, n_levels);
+        int sum = 0;
+        for (int l = lo; l < hi; ++l) sum += f.level_cnt[l];
+        sums[tid] = sum;
+        __syncthreads();
+        for (int d = 1; d < WG_THREADS; d <<= 1) {
+            const int add = tid >= d ? sums[tid - d] : 0;
+            __syncthreads();
+            sums[tid] += add;
+            __syncthreads();
+        }
+        int at = sums[tid] - sum;
+        for (int l = lo; l < hi; ++l) {
+            st_dev(f.level_off + l, at);
+            at += f.level_cnt[l];
+        }
+        if (tid == WG_THREADS - 1) {
+            st_dev(f.level_off + n_levels, at);
+            st_dev(&f.ctl->n_levels, n_levels);
+        }
+    }
+    if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return false;
+    int *hist = reinterpret_cast<int *>(sm.red), *place = hist + HIST_BINS;
+    for (long long n0 = (long long)blockIdx.x * WG_THREADS; n0 < f.n_nodes; n0 += (long long)gridDim.x * WG_THREADS) {
+        const int n = (int)n0 + tid;
+        for (int i = tid; i < HIST_BINS; i += WG_THREADS) hist[i] = 0;
+        __syncthreads();
+        const bool inner = n < f.n_nodes && f.left[n] >= 0;
+        const int height = inner ? f.height[n] : 0;
+        int i = !inner ? 0 : height < HIST_BINS ? atomicAdd(&hist[height], 1) : add_dev(f.level_fill + height, 1);
+        __syncthreads();
+        for (int k = tid; k < HIST_BINS; k += WG_THREADS)
+            if (hist[k] != 0) place[k] = add_dev(f.level_fill + k, hist[k]);
+        __syncthreads();
+        if (inner) {
+            if (height < HIST_BINS) i += place[height];
+            const int lo = ld_dev(f.level_off + height), block = i & ~15;
+            st_dev(f.level_nodes + lo + i, n);
+            st_dev(reinterpret_cast<unsigned long long *>(b.at.of + n),
+                   pack2((unsigned)(lo + block), (unsigned)(min(16, ld_dev(f.level_off + height + 1) - lo - block) | (i - block) << 8)));
+        }
+    }
+    if (!grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return false;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");      // the lists and places are read with ordinary loads from here on
+    return true;
+}
+
 // The same cell height by height: all workgroups share the blocks of a height.  The whole walk in one launch, a grid barrier per height (a batch of few
-// large bushy trees, which would leave most sets of workgroups without a tree), or a launch for the roots and for each height.
-constexpr int BACK_ALL = 0, BACK_ROOTS = 1, BACK_HEIGHT = 2;
+// large bushy trees, which would leave most sets of workgroups without a tree), the same from counts alone (a batch with trees that are large beside the others), or a
+// launch for the roots and for each height.
+constexpr int BACK_ALL = 0, BACK_ROOTS = 1, BACK_HEIGHT = 2, BACK_COUNTED = 3;
 template <int NG, int P>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_back_heights(Fwd f, BackFlow b, int what, int lo0, int rows0)
 {
@@ -580,21 +672,23 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_heights(Fwd f, BackFlow 
     using Smem = BackSmem<NG, P>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     const int tid = threadIdx.x;
-    const bool leave = tid == 0 && (batch_rejected(f) || internal_kernel_skipped(f));
+    const bool leave = tid == 0 && (batch_rejected(f) || (what == BACK_COUNTED ? !back_by_heights(f) || back_rejected(f) : internal_kernel_skipped(f)));
     const int member = (int)blockIdx.x % f.n_cg, slot = (int)blockIdx.x / f.n_cg, n_slots = (int)gridDim.x / f.n_cg;
     if (decided_to_leave(&sm.leave, leave)) return;
     const BackUnit<NG> unit(f, b, sm.stage[tid >> 6], member, tid & 63);
     unsigned epoch = 0, unused = 0;
+    if (what == BACK_COUNTED && !back_lists(sm, f, b, epoch)) return;
     if (what != BACK_HEIGHT) back_roots<NG>(f, b, unit, 0, f.n_trees, slot * (WG_THREADS / 64) + (tid >> 6), n_slots * (WG_THREADS / 64));
     if (what == BACK_ROOTS) return;
+    const bool all = what != BACK_HEIGHT;
     BackWeights<NG, P> w;
     back_load<NG, P>(w, sm, b, member, tid >> 6, tid & 63);
-    if (what == BACK_ALL && !grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
+    if (all && !grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
     __syncthreads();
-    const int n_levels = what == BACK_ALL ? f.ctl->n_levels : 2;
+    const int n_levels = all ? f.ctl->max_height + 1 : 2;
 #pragma unroll 1
     for (int lvl = n_levels - 1; lvl >= 1; --lvl) {         // roots first: a parent is always higher than its children
-        const int lo = what == BACK_ALL ? f.level_off[lvl] : lo0, n_rows = what == BACK_ALL ? f.level_off[lvl + 1] - lo : rows0;
+        const int lo = all ? ld_dev(f.level_off + lvl) : lo0, n_rows = all ? ld_dev(f.level_off + lvl + 1) - lo : rows0;
         const int32_t *list = f.level_nodes + lo;
         const int n_blocks = (n_rows + 15) >> 4, mine = slot < n_blocks ? (n_blocks - slot + n_slots - 1) / n_slots : 0;
         if (mine > 0)
@@ -605,7 +699,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_heights(Fwd f, BackFlow 
                 const int2 pl = b.at.of[l], pr = b.at.of[r];
                 return int4{pl.x, pl.y, pr.x, pr.y};
             }, [&](int blk, int) { return lo + (slot + blk * n_slots) * 16; });
-        if (what == BACK_ALL && !grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
+        if (all && !grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
     }
 }
 
@@ -623,8 +717,9 @@ __global__ __launch_bounds__(WG_THREADS) void k_back_prepare(Fwd f, BackFlow b, 
         return;
     }
     const int lane = threadIdx.x & 63, H = f.H, n_cg = f.n_cg;
-    marks = marks && !internal_kernel_skipped(f);           // (where the heights are walked nobody reads them)
+    marks = marks && !back_flow_skipped(f);                 // (where the heights are walked nobody reads them)
     const size_t first = (size_t)(blockIdx.x - n_sched) * WG_THREADS + threadIdx.x, stride = (size_t)(gridDim.x - n_sched) * WG_THREADS;
+    if (back_by_heights(f)) back_heights_of(f, reinterpret_cast<int *>(smem_raw), first, stride);
     const float ones = __uint_as_float(0xFFFFFFFFu);
     const floatx4 ones4 = floatx4{ones, ones, ones, ones};
     if (marks) {

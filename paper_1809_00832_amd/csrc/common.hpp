@@ -46,7 +46,8 @@ struct alignas(LINE) Ctl {
     int tiles_formed;             // ready scheduler: tiles of ready nodes formed
     int n_roots;                  // nodes without a parent found by the structure pass (one per tree in a valid batch)
     int n_int_seen;               // internal nodes listed (backward pass)
-    int pad0[LINE / 4 - 9];
+    int n_large, n_large_seeds;   // backward pass: large trees (back_by_heights), and their internal nodes over two leaves
+    int pad0[LINE / 4 - 11];
     Line abort;                   // set when a waiting workgroup gives up; everybody leaves
     Line q_head;                  // ready-queue entries consumed into tiles
     Line q_tail;                  // ready-queue entries reserved by producers
@@ -176,7 +177,8 @@ struct Fwd {
     int place;                        // a slot's workgroups lie on one L2 domain (see split_place)
     int flow;                         // data-flow scheduler: who fills the rows of internal nodes with the "not written" pattern: 1 the reset kernel, 2 the leaf kernel
     int gang_parts;                   // ready scheduler, RNTN cell: workgroups per tile and column group (each adds up a part of the slices), 1 or RNTN_PARTS
-    int pick;                         // batch of few large trees, both internal-node kernels launched: 1 this one runs if the trees are narrow, 2 if they are not (see internal_kernel_skipped)
+    int pick;                         // batch of few large trees, both internal-node kernels launched: 1 this one runs if the trees are narrow, 2 if they are not (see internal_kernel_skipped);
+                                      // backward pass: 3 the kernel itself picks (back_by_heights)
 };
 
 // ---- device-scope accesses -------------------------------------------------------------
@@ -359,6 +361,15 @@ __device__ inline bool internal_kernel_skipped(const Fwd &f)
     const bool narrow = (long long)f.ctl->n_seed <= (long long)FLOW_NARROW_SEEDS_PER_TREE * f.n_trees;
     return f.pick == 1 ? !narrow : narrow;
 }
+
+// The same for a backward pass over any other batch (f.pick == 3): a tree that is large beside the others keeps the set of workgroups it is dealt to busy
+// long after all others are done.  The structure pass counts the large trees (the host says from which number of nodes on, treelstm.hip: back_large_nodes)
+// and their internal nodes over two leaves; where the large trees are bushy by the line above, all workgroups walk the heights together.
+__device__ inline bool back_by_heights(const Fwd &f)
+{
+    return f.pick == 3 && (long long)f.ctl->n_large_seeds > (long long)FLOW_NARROW_SEEDS_PER_TREE * f.ctl->n_large;
+}
+__device__ inline bool back_flow_skipped(const Fwd &f) { return f.pick == 3 ? back_by_heights(f) : internal_kernel_skipped(f); }
 
 // Rows per tile when `avail` ready rows meet room for `free_tiles` more tiles: spread the rows
 // over the free room in units of 16, at most TILE_ROWS.

@@ -134,8 +134,8 @@ __global__ void k_reset(Fwd f, int with_levels)
 // One thread per node: checks, parent scatter, leaf list, counters of unfinished children.
 // Leaves are evaluated by a kernel of their own before any internal node, so pending[] counts
 // internal children only, and an internal node whose children are both leaves starts ready.
-// int_list: null, or (backward pass) receives the internal nodes, in no particular order.
-__device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list)
+// int_list: null, or (backward pass) receives the internal nodes, in no particular order.  large: 0, or the nodes that make a tree large (back_by_heights).
+__device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list, int large)
 {
     __shared__ int s_cnt[APPEND_SCRATCH];
     const int n = blockIdx.x * blockDim.x + threadIdx.x;
@@ -153,6 +153,7 @@ __device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list)
         const int lo = f.tree_off[t], hi = f.tree_off[t + 1];
         l = f.left[n];
         r = f.right[n];
+        if (large > 0 && n == lo && hi - lo >= large) atomicAdd(&ctl->n_large, 1);
         if (n < lo || n >= hi) {
             latch_error(ctl, TL_ESTRUCT);
         } else if (l < 0 && r < 0) {
@@ -165,6 +166,7 @@ __device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list)
             const int pend = (f.left[l] >= 0) + (f.left[r] >= 0);
             f.pending[n] = pend;
             is_seed = pend == 0;
+            if (large > 0 && is_seed && hi - lo >= large) atomicAdd(&ctl->n_large_seeds, 1);
         } else {
             latch_error(ctl, TL_ESTRUCT);
         }
@@ -179,9 +181,8 @@ __device__ __forceinline__ void scatter_nodes(const Fwd &f, int32_t *int_list)
         if (inner && slot < f.n_int) int_list[slot] = n;
     }
 }
-// (two kernels: a second argument behind Fwd costs a launch-bound forward 1 us of 20)
-__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f) { scatter_nodes(f, nullptr); }
-__global__ __launch_bounds__(NODE_BLOCK) void k_scatter_list(Fwd f, int32_t *int_list) { scatter_nodes(f, int_list); }
+__global__ __launch_bounds__(NODE_BLOCK) void k_scatter(Fwd f) { scatter_nodes(f, nullptr, 0); }
+__global__ __launch_bounds__(NODE_BLOCK) void k_scatter_list(Fwd f, int32_t *int_list, int large) { scatter_nodes(f, int_list, large); }
 
 // One thread per node: the node nobody points to is its tree's root; there must be exactly one.
 __global__ __launch_bounds__(NODE_BLOCK) void k_roots(Fwd f)
@@ -274,12 +275,9 @@ __global__ __launch_bounds__(NODE_BLOCK) void k_seed_place(Fwd f)
 // exchange on height[p] (zero before the pass): the first leaves 1 + its own height there and
 // finds zero, the second finds the first one's value - the data travels in the word that is
 // exchanged, so a step costs two memory round trips (the parent, the exchange) and no fence.
-// arrive[p] = 2 marks the nodes whose height is final.
-__global__ void k_climb(Fwd f)
+// arrive[p] = 2 marks the nodes whose height is final.  Called by one thread per leaf n; final(height) for every node whose height it settles.
+template <typename Final> __device__ __forceinline__ void climb_from(const Fwd &f, int n, Final final)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (batch_rejected(f) || internal_kernel_skipped(f) || i >= f.n_leaf) return;
-    int n = f.leaf_list[i];
     int hcur = 0;
     for (int guard = 0; guard < f.n_nodes; ++guard) {
         const int p = f.parent[n];
@@ -289,8 +287,15 @@ __global__ void k_climb(Fwd f)
         hcur = other > hcur + 1 ? other : hcur + 1;
         f.height[p] = hcur;
         f.arrive[p] = 2;
+        final(hcur);
         n = p;
     }
+}
+__global__ void k_climb(Fwd f)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (batch_rejected(f) || internal_kernel_skipped(f) || i >= f.n_leaf) return;
+    climb_from(f, f.leaf_list[i], [](int) {});
 }
 
 constexpr int HIST_BINS = 1024;
@@ -673,7 +678,7 @@ __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds,
     int *s_ctl = reinterpret_cast<int *>(lds);
     if (threadIdx.x >= 1 && threadIdx.x < 4) s_ctl[threadIdx.x] = 0;
     // the cuts first: what they read of a batch that is rejected is not used, and the status arrives beside it
-    const bool leave = threadIdx.x == 0 && (batch_rejected(f) || internal_kernel_skipped(f));
+    const bool leave = threadIdx.x == 0 && (batch_rejected(f) || (PLACES ? back_flow_skipped(f) : internal_kernel_skipped(f)));
     int t_lo, t_hi, nb, ne;
     flow_cut(f, slot, f.n_slots, &t_lo, &t_hi, &nb, &ne);
     if (decided_to_leave(&s_ctl[0], leave)) return;

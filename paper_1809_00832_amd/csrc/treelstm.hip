@@ -28,6 +28,21 @@ constexpr int LEVELS_AHEAD = 66;                // offsets of the per-height lis
 constexpr int BW_PERSISTENT_MIN_LEVELS = 64;    // heights from which the backward pass walks them in one persistent kernel rather than in launches per height
 constexpr int FLOW_LARGE_TREE_NODES = 256;      // mean nodes per tree from which a batch of fewer trees than sets of workgroups has the device pick its kernel
 
+// Backward pass: nodes that make a bushy tree too large for one set of workgroups beside the others of its batch (back_by_heights), 0 where no tree can have
+// that many: two and a half times a set's share of the batch, and enough for the heights' barriers.  Measured (a call in us, whole trees on sets / height by height,
+// one random tree of that many leaves among 20 or 255 of 5 to 50):
+//   TreeLSTM  H =  64   20 + 600 197 / -     20 + 770 222 / 206   255 + 1 000 309 / 275   255 + 4 000 1 113 / 342
+//             H = 150   20 + 600 233 / -     20 + 770 258 / 257   255 + 1 000 412 / 402   255 + 4 000 1 029 / 523
+//             H = 512   20 + 770 392 / 385   20 + 1 000 506 / 437 255 + 2 500 1 413 / -   255 + 4 000 1 636 / 1 234
+//   TreeRNN   H =  64   20 + 770 134 / 167   20 + 1 000 162 / 181 (balanced 138 / 130)    255 + 1 500 242 / 207
+//             H = 512   20 + 770 186 / 235   20 + 1 000 240 / 261 (balanced 214 / 196)    255 + 4 000 629 / 520
+// A batch that may hold such a tree pays a launch that mostly leaves at once (256 trees, H = 512: 3 us of a training step of 1 065).
+int back_large_nodes(bool lstm, int n_trees, int n_nodes, int n_slots)
+{
+    const long long large = std::max(lstm ? 1536ll : 1792ll, 5ll * n_nodes / (2ll * n_slots));
+    return n_nodes - (n_trees - 1) >= large ? (int)large : 0;
+}
+
 struct DevBuf {
     void *p = nullptr;
     size_t bytes = 0;
@@ -1256,6 +1271,9 @@ void td_free(tl_td_ctx *ctx)
 int batch_status(const Ctl *ctl, const Fwd &f)
 {
     if (ctl->status != 0) return ctl->status;
+    if (f.pick == 3 && (long long)ctl->n_large_seeds > (long long)FLOW_NARROW_SEEDS_PER_TREE * ctl->n_large &&
+        (ctl->n_roots != f.n_trees || ctl->reached != f.n_int))       // (back_rejected)
+        return TL_ESTRUCT;
     return (f.flow_roots ? ctl->n_leaf_seen != f.n_leaf : ctl->n_roots != f.n_trees) ? TL_ESTRUCT : TL_OK;
 }
 
@@ -1766,11 +1784,14 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const bool launches = ctx->async_backward < 0;
     const int back_slots = back ? ctx->bf_grid / ctx->n_cg : 0;
     const bool back_either = back && !launches && n_trees < back_slots && n_nodes / n_trees >= FLOW_LARGE_TREE_NODES;
+    // ... and so does any other batch that may hold a tree too large for its set (back_by_heights)
+    const int large = back && !launches && !back_either ? back_large_nodes(lstm, n_trees, n_nodes, back_slots) : 0;
     BackFlow bk{};
     if (back) {
         carve_back(ctx, &f, &bk);
         f.n_slots = back_slots;
         f.flow_roots = !launches && !back_either ? 1 : 0;
+        f.pick = large > 0 ? 3 : 0;
         const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
         f.place = ctx->n_cg <= 3 || (ctx->n_cg <= 10 && 4ll * n_trees <= 3ll * f.n_slots) || (ctx->n_cg <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
         bk.g_h = g_h; bk.dg = dg_int; bk.dc = lstm ? f.dh : nullptr;
@@ -1782,8 +1803,8 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const int nb_big = (n_nodes + 1 + NODE_BLOCK - 1) / NODE_BLOCK;
     // structure pass; with heights and per-height lists (as for the host-driven level scheduler) where something walks the heights
     const bool need_levels = !back || launches || back_either;
-    hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, need_levels ? 1 : 0);
-    hipLaunchKernelGGL(k_scatter_list, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list);
+    hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, need_levels || large > 0 ? 1 : 0);
+    hipLaunchKernelGGL(k_scatter_list, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list, large);
     if (need_levels) {
         Fwd fl = f;
         fl.pick = back_either ? 2 : 0;
@@ -1800,7 +1821,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         z.p[2] = d_b_leaf; z.n[2] = lstm ? (size_t)3 * H : 0;
         z.p[3] = d_w_leaf; z.n[3] = lstm ? (size_t)E * 3 * H : 0;
         Fwd fs = f;
-        fs.pick = back_either ? 1 : 0;
+        if (back_either) fs.pick = 1;
         const int n_sched = launches ? 0 : back_slots;
         // (as many workgroups as are resident at once, a wave per node; LDS as in forward_impl)
         const int rows = (n_nodes + 3) / 4 < 8 * ctx->n_cu ? (n_nodes + 3) / 4 : 8 * ctx->n_cu;
@@ -1834,10 +1855,11 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     auto launch_all_heights = [&]() {
         if (back) {
             Fwd g = f;
-            g.pick = back_either ? 1 : 0;
+            if (back_either) g.pick = 1;
             hipLaunchKernelGGL(back_flow(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk);
-            g.pick = 2;
-            if (back_either) hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk, BACK_ALL, 0, 0);
+            if (back_either) g.pick = 2;
+            if (back_either || large > 0)
+                hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk, large > 0 ? BACK_COUNTED : BACK_ALL, 0, 0);
             return;
         }
         if (rntn_one) {

@@ -433,3 +433,109 @@ def test_sums_that_overflow_only_when_scaled(cell, H):
         for n in np.flatnonzero(trees.left < 0):
             top = np.abs(ref[n]).max()
             assert 0 < top < 2.0 ** 127 and np.abs(out[mode]["d_x"][n] - ref[n]).max() <= 1e-4 * top, (mode, n)
+
+
+def one_large_tree(leaves, shape, at, n_small=60, seed=1200):
+    """Small trees around one that is large beside them."""
+    counts, shapes = [3 + 5 * i % 37 for i in range(n_small)], ["random"] * n_small
+    counts.insert(at, leaves)
+    shapes.insert(at, shape)
+    return synth.make_trees(seed, counts, shapes, 50)
+
+
+# bushy (all workgroups walk the heights together) and not, first, last and in between; just below and from the line of 1 536 nodes on (a tree of 768 leaves has 1 535; TreeRNN: 1 792)
+@pytest.mark.parametrize("cell,H", [("lstm", 20), ("lstm", 150), ("lstm", 512), ("rnn", 64), ("rnn", 130), ("rnn", 512)])
+@pytest.mark.parametrize("leaves,shape,at", [(768, "random", 30), (769, "random", 30), (2500, "random", 0), (2500, "balanced", 60), (1500, "chain", 7)])
+def test_a_tree_that_is_large_beside_the_others(cell, H, leaves, shape, at):
+    print("case back skewed", cell, H, leaves, shape, flush=True)
+    params, _ = make(cell, H, 1200 + H, [1], ["random"])
+    if cell == "rnn" and leaves < 1000:
+        leaves += 128
+    trees = one_large_tree(leaves, shape, at)
+    g_h = np.random.default_rng(H).standard_normal((trees.n_nodes, H)).astype(np.float32)
+    out, h, c = backward(params, trees, g_h, (-1, 0, 1, 0))
+    for mode in (0, 1):
+        assert np.array_equal(out[mode]["d_x"], out[-1]["d_x"]), mode
+    ref = oracle.backward(params, trees, h, c, g_h)
+    for k in ref:                                             # sums of at most 3 700 products, fp32, by slices of the nodes: as in the tests above
+        np.testing.assert_allclose(out[0][k], ref[k], rtol=1e-4, atol=1e-4 * max(1.0, float(np.abs(ref[k]).max())), err_msg=k)
+
+
+def test_a_large_tree_in_a_replayed_step():
+    """The same in a graph: what the kernels count for their choice starts from zero in every replay, for a batch of either kind."""
+    H = 64
+    params, _ = make("lstm", H, 1250, [1], ["random"])
+    for shape in ("random", "chain"):
+        print("case back skewed replayed", shape, flush=True)
+        trees = one_large_tree(1000, shape, 11)
+        g = torch.from_numpy(np.random.default_rng(3).standard_normal((trees.n_nodes, H)).astype(np.float32)).cuda()
+        net = binding.TreeNet(params, scheduler="dataflow")
+        try:
+            b = net.load(trees)
+            binding.tl_set_keep_gates(net.ctx, True)
+            binding.tl_set_async_backward(net.ctx, 1)
+
+            def step():
+                net.forward()
+                return binding.tl_backward(net.ctx, b, g, params.embed_dim)
+            want = step()["d_x"].clone()
+            torch.cuda.synchronize()
+            graph, got = replayed(step)
+            for _ in range(3):
+                got["d_x"].fill_(float("nan"))
+                torch.cuda.synchronize()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert torch.equal(got["d_x"], want)
+                assert torch.isfinite(torch.randn(1 << 16, device="cuda").sum())
+            assert binding.tl_status(net.ctx) == 0
+        finally:
+            net.close()
+
+
+@pytest.mark.parametrize("what", ["cycle", "roots", "root of the large tree"])
+@pytest.mark.parametrize("cell", ["lstm", "rnn"])
+@pytest.mark.parametrize("mode", [0, 1, -1])
+def test_malformed_batches_with_a_large_tree(cell, what, mode):
+    """Where the heights are walked, the walk's own preparation finds what the schedule finds elsewhere: nodes that no leaf leads to, a tree of two roots and one of none.
+    The context goes on."""
+    print("case back skewed malformed", cell, what, mode, flush=True)
+    H = 40
+    params, _ = make(cell, H, 1260, [1], ["random"])
+    good = one_large_tree(1000, "random", 20, seed=1261)
+    ranges = [tuple(np.where(a[lo:hi] >= 0, a[lo:hi] - s, -1) for a, s in ((good.left, lo), (good.right, lo), (good.word, 0))) for lo, hi in zip(good.tree_off[:-1], good.tree_off[1:])]
+    word = lambda l: np.where(l < 0, 3, -1)
+    if what == "cycle":                                       # a tree of three nodes beside a ring of two with two leaves
+        l, r = np.array([1, -1, -1, 4, 3, -1, -1]), np.array([2, -1, -1, 5, 6, -1, -1])
+        ranges.insert(40, (l, r, word(l)))
+    else:                                                     # two roots; a ring without one
+        if what == "roots":
+            l, r = np.array([1, -1, -1, 4, -1, -1]), np.array([2, -1, -1, 5, -1, -1])
+            ranges.insert(5, (l, r, word(l)))
+        else:                                                 # the large tree and a small one in one range
+            a, b = ranges[20], ranges[21]
+            n = len(a[0])
+            ranges[20:22] = [tuple(np.concatenate([x, np.where(y >= 0, y + shift, -1)]) for x, y, shift in zip(a, b, (n, n, 0)))]
+        l, r = np.array([1, 0, -1, -1]), np.array([2, 3, -1, -1])
+        ranges.insert(50, (l, r, word(l)))
+    off = np.concatenate([[0], np.cumsum([len(x[0]) for x in ranges])]).astype(np.int32)
+    cat = lambda i, rel: np.concatenate([np.where(x[i] >= 0, x[i] + (o if rel else 0), -1) for x, o in zip(ranges, off)]).astype(np.int32)
+    bad = synth.TreeBatch(off, cat(0, True), cat(1, True), cat(2, False))
+    assert (bad.n_nodes + bad.n_trees) % 2 == 0 and (bad.left < 0).sum() * 2 == bad.n_nodes + bad.n_trees
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        binding.tl_set_keep_gates(net.ctx, True)
+        binding.tl_set_async_backward(net.ctx, mode)
+        for trees, expect in ((good, binding.TL_OK), (bad, binding.TL_ESTRUCT), (good, binding.TL_OK)):
+            b = net.load(trees)
+            net.forward()
+            code = binding.TL_OK
+            try:
+                d_x = binding.tl_backward(net.ctx, b, torch.ones((trees.n_nodes, H), device="cuda"), params.embed_dim)["d_x"]
+            except binding.TLError as e:
+                code = e.code
+            assert code == (expect if mode <= 0 else binding.TL_OK)
+            assert binding.tl_status(net.ctx) == expect
+            assert expect != binding.TL_OK or bool(torch.isfinite(d_x).all())
+    finally:
+        net.close()
