@@ -814,10 +814,19 @@ int ensure_back(tl_ctx *ctx, int n_nodes)
     TL_HIP(hipDeviceSynchronize());
     if (ctx->bf) { TL_HIP(hipFree(ctx->bf)); ctx->bf = nullptr; }
     ctx->bf_nodes = 0;
-    const size_t N = (size_t)(in_back_range(ctx, ctx->cap_nodes) ? ctx->cap_nodes : n_nodes);
-    const BackSizes z = back_sizes(ctx, N);
+    // for the nodes that the context has workspace for, or as many of them as these forms take: a smaller batch that comes first leaves nothing to allocate
+    int N = ctx->cap_nodes;
+    if (!in_back_range(ctx, N)) {
+        int above = N;
+        N = n_nodes;                              // in range
+        while (above - N > 1) {
+            const int mid = N + (above - N) / 2;
+            (in_back_range(ctx, mid) ? N : above) = mid;
+        }
+    }
+    const BackSizes z = back_sizes(ctx, (size_t)N);
     TL_HIP(hipMalloc(&ctx->bf, z.gx + z.gs + 2 * z.sched + z.head + z.trees + z.list + z.place));
-    ctx->bf_nodes = (int)N;
+    ctx->bf_nodes = N;
     return TL_OK;
 }
 void carve_back(const tl_ctx *ctx, Fwd *f, BackFlow *b)

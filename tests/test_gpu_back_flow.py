@@ -539,3 +539,36 @@ def test_malformed_batches_with_a_large_tree(cell, what, mode):
             assert expect != binding.TL_OK or bool(torch.isfinite(d_x).all())
     finally:
         net.close()
+
+
+def test_captured_backward_after_a_smaller_one():
+    """A context that has evaluated more nodes than the tables hold: the first backward pass, of a small batch, allocates for all that they hold, so that a larger
+    batch's can be recorded."""
+    H, E = 512, 16
+    params, huge = make("lstm", H, 1300, [4096] * 52, ["balanced"] * 52, E)
+    assert huge.n_nodes * H * 20 >= 1 << 32
+    net = binding.TreeNet(params, scheduler="dataflow")
+    try:
+        binding.tl_set_keep_gates(net.ctx, True)
+        binding.tl_set_async_backward(net.ctx, 1)
+        net.load(huge)
+        net.forward()
+
+        for n_trees, graphed in ((2, False), (60, True), (60, False)):
+            print("case back captured after a smaller one", n_trees, graphed, flush=True)
+            trees = synth.make_trees(1301, [20] * n_trees, ["random"] * n_trees, 50)
+            b = net.load(trees)
+            g = torch.ones((trees.n_nodes, H), device="cuda")
+            net.forward()
+            torch.cuda.synchronize()
+            if graphed:
+                graph, recorded = replayed(lambda: binding.tl_backward(net.ctx, b, g, E)["d_x"])
+                graph.replay()
+                torch.cuda.synchronize()
+                recorded = recorded.clone()
+            else:
+                got = binding.tl_backward(net.ctx, b, g, E)["d_x"]
+        assert binding.tl_status(net.ctx) == 0
+        assert torch.equal(recorded, got)
+    finally:
+        net.close()
