@@ -119,6 +119,7 @@ struct tl_ctx {
     unsigned char *bf = nullptr;
     int bf_nodes = 0;
     bool bwd_packed = true;           // the matrices of the other forms belong to the current parameters (see still_packed)
+    bool bwd_wanted = false;          // the last backward pass needed them
     bool update_recorded = false;     // a capture has recorded a tl_sgd_update of this context
     Gemm g_bwd_inner1{};              // U^T once more with one column block per group: more workgroups for heights of few rows
     Gemm g_bwd_inner{}, g_bwd_leaf{};
@@ -567,6 +568,15 @@ int bwd_jobs(const tl_ctx *ctx, PackList &pl, int n)
     return n;
 }
 
+// Is a capture under way on this stream?  (The legacy stream refuses the question while another one is captured: yes, as far as anybody relies on the answer.)
+bool capturing(hipStream_t st)
+{
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
+}
+
 // After a parameter update of an fp32 TreeLSTM or TreeRNN context: everything pack_treelstm_f32 / pack_treernn_f32 derive
 // from the parameters, packed over in one launch.
 int repack_f32(tl_ctx *ctx, hipStream_t st)
@@ -579,20 +589,11 @@ int repack_f32(tl_ctx *ctx, hipStream_t st)
     int n = 0;
     if (lstm) pl.job[n++] = repack_job(ctx->g_leaf, ctx->m_w_leaf, ctx->m_b_leaf, ctx->bp_leaf, 3, H, 1, ctx->n_cg, false);
     pl.job[n++] = repack_job(ctx->g_inner, ctx->m_u, ctx->m_b, ctx->bp_inner, ng_cell, H, 2, ctx->n_cg, false);
-    // (fp32 matrices of the backward pass: where its one-kernel forms have their own, packed over when something needs them)
-    if (ctx->bf_p > 0) ctx->bwd_packed = false;
-    else n = bwd_jobs(ctx, pl, n);
+    // (fp32 matrices of the backward pass: where its one-kernel forms have their own, packed over here if the last backward pass needed them, else when one does)
+    ctx->bwd_packed = ctx->bwd_wanted && !capturing(st);
+    if (ctx->bf_p == 0 || ctx->bwd_wanted) n = bwd_jobs(ctx, pl, n);
     pl.n = n;
     return pack_split(ctx, pl, st);
-}
-
-// Is a capture under way on this stream?  (The legacy stream refuses the question while another one is captured: yes, as far as anybody relies on the answer.)
-bool capturing(hipStream_t st)
-{
-    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &capture) == hipSuccess) return capture != hipStreamCaptureStatusNone;
-    (void)hipGetLastError();
-    return true;
 }
 
 // Matrices that an update does not rebuild are packed when a backward pass needs them.  Whether they belong to the current parameters is known on the host
@@ -1755,6 +1756,7 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const bool rntn_rows = rntn && (ctx->rb_steps == 0 || ctx->async_backward < 0 || n_nodes >= (1 << 24) || (size_t)n_nodes * H * 4 >= ((size_t)1 << 32));
     if (rntn_rows && (rc = pack_rntn_wide(ctx, st)) != TL_OK) return rc;
     if (!rntn && !back && (rc = pack_bwd(ctx, st)) != TL_OK) return rc;
+    ctx->bwd_wanted = !rntn && !back;
     if (back && (rc = ensure_back(ctx, n_nodes)) != TL_OK) return rc;
     if (n_nodes > ctx->bw_nodes || (rntn_rows && !ctx->bw_rows)) {
         TL_HIP(hipDeviceSynchronize());
