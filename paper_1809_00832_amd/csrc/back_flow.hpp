@@ -550,7 +550,7 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_flow(Fwd f, BackFlow b)
     using Smem = BackSmem<NG, P>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     const int tid = threadIdx.x;
-    const bool leave = tid == 0 && (batch_rejected(f) || back_flow_skipped(f));      // (a workgroup that gives up latches that)
+    const bool leave = tid == 0 && (batch_rejected(f) || back_by_heights(f));      // (a workgroup that gives up latches that)
     int member, slot;
     split_place(f, &slot, &member);
     member = gang_cg(member, f.n_cg, f.n_cg);     // (neighbouring units from one L2 domain)
@@ -661,10 +661,9 @@ template <typename Smem> __device__ __forceinline__ bool back_lists(Smem &sm, co
     return true;
 }
 
-// The same cell height by height: all workgroups share the blocks of a height.  The whole walk in one launch, a grid barrier per height (a batch of few
-// large bushy trees, which would leave most sets of workgroups without a tree), the same from counts alone (a batch with trees that are large beside the others), or a
+// The same cell height by height: all workgroups share the blocks of a height.  The whole walk in one launch, a grid barrier per height (back_by_heights), or a
 // launch for the roots and for each height.
-constexpr int BACK_ALL = 0, BACK_ROOTS = 1, BACK_HEIGHT = 2, BACK_COUNTED = 3;
+constexpr int BACK_ALL = 0, BACK_ROOTS = 1, BACK_HEIGHT = 2;
 template <int NG, int P>
 __global__ __launch_bounds__(WG_THREADS, 1) void k_back_heights(Fwd f, BackFlow b, int what, int lo0, int rows0)
 {
@@ -672,15 +671,15 @@ __global__ __launch_bounds__(WG_THREADS, 1) void k_back_heights(Fwd f, BackFlow 
     using Smem = BackSmem<NG, P>;
     Smem &sm = *reinterpret_cast<Smem *>(smem_raw);
     const int tid = threadIdx.x;
-    const bool leave = tid == 0 && (batch_rejected(f) || (what == BACK_COUNTED ? !back_by_heights(f) || back_rejected(f) : internal_kernel_skipped(f)));
+    const bool leave = tid == 0 && (batch_rejected(f) || (what == BACK_ALL && (!back_by_heights(f) || back_rejected(f))));
     const int member = (int)blockIdx.x % f.n_cg, slot = (int)blockIdx.x / f.n_cg, n_slots = (int)gridDim.x / f.n_cg;
     if (decided_to_leave(&sm.leave, leave)) return;
     const BackUnit<NG> unit(f, b, sm.stage[tid >> 6], member, tid & 63);
     unsigned epoch = 0, unused = 0;
-    if (what == BACK_COUNTED && !back_lists(sm, f, b, epoch)) return;
+    if (what == BACK_ALL && !back_lists(sm, f, b, epoch)) return;
     if (what != BACK_HEIGHT) back_roots<NG>(f, b, unit, 0, f.n_trees, slot * (WG_THREADS / 64) + (tid >> 6), n_slots * (WG_THREADS / 64));
     if (what == BACK_ROOTS) return;
-    const bool all = what != BACK_HEIGHT;
+    const bool all = what == BACK_ALL;
     BackWeights<NG, P> w;
     back_load<NG, P>(w, sm, b, member, tid >> 6, tid & 63);
     if (all && !grid_barrier(sm, f, epoch, 0u, 0u, &unused)) return;
@@ -717,9 +716,10 @@ __global__ __launch_bounds__(WG_THREADS) void k_back_prepare(Fwd f, BackFlow b, 
         return;
     }
     const int lane = threadIdx.x & 63, H = f.H, n_cg = f.n_cg;
-    marks = marks && !back_flow_skipped(f);                 // (where the heights are walked nobody reads them)
+    const bool by_heights = back_by_heights(f);
+    marks = marks && !by_heights;                           // (where the heights are walked nobody reads them)
     const size_t first = (size_t)(blockIdx.x - n_sched) * WG_THREADS + threadIdx.x, stride = (size_t)(gridDim.x - n_sched) * WG_THREADS;
-    if (back_by_heights(f)) back_heights_of(f, reinterpret_cast<int *>(smem_raw), first, stride);
+    if (by_heights) back_heights_of(f, reinterpret_cast<int *>(smem_raw), first, stride);
     const float ones = __uint_as_float(0xFFFFFFFFu);
     const floatx4 ones4 = floatx4{ones, ones, ones, ones};
     if (marks) {

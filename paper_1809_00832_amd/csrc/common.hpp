@@ -362,14 +362,13 @@ __device__ inline bool internal_kernel_skipped(const Fwd &f)
     return f.pick == 1 ? !narrow : narrow;
 }
 
-// The same for a backward pass over any other batch (f.pick == 3): a tree that is large beside the others keeps the set of workgroups it is dealt to busy
+// The same for the backward pass (f.pick == 3), whatever the number of trees: a tree that is large beside the rest of the batch keeps the set of workgroups it is dealt to busy
 // long after all others are done.  The structure pass counts the large trees (the host says from which number of nodes on, treelstm.hip: back_large_nodes)
 // and their internal nodes over two leaves; where the large trees are bushy by the line above, all workgroups walk the heights together.
 __device__ inline bool back_by_heights(const Fwd &f)
 {
     return f.pick == 3 && (long long)f.ctl->n_large_seeds > (long long)FLOW_NARROW_SEEDS_PER_TREE * f.ctl->n_large;
 }
-__device__ inline bool back_flow_skipped(const Fwd &f) { return f.pick == 3 ? back_by_heights(f) : internal_kernel_skipped(f); }
 
 // Rows per tile when `avail` ready rows meet room for `free_tiles` more tiles: spread the rows
 // over the free room in units of 16, at most TILE_ROWS.

@@ -678,7 +678,7 @@ __device__ inline void flow_schedule(const Fwd &f, int slot, unsigned char *lds,
     int *s_ctl = reinterpret_cast<int *>(lds);
     if (threadIdx.x >= 1 && threadIdx.x < 4) s_ctl[threadIdx.x] = 0;
     // the cuts first: what they read of a batch that is rejected is not used, and the status arrives beside it
-    const bool leave = threadIdx.x == 0 && (batch_rejected(f) || (PLACES ? back_flow_skipped(f) : internal_kernel_skipped(f)));
+    const bool leave = threadIdx.x == 0 && (batch_rejected(f) || (PLACES ? back_by_heights(f) : internal_kernel_skipped(f)));
     int t_lo, t_hi, nb, ne;
     flow_cut(f, slot, f.n_slots, &t_lo, &t_hi, &nb, &ne);
     if (decided_to_leave(&s_ctl[0], leave)) return;

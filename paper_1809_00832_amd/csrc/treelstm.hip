@@ -28,14 +28,14 @@ constexpr int LEVELS_AHEAD = 66;                // offsets of the per-height lis
 constexpr int BW_PERSISTENT_MIN_LEVELS = 64;    // heights from which the backward pass walks them in one persistent kernel rather than in launches per height
 constexpr int FLOW_LARGE_TREE_NODES = 256;      // mean nodes per tree from which a batch of fewer trees than sets of workgroups has the device pick its kernel
 
-// Backward pass: nodes that make a bushy tree too large for one set of workgroups beside the others of its batch (back_by_heights), 0 where no tree can have
-// that many: two and a half times a set's share of the batch, and enough for the heights' barriers.  Measured (a call in us, whole trees on sets / height by height,
-// one random tree of that many leaves among 20 or 255 of 5 to 50):
-//   TreeLSTM  H =  64   20 + 600 197 / -     20 + 770 222 / 206   255 + 1 000 309 / 275   255 + 4 000 1 113 / 342
-//             H = 150   20 + 600 233 / -     20 + 770 258 / 257   255 + 1 000 412 / 402   255 + 4 000 1 029 / 523
-//             H = 512   20 + 770 392 / 385   20 + 1 000 506 / 437 255 + 2 500 1 413 / -   255 + 4 000 1 636 / 1 234
-//   TreeRNN   H =  64   20 + 770 134 / 167   20 + 1 000 162 / 181 (balanced 138 / 130)    255 + 1 500 242 / 207
-//             H = 512   20 + 770 186 / 235   20 + 1 000 240 / 261 (balanced 214 / 196)    255 + 4 000 629 / 520
+// Backward pass: nodes that make a bushy tree too large for one set of workgroups beside the rest of its batch (back_by_heights), 0 where no tree can have
+// that many: two and a half times a set's share of the batch, and enough for the heights' barriers.  Measured (a call in us, whole trees on sets / height by height;
+// random trees of so many leaves, alone or among 20 or 255 of 5 to 50):
+//   TreeLSTM  H =  64   3 x 300 123 / 172   3 x 600 192 / 208     20 + 770 222 / 206     255 + 1 000 309 / 275   255 + 4 000 1 113 / 342
+//             H = 150   3 x 300 168 / 215   12 x 600 285 / 388    20 + 770 258 / 257     255 + 1 000 412 / 402   255 + 4 000 1 029 / 523
+//             H = 512   3 x 600 369 / 411   6 x 1 500 925 / 1 056 20 + 1 000 506 / 437                           255 + 4 000 1 636 / 1 234
+//   TreeRNN   H =  64   3 x 600 117 / 167   20 + 770 134 / 167    20 + 1 000 162 / 181 (balanced 138 / 130)      255 + 1 500 242 / 207
+//             H = 512   3 x 600 170 / 245   20 + 770 186 / 235    20 + 1 000 240 / 261 (balanced 214 / 196)      255 + 4 000 629 / 520
 // A batch that may hold such a tree pays a launch that mostly leaves at once (256 trees, H = 512: 3 us of a training step of 1 065).
 int back_large_nodes(bool lstm, int n_trees, int n_nodes, int n_slots)
 {
@@ -949,7 +949,9 @@ back_heights_kernel back_heights(bool lstm, int p)
 }
 size_t back_lds(bool lstm, int p) { return lstm && p == 4 ? sizeof(BackSmem<5, 4>) : sizeof(BackSmem<1, 1>); }     // (weights in LDS in the largest one only)
 static_assert(sizeof(BackSmem<5, 3>) == sizeof(BackSmem<1, 1>) && sizeof(BackSmem<1, 4>) == sizeof(BackSmem<1, 1>), "one LDS layout for all but the largest");
-// ... its leaves, s k-steps of 32 per wave (3 H <= 1 536), BACK_LEAF_NC column groups of the embedding per workgroup
+// ... its leaves, s k-steps of 32 per wave (3 H <= 1 536), BACK_LEAF_NC column groups of the embedding per workgroup: as many as the registers hold at the largest size, a row is
+// read and split once for all of them.  (One / two / three, a call in us, E = 300, 256 trees: H = 64 145 / 140 / 137, H = 150 247 / 237 / 233, H = 256 336 / 319 / 321, H = 512
+// 827 / 723 / 712; what E leaves unused costs little: E = 16 119 / 120 / 119, 203 / 205 / 203, 267 / 266 / 268, 628 / 628 / 634.)
 constexpr int BACK_LEAF_NC = 3;
 const int BACK_LEAF_STEPS[] = {1, 2, 3, 4, 6, 8, 10, 12};
 typedef void (*back_leaf_kernel)(Fwd, const float *, int, const void *, const float *, const float *);
@@ -1790,19 +1792,19 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         f.keep0 = ctx->gates + HU;
         f.keep1 = f.keep0 + (size_t)ctx->gates_cap * H;
     }
-    // Whole trees on sets of workgroups (k_back_flow); a batch of few large trees leaves the choice between that and height by height on
-    // all of them to the device, as the forward does (internal_kernel_skipped); launches per height on request.
+    // Whole trees on sets of workgroups (k_back_flow); a batch that may hold a tree too large for its set leaves the choice between that and
+    // height by height on all of them to the device (back_by_heights); launches per height on request.
     const bool launches = ctx->async_backward < 0;
     const int back_slots = back ? ctx->bf_grid / ctx->n_cg : 0;
-    const bool back_either = back && !launches && n_trees < back_slots && n_nodes / n_trees >= FLOW_LARGE_TREE_NODES;
-    // ... and so does any other batch that may hold a tree too large for its set (back_by_heights)
-    const int large = back && !launches && !back_either ? back_large_nodes(lstm, n_trees, n_nodes, back_slots) : 0;
+    const int large = back && !launches ? back_large_nodes(lstm, n_trees, n_nodes, back_slots) : 0;
     BackFlow bk{};
     if (back) {
         carve_back(ctx, &f, &bk);
         f.n_slots = back_slots;
-        f.flow_roots = !launches && !back_either ? 1 : 0;
+        f.flow_roots = launches ? 0 : 1;
         f.pick = large > 0 ? 3 : 0;
+        // (the forward's line; a call in us, members of a set spread over the L2 domains / inside one: TreeRNN d = 48, 64 trees 62.0 / 57.7, d = 96, 16 chains 491 / 473, d = 128,
+        // 256 trees 96.3 / 101.7, d = 512, 64 116.7 / 124.6; TreeLSTM H = 48, 12 74.5 / 72.3, H = 96, 4 chains 697 / 673, H = 192, 64 trees 125.1 / 131.0, H = 512 263 / 283)
         const bool large_trees = (long long)n_nodes >= 128ll * n_trees;
         f.place = ctx->n_cg <= 3 || (ctx->n_cg <= 10 && 4ll * n_trees <= 3ll * f.n_slots) || (ctx->n_cg <= 16 && large_trees && 2ll * n_trees <= 3ll * f.n_slots);
         bk.g_h = g_h; bk.dg = dg_int; bk.dc = lstm ? f.dh : nullptr;
@@ -1813,17 +1815,15 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const int nb_nodes = (n_nodes + 1 + 255) / 256;
     const int nb_big = (n_nodes + 1 + NODE_BLOCK - 1) / NODE_BLOCK;
     // structure pass; with heights and per-height lists (as for the host-driven level scheduler) where something walks the heights
-    const bool need_levels = !back || launches || back_either;
+    const bool need_levels = !back || launches;
     hipLaunchKernelGGL(k_reset, dim3(256), dim3(256), 0, st, f, need_levels || large > 0 ? 1 : 0);
     hipLaunchKernelGGL(k_scatter_list, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f, bk.int_list, large);
     if (need_levels) {
-        Fwd fl = f;
-        fl.pick = back_either ? 2 : 0;
         hipLaunchKernelGGL(k_roots, dim3(nb_big), dim3(NODE_BLOCK), 0, st, f);
-        hipLaunchKernelGGL(k_climb, dim3((n_leaf + 255) / 256), dim3(256), 0, st, fl);
-        hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, fl);
-        hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, fl);
-        hipLaunchKernelGGL(k_fill_places, dim3(nb_nodes), dim3(256), 0, st, fl, bk.at.of);
+        hipLaunchKernelGGL(k_climb, dim3((n_leaf + 255) / 256), dim3(256), 0, st, f);
+        hipLaunchKernelGGL(k_level_hist, dim3(nb_nodes), dim3(256), 0, st, f);
+        hipLaunchKernelGGL(k_scan_levels, dim3(1), dim3(1024), 0, st, f);
+        hipLaunchKernelGGL(k_fill_places, dim3(nb_nodes), dim3(256), 0, st, f, bk.at.of);
     }
     if (back) {
         ClearList z{};
@@ -1831,14 +1831,12 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         z.p[1] = d_u;      z.n[1] = (size_t)2 * H * ng_cell * H;
         z.p[2] = d_b_leaf; z.n[2] = lstm ? (size_t)3 * H : 0;
         z.p[3] = d_w_leaf; z.n[3] = lstm ? (size_t)E * 3 * H : 0;
-        Fwd fs = f;
-        if (back_either) fs.pick = 1;
         const int n_sched = launches ? 0 : back_slots;
         // (as many workgroups as are resident at once, a wave per node; LDS as in forward_impl)
         const int rows = (n_nodes + 3) / 4 < 8 * ctx->n_cu ? (n_nodes + 3) / 4 : 8 * ctx->n_cu;
         const size_t small = 16 * 1024;
         const size_t lds = n_sched == 0 ? 0 : sched_lds_bytes(4 * (size_t)(n_nodes / n_sched) + 256) <= small ? small : SCHED_LDS_BYTES;
-        hipLaunchKernelGGL(k_back_prepare, dim3(n_sched + rows), dim3(WG_THREADS), lds, st, fs, bk, z, ng_cell, n_sched > 0 ? 1 : 0, n_sched, (int)lds);
+        hipLaunchKernelGGL(k_back_prepare, dim3(n_sched + rows), dim3(WG_THREADS), lds, st, f, bk, z, ng_cell, n_sched > 0 ? 1 : 0, n_sched, (int)lds);
     } else {
         // dh starts as the upstream gradient of every node, dc as zero; d_x rows of internal nodes stay zero
         ZeroList z{};
@@ -1865,12 +1863,9 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     const bool heights_on_device = ctx->async_backward > 0 && (persistent_ok || back);
     auto launch_all_heights = [&]() {
         if (back) {
-            Fwd g = f;
-            if (back_either) g.pick = 1;
-            hipLaunchKernelGGL(back_flow(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk);
-            if (back_either) g.pick = 2;
-            if (back_either || large > 0)
-                hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, g, bk, large > 0 ? BACK_COUNTED : BACK_ALL, 0, 0);
+            hipLaunchKernelGGL(back_flow(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk);
+            if (large > 0)
+                hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk, BACK_ALL, 0, 0);
             return;
         }
         if (rntn_one) {
