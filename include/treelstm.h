@@ -283,7 +283,13 @@ int tl_last_stats(tl_ctx *ctx, int *n_levels, int *n_tiles, int *n_workgroups);
  *             tensor V, [d x 2d x 2d]; d_b_leaf unused.)
  *   d_x       [n_nodes x E] fp32 out: row n = dL/d(embedding row used by leaf n);
  *             rows of internal nodes are zero (the caller scatter-adds by word)    DEVICE
- * fp32 arithmetic; the TreeLSTM gate activations are recomputed from h / c unless the forward
+ * fp32 accumulation throughout.  Operands: fp32 where the gates are recomputed and where H > 512.  From kept activations and for TreeRNN at H <= 512, in every mode of
+ * tl_set_async_backward, and for RNTN at d <= 96 the operand gradients take them as two fp16 terms with powers of two of their own: a value to 2^-23 of itself, from 2^15 below
+ * the largest that shares its power on to 2^-38 of that one, a product to 2^-21.  One power is shared by a column of the matrix, and by 16 units of a row of gate gradients (groups further apart than
+ * that are summed apart), by a quarter of a row for the leaves' d_x; sums that are not finite are taken again in fp32 (RNTN: NaN sums).  Weight
+ * gradients of larger batches or matrices take fp32 values as three bf16 terms, six of nine products.  Errors against 64 bits are those of fp32 instructions on ordinary batches
+ * (d_x 2e-7, d_u 6e-7 of their norm at H = 512, 256 trees).
+ * The TreeLSTM gate activations are recomputed from h / c unless the forward
  * kept them (tl_set_keep_gates); TreeRNN and RNTN need nothing but h.  RNTN with d <= 96 walks all heights in one
  * persistent kernel; with d > 96, in batches of 2^24 nodes or 4 GiB of h and more, and under
  * tl_set_async_backward(ctx, -1) it takes launches per height and a row of d * 2d + d values per internal node
@@ -292,7 +298,8 @@ int tl_last_stats(tl_ctx *ctx, int *n_levels, int *n_tiles, int *n_workgroups);
  * structure status: TL_OK, TL_ESTRUCT, ... (where the heights are walked by launches, one pair per height,
  * it needs their number and sizes first; where one persistent kernel walks them, it has enqueued all its
  * work by then and the device is not held up).  With tl_set_async_backward(ctx, 1) it does not wait (RNTN: it does).
- * The first call for a larger batch than any before (RNTN: or the first that needs those rows) allocates workspace
+ * The first call for a larger batch than any before (RNTN: or the first that needs those rows) allocates workspace: 7H floats per node, and
+ * from kept activations and for TreeRNN at H <= 512 what the data-flow kernels gather, 5H (TreeRNN: H) 4-byte words and 0.6 KB per internal node
  * (TL_ENOMEM if the RNTN rows would take more than 64 GiB).  TL_BF16_IN: TL_EINVAL.
  */
 int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, const int32_t *left,
@@ -335,8 +342,9 @@ int tl_get_params(tl_ctx *ctx, float *u, float *b, float *w_leaf, float *b_leaf,
  * activations, tanh(c) and its children's c (8H floats per node, in a workspace the context owns and grows like its others), and a tl_backward whose h argument and
  * n_nodes are those of that forward takes them from there instead of recomputing the forward
  * contraction.  The caller must not change h, c or the batch between the two calls.  Results of
- * tl_forward are unchanged bit for bit; those of tl_backward agree with the recomputing path to
- * rounding (the same activations, computed once instead of twice).  Other cells / precisions:
+ * tl_forward are unchanged bit for bit.  Those of tl_backward agree with the recomputing path to rounding where H > 512 (the same activations, computed once
+ * instead of twice); with H <= 512 its contractions take their operands as two fp16 terms (see tl_backward): the same relative to the largest values of a row and
+ * of its groups of 16 units, not element by element.  A caller that wants fp32 operands leaves it off.  Other cells / precisions:
  * accepted, no effect.  Off by default.
  */
 int tl_set_keep_gates(tl_ctx *ctx, int on);

@@ -1,7 +1,8 @@
 // Backward pass of the TreeLSTM forward (Section 4.2.2, recursive backpropagation): the gradient
 // of a node's cell is applied to the node, then to its children, with the forward values of each
-// node found by node index in the h / c rows.  Heights are walked from the roots down (a parent
-// is always higher than its children), one pair of launches per height:
+// node found by node index in the h / c rows.  TreeLSTM from kept activations and TreeRNN at H <= 512 have a form of their own (back_flow.hpp), RNTN at d <= 96 another
+// (k_backward_rntn below); here are the weight gradients of all, and what the rest takes: heights walked from the roots down (a parent
+// is always higher than its children), one pair of launches per height, or all of them in one kernel (k_backward_heights):
 //   1. gate gradients: the forward contraction G = [h_l ; h_r] U + b is recomputed with the
 //      streaming cell, and its epilogue turns (dh, dc, c, c_l, c_r, gates) into the gradient of
 //      the five gate pre-activations (a row of 5H values per node, kept by list position) and
