@@ -258,7 +258,7 @@ __device__ inline void split_run(SplitSmem &sm, const Fwd &f, const int4 *__rest
 #pragma unroll
                     for (int g = 0; g < NG; ++g) gate[g] += sm.sum_of[(g * HU + (lane & 15)) * 2 + 1];
                 }
-                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_gates(f, e.x, hu));
+                lstm_inner_out(gate[0], gate[1], gate[2], gate[3], gate[4], cl, cr, &cc, &hh, kept_planes(f, e.x, hu));
             }
             const unsigned word = split_word(hh * SPLIT_H_SCALE, hu);
             if ((hu & ~1) < H) buf_st_f<true>(rs_x, (unsigned)e.x * hx_row_b + split_word_off(hu), __uint_as_float(word));

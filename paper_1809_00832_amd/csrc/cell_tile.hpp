@@ -90,8 +90,8 @@ __device__ inline float tanh_f(float x)
 //   k1 = { c_l f_l (1 - f_l), c_r f_r (1 - f_r), f_l, f_r }                         of f_l, f_r dct k1[0], dct k1[1]; the children's dc are dct k1[2], dct k1[3]
 // (k1 of internal nodes only).  Two stores here and two loads there in the place of five and nine.
 struct Keep {
-    floatx4 *k0 = nullptr, *k1 = nullptr;       // the two planes, the same in all lanes (null: nothing is kept) ...
-    long long at = 0;                           // ... and this lane's place in them
+    floatx4 *k0 = nullptr, *k1 = nullptr;       // the two planes (null: nothing is kept) ...
+    long long at = 0;                           // ... and this lane's place behind these pointers
 };
 __device__ inline void keep_leaf(floatx4 *k0, float i, float og, float u, float t)
 {
@@ -119,10 +119,16 @@ __device__ inline void lstm_inner_out(float gi, float gfl, float gfr, float go, 
     *c = cc;
     *h = og * tanh_f(cc);
 }
-// Where a node's kept values are for hidden unit hu; nowhere when they are not kept.
-__device__ inline Keep kept_gates(const Fwd &f, int node, int hu)
+// Where a node's kept values are for hidden unit hu; nowhere when they are not kept.  As planes and a place in them for the split cell (see lstm_inner_out), as
+// a lane's own pointers for the others (57 ragged trees, H = 301, ready scheduler, nothing kept, kernel: 157.3 us with planes, 155.2).
+__device__ inline Keep kept_planes(const Fwd &f, int node, int hu)
 {
     return Keep{f.keep0, f.keep1, (long long)node * f.H + hu};
+}
+__device__ inline Keep kept_gates(const Fwd &f, int node, int hu)
+{
+    const size_t at = (size_t)node * f.H + hu;
+    return f.keep0 ? Keep{f.keep0 + at, f.keep1 + at, 0} : Keep();
 }
 
 // Fills node/src0/src1 of one row.  Rows without a node are marked unused.  Caller synchronises.
