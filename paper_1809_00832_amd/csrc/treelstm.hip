@@ -36,6 +36,7 @@ constexpr int FLOW_LARGE_TREE_NODES = 256;      // mean nodes per tree from whic
 //             H = 512   3 x 600 369 / 411   6 x 1 500 925 / 1 056 20 + 1 000 506 / 437                           255 + 4 000 1 636 / 1 234
 //   TreeRNN   H =  64   3 x 600 117 / 167   20 + 770 134 / 167    20 + 1 000 162 / 181 (balanced 138 / 130)      255 + 1 500 242 / 207
 //             H = 512   3 x 600 170 / 245   20 + 770 186 / 235    20 + 1 000 240 / 261 (balanced 214 / 196)      255 + 4 000 629 / 520
+// (Complete trees just below the line would be faster by heights: TreeLSTM H = 512, one of 600 leaves 259 / 212.)
 // A batch that may hold such a tree pays a launch that mostly leaves at once (256 trees, H = 512: 3 us of a training step of 1 065).
 int back_large_nodes(bool lstm, int n_trees, int n_nodes, int n_slots)
 {
@@ -1832,8 +1833,10 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         z.p[2] = d_b_leaf; z.n[2] = lstm ? (size_t)3 * H : 0;
         z.p[3] = d_w_leaf; z.n[3] = lstm ? (size_t)E * 3 * H : 0;
         const int n_sched = launches ? 0 : back_slots;
-        // (as many workgroups as are resident at once, a wave per node; LDS as in forward_impl)
-        const int rows = (n_nodes + 3) / 4 < 8 * ctx->n_cu ? (n_nodes + 3) / 4 : 8 * ctx->n_cu;
+        // A wave per node, or four values to be cleared a thread, at most as many workgroups as are resident at once (by nodes alone, one tree of five leaves at H = 512 has its 3
+        // workgroups clear 11 MB: 113 us, and 11 for four trees); LDS as in forward_impl
+        const size_t cleared = (z.n[0] + z.n[1] + z.n[2] + z.n[3] + 4 * WG_THREADS - 1) / (4 * WG_THREADS);
+        const int rows = (int)std::min(std::max((size_t)(n_nodes + 3) / 4, cleared), (size_t)8 * ctx->n_cu);
         const size_t small = 16 * 1024;
         const size_t lds = n_sched == 0 ? 0 : sched_lds_bytes(4 * (size_t)(n_nodes / n_sched) + 256) <= small ? small : SCHED_LDS_BYTES;
         hipLaunchKernelGGL(k_back_prepare, dim3(n_sched + rows), dim3(WG_THREADS), lds, st, f, bk, z, ng_cell, n_sched > 0 ? 1 : 0, n_sched, (int)lds);

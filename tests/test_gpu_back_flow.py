@@ -572,3 +572,32 @@ def test_captured_backward_after_a_smaller_one():
         assert torch.equal(recorded, got)
     finally:
         net.close()
+
+
+@pytest.mark.parametrize("cell", ["lstm", "rnn"])
+def test_a_single_small_tree_is_not_slower_than_four(cell):
+    """What a backward pass clears and packs does not depend on the number of nodes, so a batch of a few of them must not get a few workgroups for it."""
+    H = 512
+    us = []
+    for counts in ([5], [5, 34, 17, 46]):
+        params, trees = make(cell, H, 1310, counts, ["random"] * len(counts), 100)
+        print("case back single small tree", cell, counts, flush=True)
+        net = binding.TreeNet(params, scheduler="dataflow")
+        try:
+            b = net.load(trees)
+            binding.tl_set_keep_gates(net.ctx, True)
+            net.forward()
+            g = torch.ones((trees.n_nodes, H), device="cuda")
+            times = []
+            for _ in range(30):
+                begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+                begin.record()
+                binding.tl_backward(net.ctx, b, g, params.embed_dim)
+                end.record()
+                torch.cuda.synchronize()
+                times.append(begin.elapsed_time(end) * 1e3)
+            us.append(sorted(times)[10])
+        finally:
+            net.close()
+    print(us, flush=True)
+    assert us[0] < 1.1 * us[1], us
