@@ -359,7 +359,7 @@ int tl_set_keep_gates(tl_ctx *ctx, int on);
  * not finite taken again in fp32).
  * on == 0, the default: tl_backward returns the structure pass's status itself, as described there.  With H <= 512 (and
  * gates kept, or a TreeRNN) the call enqueues all its work and then waits only for the copy of that status, which sits in front of the
- * persistent kernel (H = 512, 256 trees: 0.72 ms per call; 64 trees of 1 024 heights: 3.9 ms).  Otherwise it waits for the number of heights
+ * persistent kernel (with 1 536 nodes and more it waits while that kernel runs, learns which form the batch takes, and enqueues the rest) (H = 512, 256 trees: 0.72 ms per call; 64 trees of 1 024 heights: 3.9 ms).  Otherwise it waits for the number of heights
  * and takes the persistent kernel for more than 64 of them, launches per height up to there.
  * on < 0: always launches per height.  Like the persistent schedulers of tl_forward, the persistent kernels need all their
  * workgroups resident: a caller that cannot keep the device to itself takes on < 0 (a wait that gives up is

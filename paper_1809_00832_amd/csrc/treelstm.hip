@@ -37,7 +37,7 @@ constexpr int FLOW_LARGE_TREE_NODES = 256;      // mean nodes per tree from whic
 //   TreeRNN   H =  64   3 x 600 117 / 167   20 + 770 134 / 167    20 + 1 000 162 / 181 (balanced 138 / 130)      255 + 1 500 242 / 207
 //             H = 512   3 x 600 170 / 245   20 + 770 186 / 235    20 + 1 000 240 / 261 (balanced 214 / 196)      255 + 4 000 629 / 520
 // (Complete trees just below the line would be faster by heights: TreeLSTM H = 512, one of 600 leaves 259 / 212.)
-// A batch that may hold such a tree pays a launch that mostly leaves at once (256 trees, H = 512: 3 us of a training step of 1 065).
+// A batch that may hold such a tree pays, where the call does not wait, a launch that mostly leaves at once (4 us).
 int back_large_nodes(bool lstm, int n_trees, int n_nodes, int n_slots)
 {
     const long long large = std::max(lstm ? 1536ll : 1792ll, 5ll * n_nodes / (2ll * n_slots));
@@ -1278,15 +1278,16 @@ void td_free(tl_td_ctx *ctx)
     delete ctx;
 }
 
+// back_by_heights, of a copy of the control block
+bool walked_by_heights(const Ctl *ctl, const Fwd &f) { return f.pick == 3 && (long long)ctl->n_large_seeds > (long long)FLOW_NARROW_SEEDS_PER_TREE * ctl->n_large; }
+
 // What a copy of the control block says about the batch of `f`, beyond the status that a kernel latched.  Where nobody counts the roots beforehand
 // (flow_roots) every kernel behind the structure pass leaves a batch whose leaves are not as many as N and B say (batch_rejected), the one that looks for the
 // roots among them; elsewhere a tree without a root shows as a root count below the number of trees.
 int batch_status(const Ctl *ctl, const Fwd &f)
 {
     if (ctl->status != 0) return ctl->status;
-    if (f.pick == 3 && (long long)ctl->n_large_seeds > (long long)FLOW_NARROW_SEEDS_PER_TREE * ctl->n_large &&
-        (ctl->n_roots != f.n_trees || ctl->reached != f.n_int))       // (back_rejected)
-        return TL_ESTRUCT;
+    if (walked_by_heights(ctl, f) && (ctl->n_roots != f.n_trees || ctl->reached != f.n_int)) return TL_ESTRUCT;       // (back_rejected)
     return (f.flow_roots ? ctl->n_leaf_seen != f.n_leaf : ctl->n_roots != f.n_trees) ? TL_ESTRUCT : TL_OK;
 }
 
@@ -1864,11 +1865,13 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
     // pass's status in every mode
     const bool rntn_one = rntn && !rntn_rows && n_int > 0;
     const bool heights_on_device = ctx->async_backward > 0 && (persistent_ok || back);
+    auto launch_heights = [&]() {
+        hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk, BACK_ALL, 0, 0);
+    };
     auto launch_all_heights = [&]() {
         if (back) {
             hipLaunchKernelGGL(back_flow(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk);
-            if (large > 0)
-                hipLaunchKernelGGL(back_heights(lstm, ctx->bf_p), dim3(ctx->bf_grid), dim3(WG_THREADS), back_lds(lstm, ctx->bf_p), st, f, bk, BACK_ALL, 0, 0);
+            if (large > 0 && heights_on_device) launch_heights();
             return;
         }
         if (rntn_one) {
@@ -1905,6 +1908,14 @@ int tl_backward(tl_ctx *ctx, int n_trees, int n_nodes, const int32_t *tree_off, 
         TL_HIP(hipEventRecord(ctx->ev_ctl, st));
         status_pending = true;
         launch_all_heights();
+        if (large > 0) {
+            // which of the two forms it is comes with the status, while k_back_flow runs: no launch that leaves at once (4 us; where the call does not wait it has to be there)
+            TL_HIP(hipGetLastError());
+            TL_HIP(hipEventSynchronize(ctx->ev_ctl));
+            status_pending = false;
+            if ((rc = batch_status(ctx->host_ctl, f)) != TL_OK) return rc;
+            if (walked_by_heights(ctx->host_ctl, f)) launch_heights();
+        }
     } else {
         if ((rc = read_ctl(ctx, levels_ahead)) != TL_OK) return rc;
         if (ctx->host_ctl->status != 0) return ctx->host_ctl->status;
