@@ -25,7 +25,7 @@
 // gate; what lies beyond the last pair (or, for an odd number of workgroups, in its second half) is read beyond the end of the table, as zeros.
 //
 // Measured (profiler, all heights; before: gate gradients and operand gradients with fp32 instructions, two grid barriers per height): 256 parse trees at
-// H = 512 658 + 23 (leaves' gate gradients) -> 315 us, 25 at H = 150 99 + 5 -> 48 us.  A block at H = 512 is 11 900 clocks of a wave: 4 800 products (20
+// H = 512 658 + 23 (leaves' gate gradients) -> 305 us, 25 at H = 150 99 + 5 -> 47 us.  A block at H = 512 is 11 900 clocks of a wave: 4 800 products (20
 // k-steps of six instructions of 16 clocks, eight multiplications by the pieces' powers of two, two loads), 3 500 the children's gate gradients,
 // 2 400 the start of the next block and its rows, 650 the exchange.  Bound by one wave per SIMD doing these one after the other: the weights leave
 // registers for no second one.
@@ -363,8 +363,9 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
     };
     typedef std::integral_constant<int, COH> first_policy;
     typedef std::integral_constant<int, 16> past_caches;
-    // Pieces further below their quarter's largest than FAR bits: brought there they would lose bits of their own, or all of them.  Rare: their rows are asked
-    // for again and summed band by band.  (Block of m nodes at position start; top: the largest of this lane's row's quarter.)
+    // Pieces further below their quarter's largest than FAR bits: brought there they would lose bits of their own, or all of them.  Rare: their rows and the weights are asked
+    // for again and summed band by band, in a loop that is not unrolled (with the weights where the products have them it needs registers that the block's own code then lacks: H = 48,
+    // 166 trees 48.2 -> 51.2 us).  (Block of m nodes at position start; top: the largest of this lane's row's quarter.)
     auto far_bands = [&](int start, int m, unsigned top, floatx4 *own) __attribute__((always_inline)) {
         const unsigned off = (unsigned)((lane >> 4) * m + min(lane & 15, m - 1)) * 16u;
         unsigned limit = top < 255u ? top : 0u;         // a band begins below limit - FAR (none in a row with an infinity, a NaN, or whose wait was given up)
@@ -382,7 +383,7 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
             next = max(next, (unsigned)__shfl_xor((int)next, 32));
             if (__ballot(next != 0u) == 0ull) break;
             floatx4 acc[2] = {};
-#pragma unroll
+#pragma unroll 1
             for (int s = 0; s < S; ++s) {
                 const int pair = wave * P + s / NG, line = min(pair, b.n_pairs - 1) * NG + s % NG;
                 const unsigned e = piece(s / NG), base = (unsigned)start * unit.gx_row_b + (unsigned)(line * 128 * m);
@@ -390,15 +391,13 @@ __device__ __forceinline__ void back_run(BackSmem<NG, P> &sm, const Fwd &f, cons
                 const _Float16 by = __builtin_bit_cast(_Float16, (unsigned short)(band ? (FAR + 1 + e - next) << 10 : 0u));
                 const halfx8 hi = __builtin_bit_cast(halfx8, __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)(none ? NOWHERE : off), (int)base, 16)) * by,
                              lo = __builtin_bit_cast(halfx8, __builtin_amdgcn_raw_buffer_load_b128(unit.rs_gx, (int)(none ? NOWHERE : off), (int)(base + 64u * (unsigned)m), 16)) * by;
+                const halfx8 *wt = reinterpret_cast<const halfx8 *>(b.wp) + ((size_t)unit.cg * 4 * S + (size_t)wave * S + s) * 4 * 64 + lane;
 #pragma unroll
                 for (int d = 0; d < 2; ++d) {
-                    halfx8 wt[2];
-#pragma unroll
-                    for (int t = 0; t < 2; ++t) wt[t] = G::in_lds(s) ? sm.w[(((wave * G::IN_LDS + G::lds(s)) * 2 + d) * 2 + t) * 64 + lane] : w.t[G::reg(s)][d][t];
-                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[0], acc[d], 0, 0, 0);
-                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[1], acc[d], 0, 0, 0);
-                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, wt[0], acc[d], 0, 0, 0);
-                    __builtin_amdgcn_sched_barrier(0);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[2 * d * 64], acc[d], 0, 0, 0);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(hi, wt[(2 * d + 1) * 64], acc[d], 0, 0, 0);
+                    acc[d] = __builtin_amdgcn_mfma_f32_16x16x32_f16(lo, wt[2 * d * 64], acc[d], 0, 0, 0);
+                    if constexpr (S > 16) __builtin_amdgcn_sched_barrier(0);        // (no registers for more than one side's weights)
                 }
             }
             if (lane < 16) sm.row_scale[wave][lane] = __uint_as_float((max(next, 15u) - 14u) << 23);
