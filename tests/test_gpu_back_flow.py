@@ -389,7 +389,7 @@ def test_pieces_far_apart(cell, H):
 @pytest.mark.parametrize("H", [40, 150, 512])
 @pytest.mark.parametrize("where", ["u", "w_leaf"])
 def test_infinite_weights(where, H):
-    """A column with an infinity has no two terms: its sums are taken in fp32 and are finite, infinite or NaN where the checker's are.  (The infinity is an output gate's, whose
+    """A column with an infinity has no two terms: its sums are taken in fp32 and are finite, infinite or NaN where the oracle's are.  (The infinity is an output gate's, whose
     sigmoid is 0 or 1, so that the states stay finite.)"""
     print("case back infinite weights", where, H, flush=True)
     params, trees = make("lstm", H, 1160, [20, 31, 2, 1], ["random"] * 4)
